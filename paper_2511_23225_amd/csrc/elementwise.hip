@@ -63,9 +63,11 @@ __device__ __forceinline__ float inject_one(float dy, float a, float inv_tau, fl
         for (int e = 1; e < 8; ++e)
             w = e < p ? w * u : w;
     }
-    const float t = coef * w;
-    // sign(a) = 0 for a = 0; a NaN activation poisons the gradient, as it should
-    return dy + (a > 0.0f ? t : (a < 0.0f ? -t : (a == 0.0f ? 0.0f : a)));
+    // sign(a) = 0 for a = 0; a NaN activation poisons the gradient, as it should.  Selects only: written
+    // as nested conditionals this became two branches per element (1500 in a cast kernel)
+    const float t = bits_to_f32(f32_to_bits(coef * w) ^ (f32_to_bits(a) & 0x80000000u));
+    const float v = a == 0.0f ? 0.0f : t;
+    return dy + (P == 4 || a == a ? v : a);  // p = 4: a NaN is in t already
 }
 
 // The injection as a prologue of the gradient's amax and cast passes: the gradient is formed
@@ -936,49 +938,6 @@ hipError_t launch_quantize_f8_from_partials(const void *x_bf16, int64_t rows, in
                                                    nullptr, s, amax_partials, n_partials, amax_out);
 }
 
-// amax and cast of dy' = bf16(dy + coef * sign(a) * (|a| * inv_tau)^(p-1)) without storing dy':
-// the amax launch leaves workgroup maxima, the cast launch reduces them (rows, cols multiples of 16).
-hipError_t launch_amax_quantize_inject(const void *dy_bf16, const void *a_bf16, int64_t rows, int64_t cols,
-                                       float inv_tau, float coef, int p, bool e5m2, uint32_t *partials,
-                                       float *amax_out, uint8_t *q, uint8_t *qT, float *scale_out,
-                                       float *scale_inv_out, hipStream_t s)
-{
-    const InjectArgs inj{(const uint16_t *)a_bf16, inv_tau, coef, p};
-    const int64_t n_vec = rows * cols / 8;
-    int64_t blocks = n_vec / (kAmaxUnroll * kAmaxThreads);
-    if (blocks < 1)
-        blocks = 1;
-    if (blocks > amax_cus())
-        blocks = amax_cus();
-    if (p == 4)
-        hipLaunchKernelGGL(amax_inject_kernel<4>, dim3((unsigned)blocks), dim3(kAmaxThreads), 0, s,
-                           (const uint4 *)dy_bf16, inj, n_vec, (n_vec + blocks - 1) / blocks, partials);
-    else
-        hipLaunchKernelGGL(amax_inject_kernel<0>, dim3((unsigned)blocks), dim3(kAmaxThreads), 0, s,
-                           (const uint4 *)dy_bf16, inj, n_vec, (n_vec + blocks - 1) / blocks, partials);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess)
-        return e;
-    const int64_t tiles_x = (cols + kQuantBigTile - 1) / kQuantBigTile, tiles_y = (rows + kQuantBigTile - 1) / kQuantBigTile;
-    const dim3 grid((unsigned)(tiles_x * tiles_y)), block(kQuantThreads);
-    auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, grid, block, 0, s, (const uint16_t *)dy_bf16, inj, rows, cols, tiles_x, q, qT,
-                           scale_out, scale_inv_out, (const uint32_t *)partials, (int)blocks, amax_out);
-    };
-    if (e5m2) {
-        if (p == 4)
-            launch(quantize_inject_16x16_kernel<true, 4>);
-        else
-            launch(quantize_inject_16x16_kernel<true, 1>);
-    } else {
-        if (p == 4)
-            launch(quantize_inject_16x16_kernel<false, 4>);
-        else
-            launch(quantize_inject_16x16_kernel<false, 1>);
-    }
-    return hipGetLastError();
-}
-
 // ---------------------------------------------------------------------------
 // amax and cast in ONE launch (current scaling, Sec. 4.3), the tensor held on chip in between.
 // Two passes over a tensor move 6 bytes per element (2 read for the amax, 2 read again and 2
@@ -1011,7 +970,8 @@ __device__ uint32_t g_fused_cast_timeouts;
 
 struct FusedTensor {
     const uint16_t *x;
-    int64_t rows, cols, tiles_x;  // tiles_x: 256-column tiles per row of tiles
+    int64_t rows, cols;
+    uint32_t tiles_x;  // 256-column tiles per row of tiles
     uint8_t *q, *qT;
     float *amax_store, *scale_out, *scale_inv_out;
 };
@@ -1104,20 +1064,27 @@ __device__ __forceinline__ void fused_grid_max(uint32_t mx0, uint32_t mx1, Fused
     all1 = all[1];
 }
 
-// lane's 16x16 block of wave tile `wt` (a 128x128 quadrant of a 256x256 tile): false if outside
-__device__ __forceinline__ bool fused_locate(const FusedTensor &t, int64_t wt, int lane, int64_t &r0, int64_t &c0)
+// Wave tile `wt` (a 128x128 quadrant of a 256x256 tile) and this lane's 16x16 block in it: offsets
+// uniform over the wave (scalar registers) and 32-bit lane offsets, so that a row's address costs the
+// lane one register for all rows instead of two for each.
+struct FusedPlace {
+    int64_t x0, t0;    // element offset of the wave tile in the tensor / in the transposed codes
+    uint32_t xl, tl;   // the lane's block relative to them
+    bool inside;       // the lane's block lies in the tensor (whole blocks: in or out)
+};
+__device__ __forceinline__ FusedPlace fused_locate(const FusedTensor &t, uint32_t wt, int lane)
 {
-    const int64_t big = wt >> 2, by = big / t.tiles_x, bx = big - by * t.tiles_x;
-    const int quad = (int)(wt & 3);
-    r0 = by * kQuantBigTile + (quad >> 1) * 128 + (lane >> 3) * 16;
-    c0 = bx * kQuantBigTile + (quad & 1) * 128 + (lane & 7) * 16;
-    return r0 < t.rows && c0 < t.cols;
+    const uint32_t big = wt >> 2, by = big / t.tiles_x, bx = big - by * t.tiles_x, quad = wt & 3;
+    const int64_t R = (int64_t)by * kQuantBigTile + (quad >> 1) * 128, C = (int64_t)bx * kQuantBigTile + (quad & 1) * 128;
+    const uint32_t r = (lane >> 3) * 16, c = (lane & 7) * 16;
+    return FusedPlace{R * t.cols + C, C * t.rows + R, r * (uint32_t)t.cols + c, c * (uint32_t)t.rows + r,
+                      R + r < t.rows && C + c < t.cols};
 }
 
 // rows 8*half .. +7 of a lane's block: codes into qd and out to q (16 bytes a row)
 template <bool E5M2>
 __device__ __forceinline__ void cast_rows8(const uint4 (&in)[8][2], int half, float scale, uint32_t (&qd)[16][4],
-                                           uint8_t *__restrict__ q, int64_t r0, int64_t c0, int64_t cols)
+                                           const FusedTensor &t, const FusedPlace &at)
 {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
@@ -1130,7 +1097,7 @@ __device__ __forceinline__ void cast_rows8(const uint4 (&in)[8][2], int half, fl
             qd[r][2 * w + 1] = cvt4_f8<E5M2>(bf16lo_to_f32(v.z) * scale, bf16hi_to_f32(v.z) * scale,
                                          bf16lo_to_f32(v.w) * scale, bf16hi_to_f32(v.w) * scale);
         }
-        *(uint4 *)(q + (r0 + r) * cols + c0) = make_uint4(qd[r][0], qd[r][1], qd[r][2], qd[r][3]);
+        *(uint4 *)(t.q + at.x0 + r * t.cols + (uint64_t)at.xl) = make_uint4(qd[r][0], qd[r][1], qd[r][2], qd[r][3]);
     }
 }
 
@@ -1139,8 +1106,8 @@ __device__ __forceinline__ void cast_rows8(const uint4 (&in)[8][2], int half, fl
 // pass): the stores carry the streaming hint, the lines leave for memory without displacing what
 // the next GEMM reads
 template <bool LATER = false>
-__device__ __forceinline__ void store_block_transposed(const uint32_t (&qd)[16][4], uint8_t *__restrict__ qT,
-                                                       int64_t rows, int64_t r0, int64_t c0)
+__device__ __forceinline__ void store_block_transposed(const uint32_t (&qd)[16][4], const FusedTensor &f,
+                                                       const FusedPlace &at)
 {
 #pragma unroll
     for (int C = 0; C < 4; ++C) {
@@ -1152,7 +1119,7 @@ __device__ __forceinline__ void store_block_transposed(const uint32_t (&qd)[16][
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-            v4u *dst = (v4u *)(qT + (c0 + 4 * C + k) * rows + r0);
+            v4u *dst = (v4u *)(f.qT + at.t0 + (4 * C + k) * f.rows + (uint64_t)at.tl);
             const v4u v = {t[0][k], t[1][k], t[2][k], t[3][k]};
             if constexpr (LATER)
                 __builtin_nontemporal_store(v, dst);
@@ -1162,14 +1129,51 @@ __device__ __forceinline__ void store_block_transposed(const uint32_t (&qd)[16][
     }
 }
 
-template <bool E5M2, bool T_LATER>
-__global__ __launch_bounds__(kFusedThreads, 1) void amax_cast_fused_kernel(FusedTensor t0, FusedTensor t1, int64_t wt0,
-                                                                           int64_t wt_total, int rounds,
-                                                                           FusedSlot *slots, uint64_t token)
+// Rows row .. row + ROWS - 1 of a lane's block, 32 bytes each; INJECT (as in the cast body above): the
+// penalty gradient is added on the way in, from the same places of the activation, four rows at a
+// time with a scheduling fence behind each group (beside 192 registers of kept data there is room
+// for one group of the activation's rows; without the fence the compiler hoists all of its loads
+// and spills).
+template <int INJECT, int ROWS>
+__device__ __forceinline__ void fused_load_rows(uint4 (*__restrict__ in)[2], const FusedTensor &t, const FusedPlace &at,
+                                                int row, const InjectArgs &inj)
 {
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    const int G = gridDim.x;
-    auto tile_of = [&](int k) { return ((int64_t)k * G + blockIdx.x) * kFusedWaves + wave; };
+    constexpr int GROUP = INJECT != 0 ? 4 : ROWS;
+    auto load = [&](const uint16_t *base, int i, uint4 (&v)[2]) {
+        const uint4 *src = (const uint4 *)((const uint8_t *)(base + at.x0 + (row + i) * t.cols) + (uint64_t)(at.xl * 2u));
+        v[0] = src[0];
+        v[1] = src[1];
+    };
+#pragma unroll
+    for (int g = 0; g < ROWS; g += GROUP) {
+#pragma unroll
+        for (int i = 0; i < GROUP; ++i)
+            load(t.x, g + i, in[g + i]);
+        if constexpr (INJECT != 0) {
+            constexpr int P = INJECT == 4 ? 4 : 0;
+            uint4 a[GROUP][2];
+#pragma unroll
+            for (int i = 0; i < GROUP; ++i)
+                load(inj.act, g + i, a[i]);
+#pragma unroll
+            for (int i = 0; i < GROUP; ++i) {
+                in[g + i][0] = inject_vec<P>(in[g + i][0], a[i][0], inj);
+                in[g + i][1] = inject_vec<P>(in[g + i][1], a[i][1], inj);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+}
+
+template <bool E5M2, bool T_LATER, int INJECT = 0>
+__global__ __launch_bounds__(kFusedThreads, 1) void amax_cast_fused_kernel(FusedTensor t0, FusedTensor t1, uint32_t wt0,
+                                                                           uint32_t wt_total, int rounds,
+                                                                           FusedSlot *slots, uint64_t token,
+                                                                           InjectArgs inj)
+{
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const uint32_t G = gridDim.x;
+    auto tile_of = [&](int k) { return ((uint32_t)k * G + blockIdx.x) * kFusedWaves + wave; };
 
     // this wave's tiles are k = 0 .. mine-1 (the last round of the grid may not reach it)
     const int mine = tile_of(rounds - 1) < wt_total ? rounds : rounds - 1;
@@ -1184,22 +1188,17 @@ __global__ __launch_bounds__(kFusedThreads, 1) void amax_cast_fused_kernel(Fused
         keep2[i][0] = keep2[i][1] = make_uint4(0u, 0u, 0u, 0u);
     uint32_t mx0 = 0, mx1 = 0;
     for (int k = 0; k < mine - 1; ++k) {
-        const int64_t wt = tile_of(k);
+        const uint32_t wt = tile_of(k);
         const bool first = wt < wt0;
         const FusedTensor &t = first ? t0 : t1;
-        int64_t r0, c0;
-        if (!fused_locate(t, first ? wt : wt - wt0, lane, r0, c0))
+        const FusedPlace at = fused_locate(t, first ? wt : wt - wt0, lane);
+        if (!at.inside)
             continue;
         uint32_t m = 0;
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
             uint4 in[8][2];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const uint4 *src = (const uint4 *)(t.x + (r0 + half * 8 + i) * t.cols + c0);
-                in[i][0] = src[0];
-                in[i][1] = src[1];
-            }
+            fused_load_rows<INJECT, 8>(in, t, at, half * 8, inj);
 #pragma unroll
             for (int i = 0; i < 8; ++i)
                 m = pk_absmax4(pk_absmax4(m, in[i][0]), in[i][1]);
@@ -1225,22 +1224,17 @@ __global__ __launch_bounds__(kFusedThreads, 1) void amax_cast_fused_kernel(Fused
             mx1 = pk_absmax4(mx1, make_uint4(m, 0u, 0u, 0u));
     }
     uint4 keep[16][2];
-    bool kept = false, kept_first = false;
-    int64_t kr0 = 0, kc0 = 0;
+    bool kept_first = false;
+    FusedPlace kept{};
     {
         if (mine > 0) {
-            const int64_t wt = tile_of(mine - 1);
+            const uint32_t wt = tile_of(mine - 1);
             kept_first = wt < wt0;
             const FusedTensor &t = kept_first ? t0 : t1;
-            kept = fused_locate(t, kept_first ? wt : wt - wt0, lane, kr0, kc0);
-            if (kept) {
+            kept = fused_locate(t, kept_first ? wt : wt - wt0, lane);
+            if (kept.inside) {
                 uint32_t m = 0;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const uint4 *src = (const uint4 *)(t.x + (kr0 + i) * t.cols + kc0);
-                    keep[i][0] = src[0];
-                    keep[i][1] = src[1];
-                }
+                fused_load_rows<INJECT, 16>(keep, t, kept, 0, inj);
 #pragma unroll
                 for (int i = 0; i < 16; ++i)
                     m = pk_absmax4(pk_absmax4(m, keep[i][0]), keep[i][1]);
@@ -1270,7 +1264,7 @@ __global__ __launch_bounds__(kFusedThreads, 1) void amax_cast_fused_kernel(Fused
 
     // ---- phase 2: the cast, newest data first --------------------------------------------------
     uint32_t qd[16][4];
-    if (kept) {
+    if (kept.inside) {
         const FusedTensor &t = kept_first ? t0 : t1;
         const float scale = kept_first ? scale0 : scale1;
 #pragma unroll
@@ -1281,17 +1275,17 @@ __global__ __launch_bounds__(kFusedThreads, 1) void amax_cast_fused_kernel(Fused
                 in[i][0] = keep[half * 8 + i][0];
                 in[i][1] = keep[half * 8 + i][1];
             }
-            cast_rows8<E5M2>(in, half, scale, qd, t.q, kr0, kc0, t.cols);
+            cast_rows8<E5M2>(in, half, scale, qd, t, kept);
         }
-        store_block_transposed<T_LATER>(qd, t.qT, t.rows, kr0, kc0);
+        store_block_transposed<T_LATER>(qd, t, kept);
     }
     for (int k = mine - 2; k >= 0; --k) {
-        const int64_t wt = tile_of(k);
+        const uint32_t wt = tile_of(k);
         const bool first = wt < wt0;
         const FusedTensor &t = first ? t0 : t1;
         const float scale = first ? scale0 : scale1;
-        int64_t r0, c0;
-        if (!fused_locate(t, first ? wt : wt - wt0, lane, r0, c0))
+        const FusedPlace at = fused_locate(t, first ? wt : wt - wt0, lane);
+        if (!at.inside)
             continue;
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
@@ -1309,16 +1303,11 @@ __global__ __launch_bounds__(kFusedThreads, 1) void amax_cast_fused_kernel(Fused
                     in[i][1] = keep2[i][1];
                 }
             } else {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const uint4 *src = (const uint4 *)(t.x + (r0 + half * 8 + i) * t.cols + c0);
-                    in[i][0] = src[0];
-                    in[i][1] = src[1];
-                }
+                fused_load_rows<INJECT, 8>(in, t, at, half * 8, inj);
             }
-            cast_rows8<E5M2>(in, half, scale, qd, t.q, r0, c0, t.cols);
+            cast_rows8<E5M2>(in, half, scale, qd, t, at);
         }
-        store_block_transposed<T_LATER>(qd, t.qT, t.rows, r0, c0);
+        store_block_transposed<T_LATER>(qd, t, at);
     }
 }
 
@@ -1350,6 +1339,11 @@ bool fused_cast_applies(int64_t rows0, int64_t cols0, int64_t rows1, int64_t col
     // GPT-2 block step 0.563 -> 0.561 ms)
     if (rows0 * cols0 + rows1 * cols1 < ((int64_t)1 << 24))
         return false;
+    // the kernel's lane offsets and tile numbers are 32 bits
+    const int64_t most = (int64_t)1 << 24;
+    if (rows0 > most || cols0 > most || rows1 > most || cols1 > most ||
+        rows0 * cols0 + rows1 * cols1 >= ((int64_t)1 << 42))
+        return false;
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone)
         return false;
@@ -1357,22 +1351,23 @@ bool fused_cast_applies(int64_t rows0, int64_t cols0, int64_t rows1, int64_t col
 }
 
 // x1 may be nullptr (one tensor).  slots: 16 bytes per workgroup, at most kFusedMaxWorkgroups of
-// them, no initial contents assumed.
-hipError_t launch_amax_cast_fused(const void *x0_bf16, int64_t rows0, int64_t cols0, float *amax0, uint8_t *q0,
+// them, no initial contents assumed.  inj.act: the penalty gradient is added to x0 (the only tensor
+// then) on the way in.
+static hipError_t launch_amax_cast_fused_impl(const void *x0_bf16, int64_t rows0, int64_t cols0, float *amax0, uint8_t *q0,
                                   uint8_t *q0T, float *scale0, float *scale0_inv, const void *x1_bf16,
                                   int64_t rows1, int64_t cols1, float *amax1, uint8_t *q1, uint8_t *q1T,
                                   float *scale1, float *scale1_inv, bool e5m2, bool transposed_later, void *slots,
-                                  hipStream_t s)
+                                  const InjectArgs &inj, hipStream_t s)
 {
-    auto tiles = [](int64_t v) { return (v + kQuantBigTile - 1) / kQuantBigTile; };
+    auto tiles = [](int64_t v) { return (uint32_t)((v + kQuantBigTile - 1) / kQuantBigTile); };
     const FusedTensor t0{(const uint16_t *)x0_bf16, rows0, cols0, tiles(cols0), q0, q0T, amax0, scale0, scale0_inv};
     FusedTensor t1 = t0;
-    int64_t wt1 = 0;
+    uint32_t wt1 = 0;
     if (x1_bf16 != nullptr) {
         t1 = FusedTensor{(const uint16_t *)x1_bf16, rows1, cols1, tiles(cols1), q1, q1T, amax1, scale1, scale1_inv};
         wt1 = 4 * tiles(rows1) * tiles(cols1);
     }
-    const int64_t wt0 = 4 * tiles(rows0) * tiles(cols0), wt_total = wt0 + wt1;
+    const uint32_t wt0 = 4 * tiles(rows0) * tiles(cols0), wt_total = wt0 + wt1;
     int64_t grid = (wt_total + kFusedWaves - 1) / kFusedWaves;
     const int64_t cap = amax_cus() < kFusedMaxWorkgroups ? amax_cus() : kFusedMaxWorkgroups;
     if (grid > cap)
@@ -1388,17 +1383,84 @@ hipError_t launch_amax_cast_fused(const void *x0_bf16, int64_t rows0, int64_t co
             attr_done = true;
         }
         hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kFusedThreads), kFusedLdsBytes, s, t0, t1, wt0, wt_total,
-                           rounds, (FusedSlot *)slots, token);
+                           rounds, (FusedSlot *)slots, token, inj);
         err = hipGetLastError();
     };
-    static bool done[3] = {false, false, false};
-    if (e5m2)
+    static bool done[7] = {};
+    if (inj.act != nullptr) {
+        if (e5m2)
+            inj.p == 4 ? launch(amax_cast_fused_kernel<true, false, 4>, done[3])
+                       : launch(amax_cast_fused_kernel<true, false, 1>, done[4]);
+        else
+            inj.p == 4 ? launch(amax_cast_fused_kernel<false, false, 4>, done[5])
+                       : launch(amax_cast_fused_kernel<false, false, 1>, done[6]);
+    } else if (e5m2)
         launch(amax_cast_fused_kernel<true, false>, done[0]);  // gradients: both copies are read at once
     else if (transposed_later)
         launch(amax_cast_fused_kernel<false, true>, done[1]);
     else
         launch(amax_cast_fused_kernel<false, false>, done[2]);
     return err;
+}
+
+hipError_t launch_amax_cast_fused(const void *x0_bf16, int64_t rows0, int64_t cols0, float *amax0, uint8_t *q0,
+                                  uint8_t *q0T, float *scale0, float *scale0_inv, const void *x1_bf16,
+                                  int64_t rows1, int64_t cols1, float *amax1, uint8_t *q1, uint8_t *q1T,
+                                  float *scale1, float *scale1_inv, bool e5m2, bool transposed_later, void *slots,
+                                  hipStream_t s)
+{
+    return launch_amax_cast_fused_impl(x0_bf16, rows0, cols0, amax0, q0, q0T, scale0, scale0_inv, x1_bf16, rows1, cols1,
+                                       amax1, q1, q1T, scale1, scale1_inv, e5m2, transposed_later, slots, InjectArgs{},
+                                       s);
+}
+
+// amax and cast of dy' = bf16(dy + coef * sign(a) * (|a| * inv_tau)^(p-1)) without storing dy'
+// (rows, cols multiples of 16): one launch that keeps dy' on chip between the two steps where that
+// form applies - it reads dy and the activation once, 6 bytes per element for what stays on chip
+// against 10 (50432x768: 96 us in two launches, 66 in one) - else an amax launch that leaves
+// workgroup maxima and a cast launch that reduces them.
+hipError_t launch_amax_quantize_inject(const void *dy_bf16, const void *a_bf16, int64_t rows, int64_t cols,
+                                       float inv_tau, float coef, int p, bool e5m2, uint32_t *partials,
+                                       float *amax_out, uint8_t *q, uint8_t *qT, float *scale_out,
+                                       float *scale_inv_out, hipStream_t s)
+{
+    const InjectArgs inj{(const uint16_t *)a_bf16, inv_tau, coef, p};
+    if (fused_cast_applies(rows, cols, 0, 0, s))
+        return launch_amax_cast_fused_impl(dy_bf16, rows, cols, amax_out, q, qT, scale_out, scale_inv_out, nullptr, 0, 0,
+                                           nullptr, nullptr, nullptr, nullptr, nullptr, e5m2, false, partials, inj, s);
+    const int64_t n_vec = rows * cols / 8;
+    int64_t blocks = n_vec / (kAmaxUnroll * kAmaxThreads);
+    if (blocks < 1)
+        blocks = 1;
+    if (blocks > amax_cus())
+        blocks = amax_cus();
+    if (p == 4)
+        hipLaunchKernelGGL(amax_inject_kernel<4>, dim3((unsigned)blocks), dim3(kAmaxThreads), 0, s,
+                           (const uint4 *)dy_bf16, inj, n_vec, (n_vec + blocks - 1) / blocks, partials);
+    else
+        hipLaunchKernelGGL(amax_inject_kernel<0>, dim3((unsigned)blocks), dim3(kAmaxThreads), 0, s,
+                           (const uint4 *)dy_bf16, inj, n_vec, (n_vec + blocks - 1) / blocks, partials);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess)
+        return e;
+    const int64_t tiles_x = (cols + kQuantBigTile - 1) / kQuantBigTile, tiles_y = (rows + kQuantBigTile - 1) / kQuantBigTile;
+    const dim3 grid((unsigned)(tiles_x * tiles_y)), block(kQuantThreads);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, 0, s, (const uint16_t *)dy_bf16, inj, rows, cols, tiles_x, q, qT,
+                           scale_out, scale_inv_out, (const uint32_t *)partials, (int)blocks, amax_out);
+    };
+    if (e5m2) {
+        if (p == 4)
+            launch(quantize_inject_16x16_kernel<true, 4>);
+        else
+            launch(quantize_inject_16x16_kernel<true, 1>);
+    } else {
+        if (p == 4)
+            launch(quantize_inject_16x16_kernel<false, 4>);
+        else
+            launch(quantize_inject_16x16_kernel<false, 1>);
+    }
+    return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
