@@ -1417,7 +1417,7 @@ hipError_t launch_amax_cast_fused(const void *x0_bf16, int64_t rows0, int64_t co
 // amax and cast of dy' = bf16(dy + coef * sign(a) * (|a| * inv_tau)^(p-1)) without storing dy'
 // (rows, cols multiples of 16): one launch that keeps dy' on chip between the two steps where that
 // form applies - it reads dy and the activation once, 6 bytes per element for what stays on chip
-// against 10 (50432x768: 96 us in two launches, 66 in one) - else an amax launch that leaves
+// against 10 (50432x768: 96 us in two launches, 73 in one) - else an amax launch that leaves
 // workgroup maxima and a cast launch that reduces them.
 hipError_t launch_amax_quantize_inject(const void *dy_bf16, const void *a_bf16, int64_t rows, int64_t cols,
                                        float inv_tau, float coef, int p, bool e5m2, uint32_t *partials,

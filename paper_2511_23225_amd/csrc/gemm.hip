@@ -1562,16 +1562,16 @@ static int pick_variant(int64_t M, int64_t N, int64_t K)
 }
 
 // The deferred-epilogue kernel covers whole 256x256 tiles, K in whole stages with enough of
-// them to drain a tile under, no residual, p in {0, 4}.
+// them to drain a tile under (and, with a residual, to fetch that: 16 stages), p in {0, 4}.
 static bool defer_ok(const GemmArgs &a)
 {
-    return a.M % 256 == 0 && a.N % 256 == 0 && a.K % 128 == 0 && a.K >= 512 && a.residual == nullptr &&
+    return a.M % 256 == 0 && a.N % 256 == 0 && a.K % 128 == 0 && a.K >= (a.residual != nullptr ? 2048 : 512) &&
            a.row_step == nullptr && (a.p == 0 || a.p == 4) && a.N <= ((int64_t)1 << 22);
 }
 
 static bool defer192_ok(const GemmArgs &a)
 {
-    return a.N % 256 == 0 && a.K % 128 == 0 && a.K >= 2048 && a.residual == nullptr &&
+    return a.N % 256 == 0 && a.K % 128 == 0 && a.K >= 2048 &&
            a.row_step == nullptr && (a.p == 0 || a.p == 4) && a.N <= ((int64_t)1 << 22);
 }
 
@@ -1726,14 +1726,15 @@ static hipError_t launch_stream(const GemmArgs &a, hipStream_t s)
     return launch_stream_inst<T, INT8, WG_PER_CU, false>(a, s, grid, 0);
 }
 
-template <bool INT8, int PMODE, int D, int MT, bool A_E5M2 = false>
+template <bool INT8, int PMODE, int D, int MT, bool A_E5M2 = false, bool RES = false>
 static hipError_t launch_defer_inst(const GemmArgs &a, hipStream_t s)
 {
     using T = DeferTile<MT>;
+    constexpr int LDS = RES ? T::LDS_BYTES_RES : T::LDS_BYTES;
+    constexpr auto kernel = gemm_nt_defer_kernel<INT8, PMODE, D, MT, A_E5M2, true, false, RES>;
     static bool attr_done = false;
     if (!attr_done) {
-        hipError_t e = hipFuncSetAttribute((const void *)gemm_nt_defer_kernel<INT8, PMODE, D, MT, A_E5M2>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
+        hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
         if (e != hipSuccess)
             return e;
         attr_done = true;
@@ -1747,7 +1748,7 @@ static hipError_t launch_defer_inst(const GemmArgs &a, hipStream_t s)
     g.s0 = a.s0;
     g.s1 = a.s1;
     g.alpha = a.alpha;
-    g.residual = nullptr;
+    g.residual = RES ? (const uint16_t *)a.residual : nullptr;
     g.out = (uint16_t *)a.out;
     g.inv_tau = a.inv_tau;
     g.p = a.p;
@@ -1763,7 +1764,7 @@ static hipError_t launch_defer_inst(const GemmArgs &a, hipStream_t s)
     g.tiles_m = (int)((a.M + T::BM - 1) / T::BM);
     g.tiles_n = (int)(a.N / T::BN);
     const int grid = defer_workgroups(a.M, a.N, T::BM);
-    launch_gemm_kernel(gemm_nt_defer_kernel<INT8, PMODE, D, MT, A_E5M2>, dim3((unsigned)grid), dim3(T::THREADS), T::LDS_BYTES, s, g);
+    launch_gemm_kernel(kernel, dim3((unsigned)grid), dim3(T::THREADS), LDS, s, g);
     return hipGetLastError();
 }
 
@@ -1772,12 +1773,23 @@ static hipError_t launch_defer(const GemmArgs &a, hipStream_t s)
 {
     // a tile is written out over the first 15, 7, 5 or 3 stages of the next one (never its last)
     const int64_t kt = a.K / 128;
-    if (a.p == 4) {
-        if (kt >= 16)
-            return launch_defer_inst<INT8, 4, 15, 4>(a, s);
-        if (kt >= 8)
-            return launch_defer_inst<INT8, 4, 7, 4>(a, s);
-        return kt >= 6 ? launch_defer_inst<INT8, 4, 5, 4>(a, s) : launch_defer_inst<INT8, 4, 3, 4>(a, s);
+    if constexpr (!INT8) {
+        // with a residual the write-out (D stages), the residual's ten stages and the last one must fit:
+        // seven stages of write-out from 18 on, five for 16 and 17
+        if (a.residual != nullptr) {
+            if (a.p == 4)
+                return kt >= 18 ? launch_defer_inst<false, 4, 7, 4, false, true>(a, s)
+                                : launch_defer_inst<false, 4, 5, 4, false, true>(a, s);
+            return kt >= 18 ? launch_defer_inst<false, 0, 7, 4, false, true>(a, s)
+                            : launch_defer_inst<false, 0, 5, 4, false, true>(a, s);
+        }
+        if (a.p == 4) {
+            if (kt >= 16)
+                return launch_defer_inst<false, 4, 15, 4>(a, s);
+            if (kt >= 8)
+                return launch_defer_inst<false, 4, 7, 4>(a, s);
+            return kt >= 6 ? launch_defer_inst<false, 4, 5, 4>(a, s) : launch_defer_inst<false, 4, 3, 4>(a, s);
+        }
     }
     if (kt >= 16)
         return launch_defer_inst<INT8, 0, 15, 4>(a, s);
@@ -1790,7 +1802,14 @@ static hipError_t launch_defer(const GemmArgs &a, hipStream_t s)
 template <bool INT8>
 static hipError_t launch_defer192(const GemmArgs &a, hipStream_t s)
 {
-    return a.p == 4 ? launch_defer_inst<INT8, 4, 15, 3>(a, s) : launch_defer_inst<INT8, 0, 15, 3>(a, s);
+    if constexpr (!INT8) {
+        if (a.residual != nullptr)
+            return a.p == 4 ? launch_defer_inst<false, 4, 7, 3, false, true>(a, s)
+                            : launch_defer_inst<false, 0, 7, 3, false, true>(a, s);
+        if (a.p == 4)
+            return launch_defer_inst<false, 4, 15, 3>(a, s);
+    }
+    return launch_defer_inst<INT8, 0, 15, 3>(a, s);
 }
 
 template <bool INT8>

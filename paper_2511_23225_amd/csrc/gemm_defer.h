@@ -54,6 +54,11 @@ struct DeferTile {
     static constexpr int A_BYTES = BM * BK, STAGE_BYTES = (BM + BN) * BK;
     static constexpr int STAGE_STRIDE = 65536;            // power of two: buffers are toggled by XOR
     static constexpr int LDS_BYTES = 2 * STAGE_STRIDE;
+    // residual form: 4 KB per pair of neighbouring blocks (32 rows x 128 B), two per wave, behind the stages
+    static constexpr int RES_UNITS = 2 * MT, RES_UNIT_BYTES = 4096, RES_WAVE_BYTES = 2 * RES_UNIT_BYTES;
+    static constexpr int RES_STAGES = RES_UNITS + 2;      // unit c is loaded in the c-th of them, read in the (c+2)-th
+    static constexpr int LDS_BYTES_RES = LDS_BYTES + NWAVES * RES_WAVE_BYTES;
+    static_assert(LDS_BYTES_RES <= 160 * 1024, "LDS capacity with a residual");
     static constexpr int SLAB = NB, SLOTS = 2 * NB;       // MFMA slots per K slab / per stage
     static constexpr int NA = BM / 32, NBP = BN / 32;     // operand pieces per wave per stage
     static constexpr int STEPS_PER_BLOCK = 8;             // micro-steps of writing a block out
@@ -161,7 +166,19 @@ __device__ __forceinline__ void for_each_constant(std::integer_sequence<int, Is.
 // them (unit, wave, block, quarter, lane: every store instruction writes 1 KB contiguously);
 // splitk_reduce_defer_kernel adds the runs in index order, rounds and writes the output.  One
 // unit per workgroup, so nothing is deferred.
-template <bool INT8, int PMODE, int D, int MT, bool A_E5M2 = false, bool LINES = true, bool KSPLIT = false>
+// RES (FP8): y = bf16(acc * alpha + residual).  The registers of the packed output are idle between
+// the end of a tile's write-out (stage D of the next tile) and the next conversion: the residual of
+// the current tile is brought there during the tile's last RES_STAGES stages before the final one
+// and the conversion becomes a multiply-add onto it.  It travels like the operands, by direct-to-LDS
+// loads of whole 128-byte lines (a load to registers in the MFMA layout touches 32 rows for 16 bytes
+// each, four times the address work), into 8 KB per wave behind the operand stages: nobody else
+// touches them, so no barrier is added.  Four loads per stage go in front of the B pieces, the wait
+// in front of the second barrier then leaves twelve loads in flight instead of eight, and a unit
+// has a whole stage (1.2 us) to arrive in.  Kernel times with the penalty on, against the 8-wave
+// streaming kernel, which adds the residual behind the tile with nothing running under it:
+// 50432x3072 -> 768 175 -> 133 us, 16384x5632 -> 2048 174 -> 140 us (without a residual 120 and 133).
+template <bool INT8, int PMODE, int D, int MT, bool A_E5M2 = false, bool LINES = true, bool KSPLIT = false,
+          bool RES = false>
 __global__ __launch_bounds__(256, 1) void gemm_nt_defer_kernel(GemmDev g)
 {
     using T = DeferTile<MT>;
@@ -303,34 +320,33 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_defer_kernel(GemmDev g)
     // lane (l31, lh) reads row l31 of a 32-row block; logical chunks of slab kk:
     // FP8 4kk+2lh, 4kk+2lh+1 (32 contiguous bytes of K); INT8 4kk+lh and 4kk+2+lh
     const int sw = (l31 >> 1) & 7;
-    uint32_t pa[2][2], pb[2][2];  // [slab][half]: byte offsets into smem, stage 0
-#pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-        const int c0 = INT8 ? 4 * kk + lh : 4 * kk + 2 * lh;
-        const int c1 = INT8 ? 4 * kk + 2 + lh : 4 * kk + 2 * lh + 1;
-        pa[kk][0] = (wm * MT * 32 + l31) * T::BK + ((c0 ^ sw) << 4);
-        pa[kk][1] = (wm * MT * 32 + l31) * T::BK + ((c1 ^ sw) << 4);
-        pb[kk][0] = T::A_BYTES + (wn * 128 + l31) * T::BK + ((c0 ^ sw) << 4);
-        pb[kk][1] = T::A_BYTES + (wn * 128 + l31) * T::BK + ((c1 ^ sw) << 4);
+    // [half]: byte offsets into smem of the slab that is read next.  Slab 1 is slab 0 with chunk bit 2
+    // flipped (bit 6 of the offset), so one set of registers serves both: from slot SLAB - 4 of a
+    // stage on the reads are of slab 1, from slot SLOTS - 4 on of slab 0 of the next stage.
+    uint32_t pa[2], pb[2];
+    {
+        const int c0 = INT8 ? lh : 2 * lh, c1 = INT8 ? 2 + lh : 2 * lh + 1;
+        pa[0] = (wm * MT * 32 + l31) * T::BK + ((c0 ^ sw) << 4);
+        pa[1] = (wm * MT * 32 + l31) * T::BK + ((c1 ^ sw) << 4);
+        pb[0] = T::A_BYTES + (wn * 128 + l31) * T::BK + ((c0 ^ sw) << 4);
+        pb[1] = T::A_BYTES + (wn * 128 + l31) * T::BK + ((c1 ^ sw) << 4);
     }
-    auto flip_stage = [&]() {
+    auto flip = [&](uint32_t bits) {
 #pragma unroll
-        for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                pa[kk][h] ^= T::STAGE_STRIDE;
-                pb[kk][h] ^= T::STAGE_STRIDE;
-            }
+        for (int h = 0; h < 2; ++h) {
+            pa[h] ^= bits;
+            pb[h] ^= bits;
+        }
     };
     v8i fa[2], fb[4];
-    auto load_a = [&](v8i &f, int kk, int i) {
-        const v4i x = *(const v4i *)(smem + pa[kk][0] + i * 32 * T::BK);
-        const v4i y = *(const v4i *)(smem + pa[kk][1] + i * 32 * T::BK);
+    auto load_a = [&](v8i &f, int i) {
+        const v4i x = *(const v4i *)(smem + pa[0] + i * 32 * T::BK);
+        const v4i y = *(const v4i *)(smem + pa[1] + i * 32 * T::BK);
         f = v8i{x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
     };
-    auto load_b = [&](v8i &f, int kk, int j) {
-        const v4i x = *(const v4i *)(smem + pb[kk][0] + j * 32 * T::BK);
-        const v4i y = *(const v4i *)(smem + pb[kk][1] + j * 32 * T::BK);
+    auto load_b = [&](v8i &f, int j) {
+        const v4i x = *(const v4i *)(smem + pb[0] + j * 32 * T::BK);
+        const v4i y = *(const v4i *)(smem + pb[1] + j * 32 * T::BK);
         f = v8i{x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
     };
 
@@ -399,7 +415,14 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_defer_kernel(GemmDev g)
                        "a"(acc[i][j][4 * q0 + 6]), "a"(acc[i][j][4 * q0 + 7]));
 #pragma unroll
         for (int d = 0; d < 4; ++d)
-            packed[i][j][2 * q0 + d] = pack_bf16x2((float)t[2 * d] * alpha, (float)t[2 * d + 1] * alpha);
+        {
+            uint32_t &w = packed[i][j][2 * q0 + d];
+            if constexpr (RES)
+                w = pack_bf16x2(__builtin_fmaf((float)t[2 * d], alpha, bf16lo_to_f32(w)),
+                                __builtin_fmaf((float)t[2 * d + 1], alpha, bf16hi_to_f32(w)));
+            else
+                w = pack_bf16x2((float)t[2 * d] * alpha, (float)t[2 * d + 1] * alpha);
+        }
         // make the four results exist here, not whenever the instruction selector gets round to
         // them (pure arithmetic floats past fences)
         asm volatile(""
@@ -517,6 +540,50 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_defer_kernel(GemmDev g)
             sp += rows32;
     };
 
+    // ---- residual (RES): unit c = block pair (band c / 2, columns 64 * (c % 2) .. +63) ------------
+    // load n of a unit fills rows 8n .. 8n+7 (128 bytes each, chunks XOR-swizzled with (row/2)%8 as
+    // in the operand stages); buffer c % 2 of the wave's own LDS
+    const uint32_t res_lds = lds_base + T::LDS_BYTES + wave * T::RES_WAVE_BYTES;
+    const uint8_t *rp = nullptr;  // this wave's columns of the tile, from its first row (EDGE: the tile's) on
+    int res_valid = 0;            // EDGE: rows of the tile inside the matrix
+    // chunk of a lane in an even load (rows 0..7 of 16); in an odd one its bit 2 is flipped, which is
+    // bit 6 of the offset (a row is a multiple of 512 bytes)
+    const uint32_t res_voff = (uint32_t)dma_row * (uint32_t)g.N * 2u + (uint32_t)((dma_p ^ (dma_row >> 1)) << 4);
+    auto res_begin = [&](int tm, int tn) {
+        const int64_t row0 = (int64_t)tm * T::BM + (T::EDGE ? 0 : wm * MT * 32);
+        rp = (const uint8_t *)g.residual + (row0 * g.N + (int64_t)tn * T::BN + wn * 128) * 2;
+        res_valid = g.M - tm * T::BM;
+    };
+    auto res_load = [&](int c, int n) {
+        const int i = c >> 1, jp = c & 1;
+        const uint32_t dst = res_lds + (c & 1) * T::RES_UNIT_BYTES + n * 1024;
+        const int64_t unit = (int64_t)jp * 128 + (T::EDGE ? 0 : i * rows32);
+        if constexpr (T::EDGE) {  // rows past the matrix load the last valid one
+            const int rt = wm * MT * 32 + i * 32 + 8 * n + dma_row;
+            const uint32_t v = (uint32_t)(rt < res_valid ? rt : res_valid - 1) * (uint32_t)g.N * 2u +
+                               (uint32_t)((dma_p ^ (dma_row >> 1) ^ (4 * (n & 1))) << 4);
+            dma_load16(dst, rp + unit, v);
+        } else {
+            dma_load16(dst, rp + unit + n * (rows32 >> 2), res_voff ^ (64u * (n & 1)));
+        }
+    };
+    // 16-byte piece (X, u) of lane (row, lh): columns 8 * (4X + 2u + lh) .. +7 of the unit's 64; the
+    // exchange between the half-waves leaves words 4u .. 4u+3 of block X as the accumulators lie
+    const uint32_t res_rd = (uint32_t)(T::LDS_BYTES + wave * T::RES_WAVE_BYTES + l31 * 128 + ((lh ^ sw) << 4));
+    auto res_read = [&](int c, int X, int u) {
+        const v4i v = *(const v4i *)(smem + (res_rd ^ (uint32_t)((4 * X + 2 * u) << 4)) + (c & 1) * T::RES_UNIT_BYTES);
+        uint32_t *w = &packed[c >> 1][2 * (c & 1) + X][4 * u];
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+            w[d] = (uint32_t)v[d];
+    };
+    auto res_swap = [&](int c, int X, int u) {
+        uint32_t *w = &packed[c >> 1][2 * (c & 1) + X][4 * u];
+        // the swap reads its operands early, and what follows may read its results early
+        asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %2\n\tv_permlane32_swap_b32 %1, %3\n\ts_nop 1"
+                     : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]));
+    };
+
     // The penalty terms are summed per lane over every tile of the workgroup (a few thousand
     // fp32 terms), reduced over the wave once, at the end, and written as
     // partials[workgroup][wave]; the finishing kernel adds them in index order in fp64.
@@ -536,12 +603,15 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_defer_kernel(GemmDev g)
     // micro-steps are dealt evenly over the slots of the first D stages, from slot 2 on.  FIRST: a
     // tile starts (1: the workgroup's first tile, 2: a later one, which also converts the last
     // half blocks of its predecessor).  LAST: a tile ends: its blocks are converted as they finish.
+    // RS >= 0: residual stage RS of RES_STAGES.
     constexpr int W = D * T::FREE;
     // The slot number is a compile-time constant of each slot's body (the bodies are stamped out
     // from an integer sequence): which pieces a slot carries is decided by the front end, not
     // left to constant propagation through unrolled loops.
-    auto stage = [&](auto dr_c, auto first_c, auto last_c) {
+    auto stage = [&](auto dr_c, auto first_c, auto last_c, auto... rs_c) {
         constexpr int DR = decltype(dr_c)::value, FIRST = decltype(first_c)::value;
+        constexpr int RS = (-1 + ... + (decltype(rs_c)::value + 1));
+        constexpr bool RES_LOADS = RS >= 0 && RS < T::RES_UNITS;
         constexpr bool LAST = decltype(last_c)::value;
         auto slot_body = [&](auto t_c) {
                 {
@@ -557,22 +627,25 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_defer_kernel(GemmDev g)
                         // every LDS read of this stage has been issued: wait for them and for this
                         // wave's share of the next stage (everything but the eight B pieces of the
                         // stage after next, the youngest loads), then publish
-                        asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)" ::: "memory");
+                        // (and, of a residual, the four loads in front of those)
+                        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(RES_LOADS ? 12 : 8) : "memory");
                         block_barrier();
-                        flip_stage();
+                        flip(T::STAGE_STRIDE ^ 64u);
                     }
+                    if constexpr (t == T::SLAB - 4)
+                        flip(64u);
                     if constexpr (FIRST != 0 && kk == 0)
                         mfma_first(kk, i, j);
                     else
                         mfma(kk, i, j);
                     if constexpr (j == 0) {
                         if constexpr (i < MT - 1)
-                            load_a(fa[(kk * MT + i + 1) & 1], kk, i + 1);
+                            load_a(fa[(kk * MT + i + 1) & 1], i + 1);
                         else
-                            load_a(fa[((kk ^ 1) * MT) & 1], kk ^ 1, 0);  // next slab (after the flip: next stage)
+                            load_a(fa[((kk ^ 1) * MT) & 1], 0);  // next slab
                     }
                     if constexpr (i == MT - 1)
-                        load_b(fb[j], kk ^ 1, j);
+                        load_b(fb[j], j);
                     // operand stream, at most one piece per slot: A of the next stage (second
                     // half of its pieces) in the first slots, B of the stage after next right
                     // behind the first barrier (which released its buffer half), A of the stage
@@ -587,6 +660,16 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_defer_kernel(GemmDev g)
                             stream_advance(sb, true);
                     } else if constexpr (t >= T::SLOTS - 4 && t < T::SLOTS - 4 + T::NA / 2) {
                         dma_piece_a(t - (T::SLOTS - 4));
+                    }
+                    if constexpr (RES_LOADS && t >= T::SLAB - 4 && t < T::SLAB)
+                        res_load(RS, t - (T::SLAB - 4));
+                    if constexpr (RS >= 2) {
+                        if constexpr (t == 1 || t == 2) {
+                            res_read(RS - 2, t - 1, 0);
+                            res_read(RS - 2, t - 1, 1);
+                        } else if constexpr (t >= 4 && t < 8) {
+                            res_swap(RS - 2, (t - 4) >> 1, (t - 4) & 1);
+                        }
                     }
                     // conversion of the tile that ends here / ended in the previous stage
 #pragma unroll
@@ -656,10 +739,10 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_defer_kernel(GemmDev g)
         dma_piece_a(p8);
     wait_vmcnt<T::NBP + T::NA / 2>();
     block_barrier();
-    load_a(fa[0], 0, 0);
+    load_a(fa[0], 0);
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-        load_b(fb[j], 0, j);
+        load_b(fb[j], j);
 
     if constexpr (KSPLIT) {
         stage(no_drain{}, integral_constant<int, 1>{}, false_type{});
@@ -689,8 +772,55 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_defer_kernel(GemmDev g)
             }
         return;
     }
-    // first tile: nothing to write out yet
     int id = slot;
+    if constexpr (RES) {
+        // one copy of the residual stages for the first tile and the later ones
+        auto residual_stages = [&](auto... rs) {
+            (stage(no_drain{}, mid{}, false_type{}, rs), ...);
+        };
+        int tm = first_tm, tn = first_tn, round = 0;
+        for (;;) {
+            int s;
+            if (round == 0) {
+                stage(no_drain{}, integral_constant<int, 1>{}, false_type{});
+                s = 1;
+            } else {
+                stage(integral_constant<int, 0>{}, integral_constant<int, 2>{}, false_type{});
+                stage(integral_constant<int, 1>{}, mid{}, false_type{});
+                stage(integral_constant<int, 2>{}, mid{}, false_type{});
+                stage(integral_constant<int, 3>{}, mid{}, false_type{});
+                stage(integral_constant<int, 4>{}, mid{}, false_type{});
+                if constexpr (D >= 7) {
+                    stage(integral_constant<int, 5>{}, mid{}, false_type{});
+                    stage(integral_constant<int, 6>{}, mid{}, false_type{});
+                }
+                s = D;
+            }
+            static_assert(!RES || D == 5 || D == 7, "stages stamped out above");
+            res_begin(tm, tn);
+            for (; s < kt - 1 - T::RES_STAGES; ++s)
+                stage(no_drain{}, mid{}, false_type{});
+            if constexpr (MT == 4)
+                residual_stages(integral_constant<int, 0>{}, integral_constant<int, 1>{}, integral_constant<int, 2>{},
+                                integral_constant<int, 3>{}, integral_constant<int, 4>{}, integral_constant<int, 5>{},
+                                integral_constant<int, 6>{}, integral_constant<int, 7>{}, integral_constant<int, 8>{},
+                                integral_constant<int, 9>{});
+            else
+                residual_stages(integral_constant<int, 0>{}, integral_constant<int, 1>{}, integral_constant<int, 2>{},
+                                integral_constant<int, 3>{}, integral_constant<int, 4>{}, integral_constant<int, 5>{},
+                                integral_constant<int, 6>{}, integral_constant<int, 7>{});
+            stage(no_drain{}, mid{}, true_type{});
+            store_begin(tm, tn);
+            id += G;
+            if (id >= total)
+                break;
+            tm = next_tm;  // what the last plan_next fetched: this tile
+            tn = next_tn;
+            ++round;
+            plan_next(round + 1);
+        }
+    } else {
+    // first tile: nothing to write out yet
     {
         const int tm = first_tm, tn = first_tn;
         stage(no_drain{}, integral_constant<int, 1>{}, false_type{});
@@ -730,6 +860,7 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_defer_kernel(GemmDev g)
             stage(no_drain{}, mid{}, false_type{});
         stage(no_drain{}, mid{}, true_type{});
         store_begin(tm, tn);
+    }
     }
     // The workgroup's last tile: the rest of its conversion, then its write-out with nothing to
     // hide it under.  Here every CU of the chip stores at the same time, and 16-byte pieces would

@@ -192,6 +192,44 @@ def test_fwd_stream_k_split_of_the_last_round(with_residual):
     assert np.array_equal(runs[0][0], runs[1][0]) and runs[0][1] == runs[1][1]  # deterministic
 
 
+# the deferred-epilogue kernels with a residual: stages 16 and 17 (five stages of write-out), 18 and
+# more (seven), 192-row tiles with a ragged last row; 264 tiles give some workgroups a second tile
+RESIDUAL_CASES = [
+    (15, 256, 2048, 512, PEN), (15, 512, 2304, 256, PEN), (15, 8448, 2176, 2048, PEN), (15, 8448, 2432, 2048, None),
+    (15, 512, 2048, 256, None), (16, 200, 2048, 512, PEN), (16, 4160, 2176, 3072, PEN), (16, 4160, 2048, 3072, None),
+]
+
+
+@pytest.mark.parametrize("case", RESIDUAL_CASES)
+def test_fwd_residual_on_the_deferred_kernels(case):
+    tile, M, K, N, pen = case
+    say("fwd deferred residual tile=%d M=%d K=%d N=%d pen=%s" % case)
+    x, w, _ = synth.fp8_linear_inputs(3, 0, M=M, K=K, N=N)
+    res = synth.residual_input(3, 0, M, N)
+    xq, _, sxi = oracle_quantized(x)
+    wq, _, swi = oracle_quantized(w)
+    ref, refabs, refbf = oracle.fp8_linear_fwd(xq, wq, sxi, swi, residual=res)
+    xd, wd, sx, sw = to_dev(xq), to_dev(wq), scalar_f32(sxi), scalar_f32(swi)
+    ws = workspace(tw.TWEO_OP_FP8_LINEAR_FWD, M, N, K)
+    outs = []
+    for in_place in (False, True):  # y may be the residual's own buffer
+        r = to_dev_bf16(res)
+        y = r if in_place else torch.full((M, N), float("nan"), dtype=torch.bfloat16, device=DEV)
+        S = torch.zeros(2, dtype=torch.float64, device=DEV)
+        tw.tweo_set_gemm_tile(tile)
+        try:
+            tw.tweo_fp8_linear_fwd(xd, sx, wd, sw, y, residual_bf16=r, pen=pen, penalty_sum=S if pen else None, workspace=ws)
+            torch.cuda.synchronize()
+        finally:
+            tw.tweo_set_gemm_tile(0)
+        got = bf16_bits(y)
+        check_gemm(got, ref, refabs, K, "fwd residual")
+        if pen:
+            check_penalty(float(S.cpu()[0]), got, refbf, oracle.penalty_sum(refbf, *pen), pen, strict=M * N >= 1 << 20)
+        outs.append(got)
+    assert np.array_equal(outs[0], outs[1])
+
+
 def test_fwd_residual_is_block_output():
     # y = x + f(x): the penalised tensor is the block output (Sec. 3.3)
     cfg, gi, M, K, N = 1, 3, 384, 1024, 256
