@@ -4,6 +4,7 @@
 #include <hip/hip_ext.h>
 #include <atomic>
 #include <chrono>
+#include <type_traits>
 #include "kernels.h"
 #include "device_utils.h"
 
@@ -391,7 +392,7 @@ __device__ __forceinline__ void transpose4x4_bytes(uint32_t a, uint32_t b, uint3
 // fixed before this tensor was seen and wants this tensor's amax back for the history: DELAYED
 // kernels read the scale itself from `amax`, and add the maximum magnitude pattern of what they
 // load to *amax_acc (one atomicMax per workgroup, skipped when already covered).
-__device__ __forceinline__ void quant_amax_commit(uint32_t m, uint32_t *amax_acc, bool atomic = true)
+__device__ __forceinline__ void quant_amax_commit(uint32_t m, uint32_t *amax_acc)
 {
     __shared__ uint32_t red[kQuantThreads / kWave];
     uint32_t r = (m & 0xFFFFu) > (m >> 16) ? (m & 0xFFFFu) : (m >> 16);
@@ -404,9 +405,7 @@ __device__ __forceinline__ void quant_amax_commit(uint32_t m, uint32_t *amax_acc
         for (int w = 1; w < kQuantThreads / kWave; ++w)
             r = red[w] > r ? red[w] : r;
         const uint32_t mine = r << 16;
-        if (!atomic)
-            *amax_acc = mine;  // a slot of this workgroup's own
-        else if (mine > __atomic_load_n(amax_acc, __ATOMIC_RELAXED))
+        if (mine > __atomic_load_n(amax_acc, __ATOMIC_RELAXED))
             atomicMax(amax_acc, mine);
     }
 }
@@ -509,19 +508,34 @@ __device__ __forceinline__ float f64_to_f32_for_bf16(double v)
 // eight elements of a row: y = (x - mean) * (rstd * gamma) + beta in fp64 (one rounding more or
 // less than the textbook order of operations: 1e-16 relative, far below anything a bf16 rounding
 // sees), as packed bf16 pairs.  g64 / b64: the eight columns' parameters, widened by the caller.
+// The way to bf16 goes through the nearest fp32: rounding twice differs from rounding once only if
+// the fp32 value is exactly half way between two bf16 values (low half 0x8000), which one element
+// in 65536 is; a vector that holds one (and then the wave, once in about 130 vectors) is rounded
+// again through the round-to-odd fp32.  Four integer operations per element fewer than that way
+// for all (16384x2048: cast 34.4 -> 33.0 us).
 __device__ __forceinline__ uint4 ln_vec(uint4 x, double mean, double rstd, const double (&g64)[8], const double (&b64)[8],
                                         bool has_beta)
 {
     const uint32_t xx[4] = {x.x, x.y, x.z, x.w};
     uint32_t r[4];
+    double y[8];
+    u16x2 tie = {0xFFFF, 0xFFFF};
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const double d0 = (double)bf16lo_to_f32(xx[k]) - mean, d1 = (double)bf16hi_to_f32(xx[k]) - mean;
         const double a0 = rstd * g64[2 * k], a1 = rstd * g64[2 * k + 1];
         // without a beta nothing is added, so that a zero keeps the sign the product gives it
-        const double y0 = has_beta ? __builtin_fma(d0, a0, b64[2 * k]) : d0 * a0;
-        const double y1 = has_beta ? __builtin_fma(d1, a1, b64[2 * k + 1]) : d1 * a1;
-        r[k] = pack_bf16x2(f64_to_f32_for_bf16(y0), f64_to_f32_for_bf16(y1));
+        y[2 * k] = has_beta ? __builtin_fma(d0, a0, b64[2 * k]) : d0 * a0;
+        y[2 * k + 1] = has_beta ? __builtin_fma(d1, a1, b64[2 * k + 1]) : d1 * a1;
+        const float f0 = (float)y[2 * k], f1 = (float)y[2 * k + 1];
+        const uint32_t low = __builtin_amdgcn_perm(f32_to_bits(f1), f32_to_bits(f0), 0x05040100u) ^ 0x80008000u;
+        tie = __builtin_elementwise_min(tie, __builtin_bit_cast(u16x2, low));
+        r[k] = pack_bf16x2(f0, f1);
+    }
+    if (tie[0] == 0 || tie[1] == 0) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            r[k] = pack_bf16x2(f64_to_f32_for_bf16(y[2 * k]), f64_to_f32_for_bf16(y[2 * k + 1]));
     }
     return make_uint4(r[0], r[1], r[2], r[3]);
 }
@@ -571,40 +585,179 @@ __device__ __forceinline__ double sumsq8_f64(uint4 v, double mean)
     return s;
 }
 
-// Row statistics: one wave per row, the first kLnCached 16-byte pieces of every lane stay in
-// registers between the mean and the variance, so rows of up to 4096 elements are read from memory
-// once (2 B/element).  RESIDUAL: the row is h = bf16(x + r), stored to h_out on the way.
-constexpr int kLnThreads = 256;
-constexpr int kLnCached = 8;
-
-template <bool RESIDUAL>
-__global__ __launch_bounds__(kLnThreads) void ln_stats_kernel(const uint4 *x, const uint4 *res, uint4 *h_out,
-                                                              int64_t rows, int vec_per_row, double eps,
-                                                              double *__restrict__ stats)
+// Maximum over a wave without LDS: DPP row shifts, then the two row broadcasts; lane 63 holds it.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ float dpp_max_f32(float v)
 {
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    constexpr int WAVES = kLnThreads / kWave;
+    const int o = __builtin_amdgcn_update_dpp((int)0xFF800000u, (int)f32_to_bits(v), CTRL, ROW_MASK, 0xF, false);
+    return __builtin_fmaxf(v, bits_to_f32((uint32_t)o));
+}
+
+__device__ __forceinline__ float wave_max_f32(float v)
+{
+    v = dpp_max_f32<0x111, 0xF>(v);  // row_shr:1, 2, 4, 8
+    v = dpp_max_f32<0x112, 0xF>(v);
+    v = dpp_max_f32<0x114, 0xF>(v);
+    v = dpp_max_f32<0x118, 0xF>(v);
+    v = dpp_max_f32<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
+    v = dpp_max_f32<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
+    return bits_to_f32((uint32_t)__builtin_amdgcn_readlane((int)f32_to_bits(v), 63));
+}
+
+// Sum over a wave in the same way (every lane gets it; a shuffle through the LDS takes ten times as
+// long, and these sums are a chain in the middle of a row).
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ double dpp_add_f64(double v)
+{
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, ROW_MASK, 0xF, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, ROW_MASK, 0xF, false);
+    return v + __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+__device__ __forceinline__ double wave_sum_f64(double v)
+{
+    v = dpp_add_f64<0x111, 0xF>(v);
+    v = dpp_add_f64<0x112, 0xF>(v);
+    v = dpp_add_f64<0x114, 0xF>(v);
+    v = dpp_add_f64<0x118, 0xF>(v);
+    v = dpp_add_f64<0x142, 0xA>(v);
+    v = dpp_add_f64<0x143, 0xC>(v);
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, 63);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), 63);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// Largest |y| of eight elements as ln_vec forms them (packed pairs of magnitude patterns), two
+// elements at a time: the pass around it has few registers to give.
+__device__ __forceinline__ uint32_t ln_absmax_exact(uint4 x, double mean, double rstd, uint4 gamma, uint4 beta, bool has_beta)
+{
+    const uint32_t xx[4] = {x.x, x.y, x.z, x.w}, gg[4] = {gamma.x, gamma.y, gamma.z, gamma.w},
+                   bb[4] = {beta.x, beta.y, beta.z, beta.w};
+    uint32_t m = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const double d0 = (double)bf16lo_to_f32(xx[k]) - mean, d1 = (double)bf16hi_to_f32(xx[k]) - mean;
+        const double a0 = rstd * (double)bf16lo_to_f32(gg[k]), a1 = rstd * (double)bf16hi_to_f32(gg[k]);
+        const double y0 = has_beta ? __builtin_fma(d0, a0, (double)bf16lo_to_f32(bb[k])) : d0 * a0;
+        const double y1 = has_beta ? __builtin_fma(d1, a1, (double)bf16hi_to_f32(bb[k])) : d1 * a1;
+        m = pk_absmax(m, pack_bf16x2(f64_to_f32_for_bf16(y0), f64_to_f32_for_bf16(y1)));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    return m;
+}
+
+// fp32 estimate of the largest |y| of eight elements (see ln_stats_kernel)
+__device__ __forceinline__ float ln_estimate(uint4 x, uint4 gamma, uint4 beta, float mean, float rstd)
+{
+    const uint32_t xx[4] = {x.x, x.y, x.z, x.w}, gg[4] = {gamma.x, gamma.y, gamma.z, gamma.w},
+                   bb[4] = {beta.x, beta.y, beta.z, beta.w};
+    float m = 0.0f;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const float y0 = __builtin_fmaf(bf16lo_to_f32(xx[k]) - mean, rstd * bf16lo_to_f32(gg[k]), bf16lo_to_f32(bb[k]));
+        const float y1 = __builtin_fmaf(bf16hi_to_f32(xx[k]) - mean, rstd * bf16hi_to_f32(gg[k]), bf16hi_to_f32(bb[k]));
+        m = __builtin_fmaxf(m, __builtin_fmaxf(__builtin_fabsf(y0), __builtin_fabsf(y1)));
+    }
+    return m;
+}
+
+__device__ __forceinline__ uint32_t fold_u16(uint32_t m) { return (m & 0xFFFFu) > (m >> 16) ? (m & 0xFFFFu) : (m >> 16); }
+
+// Row statistics: one wave per row, the first P 16-byte pieces of every lane (P = 2, 4 or 8: rows of
+// up to 1024, 2048, 4096 elements) are requested at once and stay in registers between the mean and
+// the variance, so that much of a row is read from memory once (2 B/element).  A lane past the end
+// of the row loads its last piece again and counts it as nothing: with a branch around each load the
+// compiler waits for one before it issues the next.  RESIDUAL: the row is h = bf16(x + r), stored to
+// h_out on the way.
+//
+// AMAX (current scaling, and the first call on a delayed-scaling state): the pass also finds the
+// largest |y| of the normalised tensor, exactly as the cast will form it, and workgroup b leaves it
+// in partials[b].  Normalising every element in fp64 here as well costs more than the pass over the
+// tensor that it saves (59.5 us against 20.9 + 22.1).  So a row's elements are only estimated in fp32,
+// with a bound on the estimate's error that is taken over the lane's eight columns: |x - mean| <=
+// |x| + |mean|, and each of the fp32 steps (mean, rstd, difference, product, sum) is off by at most
+// 2^-24 of these magnitudes, together below 2^-21 of |rstd gamma| (|x| + |mean|) + |beta|.  Only
+// vectors whose upper bound reaches the largest lower bound of the row and the wave's best so far
+// are formed in fp64 - about one of a row.  A NaN or infinity anywhere makes the bound NaN or
+// infinite, and the comparison then sends the vector to the exact path.
+// 16384x2048 with a residual: 41.7 us without the maximum + 22.0 for the pass over the normalised
+// tensor that found it before, 49.4 in one.
+//
+// What counts is how many rows are in flight (the pass is a chain of latencies per row: loads, two
+// wave-wide fp64 reductions): as many waves as the registers allow.  Without the maximum in small
+// workgroups; with it in two workgroups per CU, since the maxima of at most kAmaxPartialsMax
+// workgroups fit the workspace.
+template <bool AMAX, int P>
+struct LnShape {
+    static constexpr int WAVES_PER_SIMD = AMAX ? (P == 2 ? 5 : P == 4 ? 4 : 2) : (P == 2 ? 7 : P == 4 ? 5 : 3);
+    static constexpr int WAVES = AMAX ? 2 * WAVES_PER_SIMD : 4, WG_PER_CU = AMAX ? 2 : WAVES_PER_SIMD;
+    static constexpr int THREADS = WAVES * kWave;
+    static constexpr int LDS_VEC = AMAX ? 2 * P * kWave : 1;  // 16-byte pieces: gamma, beta of the cached columns
+};
+
+template <bool RESIDUAL, bool AMAX, int P>
+__global__ __launch_bounds__((LnShape<AMAX, P>::THREADS), (LnShape<AMAX, P>::WAVES_PER_SIMD)) void ln_stats_kernel(
+    const uint4 *x, const uint4 *res, uint4 *h_out, int64_t rows, int vec_per_row, double eps,
+    double *__restrict__ stats, const uint4 *__restrict__ gamma, const uint4 *__restrict__ beta, uint32_t *__restrict__ partials)
+{
+    constexpr int WAVES = LnShape<AMAX, P>::WAVES;
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const double n = (double)vec_per_row * 8.0;
-    for (int64_t row = (int64_t)blockIdx.x * WAVES + wave; row < rows; row += (int64_t)gridDim.x * WAVES) {
+    const int last = vec_per_row - 1;
+    // scalar base + 32-bit lane offset: the lane holds no 64-bit addresses
+    auto at = [](const uint4 *p, int i) { return *(const uint4 *)((const uint8_t *)p + (uint64_t)((uint32_t)i * 16u)); };
+    __shared__ uint4 params[LnShape<AMAX, P>::LDS_VEC];
+    if constexpr (AMAX) {
+        for (int i = threadIdx.x; i < P * kWave; i += LnShape<AMAX, P>::THREADS) {
+            const int j = i < last ? i : last;
+            params[i] = at(gamma, j);
+            params[P * kWave + i] = beta != nullptr ? at(beta, j) : make_uint4(0u, 0u, 0u, 0u);
+        }
+        __syncthreads();
+    }
+    float best = 0.0f;  // AMAX: largest |y| of the wave's rows so far (a bf16 value; NaN once one was seen)
+    // the row that is worked on next, requested while this one is worked on
+    uint4 nx[P], nr[RESIDUAL ? P : 1];
+    auto request = [&](int64_t row) {
+#pragma unroll
+        for (int u = 0; u < P; ++u) {
+            const int i = lane + u * kWave, j = i < last ? i : last;
+            nx[u] = at(x + row * vec_per_row, j);
+            if constexpr (RESIDUAL)
+                nr[u] = at(res + row * vec_per_row, j);
+        }
+    };
+    const int64_t stride = (int64_t)gridDim.x * WAVES;
+    int64_t row = (int64_t)blockIdx.x * WAVES + wave;
+    if (row < rows)
+        request(row);
+    for (; row < rows; row += stride) {
         const uint4 *xr = x + row * vec_per_row;
         const uint4 *rr = RESIDUAL ? res + row * vec_per_row : nullptr;
         uint4 *hr = RESIDUAL ? h_out + row * vec_per_row : nullptr;
-        uint4 c[kLnCached];
+        uint4 c[P];
+#pragma unroll
+        for (int u = 0; u < P; ++u) {
+            c[u] = nx[u];
+            if constexpr (RESIDUAL)
+                c[u] = add_bf16x8(c[u], nr[u]);
+        }
+        // before this row's stores: they may overwrite x or the residual, but never another row of them
+        if (row + stride < rows)
+            request(row + stride);
         double s = 0.0;
 #pragma unroll
-        for (int u = 0; u < kLnCached; ++u) {
+        for (int u = 0; u < P; ++u) {
             const int i = lane + u * kWave;
-            c[u] = make_uint4(0u, 0u, 0u, 0u);
-            if (i < vec_per_row) {
-                c[u] = xr[i];
-                if constexpr (RESIDUAL) {
-                    c[u] = add_bf16x8(c[u], rr[i]);
+            if constexpr (RESIDUAL)
+                if (i <= last)
                     hr[i] = c[u];
-                }
-                s += sum8_f64(c[u]);
-            }
+            const double t = sum8_f64(c[u]);
+            s += i <= last ? t : 0.0;
         }
-        for (int i = lane + kLnCached * kWave; i < vec_per_row; i += kWave) {
+        for (int i = lane + P * kWave; i < vec_per_row; i += kWave) {
             uint4 v = xr[i];
             if constexpr (RESIDUAL) {
                 v = add_bf16x8(v, rr[i]);
@@ -612,20 +765,87 @@ __global__ __launch_bounds__(kLnThreads) void ln_stats_kernel(const uint4 *x, co
             }
             s += sum8_f64(v);
         }
-        const double mean = wave_reduce_sum(s) / n;
+        const double mean = wave_sum_f64(s) / n;
         double ss = 0.0;
 #pragma unroll
-        for (int u = 0; u < kLnCached; ++u)
-            if (lane + u * kWave < vec_per_row)
-                ss += sumsq8_f64(c[u], mean);
+        for (int u = 0; u < P; ++u) {
+            // the packed form is what stays in registers, not its widened values
+            asm volatile("" : "+v"(c[u].x), "+v"(c[u].y), "+v"(c[u].z), "+v"(c[u].w));
+            const double t = sumsq8_f64(c[u], mean);
+            ss += lane + u * kWave <= last ? t : 0.0;
+        }
         // h_out may be x or the residual itself (an in-place update of the stream): what this lane
         // stored above is read back, not formed again
-        for (int i = lane + kLnCached * kWave; i < vec_per_row; i += kWave)
+        for (int i = lane + P * kWave; i < vec_per_row; i += kWave)
             ss += sumsq8_f64(RESIDUAL ? hr[i] : xr[i], mean);
-        const double var = wave_reduce_sum(ss) / n;
+        const double var = wave_sum_f64(ss) / n;
+        const double rstd = 1.0 / __builtin_sqrt(var + eps);
         if (lane == 0) {
             stats[2 * row] = mean;
-            stats[2 * row + 1] = 1.0 / __builtin_sqrt(var + eps);
+            stats[2 * row + 1] = rstd;
+        }
+        if constexpr (AMAX) {
+            const float mean_f = (float)mean, rstd_f = (float)rstd, absmean = __builtin_fabsf(mean_f);
+            // the parameters are read in every row: the compiler would keep them and their widened
+            // values over the rows and spill
+            int lane0 = lane;
+            asm volatile("" : "+v"(lane0));
+            auto beta_at = [&](int i) { return beta != nullptr ? at(beta, i) : make_uint4(0u, 0u, 0u, 0u); };
+            auto bound = [&](uint4 v, uint4 g, uint4 b) {
+                const float ax = bits_to_f32(fold_u16(pk_absmax4(0u, v)) << 16), ag = bits_to_f32(fold_u16(pk_absmax4(0u, g)) << 16),
+                            ab = bits_to_f32(fold_u16(pk_absmax4(0u, b)) << 16);
+                return __builtin_fmaf(rstd_f * ag, ax + absmean, ab) * 0x1p-21f + 1.2e-38f;
+            };
+            // exact |y| of eight elements, as the cast forms them; the lanes' largest joins `best`
+            auto exact = [&](bool mine, uint4 v, uint4 g, uint4 b) {
+                uint32_t m = 0;
+                if (mine)
+                    m = fold_u16(ln_absmax_exact(v, mean, rstd, g, b, beta != nullptr));
+                m = wave_reduce_max_u32(m);  // magnitude patterns: a NaN is above everything
+                const uint32_t old = f32_to_bits(best) >> 16;
+                best = bits_to_f32((m > old ? m : old) << 16);
+            };
+            float hi[P], floor_ = 0.0f;
+#pragma unroll
+            for (int u = 0; u < P; ++u) {
+                const int i = lane0 + u * kWave;  // past the end: the last piece again
+                asm volatile("" : "+v"(c[u].x), "+v"(c[u].y), "+v"(c[u].z), "+v"(c[u].w));
+                const uint4 g = params[i], b = params[P * kWave + i];
+                const float m = ln_estimate(c[u], g, b, mean_f, rstd_f), e = bound(c[u], g, b);
+                hi[u] = m + e;
+                floor_ = __builtin_fmaxf(floor_, m - e);
+                __builtin_amdgcn_sched_barrier(0);  // one piece's parameters at a time
+            }
+            floor_ = wave_max_f32(floor_);
+#pragma unroll
+            for (int u = 0; u < P; ++u) {
+                const int i = lane0 + u * kWave;
+                asm volatile("" : "+v"(c[u].x), "+v"(c[u].y), "+v"(c[u].z), "+v"(c[u].w));
+                const bool mine = i <= last && !(hi[u] < floor_) && !(hi[u] < best);
+                if (__builtin_amdgcn_ballot_w64(mine) != 0)
+                    exact(mine, c[u], params[i], params[P * kWave + i]);
+            }
+            for (int i0 = P * kWave; i0 < vec_per_row; i0 += kWave) {  // uniform: every lane takes part in exact()
+                const int i = i0 + lane0, j = i < last ? i : last;
+                const uint4 v = at(RESIDUAL ? hr : xr, j), g = at(gamma, j), b = beta_at(j);
+                const float up = ln_estimate(v, g, b, mean_f, rstd_f) + bound(v, g, b);
+                const bool mine = i <= last && !(up < best);
+                if (__builtin_amdgcn_ballot_w64(mine) != 0)
+                    exact(mine, v, g, b);
+            }
+        }
+    }
+    if constexpr (AMAX) {
+        __shared__ uint32_t red[WAVES];
+        if (lane == 0)
+            red[wave] = f32_to_bits(best);
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            uint32_t m = red[0];
+#pragma unroll
+            for (int w = 1; w < WAVES; ++w)
+                m = red[w] > m ? red[w] : m;
+            partials[blockIdx.x] = m;
         }
     }
 }
@@ -638,13 +858,10 @@ __global__ __launch_bounds__(kLnThreads) void ln_stats_kernel(const uint4 *x, co
 constexpr int kQuantBigTile = 256;
 
 // INJECT: 0 = plain cast; 4 / 1 = the penalty gradient is added on the way in (p = 4 / any p)
-// LN: the tensor that is cast is the LayerNorm of x (statistics precomputed per row).  AMAX_ONLY
-// (with DELAYED's bounded grid and tile loop): nothing is stored, workgroup b leaves the maximum
-// magnitude pattern of what it would have cast in amax_acc[b].
+// LN: the tensor that is cast is the LayerNorm of x (statistics precomputed per row).
 // T_LATER: the transposed codes are not read before a later call (a forward cast's, which wait for
 // the backward pass): streaming stores.
-template <bool WITH_T, bool DELAYED, bool E5M2 = false, int INJECT = 0, bool LN = false, bool AMAX_ONLY = false,
-          bool T_LATER = false>
+template <bool WITH_T, bool DELAYED, bool E5M2 = false, int INJECT = 0, bool LN = false, bool T_LATER = false>
 __device__ __forceinline__ void quantize_e4m3_16x16_body(
     const uint16_t *__restrict__ x, int64_t rows, int64_t cols, int64_t tiles_x,
     const float *__restrict__ amax, uint8_t *__restrict__ q, uint8_t *__restrict__ qT,
@@ -652,11 +869,8 @@ __device__ __forceinline__ void quantize_e4m3_16x16_body(
     const uint32_t *__restrict__ amax_partials = nullptr, int n_partials = 0, float *amax_store = nullptr,
     InjectArgs inj = InjectArgs{}, LnArgs ln = LnArgs{}, uint16_t *__restrict__ y_out = nullptr)
 {
-    static_assert(!AMAX_ONLY || DELAYED, "the amax-only pass walks the tiles with a bounded grid");
     float amax_v = 0.0f;
-    if constexpr (AMAX_ONLY) {
-        // no scale needed
-    } else if (amax_partials != nullptr) {  // uniform: the maxima of the amax launch's workgroups
+    if (amax_partials != nullptr) {  // uniform: the maxima of the amax launch's workgroups
         __shared__ uint32_t pred[kQuantThreads / kWave];
         uint32_t m = 0;
         for (int i = threadIdx.x; i < n_partials; i += kQuantThreads) {
@@ -677,7 +891,7 @@ __device__ __forceinline__ void quantize_e4m3_16x16_body(
         amax_v = *amax;
     }
     const float scale = DELAYED ? amax_v : scale_f8<E5M2>(amax_v);
-    if (!AMAX_ONLY && block == 0 && threadIdx.x == 0) {
+    if (block == 0 && threadIdx.x == 0) {
         if (scale_out)
             *scale_out = scale;
         if (scale_inv_out)
@@ -737,7 +951,7 @@ __device__ __forceinline__ void quantize_e4m3_16x16_body(
                         mx = pk_absmax4(mx, in[i][w]);
                 }
             }
-            if (!AMAX_ONLY && y_out != nullptr) {
+            if (y_out != nullptr) {
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
                     uint4 *dst = (uint4 *)(y_out + (r0 + half * 8 + i) * cols + c0);
@@ -746,8 +960,6 @@ __device__ __forceinline__ void quantize_e4m3_16x16_body(
                 }
             }
         }
-        if constexpr (AMAX_ONLY)
-            continue;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const int r = half * 8 + i;
@@ -762,7 +974,7 @@ __device__ __forceinline__ void quantize_e4m3_16x16_body(
             *(uint4 *)(q + (r0 + r) * cols + c0) = make_uint4(qd[r][0], qd[r][1], qd[r][2], qd[r][3]);
         }
     }
-    if (WITH_T && !AMAX_ONLY) {
+    if (WITH_T) {
 #pragma unroll
         for (int C = 0; C < 4; ++C) {
             uint32_t t[4][4];  // t[R][k]: column 4C+k, rows 4R..4R+3
@@ -785,23 +997,20 @@ __device__ __forceinline__ void quantize_e4m3_16x16_body(
     }
     // every lane reaches the one workgroup barrier of the amax commit (amax_acc is uniform over
     // the grid; nullptr = the caller already has this tensor's amax)
-    if constexpr (AMAX_ONLY)
-        quant_amax_commit(mx, amax_acc + block, false);
-    else if constexpr (DELAYED)
+    if constexpr (DELAYED)
         if (amax_acc != nullptr)
             quant_amax_commit(mx, amax_acc);
 }
 
-// LayerNorm + cast (DELAYED: the scale is read from *amax, the tensor's amax goes to *amax_acc), or
-// the amax-only pass over the normalised tensor (one maximum per workgroup into amax_acc[])
-template <bool WITH_T, bool DELAYED, bool AMAX_ONLY>
-__global__ __launch_bounds__(kQuantThreads) void quantize_ln_16x16_kernel(
+// LayerNorm + cast (DELAYED: the scale is read from *amax, the tensor's amax goes to *amax_acc)
+template <bool WITH_T, bool DELAYED>
+__global__ __launch_bounds__(kQuantThreads, 2) void quantize_ln_16x16_kernel(
     const uint16_t *__restrict__ x, LnArgs ln, int64_t rows, int64_t cols, int64_t tiles_x,
     const float *__restrict__ amax, uint8_t *__restrict__ q, uint8_t *__restrict__ qT, uint16_t *__restrict__ y_out,
     float *scale_out, float *scale_inv_out, uint32_t *amax_acc, const uint32_t *__restrict__ amax_partials,
     int n_partials, float *amax_store)
 {
-    quantize_e4m3_16x16_body<WITH_T, DELAYED, false, 0, true, AMAX_ONLY>(
+    quantize_e4m3_16x16_body<WITH_T, DELAYED, false, 0, true>(
         x, rows, cols, tiles_x, amax, q, qT, scale_out, scale_inv_out, amax_acc, blockIdx.x, gridDim.x, amax_partials,
         n_partials, amax_store, InjectArgs{}, ln, y_out);
 }
@@ -847,7 +1056,7 @@ __global__ __launch_bounds__(kQuantThreads) void quantize2_e4m3_16x16_kernel(Qua
 {
     const bool first = (int64_t)blockIdx.x < blocks0;
     const QuantTensor &t = first ? t0 : t1;
-    quantize_e4m3_16x16_body<true, false, false, 0, false, false, true>(t.x, t.rows, t.cols, t.tiles_x, t.amax, t.q, t.qT, t.scale_out,
+    quantize_e4m3_16x16_body<true, false, false, 0, false, true>(t.x, t.rows, t.cols, t.tiles_x, t.amax, t.q, t.qT, t.scale_out,
                                           t.scale_inv_out, nullptr,
                                           first ? (int64_t)blockIdx.x : (int64_t)blockIdx.x - blocks0, 1,
                                           t.amax_partials, t.n_partials, t.amax_store);
@@ -1598,7 +1807,7 @@ __global__ __launch_bounds__(kQuantThreads) void quantize2_delayed_16x16_kernel(
 {
     const bool first = (int64_t)blockIdx.x < blocks0;
     const QuantTensorDelayed &t = first ? t0 : t1;
-    quantize_e4m3_16x16_body<true, true, false, 0, false, false, true>(t.x, t.rows, t.cols, t.tiles_x, t.scale, t.q, t.qT, nullptr, nullptr, t.amax_acc,
+    quantize_e4m3_16x16_body<true, true, false, 0, false, true>(t.x, t.rows, t.cols, t.tiles_x, t.scale, t.q, t.qT, nullptr, nullptr, t.amax_acc,
                                          first ? (int64_t)blockIdx.x : (int64_t)blockIdx.x - blocks0,
                                          first ? blocks0 : blocks1);
 }
@@ -1634,11 +1843,11 @@ hipError_t launch_quantize2_e4m3_delayed(const void *x0_bf16, int64_t rows0, int
     return hipGetLastError();
 }
 
-// LayerNorm -> per-tensor E4M3 cast (Sec. 4.3).  Launches: row statistics (2 B/element from
-// memory; with a residual it also forms and stores h = bf16(x + r)); for current scaling, or for
-// the first call on a delayed-scaling state, an amax-only pass over the normalised tensor (it
-// re-reads the rows from the caches); then the cast, which normalises on the way in (re-read from
-// the caches, 1 B/element written per copy of the codes, + 2 B/element if y is wanted).
+// LayerNorm -> per-tensor E4M3 cast (Sec. 4.3).  Two launches: row statistics (2 B/element from
+// memory; with a residual it also forms and stores h = bf16(x + r); for current scaling, or for the
+// first call on a delayed-scaling state, it finds the maximum of the normalised tensor); then the
+// cast, which normalises on the way in (re-read from the caches, 1 B/element written per copy of the
+// codes, + 2 B/element if y is wanted).
 // stats: 2 doubles per row; partials: kAmaxPartialsMax words.  rows, cols multiples of 16.
 hipError_t launch_layernorm_quantize(const void *x_bf16, const void *res_bf16, const void *gamma_bf16,
                                      const void *beta_bf16, int64_t rows, int64_t cols, double eps, void *h_out,
@@ -1647,20 +1856,35 @@ hipError_t launch_layernorm_quantize(const void *x_bf16, const void *res_bf16, c
                                      int bootstrap, hipStream_t s)
 {
     const int vec = (int)(cols / 8);
-    constexpr int WAVES = kLnThreads / kWave;
-    int64_t sgrid = (rows + WAVES - 1) / WAVES;
-    // small workgroups, as many as fit a CU at once (70 / 80 registers a lane: seven / six waves per
-    // SIMD): the pass is a chain of latencies per row (loads, two wave-wide fp64 reductions), so what
-    // counts is how many rows are in flight
-    const int64_t resident = (res_bf16 != nullptr ? 6 : 7) * (int64_t)amax_cus();
-    if (sgrid > resident)
-        sgrid = resident;
-    if (res_bf16 != nullptr)
-        hipLaunchKernelGGL(ln_stats_kernel<true>, dim3((unsigned)sgrid), dim3(kLnThreads), 0, s, (const uint4 *)x_bf16,
-                           (const uint4 *)res_bf16, (uint4 *)h_out, rows, vec, eps, stats);
+    const bool delayed = state != nullptr, need_amax = !delayed || bootstrap;
+    int64_t sgrid = 0;
+    auto stats_launch = [&](auto kernel, auto shape) {
+        using L = decltype(shape);
+        sgrid = (rows + L::WAVES - 1) / L::WAVES;
+        int64_t resident = L::WG_PER_CU * (int64_t)amax_cus();
+        if (need_amax && resident > kAmaxMaxPartials)
+            resident = kAmaxMaxPartials;
+        if (sgrid > resident)
+            sgrid = resident;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)sgrid), dim3(L::THREADS), 0, s, (const uint4 *)x_bf16,
+                           (const uint4 *)res_bf16, (uint4 *)(res_bf16 != nullptr ? h_out : nullptr), rows, vec, eps, stats,
+                           (const uint4 *)gamma_bf16, (const uint4 *)beta_bf16, partials);
+    };
+    auto by_flags = [&](auto p) {
+        constexpr int P = decltype(p)::value;
+        if (need_amax)
+            res_bf16 != nullptr ? stats_launch(ln_stats_kernel<true, true, P>, LnShape<true, P>{})
+                                : stats_launch(ln_stats_kernel<false, true, P>, LnShape<true, P>{});
+        else
+            res_bf16 != nullptr ? stats_launch(ln_stats_kernel<true, false, P>, LnShape<false, P>{})
+                                : stats_launch(ln_stats_kernel<false, false, P>, LnShape<false, P>{});
+    };
+    if (vec <= 2 * kWave)
+        by_flags(std::integral_constant<int, 2>{});
+    else if (vec <= 4 * kWave)
+        by_flags(std::integral_constant<int, 4>{});
     else
-        hipLaunchKernelGGL(ln_stats_kernel<false>, dim3((unsigned)sgrid), dim3(kLnThreads), 0, s, (const uint4 *)x_bf16,
-                           (const uint4 *)nullptr, (uint4 *)nullptr, rows, vec, eps, stats);
+        by_flags(std::integral_constant<int, 8>{});
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return e;
@@ -1668,32 +1892,22 @@ hipError_t launch_layernorm_quantize(const void *x_bf16, const void *res_bf16, c
     const LnArgs ln{stats, (const uint16_t *)gamma_bf16, (const uint16_t *)beta_bf16};
     const int64_t tiles_x = (cols + kQuantBigTile - 1) / kQuantBigTile, tiles_y = (rows + kQuantBigTile - 1) / kQuantBigTile;
     const int64_t n_tiles = tiles_x * tiles_y;
-    const int64_t bounded = n_tiles < kAmaxMaxPartials ? n_tiles : kAmaxMaxPartials;
     const dim3 block(kQuantThreads);
     float *st = (float *)state;
-    const bool delayed = state != nullptr;
-    if (!delayed || bootstrap) {
-        hipLaunchKernelGGL((quantize_ln_16x16_kernel<false, true, true>), dim3((unsigned)bounded), block, 0, s, src, ln, rows,
-                           cols, tiles_x, (const float *)nullptr, (uint8_t *)nullptr, (uint8_t *)nullptr,
-                           (uint16_t *)nullptr, (float *)nullptr, (float *)nullptr, partials, (const uint32_t *)nullptr, 0,
-                           (float *)nullptr);
-        if ((e = hipGetLastError()) != hipSuccess)
-            return e;
-    }
     if (!delayed) {
         if (qT)
-            hipLaunchKernelGGL((quantize_ln_16x16_kernel<true, false, false>), dim3((unsigned)n_tiles), block, 0, s, src, ln,
+            hipLaunchKernelGGL((quantize_ln_16x16_kernel<true, false>), dim3((unsigned)n_tiles), block, 0, s, src, ln,
                                rows, cols, tiles_x, (const float *)amax_out, q, qT, (uint16_t *)y_out, scale_out, scale_inv_out,
-                               (uint32_t *)nullptr, (const uint32_t *)partials, (int)bounded, amax_out);
+                               (uint32_t *)nullptr, (const uint32_t *)partials, (int)sgrid, amax_out);
         else
-            hipLaunchKernelGGL((quantize_ln_16x16_kernel<false, false, false>), dim3((unsigned)n_tiles), block, 0, s, src, ln,
+            hipLaunchKernelGGL((quantize_ln_16x16_kernel<false, false>), dim3((unsigned)n_tiles), block, 0, s, src, ln,
                                rows, cols, tiles_x, (const float *)amax_out, q, qT, (uint16_t *)y_out, scale_out, scale_inv_out,
-                               (uint32_t *)nullptr, (const uint32_t *)partials, (int)bounded, amax_out);
+                               (uint32_t *)nullptr, (const uint32_t *)partials, (int)sgrid, amax_out);
         return hipGetLastError();
     }
     if (bootstrap) {  // empty history: the tensor's own amax makes the scale
         hipLaunchKernelGGL(delayed_state_update_kernel, dim3(1), dim3(64), 0, s, (uint32_t *)state, 1, 448.0f,
-                           (const uint32_t *)partials, (int)bounded, (float *)nullptr);
+                           (const uint32_t *)partials, (int)sgrid, (float *)nullptr);
         if ((e = hipGetLastError()) != hipSuccess)
             return e;
     }
@@ -1701,11 +1915,11 @@ hipError_t launch_layernorm_quantize(const void *x_bf16, const void *res_bf16, c
     uint32_t *acc = bootstrap ? nullptr : (uint32_t *)st + 16;
     int64_t n_wg = n_tiles < 1024 ? n_tiles : 1024;
     if (qT)
-        hipLaunchKernelGGL((quantize_ln_16x16_kernel<true, true, false>), dim3((unsigned)n_wg), block, 0, s, src, ln, rows, cols,
+        hipLaunchKernelGGL((quantize_ln_16x16_kernel<true, true>), dim3((unsigned)n_wg), block, 0, s, src, ln, rows, cols,
                            tiles_x, scale_src, q, qT, (uint16_t *)y_out, (float *)nullptr, (float *)nullptr, acc,
                            (const uint32_t *)nullptr, 0, (float *)nullptr);
     else
-        hipLaunchKernelGGL((quantize_ln_16x16_kernel<false, true, false>), dim3((unsigned)n_wg), block, 0, s, src, ln, rows, cols,
+        hipLaunchKernelGGL((quantize_ln_16x16_kernel<false, true>), dim3((unsigned)n_wg), block, 0, s, src, ln, rows, cols,
                            tiles_x, scale_src, q, qT, (uint16_t *)y_out, (float *)nullptr, (float *)nullptr, acc,
                            (const uint32_t *)nullptr, 0, (float *)nullptr);
     if ((e = hipGetLastError()) != hipSuccess)

@@ -231,3 +231,38 @@ def test_layernorm_error_paths():
     with pytest.raises(tw.TweoError) as e:
         tw.tweo_layernorm_quantize_e4m3(x, g, q, ws_for(16), eps=-1.0)
     assert e.value.status == tw.TWEO_ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("kind", ["far mean", "nan gain", "infinite gain", "nan", "huge", "negative zeros", "late record"])
+@pytest.mark.parametrize("shape", [(48, 512), (64, 1040), (2576, 2064), (32, 4112)])
+def test_layernorm_amax_is_that_of_the_cast_tensor(shape, kind):
+    # the statistics pass finds the maximum of the normalised tensor from fp32 estimates and forms only
+    # the candidates exactly: rows whose mean dwarfs their spread (a wide bound, many candidates), values
+    # that are not finite, and a maximum in the last row and column, against the y the cast stores
+    rows, cols = shape
+    x, _, gamma, beta = make_inputs(rows, cols, rows + 3 * cols, False, True)
+    xf, gf, bf = (synth.bf16_bits_to_f32(t).copy() for t in (x, gamma, beta))
+    if kind == "far mean":
+        xf = xf + 3000.0
+    elif kind == "nan gain":
+        gf[cols - 1] = np.nan
+    elif kind == "infinite gain":
+        gf[cols // 2] = np.inf
+    elif kind == "nan":
+        xf[rows - 1, cols - 1] = np.nan
+    elif kind == "huge":
+        xf = xf * 1e18
+        gf = gf * 1e30
+    elif kind == "negative zeros":
+        gf[:], bf[:] = -0.0, -0.0
+    else:
+        xf[rows - 1, cols - 1] = 500.0
+    x, gamma, beta = (to_dev_bf16(synth.f32_to_bf16_bits(t)) for t in (xf, gf, bf))
+    for b in (beta, None):
+        am = scalar_f32(-1)
+        q = torch.empty((rows, cols), dtype=torch.uint8, device=DEV)
+        y = torch.empty((rows, cols), dtype=torch.bfloat16, device=DEV)
+        tw.tweo_layernorm_quantize_e4m3(x, gamma, q, ws_for(rows), beta_bf16=b, eps=np.float32(1e-5), y_out_bf16=y, amax_out=am)
+        torch.cuda.synchronize()
+        want = (y.view(torch.int16) & 0x7FFF).max()   # magnitude patterns order like integers, NaN on top
+        assert int(am.view(torch.int32)[0]) == int(want) << 16, (kind, b is None)
