@@ -95,6 +95,9 @@ __device__ __forceinline__ uint4 inject_vec(uint4 d, uint4 a, const InjectArgs &
 // eight 16-byte loads in flight per lane (measured: ~30 % more bandwidth than a
 // grid-stride walk, whose concurrent streams are megabytes apart).
 constexpr int kAmaxUnroll = 8;
+// Smallest share of a workgroup, in 16-byte pieces (32 KB).  With 128 KB, one unrolled trip, a 12 MB
+// tensor had 96 workgroups on 256 CUs (5.6 us, now 5.2).
+constexpr int kAmaxMinChunk = 2 * kAmaxThreads;
 constexpr int kAmaxMaxPartials = kAmaxPartialsMax;  // workgroups of one amax launch (one per CU)
 
 // PARTIAL: workgroup b stores its maximum to out[b] (no atomic, nothing to clear beforehand);
@@ -118,8 +121,16 @@ __device__ __forceinline__ void amax_body(const uint4 *__restrict__ x, int64_t n
         for (int u = 0; u < kAmaxUnroll; ++u)
             m = pk_absmax4(m, v[u]);
     }
-    for (; i < b1; i += kAmaxThreads)
-        m = pk_absmax4(m, x[i]);
+    // the rest, four loads at a time; a place past the end stands for the last one (a maximum does not mind)
+    for (; i < b1; i += 4 * kAmaxThreads) {
+        uint4 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            v[u] = x[i + u * kAmaxThreads < b1 ? i + u * kAmaxThreads : b1 - 1];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            m = pk_absmax4(m, v[u]);
+    }
     if (block == 0 && (int)threadIdx.x < n_tail)
         m = pk_absmax(m, tail[threadIdx.x]);
     uint32_t r = (m & 0xFFFFu) > (m >> 16) ? (m & 0xFFFFu) : (m >> 16);
@@ -228,7 +239,7 @@ static hipError_t launch_amax2_impl(const void *x0_bf16, int64_t n0, float *amax
     // the workgroups of one wave over the CUs are shared out in proportion to the tensor sizes
     const int cus = amax_cus();
     const int64_t v0 = n0 / 8, v1 = n1 / 8;
-    const int64_t chunk = kAmaxUnroll * kAmaxThreads;
+    const int64_t chunk = kAmaxMinChunk;
     int64_t b1 = (int64_t)((double)cus * (double)v1 / (double)(v0 + v1) + 0.5);
     if (b1 < 1)
         b1 = 1;
@@ -274,9 +285,9 @@ static hipError_t launch_amax_impl(const void *x_bf16, int64_t n, float *amax_ze
 {
     const int64_t n_vec = n / 8;
     const int n_tail = (int)(n % 8);
-    // chunks of at least 128 KB (one unrolled trip), at most one workgroup per CU
+    // at most one workgroup per CU
     const int cus = amax_cus();
-    int64_t blocks = n_vec / (kAmaxUnroll * kAmaxThreads);
+    int64_t blocks = n_vec / kAmaxMinChunk;
     if (blocks < 1)
         blocks = 1;
     if (blocks > cus)
@@ -850,150 +861,147 @@ __global__ __launch_bounds__((LnShape<AMAX, P>::THREADS), (LnShape<AMAX, P>::WAV
     }
 }
 
-// Same cast for shapes with rows % 16 == 0 and cols % 16 == 0: a lane owns a
-// 16x16 block (two 16-byte loads per row), so q is written in 16-byte pieces
-// that 8 neighbouring lanes join into whole 128-byte lines, and - after sixteen
-// 4x4 byte transposes - qT likewise.  A wave covers 128x128 elements, a
-// workgroup 256x256.
-constexpr int kQuantBigTile = 256;
+// The cast of shapes with rows % 16 == 0 and cols % 16 == 0.  A workgroup owns a 128x128 tile, a lane
+// 8 rows x 8 columns of it: 16-byte loads of which 16 neighbouring lanes cover 256 bytes of a row,
+// 8-byte stores of q that join into whole 128-byte lines.  For qT the lane transposes its block in
+// registers (v_perm_b32) and the tile passes through 16 KB of LDS, from where eight lanes store a
+// column's 128 bytes: whole lines again.  The 16-byte piece of an LDS column is XOR-swizzled with the
+// column's index in units of eight, which spreads the 8-byte writes of a wave over all banks.
+//
+// HBM-bound on large tensors, latency-bound on small ones, so what counts is how much is in flight:
+// 64 elements a lane need few registers (five to six waves per SIMD).  The form before, 256x256 tiles
+// with 16x16 elements a lane and no LDS, ran two to four waves per SIMD (one under LayerNorm with
+// delayed scaling) and had 96 workgroups for an 8192x768 tensor: 13.0 us, now 7.7; 16384x5632 and
+// 2048x5632 under delayed scaling 91.4 us, now 74.0 (5.6 TB/s).
+constexpr int kTile = 128;
 
 // INJECT: 0 = plain cast; 4 / 1 = the penalty gradient is added on the way in (p = 4 / any p)
 // LN: the tensor that is cast is the LayerNorm of x (statistics precomputed per row).
 // T_LATER: the transposed codes are not read before a later call (a forward cast's, which wait for
 // the backward pass): streaming stores.
 template <bool WITH_T, bool DELAYED, bool E5M2 = false, int INJECT = 0, bool LN = false, bool T_LATER = false>
-__device__ __forceinline__ void quantize_e4m3_16x16_body(
+__device__ __forceinline__ void cast_tile_body(
     const uint16_t *__restrict__ x, int64_t rows, int64_t cols, int64_t tiles_x,
     const float *__restrict__ amax, uint8_t *__restrict__ q, uint8_t *__restrict__ qT,
     float *scale_out, float *scale_inv_out, uint32_t *amax_acc, int64_t block, int64_t n_blocks,
     const uint32_t *__restrict__ amax_partials = nullptr, int n_partials = 0, float *amax_store = nullptr,
     InjectArgs inj = InjectArgs{}, LnArgs ln = LnArgs{}, uint16_t *__restrict__ y_out = nullptr)
 {
-    float amax_v = 0.0f;
-    if (amax_partials != nullptr) {  // uniform: the maxima of the amax launch's workgroups
-        __shared__ uint32_t pred[kQuantThreads / kWave];
-        uint32_t m = 0;
-        for (int i = threadIdx.x; i < n_partials; i += kQuantThreads) {
-            const uint32_t v = amax_partials[i];
-            m = v > m ? v : m;
-        }
-        m = wave_reduce_max_u32(m);
-        if ((threadIdx.x & (kWave - 1)) == 0)
-            pred[threadIdx.x / kWave] = m;
-        __syncthreads();
-#pragma unroll
-        for (int w = 0; w < kQuantThreads / kWave; ++w)
-            m = pred[w] > m ? pred[w] : m;
-        amax_v = __uint_as_float(m);
-        if (block == 0 && threadIdx.x == 0)
-            *amax_store = amax_v;
-    } else {
-        amax_v = *amax;
-    }
-    const float scale = DELAYED ? amax_v : scale_f8<E5M2>(amax_v);
-    if (block == 0 && threadIdx.x == 0) {
-        if (scale_out)
-            *scale_out = scale;
-        if (scale_inv_out)
-            *scale_inv_out = 1.0f / scale;
-    }
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    __shared__ uint4 turned[WITH_T ? kTile * kTile / 16 : 1];
+    __shared__ uint32_t pred[kQuantThreads / kWave];
+    const int t = threadIdx.x, cg = t & 15, rg = t >> 4;
     uint32_t mx = 0;
+    float scale = 0.0f;
+    bool have_scale = false;
     // DELAYED: a bounded grid walks the tiles (its one atomic per workgroup is then a few hundred
     // per tensor, not thousands); otherwise one tile per workgroup
-    const int64_t n_tiles = DELAYED ? tiles_x * ((rows + kQuantBigTile - 1) / kQuantBigTile) : block + 1;
+    const int64_t n_tiles = DELAYED ? tiles_x * ((rows + kTile - 1) / kTile) : block + 1;
     for (int64_t tile = block; tile < n_tiles; tile += n_blocks) {
-    const int64_t by = tile / tiles_x, bx = tile % tiles_x;
-    const int64_t r0 = by * kQuantBigTile + (wave >> 1) * 128 + (lane >> 3) * 16;
-    const int64_t c0 = bx * kQuantBigTile + (wave & 1) * 128 + (lane & 7) * 16;
-    if (c0 >= cols || r0 >= rows)  // whole 16x16 blocks: in or out
-        continue;
-    uint32_t qd[16][4];
-    uint4 lg[2], lb[2];  // LN: gamma and beta of the lane's 16 columns
-    if constexpr (LN) {
-        lg[0] = ((const uint4 *)(ln.gamma + c0))[0];
-        lg[1] = ((const uint4 *)(ln.gamma + c0))[1];
-        lb[0] = lb[1] = make_uint4(0u, 0u, 0u, 0u);
-        if (ln.beta != nullptr) {
-            lb[0] = ((const uint4 *)(ln.beta + c0))[0];
-            lb[1] = ((const uint4 *)(ln.beta + c0))[1];
+        const int64_t by = tile / tiles_x, bx = tile % tiles_x;
+        const int64_t R = by * kTile, C = bx * kTile, r0 = R + rg * 8, c0 = C + cg * 8;
+        const bool active = r0 < rows && c0 < cols;  // whole 8x8 blocks: in or out
+        uint4 in[8];
+        // a lane outside the tensor loads the first block and stores nothing
+        const uint16_t *src = x + (active ? r0 * cols + c0 : 0);
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            in[i] = *(const uint4 *)(src + i * cols);
+        if constexpr (INJECT != 0) {
+            const uint16_t *asrc = inj.act + (active ? r0 * cols + c0 : 0);
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                in[i] = inject_vec<(INJECT == 4 ? 4 : 0)>(in[i], *(const uint4 *)(asrc + i * cols), inj);
         }
-    }
+        if (!have_scale) {  // behind the first loads, so that the two latencies overlap
+            have_scale = true;
+            float amax_v;
+            if (amax_partials != nullptr) {  // uniform: the maxima of the amax launch's workgroups
+                uint32_t m = 0;
+                for (int i = t; i < n_partials; i += kQuantThreads) {
+                    const uint32_t v = amax_partials[i];
+                    m = v > m ? v : m;
+                }
+                m = wave_reduce_max_u32(m);
+                if ((t & (kWave - 1)) == 0)
+                    pred[t / kWave] = m;
+                __syncthreads();
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-        uint4 in[8][2];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const uint4 *src = (const uint4 *)(x + (r0 + half * 8 + i) * cols + c0);
-            in[i][0] = src[0];
-            in[i][1] = src[1];
-            if constexpr (INJECT != 0) {
-                const uint4 *asrc = (const uint4 *)(inj.act + (r0 + half * 8 + i) * cols + c0);
-                in[i][0] = inject_vec<(INJECT == 4 ? 4 : 0)>(in[i][0], asrc[0], inj);
-                in[i][1] = inject_vec<(INJECT == 4 ? 4 : 0)>(in[i][1], asrc[1], inj);
+                for (int w = 0; w < kQuantThreads / kWave; ++w)
+                    m = pred[w] > m ? pred[w] : m;
+                amax_v = __uint_as_float(m);
+                if (block == 0 && t == 0)
+                    *amax_store = amax_v;
+            } else {
+                amax_v = *amax;
             }
-            if constexpr (DELAYED && !LN)
-                mx = pk_absmax4(pk_absmax4(mx, in[i][0]), in[i][1]);
+            scale = DELAYED ? amax_v : scale_f8<E5M2>(amax_v);
+            if (block == 0 && t == 0) {
+                if (scale_out)
+                    *scale_out = scale;
+                if (scale_inv_out)
+                    *scale_inv_out = 1.0f / scale;
+            }
         }
         if constexpr (LN) {
-            // normalise what was loaded, eight columns at a time (their widened parameters live
-            // only that long)
+            double g64[8], b64[8];
+            widen8(*(const uint4 *)(ln.gamma + (active ? c0 : 0)), g64);
+            widen8(ln.beta != nullptr ? *(const uint4 *)(ln.beta + (active ? c0 : 0)) : make_uint4(0u, 0u, 0u, 0u), b64);
 #pragma unroll
-            for (int w = 0; w < 2; ++w) {
-                double g64[8], b64[8];
-                widen8(lg[w], g64);
-                widen8(lb[w], b64);
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const double2 st = *(const double2 *)(ln.stats + 2 * (r0 + half * 8 + i));
-                    in[i][w] = ln_vec(in[i][w], st.x, st.y, g64, b64, ln.beta != nullptr);
-                    if constexpr (DELAYED)
-                        mx = pk_absmax4(mx, in[i][w]);
-                }
+            for (int i = 0; i < 8; ++i) {
+                const double2 st = *(const double2 *)(ln.stats + 2 * (active ? r0 + i : i));
+                in[i] = ln_vec(in[i], st.x, st.y, g64, b64, ln.beta != nullptr);
             }
-            if (y_out != nullptr) {
+            if (y_out != nullptr && active) {
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    uint4 *dst = (uint4 *)(y_out + (r0 + half * 8 + i) * cols + c0);
-                    dst[0] = in[i][0];
-                    dst[1] = in[i][1];
-                }
+                for (int i = 0; i < 8; ++i)
+                    *(uint4 *)(y_out + (r0 + i) * cols + c0) = in[i];
             }
         }
+        if constexpr (DELAYED) {
+            uint32_t m = 0;
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                m = pk_absmax4(m, in[i]);
+            mx = active ? pk_absmax(m, mx) : mx;
+        }
+        uint32_t lo[8], hi[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            const int r = half * 8 + i;
-#pragma unroll
-            for (int w = 0; w < 2; ++w) {
-                const uint4 v = in[i][w];
-                qd[r][2 * w] = cvt4_f8<E5M2>(bf16lo_to_f32(v.x) * scale, bf16hi_to_f32(v.x) * scale,
-                                         bf16lo_to_f32(v.y) * scale, bf16hi_to_f32(v.y) * scale);
-                qd[r][2 * w + 1] = cvt4_f8<E5M2>(bf16lo_to_f32(v.z) * scale, bf16hi_to_f32(v.z) * scale,
-                                             bf16lo_to_f32(v.w) * scale, bf16hi_to_f32(v.w) * scale);
-            }
-            *(uint4 *)(q + (r0 + r) * cols + c0) = make_uint4(qd[r][0], qd[r][1], qd[r][2], qd[r][3]);
+            lo[i] = cvt4_f8<E5M2>(bf16lo_to_f32(in[i].x) * scale, bf16hi_to_f32(in[i].x) * scale,
+                                  bf16lo_to_f32(in[i].y) * scale, bf16hi_to_f32(in[i].y) * scale);
+            hi[i] = cvt4_f8<E5M2>(bf16lo_to_f32(in[i].z) * scale, bf16hi_to_f32(in[i].z) * scale,
+                                  bf16lo_to_f32(in[i].w) * scale, bf16hi_to_f32(in[i].w) * scale);
+            if (active)
+                *(uint2 *)(q + (r0 + i) * cols + c0) = make_uint2(lo[i], hi[i]);
         }
-    }
-    if (WITH_T) {
+        if constexpr (WITH_T) {
+            uint32_t ta[8], tb[8];  // column j of the block: rows 0-3, rows 4-7
+            transpose4x4_bytes(lo[0], lo[1], lo[2], lo[3], ta[0], ta[1], ta[2], ta[3]);
+            transpose4x4_bytes(hi[0], hi[1], hi[2], hi[3], ta[4], ta[5], ta[6], ta[7]);
+            transpose4x4_bytes(lo[4], lo[5], lo[6], lo[7], tb[0], tb[1], tb[2], tb[3]);
+            transpose4x4_bytes(hi[4], hi[5], hi[6], hi[7], tb[4], tb[5], tb[6], tb[7]);
+            if (DELAYED && tile != block)
+                __syncthreads();  // the tile before has been read
+            uint8_t *w = (uint8_t *)turned + cg * 8 * kTile + (((rg >> 1) ^ (cg & 7)) << 4) + (rg & 1) * 8;
 #pragma unroll
-        for (int C = 0; C < 4; ++C) {
-            uint32_t t[4][4];  // t[R][k]: column 4C+k, rows 4R..4R+3
+            for (int j = 0; j < 8; ++j)
+                *(uint2 *)(w + j * kTile) = make_uint2(ta[j], tb[j]);
+            __syncthreads();
+            const int piece = t & 7;
 #pragma unroll
-            for (int R = 0; R < 4; ++R)
-                transpose4x4_bytes(qd[4 * R][C], qd[4 * R + 1][C], qd[4 * R + 2][C], qd[4 * R + 3][C],
-                                   t[R][0], t[R][1], t[R][2], t[R][3]);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
+            for (int i = 0; i < 4; ++i) {
                 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-                v4u *dst = (v4u *)(qT + (c0 + 4 * C + k) * rows + r0);
-                const v4u v = {t[0][k], t[1][k], t[2][k], t[3][k]};
-                if constexpr (T_LATER)
-                    __builtin_nontemporal_store(v, dst);
-                else
-                    *dst = v;
+                const int col = (t >> 3) + 32 * i;
+                const v4u v = __builtin_bit_cast(v4u, turned[col * (kTile / 16) + (piece ^ ((col >> 3) & 7))]);
+                if (C + col < cols && R + piece * 16 < rows) {
+                    v4u *dst = (v4u *)(qT + (C + col) * rows + R + piece * 16);
+                    if constexpr (T_LATER)
+                        __builtin_nontemporal_store(v, dst);
+                    else
+                        *dst = v;
+                }
             }
         }
-    }
     }
     // every lane reaches the one workgroup barrier of the amax commit (amax_acc is uniform over
     // the grid; nullptr = the caller already has this tensor's amax)
@@ -1004,36 +1012,36 @@ __device__ __forceinline__ void quantize_e4m3_16x16_body(
 
 // LayerNorm + cast (DELAYED: the scale is read from *amax, the tensor's amax goes to *amax_acc)
 template <bool WITH_T, bool DELAYED>
-__global__ __launch_bounds__(kQuantThreads, 2) void quantize_ln_16x16_kernel(
+__global__ __launch_bounds__(kQuantThreads) void cast_ln_tile_kernel(
     const uint16_t *__restrict__ x, LnArgs ln, int64_t rows, int64_t cols, int64_t tiles_x,
     const float *__restrict__ amax, uint8_t *__restrict__ q, uint8_t *__restrict__ qT, uint16_t *__restrict__ y_out,
     float *scale_out, float *scale_inv_out, uint32_t *amax_acc, const uint32_t *__restrict__ amax_partials,
     int n_partials, float *amax_store)
 {
-    quantize_e4m3_16x16_body<WITH_T, DELAYED, false, 0, true>(
+    cast_tile_body<WITH_T, DELAYED, false, 0, true>(
         x, rows, cols, tiles_x, amax, q, qT, scale_out, scale_inv_out, amax_acc, blockIdx.x, gridDim.x, amax_partials,
         n_partials, amax_store, InjectArgs{}, ln, y_out);
 }
 
 template <bool WITH_T, bool DELAYED, bool E5M2 = false>
-__global__ __launch_bounds__(kQuantThreads) void quantize_e4m3_16x16_kernel(
+__global__ __launch_bounds__(kQuantThreads) void cast_tile_kernel(
     const uint16_t *__restrict__ x, int64_t rows, int64_t cols, int64_t tiles_x,
     const float *__restrict__ amax, uint8_t *__restrict__ q, uint8_t *__restrict__ qT,
     float *scale_out, float *scale_inv_out, uint32_t *amax_acc, const uint32_t *__restrict__ amax_partials,
     int n_partials, float *amax_store)
 {
-    quantize_e4m3_16x16_body<WITH_T, DELAYED, E5M2>(x, rows, cols, tiles_x, amax, q, qT, scale_out, scale_inv_out,
+    cast_tile_body<WITH_T, DELAYED, E5M2>(x, rows, cols, tiles_x, amax, q, qT, scale_out, scale_inv_out,
                                               amax_acc, blockIdx.x, gridDim.x, amax_partials, n_partials,
                                               amax_store);
 }
 
 template <bool E5M2, int INJECT>
-__global__ __launch_bounds__(kQuantThreads) void quantize_inject_16x16_kernel(
+__global__ __launch_bounds__(kQuantThreads) void cast_inject_tile_kernel(
     const uint16_t *__restrict__ dy, InjectArgs inj, int64_t rows, int64_t cols, int64_t tiles_x,
     uint8_t *__restrict__ q, uint8_t *__restrict__ qT, float *scale_out, float *scale_inv_out,
     const uint32_t *__restrict__ amax_partials, int n_partials, float *amax_store)
 {
-    quantize_e4m3_16x16_body<true, false, E5M2, INJECT>(dy, rows, cols, tiles_x, amax_store, q, qT, scale_out,
+    cast_tile_body<true, false, E5M2, INJECT>(dy, rows, cols, tiles_x, amax_store, q, qT, scale_out,
                                                       scale_inv_out, nullptr, blockIdx.x, gridDim.x, amax_partials,
                                                       n_partials, amax_store, inj);
 }
@@ -1051,12 +1059,12 @@ struct QuantTensor {
     float *amax_store;
 };
 
-__global__ __launch_bounds__(kQuantThreads) void quantize2_e4m3_16x16_kernel(QuantTensor t0, int64_t blocks0,
+__global__ __launch_bounds__(kQuantThreads) void cast2_tile_kernel(QuantTensor t0, int64_t blocks0,
                                                                              QuantTensor t1)
 {
     const bool first = (int64_t)blockIdx.x < blocks0;
     const QuantTensor &t = first ? t0 : t1;
-    quantize_e4m3_16x16_body<true, false, false, 0, false, true>(t.x, t.rows, t.cols, t.tiles_x, t.amax, t.q, t.qT, t.scale_out,
+    cast_tile_body<true, false, false, 0, false, true>(t.x, t.rows, t.cols, t.tiles_x, t.amax, t.q, t.qT, t.scale_out,
                                           t.scale_inv_out, nullptr,
                                           first ? (int64_t)blockIdx.x : (int64_t)blockIdx.x - blocks0, 1,
                                           t.amax_partials, t.n_partials, t.amax_store);
@@ -1068,15 +1076,17 @@ hipError_t launch_quantize2_e4m3(const void *x0_bf16, int64_t rows0, int64_t col
                                  float *scale1, float *scale1_inv, hipStream_t s, const uint32_t *partials0,
                                  int n_partials0, const uint32_t *partials1, int n_partials1)
 {
-    auto tiles = [](int64_t v) { return (v + kQuantBigTile - 1) / kQuantBigTile; };
+    auto tiles = [](int64_t v) { return (v + kTile - 1) / kTile; };
     QuantTensor t0{(const uint16_t *)x0_bf16, rows0, cols0, tiles(cols0), amax0, q0, q0T, scale0, scale0_inv,
                    partials0, n_partials0, amax0};
     QuantTensor t1{(const uint16_t *)x1_bf16, rows1, cols1, tiles(cols1), amax1, q1, q1T, scale1, scale1_inv,
                    partials1, n_partials1, amax1};
     const int64_t b0 = tiles(rows0) * tiles(cols0), b1 = tiles(rows1) * tiles(cols1);
-    hipLaunchKernelGGL(quantize2_e4m3_16x16_kernel, dim3((unsigned)(b0 + b1)), dim3(kQuantThreads), 0, s, t0, b0, t1);
+    hipLaunchKernelGGL(cast2_tile_kernel, dim3((unsigned)(b0 + b1)), dim3(kQuantThreads), 0, s, t0, b0, t1);
     return hipGetLastError();
 }
+
+constexpr int kDelayedGrid = 1536;  // workgroups of a delayed-scaling cast: six per CU
 
 template <bool DELAYED, bool E5M2 = false>
 static hipError_t launch_quantize_e4m3_impl(const void *x_bf16, int64_t rows, int64_t cols, const float *amax,
@@ -1089,18 +1099,18 @@ static hipError_t launch_quantize_e4m3_impl(const void *x_bf16, int64_t rows, in
     if (amax_partials != nullptr && (rows % 16 != 0 || cols % 16 != 0))
         return hipErrorInvalidValue;  // only the whole-block kernel reduces partial maxima
     if (rows % 16 == 0 && cols % 16 == 0) {
-        const int64_t tiles_x = (cols + kQuantBigTile - 1) / kQuantBigTile;
-        const int64_t tiles_y = (rows + kQuantBigTile - 1) / kQuantBigTile;
+        const int64_t tiles_x = (cols + kTile - 1) / kTile;
+        const int64_t tiles_y = (rows + kTile - 1) / kTile;
         int64_t n_wg = tiles_x * tiles_y;
-        if (DELAYED && n_wg > 1024)
-            n_wg = 1024;
+        if (DELAYED && n_wg > kDelayedGrid)
+            n_wg = kDelayedGrid;
         const dim3 grid((unsigned)n_wg);
         if (qT)
-            hipLaunchKernelGGL((quantize_e4m3_16x16_kernel<true, DELAYED, E5M2>), grid, block, 0, s,
+            hipLaunchKernelGGL((cast_tile_kernel<true, DELAYED, E5M2>), grid, block, 0, s,
                                (const uint16_t *)x_bf16, rows, cols, tiles_x, amax, q, qT, scale_out,
                                scale_inv_out, amax_acc, amax_partials, n_partials, amax_store);
         else
-            hipLaunchKernelGGL((quantize_e4m3_16x16_kernel<false, DELAYED, E5M2>), grid, block, 0, s,
+            hipLaunchKernelGGL((cast_tile_kernel<false, DELAYED, E5M2>), grid, block, 0, s,
                                (const uint16_t *)x_bf16, rows, cols, tiles_x, amax, q, qT, scale_out,
                                scale_inv_out, amax_acc, amax_partials, n_partials, amax_store);
         return hipGetLastError();
@@ -1185,6 +1195,7 @@ struct FusedTensor {
     float *amax_store, *scale_out, *scale_inv_out;
 };
 
+constexpr int kQuantBigTile = 256;  // what eight waves cover: the fused kernel counts its tiles in quarters of it
 constexpr int kFusedThreads = 512, kFusedWaves = kFusedThreads / kWave;
 constexpr int kFusedSpinLimit = 1 << 18;  // polls of ~0.25 us each
 constexpr int kFusedLdsBytes = 8 * 2 * kFusedThreads * 16;  // eight rows of 32 bytes per lane
@@ -1652,7 +1663,7 @@ hipError_t launch_amax_quantize_inject(const void *dy_bf16, const void *a_bf16, 
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return e;
-    const int64_t tiles_x = (cols + kQuantBigTile - 1) / kQuantBigTile, tiles_y = (rows + kQuantBigTile - 1) / kQuantBigTile;
+    const int64_t tiles_x = (cols + kTile - 1) / kTile, tiles_y = (rows + kTile - 1) / kTile;
     const dim3 grid((unsigned)(tiles_x * tiles_y)), block(kQuantThreads);
     auto launch = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, grid, block, 0, s, (const uint16_t *)dy_bf16, inj, rows, cols, tiles_x, q, qT,
@@ -1660,14 +1671,14 @@ hipError_t launch_amax_quantize_inject(const void *dy_bf16, const void *a_bf16, 
     };
     if (e5m2) {
         if (p == 4)
-            launch(quantize_inject_16x16_kernel<true, 4>);
+            launch(cast_inject_tile_kernel<true, 4>);
         else
-            launch(quantize_inject_16x16_kernel<true, 1>);
+            launch(cast_inject_tile_kernel<true, 1>);
     } else {
         if (p == 4)
-            launch(quantize_inject_16x16_kernel<false, 4>);
+            launch(cast_inject_tile_kernel<false, 4>);
         else
-            launch(quantize_inject_16x16_kernel<false, 1>);
+            launch(cast_inject_tile_kernel<false, 1>);
     }
     return hipGetLastError();
 }
@@ -1802,12 +1813,12 @@ struct QuantTensorDelayed {
     uint32_t *amax_acc;
 };
 
-__global__ __launch_bounds__(kQuantThreads) void quantize2_delayed_16x16_kernel(QuantTensorDelayed t0, int64_t blocks0,
+__global__ __launch_bounds__(kQuantThreads) void cast2_delayed_tile_kernel(QuantTensorDelayed t0, int64_t blocks0,
                                                                                 QuantTensorDelayed t1, int64_t blocks1)
 {
     const bool first = (int64_t)blockIdx.x < blocks0;
     const QuantTensorDelayed &t = first ? t0 : t1;
-    quantize_e4m3_16x16_body<true, true, false, 0, false, true>(t.x, t.rows, t.cols, t.tiles_x, t.scale, t.q, t.qT, nullptr, nullptr, t.amax_acc,
+    cast_tile_body<true, true, false, 0, false, true>(t.x, t.rows, t.cols, t.tiles_x, t.scale, t.q, t.qT, nullptr, nullptr, t.amax_acc,
                                          first ? (int64_t)blockIdx.x : (int64_t)blockIdx.x - blocks0,
                                          first ? blocks0 : blocks1);
 }
@@ -1823,18 +1834,18 @@ hipError_t launch_quantize2_e4m3_delayed(const void *x0_bf16, int64_t rows0, int
             return e;
         return launch_quantize_f8_delayed<false>(x1_bf16, rows1, cols1, state1, 1, q1, q1T, s, sc1);
     }
-    auto tiles = [](int64_t v) { return (v + kQuantBigTile - 1) / kQuantBigTile; };
+    auto tiles = [](int64_t v) { return (v + kTile - 1) / kTile; };
     float *st0 = (float *)state0, *st1 = (float *)state1;
     QuantTensorDelayed t0{(const uint16_t *)x0_bf16, rows0, cols0, tiles(cols0), st0 + 17, q0, q0T, (uint32_t *)st0 + 16};
     QuantTensorDelayed t1{(const uint16_t *)x1_bf16, rows1, cols1, tiles(cols1), st1 + 17, q1, q1T, (uint32_t *)st1 + 16};
     // a bounded grid (its one atomic per workgroup stays a few hundred per tensor), shared out in
     // proportion to the tile counts
     const int64_t n0 = tiles(rows0) * tiles(cols0), n1 = tiles(rows1) * tiles(cols1);
-    int64_t b1 = (int64_t)(1024.0 * (double)n1 / (double)(n0 + n1) + 0.5);
+    int64_t b1 = (int64_t)((double)kDelayedGrid * (double)n1 / (double)(n0 + n1) + 0.5);
     b1 = b1 < 1 ? 1 : (b1 > n1 ? n1 : b1);
-    int64_t b0 = 1024 - b1;
+    int64_t b0 = kDelayedGrid - b1;
     b0 = b0 < 1 ? 1 : (b0 > n0 ? n0 : b0);
-    hipLaunchKernelGGL(quantize2_delayed_16x16_kernel, dim3((unsigned)(b0 + b1)), dim3(kQuantThreads), 0, s, t0, b0, t1, b1);
+    hipLaunchKernelGGL(cast2_delayed_tile_kernel, dim3((unsigned)(b0 + b1)), dim3(kQuantThreads), 0, s, t0, b0, t1, b1);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return e;
@@ -1890,17 +1901,17 @@ hipError_t launch_layernorm_quantize(const void *x_bf16, const void *res_bf16, c
         return e;
     const uint16_t *src = (const uint16_t *)(res_bf16 != nullptr ? h_out : x_bf16);
     const LnArgs ln{stats, (const uint16_t *)gamma_bf16, (const uint16_t *)beta_bf16};
-    const int64_t tiles_x = (cols + kQuantBigTile - 1) / kQuantBigTile, tiles_y = (rows + kQuantBigTile - 1) / kQuantBigTile;
+    const int64_t tiles_x = (cols + kTile - 1) / kTile, tiles_y = (rows + kTile - 1) / kTile;
     const int64_t n_tiles = tiles_x * tiles_y;
     const dim3 block(kQuantThreads);
     float *st = (float *)state;
     if (!delayed) {
         if (qT)
-            hipLaunchKernelGGL((quantize_ln_16x16_kernel<true, false>), dim3((unsigned)n_tiles), block, 0, s, src, ln,
+            hipLaunchKernelGGL((cast_ln_tile_kernel<true, false>), dim3((unsigned)n_tiles), block, 0, s, src, ln,
                                rows, cols, tiles_x, (const float *)amax_out, q, qT, (uint16_t *)y_out, scale_out, scale_inv_out,
                                (uint32_t *)nullptr, (const uint32_t *)partials, (int)sgrid, amax_out);
         else
-            hipLaunchKernelGGL((quantize_ln_16x16_kernel<false, false>), dim3((unsigned)n_tiles), block, 0, s, src, ln,
+            hipLaunchKernelGGL((cast_ln_tile_kernel<false, false>), dim3((unsigned)n_tiles), block, 0, s, src, ln,
                                rows, cols, tiles_x, (const float *)amax_out, q, qT, (uint16_t *)y_out, scale_out, scale_inv_out,
                                (uint32_t *)nullptr, (const uint32_t *)partials, (int)sgrid, amax_out);
         return hipGetLastError();
@@ -1913,13 +1924,13 @@ hipError_t launch_layernorm_quantize(const void *x_bf16, const void *res_bf16, c
     }
     const float *scale_src = bootstrap ? st + 21 : st + 17;
     uint32_t *acc = bootstrap ? nullptr : (uint32_t *)st + 16;
-    int64_t n_wg = n_tiles < 1024 ? n_tiles : 1024;
+    int64_t n_wg = n_tiles < kDelayedGrid ? n_tiles : kDelayedGrid;
     if (qT)
-        hipLaunchKernelGGL((quantize_ln_16x16_kernel<true, true>), dim3((unsigned)n_wg), block, 0, s, src, ln, rows, cols,
+        hipLaunchKernelGGL((cast_ln_tile_kernel<true, true>), dim3((unsigned)n_wg), block, 0, s, src, ln, rows, cols,
                            tiles_x, scale_src, q, qT, (uint16_t *)y_out, (float *)nullptr, (float *)nullptr, acc,
                            (const uint32_t *)nullptr, 0, (float *)nullptr);
     else
-        hipLaunchKernelGGL((quantize_ln_16x16_kernel<false, true>), dim3((unsigned)n_wg), block, 0, s, src, ln, rows, cols,
+        hipLaunchKernelGGL((cast_ln_tile_kernel<false, true>), dim3((unsigned)n_wg), block, 0, s, src, ln, rows, cols,
                            tiles_x, scale_src, q, qT, (uint16_t *)y_out, (float *)nullptr, (float *)nullptr, acc,
                            (const uint32_t *)nullptr, 0, (float *)nullptr);
     if ((e = hipGetLastError()) != hipSuccess)
