@@ -297,7 +297,7 @@ __device__ __forceinline__ void epilogue(const GemmDev &g, ACC (&acc)[T::MT][T::
 #undef TWEO_EPI
 }
 
-// K split: the fp32 sums of one run, straight from the MFMA layout.  Lane (l31, lh) holds row l31
+// K split: the fp32 (INT8: int32) sums of one run, straight from the MFMA layout.  Lane (l31, lh) holds row l31
 // and columns 8q + 4lh .. +3 of each 32x32 block (16-byte stores; the four q of a block complete
 // the row's 128-byte line).
 template <typename T, typename ACC>
@@ -313,9 +313,12 @@ __device__ __forceinline__ void store_ksplit_run(const GemmDev &g, ACC (&acc)[T:
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int n = tn * T::BN + wn * T::TN + j * 32 + 8 * q + 4 * lh;
-                if (m < g.M && n < g.N)
-                    *(v4f *)(dst + (int64_t)m * g.N + n) =
-                        v4f{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+                if (m < g.M && n < g.N) {
+                    typedef std::remove_reference_t<decltype(acc[i][j][0])> word_t;
+                    typedef word_t v4w __attribute__((ext_vector_type(4)));
+                    *(v4w *)(dst + (int64_t)m * g.N + n) =
+                        v4w{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+                }
             }
     }
 }
@@ -509,7 +512,9 @@ struct TileD {
 };
 
 
-template <typename T, bool INT8>
+// KSPLIT: g.ksplit runs of the tile grid (a flag of its own: compiled in for all, the second way out
+// of the kernel cost the unsplit INT8 launches 2 %)
+template <typename T, bool INT8, bool KSPLIT = false>
 __global__ __launch_bounds__(T::THREADS, T::WPE) void gemm_nt_dma_kernel(GemmDev g)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -520,10 +525,10 @@ __global__ __launch_bounds__(T::THREADS, T::WPE) void gemm_nt_dma_kernel(GemmDev
     // with a K split the grid is ksplit runs of the tile grid: run `split` takes K stages
     // [split * stages / ksplit, (split + 1) * stages / ksplit)
     const int n_tiles = g.tiles_m * g.tiles_n;
-    const int split = g.ksplit > 1 ? (int)blockIdx.x / n_tiles : 0;
+    const int split = KSPLIT ? (int)blockIdx.x / n_tiles : 0;
     tile_of_workgroup((int)blockIdx.x - split * n_tiles, g.tiles_m, g.tiles_n, tm, tn);
     int kt = g.K / T::BK, kt_begin = 0;
-    if (g.ksplit > 1) {
+    if constexpr (KSPLIT) {
         kt_begin = (int)((int64_t)split * kt / g.ksplit);
         kt = (int)((int64_t)(split + 1) * kt / g.ksplit) - kt_begin;
     }
@@ -666,15 +671,13 @@ __global__ __launch_bounds__(T::THREADS, T::WPE) void gemm_nt_dma_kernel(GemmDev
         if (s + 1 < kt)
             tail_step(s + 1, fr[1], fr[0]);
     }
-    if constexpr (!INT8) {
-        if (g.ksplit > 1) {
-            store_ksplit_run<T>(g, acc, split, tm, tn, wm, wn, l31, lh);
-            return;
-        }
+    if constexpr (KSPLIT) {
+        store_ksplit_run<T>(g, acc, split, tm, tn, wm, wn, l31, lh);
+    } else {
+        block_barrier();  // every wave is done reading the stages before they are reused
+        NoBandHook no_hook;
+        epilogue<T, INT8>(g, acc, smem, tm, tn, wm, wn, lane, wave, tid, blockIdx.x, no_hook);
     }
-    block_barrier();  // every wave is done reading the stages before they are reused
-    NoBandHook no_hook;
-    epilogue<T, INT8>(g, acc, smem, tm, tn, wm, wn, lane, wave, tid, blockIdx.x, no_hook);
 }
 
 // ---------------------------------------------------------------------------
@@ -1311,22 +1314,28 @@ __global__ __launch_bounds__(512) void w8a8_skinny_ring_kernel(const int8_t *__r
 }
 
 // Second half of a K split: out = bf16((*s0 * *s1) * (((p_0 + p_1) + p_2) + ...)), the runs added
-// in index order (the result does not depend on which workgroup finished first).
+// in index order (the result does not depend on which workgroup finished first).  INT8: the runs are
+// int32 sums, added exactly, and out = bf16(fp32(sum) * alpha_i8).
+template <bool INT8>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restrict__ partials, int splits,
                                                             int64_t mn, const float *__restrict__ s0,
-                                                            const float *__restrict__ s1, uint16_t *__restrict__ out)
+                                                            const float *__restrict__ s1, float alpha_i8,
+                                                            uint16_t *__restrict__ out)
 {
-    const float alpha = (*s0) * (*s1);
+    typedef typename std::conditional<INT8, v4i, v4f>::type sum_t;
+    const float alpha = INT8 ? alpha_i8 : (*s0) * (*s1);
     const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 8;
     if (i >= mn)
         return;
-    v4f lo = *(const v4f *)(partials + i), hi = *(const v4f *)(partials + i + 4);
+    sum_t lo = *(const sum_t *)(partials + i), hi = *(const sum_t *)(partials + i + 4);
     for (int s = 1; s < splits; ++s) {
-        lo += *(const v4f *)(partials + (int64_t)s * mn + i);
-        hi += *(const v4f *)(partials + (int64_t)s * mn + i + 4);
+        lo += *(const sum_t *)(partials + (int64_t)s * mn + i);
+        hi += *(const sum_t *)(partials + (int64_t)s * mn + i + 4);
     }
-    *(uint4 *)(out + i) = make_uint4(pack_bf16x2(lo[0] * alpha, lo[1] * alpha), pack_bf16x2(lo[2] * alpha, lo[3] * alpha),
-                                     pack_bf16x2(hi[0] * alpha, hi[1] * alpha), pack_bf16x2(hi[2] * alpha, hi[3] * alpha));
+    *(uint4 *)(out + i) = make_uint4(pack_bf16x2((float)lo[0] * alpha, (float)lo[1] * alpha),
+                                     pack_bf16x2((float)lo[2] * alpha, (float)lo[3] * alpha),
+                                     pack_bf16x2((float)hi[0] * alpha, (float)hi[1] * alpha),
+                                     pack_bf16x2((float)hi[2] * alpha, (float)hi[3] * alpha));
 }
 
 // Second half of a K split on the deferred-epilogue kernel's tiles: the runs sit in the
@@ -1878,27 +1887,62 @@ int fp8_gemm_ksplit(int64_t M, int64_t N, int64_t K)
     return splits >= 2 ? (int)splits : 1;
 }
 
+// INT8, between decode and prefill sizes: an output of few 128x128 tiles leaves CUs idle (384 rows into
+// 4096 columns: 96 tiles), so `splits` workgroups share a tile on the direct-to-LDS kernel, int32 runs
+// added exactly by the reduce kernel.  The rule is the time of both ways from measured rates: a tile
+// alone on its CU runs at 0.29 us per 64-byte stage (two on a CU share that), the runs are written and
+// read at 4 TB/s, the second launch costs 4 us; taken where that promises a quarter.
+// Quantise + linear, 11008 -> 4096 at M = 300 / 384 / 500: 44.2 / 53.6 / 53.9 -> 32.6 / 37.7 / 44.9 us;
+// 5632 -> 2048 at M = 300: 26.2 -> 18.6.
+static int i8_dma_ksplit(int64_t M, int64_t N, int64_t K)
+{
+    if (g_tile_override != 0 || K % 64 != 0 || N % 8 != 0 || M <= 128)
+        return 1;
+    const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128), kt = K / 64, cus = num_cus();
+    if (tiles * 2 > cus)
+        return 1;
+    int best = 1;
+    double best_us = 0.75 * 0.29 * (double)kt;
+    for (int s = 2; s <= 8 && kt / s >= 16; ++s) {
+        const double us = 0.29 * (double)((tiles * s + cus - 1) / cus) * (double)((kt + s - 1) / s) +
+                          (double)s * (double)M * (double)N * 8.0 / 4e6 + 4.0;
+        if (us < best_us) {
+            best = s;
+            best_us = us;
+        }
+    }
+    return best;
+}
+
+size_t i8_gemm_ksplit_bytes(int64_t M, int64_t N, int64_t K)
+{
+    int splits = defer_ksplit(M, N, K);
+    if (splits <= 1)
+        splits = i8_dma_ksplit(M, N, K);
+    return splits > 1 ? (size_t)splits * (size_t)M * (size_t)N * sizeof(int32_t) : 0;
+}
+
 size_t fp8_gemm_ksplit_bytes(int64_t M, int64_t N, int64_t K)
 {
     const int splits = fp8_gemm_ksplit(M, N, K);
     return splits > 1 ? (size_t)splits * (size_t)M * (size_t)N * sizeof(float) : 0;
 }
 
-// DMA: the direct-to-LDS kernel on 64-byte stages (K % 64 == 0, E4M3 operands), else the
+// DMA: the direct-to-LDS kernel on 64-byte stages (K % 64 == 0, E4M3 or INT8 operands), else the
 // register-staged one.
-template <bool A_E5M2, bool DMA>
+template <typename T, bool A_E5M2, bool DMA, bool INT8 = false>
 static hipError_t launch_ksplit(const GemmArgs &a, hipStream_t s, int splits)
 {
-    using T = typename std::conditional<DMA, D256x256w8, T256x256>::type;
     static_assert(!(DMA && A_E5M2), "the direct-to-LDS kernel takes E4M3 operands only");
-    const void *kern;
+    static_assert(DMA || !INT8, "INT8 runs come from the direct-to-LDS kernel");
+    void (*kern)(GemmDev);
     if constexpr (DMA)
-        kern = (const void *)gemm_nt_dma_kernel<T, false>;
+        kern = gemm_nt_dma_kernel<T, INT8, true>;
     else
-        kern = (const void *)gemm_nt_kernel<T, false, A_E5M2>;
+        kern = gemm_nt_kernel<T, false, A_E5M2>;
     static bool attr_done = false;
     if (!attr_done) {
-        hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
+        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
         if (e != hipSuccess)
             return e;
         attr_done = true;
@@ -1921,27 +1965,17 @@ static hipError_t launch_ksplit(const GemmArgs &a, hipStream_t s, int splits)
     const dim3 rgrid((unsigned)((mn / 8 + 255) / 256));
     // a profiled launch brackets both kernels: start event on the first, end event on the second
     hipEvent_t e0 = nullptr, e1 = nullptr;
-    if (g_prof_next < g_prof_count) {
-        e0 = g_prof_events[2 * g_prof_next];
-        e1 = g_prof_events[2 * g_prof_next + 1];
-        ++g_prof_next;
-    }
-    auto launch_first = [&](auto kernel) {
-        if (e0 != nullptr)
-            hipExtLaunchKernelGGL(kernel, grid, block, T::LDS_BYTES, s, e0, nullptr, 0, g);
-        else
-            hipLaunchKernelGGL(kernel, grid, block, T::LDS_BYTES, s, g);
-    };
-    if constexpr (DMA)
-        launch_first(gemm_nt_dma_kernel<T, false>);
+    take_profile_events(&e0, &e1);
+    if (e0 != nullptr)
+        hipExtLaunchKernelGGL(kern, grid, block, T::LDS_BYTES, s, e0, nullptr, 0, g);
     else
-        launch_first(gemm_nt_kernel<T, false, A_E5M2>);
+        hipLaunchKernelGGL(kern, grid, block, T::LDS_BYTES, s, g);
     if (e1 != nullptr)
-        hipExtLaunchKernelGGL(splitk_reduce_kernel, rgrid, dim3(256), 0, s, nullptr, e1, 0,
-                              (const float *)g.ksplit_out, splits, mn, a.s0, a.s1, (uint16_t *)a.out);
+        hipExtLaunchKernelGGL(splitk_reduce_kernel<INT8>, rgrid, dim3(256), 0, s, nullptr, e1, 0,
+                              (const float *)g.ksplit_out, splits, mn, a.s0, a.s1, a.alpha, (uint16_t *)a.out);
     else
-        hipLaunchKernelGGL(splitk_reduce_kernel, rgrid, dim3(256), 0, s, (const float *)g.ksplit_out, splits, mn, a.s0,
-                           a.s1, (uint16_t *)a.out);
+        hipLaunchKernelGGL(splitk_reduce_kernel<INT8>, rgrid, dim3(256), 0, s, (const float *)g.ksplit_out, splits, mn,
+                           a.s0, a.s1, a.alpha, (uint16_t *)a.out);
     return hipGetLastError();
 }
 
@@ -2023,8 +2057,9 @@ hipError_t launch_fp8_gemm(const GemmArgs &a, hipStream_t s)
             if (defer_ksplit(a.M, a.N, a.K) > 1)
                 return a.a_e5m2 ? launch_ksplit_defer<true>(a, s, splits) : launch_ksplit_defer<false>(a, s, splits);
             if (a.a_e5m2)
-                return launch_ksplit<true, false>(a, s, splits);
-            return a.K % 64 == 0 ? launch_ksplit<false, true>(a, s, splits) : launch_ksplit<false, false>(a, s, splits);
+                return launch_ksplit<T256x256, true, false>(a, s, splits);
+            return a.K % 64 == 0 ? launch_ksplit<D256x256w8, false, true>(a, s, splits)
+                                 : launch_ksplit<T256x256, false, false>(a, s, splits);
         }
     }
     return a.a_e5m2 ? launch_fp8_gemm_e5m2(a, s) : launch_gemm<false>(a, s);
@@ -2130,6 +2165,10 @@ hipError_t launch_i8_gemm(const GemmArgs &a, hipStream_t s)
         if (splits > 1 && a.sk_workspace != nullptr && ((uintptr_t)a.sk_workspace & 15u) == 0 &&
             a.sk_workspace_bytes >= (size_t)splits * (size_t)a.M * (size_t)a.N * sizeof(int32_t))
             return launch_ksplit_defer<false, true>(a, s, splits);
+        const int runs = i8_dma_ksplit(a.M, a.N, a.K);
+        if (runs > 1 && a.sk_workspace != nullptr && ((uintptr_t)a.sk_workspace & 15u) == 0 &&
+            a.sk_workspace_bytes >= (size_t)runs * (size_t)a.M * (size_t)a.N * sizeof(int32_t))
+            return launch_ksplit<D128x128w4, false, true, true>(a, s, runs);
     }
     return launch_gemm<true>(a, s);
 }

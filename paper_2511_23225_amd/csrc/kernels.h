@@ -125,6 +125,8 @@ hipError_t launch_i8_gemm(const GemmArgs &a, hipStream_t s);
 // fp32 scratch they need; given through sk_workspace like the stream-K scratch, which it shares.
 int fp8_gemm_ksplit(int64_t M, int64_t N, int64_t K);
 size_t fp8_gemm_ksplit_bytes(int64_t M, int64_t N, int64_t K);
+// int32 scratch of the INT8 K splits
+size_t i8_gemm_ksplit_bytes(int64_t M, int64_t N, int64_t K);
 
 // Bytes of stream-K scratch that let every shape use it on this device.
 size_t stream_k_workspace_bytes();

@@ -227,3 +227,24 @@ def test_w8a8_weight_streaming_up_to_256_rows_into_a_narrow_projection(shape):
     torch.cuda.synchronize()
     want_v = oracle.w8a8_linear_scaled(oxq, owq, sx.cpu().numpy(), sw.cpu().numpy())
     assert np.array_equal(bf16_bits(y), want_v)
+
+
+@pytest.mark.parametrize("shape", [(129, 4096, 512), (200, 4160, 520), (384, 11008, 4096), (700, 5632, 776), (257, 6144, 136)])
+def test_w8a8_k_split_of_128_row_tiles(shape):
+    # few 128x128 tiles under a long contraction, ragged in M and N, a stage count the runs do not
+    # divide: int32 runs added by the second launch, the same bits as without a workspace and as the oracle
+    M, K, N = shape
+    say("w8a8 k-split of 128x128 tiles M=%d K=%d N=%d" % (M, K, N))
+    assert tw.tweo_workspace_bytes(tw.TWEO_OP_W8A8_LINEAR, M, N, K) >= 2 * M * N * 4
+    rng = np.random.default_rng(M + N)
+    xq = rng.integers(-127, 128, (M, K), dtype=np.int8)
+    wq = rng.integers(-127, 128, (N, K), dtype=np.int8)
+    want = oracle.w8a8_linear(xq, wq, 0.001)
+    ws = workspace(tw.TWEO_OP_W8A8_LINEAR, M, N, K)
+    for w in (ws, ws, None):
+        y = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device=DEV)
+        if w is not None:
+            w.fill_(0xA5)
+        tw.tweo_w8a8_linear(to_dev(xq), to_dev(wq), 0.001, y, w)
+        torch.cuda.synchronize()
+        assert np.array_equal(bf16_bits(y), want)
