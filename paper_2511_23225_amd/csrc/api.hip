@@ -122,7 +122,8 @@ size_t tweo_workspace_bytes(int op, int64_t M, int64_t N, int64_t K)
     case TWEO_OP_FP8_LINEAR_BWD:  // dgrad [M,K] over N, wgrad [N,K] over M
         return 256 + round256(std::max({stream_k_candidate(M, K, N) || stream_k_candidate(N, K, M)
                                             ? stream_k_workspace_bytes() : (size_t)0,
-                                        fp8_gemm_ksplit_bytes(M, K, N), fp8_gemm_ksplit_bytes(N, K, M)}));
+                                        fp8_gemm_ksplit_bytes(M, K, N), fp8_gemm_ksplit_bytes(N, K, M),
+                                        fp8_pair_bytes(M, N, K)}));
     case TWEO_OP_FP8_LINEAR_BWD_BF16:
         return kAmaxScratchBytes + tweo_workspace_bytes(TWEO_OP_FP8_LINEAR_BWD, M, N, K);
     case TWEO_OP_W8A8_LINEAR:
@@ -357,39 +358,34 @@ static tweo_status fp8_linear_bwd_impl(const uint8_t *dyq, const uint8_t *dyqT, 
         M > ((int64_t)1 << 24) || N > ((int64_t)1 << 24))
         return TWEO_ERR_UNSUPPORTED;
     hipStream_t s = (hipStream_t)stream;
+    GemmArgs d{}, w{};
     if (dx_bf16) {  // dX[M,K] = dYq[M,N] * WqT[K,N]^T   (contraction over N)
-        GemmArgs a{};
-        a.A = dyq;
-        a.B = wqT;
-        a.M = M;
-        a.N = K;
-        a.K = N;
-        a.s0 = sdy_inv;
-        a.s1 = sw_inv;
-        a.out = dx_bf16;
-        a.a_e5m2 = dy_e5m2;
-        attach_stream_k(a, workspace, workspace_bytes, 256);
-        hipError_t e = launch_fp8_gemm(a, s);
-        if (e != hipSuccess)
-            return TWEO_ERR_HIP;
+        d.A = dyq;
+        d.B = wqT;
+        d.M = M;
+        d.N = K;
+        d.K = N;
+        d.s0 = sdy_inv;
+        d.s1 = sw_inv;
+        d.out = dx_bf16;
+        d.a_e5m2 = dy_e5m2;
+        attach_stream_k(d, workspace, workspace_bytes, 256);
     }
     if (dw_bf16) {  // dW[N,K] = dYqT[N,M] * XqT[K,M]^T  (contraction over M)
-        GemmArgs a{};
-        a.A = dyqT;
-        a.B = xqT;
-        a.M = N;
-        a.N = K;
-        a.K = M;
-        a.s0 = sdy_inv;
-        a.s1 = sx_inv;
-        a.out = dw_bf16;
-        a.a_e5m2 = dy_e5m2;
-        attach_stream_k(a, workspace, workspace_bytes, 256);
-        hipError_t e = launch_fp8_gemm(a, s);
-        if (e != hipSuccess)
-            return TWEO_ERR_HIP;
+        w.A = dyqT;
+        w.B = xqT;
+        w.M = N;
+        w.N = K;
+        w.K = M;
+        w.s0 = sdy_inv;
+        w.s1 = sx_inv;
+        w.out = dw_bf16;
+        w.a_e5m2 = dy_e5m2;
+        attach_stream_k(w, workspace, workspace_bytes, 256);
     }
-    return TWEO_OK;
+    if (dx_bf16 && dw_bf16)
+        return hip_status(launch_fp8_gemm_pair(d, w, s));
+    return hip_status(launch_fp8_gemm(dx_bf16 ? d : w, s));
 }
 
 tweo_status tweo_fp8_linear_bwd(const uint8_t *dyq, const uint8_t *dyqT, const float *sdy_inv,

@@ -16,6 +16,8 @@
 // that the 16-byte-per-lane fragment reads of 32 different rows spread over
 // all banks.
 #include <hip/hip_ext.h>
+#include <algorithm>
+#include <cmath>
 #include "gemm_common.h"
 #include "gemm_defer.h"
 
@@ -512,10 +514,11 @@ struct TileD {
 };
 
 
-// KSPLIT: g.ksplit runs of the tile grid (a flag of its own: compiled in for all, the second way out
-// of the kernel cost the unsplit INT8 launches 2 %)
-template <typename T, bool INT8, bool KSPLIT = false>
-__global__ __launch_bounds__(T::THREADS, T::WPE) void gemm_nt_dma_kernel(GemmDev g)
+// KSPLIT: 1 = g.ksplit runs of the tile grid, 0 = none (a flag of its own: compiled in for all, the
+// second way out of the kernel cost the unsplit INT8 launches 2 %), 2 = g.ksplit says.  block: the
+// workgroup's number in g's grid.
+template <typename T, bool INT8, bool A_E5M2, int KSPLIT>
+__device__ __forceinline__ void gemm_nt_dma_body(const GemmDev &g, const int block)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
@@ -525,10 +528,10 @@ __global__ __launch_bounds__(T::THREADS, T::WPE) void gemm_nt_dma_kernel(GemmDev
     // with a K split the grid is ksplit runs of the tile grid: run `split` takes K stages
     // [split * stages / ksplit, (split + 1) * stages / ksplit)
     const int n_tiles = g.tiles_m * g.tiles_n;
-    const int split = KSPLIT ? (int)blockIdx.x / n_tiles : 0;
-    tile_of_workgroup((int)blockIdx.x - split * n_tiles, g.tiles_m, g.tiles_n, tm, tn);
+    const int split = KSPLIT != 0 ? block / n_tiles : 0;
+    tile_of_workgroup(block - split * n_tiles, g.tiles_m, g.tiles_n, tm, tn);
     int kt = g.K / T::BK, kt_begin = 0;
-    if constexpr (KSPLIT) {
+    if (KSPLIT != 0) {
         kt_begin = (int)((int64_t)split * kt / g.ksplit);
         kt = (int)((int64_t)(split + 1) * kt / g.ksplit) - kt_begin;
     }
@@ -610,7 +613,7 @@ __global__ __launch_bounds__(T::THREADS, T::WPE) void gemm_nt_dma_kernel(GemmDev
                               f.a1[i][0], f.a1[i][1], f.a1[i][2], f.a1[i][3]};
                     v8i fb = {f.b0[j][0], f.b0[j][1], f.b0[j][2], f.b0[j][3],
                               f.b1[j][0], f.b1[j][1], f.b1[j][2], f.b1[j][3]};
-                    acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb, fa, acc[i][j], 0, 0,
+                    acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb, fa, acc[i][j], 0, A_E5M2 ? 1 : 0,
                                                                                 0, 0, 0, 0);
                 }
             }
@@ -671,13 +674,34 @@ __global__ __launch_bounds__(T::THREADS, T::WPE) void gemm_nt_dma_kernel(GemmDev
         if (s + 1 < kt)
             tail_step(s + 1, fr[1], fr[0]);
     }
-    if constexpr (KSPLIT) {
+    if (KSPLIT == 1 || (KSPLIT == 2 && g.ksplit > 1))
         store_ksplit_run<T>(g, acc, split, tm, tn, wm, wn, l31, lh);
-    } else {
+    if constexpr (KSPLIT != 1) {
+        if (KSPLIT == 2 && g.ksplit > 1)
+            return;
         block_barrier();  // every wave is done reading the stages before they are reused
         NoBandHook no_hook;
-        epilogue<T, INT8>(g, acc, smem, tm, tn, wm, wn, lane, wave, tid, blockIdx.x, no_hook);
+        epilogue<T, INT8>(g, acc, smem, tm, tn, wm, wn, lane, wave, tid, block, no_hook);
     }
+}
+
+template <typename T, bool INT8, int KSPLIT = 0>
+__global__ __launch_bounds__(T::THREADS, T::WPE) void gemm_nt_dma_kernel(GemmDev g)
+{
+    gemm_nt_dma_body<T, INT8, false, KSPLIT>(g, (int)blockIdx.x);
+}
+
+// The two products of a linear layer's backward in one launch: workgroups [0, n0) are the grid of g0,
+// [n0_padded, ..) that of g1 (padded to a multiple of 8 so that a workgroup's number modulo 8 is its
+// XCD in both).  For layers whose products leave the chip half empty one at a time: see pair_plan.
+template <typename T, bool A_E5M2>
+__global__ __launch_bounds__(T::THREADS, T::WPE) void gemm_nt_dma_pair_kernel(GemmDev g0, GemmDev g1, int n0, int n0_padded)
+{
+    const int b = (int)blockIdx.x;
+    if (b >= n0 && b < n0_padded)
+        return;
+    const bool first = b < n0;
+    gemm_nt_dma_body<T, false, A_E5M2, 2>(first ? g0 : g1, first ? b : b - n0_padded);
 }
 
 // ---------------------------------------------------------------------------
@@ -1937,7 +1961,7 @@ static hipError_t launch_ksplit(const GemmArgs &a, hipStream_t s, int splits)
     static_assert(DMA || !INT8, "INT8 runs come from the direct-to-LDS kernel");
     void (*kern)(GemmDev);
     if constexpr (DMA)
-        kern = gemm_nt_dma_kernel<T, INT8, true>;
+        kern = gemm_nt_dma_kernel<T, INT8, 1>;
     else
         kern = gemm_nt_kernel<T, false, A_E5M2>;
     static bool attr_done = false;
@@ -2021,6 +2045,131 @@ static hipError_t launch_ksplit_defer(const GemmArgs &a, hipStream_t s, int spli
         hipLaunchKernelGGL(splitk_reduce_defer_kernel<INT8>, rgrid, dim3(256), 0, s, (const float4 *)g.ksplit_out, splits,
                            g.tiles_m, g.tiles_n, g.N, a.s0, a.s1, a.alpha, (uint16_t *)a.out);
     return hipGetLastError();
+}
+
+// Time of one gradient product by itself in microseconds, from what the kernels measured on layers of
+// 768 to 3072 columns over 8192 rows (within 10 %): two 128x128 tiles on a CU advance one 64-byte stage
+// in 0.74 us (a lone one in 0.5), a 256x256 tile of the deferred kernel a 128-byte stage in 1.25, of the
+// 8-wave kernel in 1.45; the register-staged kernel, which takes E5M2 operands where the deferred one
+// cannot, needs twice the 128x128 time; runs of a K split are written at 5 TB/s and read at 6.5.
+static double lone_gemm_us(int64_t M, int64_t N, int64_t K, bool e5m2)
+{
+    const double cus = num_cus(), kt = (double)(K + 127) / 128;
+    auto tiles = [](int64_t r, int64_t c, int64_t tr, int64_t tc) { return ((r + tr - 1) / tr) * ((c + tc - 1) / tc); };
+    const int ds = defer_ksplit(M, N, K);
+    if (ds > 1) {
+        const double mb = (double)ds * (double)M * (double)N * 4e-6;
+        return 1.3 * kt / ds + 3.0 + mb / 5.0 + 2.5 + mb / 6.5;
+    }
+    const int v = pick_variant(M, N, K);
+    if (v == 15 || v == 16)
+        return 1.25 * kt * (v == 16 ? 0.77 : 1.0) * std::ceil((double)tiles(M, N, v == 16 ? 192 : 256, 256) / cus) + 6.0;
+    if ((v == 11 || v == 14) && !e5m2)
+        return 1.45 * kt * (v == 14 ? 0.77 : 1.0) * std::ceil((double)tiles(M, N, v == 14 ? 192 : 256, 256) / cus) + 6.0;
+    const double t = (double)tiles(M, N, 128, 128);
+    const double us = (t <= cus ? 0.5 : 0.74 * std::ceil(t / (2.0 * cus))) * 2.0 * kt + 4.0;
+    return e5m2 ? 2.0 * us : us;
+}
+
+// The two gradient products of a layer in one launch of 128x128 tiles (gemm_nt_dma_pair_kernel), the
+// weight gradient's contraction in `splits` runs; 0 = the two run one after the other.  The pair fills
+// the chip where each alone would leave CUs idle, but its kernel is no fast one (0.92 us per 64-byte
+// stage of two tiles on a CU): taken where the two ways' times, estimated from those rates, say so.
+// 8192x768 -> 768: 40.5 us in three launches, 32.9 in two; 8192x3072 -> 768 stays apart (64 against 75).
+static int pair_splits(int64_t M, int64_t N, int64_t K, bool e5m2)
+{
+    if (g_tile_override != 0 || !g_stream_k_off || M % 64 != 0 || N % 64 != 0)
+        return 0;
+    auto tiles = [](int64_t r, int64_t c) { return ((r + 127) / 128) * ((c + 127) / 128); };
+    if (M * K <= 128 * 128 * 16 || N * K <= 128 * 128 * 16)
+        return 0;
+    const double slots = 2.0 * num_cus();
+    const int64_t kd = N / 64, kw = M / 64, td = tiles(M, K), tw = tiles(N, K);
+    int best = 0;
+    double best_us = 0.97 * (lone_gemm_us(M, K, N, e5m2) + lone_gemm_us(N, K, M, e5m2));
+    for (int s = 1; s <= 16 && kw / s >= 8; ++s) {
+        // stages per slot at two tiles to a CU, or the longest unit, which ends up alone on its CU; the
+        // uneven end; the runs' way through memory
+        const double longest = (double)std::max(kd, (kw + s - 1) / s), mb = s > 1 ? (double)s * (double)N * (double)K * 4e-6 : 0.0;
+        const double us = std::max(0.92 * (double)(td * kd + tw * kw) / slots, 0.62 * longest) + 0.15 * longest + 4.0 +
+                          (s > 1 ? mb / 6.5 + 2.5 : 0.0);
+        if (us < best_us) {
+            best_us = us;
+            best = s;
+        }
+    }
+    return best;
+}
+
+static size_t pair_bytes(int64_t N, int64_t K, int splits)
+{
+    return splits > 1 ? (size_t)splits * (size_t)N * (size_t)K * sizeof(float) : 0;
+}
+
+size_t fp8_pair_bytes(int64_t M, int64_t N, int64_t K)  // either gradient format
+{
+    return pair_bytes(N, K, std::max(pair_splits(M, N, K, false), pair_splits(M, N, K, true)));
+}
+
+template <bool A_E5M2>
+static hipError_t launch_pair(const GemmArgs &d, const GemmArgs &w, int splits, hipStream_t s)
+{
+    using T = D128x128w4;
+    constexpr auto kern = gemm_nt_dma_pair_kernel<T, A_E5M2>;
+    static bool attr_done = false;
+    if (!attr_done) {
+        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
+        if (e != hipSuccess)
+            return e;
+        attr_done = true;
+    }
+    auto dev = [](const GemmArgs &a, int ks) {
+        GemmDev g{};
+        g.A = a.A;
+        g.B = a.B;
+        g.M = (int)a.M;
+        g.N = (int)a.N;
+        g.K = (int)a.K;
+        g.s0 = a.s0;
+        g.s1 = a.s1;
+        g.out = (uint16_t *)a.out;
+        g.tiles_m = (int)((a.M + T::BM - 1) / T::BM);
+        g.tiles_n = (int)((a.N + T::BN - 1) / T::BN);
+        g.ksplit = ks;
+        g.ksplit_out = ks > 1 ? (float *)a.sk_workspace : nullptr;
+        return g;
+    };
+    GemmDev g0 = dev(d, 1), g1 = dev(w, splits);
+    if (g0.K < g1.K / splits)  // the longer units first
+        std::swap(g0, g1);
+    const int n0 = g0.tiles_m * g0.tiles_n * g0.ksplit, n1 = g1.tiles_m * g1.tiles_n * g1.ksplit;
+    const int n0_padded = (n0 + 7) / 8 * 8;
+    launch_gemm_kernel(kern, dim3((unsigned)(n0_padded + n1)), dim3(T::THREADS), T::LDS_BYTES, s, g0, g1, n0, n0_padded);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || splits == 1)
+        return e;
+    const int64_t mn = w.M * w.N;
+    launch_gemm_kernel(splitk_reduce_kernel<false>, dim3((unsigned)((mn / 8 + 255) / 256)), dim3(256), 0, s,
+                       (const float *)w.sk_workspace, splits, mn, w.s0, w.s1, 0.0f, (uint16_t *)w.out);
+    return hipGetLastError();
+}
+
+// both gradient products of a layer (d: [M, K] over N, w: [N, K] over M, no penalty, no residual)
+hipError_t launch_fp8_gemm_pair(const GemmArgs &d, const GemmArgs &w, hipStream_t s)
+{
+    int splits = pair_splits(d.M, d.K, d.N, d.a_e5m2);
+    // one after the other the weight gradient may overwrite what only the input gradient reads
+    auto overlap = [](const void *p, int64_t np, const void *q, int64_t nq) {
+        return (uintptr_t)p < (uintptr_t)q + (uint64_t)nq && (uintptr_t)q < (uintptr_t)p + (uint64_t)np;
+    };
+    if (overlap(w.out, w.M * w.N * 2, d.A, d.M * d.K) || overlap(w.out, w.M * w.N * 2, d.B, d.N * d.K))
+        splits = 0;
+    const bool fits = splits == 1 || (w.sk_workspace != nullptr && ((uintptr_t)w.sk_workspace & 15u) == 0 &&
+                                      w.sk_workspace_bytes >= pair_bytes(w.M, w.N, splits));
+    if (splits > 0 && fits)
+        return d.a_e5m2 ? launch_pair<true>(d, w, splits, s) : launch_pair<false>(d, w, splits, s);
+    const hipError_t e = launch_fp8_gemm(d, s);
+    return e != hipSuccess ? e : launch_fp8_gemm(w, s);
 }
 
 // E5M2 A operand (gradient GEMMs of the HYBRID recipe; no penalty, no residual): the deferred

@@ -120,6 +120,10 @@ struct GemmArgs {
 int fp8_gemm_partials(const GemmArgs &a);
 hipError_t launch_fp8_gemm(const GemmArgs &a, hipStream_t s);
 hipError_t launch_i8_gemm(const GemmArgs &a, hipStream_t s);
+// the two gradient products of a linear layer, in one launch where that is the faster way, and the
+// fp32 scratch that way needs (M, N, K of the layer)
+hipError_t launch_fp8_gemm_pair(const GemmArgs &dgrad, const GemmArgs &wgrad, hipStream_t s);
+size_t fp8_pair_bytes(int64_t M, int64_t N, int64_t K);
 
 // K split of tile-starved FP8 GEMMs (no penalty, no residual): number of runs (1 = none) and the
 // fp32 scratch they need; given through sk_workspace like the stream-K scratch, which it shares.

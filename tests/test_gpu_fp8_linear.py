@@ -443,3 +443,38 @@ def test_error_paths_need_no_launch():
     with pytest.raises(tw.TweoError) as e:
         tw.tweo_fp8_linear_fwd(q[:, :8].contiguous(), s, q[:, :8].contiguous(), s, y)
     assert e.value.status == tw.TWEO_ERR_UNSUPPORTED  # K % 16 != 0
+
+
+# both gradient products in one launch of 128x128 tiles: ragged in every direction, the weight
+# gradient's contraction in one run and in several, a stage count the runs do not divide
+@pytest.mark.parametrize("hybrid", [False, True])
+@pytest.mark.parametrize("shape", [(576, 640, 520), (3136, 704, 512), (1024, 1024, 1024), (4096, 576, 1032)])
+def test_bwd_of_narrow_layers_in_one_launch(shape, hybrid):
+    M, N, K = shape
+    say("bwd pair M=%d N=%d K=%d hybrid=%s" % (M, N, K, hybrid))
+    x, w, dy = synth.fp8_linear_inputs(1, 0, M=M, K=K, N=N)
+    xq, xqT, sxi = oracle_quantized(x)
+    wq, wqT, swi = oracle_quantized(w)
+    if hybrid:
+        s, sdi = oracle.scale_from_amax_e5m2(oracle.amax_bf16(dy))
+        dyq, dyqT = oracle.quantize_e5m2(dy, s)
+    else:
+        dyq, dyqT, sdi = oracle_quantized(dy)
+    args = [to_dev(np.ascontiguousarray(t)) for t in (dyq, dyqT, wqT, xqT)]
+    call = tw.tweo_fp8_linear_bwd_hybrid if hybrid else tw.tweo_fp8_linear_bwd
+    ws = workspace(tw.TWEO_OP_FP8_LINEAR_BWD, M, N, K)
+    outs = []
+    for wsp in (ws, ws, None):  # without a workspace the products may run one after the other
+        if wsp is not None:
+            wsp.fill_(0xFF)
+        dx = torch.full((M, K), float("nan"), dtype=torch.bfloat16, device=DEV)
+        dw = torch.full((N, K), float("nan"), dtype=torch.bfloat16, device=DEV)
+        call(args[0], args[1], scalar_f32(sdi), args[2], scalar_f32(swi), args[3], scalar_f32(sxi), M, N, K, dx, dw, wsp)
+        torch.cuda.synchronize()
+        outs.append((bf16_bits(dx), bf16_bits(dw)))
+    assert all(np.array_equal(a, b) for a, b in zip(outs[0], outs[1]))  # run-to-run identical
+    dxr, dxa = oracle.fp8_linear_dgrad(dyq, wq, sdi, swi, dy_e5m2=hybrid)
+    dwr, dwa = oracle.fp8_linear_wgrad(dyq, xq, sdi, sxi, dy_e5m2=hybrid)
+    for got in (outs[0], outs[2]):
+        check_gemm(got[0], dxr, dxa, N, "dgrad")
+        check_gemm(got[1], dwr, dwa, M, "wgrad")
