@@ -685,10 +685,10 @@ __device__ __forceinline__ void gemm_nt_dma_body(const GemmDev &g, const int blo
     }
 }
 
-template <typename T, bool INT8, int KSPLIT = 0>
+template <typename T, bool INT8, int KSPLIT = 0, bool A_E5M2 = false>
 __global__ __launch_bounds__(T::THREADS, T::WPE) void gemm_nt_dma_kernel(GemmDev g)
 {
-    gemm_nt_dma_body<T, INT8, false, KSPLIT>(g, (int)blockIdx.x);
+    gemm_nt_dma_body<T, INT8, A_E5M2, KSPLIT>(g, (int)blockIdx.x);
 }
 
 // The two products of a linear layer's backward in one launch: workgroups [0, n0) are the grid of g0,
@@ -762,7 +762,7 @@ struct TileS {
 // finished by a fixup at the very end of the kernel: a burst of device-scope slot traffic with
 // nothing left to hide it under; 192x256 tiles fix the common tile counts instead), so it is
 // off unless tweo_set_stream_k(1) asks for it; the parity tests keep it honest.
-template <typename T, bool INT8, bool SK>
+template <typename T, bool INT8, bool SK, bool A_E5M2 = false>
 __global__ __launch_bounds__(T::THREADS, T::WPE) void gemm_nt_stream_kernel(GemmDev g)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -856,7 +856,7 @@ __global__ __launch_bounds__(T::THREADS, T::WPE) void gemm_nt_stream_kernel(Gemm
                               f.a1[i][0], f.a1[i][1], f.a1[i][2], f.a1[i][3]};
                     v8i fb = {f.b0[j][0], f.b0[j][1], f.b0[j][2], f.b0[j][3],
                               f.b1[j][0], f.b1[j][1], f.b1[j][2], f.b1[j][3]};
-                    acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb, fa, acc[i][j], 0, 0,
+                    acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb, fa, acc[i][j], 0, A_E5M2 ? 1 : 0,
                                                                                 0, 0, 0, 0);
                 }
             }
@@ -893,7 +893,7 @@ __global__ __launch_bounds__(T::THREADS, T::WPE) void gemm_nt_stream_kernel(Gemm
                           cur.a1[i][0], cur.a1[i][1], cur.a1[i][2], cur.a1[i][3]};
                 v8i fb = {cur.b0[j][0], cur.b0[j][1], cur.b0[j][2], cur.b0[j][3],
                           cur.b1[j][0], cur.b1[j][1], cur.b1[j][2], cur.b1[j][3]};
-                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb, fa, acc[i][j], 0, 0, 0, 0,
+                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb, fa, acc[i][j], 0, A_E5M2 ? 1 : 0, 0, 0,
                                                                             0, 0);
             }
             if (k < T::MT) {
@@ -1632,7 +1632,7 @@ static hipError_t launch_tile(const GemmArgs &a, hipStream_t s)
     static bool attr_done = false;  // per instantiation
     const void *kern;
     if constexpr (DMA)
-        kern = (const void *)gemm_nt_dma_kernel<T, INT8>;
+        kern = (const void *)gemm_nt_dma_kernel<T, INT8, 0, A_E5M2>;
     else
         kern = (const void *)gemm_nt_kernel<T, INT8, A_E5M2>;
     if (!attr_done) {
@@ -1668,7 +1668,7 @@ static hipError_t launch_tile(const GemmArgs &a, hipStream_t s)
     g.tiles_n = (int)((a.N + T::BN - 1) / T::BN);
     const dim3 grid((unsigned)(g.tiles_m * g.tiles_n)), block(T::THREADS);
     if constexpr (DMA)
-        launch_gemm_kernel(gemm_nt_dma_kernel<T, INT8>, grid, block, T::LDS_BYTES, s, g);
+        launch_gemm_kernel(gemm_nt_dma_kernel<T, INT8, 0, A_E5M2>, grid, block, T::LDS_BYTES, s, g);
     else
         launch_gemm_kernel(gemm_nt_kernel<T, INT8, A_E5M2>, grid, block, T::LDS_BYTES, s, g);
     return hipGetLastError();
@@ -1693,12 +1693,12 @@ static bool stream_k_plan(int64_t total_tiles, int64_t kt, int grid, const GemmA
            ((uintptr_t)a.sk_workspace & 255u) == 0;
 }
 
-template <typename T, bool INT8, int WG_PER_CU, bool SK>
+template <typename T, bool INT8, int WG_PER_CU, bool SK, bool A_E5M2 = false>
 static hipError_t launch_stream_inst(const GemmArgs &a, hipStream_t s, int grid, int full_rounds)
 {
     static bool attr_done = false;
     if (!attr_done) {
-        hipError_t e = hipFuncSetAttribute((const void *)gemm_nt_stream_kernel<T, INT8, SK>,
+        hipError_t e = hipFuncSetAttribute((const void *)gemm_nt_stream_kernel<T, INT8, SK, A_E5M2>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
         if (e != hipSuccess)
             return e;
@@ -1736,18 +1736,18 @@ static hipError_t launch_stream_inst(const GemmArgs &a, hipStream_t s, int grid,
         if (e != hipSuccess)
             return e;
     }
-    launch_gemm_kernel(gemm_nt_stream_kernel<T, INT8, SK>, dim3((unsigned)grid), dim3(T::THREADS), T::LDS_BYTES, s, g);
+    launch_gemm_kernel(gemm_nt_stream_kernel<T, INT8, SK, A_E5M2>, dim3((unsigned)grid), dim3(T::THREADS), T::LDS_BYTES, s, g);
     return hipGetLastError();
 }
 
-template <typename T, bool INT8, int WG_PER_CU>
+template <typename T, bool INT8, int WG_PER_CU, bool A_E5M2 = false>
 static hipError_t launch_stream(const GemmArgs &a, hipStream_t s)
 {
     const int64_t total = ((a.M + T::BM - 1) / T::BM) * ((a.N + T::BN - 1) / T::BN);
     int grid = num_cus() * WG_PER_CU;
     if (grid > total)
         grid = (int)total;
-    if constexpr (WG_PER_CU == 1) {
+    if constexpr (WG_PER_CU == 1 && !A_E5M2) {
         // stream-K always runs one workgroup on every CU (with fewer tiles than CUs the split
         // remainder is the whole job)
         int full_rounds = 0;
@@ -1756,7 +1756,7 @@ static hipError_t launch_stream(const GemmArgs &a, hipStream_t s)
             stream_k_plan(total, a.K / T::BK, cus, a, (size_t)T::BM * T::BN * 4, full_rounds))
             return launch_stream_inst<T, INT8, WG_PER_CU, true>(a, s, cus, full_rounds);
     }
-    return launch_stream_inst<T, INT8, WG_PER_CU, false>(a, s, grid, 0);
+    return launch_stream_inst<T, INT8, WG_PER_CU, false, A_E5M2>(a, s, grid, 0);
 }
 
 template <bool INT8, int PMODE, int D, int MT, bool A_E5M2 = false, bool RES = false>
@@ -1952,16 +1952,14 @@ size_t fp8_gemm_ksplit_bytes(int64_t M, int64_t N, int64_t K)
     return splits > 1 ? (size_t)splits * (size_t)M * (size_t)N * sizeof(float) : 0;
 }
 
-// DMA: the direct-to-LDS kernel on 64-byte stages (K % 64 == 0, E4M3 or INT8 operands), else the
-// register-staged one.
+// DMA: the direct-to-LDS kernel on 64-byte stages (K % 64 == 0), else the register-staged one.
 template <typename T, bool A_E5M2, bool DMA, bool INT8 = false>
 static hipError_t launch_ksplit(const GemmArgs &a, hipStream_t s, int splits)
 {
-    static_assert(!(DMA && A_E5M2), "the direct-to-LDS kernel takes E4M3 operands only");
     static_assert(DMA || !INT8, "INT8 runs come from the direct-to-LDS kernel");
     void (*kern)(GemmDev);
     if constexpr (DMA)
-        kern = gemm_nt_dma_kernel<T, INT8, 1>;
+        kern = gemm_nt_dma_kernel<T, INT8, 1, A_E5M2>;
     else
         kern = gemm_nt_kernel<T, false, A_E5M2>;
     static bool attr_done = false;
@@ -2050,9 +2048,8 @@ static hipError_t launch_ksplit_defer(const GemmArgs &a, hipStream_t s, int spli
 // Time of one gradient product by itself in microseconds, from what the kernels measured on layers of
 // 768 to 3072 columns over 8192 rows (within 10 %): two 128x128 tiles on a CU advance one 64-byte stage
 // in 0.74 us (a lone one in 0.5), a 256x256 tile of the deferred kernel a 128-byte stage in 1.25, of the
-// 8-wave kernel in 1.45; the register-staged kernel, which takes E5M2 operands where the deferred one
-// cannot, needs twice the 128x128 time; runs of a K split are written at 5 TB/s and read at 6.5.
-static double lone_gemm_us(int64_t M, int64_t N, int64_t K, bool e5m2)
+// 8-wave kernel in 1.45; runs of a K split are written at 5 TB/s and read at 6.5.
+static double lone_gemm_us(int64_t M, int64_t N, int64_t K)
 {
     const double cus = num_cus(), kt = (double)(K + 127) / 128;
     auto tiles = [](int64_t r, int64_t c, int64_t tr, int64_t tc) { return ((r + tr - 1) / tr) * ((c + tc - 1) / tc); };
@@ -2064,11 +2061,10 @@ static double lone_gemm_us(int64_t M, int64_t N, int64_t K, bool e5m2)
     const int v = pick_variant(M, N, K);
     if (v == 15 || v == 16)
         return 1.25 * kt * (v == 16 ? 0.77 : 1.0) * std::ceil((double)tiles(M, N, v == 16 ? 192 : 256, 256) / cus) + 6.0;
-    if ((v == 11 || v == 14) && !e5m2)
+    if (v == 11 || v == 14)
         return 1.45 * kt * (v == 14 ? 0.77 : 1.0) * std::ceil((double)tiles(M, N, v == 14 ? 192 : 256, 256) / cus) + 6.0;
     const double t = (double)tiles(M, N, 128, 128);
-    const double us = (t <= cus ? 0.5 : 0.74 * std::ceil(t / (2.0 * cus))) * 2.0 * kt + 4.0;
-    return e5m2 ? 2.0 * us : us;
+    return (t <= cus ? 0.5 : 0.74 * std::ceil(t / (2.0 * cus))) * 2.0 * kt + 4.0;
 }
 
 // The two gradient products of a layer in one launch of 128x128 tiles (gemm_nt_dma_pair_kernel), the
@@ -2076,7 +2072,7 @@ static double lone_gemm_us(int64_t M, int64_t N, int64_t K, bool e5m2)
 // the chip where each alone would leave CUs idle, but its kernel is no fast one (0.92 us per 64-byte
 // stage of two tiles on a CU): taken where the two ways' times, estimated from those rates, say so.
 // 8192x768 -> 768: 40.5 us in three launches, 32.9 in two; 8192x3072 -> 768 stays apart (64 against 75).
-static int pair_splits(int64_t M, int64_t N, int64_t K, bool e5m2)
+static int pair_splits(int64_t M, int64_t N, int64_t K)
 {
     if (g_tile_override != 0 || !g_stream_k_off || M % 64 != 0 || N % 64 != 0)
         return 0;
@@ -2086,7 +2082,7 @@ static int pair_splits(int64_t M, int64_t N, int64_t K, bool e5m2)
     const double slots = 2.0 * num_cus();
     const int64_t kd = N / 64, kw = M / 64, td = tiles(M, K), tw = tiles(N, K);
     int best = 0;
-    double best_us = 0.97 * (lone_gemm_us(M, K, N, e5m2) + lone_gemm_us(N, K, M, e5m2));
+    double best_us = 0.97 * (lone_gemm_us(M, K, N) + lone_gemm_us(N, K, M));
     for (int s = 1; s <= 16 && kw / s >= 8; ++s) {
         // stages per slot at two tiles to a CU, or the longest unit, which ends up alone on its CU; the
         // uneven end; the runs' way through memory
@@ -2106,10 +2102,7 @@ static size_t pair_bytes(int64_t N, int64_t K, int splits)
     return splits > 1 ? (size_t)splits * (size_t)N * (size_t)K * sizeof(float) : 0;
 }
 
-size_t fp8_pair_bytes(int64_t M, int64_t N, int64_t K)  // either gradient format
-{
-    return pair_bytes(N, K, std::max(pair_splits(M, N, K, false), pair_splits(M, N, K, true)));
-}
+size_t fp8_pair_bytes(int64_t M, int64_t N, int64_t K) { return pair_bytes(N, K, pair_splits(M, N, K)); }
 
 template <bool A_E5M2>
 static hipError_t launch_pair(const GemmArgs &d, const GemmArgs &w, int splits, hipStream_t s)
@@ -2157,7 +2150,7 @@ static hipError_t launch_pair(const GemmArgs &d, const GemmArgs &w, int splits, 
 // both gradient products of a layer (d: [M, K] over N, w: [N, K] over M, no penalty, no residual)
 hipError_t launch_fp8_gemm_pair(const GemmArgs &d, const GemmArgs &w, hipStream_t s)
 {
-    int splits = pair_splits(d.M, d.K, d.N, d.a_e5m2);
+    int splits = pair_splits(d.M, d.K, d.N);
     // one after the other the weight gradient may overwrite what only the input gradient reads
     auto overlap = [](const void *p, int64_t np, const void *q, int64_t nq) {
         return (uintptr_t)p < (uintptr_t)q + (uint64_t)nq && (uintptr_t)q < (uintptr_t)p + (uint64_t)np;
@@ -2172,14 +2165,22 @@ hipError_t launch_fp8_gemm_pair(const GemmArgs &d, const GemmArgs &w, hipStream_
     return e != hipSuccess ? e : launch_fp8_gemm(w, s);
 }
 
-// E5M2 A operand (gradient GEMMs of the HYBRID recipe; no penalty, no residual): the deferred
-// kernel where it applies, else the register-staged kernel.
+// E5M2 A operand (gradient GEMMs of the HYBRID recipe; no penalty, no residual): the kernels that the
+// same product of E4M3 codes runs on, except that K in neither whole 64-byte stages nor few elements
+// goes to the register-staged 256x256 tiles.  (The streaming and direct-to-LDS kernels did not take
+// E5M2 before and everything but the deferred kernel's shapes ran register-staged; delayed scaling,
+// forward + backward: 8192x3072 -> 768 155 -> 137 us, 22480x512 -> 512 139 -> 119.)
 static hipError_t launch_fp8_gemm_e5m2(const GemmArgs &a, hipStream_t s)
 {
     if (a.p != 0 || a.residual != nullptr)
         return hipErrorInvalidValue;
-    const int v = resolve_variant(a);
-    if (v == 15) {
+    switch (resolve_variant(a)) {
+    case 6: return launch_tile<D256x256w8, false, true, true>(a, s);
+    case 8: return launch_tile<D128x128w4, false, true, true>(a, s);
+    case 11: return launch_stream<S256x256w8, false, 1, true>(a, s);
+    case 13: return launch_stream<S128x128w4, false, 2, true>(a, s);
+    case 14: return launch_stream<S192x256w8, false, 1, true>(a, s);
+    case 15: {
         const int64_t kt = a.K / 128;
         if (kt >= 16)
             return launch_defer_inst<false, 0, 15, 4, true>(a, s);
@@ -2187,8 +2188,9 @@ static hipError_t launch_fp8_gemm_e5m2(const GemmArgs &a, hipStream_t s)
             return launch_defer_inst<false, 0, 7, 4, true>(a, s);
         return kt >= 6 ? launch_defer_inst<false, 0, 5, 4, true>(a, s) : launch_defer_inst<false, 0, 3, 4, true>(a, s);
     }
-    if (v == 16)
-        return launch_defer_inst<false, 0, 15, 3, true>(a, s);
+    case 16: return launch_defer_inst<false, 0, 15, 3, true>(a, s);
+    default: break;
+    }
     if (a.M * a.N <= 128 * 128 * 16)
         return launch_tile<T64x64, false, false, true>(a, s);
     if (a.M * a.N <= 1024 * 1024)
@@ -2206,7 +2208,8 @@ hipError_t launch_fp8_gemm(const GemmArgs &a, hipStream_t s)
             if (defer_ksplit(a.M, a.N, a.K) > 1)
                 return a.a_e5m2 ? launch_ksplit_defer<true>(a, s, splits) : launch_ksplit_defer<false>(a, s, splits);
             if (a.a_e5m2)
-                return launch_ksplit<T256x256, true, false>(a, s, splits);
+                return a.K % 64 == 0 ? launch_ksplit<D256x256w8, true, true>(a, s, splits)
+                                     : launch_ksplit<T256x256, true, false>(a, s, splits);
             return a.K % 64 == 0 ? launch_ksplit<D256x256w8, false, true>(a, s, splits)
                                  : launch_ksplit<T256x256, false, false>(a, s, splits);
         }

@@ -227,3 +227,37 @@ def test_backward_with_fused_penalty_gradient_injection(e5m2, pen):
         assert sc[7] == s_ref and sc[8] == si_ref
         assert np.mean(dyq.cpu().numpy() == q_ref) > 0.99 and np.mean(dyqT.cpu().numpy() == qT_ref) > 0.99
         assert np.array_equal(dyqT.cpu().numpy(), dyq.cpu().numpy().T)
+
+
+# E5M2 gradients on every kernel that the same product of E4M3 codes can run on: whole 128-byte stages
+# (11, 13, 14), whole 64-byte stages (6, 8), K split of ragged tiles (no override), ragged rows and columns
+@pytest.mark.parametrize("tile,shape", [(11, (384, 640, 520)), (13, (384, 640, 520)), (14, (640, 384, 264)), (6, (448, 576, 520)),
+                                        (8, (448, 576, 520)), (0, (16448, 200 // 8 * 8, 264)), (0, (2048, 336, 136)),
+                                        (0, (96, 1872, 1120))])
+def test_e5m2_gradients_on_the_tiled_kernels(tile, shape):
+    M, N, K = shape
+    N = (N + 15) // 16 * 16
+    say("e5m2 tile=%d M=%d N=%d K=%d" % (tile, M, N, K))
+    x, w, dy = synth.fp8_linear_inputs(1, 0, M=M, K=K, N=N)
+    sx, sxi = oracle.scale_from_amax(oracle.amax_bf16(x))
+    sw, swi = oracle.scale_from_amax(oracle.amax_bf16(w))
+    sd, sdi = oracle.scale_from_amax_e5m2(oracle.amax_bf16(dy))
+    xq, xqT = oracle.quantize_e4m3(x, sx)
+    wq, wqT = oracle.quantize_e4m3(w, sw)
+    dyq, dyqT = oracle.quantize_e5m2(dy, sd)
+    ws = workspace(tw.TWEO_OP_FP8_LINEAR_BWD, M, N, K)
+    dx = torch.full((M, K), float("nan"), dtype=torch.bfloat16, device=DEV)
+    dw = torch.full((N, K), float("nan"), dtype=torch.bfloat16, device=DEV)
+    d = [to_dev(np.ascontiguousarray(t)) for t in (dyq, dyqT, wqT, xqT)]
+    tw.tweo_set_gemm_tile(tile)
+    try:
+        for out in (dict(dx_bf16=dx), dict(dw_bf16=dw)):  # one product at a time
+            tw.tweo_fp8_linear_bwd_hybrid(d[0], d[1], scalar_f32(sdi), d[2], scalar_f32(swi), d[3], scalar_f32(sxi), M, N, K,
+                                          workspace=ws, **out)
+        torch.cuda.synchronize()
+    finally:
+        tw.tweo_set_gemm_tile(0)
+    ref, refabs = oracle.fp8_linear_dgrad(dyq, wq, sdi, swi, dy_e5m2=True)
+    check_gemm(bf16_bits(dx), ref, refabs, N, "dgrad")
+    ref, refabs = oracle.fp8_linear_wgrad(dyq, xq, sdi, sxi, dy_e5m2=True)
+    check_gemm(bf16_bits(dw), ref, refabs, M, "wgrad")
