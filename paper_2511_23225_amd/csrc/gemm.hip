@@ -333,11 +333,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_nt_kernel(GemmDev g)
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     const int wm = wave / T::WN, wn = wave % T::WN;
     int tm, tn;
-    // with a K split the grid is ksplit runs of the tile grid: run `split` takes K stages
-    // [split * k_tiles / ksplit, (split + 1) * k_tiles / ksplit)
-    const int n_tiles = g.tiles_m * g.tiles_n;
-    const int split = g.ksplit > 1 ? (int)blockIdx.x / n_tiles : 0;
-    tile_of_workgroup((int)blockIdx.x - split * n_tiles, g.tiles_m, g.tiles_n, tm, tn);
+    tile_of_workgroup((int)blockIdx.x, g.tiles_m, g.tiles_n, tm, tn);
 
     // ---- global -> register -> LDS staging --------------------------------
     // chunk id = tid + i*THREADS : row = id/8, chunk-in-row = id%8 (same for all i)
@@ -456,30 +452,19 @@ __global__ __launch_bounds__(T::THREADS) void gemm_nt_kernel(GemmDev g)
 
     // ---- main loop ----------------------------------------------------------
     const int k_tiles = (g.K + kBK - 1) / kBK;
-    int kt_begin = 0, kt_end = k_tiles;
-    if (g.ksplit > 1) {
-        kt_begin = (int)((int64_t)split * k_tiles / g.ksplit);
-        kt_end = (int)((int64_t)(split + 1) * k_tiles / g.ksplit);
-    }
-    load_global(kt_begin * kBK);
+    load_global(0);
     store_lds(0);
     __syncthreads();
-    for (int kt = kt_begin; kt < kt_end; ++kt) {
-        const bool more = kt + 1 < kt_end;
+    for (int kt = 0; kt < k_tiles; ++kt) {
+        const bool more = kt + 1 < k_tiles;
         if (more)
             load_global((kt + 1) * kBK);
-        compute_stage((kt - kt_begin) & 1);
+        compute_stage(kt & 1);
         if (more)
-            store_lds((kt - kt_begin + 1) & 1);
+            store_lds((kt + 1) & 1);
         __syncthreads();
     }
 
-    if constexpr (!INT8) {
-        if (g.ksplit > 1) {
-            store_ksplit_run<T>(g, acc, split, tm, tn, wm, wn, l31, lh);
-            return;
-        }
-    }
     // the loop ends with a barrier: every wave is done reading the stages
     NoBandHook no_hook;
     epilogue<T, INT8>(g, acc, smem, tm, tn, wm, wn, lane, wave, tid, blockIdx.x, no_hook);
@@ -489,7 +474,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_nt_kernel(GemmDev g)
 // Pipelined kernel: global -> LDS by direct DMA loads (global_load_lds_dwordx4,
 // no staging registers), NS stages of 64 bytes of K each, one workgroup barrier
 // per stage, MFMA operand fragments double-buffered in registers so that the
-// LDS reads of stage s+1 run under the MFMAs of stage s.  Needs K % 64 == 0.
+// LDS reads of stage s+1 run under the MFMAs of stage s.  K in multiples of 16.
 //
 // LDS layout of a stage: BM rows of A then BN rows of B, 64 bytes per row, the
 // four 16-byte chunks of a row XOR-swizzled with (row/4)%4: 16 consecutive rows
@@ -530,11 +515,19 @@ __device__ __forceinline__ void gemm_nt_dma_body(const GemmDev &g, const int blo
     const int n_tiles = g.tiles_m * g.tiles_n;
     const int split = KSPLIT != 0 ? block / n_tiles : 0;
     tile_of_workgroup(block - split * n_tiles, g.tiles_m, g.tiles_n, tm, tn);
-    int kt = g.K / T::BK, kt_begin = 0;
+    int kt = (g.K + T::BK - 1) / T::BK, kt_begin = 0;
+    const int kt_all = kt;
     if (KSPLIT != 0) {
         kt_begin = (int)((int64_t)split * kt / g.ksplit);
         kt = (int)((int64_t)(split + 1) * kt / g.ksplit) - kt_begin;
     }
+
+    // K % 64 != 0 (a multiple of 16): the last stage of the contraction holds `tail` chunks of 16 bytes.
+    // The lanes of the chunks past them load their row's first chunk of K instead, and the A fragments
+    // of those chunks are cleared: 0 times any code of that row of B but a NaN, which makes the whole
+    // column a NaN anyway.
+    const int tail = (g.K & (T::BK - 1)) >> 4;
+    const bool ragged = tail != 0 && kt_begin + kt == kt_all;
 
     // ---- DMA addressing -----------------------------------------------------
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)smem;
@@ -567,6 +560,29 @@ __device__ __forceinline__ void gemm_nt_dma_body(const GemmDev &g, const int blo
             dma_load16(dst + T::A_BYTES + i * T::NWAVES * 1024, bp, b_voff[i]);
     };
 
+    auto issue_last_stage = [&](int s) {
+        const uint32_t dst = lds_base + (s % T::NS) * T::STAGE_BYTES + wave * 1024;
+        const uint8_t *ap = Ag + (int64_t)s * T::BK, *bp = Bg + (int64_t)s * T::BK;
+        // chunks past the end: back to the start of the row
+        const int back = (kt_begin + s) * T::BK;
+#pragma unroll
+        for (int i = 0; i < T::A_DMA; ++i) {
+            const int row = (i * T::NWAVES + wave) * 16 + (lane >> 2), c = (lane & 3) ^ ((row >> 2) & 3);
+            dma_load16(dst + i * T::NWAVES * 1024, ap - back, a_voff[i] + (c < tail ? back : -c * 16));
+        }
+#pragma unroll
+        for (int i = 0; i < T::B_DMA; ++i) {
+            const int row = (i * T::NWAVES + wave) * 16 + (lane >> 2), c = (lane & 3) ^ ((row >> 2) & 3);
+            dma_load16(dst + T::A_BYTES + i * T::NWAVES * 1024, bp - back, b_voff[i] + (c < tail ? back : -c * 16));
+        }
+    };
+    auto issue_any_stage = [&](int s) {
+        if (ragged && s == kt - 1)
+            issue_last_stage(s);
+        else
+            issue_stage(s);
+    };
+
     // ---- fragments ------------------------------------------------------------
     const int l31 = lane & 31, lh = lane >> 5;
     const int sw = (l31 >> 2) & 3;
@@ -589,6 +605,16 @@ __device__ __forceinline__ void gemm_nt_dma_body(const GemmDev &g, const int blo
         for (int j = 0; j < T::NT; ++j) {
             f.b0[j] = *(const v4i *)(st + b_frag0 + j * 32 * T::BK + off0);
             f.b1[j] = *(const v4i *)(st + b_frag0 + j * 32 * T::BK + off1);
+        }
+    };
+    auto load_any_frags = [&](Frag &f, int s) {
+        load_frags(f, s);
+        if (ragged && s == kt - 1) {
+#pragma unroll
+            for (int i = 0; i < T::MT; ++i) {
+                f.a0[i] = c0 < tail ? f.a0[i] : v4i{0, 0, 0, 0};
+                f.a1[i] = c1 < tail ? f.a1[i] : v4i{0, 0, 0, 0};
+            }
         }
     };
     using acc_t = typename std::conditional<INT8, v16i, v16f>::type;
@@ -624,14 +650,14 @@ __device__ __forceinline__ void gemm_nt_dma_body(const GemmDev &g, const int blo
 #pragma unroll
     for (int s = 0; s < T::NS - 1; ++s)
         if (s < kt)
-            issue_stage(s);
+            issue_any_stage(s);
     if (kt >= T::NS - 1)
         wait_vmcnt<T::LOADS *(T::NS - 2)>();
     else
         wait_vmcnt<0>();
     block_barrier();
     Frag fr[2];
-    load_frags(fr[0], 0);
+    load_any_frags(fr[0], 0);
     // Steady state: stage ss with ss + NS - 1 < kt.  Two stages per trip so that the two
     // fragment buffers have fixed names; the body is one basic block (no conditions), which
     // lets the scheduler run the LDS reads of stage ss+1 under the MFMAs of stage ss.
@@ -658,13 +684,13 @@ __device__ __forceinline__ void gemm_nt_dma_body(const GemmDev &g, const int blo
             wait_vmcnt<0>();
             block_barrier();
             if (ss + T::NS - 1 < kt)
-                issue_stage(ss + T::NS - 1);
-            load_frags(nxt, ss + 1);
+                issue_any_stage(ss + T::NS - 1);
+            load_any_frags(nxt, ss + 1);
         }
         mfma_stage(cur);
     };
     int s = 0;
-    const int steady_end = kt - (T::NS - 1);
+    const int steady_end = kt - (T::NS - 1) - (ragged ? 1 : 0);  // a ragged stage is issued by the tail
     for (; s + 1 < steady_end; s += 2) {
         steady_step(s, fr[0], fr[1]);
         steady_step(s + 1, fr[1], fr[0]);
@@ -1491,7 +1517,7 @@ size_t stream_k_workspace_bytes()
 
 // Kernel variants (the numbers are what tweo_set_gemm_tile takes; retired ones are refused).
 // 1, 3, 4: register-staged kernel (any K % 16 == 0), tiles 256x256, 128x128, 64x64.  6, 8:
-// DMA-pipelined kernel on 64-byte stages (K % 64 == 0), 256x256 with 8 waves and 128x128.  11, 13,
+// DMA-pipelined kernel on 64-byte stages, 256x256 with 8 waves and 128x128.  11, 13,
 // 14: persistent streaming kernel (K % 128 == 0): 256x256, 128x128, 192x256.  15: deferred-epilogue
 // persistent kernel (256x256, four waves; M, N % 256 == 0, K % 128 == 0, K >= 512).  16: the same
 // kernel on 192x256 tiles (any M, K >= 2048).  17: the INT8 weight-streaming kernel (M <= 128).
@@ -1583,14 +1609,12 @@ static int pick_variant(int64_t M, int64_t N, int64_t K)
             // kernel with its four-stage ring is 10-15 % ahead (weight gradients of narrow layers);
             // with more tiles than CUs it falls behind (INT8, 12288 wide over 4096 at M = 384 / 512:
             // 39 / 47 us against 32 / 37)
-            if (v == 13 && K >= 4096 && K % 64 == 0 && tiles(128, 128) <= (int64_t)cus)
+            if (v == 13 && K >= 4096 && tiles(128, 128) <= (int64_t)cus)
                 v = 8;
         }
     }
     if (v >= 11 && K % 128 != 0)  // the persistent kernels need whole 128-byte stages
         v = v == 13 ? 8 : 6;
-    if (v >= 5 && K % 64 != 0)
-        v = v == 6 ? 1 : 3;
     return v;
 }
 
@@ -1920,9 +1944,9 @@ int fp8_gemm_ksplit(int64_t M, int64_t N, int64_t K)
 // 5632 -> 2048 at M = 300: 26.2 -> 18.6.
 static int i8_dma_ksplit(int64_t M, int64_t N, int64_t K)
 {
-    if (g_tile_override != 0 || K % 64 != 0 || N % 8 != 0 || M <= 128)
+    if (g_tile_override != 0 || N % 8 != 0 || M <= 128)
         return 1;
-    const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128), kt = K / 64, cus = num_cus();
+    const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128), kt = (K + 63) / 64, cus = num_cus();
     if (tiles * 2 > cus)
         return 1;
     int best = 1;
@@ -1952,16 +1976,11 @@ size_t fp8_gemm_ksplit_bytes(int64_t M, int64_t N, int64_t K)
     return splits > 1 ? (size_t)splits * (size_t)M * (size_t)N * sizeof(float) : 0;
 }
 
-// DMA: the direct-to-LDS kernel on 64-byte stages (K % 64 == 0), else the register-staged one.
-template <typename T, bool A_E5M2, bool DMA, bool INT8 = false>
+// On the direct-to-LDS kernel.
+template <typename T, bool A_E5M2, bool INT8 = false>
 static hipError_t launch_ksplit(const GemmArgs &a, hipStream_t s, int splits)
 {
-    static_assert(DMA || !INT8, "INT8 runs come from the direct-to-LDS kernel");
-    void (*kern)(GemmDev);
-    if constexpr (DMA)
-        kern = gemm_nt_dma_kernel<T, INT8, 1, A_E5M2>;
-    else
-        kern = gemm_nt_kernel<T, false, A_E5M2>;
+    constexpr auto kern = gemm_nt_dma_kernel<T, INT8, 1, A_E5M2>;
     static bool attr_done = false;
     if (!attr_done) {
         hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
@@ -2074,13 +2093,13 @@ static double lone_gemm_us(int64_t M, int64_t N, int64_t K)
 // 8192x768 -> 768: 40.5 us in three launches, 32.9 in two; 8192x3072 -> 768 stays apart (64 against 75).
 static int pair_splits(int64_t M, int64_t N, int64_t K)
 {
-    if (g_tile_override != 0 || !g_stream_k_off || M % 64 != 0 || N % 64 != 0)
+    if (g_tile_override != 0 || !g_stream_k_off)
         return 0;
     auto tiles = [](int64_t r, int64_t c) { return ((r + 127) / 128) * ((c + 127) / 128); };
     if (M * K <= 128 * 128 * 16 || N * K <= 128 * 128 * 16)
         return 0;
     const double slots = 2.0 * num_cus();
-    const int64_t kd = N / 64, kw = M / 64, td = tiles(M, K), tw = tiles(N, K);
+    const int64_t kd = (N + 63) / 64, kw = (M + 63) / 64, td = tiles(M, K), tw = tiles(N, K);
     int best = 0;
     double best_us = 0.97 * (lone_gemm_us(M, K, N) + lone_gemm_us(N, K, M));
     for (int s = 1; s <= 16 && kw / s >= 8; ++s) {
@@ -2166,8 +2185,7 @@ hipError_t launch_fp8_gemm_pair(const GemmArgs &d, const GemmArgs &w, hipStream_
 }
 
 // E5M2 A operand (gradient GEMMs of the HYBRID recipe; no penalty, no residual): the kernels that the
-// same product of E4M3 codes runs on, except that K in neither whole 64-byte stages nor few elements
-// goes to the register-staged 256x256 tiles.  (The streaming and direct-to-LDS kernels did not take
+// same product of E4M3 codes runs on.  (The streaming and direct-to-LDS kernels did not take
 // E5M2 before and everything but the deferred kernel's shapes ran register-staged; delayed scaling,
 // forward + backward: 8192x3072 -> 768 155 -> 137 us, 22480x512 -> 512 139 -> 119.)
 static hipError_t launch_fp8_gemm_e5m2(const GemmArgs &a, hipStream_t s)
@@ -2207,11 +2225,7 @@ hipError_t launch_fp8_gemm(const GemmArgs &a, hipStream_t s)
         {
             if (defer_ksplit(a.M, a.N, a.K) > 1)
                 return a.a_e5m2 ? launch_ksplit_defer<true>(a, s, splits) : launch_ksplit_defer<false>(a, s, splits);
-            if (a.a_e5m2)
-                return a.K % 64 == 0 ? launch_ksplit<D256x256w8, true, true>(a, s, splits)
-                                     : launch_ksplit<T256x256, true, false>(a, s, splits);
-            return a.K % 64 == 0 ? launch_ksplit<D256x256w8, false, true>(a, s, splits)
-                                 : launch_ksplit<T256x256, false, false>(a, s, splits);
+            return a.a_e5m2 ? launch_ksplit<D256x256w8, true>(a, s, splits) : launch_ksplit<D256x256w8, false>(a, s, splits);
         }
     }
     return a.a_e5m2 ? launch_fp8_gemm_e5m2(a, s) : launch_gemm<false>(a, s);
@@ -2320,7 +2334,7 @@ hipError_t launch_i8_gemm(const GemmArgs &a, hipStream_t s)
         const int runs = i8_dma_ksplit(a.M, a.N, a.K);
         if (runs > 1 && a.sk_workspace != nullptr && ((uintptr_t)a.sk_workspace & 15u) == 0 &&
             a.sk_workspace_bytes >= (size_t)runs * (size_t)a.M * (size_t)a.N * sizeof(int32_t))
-            return launch_ksplit<D128x128w4, false, true, true>(a, s, runs);
+            return launch_ksplit<D128x128w4, false, true>(a, s, runs);
     }
     return launch_gemm<true>(a, s);
 }

@@ -30,9 +30,8 @@ struct GemmDev {
     // with step vectors only: out holds int8 [M,N] = clamp(rne(y * out_inv_step), +-127) instead of bf16
     int out_i8;
     float out_inv_step;
-    // K split (register-staged FP8 kernel only): ksplit > 1 workgroups share a tile, workgroup
-    // `split` multiplies its run of K stages and stores the fp32 sums to
-    // ksplit_out[split][M][N]; a second kernel adds the runs in order and rounds
+    // K split: ksplit > 1 workgroups share a tile, workgroup `split` multiplies its run of K stages and
+    // stores the fp32 (INT8: int32) sums to ksplit_out; a second kernel adds the runs in order and rounds
     int ksplit;
     float *ksplit_out;
 };

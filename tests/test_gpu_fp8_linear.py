@@ -450,6 +450,10 @@ def test_error_paths_need_no_launch():
 @pytest.mark.parametrize("hybrid", [False, True])
 @pytest.mark.parametrize("shape", [(576, 640, 520), (3136, 704, 512), (1024, 1024, 1024), (4096, 576, 1032)])
 def test_bwd_of_narrow_layers_in_one_launch(shape, hybrid):
+    check_bwd_pair(shape, hybrid)
+
+
+def check_bwd_pair(shape, hybrid):
     M, N, K = shape
     say("bwd pair M=%d N=%d K=%d hybrid=%s" % (M, N, K, hybrid))
     x, w, dy = synth.fp8_linear_inputs(1, 0, M=M, K=K, N=N)
@@ -478,3 +482,37 @@ def test_bwd_of_narrow_layers_in_one_launch(shape, hybrid):
     for got in (outs[0], outs[2]):
         check_gemm(got[0], dxr, dxa, N, "dgrad")
         check_gemm(got[1], dwr, dwa, M, "wgrad")
+
+
+# the direct-to-LDS kernels under a contraction that ends inside a 64-byte stage: one to three chunks of
+# 16 in the last stage, fewer stages than the ring, one more and many
+@pytest.mark.parametrize("tile", [6, 8])
+@pytest.mark.parametrize("K", [16, 48, 80, 176, 208, 272, 1056, 2064])
+def test_fwd_contraction_ends_inside_a_stage(tile, K):
+    M, N = 200, 264
+    say("fwd ragged K=%d tile=%d" % (K, tile))
+    x, w, _ = synth.fp8_linear_inputs(1, 0, M=M, K=K, N=N)
+    xq, _, sxi = oracle_quantized(x)
+    wq, _, swi = oracle_quantized(w)
+    xq, wq = xq.copy(), wq.copy()
+    wq[5, 0] = 0x7F  # a NaN in the chunk that stands in for those past the end: column 5 alone is NaN
+    tw.tweo_set_gemm_tile(tile)
+    try:
+        got, _ = run_fwd(xq, wq, sxi, swi, M, N, K, pen=None)
+    finally:
+        tw.tweo_set_gemm_tile(0)
+    val = (got.astype(np.uint32) << 16).view(np.float32)
+    assert np.isnan(val[:, 5]).all() and not np.isnan(np.delete(val, 5, axis=1)).any()
+    wq[5, 0] = 0
+    ref, refabs, _ = oracle.fp8_linear_fwd(xq, wq, sxi, swi)
+    got[:, 5] = 0
+    ref[:, 5], refabs[:, 5] = 0.0, 0.0
+    check_gemm(got, ref, refabs, K, "fwd ragged K")
+
+
+# backward products whose contractions (tokens, output columns) are multiples of 16 only: one launch,
+# a K split of ragged tiles, and the shapes' plain kernels
+@pytest.mark.parametrize("hybrid", [False, True])
+@pytest.mark.parametrize("shape", [(592, 656, 520), (3152, 720, 512), (16400, 272, 264), (1040, 2000, 1544)])
+def test_bwd_ragged_contractions(shape, hybrid):
+    check_bwd_pair(shape, hybrid)
