@@ -672,7 +672,7 @@ __device__ __forceinline__ void gemm_nt_dma_body(const GemmDev &g, const int blo
         // ask the scheduler for: MFMA, a few LDS reads, MFMA, ... so the reads of the next
         // stage are in flight while this stage's MFMAs occupy the matrix pipe
         constexpr int N_MFMA = T::MT * T::NT * (INT8 ? 2 : 1), N_DS = 2 * (T::MT + T::NT);
-        constexpr int DS_PER = (N_DS + N_MFMA - 2) / (N_MFMA - 1);
+        constexpr int DS_PER = N_MFMA > 1 ? (N_DS + N_MFMA - 2) / (N_MFMA - 1) : N_DS;
 #pragma unroll
         for (int k = 0; k < N_MFMA; ++k) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);       // one MFMA
@@ -1456,9 +1456,11 @@ __global__ __launch_bounds__(256) void splitk_reduce_defer_kernel(const float4 *
 
 typedef Tile<256, 256, 2, 2> T256x256;
 typedef Tile<128, 128, 2, 2> T128x128;
-typedef Tile<64, 64, 1, 1> T64x64;
 typedef TileD<256, 256, 2, 4, 4, 2> D256x256w8;
 typedef TileD<128, 128, 2, 2, 4, 2> D128x128w4;
+// Small outputs: a contraction of 512 is one memory latency, all eight stages in flight at once, and
+// four waves share what a register-staged wave did alone (256x512x512: 6.8 us, now 4.0).
+typedef TileD<64, 64, 2, 2, 8, 2> D64x64w4;
 typedef TileS<256, 256, 2, 4, 2, 2> S256x256w8;  // persistent, 8 waves, one workgroup per CU
 typedef TileS<128, 128, 2, 2, 2, 2> S128x128w4;  // two workgroups per CU
 typedef TileS<192, 256, 2, 4, 2, 2> S192x256w8;  // for tile counts that 256x256 quantises badly
@@ -1516,8 +1518,8 @@ size_t stream_k_workspace_bytes()
 }
 
 // Kernel variants (the numbers are what tweo_set_gemm_tile takes; retired ones are refused).
-// 1, 3, 4: register-staged kernel (any K % 16 == 0), tiles 256x256, 128x128, 64x64.  6, 8:
-// DMA-pipelined kernel on 64-byte stages, 256x256 with 8 waves and 128x128.  11, 13,
+// 1, 3: register-staged kernel, tiles 256x256, 128x128 (no shape is sent there any more).  6, 8, 4:
+// DMA-pipelined kernel on 64-byte stages, 256x256 with 8 waves, 128x128 and 64x64.  11, 13,
 // 14: persistent streaming kernel (K % 128 == 0): 256x256, 128x128, 192x256.  15: deferred-epilogue
 // persistent kernel (256x256, four waves; M, N % 256 == 0, K % 128 == 0, K >= 512).  16: the same
 // kernel on 192x256 tiles (any M, K >= 2048).  17: the INT8 weight-streaming kernel (M <= 128).
@@ -1554,12 +1556,17 @@ static int defer_workgroups(int64_t M, int64_t N, int bm = 256)
     return (int)(tiles < cap ? tiles : cap);
 }
 
+// Outputs that go to 64x64 tiles: as long as three of them go to two CUs.  Measured (FP8, us, 64x64 / the
+// faster of the 128x128 kernels): 1024x1024 (256 tiles) under 512 / 2048 / 4096: 4.3 / 4.6, 7.3 / 11.8,
+// 11.0 / 18.3; 1024x2048 (512 tiles): 5.1 / 5.0, 11.6 / 11.6; 2048x2048 under 2048: 19.2 / 13.4.
+static int64_t tiles64(int64_t M, int64_t N) { return ((M + 63) / 64) * ((N + 63) / 64); }
+static bool small_output(int64_t M, int64_t N) { return M * N <= 128 * 128 * 16 || 2 * tiles64(M, N) <= 3 * (int64_t)num_cus(); }
 static int pick_variant(int64_t M, int64_t N, int64_t K)
 {
     auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
     int v = g_tile_override >= 17 ? 4 : g_tile_override;
     if (v == 0) {
-        if (M * N <= 128 * 128 * 16) {
+        if (small_output(M, N)) {
             v = 4;
         } else {
             // rounds of tiles over the machine x cost of a tile; per-workgroup speeds are measured
@@ -1875,7 +1882,7 @@ static hipError_t launch_gemm(const GemmArgs &a, hipStream_t s)
     switch (resolve_variant(a)) {
     case 1: return launch_tile<T256x256, INT8, false>(a, s);
     case 3: return launch_tile<T128x128, INT8, false>(a, s);
-    case 4: return launch_tile<T64x64, INT8, false>(a, s);
+    case 4: return launch_tile<D64x64w4, INT8, true>(a, s);
     case 6: return launch_tile<D256x256w8, INT8, true>(a, s);
     case 8: return launch_tile<D128x128w4, INT8, true>(a, s);
     case 11: return launch_stream<S256x256w8, INT8, 1>(a, s);
@@ -1938,8 +1945,9 @@ int fp8_gemm_ksplit(int64_t M, int64_t N, int64_t K)
 // INT8, between decode and prefill sizes: an output of few 128x128 tiles leaves CUs idle (384 rows into
 // 4096 columns: 96 tiles), so `splits` workgroups share a tile on the direct-to-LDS kernel, int32 runs
 // added exactly by the reduce kernel.  The rule is the time of both ways from measured rates: a tile
-// alone on its CU runs at 0.29 us per 64-byte stage (two on a CU share that), the runs are written and
-// read at 4 TB/s, the second launch costs 4 us; taken where that promises a quarter.
+// alone on its CU runs at 0.29 us per 64-byte stage (two on a CU share that; 0.135 and 0.26 for the
+// 64x64 tiles of small outputs), the runs are written and read at 4 TB/s, the second launch costs 4 us;
+// taken where that promises a tenth.
 // Quantise + linear, 11008 -> 4096 at M = 300 / 384 / 500: 44.2 / 53.6 / 53.9 -> 32.6 / 37.7 / 44.9 us;
 // 5632 -> 2048 at M = 300: 26.2 -> 18.6.
 static int i8_dma_ksplit(int64_t M, int64_t N, int64_t K)
@@ -1950,7 +1958,8 @@ static int i8_dma_ksplit(int64_t M, int64_t N, int64_t K)
     if (tiles * 2 > cus)
         return 1;
     int best = 1;
-    double best_us = 0.75 * 0.29 * (double)kt;
+    const double plain = small_output(M, N) ? (tiles64(M, N) <= cus ? 0.135 : 0.26) : 0.29;
+    double best_us = 0.9 * (plain * (double)kt + 3.0);
     for (int s = 2; s <= 8 && kt / s >= 16; ++s) {
         const double us = 0.29 * (double)((tiles * s + cus - 1) / cus) * (double)((kt + s - 1) / s) +
                           (double)s * (double)M * (double)N * 8.0 / 4e6 + 4.0;
@@ -2067,7 +2076,8 @@ static hipError_t launch_ksplit_defer(const GemmArgs &a, hipStream_t s, int spli
 // Time of one gradient product by itself in microseconds, from what the kernels measured on layers of
 // 768 to 3072 columns over 8192 rows (within 10 %): two 128x128 tiles on a CU advance one 64-byte stage
 // in 0.74 us (a lone one in 0.5), a 256x256 tile of the deferred kernel a 128-byte stage in 1.25, of the
-// 8-wave kernel in 1.45; runs of a K split are written at 5 TB/s and read at 6.5.
+// 8-wave kernel in 1.45, a 64x64 tile alone on its CU a 64-byte stage in 0.135; runs of a K split are
+// written at 5 TB/s and read at 6.5.
 static double lone_gemm_us(int64_t M, int64_t N, int64_t K)
 {
     const double cus = num_cus(), kt = (double)(K + 127) / 128;
@@ -2078,6 +2088,8 @@ static double lone_gemm_us(int64_t M, int64_t N, int64_t K)
         return 1.3 * kt / ds + 3.0 + mb / 5.0 + 2.5 + mb / 6.5;
     }
     const int v = pick_variant(M, N, K);
+    if (v == 4)
+        return (tiles64(M, N) <= (int64_t)cus ? 0.135 : 0.26) * 2.0 * kt + 3.0;
     if (v == 15 || v == 16)
         return 1.25 * kt * (v == 16 ? 0.77 : 1.0) * std::ceil((double)tiles(M, N, v == 16 ? 192 : 256, 256) / cus) + 6.0;
     if (v == 11 || v == 14)
@@ -2091,10 +2103,15 @@ static double lone_gemm_us(int64_t M, int64_t N, int64_t K)
 // the chip where each alone would leave CUs idle, but its kernel is no fast one (0.92 us per 64-byte
 // stage of two tiles on a CU): taken where the two ways' times, estimated from those rates, say so.
 // 8192x768 -> 768: 40.5 us in three launches, 32.9 in two; 8192x3072 -> 768 stays apart (64 against 75).
+static bool pair_is_small(int64_t M, int64_t N, int64_t K) { return tiles64(M, K) + tiles64(N, K) <= 2 * (int64_t)num_cus(); }
 static int pair_splits(int64_t M, int64_t N, int64_t K)
 {
     if (g_tile_override != 0 || !g_stream_k_off)
         return 0;
+    // few 64x64 tiles each, all of them resident at once; a long contraction beside few tiles is better
+    // off with a K split of its own
+    if (pair_is_small(M, N, K) && fp8_gemm_ksplit(N, K, M) == 1)
+        return 1;
     auto tiles = [](int64_t r, int64_t c) { return ((r + 127) / 128) * ((c + 127) / 128); };
     if (M * K <= 128 * 128 * 16 || N * K <= 128 * 128 * 16)
         return 0;
@@ -2123,10 +2140,9 @@ static size_t pair_bytes(int64_t N, int64_t K, int splits)
 
 size_t fp8_pair_bytes(int64_t M, int64_t N, int64_t K) { return pair_bytes(N, K, pair_splits(M, N, K)); }
 
-template <bool A_E5M2>
+template <typename T, bool A_E5M2>
 static hipError_t launch_pair(const GemmArgs &d, const GemmArgs &w, int splits, hipStream_t s)
 {
-    using T = D128x128w4;
     constexpr auto kern = gemm_nt_dma_pair_kernel<T, A_E5M2>;
     static bool attr_done = false;
     if (!attr_done) {
@@ -2179,7 +2195,11 @@ hipError_t launch_fp8_gemm_pair(const GemmArgs &d, const GemmArgs &w, hipStream_
     const bool fits = splits == 1 || (w.sk_workspace != nullptr && ((uintptr_t)w.sk_workspace & 15u) == 0 &&
                                       w.sk_workspace_bytes >= pair_bytes(w.M, w.N, splits));
     if (splits > 0 && fits)
-        return d.a_e5m2 ? launch_pair<true>(d, w, splits, s) : launch_pair<false>(d, w, splits, s);
+    {
+        if (splits == 1 && pair_is_small(d.M, d.K, d.N))
+            return d.a_e5m2 ? launch_pair<D64x64w4, true>(d, w, 1, s) : launch_pair<D64x64w4, false>(d, w, 1, s);
+        return d.a_e5m2 ? launch_pair<D128x128w4, true>(d, w, splits, s) : launch_pair<D128x128w4, false>(d, w, splits, s);
+    }
     const hipError_t e = launch_fp8_gemm(d, s);
     return e != hipSuccess ? e : launch_fp8_gemm(w, s);
 }
@@ -2193,6 +2213,9 @@ static hipError_t launch_fp8_gemm_e5m2(const GemmArgs &a, hipStream_t s)
     if (a.p != 0 || a.residual != nullptr)
         return hipErrorInvalidValue;
     switch (resolve_variant(a)) {
+    case 1: return launch_tile<T256x256, false, false, true>(a, s);
+    case 3: return launch_tile<T128x128, false, false, true>(a, s);
+    case 4: return launch_tile<D64x64w4, false, true, true>(a, s);
     case 6: return launch_tile<D256x256w8, false, true, true>(a, s);
     case 8: return launch_tile<D128x128w4, false, true, true>(a, s);
     case 11: return launch_stream<S256x256w8, false, 1, true>(a, s);
@@ -2206,14 +2229,8 @@ static hipError_t launch_fp8_gemm_e5m2(const GemmArgs &a, hipStream_t s)
             return launch_defer_inst<false, 0, 7, 4, true>(a, s);
         return kt >= 6 ? launch_defer_inst<false, 0, 5, 4, true>(a, s) : launch_defer_inst<false, 0, 3, 4, true>(a, s);
     }
-    case 16: return launch_defer_inst<false, 0, 15, 3, true>(a, s);
-    default: break;
+    default: return launch_defer_inst<false, 0, 15, 3, true>(a, s);
     }
-    if (a.M * a.N <= 128 * 128 * 16)
-        return launch_tile<T64x64, false, false, true>(a, s);
-    if (a.M * a.N <= 1024 * 1024)
-        return launch_tile<T128x128, false, false, true>(a, s);
-    return launch_tile<T256x256, false, false, true>(a, s);
 }
 
 hipError_t launch_fp8_gemm(const GemmArgs &a, hipStream_t s)

@@ -229,7 +229,7 @@ def test_w8a8_weight_streaming_up_to_256_rows_into_a_narrow_projection(shape):
     assert np.array_equal(bf16_bits(y), want_v)
 
 
-@pytest.mark.parametrize("shape", [(129, 4096, 512), (200, 4160, 520), (384, 11008, 4096), (700, 5632, 776), (257, 6160, 136)])
+@pytest.mark.parametrize("shape", [(129, 4096, 512), (200, 4160, 520), (384, 11008, 4096), (300, 11008, 1032), (257, 6160, 136)])
 def test_w8a8_k_split_of_128_row_tiles(shape):
     # few 128x128 tiles under a long contraction, ragged in M and N, a stage count the runs do not
     # divide: int32 runs added by the second launch, the same bits as without a workspace and as the oracle
