@@ -1550,13 +1550,10 @@ static uint64_t next_fused_token()
 
 // Whether the fused launch applies: whole 16x16 blocks, enough work to pay for the wait, not under
 // stream capture (a replayed graph would replay the token).
-bool fused_cast_applies(int64_t rows0, int64_t cols0, int64_t rows1, int64_t cols1, hipStream_t s)
+static bool fused_cast_possible(int64_t rows0, int64_t cols0, int64_t rows1, int64_t cols1, hipStream_t s)
 {
     if (!g_fused_cast_on || rows0 % 16 != 0 || cols0 % 16 != 0 || rows1 % 16 != 0 || cols1 % 16 != 0)
         return false;
-    // small tensors: two short launches are as fast (measured: no gain below ~16M elements, also not
-    // with a form of this kernel in which every lane keeps one 8x8 block and nothing is read twice:
-    // GPT-2 block step 0.563 -> 0.561 ms)
     if (rows0 * cols0 + rows1 * cols1 < ((int64_t)1 << 24))
         return false;
     // the kernel's lane offsets and tile numbers are 32 bits
@@ -1568,6 +1565,22 @@ bool fused_cast_applies(int64_t rows0, int64_t cols0, int64_t rows1, int64_t col
     if (hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone)
         return false;
     return true;
+}
+
+// Plain casts: the one launch moves 4 bytes per element instead of 6 for what stays on chip but runs two
+// waves per SIMD in lockstep; the two launches, with the 128x128 tiles of the cast, are ahead where the
+// wave tiles fill the rounds to less than about two thirds.  Measured cold, one launch / two, us:
+// 16.9M elements (1088 of 2048 wave tiles) 30.3 / 28.6, 25.2M 31.6 / 30.4, 33.6M (2048) 37.3 / 41.2,
+// 50432x768 (2364 of 4096) 52.0 / 48.1, 50.3M (3072) 55.8 / 61.1, 67M 63.2 / 84.6, 101M 112 / 122,
+// 268M 313 / 326; 16384x2048 with 6144x2048 (2816 of 4096) 51 / 54 within a training step.
+bool fused_cast_applies(int64_t rows0, int64_t cols0, int64_t rows1, int64_t cols1, hipStream_t s)
+{
+    const int64_t wt = 4 * (((rows0 + 255) / 256) * ((cols0 + 255) / 256) + ((rows1 + 255) / 256) * ((cols1 + 255) / 256));
+    const int64_t cap = amax_cus() < kFusedMaxWorkgroups ? amax_cus() : kFusedMaxWorkgroups, round = cap * kFusedWaves;
+    const int64_t rounds = (wt + round - 1) / round;
+    if (100 * wt < 65 * rounds * round)
+        return false;
+    return fused_cast_possible(rows0, cols0, rows1, cols1, s);
 }
 
 // x1 may be nullptr (one tensor).  slots: 16 bytes per workgroup, at most kFusedMaxWorkgroups of
@@ -1645,7 +1658,8 @@ hipError_t launch_amax_quantize_inject(const void *dy_bf16, const void *a_bf16, 
                                        float *scale_inv_out, hipStream_t s)
 {
     const InjectArgs inj{(const uint16_t *)a_bf16, inv_tau, coef, p};
-    if (fused_cast_applies(rows, cols, 0, 0, s))
+    // (both tensors would be read twice: one launch wherever it is possible)
+    if (fused_cast_possible(rows, cols, 0, 0, s))
         return launch_amax_cast_fused_impl(dy_bf16, rows, cols, amax_out, q, qT, scale_out, scale_inv_out, nullptr, 0, 0,
                                            nullptr, nullptr, nullptr, nullptr, nullptr, e5m2, false, partials, inj, s);
     const int64_t n_vec = rows * cols / 8;
