@@ -72,10 +72,13 @@ enum {
  * the second part gets the same results up to the fp32 summation order, from
  * the plain schedule.  The second part also serves, without any switch, a GEMM
  * without penalty whose output has far fewer 256x256 tiles than the device has
- * CUs under a contraction of 16384 or more (weight gradients of narrow layers
- * over many tokens): several workgroups share a tile, each multiplies a run of
- * K and stores fp32 sums here (runs x rows x cols x 4 bytes), a second launch
- * adds the runs in index order - run-to-run identical results. */
+ * CUs under a long contraction (weight gradients of narrow layers over many
+ * tokens; an INT8 linear of a few hundred rows): several workgroups share a tile,
+ * each multiplies a run of K and stores fp32 (INT8: int32) sums here (runs x rows x
+ * cols x 4 bytes), a second launch adds the runs in index order - run-to-run
+ * identical results.  A backward call whose layer is narrow runs both of its
+ * products in one launch with the weight gradient's runs here; with less, or with
+ * none, the products run one after the other on the plain schedule. */
 size_t tweo_workspace_bytes(int op, int64_t M, int64_t N, int64_t K);
 
 const char *tweo_status_string(tweo_status s);
@@ -454,9 +457,9 @@ tweo_status tweo_fp8_linear_bwd_bf16_inject(const void *dy_bf16, const void *a_b
  * amax, scale and cast of one tensor in one call (Sec. 4.3, current scaling: the
  * scale comes from this tensor's own amax; E4M3 range +-448, Sec. 1; e5m2 != 0:
  * the gradient format of the HYBRID recipe, range +-57344).  The same results as
- * tweo_amax followed by tweo_quantize_e4m3 / tweo_quantize_e5m2; from 2^24
- * elements on it is one launch that keeps the tensor on chip between the two steps
- * (see tweo_set_fused_cast below), otherwise two launches.
+ * tweo_amax followed by tweo_quantize_e4m3 / tweo_quantize_e5m2; for most tensors of
+ * 2^24 elements and more it is one launch that keeps the tensor on chip between the
+ * two steps (see tweo_set_fused_cast below), otherwise two launches.
  *   x_bf16 [rows, cols], rows % 16 == 0 and cols % 16 == 0.
  *   amax_out, scale_out, scale_inv_out: one fp32 each on the device, all required.
  *   q [rows, cols] and qT [cols, rows] codes, both required.

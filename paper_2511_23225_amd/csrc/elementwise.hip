@@ -1349,47 +1349,23 @@ __device__ __forceinline__ void store_block_transposed(const uint32_t (&qd)[16][
     }
 }
 
-// Rows row .. row + ROWS - 1 of a lane's block, 32 bytes each; INJECT (as in the cast body above): the
-// penalty gradient is added on the way in, from the same places of the activation, four rows at a
-// time with a scheduling fence behind each group (beside 192 registers of kept data there is room
-// for one group of the activation's rows; without the fence the compiler hoists all of its loads
-// and spills).
-template <int INJECT, int ROWS>
+// Rows row .. row + ROWS - 1 of a lane's block, 32 bytes each.
+template <int ROWS>
 __device__ __forceinline__ void fused_load_rows(uint4 (*__restrict__ in)[2], const FusedTensor &t, const FusedPlace &at,
-                                                int row, const InjectArgs &inj)
+                                                int row)
 {
-    constexpr int GROUP = INJECT != 0 ? 4 : ROWS;
-    auto load = [&](const uint16_t *base, int i, uint4 (&v)[2]) {
-        const uint4 *src = (const uint4 *)((const uint8_t *)(base + at.x0 + (row + i) * t.cols) + (uint64_t)(at.xl * 2u));
-        v[0] = src[0];
-        v[1] = src[1];
-    };
 #pragma unroll
-    for (int g = 0; g < ROWS; g += GROUP) {
-#pragma unroll
-        for (int i = 0; i < GROUP; ++i)
-            load(t.x, g + i, in[g + i]);
-        if constexpr (INJECT != 0) {
-            constexpr int P = INJECT == 4 ? 4 : 0;
-            uint4 a[GROUP][2];
-#pragma unroll
-            for (int i = 0; i < GROUP; ++i)
-                load(inj.act, g + i, a[i]);
-#pragma unroll
-            for (int i = 0; i < GROUP; ++i) {
-                in[g + i][0] = inject_vec<P>(in[g + i][0], a[i][0], inj);
-                in[g + i][1] = inject_vec<P>(in[g + i][1], a[i][1], inj);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }
+    for (int i = 0; i < ROWS; ++i) {
+        const uint4 *src = (const uint4 *)((const uint8_t *)(t.x + at.x0 + (row + i) * t.cols) + (uint64_t)(at.xl * 2u));
+        in[i][0] = src[0];
+        in[i][1] = src[1];
     }
 }
 
-template <bool E5M2, bool T_LATER, int INJECT = 0>
+template <bool E5M2, bool T_LATER>
 __global__ __launch_bounds__(kFusedThreads, 1) void amax_cast_fused_kernel(FusedTensor t0, FusedTensor t1, uint32_t wt0,
                                                                            uint32_t wt_total, int rounds,
-                                                                           FusedSlot *slots, uint64_t token,
-                                                                           InjectArgs inj)
+                                                                           FusedSlot *slots, uint64_t token)
 {
     const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const uint32_t G = gridDim.x;
@@ -1418,7 +1394,7 @@ __global__ __launch_bounds__(kFusedThreads, 1) void amax_cast_fused_kernel(Fused
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
             uint4 in[8][2];
-            fused_load_rows<INJECT, 8>(in, t, at, half * 8, inj);
+            fused_load_rows<8>(in, t, at, half * 8);
 #pragma unroll
             for (int i = 0; i < 8; ++i)
                 m = pk_absmax4(pk_absmax4(m, in[i][0]), in[i][1]);
@@ -1454,7 +1430,7 @@ __global__ __launch_bounds__(kFusedThreads, 1) void amax_cast_fused_kernel(Fused
             kept = fused_locate(t, kept_first ? wt : wt - wt0, lane);
             if (kept.inside) {
                 uint32_t m = 0;
-                fused_load_rows<INJECT, 16>(keep, t, kept, 0, inj);
+                fused_load_rows<16>(keep, t, kept, 0);
 #pragma unroll
                 for (int i = 0; i < 16; ++i)
                     m = pk_absmax4(pk_absmax4(m, keep[i][0]), keep[i][1]);
@@ -1523,7 +1499,7 @@ __global__ __launch_bounds__(kFusedThreads, 1) void amax_cast_fused_kernel(Fused
                     in[i][1] = keep2[i][1];
                 }
             } else {
-                fused_load_rows<INJECT, 8>(in, t, at, half * 8, inj);
+                fused_load_rows<8>(in, t, at, half * 8);
             }
             cast_rows8<E5M2>(in, half, scale, qd, t, at);
         }
@@ -1550,11 +1526,22 @@ static uint64_t next_fused_token()
 
 // Whether the fused launch applies: whole 16x16 blocks, enough work to pay for the wait, not under
 // stream capture (a replayed graph would replay the token).
-static bool fused_cast_possible(int64_t rows0, int64_t cols0, int64_t rows1, int64_t cols1, hipStream_t s)
+// Plain casts: the one launch moves 4 bytes per element instead of 6 for what stays on chip but runs two
+// waves per SIMD in lockstep; the two launches, with the 128x128 tiles of the cast, are ahead where the
+// wave tiles fill the rounds to less than about two thirds.  Measured cold, one launch / two, us:
+// 16.9M elements (1088 of 2048 wave tiles) 30.3 / 28.6, 25.2M 31.6 / 30.4, 33.6M (2048) 37.3 / 41.2,
+// 50432x768 (2364 of 4096) 52.0 / 48.1, 50.3M (3072) 55.8 / 61.1, 67M 63.2 / 84.6, 101M 112 / 122,
+// 268M 313 / 326; 16384x2048 with 6144x2048 (2816 of 4096) 51 / 54 within a training step.
+bool fused_cast_applies(int64_t rows0, int64_t cols0, int64_t rows1, int64_t cols1, hipStream_t s)
 {
     if (!g_fused_cast_on || rows0 % 16 != 0 || cols0 % 16 != 0 || rows1 % 16 != 0 || cols1 % 16 != 0)
         return false;
     if (rows0 * cols0 + rows1 * cols1 < ((int64_t)1 << 24))
+        return false;
+    const int64_t wt = 4 * (((rows0 + 255) / 256) * ((cols0 + 255) / 256) + ((rows1 + 255) / 256) * ((cols1 + 255) / 256));
+    const int64_t cap = amax_cus() < kFusedMaxWorkgroups ? amax_cus() : kFusedMaxWorkgroups, round = cap * kFusedWaves;
+    const int64_t rounds = (wt + round - 1) / round;
+    if (100 * wt < 65 * rounds * round)
         return false;
     // the kernel's lane offsets and tile numbers are 32 bits
     const int64_t most = (int64_t)1 << 24;
@@ -1567,30 +1554,13 @@ static bool fused_cast_possible(int64_t rows0, int64_t cols0, int64_t rows1, int
     return true;
 }
 
-// Plain casts: the one launch moves 4 bytes per element instead of 6 for what stays on chip but runs two
-// waves per SIMD in lockstep; the two launches, with the 128x128 tiles of the cast, are ahead where the
-// wave tiles fill the rounds to less than about two thirds.  Measured cold, one launch / two, us:
-// 16.9M elements (1088 of 2048 wave tiles) 30.3 / 28.6, 25.2M 31.6 / 30.4, 33.6M (2048) 37.3 / 41.2,
-// 50432x768 (2364 of 4096) 52.0 / 48.1, 50.3M (3072) 55.8 / 61.1, 67M 63.2 / 84.6, 101M 112 / 122,
-// 268M 313 / 326; 16384x2048 with 6144x2048 (2816 of 4096) 51 / 54 within a training step.
-bool fused_cast_applies(int64_t rows0, int64_t cols0, int64_t rows1, int64_t cols1, hipStream_t s)
-{
-    const int64_t wt = 4 * (((rows0 + 255) / 256) * ((cols0 + 255) / 256) + ((rows1 + 255) / 256) * ((cols1 + 255) / 256));
-    const int64_t cap = amax_cus() < kFusedMaxWorkgroups ? amax_cus() : kFusedMaxWorkgroups, round = cap * kFusedWaves;
-    const int64_t rounds = (wt + round - 1) / round;
-    if (100 * wt < 65 * rounds * round)
-        return false;
-    return fused_cast_possible(rows0, cols0, rows1, cols1, s);
-}
-
 // x1 may be nullptr (one tensor).  slots: 16 bytes per workgroup, at most kFusedMaxWorkgroups of
-// them, no initial contents assumed.  inj.act: the penalty gradient is added to x0 (the only tensor
-// then) on the way in.
-static hipError_t launch_amax_cast_fused_impl(const void *x0_bf16, int64_t rows0, int64_t cols0, float *amax0, uint8_t *q0,
+// them, no initial contents assumed.
+hipError_t launch_amax_cast_fused(const void *x0_bf16, int64_t rows0, int64_t cols0, float *amax0, uint8_t *q0,
                                   uint8_t *q0T, float *scale0, float *scale0_inv, const void *x1_bf16,
                                   int64_t rows1, int64_t cols1, float *amax1, uint8_t *q1, uint8_t *q1T,
                                   float *scale1, float *scale1_inv, bool e5m2, bool transposed_later, void *slots,
-                                  const InjectArgs &inj, hipStream_t s)
+                                  hipStream_t s)
 {
     auto tiles = [](int64_t v) { return (uint32_t)((v + kQuantBigTile - 1) / kQuantBigTile); };
     const FusedTensor t0{(const uint16_t *)x0_bf16, rows0, cols0, tiles(cols0), q0, q0T, amax0, scale0, scale0_inv};
@@ -1616,18 +1586,11 @@ static hipError_t launch_amax_cast_fused_impl(const void *x0_bf16, int64_t rows0
             attr_done = true;
         }
         hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kFusedThreads), kFusedLdsBytes, s, t0, t1, wt0, wt_total,
-                           rounds, (FusedSlot *)slots, token, inj);
+                           rounds, (FusedSlot *)slots, token);
         err = hipGetLastError();
     };
-    static bool done[7] = {};
-    if (inj.act != nullptr) {
-        if (e5m2)
-            inj.p == 4 ? launch(amax_cast_fused_kernel<true, false, 4>, done[3])
-                       : launch(amax_cast_fused_kernel<true, false, 1>, done[4]);
-        else
-            inj.p == 4 ? launch(amax_cast_fused_kernel<false, false, 4>, done[5])
-                       : launch(amax_cast_fused_kernel<false, false, 1>, done[6]);
-    } else if (e5m2)
+    static bool done[3] = {false, false, false};
+    if (e5m2)
         launch(amax_cast_fused_kernel<true, false>, done[0]);  // gradients: both copies are read at once
     else if (transposed_later)
         launch(amax_cast_fused_kernel<false, true>, done[1]);
@@ -1636,32 +1599,18 @@ static hipError_t launch_amax_cast_fused_impl(const void *x0_bf16, int64_t rows0
     return err;
 }
 
-hipError_t launch_amax_cast_fused(const void *x0_bf16, int64_t rows0, int64_t cols0, float *amax0, uint8_t *q0,
-                                  uint8_t *q0T, float *scale0, float *scale0_inv, const void *x1_bf16,
-                                  int64_t rows1, int64_t cols1, float *amax1, uint8_t *q1, uint8_t *q1T,
-                                  float *scale1, float *scale1_inv, bool e5m2, bool transposed_later, void *slots,
-                                  hipStream_t s)
-{
-    return launch_amax_cast_fused_impl(x0_bf16, rows0, cols0, amax0, q0, q0T, scale0, scale0_inv, x1_bf16, rows1, cols1,
-                                       amax1, q1, q1T, scale1, scale1_inv, e5m2, transposed_later, slots, InjectArgs{},
-                                       s);
-}
-
-// amax and cast of dy' = bf16(dy + coef * sign(a) * (|a| * inv_tau)^(p-1)) without storing dy'
-// (rows, cols multiples of 16): one launch that keeps dy' on chip between the two steps where that
-// form applies - it reads dy and the activation once, 6 bytes per element for what stays on chip
-// against 10 (50432x768: 96 us in two launches, 73 in one) - else an amax launch that leaves
-// workgroup maxima and a cast launch that reduces them.
+// amax and cast of dy' = bf16(dy + coef * sign(a) * (|a| * inv_tau)^(p-1)) without storing dy':
+// the amax launch leaves workgroup maxima, the cast launch reduces them (rows, cols multiples of 16).
+// One launch that keeps dy' on chip in between was built (6 bytes per element for what stays against
+// 10) and measured no faster: 50432x768 79 us in two launches (96 before the injection lost its branches
+// and the cast got its 128x128 tiles), 73 to 79 in one, which besides waits inside
+// for all of its workgroups.
 hipError_t launch_amax_quantize_inject(const void *dy_bf16, const void *a_bf16, int64_t rows, int64_t cols,
                                        float inv_tau, float coef, int p, bool e5m2, uint32_t *partials,
                                        float *amax_out, uint8_t *q, uint8_t *qT, float *scale_out,
                                        float *scale_inv_out, hipStream_t s)
 {
     const InjectArgs inj{(const uint16_t *)a_bf16, inv_tau, coef, p};
-    // (both tensors would be read twice: one launch wherever it is possible)
-    if (fused_cast_possible(rows, cols, 0, 0, s))
-        return launch_amax_cast_fused_impl(dy_bf16, rows, cols, amax_out, q, qT, scale_out, scale_inv_out, nullptr, 0, 0,
-                                           nullptr, nullptr, nullptr, nullptr, nullptr, e5m2, false, partials, inj, s);
     const int64_t n_vec = rows * cols / 8;
     int64_t blocks = n_vec / (kAmaxUnroll * kAmaxThreads);
     if (blocks < 1)
