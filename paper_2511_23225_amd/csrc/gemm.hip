@@ -2119,7 +2119,9 @@ static int pair_splits(int64_t M, int64_t N, int64_t K)
     const int64_t kd = (N + 63) / 64, kw = (M + 63) / 64, td = tiles(M, K), tw = tiles(N, K);
     int best = 0;
     double best_us = 0.97 * (lone_gemm_us(M, K, N) + lone_gemm_us(N, K, M));
-    for (int s = 1; s <= 16 && kw / s >= 8; ++s) {
+    // a contraction of up to 4096 stays whole, as on the deferred kernel (whose split lost there, 14 ->
+    // 20 us), so that such a layer's backward needs no scratch beyond its scalars
+    for (int s = 1; s <= (kw > 64 ? 16 : 1) && kw / s >= 8; ++s) {
         // stages per slot at two tiles to a CU, or the longest unit, which ends up alone on its CU; the
         // uneven end; the runs' way through memory
         const double longest = (double)std::max(kd, (kw + s - 1) / s), mb = s > 1 ? (double)s * (double)N * (double)K * 4e-6 : 0.0;

@@ -448,7 +448,7 @@ def test_error_paths_need_no_launch():
 # both gradient products in one launch of 128x128 tiles: ragged in every direction, the weight
 # gradient's contraction in one run and in several, a stage count the runs do not divide
 @pytest.mark.parametrize("hybrid", [False, True])
-@pytest.mark.parametrize("shape", [(576, 640, 520), (3136, 704, 512), (1024, 1024, 1024), (4096, 576, 1032)])
+@pytest.mark.parametrize("shape", [(576, 640, 520), (6336, 704, 512), (1024, 1024, 1024), (6208, 576, 1032)])
 def test_bwd_of_narrow_layers_in_one_launch(shape, hybrid):
     check_bwd_pair(shape, hybrid)
 
@@ -513,6 +513,6 @@ def test_fwd_contraction_ends_inside_a_stage(tile, K):
 # backward products whose contractions (tokens, output columns) are multiples of 16 only: one launch,
 # a K split of ragged tiles, and the shapes' plain kernels
 @pytest.mark.parametrize("hybrid", [False, True])
-@pytest.mark.parametrize("shape", [(592, 656, 520), (3152, 720, 512), (16400, 272, 264), (1040, 2000, 1544)])
+@pytest.mark.parametrize("shape", [(592, 656, 520), (6224, 720, 512), (16400, 272, 264), (1040, 2000, 1544)])
 def test_bwd_ragged_contractions(shape, hybrid):
     check_bwd_pair(shape, hybrid)
