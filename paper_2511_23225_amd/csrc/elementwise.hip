@@ -689,7 +689,9 @@ __device__ __forceinline__ uint32_t fold_u16(uint32_t m) { return (m & 0xFFFFu) 
 // tensor that it saves (59.5 us against 20.9 + 22.1).  So a row's elements are only estimated in fp32,
 // with a bound on the estimate's error that is taken over the lane's eight columns: |x - mean| <=
 // |x| + |mean|, and each of the fp32 steps (mean, rstd, difference, product, sum) is off by at most
-// 2^-24 of these magnitudes, together below 2^-21 of |rstd gamma| (|x| + |mean|) + |beta|.  Only
+// 2^-24 of these magnitudes, together below 2^-21 of |rstd gamma| (|x| + |mean|) + |beta|.  A
+// subnormal rstd, product or difference is off by up to 2^-150 whatever its size, 2^-24 of the least
+// normal number: the bound takes each factor as at least 2^-126.  Only
 // vectors whose upper bound reaches the largest lower bound of the row and the wave's best so far
 // are formed in fp64 - about one of a row.  A NaN or infinity anywhere makes the bound NaN or
 // infinite, and the comparison then sends the vector to the exact path.
@@ -796,7 +798,8 @@ __global__ __launch_bounds__((LnShape<AMAX, P>::THREADS), (LnShape<AMAX, P>::WAV
             stats[2 * row + 1] = rstd;
         }
         if constexpr (AMAX) {
-            const float mean_f = (float)mean, rstd_f = (float)rstd, absmean = __builtin_fabsf(mean_f);
+            auto normal = [](float v) { return v < 0x1p-126f ? 0x1p-126f : v; };  // keeps a NaN, unlike a maximum
+            const float mean_f = (float)mean, rstd_f = (float)rstd, absmean = __builtin_fabsf(mean_f), rstd_up = normal(rstd_f);
             // the parameters are read in every row: the compiler would keep them and their widened
             // values over the rows and spill
             int lane0 = lane;
@@ -805,7 +808,7 @@ __global__ __launch_bounds__((LnShape<AMAX, P>::THREADS), (LnShape<AMAX, P>::WAV
             auto bound = [&](uint4 v, uint4 g, uint4 b) {
                 const float ax = bits_to_f32(fold_u16(pk_absmax4(0u, v)) << 16), ag = bits_to_f32(fold_u16(pk_absmax4(0u, g)) << 16),
                             ab = bits_to_f32(fold_u16(pk_absmax4(0u, b)) << 16);
-                return __builtin_fmaf(rstd_f * ag, ax + absmean, ab) * 0x1p-21f + 1.2e-38f;
+                return __builtin_fmaf(normal(rstd_up * ag), normal(ax + absmean), ab) * 0x1p-21f + 1.2e-38f;
             };
             // exact |y| of eight elements, as the cast forms them; the lanes' largest joins `best`
             auto exact = [&](bool mine, uint4 v, uint4 g, uint4 b) {

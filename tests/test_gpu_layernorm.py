@@ -233,7 +233,8 @@ def test_layernorm_error_paths():
     assert e.value.status == tw.TWEO_ERR_INVALID_ARG
 
 
-@pytest.mark.parametrize("kind", ["far mean", "nan gain", "infinite gain", "nan", "huge", "negative zeros", "late record"])
+@pytest.mark.parametrize("kind", ["far mean", "nan gain", "infinite gain", "nan", "huge", "negative zeros", "late record",
+                                  "gain below fp32 beside rstd", "gain of two bits beside rstd", "subnormal stream"])
 @pytest.mark.parametrize("shape", [(48, 512), (64, 1040), (2576, 2064), (32, 4112)])
 def test_layernorm_amax_is_that_of_the_cast_tensor(shape, kind):
     # the statistics pass finds the maximum of the normalised tensor from fp32 estimates and forms only
@@ -253,6 +254,15 @@ def test_layernorm_amax_is_that_of_the_cast_tensor(shape, kind):
     elif kind == "huge":
         xf = xf * 1e18
         gf = gf * 1e30
+    elif kind in ("gain below fp32 beside rstd", "gain of two bits beside rstd", "subnormal stream"):
+        # rstd * gamma (or the stream itself) has few bits or none left in fp32, y is an ordinary number; the
+        # seeds are such that estimates without those bits pass over the maximum
+        up, down = {"gain below fp32 beside rstd": (1e37, 1e-37), "gain of two bits beside rstd": (5e22, 1e-22),
+                    "subnormal stream": (1e-39, 5e37)}[kind]
+        rng = np.random.default_rng(11 if rows == 48 else 0)
+        xf = (rng.standard_normal((rows, cols)) * up).astype(np.float32)
+        gf = ((1 + 0.1 * rng.standard_normal(cols)) * down).astype(np.float32)
+        bf = bf if kind == "subnormal stream" else (bf * down).astype(np.float32)
     elif kind == "negative zeros":
         gf[:], bf[:] = -0.0, -0.0
     else:
