@@ -484,6 +484,34 @@ def check_bwd_pair(shape, hybrid):
         check_gemm(got[1], dwr, dwa, M, "wgrad")
 
 
+# dW may overwrite what only the input gradient reads (dYq, Wq transposed), as it could when the two
+# products always ran one after the other: shapes that otherwise share a launch, in one run and in several
+@pytest.mark.parametrize("over", ["dyq", "wqT", "dyq, last byte"])
+@pytest.mark.parametrize("shape", [(1024, 512, 512), (1040, 656, 520), (6336, 704, 512)])
+def test_bwd_weight_gradient_over_what_the_input_gradient_reads(shape, over):
+    M, N, K = shape
+    say("bwd pair overlap M=%d N=%d K=%d over=%s" % (M, N, K, over))
+    x, w, dy = synth.fp8_linear_inputs(1, 0, M=M, K=K, N=N)
+    (xq, xqT, sxi), (wq, wqT, swi), (dyq, dyqT, sdi) = (oracle_quantized(t) for t in (x, w, dy))
+    ws = workspace(tw.TWEO_OP_FP8_LINEAR_BWD, M, N, K)
+    dxr, dxa = oracle.fp8_linear_dgrad(dyq, wq, sdi, swi)
+    dwr, dwa = oracle.fp8_linear_wgrad(dyq, xq, sdi, sxi)
+    for _ in range(3):
+        buf = torch.zeros(max(M * N, K * N) + 2 * N * K + 64, dtype=torch.uint8, device=DEV)
+        src = torch.from_numpy(np.ascontiguousarray(wqT if over == "wqT" else dyq)).to(DEV)
+        held = buf[:src.numel()].view(src.shape)
+        held.copy_(src)
+        at = (src.numel() - 1) // 16 * 16 if over == "dyq, last byte" else 0
+        dw = buf[at:at + 2 * N * K].view(torch.bfloat16).view(N, K)
+        dx = torch.full((M, K), float("nan"), dtype=torch.bfloat16, device=DEV)
+        tw.tweo_fp8_linear_bwd(to_dev(dyq) if over == "wqT" else held, to_dev(np.ascontiguousarray(dyqT)), scalar_f32(sdi),
+                               held if over == "wqT" else to_dev(np.ascontiguousarray(wqT)), scalar_f32(swi),
+                               to_dev(np.ascontiguousarray(xqT)), scalar_f32(sxi), M, N, K, dx, dw, ws)
+        torch.cuda.synchronize()
+        check_gemm(bf16_bits(dx), dxr, dxa, N, "dgrad")
+        check_gemm(bf16_bits(dw), dwr, dwa, M, "wgrad")
+
+
 # the direct-to-LDS kernels under a contraction that ends inside a 64-byte stage: one to three chunks of
 # 16 in the last stage, fewer stages than the ring, one more and many
 @pytest.mark.parametrize("tile", [6, 8])
