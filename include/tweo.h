@@ -520,7 +520,9 @@ tweo_status tweo_set_gemm_tile(int variant);
  * entry point) or reduction kernels of tweo_amax that the library launches record events[2i] when the
  * kernel starts and events[2i + 1] when it ends, i.e. the kernel's own duration
  * (events recorded on the stream around a call also time the gap that recording
- * them opens in front of the kernel).  `events`: host array of 2 * pairs
+ * them opens in front of the kernel).  A GEMM of two kernels (a K split and the addition
+ * of its runs), and both products of a narrow layer's backward where they share a launch,
+ * record one pair: start of the first kernel, end of the last.  `events`: host array of 2 * pairs
  * hipEvent_t handles created by the caller with timing enabled; at most 8
  * pairs; pairs = 0 cancels.  Process-wide, not thread safe.  Returns
  * TWEO_ERR_INVALID_ARG for a null handle, TWEO_ERR_UNSUPPORTED for more than 8

@@ -2174,13 +2174,25 @@ static hipError_t launch_pair(const GemmArgs &d, const GemmArgs &w, int splits, 
         std::swap(g0, g1);
     const int n0 = g0.tiles_m * g0.tiles_n * g0.ksplit, n1 = g1.tiles_m * g1.tiles_n * g1.ksplit;
     const int n0_padded = (n0 + 7) / 8 * 8;
-    launch_gemm_kernel(kern, dim3((unsigned)(n0_padded + n1)), dim3(T::THREADS), T::LDS_BYTES, s, g0, g1, n0, n0_padded);
+    const dim3 grid((unsigned)(n0_padded + n1)), block(T::THREADS);
+    // one pair of profile events for the call: start event on its first kernel, end event on its last
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    take_profile_events(&e0, &e1);
+    if (e0 != nullptr)
+        hipExtLaunchKernelGGL(kern, grid, block, T::LDS_BYTES, s, e0, splits == 1 ? e1 : nullptr, 0, g0, g1, n0, n0_padded);
+    else
+        hipLaunchKernelGGL(kern, grid, block, T::LDS_BYTES, s, g0, g1, n0, n0_padded);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || splits == 1)
         return e;
     const int64_t mn = w.M * w.N;
-    launch_gemm_kernel(splitk_reduce_kernel<false>, dim3((unsigned)((mn / 8 + 255) / 256)), dim3(256), 0, s,
-                       (const float *)w.sk_workspace, splits, mn, w.s0, w.s1, 0.0f, (uint16_t *)w.out);
+    const dim3 rgrid((unsigned)((mn / 8 + 255) / 256));
+    if (e1 != nullptr)
+        hipExtLaunchKernelGGL(splitk_reduce_kernel<false>, rgrid, dim3(256), 0, s, nullptr, e1, 0,
+                              (const float *)w.sk_workspace, splits, mn, w.s0, w.s1, 0.0f, (uint16_t *)w.out);
+    else
+        hipLaunchKernelGGL(splitk_reduce_kernel<false>, rgrid, dim3(256), 0, s, (const float *)w.sk_workspace, splits, mn,
+                           w.s0, w.s1, 0.0f, (uint16_t *)w.out);
     return hipGetLastError();
 }
 

@@ -484,6 +484,34 @@ def check_bwd_pair(shape, hybrid):
         check_gemm(got[1], dwr, dwa, M, "wgrad")
 
 
+# events armed for both products of a backward call: products that share a launch record the first pair,
+# around all of their kernels, and leave the second to the next GEMM; apart they record one each
+@pytest.mark.parametrize("shape,pairs", [((1024, 512, 512), 1), ((6336, 704, 512), 1), ((8192, 768, 3072), 2)])
+def test_profile_events_of_a_backward_call(shape, pairs):
+    M, N, K = shape
+    say("profile events M=%d N=%d K=%d" % (M, N, K))
+    u8 = lambda *s: torch.full(s, 0x30, dtype=torch.uint8, device=DEV)
+    dyq, dyqT, wqT, xqT = u8(M, N), u8(N, M), u8(K, N), u8(K, M)
+    dx, dw = (torch.empty(s, dtype=torch.bfloat16, device=DEV) for s in ((M, K), (N, K)))
+    ws = workspace(tw.TWEO_OP_FP8_LINEAR_BWD, M, N, K)
+    one = scalar_f32(1.0)
+    call = lambda: tw.tweo_fp8_linear_bwd(dyq, dyqT, one, wqT, one, xqT, one, M, N, K, dx, dw, ws)
+    call()
+    torch.cuda.synchronize()
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(6)]
+    for e in ev:
+        e.record()   # creates the handle, in front of the call
+    tw.tweo_profile_gemm_launches([e.cuda_event for e in ev[:4]])
+    call()
+    tw.tweo_profile_gemm_launches([])
+    ev[5].record()
+    torch.cuda.synchronize()
+    recorded = [ev[4].elapsed_time(e) > 0.0 for e in ev[:4]]
+    assert recorded == [i < 2 * pairs for i in range(4)]
+    for i in range(pairs):
+        assert 0.0 < ev[2 * i].elapsed_time(ev[2 * i + 1]) < ev[4].elapsed_time(ev[5])
+
+
 # dW may overwrite what only the input gradient reads (dYq, Wq transposed), as it could when the two
 # products always ran one after the other: shapes that otherwise share a launch, in one run and in several
 @pytest.mark.parametrize("over", ["dyq", "wqT", "dyq, last byte"])
