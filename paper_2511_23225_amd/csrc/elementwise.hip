@@ -95,9 +95,13 @@ __device__ __forceinline__ uint4 inject_vec(uint4 d, uint4 a, const InjectArgs &
 // eight 16-byte loads in flight per lane (measured: ~30 % more bandwidth than a
 // grid-stride walk, whose concurrent streams are megabytes apart).
 constexpr int kAmaxUnroll = 8;
-// Smallest share of a workgroup, in 16-byte pieces (32 KB).  With 128 KB, one unrolled trip, a 12 MB
-// tensor had 96 workgroups on 256 CUs (5.6 us, now 5.2).
+// Smallest share of a workgroup, in 16-byte pieces, where each stores its own maximum (32 KB).  With
+// 128 KB, one unrolled trip, a 12 MB tensor had 96 workgroups on 256 CUs (5.6 us, now 5.2).
 constexpr int kAmaxMinChunk = 2 * kAmaxThreads;
+// Where the workgroups meet in one atomic maximum (128 KB): more of them that end together wait longer
+// for it than the shorter shares save (1000x4096 behind a clearing launch: 250 workgroups 5.4 us, 62
+// 3.9; amax + cast + GEMM into 6144 columns 37.6 us, 35.9).
+constexpr int kAmaxMinChunkAtomic = kAmaxUnroll * kAmaxThreads;
 constexpr int kAmaxMaxPartials = kAmaxPartialsMax;  // workgroups of one amax launch (one per CU)
 
 // PARTIAL: workgroup b stores its maximum to out[b] (no atomic, nothing to clear beforehand);
@@ -239,7 +243,7 @@ static hipError_t launch_amax2_impl(const void *x0_bf16, int64_t n0, float *amax
     // the workgroups of one wave over the CUs are shared out in proportion to the tensor sizes
     const int cus = amax_cus();
     const int64_t v0 = n0 / 8, v1 = n1 / 8;
-    const int64_t chunk = kAmaxMinChunk;
+    const int64_t chunk = partial ? kAmaxMinChunk : kAmaxMinChunkAtomic;
     int64_t b1 = (int64_t)((double)cus * (double)v1 / (double)(v0 + v1) + 0.5);
     if (b1 < 1)
         b1 = 1;
@@ -287,7 +291,7 @@ static hipError_t launch_amax_impl(const void *x_bf16, int64_t n, float *amax_ze
     const int n_tail = (int)(n % 8);
     // at most one workgroup per CU
     const int cus = amax_cus();
-    int64_t blocks = n_vec / kAmaxMinChunk;
+    int64_t blocks = n_vec / (partial ? kAmaxMinChunk : kAmaxMinChunkAtomic);
     if (blocks < 1)
         blocks = 1;
     if (blocks > cus)
