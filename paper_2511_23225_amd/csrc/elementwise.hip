@@ -1093,7 +1093,20 @@ hipError_t launch_quantize2_e4m3(const void *x0_bf16, int64_t rows0, int64_t col
     return hipGetLastError();
 }
 
-constexpr int kDelayedGrid = 1536;  // workgroups of a delayed-scaling cast: six per CU
+// Workgroups of a delayed-scaling cast.  Each ends with a look at one word of the state and, unless
+// that covers it, an atomic maximum there, and these queue up: so as few as keep the memory busy, two
+// tiles or more each, at most four per CU (two without the transposed copy, whose stores make most of
+// the time).  With one tile each up to six per CU the queue cost more than it hid (cast + state update,
+// us, then / now): 16384x1024 23.5 / 20.7, 8192x3072 34.0 / 27.8, 16384x5632 80.5 / 75.4; without the
+// copy 16384x1024 21.7 / 16.3, 8192x3072 32.1 / 21.6, 50432x768 35.1 / 26.3.
+static int64_t delayed_workgroups(int64_t tiles, bool transposed)
+{
+    const int64_t cus = amax_cus(), cap = (transposed ? 4 : 2) * cus;
+    if (tiles <= cus)
+        return tiles;
+    const int64_t n = tiles / 2 > cus ? tiles / 2 : cus;
+    return n < cap ? n : cap;
+}
 
 template <bool DELAYED, bool E5M2 = false>
 static hipError_t launch_quantize_e4m3_impl(const void *x_bf16, int64_t rows, int64_t cols, const float *amax,
@@ -1109,8 +1122,8 @@ static hipError_t launch_quantize_e4m3_impl(const void *x_bf16, int64_t rows, in
         const int64_t tiles_x = (cols + kTile - 1) / kTile;
         const int64_t tiles_y = (rows + kTile - 1) / kTile;
         int64_t n_wg = tiles_x * tiles_y;
-        if (DELAYED && n_wg > kDelayedGrid)
-            n_wg = kDelayedGrid;
+        if (DELAYED)
+            n_wg = delayed_workgroups(n_wg, qT != nullptr);
         const dim3 grid((unsigned)n_wg);
         if (qT)
             hipLaunchKernelGGL((cast_tile_kernel<true, DELAYED, E5M2>), grid, block, 0, s,
@@ -1808,12 +1821,12 @@ hipError_t launch_quantize2_e4m3_delayed(const void *x0_bf16, int64_t rows0, int
     float *st0 = (float *)state0, *st1 = (float *)state1;
     QuantTensorDelayed t0{(const uint16_t *)x0_bf16, rows0, cols0, tiles(cols0), st0 + 17, q0, q0T, (uint32_t *)st0 + 16};
     QuantTensorDelayed t1{(const uint16_t *)x1_bf16, rows1, cols1, tiles(cols1), st1 + 17, q1, q1T, (uint32_t *)st1 + 16};
-    // a bounded grid (its one atomic per workgroup stays a few hundred per tensor), shared out in
-    // proportion to the tile counts
+    // shared out in proportion to the tile counts
     const int64_t n0 = tiles(rows0) * tiles(cols0), n1 = tiles(rows1) * tiles(cols1);
-    int64_t b1 = (int64_t)((double)kDelayedGrid * (double)n1 / (double)(n0 + n1) + 0.5);
+    const int64_t n_wg = delayed_workgroups(n0 + n1, true);
+    int64_t b1 = (int64_t)((double)n_wg * (double)n1 / (double)(n0 + n1) + 0.5);
     b1 = b1 < 1 ? 1 : (b1 > n1 ? n1 : b1);
-    int64_t b0 = kDelayedGrid - b1;
+    int64_t b0 = n_wg - b1;
     b0 = b0 < 1 ? 1 : (b0 > n0 ? n0 : b0);
     hipLaunchKernelGGL(cast2_delayed_tile_kernel, dim3((unsigned)(b0 + b1)), dim3(kQuantThreads), 0, s, t0, b0, t1, b1);
     hipError_t e = hipGetLastError();
@@ -1894,7 +1907,11 @@ hipError_t launch_layernorm_quantize(const void *x_bf16, const void *res_bf16, c
     }
     const float *scale_src = bootstrap ? st + 21 : st + 17;
     uint32_t *acc = bootstrap ? nullptr : (uint32_t *)st + 16;
-    int64_t n_wg = n_tiles < kDelayedGrid ? n_tiles : kDelayedGrid;
+    // as in delayed_workgroups, with more arithmetic between the looks at the state: at most four per CU,
+    // six from two tiles for each of the four on (16384x1536 with six 49.7 us, with four 45.5; 43680x768
+    // 61.2 and 63.8)
+    const int64_t cus = amax_cus(), cap = (n_tiles < 8 * cus ? 4 : 6) * cus;
+    const int64_t n_wg = n_tiles < cap ? n_tiles : cap;
     if (qT)
         hipLaunchKernelGGL((cast_ln_tile_kernel<true, true>), dim3((unsigned)n_wg), block, 0, s, src, ln, rows, cols,
                            tiles_x, scale_src, q, qT, (uint16_t *)y_out, (float *)nullptr, (float *)nullptr, acc,

@@ -81,3 +81,37 @@ def test_delayed_linear_error_paths():
     with pytest.raises(tw.TweoError) as e:
         tw.tweo_fp8_linear_bwd_bf16_delayed(t, saved, None, 16, q, q, t, t)
     assert e.value.status == tw.TWEO_ERR_INVALID_ARG
+
+
+# the cast's workgroups take one 128x128 tile each or several, depending on how many there are: tile counts
+# on either side of each change, a last tile of 16 rows, the maximum anywhere
+@pytest.mark.parametrize("with_t", [True, False])
+@pytest.mark.parametrize("tiles", [1, 256, 257, 514, 1023, 1025, 2047, 2049, 2053])
+def test_delayed_cast_over_the_tile_counts(tiles, with_t):
+    rows, cols = tiles * 128 - 112, 16
+    print("delayed cast tiles=%d T=%s" % (tiles, with_t), flush=True)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(tiles)
+    before = torch.randn((rows, cols), generator=g, device=DEV).bfloat16()
+    state = torch.zeros(tw.DELAYED_STATE_WORDS, dtype=torch.float32, device=DEV)
+    u8 = lambda *s: torch.full(s, 0x55, dtype=torch.uint8, device=DEV)
+    q, qT, want, wantT = u8(rows, cols), u8(cols, rows), u8(rows, cols), u8(cols, rows)
+    gamma = torch.ones(cols, device=DEV).bfloat16()
+    y = torch.empty((rows, cols), dtype=torch.bfloat16, device=DEV)
+    ws = torch.empty(tw.tweo_workspace_bytes(tw.TWEO_OP_LAYERNORM_QUANTIZE, rows, 1, 1), dtype=torch.uint8, device=DEV)
+    amax = lambda t: (t.view(torch.int16) & 0x7FFF).max().int() << 16
+    for at in (0, rows - 1, rows // 2):
+        x = torch.randn((rows, cols), generator=g, device=DEV).bfloat16()
+        x[at, at % cols] = -1000.0
+        for layernorm in (False, True):
+            tw.tweo_delayed_state_init(state)
+            tw.tweo_quantize_e4m3_delayed(before, state, q, qT if with_t else None, bootstrap=True)
+            if layernorm:
+                tw.tweo_layernorm_quantize_e4m3_delayed(x, gamma, state, q, ws, qT=qT if with_t else None, y_out_bf16=y)
+            else:
+                tw.tweo_quantize_e4m3_delayed(x, state, q, qT if with_t else None)
+            cast = y if layernorm else x
+            tw.tweo_quantize_e4m3(cast, state[0:1], want, wantT)   # the scale of the call: from `before`'s amax
+            torch.cuda.synchronize()
+            assert int(state.view(torch.int32)[0]) == int(amax(before)) and int(state.view(torch.int32)[1]) == int(amax(cast))
+            assert torch.equal(q, want) and (not with_t or torch.equal(qT, wantT))
