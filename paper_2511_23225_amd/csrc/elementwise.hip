@@ -680,11 +680,12 @@ __device__ __forceinline__ float ln_estimate(uint4 x, uint4 gamma, uint4 beta, f
 
 __device__ __forceinline__ uint32_t fold_u16(uint32_t m) { return (m & 0xFFFFu) > (m >> 16) ? (m & 0xFFFFu) : (m >> 16); }
 
-// Row statistics: one wave per row, the first P 16-byte pieces of every lane (P = 2, 4 or 8: rows of
-// up to 1024, 2048, 4096 elements) are requested at once and stay in registers between the mean and
-// the variance, so that much of a row is read from memory once (2 B/element).  A lane past the end
+// Row statistics: one wave per row, the first P 16-byte pieces of every lane (P = 1, 2, 4 or 8: rows
+// of up to 512, 1024, 2048, 4096 elements) are requested at once and stay in registers between the mean
+// and the variance, so that much of a row is read from memory once (2 B/element).  A lane past the end
 // of the row loads its last piece again and counts it as nothing: with a branch around each load the
-// compiler waits for one before it issues the next.  RESIDUAL: the row is h = bf16(x + r), stored to
+// compiler waits for one before it issues the next.  (Pieces wholly past the end are worth a form of
+// their own: 32768x512 with a residual, current scaling, 69.5 us with P = 2, 48.7 with P = 1.)  RESIDUAL: the row is h = bf16(x + r), stored to
 // h_out on the way.
 //
 // AMAX (current scaling, and the first call on a delayed-scaling state): the pass also finds the
@@ -708,7 +709,7 @@ __device__ __forceinline__ uint32_t fold_u16(uint32_t m) { return (m & 0xFFFFu) 
 // workgroups fit the workspace.
 template <bool AMAX, int P>
 struct LnShape {
-    static constexpr int WAVES_PER_SIMD = AMAX ? (P == 2 ? 5 : P == 4 ? 4 : 2) : (P == 2 ? 7 : P == 4 ? 5 : 3);
+    static constexpr int WAVES_PER_SIMD = AMAX ? (P == 1 ? 4 : P == 2 ? 5 : P == 4 ? 4 : 2) : (P == 1 ? 8 : P == 2 ? 7 : P == 4 ? 5 : 3);
     static constexpr int WAVES = AMAX ? 2 * WAVES_PER_SIMD : 4, WG_PER_CU = AMAX ? 2 : WAVES_PER_SIMD;
     static constexpr int THREADS = WAVES * kWave;
     static constexpr int LDS_VEC = AMAX ? 2 * P * kWave : 1;  // 16-byte pieces: gamma, beta of the cached columns
@@ -1873,7 +1874,9 @@ hipError_t launch_layernorm_quantize(const void *x_bf16, const void *res_bf16, c
             res_bf16 != nullptr ? stats_launch(ln_stats_kernel<true, false, P>, LnShape<false, P>{})
                                 : stats_launch(ln_stats_kernel<false, false, P>, LnShape<false, P>{});
     };
-    if (vec <= 2 * kWave)
+    if (vec <= kWave)
+        by_flags(std::integral_constant<int, 1>{});
+    else if (vec <= 2 * kWave)
         by_flags(std::integral_constant<int, 2>{});
     else if (vec <= 4 * kWave)
         by_flags(std::integral_constant<int, 4>{});

@@ -235,7 +235,7 @@ def test_layernorm_error_paths():
 
 @pytest.mark.parametrize("kind", ["far mean", "nan gain", "infinite gain", "nan", "huge", "negative zeros", "late record",
                                   "gain below fp32 beside rstd", "gain of two bits beside rstd", "subnormal stream"])
-@pytest.mark.parametrize("shape", [(48, 512), (64, 1040), (2576, 2064), (32, 4112)])
+@pytest.mark.parametrize("shape", [(48, 512), (4112, 272), (80, 784), (64, 1040), (2576, 2064), (32, 4112)])
 def test_layernorm_amax_is_that_of_the_cast_tensor(shape, kind):
     # the statistics pass finds the maximum of the normalised tensor from fp32 estimates and forms only
     # the candidates exactly: rows whose mean dwarfs their spread (a wide bound, many candidates), values
