@@ -210,3 +210,69 @@ def test_delayed_scaling_state_checkpoint_and_restore():
         assert st[tw.DELAYED_USED_SCALE].view(np.uint32) == np.float32(used).view(np.uint32), step
         assert st[tw.DELAYED_NEXT_SCALE].view(np.uint32) == np.float32(ref.next_scale).view(np.uint32), step
         assert not st[23:].view(np.uint32).any()                # words beyond the documented ones stay 0
+
+
+# the order in which the casts' workgroups walk the tiles: rows of qT that are no whole lines (a walk wider
+# than the tensor from 7 tiles a row on, not at 18), rows of q that are none (a run of tiles for each XCD),
+# tile counts that are no multiple of 8, fewer tiles than XCDs
+@pytest.mark.parametrize("shape", [(272, 896), (400, 3968), (80, 2560), (272, 2304), (272, 1040), (400, 3088), (144, 16),
+                                   (4112, 1024), (16, 5200)])
+def test_casts_over_the_walks_of_tiles(shape):
+    say("cast walk", shape)
+    rows, cols = shape
+    rng = np.random.default_rng(rows + cols)
+    x = synth.f32_to_bf16_bits(rng.standard_normal((rows, cols)).astype(np.float32) * 3)
+    w = synth.f32_to_bf16_bits(rng.standard_normal((208, cols)).astype(np.float32))
+    xd, wd = to_dev_bf16(x), to_dev_bf16(w)
+    amax = oracle.amax_bf16(x)
+    s, _ = oracle.scale_from_amax(amax)
+    want, wantT = oracle.quantize_e4m3(x, s)
+    sw, _ = oracle.scale_from_amax(oracle.amax_bf16(w))
+    wantw, wantwT = oracle.quantize_e4m3(w, sw)
+    u8 = lambda *d: torch.full(d, 0x55, dtype=torch.uint8, device=DEV)
+    same = lambda t, ref: np.array_equal(t.cpu().numpy(), ref)
+    for transposed in (True, False):
+        q, qT, sc = u8(rows, cols), u8(cols, rows) if transposed else None, scalar_f32(float(amax))
+        tw.tweo_quantize_e4m3(xd, sc, q, qT)
+        assert same(q, want) and (not transposed or same(qT, wantT))
+        q, qT, st = u8(rows, cols), u8(cols, rows) if transposed else None, torch.zeros(32, dtype=torch.float32, device=DEV)
+        tw.tweo_delayed_state_init(st)
+        tw.tweo_quantize_e4m3_delayed(xd, st, q, qT, bootstrap=True)
+        assert same(q, want) and (not transposed or same(qT, wantT))
+        q, qT = u8(rows, cols), u8(cols, rows) if transposed else None
+        tw.tweo_quantize_e4m3_delayed(xd, st, q, qT)   # the scale of the same tensor
+        assert same(q, want) and (not transposed or same(qT, wantT))
+        # LayerNorm in front: codes of the y it stores
+        q, qT, y = u8(rows, cols), u8(cols, rows) if transposed else None, torch.empty_like(xd)
+        ws = torch.empty(tw.tweo_workspace_bytes(tw.TWEO_OP_LAYERNORM_QUANTIZE, rows, 1, 1), dtype=torch.uint8, device=DEV)
+        tw.tweo_layernorm_quantize_e4m3(xd, torch.ones(cols, device=DEV).bfloat16(), q, ws, y_out_bf16=y, qT=qT)
+        yb = y.view(torch.int16).cpu().numpy().view(np.uint16)
+        ln, lnT = oracle.quantize_e4m3(yb, oracle.scale_from_amax(oracle.amax_bf16(yb))[0])
+        assert same(q, ln) and (not transposed or same(qT, lnT))
+    # activation and weight in one launch, and the gradient with the penalty's injected
+    ws = torch.empty(max(tw.tweo_workspace_bytes(op, rows, 208, cols) for op in
+                         (tw.TWEO_OP_FP8_LINEAR_FWD_BF16, tw.TWEO_OP_FP8_LINEAR_BWD_BF16)), dtype=torch.uint8, device=DEV)
+    for delayed in (False, True):
+        xq, xqT, wq, wqT = u8(rows, cols), u8(cols, rows), u8(208, cols), u8(cols, 208)
+        saved = tw.make_saved(xq, xqT, wq, wqT, torch.zeros(16, dtype=torch.float32, device=DEV))
+        yo = torch.empty((rows, 208), dtype=torch.bfloat16, device=DEV)
+        if delayed:
+            states = [torch.zeros(32, dtype=torch.float32, device=DEV) for _ in range(2)]
+            for st in states:
+                tw.tweo_delayed_state_init(st)
+            for boot in (True, False):
+                for t in (xq, xqT, wq, wqT):
+                    t.fill_(0x55)
+                tw.tweo_fp8_linear_fwd_bf16_delayed(xd, wd, yo, saved, *states, bootstrap=boot, workspace=ws)
+        else:
+            tw.tweo_fp8_linear_fwd_bf16(xd, wd, yo, saved, workspace=ws)
+        assert same(xq, want) and same(xqT, wantT) and same(wq, wantw) and same(wqT, wantwT)
+    g = torch.zeros_like(xd)
+    wT, xT = torch.zeros((16, cols), dtype=torch.uint8, device=DEV), torch.zeros((16, rows), dtype=torch.uint8, device=DEV)
+    saved = tw.make_saved(xT, xT, wT, wT, torch.ones(16, dtype=torch.float32, device=DEV))
+    q, qT = u8(rows, cols), u8(cols, rows)
+    dx = torch.empty((rows, 16), dtype=torch.bfloat16, device=DEV)
+    ws = torch.empty(tw.tweo_workspace_bytes(tw.TWEO_OP_FP8_LINEAR_BWD_BF16, rows, cols, 16), dtype=torch.uint8, device=DEV)
+    tw.tweo_fp8_linear_bwd_bf16_inject(xd, g, (3.0, 1e-6, 4), 0.125, saved, 16, q, qT, dx, None, ws)
+    torch.cuda.synchronize()
+    assert same(q, want) and same(qT, wantT)
