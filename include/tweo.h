@@ -493,9 +493,9 @@ tweo_status tweo_fused_cast_timeouts(unsigned *count);
 
 /*
  * Tuning hook for benchmarks and tests: forces the GEMM kernel variant.
- * 0 = choose from the shape (the default).  6, 8, 4 = DMA-pipelined kernel with 64-byte
- * stages (any K % 16 == 0): 256x256 with 8 waves, 128x128, 64x64; 1 and 3 are older
- * names of 6 and 8.  11, 13, 14 =
+ * 0 = choose from the shape (the default).  1, 3 = register-staged kernel, tiles
+ * 256x256, 128x128 (any K % 16 == 0).  6, 8, 4 = DMA-pipelined kernel with 64-byte
+ * stages (any K % 16 == 0): 256x256 with 8 waves, 128x128, 64x64.  11, 13, 14 =
  * persistent streaming kernel with 128-byte stages (K % 128 == 0): 256x256,
  * 128x128, 192x256.  15 = the deferred-epilogue persistent kernel (256x256 tiles, M
  * and N multiples of 256, K a multiple of 128 and at least 512, no residual, p in

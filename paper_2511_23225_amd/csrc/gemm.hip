@@ -11,10 +11,10 @@
 // Structure of a workgroup: BM x BN output tile, WM x WN waves, each wave
 // owning a (BM/WM) x (BN/WN) sub-tile made of 32x32 MFMA blocks
 // (v_mfma_f32_32x32x64_f8f6f4 / v_mfma_i32_32x32x32_i8).  K is walked in
-// stages of 64 or 128 bytes that direct-to-LDS loads bring into a ring of LDS
-// buffers.  An LDS row is split in 16-byte chunks whose position is
-// XOR-swizzled with the row number so that the 16-byte-per-lane fragment reads
-// of 32 different rows spread over all banks.
+// slabs of 128 bytes, double buffered in LDS.  A 128-byte LDS row is split in
+// eight 16-byte chunks whose position is XOR-swizzled with the row number so
+// that the 16-byte-per-lane fragment reads of 32 different rows spread over
+// all banks.
 #include <hip/hip_ext.h>
 #include <algorithm>
 #include <cmath>
@@ -22,6 +22,26 @@
 #include "gemm_defer.h"
 
 namespace tweo {
+
+constexpr int kBK = 128;  // bytes of K per LDS stage
+
+// Physical 16-byte chunk of logical chunk c in LDS row `row`.
+__device__ __forceinline__ int swz(int row, int c) { return c ^ ((row ^ (row >> 3)) & 7); }
+
+template <int BM_, int BN_, int WM_, int WN_>
+struct Tile {
+    static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_;
+    static constexpr int THREADS = WM * WN * kWave;
+    static constexpr int TM = BM / WM, TN = BN / WN;  // per-wave sub-tile
+    static constexpr int MT = TM / 32, NT = TN / 32;  // 32x32 MFMA blocks per wave
+    static constexpr int STAGE_BYTES = (BM + BN) * kBK;
+    static constexpr int LDS_BYTES = 2 * STAGE_BYTES;
+    static constexpr int A_LD = BM * 8 / THREADS;  // 16-byte chunks per thread per stage
+    static constexpr int B_LD = BN * 8 / THREADS;
+    static_assert(TM % 32 == 0 && TN % 32 == 0, "wave tile must be made of 32x32 blocks");
+    static_assert((BM * 8) % THREADS == 0 && (BN * 8) % THREADS == 0, "loader split");
+};
+
 
 // Workgroups are dealt round-robin to the 8 XCDs (each with its own L2).  Give
 // every XCD a contiguous run of tile ids, and walk tile ids in groups of 8 tile
@@ -303,6 +323,151 @@ __device__ __forceinline__ void store_ksplit_run(const GemmDev &g, ACC (&acc)[T:
                 }
             }
     }
+}
+
+template <typename T, bool INT8, bool A_E5M2 = false>
+__global__ __launch_bounds__(T::THREADS) void gemm_nt_kernel(GemmDev g)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    constexpr int BM = T::BM, BN = T::BN;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int wm = wave / T::WN, wn = wave % T::WN;
+    int tm, tn;
+    tile_of_workgroup((int)blockIdx.x, g.tiles_m, g.tiles_n, tm, tn);
+
+    // ---- global -> register -> LDS staging --------------------------------
+    // chunk id = tid + i*THREADS : row = id/8, chunk-in-row = id%8 (same for all i)
+    const int ld_row0 = tid >> 3, ld_ch = tid & 7;
+    constexpr int ROW_STEP = T::THREADS / 8;
+    const uint8_t *Abase = g.A + (int64_t)tm * BM * g.K + ld_ch * 16;
+    const uint8_t *Bbase = g.B + (int64_t)tn * BN * g.K + ld_ch * 16;
+    const int a_rows = g.M - tm * BM, b_rows = g.N - tn * BN;  // valid rows in this tile (>0)
+    uint32_t a_off[T::A_LD], b_off[T::B_LD];
+    int a_lds[T::A_LD], b_lds[T::B_LD];
+#pragma unroll
+    for (int i = 0; i < T::A_LD; ++i) {
+        int row = ld_row0 + i * ROW_STEP;
+        int grow = row < a_rows ? row : a_rows - 1;  // clamp: rows past M are never stored
+        a_off[i] = (uint32_t)grow * (uint32_t)g.K;
+        a_lds[i] = row * kBK + swz(row, ld_ch) * 16;
+    }
+#pragma unroll
+    for (int i = 0; i < T::B_LD; ++i) {
+        int row = ld_row0 + i * ROW_STEP;
+        int grow = row < b_rows ? row : b_rows - 1;
+        b_off[i] = (uint32_t)grow * (uint32_t)g.K;
+        b_lds[i] = BM * kBK + row * kBK + swz(row, ld_ch) * 16;
+    }
+    v4i a_reg[T::A_LD], b_reg[T::B_LD];
+    auto load_global = [&](int k0) {
+        const bool k_ok = k0 + ld_ch * 16 < g.K;  // K % 16 == 0: a chunk is all in or all out
+#pragma unroll
+        for (int i = 0; i < T::A_LD; ++i)
+            a_reg[i] = k_ok ? *(const v4i *)(Abase + a_off[i] + k0) : v4i{0, 0, 0, 0};
+#pragma unroll
+        for (int i = 0; i < T::B_LD; ++i)
+            b_reg[i] = k_ok ? *(const v4i *)(Bbase + b_off[i] + k0) : v4i{0, 0, 0, 0};
+    };
+    auto store_lds = [&](int stage) {
+        uint8_t *s = smem + stage * T::STAGE_BYTES;
+#pragma unroll
+        for (int i = 0; i < T::A_LD; ++i)
+            *(v4i *)(s + a_lds[i]) = a_reg[i];
+#pragma unroll
+        for (int i = 0; i < T::B_LD; ++i)
+            *(v4i *)(s + b_lds[i]) = b_reg[i];
+    };
+
+    // ---- accumulators -------------------------------------------------------
+    using acc_t = typename std::conditional<INT8, v16i, v16f>::type;
+    acc_t acc[T::MT][T::NT];
+#pragma unroll
+    for (int i = 0; i < T::MT; ++i)
+#pragma unroll
+        for (int j = 0; j < T::NT; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                acc[i][j][v] = 0;
+
+    // fragment rows of this lane inside the stage
+    const int l31 = lane & 31, lh = lane >> 5;
+    const int a_row0 = wm * T::TM + l31;  // + mt*32
+    const int b_row0 = wn * T::TN + l31;  // + nt*32
+
+    auto compute_stage = [&](int stage) {
+        const uint8_t *sA = smem + stage * T::STAGE_BYTES;
+        const uint8_t *sB = sA + BM * kBK;
+        if constexpr (!INT8) {
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk) {  // two K=64 slabs
+                v8i fa[T::MT], fb[T::NT];
+                const int c0 = kk * 4 + lh * 2;
+#pragma unroll
+                for (int i = 0; i < T::MT; ++i) {
+                    int row = a_row0 + i * 32;
+                    v4i x0 = *(const v4i *)(sA + row * kBK + swz(row, c0) * 16);
+                    v4i x1 = *(const v4i *)(sA + row * kBK + swz(row, c0 + 1) * 16);
+                    fa[i] = v8i{x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
+                }
+#pragma unroll
+                for (int j = 0; j < T::NT; ++j) {
+                    int row = b_row0 + j * 32;
+                    v4i x0 = *(const v4i *)(sB + row * kBK + swz(row, c0) * 16);
+                    v4i x1 = *(const v4i *)(sB + row * kBK + swz(row, c0 + 1) * 16);
+                    fb[j] = v8i{x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
+                }
+#pragma unroll
+                for (int i = 0; i < T::MT; ++i)
+#pragma unroll
+                    for (int j = 0; j < T::NT; ++j)
+                        // first operand -> register-distributed index (n), second -> lane index (m)
+                        // source formats: the first (B) always E4M3, the second (A) E4M3 or E5M2
+                        acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+                            fb[j], fa[i], acc[i][j], 0, A_E5M2 ? 1 : 0, 0, 0, 0, 0);
+            }
+        } else {
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) {  // four K=32 slabs
+                v4i fa[T::MT], fb[T::NT];
+                const int c0 = kk * 2 + lh;
+#pragma unroll
+                for (int i = 0; i < T::MT; ++i) {
+                    int row = a_row0 + i * 32;
+                    fa[i] = *(const v4i *)(sA + row * kBK + swz(row, c0) * 16);
+                }
+#pragma unroll
+                for (int j = 0; j < T::NT; ++j) {
+                    int row = b_row0 + j * 32;
+                    fb[j] = *(const v4i *)(sB + row * kBK + swz(row, c0) * 16);
+                }
+#pragma unroll
+                for (int i = 0; i < T::MT; ++i)
+#pragma unroll
+                    for (int j = 0; j < T::NT; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fb[j], fa[i], acc[i][j],
+                                                                          0, 0, 0);
+            }
+        }
+    };
+
+    // ---- main loop ----------------------------------------------------------
+    const int k_tiles = (g.K + kBK - 1) / kBK;
+    load_global(0);
+    store_lds(0);
+    __syncthreads();
+    for (int kt = 0; kt < k_tiles; ++kt) {
+        const bool more = kt + 1 < k_tiles;
+        if (more)
+            load_global((kt + 1) * kBK);
+        compute_stage(kt & 1);
+        if (more)
+            store_lds((kt + 1) & 1);
+        __syncthreads();
+    }
+
+    // the loop ends with a barrier: every wave is done reading the stages
+    NoBandHook no_hook;
+    epilogue<T, INT8>(g, acc, smem, tm, tn, wm, wn, lane, wave, tid, blockIdx.x, no_hook);
 }
 
 // ---------------------------------------------------------------------------
@@ -1289,10 +1454,12 @@ __global__ __launch_bounds__(256) void splitk_reduce_defer_kernel(const float4 *
 // ---------------------------------------------------------------------------
 // host side
 
+typedef Tile<256, 256, 2, 2> T256x256;
+typedef Tile<128, 128, 2, 2> T128x128;
 typedef TileD<256, 256, 2, 4, 4, 2> D256x256w8;
 typedef TileD<128, 128, 2, 2, 4, 2> D128x128w4;
 // Small outputs: a contraction of 512 is one memory latency, all eight stages in flight at once, and
-// four waves a tile (256x512x512: 4.0 us; staged through registers by one wave a tile it took 6.8).
+// four waves share what a register-staged wave did alone (256x512x512: 6.8 us, now 4.0).
 typedef TileD<64, 64, 2, 2, 8, 2> D64x64w4;
 typedef TileS<256, 256, 2, 4, 2, 2> S256x256w8;  // persistent, 8 waves, one workgroup per CU
 typedef TileS<128, 128, 2, 2, 2, 2> S128x128w4;  // two workgroups per CU
@@ -1337,8 +1504,7 @@ static void launch_gemm_kernel(KERNEL kernel, dim3 grid, dim3 block, size_t lds,
 int num_cus_public();
 static int g_tile_override = 0;
 static bool g_stream_k_off = true;  // measured slower than the plain schedule on MI355X: opt-in
-// 1 and 3 are the numbers of a retired kernel of the tiles of 6 and 8
-void set_gemm_tile_override(int variant) { g_tile_override = variant == 1 ? 6 : (variant == 3 ? 8 : variant); }
+void set_gemm_tile_override(int variant) { g_tile_override = variant; }
 void set_stream_k(bool on) { g_stream_k_off = !on; }
 bool stream_k_enabled() { return !g_stream_k_off; }
 
@@ -1352,7 +1518,7 @@ size_t stream_k_workspace_bytes()
 }
 
 // Kernel variants (the numbers are what tweo_set_gemm_tile takes; retired ones are refused).
-// 6, 8, 4:
+// 1, 3: register-staged kernel, tiles 256x256, 128x128 (no shape is sent there any more).  6, 8, 4:
 // DMA-pipelined kernel on 64-byte stages, 256x256 with 8 waves, 128x128 and 64x64.  11, 13,
 // 14: persistent streaming kernel (K % 128 == 0): 256x256, 128x128, 192x256.  15: deferred-epilogue
 // persistent kernel (256x256, four waves; M, N % 256 == 0, K % 128 == 0, K >= 512).  16: the same
@@ -1491,13 +1657,18 @@ int fp8_gemm_partials(const GemmArgs &a)
     return (int)(((a.M + kVariantBM[v] - 1) / kVariantBM[v]) * ((a.N + kVariantBN[v] - 1) / kVariantBN[v]));
 }
 
-template <typename T, bool INT8, bool A_E5M2 = false>
+template <typename T, bool INT8, bool DMA, bool A_E5M2 = false>
 static hipError_t launch_tile(const GemmArgs &a, hipStream_t s)
 {
-    constexpr auto kern = gemm_nt_dma_kernel<T, INT8, 0, A_E5M2>;
     static bool attr_done = false;  // per instantiation
+    const void *kern;
+    if constexpr (DMA)
+        kern = (const void *)gemm_nt_dma_kernel<T, INT8, 0, A_E5M2>;
+    else
+        kern = (const void *)gemm_nt_kernel<T, INT8, A_E5M2>;
     if (!attr_done) {
-        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
+        hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           T::LDS_BYTES);
         if (e != hipSuccess)
             return e;
         attr_done = true;
@@ -1527,7 +1698,10 @@ static hipError_t launch_tile(const GemmArgs &a, hipStream_t s)
     g.tiles_m = (int)((a.M + T::BM - 1) / T::BM);
     g.tiles_n = (int)((a.N + T::BN - 1) / T::BN);
     const dim3 grid((unsigned)(g.tiles_m * g.tiles_n)), block(T::THREADS);
-    launch_gemm_kernel(kern, grid, block, T::LDS_BYTES, s, g);
+    if constexpr (DMA)
+        launch_gemm_kernel(gemm_nt_dma_kernel<T, INT8, 0, A_E5M2>, grid, block, T::LDS_BYTES, s, g);
+    else
+        launch_gemm_kernel(gemm_nt_kernel<T, INT8, A_E5M2>, grid, block, T::LDS_BYTES, s, g);
     return hipGetLastError();
 }
 
@@ -1706,9 +1880,11 @@ template <bool INT8>
 static hipError_t launch_gemm(const GemmArgs &a, hipStream_t s)
 {
     switch (resolve_variant(a)) {
-    case 4: return launch_tile<D64x64w4, INT8>(a, s);
-    case 6: return launch_tile<D256x256w8, INT8>(a, s);
-    case 8: return launch_tile<D128x128w4, INT8>(a, s);
+    case 1: return launch_tile<T256x256, INT8, false>(a, s);
+    case 3: return launch_tile<T128x128, INT8, false>(a, s);
+    case 4: return launch_tile<D64x64w4, INT8, true>(a, s);
+    case 6: return launch_tile<D256x256w8, INT8, true>(a, s);
+    case 8: return launch_tile<D128x128w4, INT8, true>(a, s);
     case 11: return launch_stream<S256x256w8, INT8, 1>(a, s);
     case 13: return launch_stream<S128x128w4, INT8, 2>(a, s);
     case 14: return launch_stream<S192x256w8, INT8, 1>(a, s);
@@ -1754,7 +1930,7 @@ int fp8_gemm_ksplit(int64_t M, int64_t N, int64_t K)
     const int ds = defer_ksplit(M, N, K);
     if (ds > 1)
         return ds;
-    const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256), k_tiles = (K + 127) / 128;
+    const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256), k_tiles = (K + kBK - 1) / kBK;
     const int64_t cus = num_cus();
     if (tiles * 4 > cus || k_tiles < 128)
         return 1;
@@ -2043,16 +2219,19 @@ hipError_t launch_fp8_gemm_pair(const GemmArgs &d, const GemmArgs &w, hipStream_
 }
 
 // E5M2 A operand (gradient GEMMs of the HYBRID recipe; no penalty, no residual): the kernels that the
-// same product of E4M3 codes runs on (delayed scaling, forward + backward: 8192x3072 -> 768 137 us,
-// 22480x512 -> 512 119 us; 155 and 139 on a kernel that staged through registers).
+// same product of E4M3 codes runs on.  (The streaming and direct-to-LDS kernels did not take
+// E5M2 before and everything but the deferred kernel's shapes ran register-staged; delayed scaling,
+// forward + backward: 8192x3072 -> 768 155 -> 137 us, 22480x512 -> 512 139 -> 119.)
 static hipError_t launch_fp8_gemm_e5m2(const GemmArgs &a, hipStream_t s)
 {
     if (a.p != 0 || a.residual != nullptr)
         return hipErrorInvalidValue;
     switch (resolve_variant(a)) {
-    case 4: return launch_tile<D64x64w4, false, true>(a, s);
-    case 6: return launch_tile<D256x256w8, false, true>(a, s);
-    case 8: return launch_tile<D128x128w4, false, true>(a, s);
+    case 1: return launch_tile<T256x256, false, false, true>(a, s);
+    case 3: return launch_tile<T128x128, false, false, true>(a, s);
+    case 4: return launch_tile<D64x64w4, false, true, true>(a, s);
+    case 6: return launch_tile<D256x256w8, false, true, true>(a, s);
+    case 8: return launch_tile<D128x128w4, false, true, true>(a, s);
     case 11: return launch_stream<S256x256w8, false, 1, true>(a, s);
     case 13: return launch_stream<S128x128w4, false, 2, true>(a, s);
     case 14: return launch_stream<S192x256w8, false, 1, true>(a, s);

@@ -75,7 +75,7 @@ def oracle_e5m2(x):
     return q, qT, si
 
 
-# tiny (64x64 tiles), ragged, mid-sized (both products in one launch), whole-tile shapes for
+# tiny (64x64 tiles), ragged, mid-sized (register-staged 128 / 256 tiles), whole-tile shapes for
 # the deferred-epilogue kernel (dgrad: rows M, contraction N; wgrad: rows N, contraction M) with
 # one and with several tiles per workgroup, and a long contraction that takes the 192-row tiles
 HYBRID_CASES = [
