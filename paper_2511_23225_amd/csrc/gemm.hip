@@ -1518,7 +1518,8 @@ size_t stream_k_workspace_bytes()
 }
 
 // Kernel variants (the numbers are what tweo_set_gemm_tile takes; retired ones are refused).
-// 1, 3: register-staged kernel, tiles 256x256, 128x128 (no shape is sent there any more).  6, 8, 4:
+// 1, 3: register-staged kernel, tiles 256x256 (no shape is sent there any more), 128x128 (ragged
+// contractions under many tiles).  6, 8, 4:
 // DMA-pipelined kernel on 64-byte stages, 256x256 with 8 waves, 128x128 and 64x64.  11, 13,
 // 14: persistent streaming kernel (K % 128 == 0): 256x256, 128x128, 192x256.  15: deferred-epilogue
 // persistent kernel (256x256, four waves; M, N % 256 == 0, K % 128 == 0, K >= 512).  16: the same
@@ -1622,6 +1623,14 @@ static int pick_variant(int64_t M, int64_t N, int64_t K)
     }
     if (v >= 11 && K % 128 != 0)  // the persistent kernels need whole 128-byte stages
         v = v == 13 ? 8 : 6;
+    // Rows that are no whole number of 64-byte stages: a direct-to-LDS stage of a row then lies across two
+    // lines, and two such tiles on a CU wait for twice the lines.  With more 128x128 tiles than CUs the
+    // register-staged kernel, whose stages are whole 128 bytes, is ahead from a contraction of 512 on (us,
+    // direct-to-LDS / register-staged: 2560x2048 under 528 / 2064 / 16400: 10.4 / 10.2, 26.9 / 21.9, 194 /
+    // 133; 50448x768 under 528 / 3088: 52 / 49, 233 / 180); with at most one tile per CU it is behind
+    // (2048x2048 under 2064 18.4 / 21.4), and below 512 (2560x2048 under 400 8.6 / 9.5).
+    if (g_tile_override == 0 && v == 8 && K % 64 != 0 && K >= 512 && tiles(128, 128) > (int64_t)num_cus())
+        v = 3;
     return v;
 }
 
@@ -2095,6 +2104,8 @@ static double lone_gemm_us(int64_t M, int64_t N, int64_t K)
     if (v == 11 || v == 14)
         return 1.45 * kt * (v == 14 ? 0.77 : 1.0) * std::ceil((double)tiles(M, N, v == 14 ? 192 : 256, 256) / cus) + 6.0;
     const double t = (double)tiles(M, N, 128, 128);
+    if (v == 3)
+        return 0.57 * std::ceil(t / (2.0 * cus)) * 2.0 * kt + 4.0;
     return (t <= cus ? 0.5 : 0.74 * std::ceil(t / (2.0 * cus))) * 2.0 * kt + 4.0;
 }
 

@@ -566,6 +566,46 @@ def test_fwd_contraction_ends_inside_a_stage(tile, K):
     check_gemm(got, ref, refabs, K, "fwd ragged K")
 
 
+# a contraction that is no multiple of 64 under more 128x128 tiles than CUs: register-staged from 512 on,
+# direct-to-LDS below; forward with residual and penalty, both gradient formats, INT8
+@pytest.mark.parametrize("K", [496, 528, 1040])
+def test_ragged_contraction_under_many_tiles(K):
+    M, N = 2176, 2168
+    say("ragged K=%d under many tiles" % K)
+    x, w, _ = synth.fp8_linear_inputs(1, 0, M=M, K=K, N=N)
+    xq, xqT, sxi = oracle_quantized(x)
+    wq, wqT, swi = oracle_quantized(w)
+    res = synth.residual_input(1, 0, M, N)
+    for r in (None, res):
+        ref, refabs, refbf = oracle.fp8_linear_fwd(xq, wq, sxi, swi, residual=r)
+        got, S = run_fwd(xq, wq, sxi, swi, M, N, K, residual=r)
+        check_gemm(got, ref, refabs, K, "fwd")
+        check_penalty(S, got, refbf, oracle.penalty_sum(refbf, *PEN), PEN, strict=True)
+    # the weight gradient [N2, M] = dy^T x over K tokens
+    N2 = 2160
+    for hybrid in (False, True):
+        dy = synth.fp8_linear_inputs(1, 1, M=K, K=N2, N=16)[0]
+        if hybrid:
+            s, sdi = oracle.scale_from_amax_e5m2(oracle.amax_bf16(dy))
+            dyq, dyqT = oracle.quantize_e5m2(dy, s)
+        else:
+            dyq, dyqT, sdi = oracle_quantized(dy)
+        act = np.ascontiguousarray(xqT)   # [K, M] codes: K tokens of M channels
+        dw = torch.full((N2, M), float("nan"), dtype=torch.bfloat16, device=DEV)
+        call = tw.tweo_fp8_linear_bwd_hybrid if hybrid else tw.tweo_fp8_linear_bwd
+        d = [to_dev(np.ascontiguousarray(t)) for t in (dyq, dyqT, act, act.T)]
+        call(d[0], d[1], scalar_f32(sdi), d[2], scalar_f32(swi), d[3], scalar_f32(sxi), K, N2, M, dw_bf16=dw)
+        torch.cuda.synchronize()
+        ref, refabs = oracle.fp8_linear_wgrad(dyq, act, sdi, sxi, dy_e5m2=hybrid)
+        check_gemm(bf16_bits(dw), ref, refabs, K, "wgrad")
+    rng = np.random.default_rng(K)
+    a8, b8 = (rng.integers(-127, 128, (n, K), dtype=np.int8) for n in (M, N))
+    y = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device=DEV)
+    tw.tweo_w8a8_linear(to_dev(a8), to_dev(b8), 0.001, y)
+    torch.cuda.synchronize()
+    assert np.array_equal(bf16_bits(y), oracle.w8a8_linear(a8, b8, 0.001))
+
+
 # backward products whose contractions (tokens, output columns) are multiples of 16 only: one launch,
 # a K split of ragged tiles, and the shapes' plain kernels
 @pytest.mark.parametrize("hybrid", [False, True])
