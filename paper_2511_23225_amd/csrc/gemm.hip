@@ -500,9 +500,11 @@ struct TileD {
 
 
 // KSPLIT: 1 = g.ksplit runs of the tile grid, 0 = none (a flag of its own: compiled in for all, the
-// second way out of the kernel cost the unsplit INT8 launches 2 %), 2 = g.ksplit says.  block: the
-// workgroup's number in g's grid.
-template <typename T, bool INT8, bool A_E5M2, int KSPLIT>
+// second way out of the kernel cost the unsplit INT8 launches 2 %), 2 = g.ksplit says.  RAGGED: K may
+// be no multiple of 64 (without a flag the last stage's conditions cost whole stages 1-4 %: 8208x4000 under
+// 320 28.9 us against 28.2, INT8 16400x768 under 576 15.0 against 14.4).  block: the workgroup's number
+// in g's grid.
+template <typename T, bool INT8, bool A_E5M2, int KSPLIT, bool RAGGED>
 __device__ __forceinline__ void gemm_nt_dma_body(const GemmDev &g, const int block)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -527,7 +529,7 @@ __device__ __forceinline__ void gemm_nt_dma_body(const GemmDev &g, const int blo
     // of those chunks are cleared: 0 times any code of that row of B but a NaN, which makes the whole
     // column a NaN anyway.
     const int tail = (g.K & (T::BK - 1)) >> 4;
-    const bool ragged = tail != 0 && kt_begin + kt == kt_all;
+    const bool ragged = RAGGED && tail != 0 && kt_begin + kt == kt_all;
 
     // ---- DMA addressing -----------------------------------------------------
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)smem;
@@ -711,10 +713,10 @@ __device__ __forceinline__ void gemm_nt_dma_body(const GemmDev &g, const int blo
     }
 }
 
-template <typename T, bool INT8, int KSPLIT = 0, bool A_E5M2 = false>
+template <typename T, bool INT8, int KSPLIT = 0, bool A_E5M2 = false, bool RAGGED = true>
 __global__ __launch_bounds__(T::THREADS, T::WPE) void gemm_nt_dma_kernel(GemmDev g)
 {
-    gemm_nt_dma_body<T, INT8, A_E5M2, KSPLIT>(g, (int)blockIdx.x);
+    gemm_nt_dma_body<T, INT8, A_E5M2, KSPLIT, RAGGED>(g, (int)blockIdx.x);
 }
 
 // The two products of a linear layer's backward in one launch: workgroups [0, n0) are the grid of g0,
@@ -727,7 +729,7 @@ __global__ __launch_bounds__(T::THREADS, T::WPE) void gemm_nt_dma_pair_kernel(Ge
     if (b >= n0 && b < n0_padded)
         return;
     const bool first = b < n0;
-    gemm_nt_dma_body<T, false, A_E5M2, 2>(first ? g0 : g1, first ? b : b - n0_padded);
+    gemm_nt_dma_body<T, false, A_E5M2, 2, true>(first ? g0 : g1, first ? b : b - n0_padded);
 }
 
 // ---------------------------------------------------------------------------
@@ -1666,13 +1668,13 @@ int fp8_gemm_partials(const GemmArgs &a)
     return (int)(((a.M + kVariantBM[v] - 1) / kVariantBM[v]) * ((a.N + kVariantBN[v] - 1) / kVariantBN[v]));
 }
 
-template <typename T, bool INT8, bool DMA, bool A_E5M2 = false>
-static hipError_t launch_tile(const GemmArgs &a, hipStream_t s)
+template <typename T, bool INT8, bool DMA, bool A_E5M2, bool RAGGED>
+static hipError_t launch_tile_inst(const GemmArgs &a, hipStream_t s)
 {
     static bool attr_done = false;  // per instantiation
     const void *kern;
     if constexpr (DMA)
-        kern = (const void *)gemm_nt_dma_kernel<T, INT8, 0, A_E5M2>;
+        kern = (const void *)gemm_nt_dma_kernel<T, INT8, 0, A_E5M2, RAGGED>;
     else
         kern = (const void *)gemm_nt_kernel<T, INT8, A_E5M2>;
     if (!attr_done) {
@@ -1708,10 +1710,19 @@ static hipError_t launch_tile(const GemmArgs &a, hipStream_t s)
     g.tiles_n = (int)((a.N + T::BN - 1) / T::BN);
     const dim3 grid((unsigned)(g.tiles_m * g.tiles_n)), block(T::THREADS);
     if constexpr (DMA)
-        launch_gemm_kernel(gemm_nt_dma_kernel<T, INT8, 0, A_E5M2>, grid, block, T::LDS_BYTES, s, g);
+        launch_gemm_kernel(gemm_nt_dma_kernel<T, INT8, 0, A_E5M2, RAGGED>, grid, block, T::LDS_BYTES, s, g);
     else
         launch_gemm_kernel(gemm_nt_kernel<T, INT8, A_E5M2>, grid, block, T::LDS_BYTES, s, g);
     return hipGetLastError();
+}
+
+template <typename T, bool INT8, bool DMA, bool A_E5M2 = false>
+static hipError_t launch_tile(const GemmArgs &a, hipStream_t s)
+{
+    if constexpr (DMA)
+        if (a.K % 64 != 0)
+            return launch_tile_inst<T, INT8, true, A_E5M2, true>(a, s);
+    return launch_tile_inst<T, INT8, DMA, A_E5M2, false>(a, s);
 }
 
 // Stream-K pays when a tile count leaves a noticeable part of the last round idle and each
