@@ -2093,38 +2093,45 @@ static hipError_t launch_ksplit_defer(const GemmArgs &a, hipStream_t s, int spli
     return hipGetLastError();
 }
 
-// Time of one gradient product by itself in microseconds, from what the kernels measured on layers of
-// 768 to 3072 columns over 8192 rows (within 10 %): two 128x128 tiles on a CU advance one 64-byte stage
-// in 0.74 us (a lone one in 0.5), a 256x256 tile of the deferred kernel a 128-byte stage in 1.25, of the
-// 8-wave kernel in 1.45, a 64x64 tile alone on its CU a 64-byte stage in 0.135; runs of a K split are
-// written at 5 TB/s and read at 6.5.
+// Time of one gradient product by itself in microseconds, from what the kernels measured (190 layers of 256
+// to 6144 columns over 256 to 50432 rows, medians within 5 % per kernel, single ones within 25 %).  Per
+// 64-byte stage: a 64x64 tile alone on its CU 0.135; a 128x128 tile alone on its CU 0.28, two 0.58
+// (streaming: 0.37; a contraction that is no multiple of 64: 0.375 and 0.8, register-staged 0.57); a
+// 256x256 tile 0.8 (1.05).  Per 128-byte stage: a 256x256 tile of the deferred kernel 1.25, of the 8-wave
+// kernel 1.45.  Runs of a K split are written at 5 TB/s and read at 6.5.
 static double lone_gemm_us(int64_t M, int64_t N, int64_t K)
 {
     const double cus = num_cus(), kt = (double)(K + 127) / 128;
-    auto tiles = [](int64_t r, int64_t c, int64_t tr, int64_t tc) { return ((r + tr - 1) / tr) * ((c + tc - 1) / tc); };
-    const int ds = defer_ksplit(M, N, K);
-    if (ds > 1) {
-        const double mb = (double)ds * (double)M * (double)N * 4e-6;
-        return 1.3 * kt / ds + 3.0 + mb / 5.0 + 2.5 + mb / 6.5;
+    const bool ragged = K % 64 != 0;
+    auto rounds = [&](int64_t tr, int64_t tc, double slots) {
+        return std::ceil((double)(((M + tr - 1) / tr) * ((N + tc - 1) / tc)) / slots);
+    };
+    const int ds = defer_ksplit(M, N, K), ks = ds > 1 ? ds : fp8_gemm_ksplit(M, N, K);
+    if (ks > 1) {
+        const double mb = (double)ks * (double)M * (double)N * 4e-6, runs = mb / 5.0 + 2.5 + mb / 6.5;
+        return (ds > 1 ? 1.3 * kt / ks + 3.0 : (ragged ? 1.3 : 0.85) * 2.0 * kt / ks + 5.0) + runs;
     }
     const int v = pick_variant(M, N, K);
     if (v == 4)
         return (tiles64(M, N) <= (int64_t)cus ? 0.135 : 0.26) * 2.0 * kt + 3.0;
     if (v == 15 || v == 16)
-        return 1.25 * kt * (v == 16 ? 0.77 : 1.0) * std::ceil((double)tiles(M, N, v == 16 ? 192 : 256, 256) / cus) + 6.0;
+        return 1.25 * kt * (v == 16 ? 0.77 : 1.0) * rounds(v == 16 ? 192 : 256, 256, cus) + 6.0;
     if (v == 11 || v == 14)
-        return 1.45 * kt * (v == 14 ? 0.77 : 1.0) * std::ceil((double)tiles(M, N, v == 14 ? 192 : 256, 256) / cus) + 6.0;
-    const double t = (double)tiles(M, N, 128, 128);
-    if (v == 3)
-        return 0.57 * std::ceil(t / (2.0 * cus)) * 2.0 * kt + 4.0;
-    return (t <= cus ? 0.5 : 0.74 * std::ceil(t / (2.0 * cus))) * 2.0 * kt + 4.0;
+        return 1.45 * kt * (v == 14 ? 0.77 : 1.0) * rounds(v == 14 ? 192 : 256, 256, cus) + 6.0;
+    if (v == 6)
+        return (ragged ? 1.05 : 0.8) * 2.0 * kt * rounds(256, 256, cus) + 5.0;
+    const bool alone = rounds(128, 128, cus) <= 1.0;
+    const double stage = v == 3 ? 0.57 : v == 13 ? (alone ? 0.28 : 0.37)
+                                                 : (ragged ? (alone ? 0.375 : 0.8) : (alone ? 0.28 : 0.58));
+    return stage * 2.0 * kt * rounds(128, 128, alone && v != 3 ? cus : 2.0 * cus) + 4.0;
 }
 
 // The two gradient products of a layer in one launch of 128x128 tiles (gemm_nt_dma_pair_kernel), the
 // weight gradient's contraction in `splits` runs; 0 = the two run one after the other.  The pair fills
-// the chip where each alone would leave CUs idle, but its kernel is no fast one (0.92 us per 64-byte
-// stage of two tiles on a CU): taken where the two ways' times, estimated from those rates, say so.
-// 8192x768 -> 768: 40.5 us in three launches, 32.9 in two; 8192x3072 -> 768 stays apart (64 against 75).
+// the chip where each alone would leave CUs idle, but its kernel is no fast one: taken where the two ways'
+// times, estimated from measured rates, say so (backward, us, apart / paired: 8192x768 -> 768 36.6 / 30.0,
+// 2128x3776 -> 880 40.8 / 36.3; 8192x3072 -> 768 stays apart, 54 / 66, and so does 35984x1536 -> 1280,
+// 202 / 241).
 static bool pair_is_small(int64_t M, int64_t N, int64_t K) { return tiles64(M, K) + tiles64(N, K) <= 2 * (int64_t)num_cus(); }
 static int pair_splits(int64_t M, int64_t N, int64_t K)
 {
@@ -2139,22 +2146,35 @@ static int pair_splits(int64_t M, int64_t N, int64_t K)
         return 0;
     const double slots = 2.0 * num_cus();
     const int64_t kd = (N + 63) / 64, kw = (M + 63) / 64, td = tiles(M, K), tw = tiles(N, K);
+    // stages that lie across lines take a sixth longer
+    const double fd = N % 64 != 0 ? 1.16 : 1.0, fw = M % 64 != 0 ? 1.16 : 1.0;
+    auto runs_us = [&](int r) { return r > 1 ? (double)r * (double)N * (double)K * 4e-6 / 6.5 + 2.5 : 0.0; };
+    // The number of runs: the cost of a long last unit against the runs' way through memory.  A contraction
+    // of up to 4096 stays whole, as on the deferred kernel (whose split lost there, 14 -> 20 us), so that
+    // such a layer's backward needs no scratch beyond its scalars.
+    const double load = (fd * (double)(td * kd) + fw * (double)(tw * kw)) / slots;
     int best = 0;
-    double best_us = 0.97 * (lone_gemm_us(M, K, N) + lone_gemm_us(N, K, M));
-    // a contraction of up to 4096 stays whole, as on the deferred kernel (whose split lost there, 14 ->
-    // 20 us), so that such a layer's backward needs no scratch beyond its scalars
-    for (int s = 1; s <= (kw > 64 ? 16 : 1) && kw / s >= 8; ++s) {
-        // stages per slot at two tiles to a CU, or the longest unit, which ends up alone on its CU; the
-        // uneven end; the runs' way through memory
-        const double longest = (double)std::max(kd, (kw + s - 1) / s), mb = s > 1 ? (double)s * (double)N * (double)K * 4e-6 : 0.0;
-        const double us = std::max(0.92 * (double)(td * kd + tw * kw) / slots, 0.62 * longest) + 0.15 * longest + 4.0 +
-                          (s > 1 ? mb / 6.5 + 2.5 : 0.0);
+    double best_us = 1e300, d = 0.0, w = 0.0;
+    for (int r = 1; r <= (kw > 64 ? 16 : 1) && kw / r >= 8; ++r) {
+        const double unit = (double)std::max(kd, (kw + r - 1) / r);
+        const double us = std::max(0.92 * load, 0.62 * unit) + 0.15 * unit + runs_us(r);
         if (us < best_us) {
             best_us = us;
-            best = s;
+            best = r;
+            d = fd * (double)kd;
+            w = fw * (double)((kw + r - 1) / r);
         }
     }
-    return best;
+    if (best == 0)
+        return 0;
+    // its time, fitted to the same layers (nine in ten within 20 %): stages per slot at two tiles to a CU and
+    // the uneven end (none if all units are resident at once and about as long: 2048x2048 -> 2048 28.7 us
+    // apart, 25.1 paired), or the longest unit, which ends up alone on its CU; the runs
+    const double longer = std::max(d, w), shorter = std::min(d, w);
+    const bool even = (double)(td + tw * best) <= slots && shorter > 0.8 * longer;
+    const double us = std::max(0.69 * load + (even ? 0.0 : 0.11 * shorter), 0.23 * longer) + (even ? 0.0 : 0.06 * longer) + 4.0 +
+                      runs_us(best);
+    return us < 0.97 * (lone_gemm_us(M, K, N) + lone_gemm_us(N, K, M)) ? best : 0;
 }
 
 static size_t pair_bytes(int64_t N, int64_t K, int splits)
