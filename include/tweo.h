@@ -498,8 +498,8 @@ tweo_status tweo_fused_cast_timeouts(unsigned *count);
  * stages (any K % 16 == 0): 256x256 with 8 waves, 128x128, 64x64.  11, 13, 14 =
  * persistent streaming kernel with 128-byte stages (K % 128 == 0): 256x256,
  * 128x128, 192x256.  15 = the deferred-epilogue persistent kernel (256x256 tiles, M
- * and N multiples of 256, K a multiple of 128 and at least 512, no residual, p in
- * {0, 4}); it falls back to variant 11 otherwise.  16 = the same kernel on 192x256
+ * and N multiples of 256, K a multiple of 128 and at least 512, with a residual at
+ * least 2048, p in {0, 4}); it falls back to variant 11 otherwise.  16 = the same kernel on 192x256
  * tiles (any M, N a multiple of 256, K a multiple of 128 and at least 2048); it
  * falls back to variant 14 otherwise.  17 (INT8 only, M <= 128, K % 64 == 0,
  * N % 4 == 0; M <= 256 when K >= 8192 and N <= 16 x the CU count) = the

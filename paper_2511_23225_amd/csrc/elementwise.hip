@@ -877,7 +877,8 @@ __global__ __launch_bounds__((LnShape<AMAX, P>::THREADS), (LnShape<AMAX, P>::WAV
 // column's index in units of eight, which spreads the 8-byte writes of a wave over all banks.
 //
 // HBM-bound on large tensors, latency-bound on small ones, so what counts is how much is in flight:
-// 64 elements a lane need few registers (five to six waves per SIMD).  The form before, 256x256 tiles
+// 64 elements a lane need few registers (five to eight waves per SIMD; the injecting form four, the
+// LayerNorm form, which holds its fp64 parameters, three).  The form before, 256x256 tiles
 // with 16x16 elements a lane and no LDS, ran two to four waves per SIMD (one under LayerNorm with
 // delayed scaling) and had 96 workgroups for an 8192x768 tensor: 13.0 us, now 7.7; 16384x5632 and
 // 2048x5632 under delayed scaling 91.4 us, now 74.0 (5.6 TB/s).

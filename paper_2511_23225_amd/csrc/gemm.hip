@@ -721,7 +721,7 @@ __global__ __launch_bounds__(T::THREADS, T::WPE) void gemm_nt_dma_kernel(GemmDev
 
 // The two products of a linear layer's backward in one launch: workgroups [0, n0) are the grid of g0,
 // [n0_padded, ..) that of g1 (padded to a multiple of 8 so that a workgroup's number modulo 8 is its
-// XCD in both).  For layers whose products leave the chip half empty one at a time: see pair_plan.
+// XCD in both).  For layers whose products leave the chip half empty one at a time: see pair_splits.
 template <typename T, bool A_E5M2>
 __global__ __launch_bounds__(T::THREADS, T::WPE) void gemm_nt_dma_pair_kernel(GemmDev g0, GemmDev g1, int n0, int n0_padded)
 {
@@ -1968,8 +1968,9 @@ int fp8_gemm_ksplit(int64_t M, int64_t N, int64_t K)
 // alone on its CU runs at 0.29 us per 64-byte stage (two on a CU share that; 0.135 and 0.26 for the
 // 64x64 tiles of small outputs), the runs are written and read at 4 TB/s, the second launch costs 4 us;
 // taken where that promises a tenth.
+// (A lone FP8 tile is as fast, see lone_gemm_us.)
 // Quantise + linear, 11008 -> 4096 at M = 300 / 384 / 500: 44.2 / 53.6 / 53.9 -> 32.6 / 37.7 / 44.9 us;
-// 5632 -> 2048 at M = 300: 26.2 -> 18.6.
+// 5632 -> 2048 at M = 300 is not split: its 160 tiles of 64x64 are the faster way.
 static int i8_dma_ksplit(int64_t M, int64_t N, int64_t K)
 {
     if (g_tile_override != 0 || N % 8 != 0 || M <= 128)
