@@ -177,6 +177,10 @@ __device__ __forceinline__ void for_each_constant(std::integer_sequence<int, Is.
 // has a whole stage (1.2 us) to arrive in.  Kernel times with the penalty on, against the 8-wave
 // streaming kernel, which adds the residual behind the tile with nothing running under it:
 // 50432x3072 -> 768 175 -> 133 us, 16384x5632 -> 2048 174 -> 140 us (without a residual 120 and 133).
+// On 256x256 tiles it needs more registers than there are: 28-31 vector and 15-23 scalar registers are
+// spilled (88-100 bytes a lane; on 192x256 tiles, and without a residual, nothing goes to memory).  The
+// reloads at the tile boundary and in a tile's first stage each wait for the operand stream as well; the
+// counted waits stay right, since further memory operations only make them stricter.
 template <bool INT8, int PMODE, int D, int MT, bool A_E5M2 = false, bool LINES = true, bool KSPLIT = false,
           bool RES = false>
 __global__ __launch_bounds__(256, 1) void gemm_nt_defer_kernel(GemmDev g)
