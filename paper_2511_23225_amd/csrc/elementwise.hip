@@ -911,12 +911,12 @@ __device__ __forceinline__ void cast_tile_body(
         // whole 128- and 64-byte pieces, horizontal neighbours share lines: every XCD gets a run of
         // tiles of its own, or two L2s read and write the same lines (16384x4112: 84.8 us, 64.8).  In
         // whole lines the plain order is ahead (16384x4096: 53.5 against 61.1 in runs).
-        int64_t id = tile;
+        uint32_t id = (uint32_t)tile;  // a grid holds fewer than 2^31 workgroups
         if ((cols & 63) != 0) {
-            const int64_t per = all_tiles >> 3, rem = all_tiles & 7, xcd = tile & 7;
-            id = xcd * per + (xcd < rem ? xcd : rem) + (tile >> 3);
+            const uint32_t per = (uint32_t)(all_tiles >> 3), rem = (uint32_t)all_tiles & 7u, xcd = id & 7u;
+            id = xcd * per + (xcd < rem ? xcd : rem) + (id >> 3);
         }
-        const int64_t by = id / tiles_x, bx = id % tiles_x;
+        const int64_t by = id / (uint32_t)tiles_x, bx = id % (uint32_t)tiles_x;
         if (bx * kTile >= cols)
             continue;  // the walk is wider than the tensor
         const int64_t R = by * kTile, C = bx * kTile, r0 = R + rg * 8, c0 = C + cg * 8;
