@@ -56,6 +56,21 @@ __device__ __forceinline__ uint32_t round_to_i8(float v, float inv_step)
     return (uint32_t)(int)r & 0xFFu;
 }
 
+// Stores of a kernel's output that go through the XCD's L2 to memory at once (device scope, sc1) instead of
+// staying there dirty: what is dirty at a kernel's end is written back between it and the next one, with
+// nothing running (the next kernel reads it from memory either way).
+__device__ __forceinline__ void store_through(void *p, uint2 v)
+{
+    __hip_atomic_store((uint64_t *)p, __builtin_bit_cast(uint64_t, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void store_through(void *p, v4i v)
+{
+    // a store of more than 8 bytes reads its data late: nothing may write those registers in the next
+    // wait states (the compiler does not know this is a store)
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
+}
+__device__ __forceinline__ void store_through(void *p, uint4 v) { store_through(p, __builtin_bit_cast(v4i, v)); }
+
 template <typename T>
 __device__ __forceinline__ T wave_reduce_sum(T v)
 {

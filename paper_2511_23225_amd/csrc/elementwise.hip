@@ -883,12 +883,13 @@ __global__ __launch_bounds__((LnShape<AMAX, P>::THREADS), (LnShape<AMAX, P>::WAV
 // delayed scaling) and had 96 workgroups for an 8192x768 tensor: 13.0 us, now 7.7; 16384x5632 and
 // 2048x5632 under delayed scaling 91.4 us, now 74.0 (5.6 TB/s).
 constexpr int kTile = 128;
-
 // INJECT: 0 = plain cast; 4 / 1 = the penalty gradient is added on the way in (p = 4 / any p)
 // LN: the tensor that is cast is the LayerNorm of x (statistics precomputed per row).
 // T_LATER: the transposed codes are not read before a later call (a forward cast's, which wait for
 // the backward pass): streaming stores.
-template <bool WITH_T, bool DELAYED, bool E5M2 = false, int INJECT = 0, bool LN = false, bool T_LATER = false>
+// THROUGH: the codes are written through the L2s (see writes_through).
+template <bool WITH_T, bool DELAYED, bool E5M2 = false, int INJECT = 0, bool LN = false, bool T_LATER = false,
+          bool THROUGH = false>
 __device__ __forceinline__ void cast_tile_body(
     const uint16_t *__restrict__ x, int64_t rows, int64_t cols, int64_t tiles_x,
     const float *__restrict__ amax, uint8_t *__restrict__ q, uint8_t *__restrict__ qT,
@@ -992,8 +993,12 @@ __device__ __forceinline__ void cast_tile_body(
                                   bf16lo_to_f32(in[i].y) * scale, bf16hi_to_f32(in[i].y) * scale);
             hi[i] = cvt4_f8<E5M2>(bf16lo_to_f32(in[i].z) * scale, bf16hi_to_f32(in[i].z) * scale,
                                   bf16lo_to_f32(in[i].w) * scale, bf16hi_to_f32(in[i].w) * scale);
-            if (active)
-                *(uint2 *)(q + (r0 + i) * cols + c0) = make_uint2(lo[i], hi[i]);
+            if (active) {
+                if constexpr (THROUGH)
+                    store_through(q + (r0 + i) * cols + c0, make_uint2(lo[i], hi[i]));
+                else
+                    *(uint2 *)(q + (r0 + i) * cols + c0) = make_uint2(lo[i], hi[i]);
+            }
         }
         if constexpr (WITH_T) {
             uint32_t ta[8], tb[8];  // column j of the block: rows 0-3, rows 4-7
@@ -1011,12 +1016,13 @@ __device__ __forceinline__ void cast_tile_body(
             const int piece = t & 7;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                typedef uint32_t v4u __attribute__((ext_vector_type(4)));
                 const int col = (t >> 3) + 32 * i;
-                const v4u v = __builtin_bit_cast(v4u, turned[col * (kTile / 16) + (piece ^ ((col >> 3) & 7))]);
+                const v4i v = __builtin_bit_cast(v4i, turned[col * (kTile / 16) + (piece ^ ((col >> 3) & 7))]);
                 if (C + col < cols && R + piece * 16 < rows) {
-                    v4u *dst = (v4u *)(qT + (C + col) * rows + R + piece * 16);
-                    if constexpr (T_LATER)
+                    v4i *dst = (v4i *)(qT + (C + col) * rows + R + piece * 16);
+                    if constexpr (THROUGH)
+                        store_through(dst, v);
+                    else if constexpr (T_LATER)
                         __builtin_nontemporal_store(v, dst);
                     else
                         *dst = v;
@@ -1042,27 +1048,40 @@ static int64_t walk_width(int64_t rows, int64_t cols, bool transposed)
     return transposed && (rows & 63) != 0 && (cols & 63) == 0 && 4 * (wide - w) <= w ? wide : w;
 }
 
+// Where a cast with a transposed copy writes its codes through the L2s (store_through): whole lines in both
+// copies, and an output that the L2s (32 MB) would hold for the most part when the kernel ends.  Cold, us,
+// dirty / through: amax + cast 8192x768 11.6 / 10.4, 4096x2048 13.2 / 11.8, 4096x3072 15.8 / 14.8; LayerNorm +
+// cast 8192x1024 26.3 / 24.8, 4096x4096 35.9 / 34.1, 16384x2048 61.6 / 59.3.  On both sides of that it
+// loses: the last stores' way to memory is longer (1024x1024 7.8 / 8.3), and a stream of pieces of 128 bytes is
+// slower written through than evicted (8192x2304 12.3 / 13.4 for the cast alone; behind a LayerNorm, paced
+// by its arithmetic, from 4096 tiles on: 8192x8192 133 / 137).
+static bool writes_through(int64_t rows, int64_t cols, int64_t tiles, int64_t most)
+{
+    return ((rows | cols) & (kTile - 1)) == 0 && tiles >= 256 && tiles <= most;
+}
+constexpr int64_t kThroughTiles = 768, kThroughTilesLn = 2048;
+
 // LayerNorm + cast (DELAYED: the scale is read from *amax, the tensor's amax goes to *amax_acc)
-template <bool WITH_T, bool DELAYED>
+template <bool WITH_T, bool DELAYED, bool THROUGH = false>
 __global__ __launch_bounds__(kQuantThreads) void cast_ln_tile_kernel(
     const uint16_t *__restrict__ x, LnArgs ln, int64_t rows, int64_t cols, int64_t tiles_x,
     const float *__restrict__ amax, uint8_t *__restrict__ q, uint8_t *__restrict__ qT, uint16_t *__restrict__ y_out,
     float *scale_out, float *scale_inv_out, uint32_t *amax_acc, const uint32_t *__restrict__ amax_partials,
     int n_partials, float *amax_store)
 {
-    cast_tile_body<WITH_T, DELAYED, false, 0, true>(
+    cast_tile_body<WITH_T, DELAYED, false, 0, true, false, THROUGH>(
         x, rows, cols, tiles_x, amax, q, qT, scale_out, scale_inv_out, amax_acc, blockIdx.x, gridDim.x, amax_partials,
         n_partials, amax_store, InjectArgs{}, ln, y_out);
 }
 
-template <bool WITH_T, bool DELAYED, bool E5M2 = false>
+template <bool WITH_T, bool DELAYED, bool E5M2 = false, bool THROUGH = false>
 __global__ __launch_bounds__(kQuantThreads) void cast_tile_kernel(
     const uint16_t *__restrict__ x, int64_t rows, int64_t cols, int64_t tiles_x,
     const float *__restrict__ amax, uint8_t *__restrict__ q, uint8_t *__restrict__ qT,
     float *scale_out, float *scale_inv_out, uint32_t *amax_acc, const uint32_t *__restrict__ amax_partials,
     int n_partials, float *amax_store)
 {
-    cast_tile_body<WITH_T, DELAYED, E5M2>(x, rows, cols, tiles_x, amax, q, qT, scale_out, scale_inv_out,
+    cast_tile_body<WITH_T, DELAYED, E5M2, 0, false, false, THROUGH>(x, rows, cols, tiles_x, amax, q, qT, scale_out, scale_inv_out,
                                               amax_acc, blockIdx.x, gridDim.x, amax_partials, n_partials,
                                               amax_store);
 }
@@ -1091,12 +1110,13 @@ struct QuantTensor {
     float *amax_store;
 };
 
+template <bool THROUGH>
 __global__ __launch_bounds__(kQuantThreads) void cast2_tile_kernel(QuantTensor t0, int64_t blocks0,
                                                                              QuantTensor t1)
 {
     const bool first = (int64_t)blockIdx.x < blocks0;
     const QuantTensor &t = first ? t0 : t1;
-    cast_tile_body<true, false, false, 0, false, true>(t.x, t.rows, t.cols, t.tiles_x, t.amax, t.q, t.qT, t.scale_out,
+    cast_tile_body<true, false, false, 0, false, true, THROUGH>(t.x, t.rows, t.cols, t.tiles_x, t.amax, t.q, t.qT, t.scale_out,
                                           t.scale_inv_out, nullptr,
                                           first ? (int64_t)blockIdx.x : (int64_t)blockIdx.x - blocks0, 1,
                                           t.amax_partials, t.n_partials, t.amax_store);
@@ -1114,7 +1134,10 @@ hipError_t launch_quantize2_e4m3(const void *x0_bf16, int64_t rows0, int64_t col
     QuantTensor t1{(const uint16_t *)x1_bf16, rows1, cols1, walk_width(rows1, cols1, true), amax1, q1, q1T, scale1, scale1_inv,
                    partials1, n_partials1, amax1};
     const int64_t b0 = tiles(rows0) * t0.tiles_x, b1 = tiles(rows1) * t1.tiles_x;
-    hipLaunchKernelGGL(cast2_tile_kernel, dim3((unsigned)(b0 + b1)), dim3(kQuantThreads), 0, s, t0, b0, t1);
+    if (writes_through(rows0 | rows1, cols0 | cols1, b0 + b1, kThroughTiles))
+        hipLaunchKernelGGL(cast2_tile_kernel<true>, dim3((unsigned)(b0 + b1)), dim3(kQuantThreads), 0, s, t0, b0, t1);
+    else
+        hipLaunchKernelGGL(cast2_tile_kernel<false>, dim3((unsigned)(b0 + b1)), dim3(kQuantThreads), 0, s, t0, b0, t1);
     return hipGetLastError();
 }
 
@@ -1150,14 +1173,16 @@ static hipError_t launch_quantize_e4m3_impl(const void *x_bf16, int64_t rows, in
         if (DELAYED)
             n_wg = delayed_workgroups(n_wg, qT != nullptr);
         const dim3 grid((unsigned)n_wg);
-        if (qT)
-            hipLaunchKernelGGL((cast_tile_kernel<true, DELAYED, E5M2>), grid, block, 0, s,
-                               (const uint16_t *)x_bf16, rows, cols, tiles_x, amax, q, qT, scale_out,
-                               scale_inv_out, amax_acc, amax_partials, n_partials, amax_store);
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, grid, block, 0, s, (const uint16_t *)x_bf16, rows, cols, tiles_x, amax, q, qT,
+                               scale_out, scale_inv_out, amax_acc, amax_partials, n_partials, amax_store);
+        };
+        if (!qT)
+            launch(cast_tile_kernel<false, DELAYED, E5M2>);
+        else if (!DELAYED && writes_through(rows, cols, n_wg, kThroughTiles))
+            launch(cast_tile_kernel<true, DELAYED, E5M2, !DELAYED>);
         else
-            hipLaunchKernelGGL((cast_tile_kernel<false, DELAYED, E5M2>), grid, block, 0, s,
-                               (const uint16_t *)x_bf16, rows, cols, tiles_x, amax, q, qT, scale_out,
-                               scale_inv_out, amax_acc, amax_partials, n_partials, amax_store);
+            launch(cast_tile_kernel<true, DELAYED, E5M2>);
         return hipGetLastError();
     }
     const int64_t tiles_x = (cols + kQuantTileCols - 1) / kQuantTileCols;
@@ -1915,15 +1940,17 @@ hipError_t launch_layernorm_quantize(const void *x_bf16, const void *res_bf16, c
     const int64_t n_tiles = tiles_x * tiles_y;
     const dim3 block(kQuantThreads);
     float *st = (float *)state;
+    const bool through = qT != nullptr && writes_through(rows, cols, n_tiles, kThroughTilesLn);
     if (!delayed) {
-        if (qT)
-            hipLaunchKernelGGL((cast_ln_tile_kernel<true, false>), dim3((unsigned)n_tiles), block, 0, s, src, ln,
-                               rows, cols, tiles_x, (const float *)amax_out, q, qT, (uint16_t *)y_out, scale_out, scale_inv_out,
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)n_tiles), block, 0, s, src, ln, rows, cols, tiles_x,
+                               (const float *)amax_out, q, qT, (uint16_t *)y_out, scale_out, scale_inv_out,
                                (uint32_t *)nullptr, (const uint32_t *)partials, (int)sgrid, amax_out);
+        };
+        if (!qT)
+            launch(cast_ln_tile_kernel<false, false>);
         else
-            hipLaunchKernelGGL((cast_ln_tile_kernel<false, false>), dim3((unsigned)n_tiles), block, 0, s, src, ln,
-                               rows, cols, tiles_x, (const float *)amax_out, q, qT, (uint16_t *)y_out, scale_out, scale_inv_out,
-                               (uint32_t *)nullptr, (const uint32_t *)partials, (int)sgrid, amax_out);
+            through ? launch(cast_ln_tile_kernel<true, false, true>) : launch(cast_ln_tile_kernel<true, false>);
         return hipGetLastError();
     }
     if (bootstrap) {  // empty history: the tensor's own amax makes the scale
@@ -1939,14 +1966,15 @@ hipError_t launch_layernorm_quantize(const void *x_bf16, const void *res_bf16, c
     // 61.2 and 63.8)
     const int64_t cus = amax_cus(), cap = (n_tiles < 8 * cus ? 4 : 6) * cus;
     const int64_t n_wg = n_tiles < cap ? n_tiles : cap;
-    if (qT)
-        hipLaunchKernelGGL((cast_ln_tile_kernel<true, true>), dim3((unsigned)n_wg), block, 0, s, src, ln, rows, cols,
-                           tiles_x, scale_src, q, qT, (uint16_t *)y_out, (float *)nullptr, (float *)nullptr, acc,
-                           (const uint32_t *)nullptr, 0, (float *)nullptr);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)n_wg), block, 0, s, src, ln, rows, cols, tiles_x, scale_src, q, qT,
+                           (uint16_t *)y_out, (float *)nullptr, (float *)nullptr, acc, (const uint32_t *)nullptr, 0,
+                           (float *)nullptr);
+    };
+    if (!qT)
+        launch(cast_ln_tile_kernel<false, true>);
     else
-        hipLaunchKernelGGL((cast_ln_tile_kernel<false, true>), dim3((unsigned)n_wg), block, 0, s, src, ln, rows, cols,
-                           tiles_x, scale_src, q, qT, (uint16_t *)y_out, (float *)nullptr, (float *)nullptr, acc,
-                           (const uint32_t *)nullptr, 0, (float *)nullptr);
+        through ? launch(cast_ln_tile_kernel<true, true, true>) : launch(cast_ln_tile_kernel<true, true>);
     if ((e = hipGetLastError()) != hipSuccess)
         return e;
     if (!bootstrap)

@@ -276,3 +276,10 @@ def test_casts_over_the_walks_of_tiles(shape):
     tw.tweo_fp8_linear_bwd_bf16_inject(xd, g, (3.0, 1e-6, 4), 0.125, saved, 16, q, qT, dx, None, ws)
     torch.cuda.synchronize()
     assert same(q, want) and same(qT, wantT)
+
+
+# casts that write their codes through the L2s: the tile counts at which that begins and ends (256 to 768 tiles,
+# to 2048 behind a LayerNorm), whole lines in both copies or not
+@pytest.mark.parametrize("shape", [(2048, 2048), (4080, 1024), (2048, 1920), (4096, 3072), (4096, 3200), (8192, 4096)])
+def test_casts_that_write_through_the_caches(shape):
+    test_casts_over_the_walks_of_tiles(shape)
