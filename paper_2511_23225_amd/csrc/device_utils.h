@@ -70,6 +70,7 @@ __device__ __forceinline__ void store_through(void *p, v4i v)
     asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
 }
 __device__ __forceinline__ void store_through(void *p, uint4 v) { store_through(p, __builtin_bit_cast(v4i, v)); }
+__device__ __forceinline__ void store_through(void *p, float4 v) { store_through(p, __builtin_bit_cast(v4i, v)); }
 
 template <typename T>
 __device__ __forceinline__ T wave_reduce_sum(T v)

@@ -34,6 +34,7 @@ struct GemmDev {
     // stores the fp32 (INT8: int32) sums to ksplit_out; a second kernel adds the runs in order and rounds
     int ksplit;
     float *ksplit_out;
+    int through;  // the output is written through the L2s (store_through)
 };
 
 // raster of tile ids: groups of 8 tile rows, column-major inside a group

@@ -756,6 +756,8 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_defer_kernel(GemmDev g)
         // read written as asm against them): a few hundred cycles
         asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7\n\ts_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
         wait_vmcnt<0>();
+        // written through the L2s: the reduce kernel starts when they are clean (3072x768 over 8192 tokens,
+        // 38 MB of runs, both launches 33.4 us with the runs left dirty, 31.8 now)
         float4 *dst = (float4 *)g.ksplit_out + ((int64_t)slot * T::NWAVES + wave) * (T::NB * 4 * kWave) + lane;
 #pragma unroll
         for (int b = 0; b < T::NB; ++b)
@@ -771,8 +773,8 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_defer_kernel(GemmDev g)
                                "a"(acc[b >> 2][b & 3][8 * hq + 2]), "a"(acc[b >> 2][b & 3][8 * hq + 3]),
                                "a"(acc[b >> 2][b & 3][8 * hq + 4]), "a"(acc[b >> 2][b & 3][8 * hq + 5]),
                                "a"(acc[b >> 2][b & 3][8 * hq + 6]), "a"(acc[b >> 2][b & 3][8 * hq + 7]));
-                dst[(b * 4 + 2 * hq) * kWave] = make_float4(t[0], t[1], t[2], t[3]);
-                dst[(b * 4 + 2 * hq + 1) * kWave] = make_float4(t[4], t[5], t[6], t[7]);
+                store_through(dst + (b * 4 + 2 * hq) * kWave, make_float4(t[0], t[1], t[2], t[3]));
+                store_through(dst + (b * 4 + 2 * hq + 1) * kWave, make_float4(t[4], t[5], t[6], t[7]));
             }
         return;
     }

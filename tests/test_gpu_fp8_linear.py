@@ -612,3 +612,25 @@ def test_ragged_contraction_under_many_tiles(K):
 @pytest.mark.parametrize("shape", [(592, 656, 520), (6224, 720, 512), (16400, 272, 264), (1040, 2000, 1544)])
 def test_bwd_ragged_contractions(shape, hybrid):
     check_bwd_pair(shape, hybrid)
+
+
+# outputs that the tiled kernels write through the L2s (2^21 to 2^23 elements, columns in whole lines), and
+# just outside of that; whole tiles and a ragged last row of them; with and without the penalty
+@pytest.mark.parametrize("tile", [4, 6, 8, 13])
+@pytest.mark.parametrize("shape", [(2048, 1024), (2047, 1024), (2064, 1088), (2056, 1096)])
+def test_fwd_written_through_the_caches(shape, tile):
+    (M, N), K = shape, 128
+    say("fwd written through M=%d N=%d tile=%d" % (M, N, tile))
+    x, w, _ = synth.fp8_linear_inputs(3, 0, M=M, K=K, N=N)
+    xq, _, sxi = oracle_quantized(x)
+    wq, _, swi = oracle_quantized(w)
+    ref, refabs, refbf = oracle.fp8_linear_fwd(xq, wq, sxi, swi)
+    tw.tweo_set_gemm_tile(tile)
+    try:
+        for pen in (None, PEN):
+            got, S = run_fwd(xq, wq, sxi, swi, M, N, K, pen=pen)
+            check_gemm(got, ref, refabs, K, "fwd")
+            if pen:
+                check_penalty(S, got, refbf, oracle.penalty_sum(refbf, *pen), pen, strict=False)
+    finally:
+        tw.tweo_set_gemm_tile(0)
