@@ -1732,59 +1732,64 @@ __global__ void delayed_state_init_kernel(uint32_t *st)
 }
 
 // Consumes the accumulated amax: remembers the scale that was just used, pushes the amax into
-// the ring, derives the next scale, clears the accumulator.  One thread.  sc_out (optional): three
-// fp32 of the caller's: this tensor's amax, the scale its cast uses / used, and its inverse.
-__device__ __forceinline__ void delayed_state_update(uint32_t *st, int bootstrap, float range, float *sc_out)
+// the ring, derives the next scale, clears the accumulator.  sc_out (optional): three fp32 of the
+// caller's: this tensor's amax, the scale its cast uses / used, and its inverse.  given (optional): the
+// tensor's amax, instead of the accumulated one.
+// One wave, lane i holds word i: one load and one store of the state.  (A single thread's chain of loads and
+// stores took 2.5 us more: this launch is all latency.)
+__device__ __forceinline__ void delayed_state_update(uint32_t *st, int bootstrap, float range, float *sc_out,
+                                                     const uint32_t *given = nullptr)
 {
-    int pos = (int)st[19], filled = (int)st[20];
-    if (!bootstrap) {  // a bootstrap cast has not happened yet: nothing was "used"
-        st[21] = st[17];
-        st[22] = st[18];
-    }
-    const uint32_t mine = st[16];
-    st[pos & 15] = mine;
-    pos = (pos + 1) & 15;
-    filled = filled < 16 ? filled + 1 : 16;
-    uint32_t m = 0;
-    for (int k = 0; k < 16; ++k)
-        m = st[k] > m ? st[k] : m;  // magnitude patterns order like unsigned integers (NaN on top)
+    const int lane = threadIdx.x & (kWave - 1);
+    const uint32_t v = lane < 32 ? st[lane] : 0u;
+    auto word = [&](int i) { return (uint32_t)__builtin_amdgcn_readlane((int)v, i); };
+    const uint32_t mine = given != nullptr ? *given : word(16);
+    const int pos = (int)word(19), filled = (int)word(20);
+    const uint32_t h = lane == (pos & 15) ? mine : v;  // the ring with this amax in it
+    // magnitude patterns order like unsigned integers (NaN on top)
+    const uint32_t m = wave_reduce_max_u32(lane < 16 ? h : 0u);
     const float scale = scale_from_amax_range(bits_to_f32(m), range);  // 448 (E4M3) or 57344 (E5M2)
-    st[17] = f32_to_bits(scale);
-    st[18] = f32_to_bits(1.0f / scale);
-    st[19] = (uint32_t)pos;
-    st[20] = (uint32_t)filled;
-    st[16] = 0u;
-    if (bootstrap) {  // the cast that follows uses this scale
-        st[21] = st[17];
-        st[22] = st[18];
-    }
-    if (sc_out != nullptr) {
-        sc_out[0] = bits_to_f32(mine);
-        sc_out[1] = bits_to_f32(st[21]);
-        sc_out[2] = bits_to_f32(st[22]);
-    }
+    const uint32_t next = f32_to_bits(scale), next_inv = f32_to_bits(1.0f / scale);
+    // a bootstrap cast has not happened yet: it uses the new scale
+    const uint32_t used = bootstrap ? next : word(17), used_inv = bootstrap ? next_inv : word(18);
+    uint32_t w = h;
+    w = lane == 16 ? 0u : w;
+    w = lane == 17 ? next : w;
+    w = lane == 18 ? next_inv : w;
+    w = lane == 19 ? (uint32_t)((pos + 1) & 15) : w;
+    w = lane == 20 ? (uint32_t)(filled < 16 ? filled + 1 : 16) : w;
+    w = lane == 21 ? used : w;
+    w = lane == 22 ? used_inv : w;
+    if (lane < 23)
+        st[lane] = w;
+    if (sc_out != nullptr && lane < 3)
+        sc_out[lane] = bits_to_f32(lane == 0 ? mine : lane == 1 ? used : used_inv);
 }
 
-__global__ void delayed_state_update_kernel(uint32_t *st, int bootstrap, float range,
-                                            const uint32_t *partials = nullptr, int n_partials = 0,
-                                            float *sc_out = nullptr)
+__global__ __launch_bounds__(kWave) void delayed_state_update_kernel(uint32_t *st, int bootstrap, float range,
+                                                                     const uint32_t *partials = nullptr,
+                                                                     int n_partials = 0, float *sc_out = nullptr)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0)
-        return;
+    uint32_t m = 0;
     if (partials != nullptr) {  // the tensor's amax arrives as one maximum per workgroup of an earlier launch
-        uint32_t m = 0;
-        for (int i = 0; i < n_partials; ++i)
+        for (int i = threadIdx.x; i < n_partials; i += kWave)
             m = partials[i] > m ? partials[i] : m;
-        st[16] = m;
+        m = wave_reduce_max_u32(m);
     }
-    delayed_state_update(st, bootstrap, range, sc_out);
+    delayed_state_update(st, bootstrap, range, sc_out, partials != nullptr ? &m : nullptr);
 }
 
-// two states in one launch (the activation's and the weight's of a linear layer): block b, thread 0
-__global__ void delayed_state_update2_kernel(uint32_t *st0, float *sc0, uint32_t *st1, float *sc1, float range)
+// two states in one launch (the activation's and the weight's of a linear layer): one block each
+__global__ __launch_bounds__(kWave) void delayed_state_update2_kernel(DelayedUpdate2 u)
 {
-    if (threadIdx.x == 0)
-        delayed_state_update(blockIdx.x == 0 ? st0 : st1, 0, range, blockIdx.x == 0 ? sc0 : sc1);
+    const bool first = blockIdx.x == 0;
+    delayed_state_update(first ? u.st0 : u.st1, 0, 448.0f, first ? u.sc0 : u.sc1);
+}
+
+hipError_t launch_delayed_update2(const DelayedUpdate2 &u, hipStream_t s)
+{
+    hipLaunchKernelGGL(delayed_state_update2_kernel, dim3(2), dim3(kWave), 0, s, u);
+    return hipGetLastError();
 }
 
 hipError_t launch_delayed_state_init(void *state, hipStream_t s)
@@ -1836,8 +1841,8 @@ hipError_t launch_quantize_e5m2_delayed(const void *x_bf16, int64_t rows, int64_
     return launch_quantize_f8_delayed<true>(x_bf16, rows, cols, state, bootstrap, q, qT, s, sc_out);
 }
 
-// The activation and the weight of a linear layer under delayed scaling in one cast launch and one
-// state-update launch (each tensor with its transposed copy; rows, cols multiples of 16).
+// The activation and the weight of a linear layer under delayed scaling in one cast launch (each tensor
+// with its transposed copy; rows, cols multiples of 16).
 struct QuantTensorDelayed {
     const uint16_t *x;
     int64_t rows, cols, tiles_x;
@@ -1861,6 +1866,7 @@ hipError_t launch_quantize2_e4m3_delayed(const void *x0_bf16, int64_t rows0, int
                                          void *state1, uint8_t *q1, uint8_t *q1T, float *sc1, int bootstrap,
                                          hipStream_t s)
 {
+    // (not bootstrap: the caller launches the states' update)
     if (bootstrap) {  // empty histories: each tensor's own amax first (once per state)
         hipError_t e = launch_quantize_f8_delayed<false>(x0_bf16, rows0, cols0, state0, 1, q0, q0T, s, sc0);
         if (e != hipSuccess)
@@ -1879,11 +1885,6 @@ hipError_t launch_quantize2_e4m3_delayed(const void *x0_bf16, int64_t rows0, int
     int64_t b0 = n_wg - b1;
     b0 = b0 < 1 ? 1 : (b0 > n0 ? n0 : b0);
     hipLaunchKernelGGL(cast2_delayed_tile_kernel, dim3((unsigned)(b0 + b1)), dim3(kQuantThreads), 0, s, t0, b0, t1, b1);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess)
-        return e;
-    hipLaunchKernelGGL(delayed_state_update2_kernel, dim3(2), dim3(64), 0, s, (uint32_t *)state0, sc0, (uint32_t *)state1,
-                       sc1, 448.0f);
     return hipGetLastError();
 }
 
@@ -2157,8 +2158,7 @@ hipError_t launch_penalty_grad_inject(const void *dy_bf16, const void *a_bf16, i
 // Penalty finish: sums the per-workgroup fp32 partials in a fixed order in fp64.
 constexpr int kFinishThreads = 256;
 
-__global__ __launch_bounds__(kFinishThreads) void penalty_finish_kernel(
-    const float *__restrict__ partials, int n, double *out)
+__device__ __forceinline__ void penalty_finish(const float *__restrict__ partials, int n, double *out)
 {
     __shared__ double red[kFinishThreads];
     double s = 0.0;
@@ -2175,9 +2175,28 @@ __global__ __launch_bounds__(kFinishThreads) void penalty_finish_kernel(
         *out = red[0];
 }
 
-hipError_t launch_penalty_finish(const float *partials, int n, double *out, hipStream_t s)
+__global__ __launch_bounds__(kFinishThreads) void penalty_finish_kernel(const float *__restrict__ partials, int n,
+                                                                        double *out)
 {
-    hipLaunchKernelGGL(penalty_finish_kernel, dim3(1), dim3(kFinishThreads), 0, s, partials, n, out);
+    penalty_finish(partials, n, out);
+}
+
+// ... and the update of two delayed-scaling states in the same launch
+__global__ __launch_bounds__(kFinishThreads) void penalty_finish_update2_kernel(const float *__restrict__ partials, int n,
+                                                                                double *out, DelayedUpdate2 u)
+{
+    if (blockIdx.x == 0)
+        penalty_finish(partials, n, out);
+    else if (threadIdx.x < kWave)
+        delayed_state_update(blockIdx.x == 1 ? u.st0 : u.st1, 0, 448.0f, blockIdx.x == 1 ? u.sc0 : u.sc1);
+}
+
+hipError_t launch_penalty_finish(const float *partials, int n, double *out, hipStream_t s, const DelayedUpdate2 *update)
+{
+    if (update != nullptr)
+        hipLaunchKernelGGL(penalty_finish_update2_kernel, dim3(3), dim3(kFinishThreads), 0, s, partials, n, out, *update);
+    else
+        hipLaunchKernelGGL(penalty_finish_kernel, dim3(1), dim3(kFinishThreads), 0, s, partials, n, out);
     return hipGetLastError();
 }
 

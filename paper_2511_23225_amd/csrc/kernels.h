@@ -62,8 +62,16 @@ hipError_t launch_quantize_e4m3_delayed(const void *x_bf16, int64_t rows, int64_
 hipError_t launch_quantize_e5m2_delayed(const void *x_bf16, int64_t rows, int64_t cols, void *state,
                                         int bootstrap, uint8_t *q, uint8_t *qT, hipStream_t s,
                                         float *sc_out = nullptr);
-// two tensors (rows, cols multiples of 16; transposed copies required) on their two states: one
-// cast launch and one state-update launch
+// two tensors (rows, cols multiples of 16; transposed copies required) on their two states in one cast
+// launch; the scales used are words 17 and 18 (inverse) of the states until the caller launches their
+// update (already done in the bootstrap form, which leaves them in sc0, sc1)
+struct DelayedUpdate2 {
+    uint32_t *st0;
+    float *sc0;
+    uint32_t *st1;
+    float *sc1;
+};
+hipError_t launch_delayed_update2(const DelayedUpdate2 &u, hipStream_t s);
 hipError_t launch_quantize2_e4m3_delayed(const void *x0_bf16, int64_t rows0, int64_t cols0, void *state0, uint8_t *q0,
                                          uint8_t *q0T, float *sc0, const void *x1_bf16, int64_t rows1, int64_t cols1,
                                          void *state1, uint8_t *q1, uint8_t *q1T, float *sc1, int bootstrap,
@@ -81,7 +89,9 @@ hipError_t launch_quantize_i8(const void *x_bf16, int64_t n, float inv_step, int
 // Row-granular AbsMax INT8: q [rows, cols] and one dequantisation step per row (cols % 8 == 0).
 hipError_t launch_quantize_i8_rows(const void *x_bf16, int64_t rows, int64_t cols, float eps, int8_t *q,
                                    float *step, hipStream_t s);
-hipError_t launch_penalty_finish(const float *partials, int n, double *out, hipStream_t s);
+// update (optional): the update of two states in the same launch
+hipError_t launch_penalty_finish(const float *partials, int n, double *out, hipStream_t s,
+                                 const DelayedUpdate2 *update = nullptr);
 hipError_t launch_penalty_grad_inject(const void *dy_bf16, const void *a_bf16, int64_t n, float inv_tau,
                                       float coef, int p, void *out_bf16, hipStream_t s);
 // the injection fused into the gradient's amax and cast launches (rows, cols multiples of 16;

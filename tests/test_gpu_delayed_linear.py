@@ -115,3 +115,45 @@ def test_delayed_cast_over_the_tile_counts(tiles, with_t):
             torch.cuda.synchronize()
             assert int(state.view(torch.int32)[0]) == int(amax(before)) and int(state.view(torch.int32)[1]) == int(amax(cast))
             assert torch.equal(q, want) and (not with_t or torch.equal(qT, wantT))
+
+
+# the states' update behind the forward GEMM: in the launch that finishes the penalty, in one of its own without
+# a penalty, and where the product is refused (no workspace for the penalty) after the cast has run: the words of
+# both states and the saved scalars, against casts of each tensor by itself
+@pytest.mark.parametrize("how", ["penalty", "plain", "refused"])
+def test_states_are_updated_behind_the_gemm(how):
+    M, K, N = 272, 256, 144
+    print("delayed forward, update: %s" % how, flush=True)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(7)
+    u8 = lambda *s: torch.zeros(s, dtype=torch.uint8, device=DEV)
+    states = [torch.zeros(tw.DELAYED_STATE_WORDS, dtype=torch.float32, device=DEV) for _ in range(4)]
+    for st in states:
+        tw.tweo_delayed_state_init(st)
+    sc = torch.zeros(16, dtype=torch.float32, device=DEV)
+    xq, xqT, wq, wqT, q, qT = u8(M, K), u8(K, M), u8(N, K), u8(K, N), u8(M, K), u8(K, M)
+    saved = tw.make_saved(xq, xqT, wq, wqT, sc)
+    y = torch.empty((M, N), dtype=torch.bfloat16, device=DEV)
+    S = torch.zeros(1, dtype=torch.float64, device=DEV)
+    ws = torch.empty(tw.tweo_workspace_bytes(tw.TWEO_OP_FP8_LINEAR_FWD_BF16, M, N, K), dtype=torch.uint8, device=DEV)
+    for step in range(19):  # past the length of the history
+        x = (torch.randn((M, K), generator=g, device=DEV) * (1 + step % 5)).bfloat16()
+        w = (torch.randn((N, K), generator=g, device=DEV) * 0.02).bfloat16()
+        args = dict(bootstrap=step == 0, workspace=ws)
+        if how == "penalty":
+            args.update(pen=PEN, penalty_sum=S)
+        if how == "refused" and step > 0:
+            with pytest.raises(tw.TweoError) as e:
+                tw.tweo_fp8_linear_fwd_bf16_delayed(x, w, y, saved, states[0], states[1], pen=PEN, penalty_sum=S)
+            assert e.value.status == tw.TWEO_ERR_WORKSPACE
+        else:
+            tw.tweo_fp8_linear_fwd_bf16_delayed(x, w, y, saved, states[0], states[1], **args)
+        tw.tweo_quantize_e4m3_delayed(x, states[2], q, qT, bootstrap=step == 0)
+        tw.tweo_quantize_e4m3_delayed(w, states[3], wq[:], None, bootstrap=step == 0)
+        torch.cuda.synchronize()
+        assert torch.equal(xq, q) and torch.equal(xqT, qT)
+        for k in (0, 1):
+            assert torch.equal(states[k].view(torch.int32), states[k + 2].view(torch.int32)), (step, k)
+            newest = int(states[k].view(torch.int32)[19]) - 1 & 15
+            want = torch.stack([states[k][newest], states[k][tw.DELAYED_USED_SCALE], states[k][tw.DELAYED_USED_SCALE_INV]])
+            assert torch.equal(sc[3 * k:3 * k + 3].view(torch.int32), want.view(torch.int32)), (step, k)
