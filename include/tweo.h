@@ -76,9 +76,8 @@ enum {
  * tokens; an INT8 linear of a few hundred rows): several workgroups share a tile,
  * each multiplies a run of K and stores fp32 (INT8: int32) sums here (runs x rows x
  * cols x 4 bytes), a second launch adds the runs in index order - run-to-run
- * identical results.  A backward call whose layer is narrow runs both of its
- * products in one launch with the weight gradient's runs here; with less, or with
- * none, the products run one after the other on the plain schedule. */
+ * identical results.  With less, or with none, such a product runs on the plain
+ * schedule. */
 size_t tweo_workspace_bytes(int op, int64_t M, int64_t N, int64_t K);
 
 const char *tweo_status_string(tweo_status s);
@@ -494,17 +493,17 @@ tweo_status tweo_fused_cast_timeouts(unsigned *count);
 /*
  * Tuning hook for benchmarks and tests: forces the GEMM kernel variant.
  * 0 = choose from the shape (the default).  1, 3 = register-staged kernel, tiles
- * 256x256, 128x128 (any K % 16 == 0).  6, 8, 4 = DMA-pipelined kernel with 64-byte
- * stages (any K % 16 == 0): 256x256 with 8 waves, 128x128, 64x64.  11, 13, 14 =
+ * 256x256, 128x128 (any K % 16 == 0).  6, 8 = DMA-pipelined kernel with 64-byte
+ * stages (any K % 16 == 0): 256x256 with 8 waves, 128x128.  4, 18 to 22 = the ring
+ * kernel (any K % 16 == 0): 64x64, 64x64 and 64x128 with K split between two groups of
+ * waves (18, 20), 64x128 (19), 128x128 (21), 96x128 (22).  11, 13, 14 =
  * persistent streaming kernel with 128-byte stages (K % 128 == 0): 256x256,
  * 128x128, 192x256.  15 = the deferred-epilogue persistent kernel (256x256 tiles, M
  * and N multiples of 256, K a multiple of 128 and at least 512, with a residual at
  * least 2048, p in {0, 4}); it falls back to variant 11 otherwise.  16 = the same kernel on 192x256
  * tiles (any M, N a multiple of 256, K a multiple of 128 and at least 2048); it
- * falls back to variant 14 otherwise.  17 (INT8 only, M <= 128, K % 64 == 0,
- * N % 4 == 0; M <= 256 when K >= 8192 and N <= 16 x the CU count) = the
- * weight-streaming kernel (what such shapes get anyway);
- * elsewhere it means variant 4.  A variant whose K requirement is not met falls
+ * falls back to variant 14 otherwise.  17 (INT8 only, M <= 64, K % 64 == 0,
+ * N % 4 == 0) = the weight-streaming kernel; elsewhere it means variant 4.  A variant whose K requirement is not met falls
  * back to the nearest one that fits.  Results are identical up to the fp32
  * summation order.  Returns TWEO_ERR_INVALID_ARG for an unknown (or retired:
  * 2, 5, 7, 9, 10, 12) variant.

@@ -20,6 +20,7 @@
 #include <cmath>
 #include "gemm_common.h"
 #include "gemm_defer.h"
+#include "gemm_epilogue.h"
 
 namespace tweo {
 
@@ -59,279 +60,6 @@ __device__ __forceinline__ void tile_of_workgroup(int wg, int tiles_m, int tiles
     const int in_group = id - group * width;
     tm = first_m + in_group % gsz;
     tn = in_group / gsz;
-}
-
-// Epilogue shared by the GEMM kernels.  An MFMA 32x32 block leaves C[m, n] in
-// acc[4q + r] with m = lane%32 and n = 8q + 4*(lane/32) + r, i.e. a lane holds
-// four consecutive n of one row.  To write whole 128-byte lines, each wave
-// passes one 32-row band of its sub-tile at a time through its own slice of LDS
-// (fp32, row stride TN*4+16 bytes: conflict-free for the 16-byte writes and
-// reads) and reads it back with TN/8 lanes per row, 8 consecutive n per lane.
-// That lane then applies the scale, adds the residual (16-byte load), rounds to
-// bf16, stores 16 bytes, and accumulates the penalty term (|a| / (tau+eps))^p of
-// the value as stored (Sec. 3.3); the terms are reduced lane -> wave ->
-// workgroup into one fp32 partial per workgroup.  The caller must have placed a
-// workgroup barrier between the last LDS read of the main loop and this call.
-template <typename T>
-struct EpiLayout {
-    static constexpr int ROW_BYTES = T::TN * 4 + 16;
-    static constexpr int WAVE_BYTES = 32 * ROW_BYTES;
-    static constexpr int LPR = T::TN / 8;       // lanes per row when reading back
-    static constexpr int ROWS_PER_PASS = kWave / LPR;
-    static constexpr int PASSES = 32 / ROWS_PER_PASS;
-    // bf16 staging (no residual): half the bytes, so two bands fit and band i+1 can be written
-    // while band i is still being read back
-    static constexpr int ROW2_BYTES = T::TN * 2 + 16;
-    static constexpr int BAND2_BYTES = 32 * ROW2_BYTES;
-    static_assert(2 * BAND2_BYTES <= WAVE_BYTES + 1024, "bf16 double buffer fits the slice (with slack)");
-    static constexpr int SLICE_BYTES = WAVE_BYTES > 2 * BAND2_BYTES ? WAVE_BYTES : 2 * BAND2_BYTES;
-    static_assert(SLICE_BYTES * (T::THREADS / kWave) <= T::LDS_BYTES, "epilogue staging fits in LDS");
-};
-
-// Specialisations: PMODE 4 (p == 4, the paper's setting), 0 (no penalty) or -1 (p read at run
-// time); RES 1 / 0 (residual present / absent) or -1 (tested at run time); INTERIOR true when the
-// whole tile lies inside the matrix, so that no store needs a predicate.  The interior
-// specialisations are straight-line code per band: a predicate or a run-time test per pass
-// would cut the code into one basic block per pass and chain sixteen LDS round trips.
-template <typename T, bool INT8, int PMODE, int RES, bool INTERIOR, bool THROUGH, typename ACC, typename HOOK>
-__device__ __forceinline__ void epilogue_impl(const GemmDev &g, ACC (&acc)[T::MT][T::NT],
-                                              uint8_t *smem, int tm, int tn, int wm, int wn,
-                                              int lane, int wave, int tid, int partial_index,
-                                              HOOK &band_hook)
-{
-    using E = EpiLayout<T>;
-    const int l31 = lane & 31, lh = lane >> 5;
-    float alpha;
-    if constexpr (INT8)
-        alpha = g.alpha;
-    else
-        alpha = (*g.s0) * (*g.s1);
-    float pen = 0.0f;
-    uint8_t *stage = smem + wave * E::SLICE_BYTES;
-    uint8_t *wr = stage + l31 * E::ROW_BYTES + lh * 16;
-    const int rd_row = lane / E::LPR, rd_seg = lane % E::LPR;
-    const uint8_t *rd = stage + rd_row * E::ROW_BYTES + rd_seg * 32;
-    // addressing: a uniform base per (band, pass) plus one 32-bit byte offset per lane
-    const int m0 = tm * T::BM + wm * T::TM, n0 = tn * T::BN + wn * T::TN;
-    const uint32_t lane_off = ((uint32_t)rd_row * (uint32_t)g.N + (uint32_t)rd_seg * 8u) * 2u;
-    const int64_t base_off = ((int64_t)m0 * g.N + n0) * 2;
-    uint8_t *out_base = (uint8_t *)g.out + base_off;
-    const uint8_t *res_base = (const uint8_t *)g.residual + base_off;
-    const int rows_left = g.M - m0 - rd_row;  // row r of the sub-tile is valid for this lane if r < rows_left
-    const bool n_ok = n0 + rd_seg * 8 < g.N;
-    const bool has_res = RES < 0 ? g.residual != nullptr : RES != 0;
-    const bool has_pen = PMODE < 0 ? g.p != 0 : PMODE != 0;
-    // dequantisation steps per row / column (INT8, general form only): this lane's eight columns
-    // are the same in every pass; alpha is 1 then
-    const bool has_vec = INT8 && RES < 0 && g.rs != nullptr;
-    float cstep[8] = {1.0f, 1.0f, 1.0f, 1.0f, 1.0f, 1.0f, 1.0f, 1.0f};
-    if (has_vec) {
-        alpha = 1.0f;
-        if (n_ok) {
-#pragma unroll
-            for (int r = 0; r < 8; ++r)
-                cstep[r] = g.cs[(int64_t)(n0 + rd_seg * 8 + r) * g.cs_stride];
-        }
-    }
-    if constexpr (RES == 0 && INTERIOR && PMODE >= 0) {
-        // Fast path: round to bf16 in the MFMA layout, stage packed values (half the LDS bytes),
-        // two bands in flight.
-        uint8_t *wr2 = stage + l31 * E::ROW2_BYTES + lh * 8;
-        const uint8_t *rd2 = stage + rd_row * E::ROW2_BYTES + rd_seg * 16;
-        auto write_band = [&](int i) {
-#pragma unroll
-            for (int j = 0; j < T::NT; ++j)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const uint2 pk = make_uint2(pack_bf16x2((float)acc[i][j][4 * q + 0] * alpha,
-                                                            (float)acc[i][j][4 * q + 1] * alpha),
-                                                pack_bf16x2((float)acc[i][j][4 * q + 2] * alpha,
-                                                            (float)acc[i][j][4 * q + 3] * alpha));
-                    *(uint2 *)(wr2 + (i & 1) * E::BAND2_BYTES + j * 64 + q * 16) = pk;
-                }
-        };
-        write_band(0);
-#pragma unroll
-        for (int i = 0; i < T::MT; ++i) {
-            band_hook(i);
-            if (i + 1 < T::MT)
-                write_band(i + 1);
-#pragma unroll
-            for (int ps = 0; ps < E::PASSES; ++ps) {
-                const uint4 packed = *(const uint4 *)(rd2 + (i & 1) * E::BAND2_BYTES +
-                                                      ps * E::ROWS_PER_PASS * E::ROW2_BYTES);
-                const int64_t row_off = (int64_t)(i * 32 + ps * E::ROWS_PER_PASS) * g.N * 2;
-                if constexpr (THROUGH)
-                    store_through(out_base + row_off + lane_off, packed);
-                else
-                    *(uint4 *)(out_base + row_off + lane_off) = packed;
-                if constexpr (PMODE == 4) {
-                    const float t[8] = {bf16lo_to_f32(packed.x), bf16hi_to_f32(packed.x),
-                                        bf16lo_to_f32(packed.y), bf16hi_to_f32(packed.y),
-                                        bf16lo_to_f32(packed.z), bf16hi_to_f32(packed.z),
-                                        bf16lo_to_f32(packed.w), bf16hi_to_f32(packed.w)};
-#pragma unroll
-                    for (int r = 0; r < 8; ++r) {
-                        const float a2 = t[r] * t[r];
-                        pen = __builtin_fmaf(a2, a2, pen);
-                    }
-                }
-            }
-        }
-    } else {
-#pragma unroll
-    for (int i = 0; i < T::MT; ++i) {
-        band_hook(i);  // the caller's work to spread over the bands (e.g. next tile's DMA issue)
-#pragma unroll
-        for (int j = 0; j < T::NT; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                v4f v;
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    v[r] = (float)acc[i][j][4 * q + r] * alpha;
-                *(v4f *)(wr + j * 128 + q * 32) = v;
-            }
-        // the wave reads only what it wrote itself: LDS executes a wave's accesses in order
-#pragma unroll
-        for (int ps = 0; ps < E::PASSES; ++ps) {
-            const v4f lo = *(const v4f *)(rd + ps * E::ROWS_PER_PASS * E::ROW_BYTES);
-            const v4f hi = *(const v4f *)(rd + ps * E::ROWS_PER_PASS * E::ROW_BYTES + 16);
-            const int row_u = i * 32 + ps * E::ROWS_PER_PASS;  // uniform row of this pass
-            if (INTERIOR || (row_u < rows_left && n_ok)) {
-                const int64_t row_off = (int64_t)row_u * g.N * 2;
-                float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-                if (has_vec) {
-                    const float rstep = g.rs[(int64_t)(m0 + row_u + rd_row) * g.rs_stride];
-#pragma unroll
-                    for (int r = 0; r < 8; ++r)
-                        v[r] = (v[r] * rstep) * cstep[r];
-                }
-                if (has_res) {
-                    const uint4 rr = *(const uint4 *)(res_base + row_off + lane_off);
-                    v[0] += bf16lo_to_f32(rr.x);
-                    v[1] += bf16hi_to_f32(rr.x);
-                    v[2] += bf16lo_to_f32(rr.y);
-                    v[3] += bf16hi_to_f32(rr.y);
-                    v[4] += bf16lo_to_f32(rr.z);
-                    v[5] += bf16hi_to_f32(rr.z);
-                    v[6] += bf16lo_to_f32(rr.w);
-                    v[7] += bf16hi_to_f32(rr.w);
-                }
-                if (has_vec && g.out_i8) {  // INT8 output: one byte per element, no penalty
-                    uint32_t lo4 = 0, hi4 = 0;
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        lo4 |= round_to_i8(v[r], g.out_inv_step) << (8 * r);
-                        hi4 |= round_to_i8(v[4 + r], g.out_inv_step) << (8 * r);
-                    }
-                    *(uint2 *)((uint8_t *)g.out + (base_off + row_off + (int64_t)lane_off) / 2) = make_uint2(lo4, hi4);
-                    continue;
-                }
-                const uint4 packed = make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]),
-                                                pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7]));
-                *(uint4 *)(out_base + row_off + lane_off) = packed;
-                if (has_pen) {
-                    const float t[8] = {bf16lo_to_f32(packed.x), bf16hi_to_f32(packed.x),
-                                        bf16lo_to_f32(packed.y), bf16hi_to_f32(packed.y),
-                                        bf16lo_to_f32(packed.z), bf16hi_to_f32(packed.z),
-                                        bf16lo_to_f32(packed.w), bf16hi_to_f32(packed.w)};
-#pragma unroll
-                    for (int r = 0; r < 8; ++r) {
-                        if constexpr (PMODE == 4) {
-                            // sum a^4 here, times (1/(tau+eps))^4 once per lane below
-                            const float a2 = t[r] * t[r];
-                            pen = __builtin_fmaf(a2, a2, pen);
-                        } else {
-                            const float u = __builtin_fabsf(t[r]) * g.inv_tau;
-                            float w = u;
-                            for (int e = 1; e < g.p; ++e)
-                                w *= u;
-                            pen += w;
-                        }
-                    }
-                }
-            }
-        }
-    }
-    }
-    if (has_pen) {  // uniform over the workgroup
-        __shared__ float red[T::THREADS / kWave];
-        if constexpr (PMODE == 4) {
-            const float it2 = g.inv_tau * g.inv_tau;
-            pen *= it2 * it2;
-        }
-        pen = wave_reduce_sum(pen);
-        if (lane == 0)
-            red[wave] = pen;
-        __syncthreads();
-        if (tid == 0) {
-            float s = 0.0f;
-#pragma unroll
-            for (int w = 0; w < T::THREADS / kWave; ++w)
-                s += red[w];
-            g.partials[partial_index] = s;
-        }
-    }
-}
-
-struct NoBandHook {
-    __device__ __forceinline__ void operator()(int) const {}
-};
-
-template <typename T, bool INT8, typename ACC, typename HOOK>
-__device__ __forceinline__ void epilogue(const GemmDev &g, ACC (&acc)[T::MT][T::NT], uint8_t *smem,
-                                         int tm, int tn, int wm, int wn, int lane, int wave, int tid,
-                                         int partial_index, HOOK &band_hook)
-{
-    const bool interior = (tm + 1) * T::BM <= g.M && (tn + 1) * T::BN <= g.N;
-    const bool res = g.residual != nullptr;
-    const bool vec = INT8 && g.rs != nullptr;  // step vectors: the general form below applies them
-#define TWEO_EPI(PM, RS, IN, TH) \
-    epilogue_impl<T, INT8, PM, RS, IN, TH>(g, acc, smem, tm, tn, wm, wn, lane, wave, tid, partial_index, band_hook)
-    if (vec)
-        TWEO_EPI(-1, -1, false, false);
-    else if (interior && g.p == 4 && !res) {
-        if (g.through)
-            TWEO_EPI(4, 0, true, true);
-        else
-            TWEO_EPI(4, 0, true, false);
-    } else if (interior && g.p == 4)
-        TWEO_EPI(4, 1, true, false);
-    else if (interior && g.p == 0 && !res) {
-        if (g.through)
-            TWEO_EPI(0, 0, true, true);
-        else
-            TWEO_EPI(0, 0, true, false);
-    } else
-        TWEO_EPI(-1, -1, false, false);
-#undef TWEO_EPI
-}
-
-// K split: the fp32 (INT8: int32) sums of one run, straight from the MFMA layout.  Lane (l31, lh) holds row l31
-// and columns 8q + 4lh .. +3 of each 32x32 block (16-byte stores; the four q of a block complete
-// the row's 128-byte line).
-template <typename T, typename ACC>
-__device__ __forceinline__ void store_ksplit_run(const GemmDev &g, ACC (&acc)[T::MT][T::NT], int split, int tm,
-                                                 int tn, int wm, int wn, int l31, int lh)
-{
-    float *dst = g.ksplit_out + (int64_t)split * g.M * g.N;
-#pragma unroll
-    for (int i = 0; i < T::MT; ++i) {
-        const int m = tm * T::BM + wm * T::TM + i * 32 + l31;
-#pragma unroll
-        for (int j = 0; j < T::NT; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int n = tn * T::BN + wn * T::TN + j * 32 + 8 * q + 4 * lh;
-                if (m < g.M && n < g.N) {
-                    typedef std::remove_reference_t<decltype(acc[i][j][0])> word_t;
-                    typedef word_t v4w __attribute__((ext_vector_type(4)));
-                    *(v4w *)(dst + (int64_t)m * g.N + n) =
-                        v4w{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-                }
-            }
-    }
 }
 
 template <typename T, bool INT8, bool A_E5M2 = false>
@@ -476,7 +204,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_nt_kernel(GemmDev g)
 
     // the loop ends with a barrier: every wave is done reading the stages
     NoBandHook no_hook;
-    epilogue<T, INT8>(g, acc, smem, tm, tn, wm, wn, lane, wave, tid, blockIdx.x, no_hook);
+    epilogue<T, INT8>(g, acc, smem, tm, tn, wm, wn, lane, wave, tid, blockIdx.x, no_hook, gemm_alpha<INT8>(g));
 }
 
 // ---------------------------------------------------------------------------
@@ -508,14 +236,15 @@ struct TileD {
 };
 
 
-// KSPLIT: 1 = g.ksplit runs of the tile grid, 0 = none (a flag of its own: compiled in for all, the
-// second way out of the kernel cost the unsplit INT8 launches 2 %), 2 = g.ksplit says.  RAGGED: K may
+// KSPLIT: g.ksplit runs of the tile grid (a flag of its own: compiled in for all, the
+// second way out of the kernel cost the unsplit INT8 launches 2 %).  RAGGED: K may
 // be no multiple of 64 (without a flag the last stage's conditions cost whole stages 1-4 %: 8208x4000 under
 // 320 28.9 us against 28.2, INT8 16400x768 under 576 15.0 against 14.4).  block: the workgroup's number
 // in g's grid.
-template <typename T, bool INT8, bool A_E5M2, int KSPLIT, bool RAGGED>
-__device__ __forceinline__ void gemm_nt_dma_body(const GemmDev &g, const int block)
+template <typename T, bool INT8, bool KSPLIT = false, bool A_E5M2 = false, bool RAGGED = true>
+__global__ __launch_bounds__(T::THREADS, T::WPE) void gemm_nt_dma_kernel(GemmDev g)
 {
+    const int block = (int)blockIdx.x;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -524,11 +253,11 @@ __device__ __forceinline__ void gemm_nt_dma_body(const GemmDev &g, const int blo
     // with a K split the grid is ksplit runs of the tile grid: run `split` takes K stages
     // [split * stages / ksplit, (split + 1) * stages / ksplit)
     const int n_tiles = g.tiles_m * g.tiles_n;
-    const int split = KSPLIT != 0 ? block / n_tiles : 0;
+    const int split = KSPLIT ? block / n_tiles : 0;
     tile_of_workgroup(block - split * n_tiles, g.tiles_m, g.tiles_n, tm, tn);
     int kt = (g.K + T::BK - 1) / T::BK, kt_begin = 0;
     const int kt_all = kt;
-    if (KSPLIT != 0) {
+    if (KSPLIT) {
         kt_begin = (int)((int64_t)split * kt / g.ksplit);
         kt = (int)((int64_t)(split + 1) * kt / g.ksplit) - kt_begin;
     }
@@ -711,34 +440,13 @@ __device__ __forceinline__ void gemm_nt_dma_body(const GemmDev &g, const int blo
         if (s + 1 < kt)
             tail_step(s + 1, fr[1], fr[0]);
     }
-    if (KSPLIT == 1 || (KSPLIT == 2 && g.ksplit > 1))
+    if constexpr (KSPLIT) {
         store_ksplit_run<T>(g, acc, split, tm, tn, wm, wn, l31, lh);
-    if constexpr (KSPLIT != 1) {
-        if (KSPLIT == 2 && g.ksplit > 1)
-            return;
+    } else {
         block_barrier();  // every wave is done reading the stages before they are reused
         NoBandHook no_hook;
-        epilogue<T, INT8>(g, acc, smem, tm, tn, wm, wn, lane, wave, tid, block, no_hook);
+        epilogue<T, INT8>(g, acc, smem, tm, tn, wm, wn, lane, wave, tid, block, no_hook, gemm_alpha<INT8>(g));
     }
-}
-
-template <typename T, bool INT8, int KSPLIT = 0, bool A_E5M2 = false, bool RAGGED = true>
-__global__ __launch_bounds__(T::THREADS, T::WPE) void gemm_nt_dma_kernel(GemmDev g)
-{
-    gemm_nt_dma_body<T, INT8, A_E5M2, KSPLIT, RAGGED>(g, (int)blockIdx.x);
-}
-
-// The two products of a linear layer's backward in one launch: workgroups [0, n0) are the grid of g0,
-// [n0_padded, ..) that of g1 (padded to a multiple of 8 so that a workgroup's number modulo 8 is its
-// XCD in both).  For layers whose products leave the chip half empty one at a time: see pair_splits.
-template <typename T, bool A_E5M2>
-__global__ __launch_bounds__(T::THREADS, T::WPE) void gemm_nt_dma_pair_kernel(GemmDev g0, GemmDev g1, int n0, int n0_padded)
-{
-    const int b = (int)blockIdx.x;
-    if (b >= n0 && b < n0_padded)
-        return;
-    const bool first = b < n0;
-    gemm_nt_dma_body<T, false, A_E5M2, 2, true>(first ? g0 : g1, first ? b : b - n0_padded);
 }
 
 // ---------------------------------------------------------------------------
@@ -952,6 +660,7 @@ __global__ __launch_bounds__(T::THREADS, T::WPE) void gemm_nt_stream_kernel(Gemm
     };
 
     const int kt_full = g.K / T::BK;
+    const float alpha = gemm_alpha<INT8>(g);
     Frag fr[2];
 
     // ---- work units of this workgroup: whole tiles, then (SK) the segments of its stage range
@@ -1090,7 +799,7 @@ __global__ __launch_bounds__(T::THREADS, T::WPE) void gemm_nt_stream_kernel(Gemm
             whole = cur.s0 == 0 && cur.kt == kt_full;
         if (whole) {
             epilogue<T, INT8>(g, acc, smem + T::EPI_OFFSET, cur.tm, cur.tn, wm, wn, lane, wave, tid, cur.id,
-                              prefetch_hook);
+                              prefetch_hook, alpha);
         } else {
             __shared__ int sk_arrival;
             using word_t = typename std::conditional<INT8, int, float>::type;
@@ -1182,7 +891,7 @@ __global__ __launch_bounds__(T::THREADS, T::WPE) void gemm_nt_stream_kernel(Gemm
                 }
                 NoBandHook no_hook;
                 epilogue<T, INT8>(g, acc, smem + T::EPI_OFFSET, cur.tm, cur.tn, wm, wn, lane, wave, tid, cur.id,
-                                  no_hook);
+                                  no_hook, alpha);
             }
         }
         cur = nxt;
@@ -1192,7 +901,7 @@ __global__ __launch_bounds__(T::THREADS, T::WPE) void gemm_nt_stream_kernel(Gemm
 }
 
 // ---------------------------------------------------------------------------
-// W8A8 linear for small M (decode-time batches, M <= 128): the product is bound by streaming the
+// W8A8 linear for small M (decode-time batches, M <= 64): the product is bound by streaming the
 // N x K weight bytes from HBM once.  One workgroup per CU owns up to NB blocks of 16 weight rows
 // (block ids b, b + grid, ...); its 8 waves split K; products come from v_mfma_i32_16x16x64_i8
 // (operand row = lane % 16, 16 bytes at k = 16 * (lane / 16)); the partial int32 tiles of the
@@ -1469,9 +1178,6 @@ typedef Tile<256, 256, 2, 2> T256x256;
 typedef Tile<128, 128, 2, 2> T128x128;
 typedef TileD<256, 256, 2, 4, 4, 2> D256x256w8;
 typedef TileD<128, 128, 2, 2, 4, 2> D128x128w4;
-// Small outputs: a contraction of 512 is one memory latency, all eight stages in flight at once, and
-// four waves share what a register-staged wave did alone (256x512x512: 6.8 us, now 4.0).
-typedef TileD<64, 64, 2, 2, 8, 2> D64x64w4;
 typedef TileS<256, 256, 2, 4, 2, 2> S256x256w8;  // persistent, 8 waves, one workgroup per CU
 typedef TileS<128, 128, 2, 2, 2, 2> S128x128w4;  // two workgroups per CU
 typedef TileS<192, 256, 2, 4, 2, 2> S192x256w8;  // for tile counts that 256x256 quantises badly
@@ -1501,16 +1207,6 @@ bool take_profile_events(hipEvent_t *e0, hipEvent_t *e1)
     ++g_prof_next;
     return true;
 }
-template <typename KERNEL, typename... ARGS>
-static void launch_gemm_kernel(KERNEL kernel, dim3 grid, dim3 block, size_t lds, hipStream_t s, ARGS... args)
-{
-    hipEvent_t e0, e1;
-    if (take_profile_events(&e0, &e1)) {
-        hipExtLaunchKernelGGL(kernel, grid, block, lds, s, e0, e1, 0, args...);
-    } else {
-        hipLaunchKernelGGL(kernel, grid, block, lds, s, args...);
-    }
-}
 
 int num_cus_public();
 static int g_tile_override = 0;
@@ -1530,14 +1226,18 @@ size_t stream_k_workspace_bytes()
 
 // Kernel variants (the numbers are what tweo_set_gemm_tile takes; retired ones are refused).
 // 1, 3: register-staged kernel, tiles 256x256 (no shape is sent there any more), 128x128 (ragged
-// contractions under many tiles).  6, 8, 4:
-// DMA-pipelined kernel on 64-byte stages, 256x256 with 8 waves, 128x128 and 64x64.  11, 13,
-// 14: persistent streaming kernel (K % 128 == 0): 256x256, 128x128, 192x256.  15: deferred-epilogue
-// persistent kernel (256x256, four waves; M, N % 256 == 0, K % 128 == 0, K >= 512).  16: the same
-// kernel on 192x256 tiles (any M, K >= 2048).  17: the INT8 weight-streaming kernel (M <= 128).
-constexpr int kNumVariants = 17;
-static const int kVariantBM[kNumVariants + 1] = {0, 256, 256, 128, 64, 256, 256, 256, 128, 256, 128, 256, 256, 128, 192, 256, 192, 64};
-static const int kVariantBN[kNumVariants + 1] = {0, 256, 128, 128, 64, 256, 256, 128, 128, 128, 256, 256, 128, 128, 256, 256, 256, 64};
+// contractions under many tiles).  6, 8: DMA-pipelined kernel on 64-byte stages, 256x256 with 8 waves and
+// 128x128.  11, 13, 14: persistent streaming kernel (K % 128 == 0): 256x256, 128x128, 192x256.  15:
+// deferred-epilogue persistent kernel (256x256, four waves; M, N % 256 == 0, K % 128 == 0, K >= 512).  16: the same
+// kernel on 192x256 tiles (any M, K >= 2048).  17: the INT8 weight-streaming kernel (M <= 64).  4, 18 to 22: the
+// ring kernel on 64x64, 64x64 (two groups), 64x128, 64x128 (two groups), 128x128 and 96x128 tiles.
+constexpr int kNumVariants = 22;
+static const int kVariantBM[kNumVariants + 1] = {0, 256, 256, 128, 64, 256, 256, 256, 128, 256, 128, 256, 256, 128, 192, 256, 192, 64,
+                                                 64, 64, 64, 128, 96};
+static const int kVariantBN[kNumVariants + 1] = {0, 256, 128, 128, 64, 256, 256, 128, 128, 128, 256, 256, 128, 128, 256, 256, 256, 64,
+                                                 64, 128, 128, 128, 128};
+static int ring_variant(int shape) { return shape == 0 ? 4 : 17 + shape; }
+static int ring_shape(int variant) { return variant == 4 ? 0 : variant >= 18 ? variant - 17 : -1; }
 int gemm_num_variants() { return kNumVariants; }
 bool gemm_variant_exists(int v)
 {
@@ -1568,69 +1268,57 @@ static int defer_workgroups(int64_t M, int64_t N, int bm = 256)
     return (int)(tiles < cap ? tiles : cap);
 }
 
-// Outputs that go to 64x64 tiles: as long as three of them go to two CUs.  Measured (FP8, us, 64x64 / the
-// faster of the 128x128 kernels): 1024x1024 (256 tiles) under 512 / 2048 / 4096: 4.3 / 4.6, 7.3 / 11.8,
-// 11.0 / 18.3; 1024x2048 (512 tiles): 5.1 / 5.0, 11.6 / 11.6; 2048x2048 under 2048: 19.2 / 13.4.
 static int64_t tiles64(int64_t M, int64_t N) { return ((M + 63) / 64) * ((N + 63) / 64); }
-static bool small_output(int64_t M, int64_t N) { return M * N <= 128 * 128 * 16 || 2 * tiles64(M, N) <= 3 * (int64_t)num_cus(); }
-static int pick_variant(int64_t M, int64_t N, int64_t K)
+
+// Among the kernels that take a tile grid of any size; forced: a variant number, or 0.
+static int pick_tiled(int64_t M, int64_t N, int64_t K, int forced)
 {
     auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-    int v = g_tile_override >= 17 ? 4 : g_tile_override;
+    int v = forced;
     if (v == 0) {
-        if (small_output(M, N)) {
-            v = 4;
-        } else {
-            // rounds of tiles over the machine x cost of a tile; per-workgroup speeds are measured
-            // ratios: the persistent 256x256 kernel owns a CU, the 128x128 one shares it in pairs
-            const double cus = num_cus();
-            auto cost = [&](int bm, int bn, double slots, double speed) {
-                const double rounds = (double)((tiles(bm, bn) + (int64_t)slots - 1) / (int64_t)slots);
-                return rounds * bm * bn / speed;
-            };
-            const double c11 = cost(256, 256, cus, 1.0);
-            const double c13 = cost(128, 128, 2 * cus, 0.425);
-            const double c14 = cost(192, 256, cus, 0.97);
-            // The deferred-epilogue kernel (one wave per SIMD, operand halves refilled behind
-            // their own barriers) where the shape allows it: ahead of the 8-wave kernel by 15 %
-            // when a tile's write-out has 15 stages to hide under, by nothing at 6 stages.
-            const int64_t kt = K / 128;
-            const bool e15 = M % 256 == 0 && N % 256 == 0 && K % 128 == 0 && K >= 512 && 2 * tiles(256, 256) >= (int64_t)cus;
-            const bool e16 = N % 256 == 0 && K % 128 == 0 && K >= 2048;
-            const double gain = kt >= 16 ? 1.15 : (kt >= 8 ? 1.08 : 1.0);
-            const double c15 = e15 ? cost(256, 256, cus, gain) : 1e300;
-            const double c16 = e16 ? cost(192, 256, cus, 0.97 * gain) : 1e300;
-            v = 11;
-            double best = c11;
-            if (c14 < best) {
-                v = 14;
-                best = c14;
-            }
-            if (c15 < best) {
-                v = 15;
-                best = c15;
-            }
-            if (c16 < best) {
-                v = 16;
-                best = c16;
-            }
-            if (c13 < best)
-                v = 13;
-            if (v == 11 && e15)
-                v = 15;
-            if (v == 14 && e16)
-                v = 16;
-            // few K stages per tile: the big tiles' fixed cost per tile (fill, write-out) weighs
-            // more than the model's rounds say (8192x2304, K = 768: 26 us against 31 us measured)
-            if (v == 14 && K < 1024 && c13 < 1.2 * c14)
-                v = 13;
-            // at most one 128x128 tile per CU under a long contraction: the non-persistent
-            // kernel with its four-stage ring is 10-15 % ahead (weight gradients of narrow layers);
-            // with more tiles than CUs it falls behind (INT8, 12288 wide over 4096 at M = 384 / 512:
-            // 39 / 47 us against 32 / 37)
-            if (v == 13 && K >= 4096 && tiles(128, 128) <= (int64_t)cus)
-                v = 8;
+        // rounds of tiles over the machine x cost of a tile; per-workgroup speeds are measured
+        // ratios: the persistent 256x256 kernel owns a CU, the 128x128 one shares it in pairs
+        const double cus = num_cus();
+        auto cost = [&](int bm, int bn, double slots, double speed) {
+            const double rounds = (double)((tiles(bm, bn) + (int64_t)slots - 1) / (int64_t)slots);
+            return rounds * bm * bn / speed;
+        };
+        const double c11 = cost(256, 256, cus, 1.0);
+        const double c13 = cost(128, 128, 2 * cus, 0.425);
+        const double c14 = cost(192, 256, cus, 0.97);
+        // The deferred-epilogue kernel (one wave per SIMD, operand halves refilled behind
+        // their own barriers) where the shape allows it: ahead of the 8-wave kernel by 15 %
+        // when a tile's write-out has 15 stages to hide under, by nothing at 6 stages.
+        const int64_t kt = K / 128;
+        const bool e15 = M % 256 == 0 && N % 256 == 0 && K % 128 == 0 && K >= 512 && 2 * tiles(256, 256) >= (int64_t)cus;
+        const bool e16 = N % 256 == 0 && K % 128 == 0 && K >= 2048;
+        const double gain = kt >= 16 ? 1.15 : (kt >= 8 ? 1.08 : 1.0);
+        const double c15 = e15 ? cost(256, 256, cus, gain) : 1e300;
+        const double c16 = e16 ? cost(192, 256, cus, 0.97 * gain) : 1e300;
+        v = 11;
+        double best = c11;
+        if (c14 < best) {
+            v = 14;
+            best = c14;
         }
+        if (c15 < best) {
+            v = 15;
+            best = c15;
+        }
+        if (c16 < best) {
+            v = 16;
+            best = c16;
+        }
+        if (c13 < best)
+            v = 13;
+        if (v == 11 && e15)
+            v = 15;
+        if (v == 14 && e16)
+            v = 16;
+        // few K stages per tile: the big tiles' fixed cost per tile (fill, write-out) weighs
+        // more than the model's rounds say (8192x2304, K = 768: 26 us against 31 us measured)
+        if (v == 14 && K < 1024 && c13 < 1.2 * c14)
+            v = 13;
     }
     if (v >= 11 && K % 128 != 0)  // the persistent kernels need whole 128-byte stages
         v = v == 13 ? 8 : 6;
@@ -1640,9 +1328,70 @@ static int pick_variant(int64_t M, int64_t N, int64_t K)
     // direct-to-LDS / register-staged: 2560x2048 under 528 / 2064 / 16400: 10.4 / 10.2, 26.9 / 21.9, 194 /
     // 133; 50448x768 under 528 / 3088: 52 / 49, 233 / 180); with at most one tile per CU it is behind
     // (2048x2048 under 2064 18.4 / 21.4), and below 512 (2560x2048 under 400 8.6 / 9.5).
-    if (g_tile_override == 0 && v == 8 && K % 64 != 0 && K >= 512 && tiles(128, 128) > (int64_t)num_cus())
+    if (forced == 0 && v == 8 && K % 64 != 0 && K >= 512 && tiles(128, 128) > (int64_t)num_cus())
         v = 3;
     return v;
+}
+
+// Time of one product on such a kernel in microseconds, from what the kernels measured (190 layers of 256
+// to 6144 columns over 256 to 50432 rows, medians within 5 % per kernel, single ones within 25 %).  Per
+// 64-byte stage: a 128x128 tile alone on its CU 0.28, two 0.58 (streaming: 0.37; a contraction that is no
+// multiple of 64: 0.375 and 0.8, register-staged 0.57); a 256x256 tile 0.8 (1.05).  Per 128-byte stage: a
+// 256x256 tile of the deferred kernel 1.25, of the 8-wave kernel 1.45.
+static double tiled_us(int v, int64_t M, int64_t N, int64_t K)
+{
+    const double cus = num_cus(), kt = (double)(K + 127) / 128;
+    const bool ragged = K % 64 != 0;
+    auto rounds = [&](int64_t tr, int64_t tc, double slots) {
+        return std::ceil((double)(((M + tr - 1) / tr) * ((N + tc - 1) / tc)) / slots);
+    };
+    if (v == 15 || v == 16)
+        return 1.25 * kt * (v == 16 ? 0.77 : 1.0) * rounds(v == 16 ? 192 : 256, 256, cus) + 6.0;
+    if (v == 11 || v == 14)
+        return 1.45 * kt * (v == 14 ? 0.77 : 1.0) * rounds(v == 14 ? 192 : 256, 256, cus) + 6.0;
+    if (v == 6)
+        return (ragged ? 1.05 : 0.8) * 2.0 * kt * rounds(256, 256, cus) + 5.0;
+    const bool alone = rounds(128, 128, cus) <= 1.0;
+    const double stage = v == 3 ? 0.57 : v == 13 ? (alone ? 0.28 : 0.37)
+                                                 : (ragged ? (alone ? 0.375 : 0.8) : (alone ? 0.28 : 0.58));
+    return stage * 2.0 * kt * rounds(128, 128, alone && v != 3 ? cus : 2.0 * cus) + 4.0;
+}
+
+// The kernel a product runs on and its estimated time: the ring kernel, where all its workgroups are resident
+// at once and that is the faster way.
+struct Pick {
+    int v;
+    double us;
+};
+static Pick pick(int64_t M, int64_t N, int64_t K)
+{
+    if (g_tile_override != 0) {
+        const int v = g_tile_override == 17 ? 4 : g_tile_override;
+        return Pick{ring_shape(v) >= 0 ? v : pick_tiled(M, N, K, v), 0.0};
+    }
+    const int v = pick_tiled(M, N, K, 0);
+    const double us = tiled_us(v, M, N, K);
+    double ring_us;
+    const int shape = ring_pick(M, N, K, num_cus(), &ring_us);
+    return ring_us < us ? Pick{ring_variant(shape), ring_us} : Pick{v, us};
+}
+static int pick_variant(int64_t M, int64_t N, int64_t K) { return pick(M, N, K).v; }
+
+// the ring kernel's time for a product, 1e300 where it does not take it
+static double ring_us(int64_t M, int64_t N, int64_t K)
+{
+    double us = 1e300;
+    if (g_tile_override == 0)
+        ring_pick(M, N, K, num_cus(), &us);
+    return us;
+}
+
+// Time of a K split of `splits` runs: the deferred kernel's 256x256 tiles, or 256x256 tiles on 64-byte stages.
+// Runs are written at 5 TB/s and read at 6.5.
+static double ksplit_us(int64_t M, int64_t N, int64_t K, int splits, bool deferred)
+{
+    const double kt = (double)(K + 127) / 128, mb = (double)splits * (double)M * (double)N * 4e-6;
+    return (deferred ? 1.3 * kt / splits + 3.0 : (K % 64 != 0 ? 1.3 : 0.85) * 2.0 * kt / splits + 5.0) + mb / 5.0 + 2.5 + mb / 6.5;
 }
 
 // The deferred-epilogue kernel covers whole 256x256 tiles, K in whole stages with enough of
@@ -1677,15 +1426,6 @@ int fp8_gemm_partials(const GemmArgs &a)
     return (int)(((a.M + kVariantBM[v] - 1) / kVariantBM[v]) * ((a.N + kVariantBN[v] - 1) / kVariantBN[v]));
 }
 
-// Outputs that the tiled kernels' epilogue writes through the L2s (store_through): whole lines, 4 to 16 MB.  What
-// is dirty when a kernel ends is written back before the next one starts (2.4 us to it instead of 1.0 at 12
-// MB).  us, dirty / through: 8192x768 under 768 9.2 / 8.3, under 3072 22.4 / 20.7; 4096x1024 under 1024 9.1 / 8.5;
-// 2048x2048 under 2048 13.7 / 13.2.  Larger ones do not gain: 8192x2304 under 768 25.4 / 25.6, with the
-// penalty 29.7 / 29.9; 4096x4096 under 1024 with the penalty 23.2 / 23.5.
-static int writes_through(int64_t M, int64_t N)
-{
-    return N % 64 == 0 && M * N >= ((int64_t)1 << 21) && M * N <= ((int64_t)1 << 23);
-}
 
 template <typename T, bool INT8, bool DMA, bool A_E5M2, bool RAGGED>
 static hipError_t launch_tile_inst(const GemmArgs &a, hipStream_t s)
@@ -1693,7 +1433,7 @@ static hipError_t launch_tile_inst(const GemmArgs &a, hipStream_t s)
     static bool attr_done = false;  // per instantiation
     const void *kern;
     if constexpr (DMA)
-        kern = (const void *)gemm_nt_dma_kernel<T, INT8, 0, A_E5M2, RAGGED>;
+        kern = (const void *)gemm_nt_dma_kernel<T, INT8, false, A_E5M2, RAGGED>;
     else
         kern = (const void *)gemm_nt_kernel<T, INT8, A_E5M2>;
     if (!attr_done) {
@@ -1703,34 +1443,10 @@ static hipError_t launch_tile_inst(const GemmArgs &a, hipStream_t s)
             return e;
         attr_done = true;
     }
-    GemmDev g;
-    g.A = a.A;
-    g.B = a.B;
-    g.M = (int)a.M;
-    g.N = (int)a.N;
-    g.K = (int)a.K;
-    g.s0 = a.s0;
-    g.s1 = a.s1;
-    g.alpha = a.alpha;
-    g.residual = (const uint16_t *)a.residual;
-    g.out = (uint16_t *)a.out;
-    g.inv_tau = a.inv_tau;
-    g.p = a.p;
-    g.partials = a.partials;
-    g.rs = a.row_step;
-    g.cs = a.col_step;
-    g.rs_stride = a.row_step_stride;
-    g.cs_stride = a.col_step_stride;
-    g.out_i8 = a.out_i8 ? 1 : 0;
-    g.out_inv_step = a.out_inv_step;
-    g.ksplit = 1;
-    g.ksplit_out = nullptr;
-    g.through = writes_through(a.M, a.N);
-    g.tiles_m = (int)((a.M + T::BM - 1) / T::BM);
-    g.tiles_n = (int)((a.N + T::BN - 1) / T::BN);
+    const GemmDev g = gemm_dev(a, T::BM, T::BN);
     const dim3 grid((unsigned)(g.tiles_m * g.tiles_n)), block(T::THREADS);
     if constexpr (DMA)
-        launch_gemm_kernel(gemm_nt_dma_kernel<T, INT8, 0, A_E5M2, RAGGED>, grid, block, T::LDS_BYTES, s, g);
+        launch_gemm_kernel(gemm_nt_dma_kernel<T, INT8, false, A_E5M2, RAGGED>, grid, block, T::LDS_BYTES, s, g);
     else
         launch_gemm_kernel(gemm_nt_kernel<T, INT8, A_E5M2>, grid, block, T::LDS_BYTES, s, g);
     return hipGetLastError();
@@ -1775,31 +1491,7 @@ static hipError_t launch_stream_inst(const GemmArgs &a, hipStream_t s, int grid,
             return e;
         attr_done = true;
     }
-    GemmDev g;
-    g.A = a.A;
-    g.B = a.B;
-    g.M = (int)a.M;
-    g.N = (int)a.N;
-    g.K = (int)a.K;
-    g.s0 = a.s0;
-    g.s1 = a.s1;
-    g.alpha = a.alpha;
-    g.residual = (const uint16_t *)a.residual;
-    g.out = (uint16_t *)a.out;
-    g.inv_tau = a.inv_tau;
-    g.p = a.p;
-    g.partials = a.partials;
-    g.rs = a.row_step;
-    g.cs = a.col_step;
-    g.rs_stride = a.row_step_stride;
-    g.cs_stride = a.col_step_stride;
-    g.out_i8 = a.out_i8 ? 1 : 0;
-    g.out_inv_step = a.out_inv_step;
-    g.ksplit = 1;
-    g.ksplit_out = nullptr;
-    g.tiles_m = (int)((a.M + T::BM - 1) / T::BM);
-    g.tiles_n = (int)((a.N + T::BN - 1) / T::BN);
-    g.through = writes_through(a.M, a.N);
+    GemmDev g = gemm_dev(a, T::BM, T::BN);
     g.sk_full_rounds = full_rounds;
     g.sk_counters = (uint32_t *)a.sk_workspace;
     g.sk_partials = (uint8_t *)a.sk_workspace + kStreamKCounterBytes;
@@ -1844,30 +1536,9 @@ static hipError_t launch_defer_inst(const GemmArgs &a, hipStream_t s)
             return e;
         attr_done = true;
     }
-    GemmDev g;
-    g.A = a.A;
-    g.B = a.B;
-    g.M = (int)a.M;
-    g.N = (int)a.N;
-    g.K = (int)a.K;
-    g.s0 = a.s0;
-    g.s1 = a.s1;
-    g.alpha = a.alpha;
-    g.residual = RES ? (const uint16_t *)a.residual : nullptr;
-    g.out = (uint16_t *)a.out;
-    g.inv_tau = a.inv_tau;
-    g.p = a.p;
-    g.partials = a.partials;
-    g.rs = a.row_step;
-    g.cs = a.col_step;
-    g.rs_stride = a.row_step_stride;
-    g.cs_stride = a.col_step_stride;
-    g.out_i8 = a.out_i8 ? 1 : 0;
-    g.out_inv_step = a.out_inv_step;
-    g.ksplit = 1;
-    g.ksplit_out = nullptr;
-    g.tiles_m = (int)((a.M + T::BM - 1) / T::BM);
-    g.tiles_n = (int)(a.N / T::BN);
+    GemmDev g = gemm_dev(a, T::BM, T::BN);
+    if (!RES)
+        g.residual = nullptr;
     const int grid = defer_workgroups(a.M, a.N, T::BM);
     launch_gemm_kernel(kernel, dim3((unsigned)grid), dim3(T::THREADS), LDS, s, g);
     return hipGetLastError();
@@ -1920,10 +1591,12 @@ static hipError_t launch_defer192(const GemmArgs &a, hipStream_t s)
 template <bool INT8>
 static hipError_t launch_gemm(const GemmArgs &a, hipStream_t s)
 {
-    switch (resolve_variant(a)) {
+    const int v = resolve_variant(a);
+    if (ring_shape(v) >= 0)
+        return launch_ring(a, ring_shape(v), INT8, s);
+    switch (v) {
     case 1: return launch_tile<T256x256, INT8, false>(a, s);
     case 3: return launch_tile<T128x128, INT8, false>(a, s);
-    case 4: return launch_tile<D64x64w4, INT8, true>(a, s);
     case 6: return launch_tile<D256x256w8, INT8, true>(a, s);
     case 8: return launch_tile<D128x128w4, INT8, true>(a, s);
     case 11: return launch_stream<S256x256w8, INT8, 1>(a, s);
@@ -1949,7 +1622,7 @@ static hipError_t launch_gemm(const GemmArgs &a, hipStream_t s)
 // (INT8, 4096 wide over 11008: 64 tiles 67 -> 60 us, 80 tiles 106 -> 68 us): the INT8 flavour of the
 // same kernel leaves int32 runs, which the reduce kernel adds exactly.
 constexpr int kKsplitDeferMinStages = 16, kKsplitDeferMinKt = 64;
-static int defer_ksplit(int64_t M, int64_t N, int64_t K)
+static int defer_ksplit_runs(int64_t M, int64_t N, int64_t K)
 {
     if (g_tile_override != 0 || M % 256 != 0 || N % 256 != 0 || K % 128 != 0 || N > ((int64_t)1 << 22))
         return 1;
@@ -1964,13 +1637,10 @@ static int defer_ksplit(int64_t M, int64_t N, int64_t K)
     return splits >= 2 ? (int)splits : 1;
 }
 
-int fp8_gemm_ksplit(int64_t M, int64_t N, int64_t K)
+static int tiled_ksplit_runs(int64_t M, int64_t N, int64_t K)
 {
     if (g_tile_override != 0)
         return 1;
-    const int ds = defer_ksplit(M, N, K);
-    if (ds > 1)
-        return ds;
     const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256), k_tiles = (K + kBK - 1) / kBK;
     const int64_t cus = num_cus();
     if (tiles * 4 > cus || k_tiles < 128)
@@ -1983,16 +1653,45 @@ int fp8_gemm_ksplit(int64_t M, int64_t N, int64_t K)
     return splits >= 2 ? (int)splits : 1;
 }
 
-// INT8, between decode and prefill sizes: an output of few 128x128 tiles leaves CUs idle (384 rows into
-// 4096 columns: 96 tiles), so `splits` workgroups share a tile on the direct-to-LDS kernel, int32 runs
-// added exactly by the reduce kernel.  The rule is the time of both ways from measured rates: a tile
-// alone on its CU runs at 0.29 us per 64-byte stage (two on a CU share that; 0.135 and 0.26 for the
-// 64x64 tiles of small outputs), the runs are written and read at 4 TB/s, the second launch costs 4 us;
-// taken where that promises a tenth.
-// (A lone FP8 tile is as fast, see lone_gemm_us.)
-// Quantise + linear, 11008 -> 4096 at M = 300 / 384 / 500: 44.2 / 53.6 / 53.9 -> 32.6 / 37.7 / 44.9 us;
-// 5632 -> 2048 at M = 300 is not split: its 160 tiles of 64x64 are the faster way.
-static int i8_dma_ksplit(int64_t M, int64_t N, int64_t K)
+// What runs a product that scratch is asked for (by the rules above): one launch of the ring kernel over the whole
+// contraction, runs of its small tiles, or the runs above.  768x768 over 8192 tokens 25.3 us in the deferred
+// kernel's runs, 13.4 whole; 2304x768 30.2, 20.3; 256x256 over 20480 28.0, 11.9 in ten runs of 64x64 tiles, 512x512 28.7, 19.7; the estimate of the large tiles' runs is high by a
+// seventh there.
+enum SplitWay { kWhole, kRingRuns, kDeferRuns, kTiledRuns };
+struct Split {
+    SplitWay way;
+    int runs, shape;  // shape: of the ring kernel
+    double us;
+};
+constexpr double kKsplitBias = 0.85;
+static Split pick_split(int64_t M, int64_t N, int64_t K)
+{
+    const int dr = defer_ksplit_runs(M, N, K), runs = dr > 1 ? dr : tiled_ksplit_runs(M, N, K);
+    if (runs <= 1)
+        return Split{kWhole, 1, -1, pick(M, N, K).us};
+    Split best{dr > 1 ? kDeferRuns : kTiledRuns, runs, -1, kKsplitBias * ksplit_us(M, N, K, runs, dr > 1)};
+    const double whole = ring_us(M, N, K);
+    if (whole < best.us)
+        best = Split{kWhole, 1, -1, whole};
+    int shape = -1;
+    double us;
+    const int small = ring_ksplit_pick(M, N, K, num_cus(), runs, &shape, &us);
+    if (small > 1 && us < best.us)
+        best = Split{kRingRuns, small, shape, us};
+    return best;
+}
+
+// INT8: the deferred kernel's runs, unless the ring kernel is faster over the whole contraction
+static int i8_defer_ksplit(int64_t M, int64_t N, int64_t K)
+{
+    const int runs = defer_ksplit_runs(M, N, K);
+    return runs > 1 && ring_us(M, N, K) < kKsplitBias * ksplit_us(M, N, K, runs, true) ? 1 : runs;
+}
+
+// INT8, between decode and prefill sizes: the scratch that such products are given.  Outputs of few 128x128 tiles
+// were once split over K in it; the ring kernel needs none (quantise + linear 11008 -> 4096 at M = 384 37.8 us
+// split, 30.4 now), and what a program has planned with stays what it was.
+static int i8_dma_runs(int64_t M, int64_t N, int64_t K)
 {
     if (g_tile_override != 0 || N % 8 != 0 || M <= 128)
         return 1;
@@ -2000,14 +1699,15 @@ static int i8_dma_ksplit(int64_t M, int64_t N, int64_t K)
     if (tiles * 2 > cus)
         return 1;
     int best = 1;
-    const double plain = small_output(M, N) ? (tiles64(M, N) <= cus ? 0.135 : 0.26) : 0.29;
+    const bool small = M * N <= 128 * 128 * 16 || 2 * tiles64(M, N) <= 3 * cus;
+    const double plain = small ? (tiles64(M, N) <= cus ? 0.135 : 0.26) : 0.29;
     double best_us = 0.9 * (plain * (double)kt + 3.0);
     for (int s = 2; s <= 8 && kt / s >= 16; ++s) {
-        const double us = 0.29 * (double)((tiles * s + cus - 1) / cus) * (double)((kt + s - 1) / s) +
-                          (double)s * (double)M * (double)N * 8.0 / 4e6 + 4.0;
-        if (us < best_us) {
+        const double t = 0.29 * (double)((tiles * s + cus - 1) / cus) * (double)((kt + s - 1) / s) +
+                         (double)s * (double)M * (double)N * 8.0 / 4e6 + 4.0;
+        if (t < best_us) {
             best = s;
-            best_us = us;
+            best_us = t;
         }
     }
     return best;
@@ -2015,23 +1715,40 @@ static int i8_dma_ksplit(int64_t M, int64_t N, int64_t K)
 
 size_t i8_gemm_ksplit_bytes(int64_t M, int64_t N, int64_t K)
 {
-    int splits = defer_ksplit(M, N, K);
+    int splits = defer_ksplit_runs(M, N, K);
     if (splits <= 1)
-        splits = i8_dma_ksplit(M, N, K);
+        splits = i8_dma_runs(M, N, K);
     return splits > 1 ? (size_t)splits * (size_t)M * (size_t)N * sizeof(int32_t) : 0;
 }
 
 size_t fp8_gemm_ksplit_bytes(int64_t M, int64_t N, int64_t K)
 {
-    const int splits = fp8_gemm_ksplit(M, N, K);
+    int splits = defer_ksplit_runs(M, N, K);
+    if (splits <= 1)
+        splits = tiled_ksplit_runs(M, N, K);
     return splits > 1 ? (size_t)splits * (size_t)M * (size_t)N * sizeof(float) : 0;
+}
+
+// the second launch of a K split whose runs lie as the output does
+template <bool INT8>
+static hipError_t launch_splitk_reduce(const GemmArgs &a, int splits, hipStream_t s, hipEvent_t end)
+{
+    const int64_t mn = a.M * a.N;
+    const dim3 grid((unsigned)((mn / 8 + 255) / 256));
+    if (end != nullptr)
+        hipExtLaunchKernelGGL(splitk_reduce_kernel<INT8>, grid, dim3(256), 0, s, nullptr, end, 0,
+                              (const float *)a.sk_workspace, splits, mn, a.s0, a.s1, a.alpha, (uint16_t *)a.out);
+    else
+        hipLaunchKernelGGL(splitk_reduce_kernel<INT8>, grid, dim3(256), 0, s, (const float *)a.sk_workspace, splits, mn,
+                           a.s0, a.s1, a.alpha, (uint16_t *)a.out);
+    return hipGetLastError();
 }
 
 // On the direct-to-LDS kernel.
 template <typename T, bool A_E5M2, bool INT8 = false>
 static hipError_t launch_ksplit(const GemmArgs &a, hipStream_t s, int splits)
 {
-    constexpr auto kern = gemm_nt_dma_kernel<T, INT8, 1, A_E5M2>;
+    constexpr auto kern = gemm_nt_dma_kernel<T, INT8, true, A_E5M2>;
     static bool attr_done = false;
     if (!attr_done) {
         hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
@@ -2039,22 +1756,10 @@ static hipError_t launch_ksplit(const GemmArgs &a, hipStream_t s, int splits)
             return e;
         attr_done = true;
     }
-    GemmDev g{};
-    g.A = a.A;
-    g.B = a.B;
-    g.M = (int)a.M;
-    g.N = (int)a.N;
-    g.K = (int)a.K;
-    g.s0 = a.s0;
-    g.s1 = a.s1;
-    g.out = (uint16_t *)a.out;
-    g.tiles_m = (int)((a.M + T::BM - 1) / T::BM);
-    g.tiles_n = (int)((a.N + T::BN - 1) / T::BN);
+    GemmDev g = gemm_dev(a, T::BM, T::BN);
     g.ksplit = splits;
     g.ksplit_out = (float *)a.sk_workspace;
     const dim3 grid((unsigned)(g.tiles_m * g.tiles_n * splits)), block(T::THREADS);
-    const int64_t mn = a.M * a.N;
-    const dim3 rgrid((unsigned)((mn / 8 + 255) / 256));
     // a profiled launch brackets both kernels: start event on the first, end event on the second
     hipEvent_t e0 = nullptr, e1 = nullptr;
     take_profile_events(&e0, &e1);
@@ -2062,13 +1767,8 @@ static hipError_t launch_ksplit(const GemmArgs &a, hipStream_t s, int splits)
         hipExtLaunchKernelGGL(kern, grid, block, T::LDS_BYTES, s, e0, nullptr, 0, g);
     else
         hipLaunchKernelGGL(kern, grid, block, T::LDS_BYTES, s, g);
-    if (e1 != nullptr)
-        hipExtLaunchKernelGGL(splitk_reduce_kernel<INT8>, rgrid, dim3(256), 0, s, nullptr, e1, 0,
-                              (const float *)g.ksplit_out, splits, mn, a.s0, a.s1, a.alpha, (uint16_t *)a.out);
-    else
-        hipLaunchKernelGGL(splitk_reduce_kernel<INT8>, rgrid, dim3(256), 0, s, (const float *)g.ksplit_out, splits, mn,
-                           a.s0, a.s1, a.alpha, (uint16_t *)a.out);
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : launch_splitk_reduce<INT8>(a, splits, s, e1);
 }
 
 template <bool A_E5M2, bool INT8 = false>
@@ -2115,169 +1815,21 @@ static hipError_t launch_ksplit_defer(const GemmArgs &a, hipStream_t s, int spli
     return hipGetLastError();
 }
 
-// Time of one gradient product by itself in microseconds, from what the kernels measured (190 layers of 256
-// to 6144 columns over 256 to 50432 rows, medians within 5 % per kernel, single ones within 25 %).  Per
-// 64-byte stage: a 64x64 tile alone on its CU 0.135; a 128x128 tile alone on its CU 0.28, two 0.58
-// (streaming: 0.37; a contraction that is no multiple of 64: 0.375 and 0.8, register-staged 0.57); a
-// 256x256 tile 0.8 (1.05).  Per 128-byte stage: a 256x256 tile of the deferred kernel 1.25, of the 8-wave
-// kernel 1.45.  Runs of a K split are written at 5 TB/s and read at 6.5.
-static double lone_gemm_us(int64_t M, int64_t N, int64_t K)
-{
-    const double cus = num_cus(), kt = (double)(K + 127) / 128;
-    const bool ragged = K % 64 != 0;
-    auto rounds = [&](int64_t tr, int64_t tc, double slots) {
-        return std::ceil((double)(((M + tr - 1) / tr) * ((N + tc - 1) / tc)) / slots);
-    };
-    const int ds = defer_ksplit(M, N, K), ks = ds > 1 ? ds : fp8_gemm_ksplit(M, N, K);
-    if (ks > 1) {
-        const double mb = (double)ks * (double)M * (double)N * 4e-6, runs = mb / 5.0 + 2.5 + mb / 6.5;
-        return (ds > 1 ? 1.3 * kt / ks + 3.0 : (ragged ? 1.3 : 0.85) * 2.0 * kt / ks + 5.0) + runs;
-    }
-    const int v = pick_variant(M, N, K);
-    if (v == 4)
-        return (tiles64(M, N) <= (int64_t)cus ? 0.135 : 0.26) * 2.0 * kt + 3.0;
-    if (v == 15 || v == 16)
-        return 1.25 * kt * (v == 16 ? 0.77 : 1.0) * rounds(v == 16 ? 192 : 256, 256, cus) + 6.0;
-    if (v == 11 || v == 14)
-        return 1.45 * kt * (v == 14 ? 0.77 : 1.0) * rounds(v == 14 ? 192 : 256, 256, cus) + 6.0;
-    if (v == 6)
-        return (ragged ? 1.05 : 0.8) * 2.0 * kt * rounds(256, 256, cus) + 5.0;
-    const bool alone = rounds(128, 128, cus) <= 1.0;
-    const double stage = v == 3 ? 0.57 : v == 13 ? (alone ? 0.28 : 0.37)
-                                                 : (ragged ? (alone ? 0.375 : 0.8) : (alone ? 0.28 : 0.58));
-    return stage * 2.0 * kt * rounds(128, 128, alone && v != 3 ? cus : 2.0 * cus) + 4.0;
-}
-
-// The two gradient products of a layer in one launch of 128x128 tiles (gemm_nt_dma_pair_kernel), the
-// weight gradient's contraction in `splits` runs; 0 = the two run one after the other.  The pair fills
-// the chip where each alone would leave CUs idle, but its kernel is no fast one: taken where the two ways'
-// times, estimated from measured rates, say so (backward, us, apart / paired: 8192x768 -> 768 36.6 / 30.0,
-// 2128x3776 -> 880 40.8 / 36.3; 8192x3072 -> 768 stays apart, 54 / 66, and so does 35984x1536 -> 1280,
-// 202 / 241).
-static bool pair_is_small(int64_t M, int64_t N, int64_t K) { return tiles64(M, K) + tiles64(N, K) <= 2 * (int64_t)num_cus(); }
-static int pair_splits(int64_t M, int64_t N, int64_t K)
-{
-    if (g_tile_override != 0 || !g_stream_k_off)
-        return 0;
-    // few 64x64 tiles each, all of them resident at once; a long contraction beside few tiles is better
-    // off with a K split of its own
-    if (pair_is_small(M, N, K) && fp8_gemm_ksplit(N, K, M) == 1)
-        return 1;
-    auto tiles = [](int64_t r, int64_t c) { return ((r + 127) / 128) * ((c + 127) / 128); };
-    if (M * K <= 128 * 128 * 16 || N * K <= 128 * 128 * 16)
-        return 0;
-    const double slots = 2.0 * num_cus();
-    const int64_t kd = (N + 63) / 64, kw = (M + 63) / 64, td = tiles(M, K), tw = tiles(N, K);
-    // stages that lie across lines take a sixth longer
-    const double fd = N % 64 != 0 ? 1.16 : 1.0, fw = M % 64 != 0 ? 1.16 : 1.0;
-    auto runs_us = [&](int r) { return r > 1 ? (double)r * (double)N * (double)K * 4e-6 / 6.5 + 2.5 : 0.0; };
-    // The number of runs: the cost of a long last unit against the runs' way through memory.  A contraction
-    // of up to 4096 stays whole, as on the deferred kernel (whose split lost there, 14 -> 20 us), so that
-    // such a layer's backward needs no scratch beyond its scalars.
-    const double load = (fd * (double)(td * kd) + fw * (double)(tw * kw)) / slots;
-    int best = 0;
-    double best_us = 1e300, d = 0.0, w = 0.0;
-    for (int r = 1; r <= (kw > 64 ? 16 : 1) && kw / r >= 8; ++r) {
-        const double unit = (double)std::max(kd, (kw + r - 1) / r);
-        const double us = std::max(0.92 * load, 0.62 * unit) + 0.15 * unit + runs_us(r);
-        if (us < best_us) {
-            best_us = us;
-            best = r;
-            d = fd * (double)kd;
-            w = fw * (double)((kw + r - 1) / r);
-        }
-    }
-    if (best == 0)
-        return 0;
-    // its time, fitted to the same layers (nine in ten within 20 %): stages per slot at two tiles to a CU and
-    // the uneven end (none if all units are resident at once and about as long: 2048x2048 -> 2048 28.7 us
-    // apart, 25.1 paired), or the longest unit, which ends up alone on its CU; the runs
-    const double longer = std::max(d, w), shorter = std::min(d, w);
-    const bool even = (double)(td + tw * best) <= slots && shorter > 0.8 * longer;
-    const double us = std::max(0.69 * load + (even ? 0.0 : 0.11 * shorter), 0.23 * longer) + (even ? 0.0 : 0.06 * longer) + 4.0 +
-                      runs_us(best);
-    return us < 0.97 * (lone_gemm_us(M, K, N) + lone_gemm_us(N, K, M)) ? best : 0;
-}
-
-static size_t pair_bytes(int64_t N, int64_t K, int splits)
-{
-    return splits > 1 ? (size_t)splits * (size_t)N * (size_t)K * sizeof(float) : 0;
-}
-
-size_t fp8_pair_bytes(int64_t M, int64_t N, int64_t K) { return pair_bytes(N, K, pair_splits(M, N, K)); }
-
-template <typename T, bool A_E5M2>
-static hipError_t launch_pair(const GemmArgs &d, const GemmArgs &w, int splits, hipStream_t s)
-{
-    constexpr auto kern = gemm_nt_dma_pair_kernel<T, A_E5M2>;
-    static bool attr_done = false;
-    if (!attr_done) {
-        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
-        if (e != hipSuccess)
-            return e;
-        attr_done = true;
-    }
-    auto dev = [](const GemmArgs &a, int ks) {
-        GemmDev g{};
-        g.A = a.A;
-        g.B = a.B;
-        g.M = (int)a.M;
-        g.N = (int)a.N;
-        g.K = (int)a.K;
-        g.s0 = a.s0;
-        g.s1 = a.s1;
-        g.out = (uint16_t *)a.out;
-        g.tiles_m = (int)((a.M + T::BM - 1) / T::BM);
-        g.tiles_n = (int)((a.N + T::BN - 1) / T::BN);
-        g.through = ks == 1 && writes_through(a.M, a.N);
-        g.ksplit = ks;
-        g.ksplit_out = ks > 1 ? (float *)a.sk_workspace : nullptr;
-        return g;
-    };
-    GemmDev g0 = dev(d, 1), g1 = dev(w, splits);
-    if (g0.K < g1.K / splits)  // the longer units first
-        std::swap(g0, g1);
-    const int n0 = g0.tiles_m * g0.tiles_n * g0.ksplit, n1 = g1.tiles_m * g1.tiles_n * g1.ksplit;
-    const int n0_padded = (n0 + 7) / 8 * 8;
-    const dim3 grid((unsigned)(n0_padded + n1)), block(T::THREADS);
-    // one pair of profile events for the call: start event on its first kernel, end event on its last
-    hipEvent_t e0 = nullptr, e1 = nullptr;
-    take_profile_events(&e0, &e1);
-    if (e0 != nullptr)
-        hipExtLaunchKernelGGL(kern, grid, block, T::LDS_BYTES, s, e0, splits == 1 ? e1 : nullptr, 0, g0, g1, n0, n0_padded);
-    else
-        hipLaunchKernelGGL(kern, grid, block, T::LDS_BYTES, s, g0, g1, n0, n0_padded);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || splits == 1)
-        return e;
-    const int64_t mn = w.M * w.N;
-    const dim3 rgrid((unsigned)((mn / 8 + 255) / 256));
-    if (e1 != nullptr)
-        hipExtLaunchKernelGGL(splitk_reduce_kernel<false>, rgrid, dim3(256), 0, s, nullptr, e1, 0,
-                              (const float *)w.sk_workspace, splits, mn, w.s0, w.s1, 0.0f, (uint16_t *)w.out);
-    else
-        hipLaunchKernelGGL(splitk_reduce_kernel<false>, rgrid, dim3(256), 0, s, (const float *)w.sk_workspace, splits, mn,
-                           w.s0, w.s1, 0.0f, (uint16_t *)w.out);
-    return hipGetLastError();
-}
-
 // both gradient products of a layer (d: [M, K] over N, w: [N, K] over M, no penalty, no residual)
 hipError_t launch_fp8_gemm_pair(const GemmArgs &d, const GemmArgs &w, hipStream_t s)
 {
-    int splits = pair_splits(d.M, d.K, d.N);
     // one after the other the weight gradient may overwrite what only the input gradient reads
     auto overlap = [](const void *p, int64_t np, const void *q, int64_t nq) {
         return (uintptr_t)p < (uintptr_t)q + (uint64_t)nq && (uintptr_t)q < (uintptr_t)p + (uint64_t)np;
     };
-    if (overlap(w.out, w.M * w.N * 2, d.A, d.M * d.K) || overlap(w.out, w.M * w.N * 2, d.B, d.N * d.K))
-        splits = 0;
-    const bool fits = splits == 1 || (w.sk_workspace != nullptr && ((uintptr_t)w.sk_workspace & 15u) == 0 &&
-                                      w.sk_workspace_bytes >= pair_bytes(w.M, w.N, splits));
-    if (splits > 0 && fits)
-    {
-        if (splits == 1 && pair_is_small(d.M, d.K, d.N))
-            return d.a_e5m2 ? launch_pair<D64x64w4, true>(d, w, 1, s) : launch_pair<D64x64w4, false>(d, w, 1, s);
-        return d.a_e5m2 ? launch_pair<D128x128w4, true>(d, w, splits, s) : launch_pair<D128x128w4, false>(d, w, splits, s);
+    if (g_tile_override == 0 && g_stream_k_off && !overlap(w.out, w.M * w.N * 2, d.A, d.M * d.K) &&
+        !overlap(w.out, w.M * w.N * 2, d.B, d.N * d.K)) {
+        // in one launch where both grids of tiles are resident at once and that is the faster way: a launch less, and
+        // no half-empty chip (1024x1024 -> 1024 8.4 us on 64-byte stages, 6.0; 2048x1024 -> 1024 12.8, 9.2)
+        double us;
+        const int shape = ring_pair_pick(d.M, d.K, d.N, num_cus(), &us);
+        if (shape >= 0 && us < pick_split(d.M, d.N, d.K).us + pick_split(w.M, w.N, w.K).us)
+            return launch_ring_pair(d, w, shape, s);
     }
     const hipError_t e = launch_fp8_gemm(d, s);
     return e != hipSuccess ? e : launch_fp8_gemm(w, s);
@@ -2291,10 +1843,12 @@ static hipError_t launch_fp8_gemm_e5m2(const GemmArgs &a, hipStream_t s)
 {
     if (a.p != 0 || a.residual != nullptr)
         return hipErrorInvalidValue;
-    switch (resolve_variant(a)) {
+    const int v = resolve_variant(a);
+    if (ring_shape(v) >= 0)
+        return launch_ring(a, ring_shape(v), false, s);
+    switch (v) {
     case 1: return launch_tile<T256x256, false, false, true>(a, s);
     case 3: return launch_tile<T128x128, false, false, true>(a, s);
-    case 4: return launch_tile<D64x64w4, false, true, true>(a, s);
     case 6: return launch_tile<D256x256w8, false, true, true>(a, s);
     case 8: return launch_tile<D128x128w4, false, true, true>(a, s);
     case 11: return launch_stream<S256x256w8, false, 1, true>(a, s);
@@ -2315,13 +1869,18 @@ static hipError_t launch_fp8_gemm_e5m2(const GemmArgs &a, hipStream_t s)
 hipError_t launch_fp8_gemm(const GemmArgs &a, hipStream_t s)
 {
     if (a.p == 0 && a.residual == nullptr) {
-        const int splits = fp8_gemm_ksplit(a.M, a.N, a.K);
-        if (splits > 1 && a.sk_workspace != nullptr && ((uintptr_t)a.sk_workspace & 15u) == 0 &&
-            a.sk_workspace_bytes >= (size_t)splits * (size_t)a.M * (size_t)a.N * sizeof(float))
-        {
-            if (defer_ksplit(a.M, a.N, a.K) > 1)
-                return a.a_e5m2 ? launch_ksplit_defer<true>(a, s, splits) : launch_ksplit_defer<false>(a, s, splits);
-            return a.a_e5m2 ? launch_ksplit<D256x256w8, true>(a, s, splits) : launch_ksplit<D256x256w8, false>(a, s, splits);
+        const Split split = pick_split(a.M, a.N, a.K);
+        if (split.way != kWhole && a.sk_workspace != nullptr && ((uintptr_t)a.sk_workspace & 15u) == 0 &&
+            a.sk_workspace_bytes >= (size_t)split.runs * (size_t)a.M * (size_t)a.N * sizeof(float)) {
+            if (split.way == kDeferRuns)
+                return a.a_e5m2 ? launch_ksplit_defer<true>(a, s, split.runs) : launch_ksplit_defer<false>(a, s, split.runs);
+            if (split.way == kTiledRuns)
+                return a.a_e5m2 ? launch_ksplit<D256x256w8, true>(a, s, split.runs)
+                                : launch_ksplit<D256x256w8, false>(a, s, split.runs);
+            hipEvent_t e0 = nullptr, e1 = nullptr;  // a profiled launch brackets both kernels
+            take_profile_events(&e0, &e1);
+            const hipError_t e = launch_ring_ksplit(a, split.shape, split.runs, s, e0);
+            return e != hipSuccess ? e : launch_splitk_reduce<false>(a, split.runs, s, e1);
         }
     }
     return a.a_e5m2 ? launch_fp8_gemm_e5m2(a, s) : launch_gemm<false>(a, s);
@@ -2359,7 +1918,7 @@ static hipError_t launch_skinny_ring(const GemmArgs &a, hipStream_t s)
 // stage shapes: M <= 16: 512 bytes of K a stage (eight k steps, one per wave); above: 256 bytes (four
 // k steps x two parts of the M blocks; 512 where a workgroup has one block of weight rows); ring depth
 // what 160 KB of LDS allow (the depth hardly matters: two stages measured like five)
-constexpr int64_t kSkinnyMaxM = 128;  // rows of X the weight-streaming kernel takes
+constexpr int64_t kSkinnyMaxM = 64;  // rows of X the weight-streaming kernel takes
 static hipError_t launch_skinny_ring_any(const GemmArgs &a, hipStream_t s)
 {
     const int64_t blocks = (a.N + 15) / 16, cus = num_cus();
@@ -2382,55 +1941,34 @@ static hipError_t launch_skinny_ring_any(const GemmArgs &a, hipStream_t s)
             return launch_skinny_ring<2, 3, 4, 6>(a, s);
         return launch_skinny_ring<2, 4, 4, 6>(a, s);
     }
-    if (a.M <= 64) {
-        if (per <= 1)  // 512-byte stages: half as many barriers (11008 -> 4096 at M = 64: 18.0 -> 16.7 us)
-            return launch_skinny_ring<4, 1, 8, 3>(a, s);
-        if (per == 2)
-            return launch_skinny_ring<4, 2, 4, 6>(a, s);
-        if (per == 3)
-            return launch_skinny_ring<4, 3, 4, 5>(a, s);
-        return launch_skinny_ring<4, 4, 4, 4>(a, s);
-    }
-    if (a.M > 128)  // up to 256 rows for one block of weight rows per workgroup (see launch_i8_gemm)
-        return a.M <= 192 ? launch_skinny_ring<12, 1, 4, 3>(a, s) : launch_skinny_ring<16, 1, 4, 2>(a, s);
-    // 64 < M <= 128: eight blocks of 16 rows of X beside the weight rows, 256-byte stages
-    if (per <= 1)
-        return launch_skinny_ring<8, 1, 4, 4>(a, s);
+    if (per <= 1)  // 512-byte stages: half as many barriers (11008 -> 4096 at M = 64: 18.0 -> 16.7 us)
+        return launch_skinny_ring<4, 1, 8, 3>(a, s);
     if (per == 2)
-        return launch_skinny_ring<8, 2, 4, 4>(a, s);
+        return launch_skinny_ring<4, 2, 4, 6>(a, s);
     if (per == 3)
-        return launch_skinny_ring<8, 3, 4, 3>(a, s);
-    return launch_skinny_ring<8, 4, 4, 3>(a, s);
+        return launch_skinny_ring<4, 3, 4, 5>(a, s);
+    return launch_skinny_ring<4, 4, 4, 4>(a, s);
 }
 
 hipError_t launch_i8_gemm(const GemmArgs &a, hipStream_t s)
 {
-    // small M: the weight-streaming kernel (forced tiled variants keep the tiled kernels, for
-    // tests; 17 forces this one).  Measured cold at the 7B shapes, kernel time in us for M = 1 /
-    // 16 / 32 / 64 / 128: 4096 -> 12288: 10.7 / 11.3 / 13.0 / 15.6 / 19.6, 11008 -> 4096: 10.2 / 10.8 /
-    // 14.1 / 16.8 / 27.0 (a plain read of the 45-50 MB of weights by one kernel takes 10.2-11.1; the
-    // tiled kernels at M = 128: 27 and 66).
-    if ((g_tile_override == 0 || g_tile_override == 17) && a.M <= kSkinnyMaxM && a.K % 64 == 0 && a.N % 4 == 0)
+    // Small M: the weight-streaming kernel (forced tiled variants keep the tiled kernels, for tests; 17 forces
+    // this one).  Up to 16 rows it pulls the weights at what one short kernel can (4096 -> 12288 10.7 us, 11008 ->
+    // 4096 10.2; a plain read of them 10.2-11.1).  From 17 rows on, the ring kernel's 64x64 tiles, where the output
+    // has them for a third of the CUs (call, cold, us, streaming / ring: 4096 -> 12288 at M = 48 / 64 14.1 / 13.5,
+    // 15.0 / 14.0; 2048 -> 5632 at M = 32 / 64 6.6 / 6.0, 7.3 / 6.1; with 64 and 32 tiles the stream is ahead:
+    // 11008 -> 4096 at M = 64 18.2 / 29.0, 5632 -> 2048 9.2 / 10.2); above 64 rows the ring kernel throughout (M =
+    // 128, 4096 -> 11008 18.7 / 18.0, 11008 -> 4096 29.1 / 28.0, 5632 -> 2048 15.2 / 10.3, 2048 -> 5632 9.4 / 6.2).
+    const bool streaming = a.M <= 16 || (a.M <= kSkinnyMaxM && 3 * ((a.N + 63) / 64) < num_cus());
+    if (((g_tile_override == 0 && streaming) || (g_tile_override == 17 && a.M <= kSkinnyMaxM)) && a.K % 64 == 0 && a.N % 4 == 0)
         return launch_skinny_ring_any(a, s);
-    // up to 256 rows into a projection of at most one block of 16 weight rows per CU under a long
-    // contraction (11008 -> 4096: 16 tiles of 256x256): still the weight stream, unless the K split
-    // below applies (M = 256 with a workspace)
-    if ((g_tile_override == 0 || g_tile_override == 17) && a.M <= 256 && a.K % 64 == 0 && a.N % 4 == 0 &&
-        a.K >= 8192 && (a.N + 15) / 16 <= num_cus() &&
-        !(a.row_step == nullptr && !a.out_i8 && defer_ksplit(a.M, a.N, a.K) > 1 && a.sk_workspace != nullptr &&
-          a.sk_workspace_bytes >= (size_t)defer_ksplit(a.M, a.N, a.K) * (size_t)a.M * (size_t)a.N * sizeof(int32_t)))
-        return launch_skinny_ring_any(a, s);
-    // few whole 256x256 tiles under a long contraction (prefill chunks of a few hundred tokens into
-    // a narrow projection): the K split of the deferred-epilogue kernel, int32 runs added exactly
+    // few whole 256x256 tiles under a long contraction (prefill chunks into a narrow projection): the K
+    // split of the deferred-epilogue kernel, int32 runs added exactly
     if (a.row_step == nullptr && !a.out_i8) {
-        const int splits = defer_ksplit(a.M, a.N, a.K);
+        const int splits = i8_defer_ksplit(a.M, a.N, a.K);
         if (splits > 1 && a.sk_workspace != nullptr && ((uintptr_t)a.sk_workspace & 15u) == 0 &&
             a.sk_workspace_bytes >= (size_t)splits * (size_t)a.M * (size_t)a.N * sizeof(int32_t))
             return launch_ksplit_defer<false, true>(a, s, splits);
-        const int runs = i8_dma_ksplit(a.M, a.N, a.K);
-        if (runs > 1 && a.sk_workspace != nullptr && ((uintptr_t)a.sk_workspace & 15u) == 0 &&
-            a.sk_workspace_bytes >= (size_t)runs * (size_t)a.M * (size_t)a.N * sizeof(int32_t))
-            return launch_ksplit<D128x128w4, false, true>(a, s, runs);
     }
     return launch_gemm<true>(a, s);
 }

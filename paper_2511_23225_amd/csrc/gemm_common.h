@@ -1,6 +1,8 @@
 // Pieces shared by the 8-bit GEMM kernels (gfx950).
 #pragma once
+#include <hip/hip_ext.h>
 #include <type_traits>
+#include <utility>
 #include "kernels.h"
 #include "device_utils.h"
 
@@ -36,6 +38,13 @@ struct GemmDev {
     float *ksplit_out;
     int through;  // the output is written through the L2s (store_through)
 };
+
+// calls f(integral_constant<int, 0>), f(integral_constant<int, 1>), ... in order
+template <typename F, int... Is>
+__device__ __forceinline__ void for_each_constant(std::integer_sequence<int, Is...>, F &f)
+{
+    (f(std::integral_constant<int, Is>{}), ...);
+}
 
 // raster of tile ids: groups of 8 tile rows, column-major inside a group
 __device__ __forceinline__ void tile_from_id(int id, int tiles_m, int tiles_n, int &tm, int &tn)
@@ -128,6 +137,58 @@ __device__ __forceinline__ void block_barrier()
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
+}
+
+// ---- host side
+template <typename KERNEL, typename... ARGS>
+static inline void launch_gemm_kernel(KERNEL kernel, dim3 grid, dim3 block, size_t lds, hipStream_t s, ARGS... args)
+{
+    hipEvent_t e0, e1;
+    if (take_profile_events(&e0, &e1)) {
+        hipExtLaunchKernelGGL(kernel, grid, block, lds, s, e0, e1, 0, args...);
+    } else {
+        hipLaunchKernelGGL(kernel, grid, block, lds, s, args...);
+    }
+}
+
+// Outputs that the tiled kernels' epilogue writes through the L2s (store_through): whole lines, 4 to 16 MB.  What
+// is dirty when a kernel ends is written back before the next one starts (2.4 us to it instead of 1.0 at 12
+// MB).  us, dirty / through: 8192x768 under 768 9.2 / 8.3, under 3072 22.4 / 20.7; 4096x1024 under 1024 9.1 / 8.5;
+// 2048x2048 under 2048 13.7 / 13.2.  Larger ones do not gain: 8192x2304 under 768 25.4 / 25.6, with the
+// penalty 29.7 / 29.9; 4096x4096 under 1024 with the penalty 23.2 / 23.5.
+static inline int writes_through(int64_t M, int64_t N)
+{
+    return N % 64 == 0 && M * N >= ((int64_t)1 << 21) && M * N <= ((int64_t)1 << 23);
+}
+
+// the fields every launch of an unsplit product fills (bm, bn: its tiles)
+static inline GemmDev gemm_dev(const GemmArgs &a, int bm, int bn)
+{
+    GemmDev g{};
+    g.A = a.A;
+    g.B = a.B;
+    g.M = (int)a.M;
+    g.N = (int)a.N;
+    g.K = (int)a.K;
+    g.s0 = a.s0;
+    g.s1 = a.s1;
+    g.alpha = a.alpha;
+    g.residual = (const uint16_t *)a.residual;
+    g.out = (uint16_t *)a.out;
+    g.inv_tau = a.inv_tau;
+    g.p = a.p;
+    g.partials = a.partials;
+    g.rs = a.row_step;
+    g.cs = a.col_step;
+    g.rs_stride = a.row_step_stride;
+    g.cs_stride = a.col_step_stride;
+    g.out_i8 = a.out_i8 ? 1 : 0;
+    g.out_inv_step = a.out_inv_step;
+    g.ksplit = 1;
+    g.through = writes_through(a.M, a.N);
+    g.tiles_m = (int)((a.M + bm - 1) / bm);
+    g.tiles_n = (int)((a.N + bn - 1) / bn);
+    return g;
 }
 
 }  // namespace tweo

@@ -147,13 +147,6 @@ struct DrainPlanOf {  // evaluated once per tile shape and D, not once per slot 
 // PMODE: 4 = TWEO penalty with p = 4 (the paper's setting), 0 = none.  D: number of stages of
 // the next tile over which the write-out of a tile is spread (3, 5, 7 or 15; needs K >= 128 * (D + 1):
 // the tile's last stage, which converts its own blocks, takes no part in it).
-// calls f(integral_constant<int, 0>), f(integral_constant<int, 1>), ... in order
-template <typename F, int... Is>
-__device__ __forceinline__ void for_each_constant(std::integer_sequence<int, Is...>, F &f)
-{
-    (f(std::integral_constant<int, Is>{}), ...);
-}
-
 // A_E5M2 (FP8 only): the A operand holds E5M2 codes (the gradient of the HYBRID recipe, Sec. 4.3);
 // B is always E4M3.  The MFMA takes the format of each source from a modifier.
 // LINES: the write-out regroups the packed values among lanes first, so that the four lanes of a

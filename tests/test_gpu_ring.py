@@ -1,0 +1,101 @@
+"""The ring GEMM (128-byte stages in a deep ring, one tile per workgroup): every tile shape against the oracle where
+it can go wrong - edges of tiles, fewer stages than the ring, one more, contractions that end inside a stage -
+in every operand format and with everything its way out can do; runs of a K split; both gradients in one launch."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2511_23225_amd as tw
+from paper_2511_23225_amd import synth
+from gpu_util import DEV, PEN, to_dev, bf16_bits, scalar_f32, workspace, check_gemm, check_penalty
+from test_gpu_fp8_linear import run_fwd, oracle_quantized, check_bwd_pair
+from test_gpu_w8a8_rows import run_scaled
+
+pytestmark = pytest.mark.gpu
+
+# 64x64, 64x64 and 64x128 in two groups of waves, 64x128, 128x128, 96x128; stages in the ring: 4, 8, 3, 6, 4, 5
+RING = [4, 18, 19, 20, 21, 22]
+
+
+def say(*a):
+    print(*a, flush=True)
+
+
+@pytest.fixture
+def tile(request):
+    tw.tweo_set_gemm_tile(request.param)
+    yield request.param
+    tw.tweo_set_gemm_tile(0)
+
+
+# one chunk, one stage, inside the second, as many stages as each ring has and one more, many; rows and columns
+# on the edges of tiles and just past them
+@pytest.mark.parametrize("tile", RING, indirect=True)
+@pytest.mark.parametrize("shape", [(64, 64, 16), (1, 8, 128), (96, 128, 144), (128, 128, 384), (129, 136, 512), (97, 264, 528),
+                                   (200, 520, 640), (192, 192, 784), (65, 72, 1024), (256, 128, 1152), (130, 200, 2064)])
+def test_forward(shape, tile):
+    M, N, K = shape
+    say("ring fwd M=%d N=%d K=%d tile=%d" % (M, N, K, tile))
+    x, w, _ = synth.fp8_linear_inputs(1, 0, M=M, K=K, N=N)
+    xq, _, sxi = oracle_quantized(x)
+    wq, _, swi = oracle_quantized(w)
+    for res, pen in ((None, None), (None, PEN), (synth.residual_input(1, 0, M, N), PEN), (None, (2.0, 0.5, 3))):
+        ref, refabs, refbf = oracle.fp8_linear_fwd(xq, wq, sxi, swi, residual=res)
+        got, S = run_fwd(xq, wq, sxi, swi, M, N, K, residual=res, pen=pen)
+        check_gemm(got, ref, refabs, K, "fwd")
+        if pen:
+            check_penalty(S, got, refbf, oracle.penalty_sum(refbf, *pen), pen, strict=False)
+
+
+@pytest.mark.parametrize("tile", RING, indirect=True)
+@pytest.mark.parametrize("K", [48, 144, 1040, 1056])
+def test_a_nan_stays_in_its_column(K, tile):
+    # in the chunk that stands in for those past a contraction's end
+    M, N = 70, 136
+    say("ring NaN K=%d tile=%d" % (K, tile))
+    x, w, _ = synth.fp8_linear_inputs(1, 0, M=M, K=K, N=N)
+    xq, _, sxi = oracle_quantized(x)
+    wq = oracle_quantized(w)[0].copy()
+    wq[5, 0] = 0x7F
+    got, _ = run_fwd(xq, wq, sxi, np.float32(1.0), M, N, K, pen=None)
+    val = (got.astype(np.uint32) << 16).view(np.float32)
+    assert np.isnan(val[:, 5]).all() and not np.isnan(np.delete(val, 5, axis=1)).any()
+
+
+@pytest.mark.parametrize("tile", RING, indirect=True)
+@pytest.mark.parametrize("shape", [(65, 72, 1040), (129, 264, 528), (96, 128, 1152), (40, 136, 80)])
+def test_int8(shape, tile):
+    M, N, K = shape
+    say("ring INT8 M=%d N=%d K=%d tile=%d" % (M, N, K, tile))
+    rng = np.random.default_rng(M + K)
+    xq, wq = (rng.integers(-127, 128, (n, K), dtype=np.int8) for n in (M, N))
+    y = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device=DEV)
+    tw.tweo_w8a8_linear(to_dev(xq), to_dev(wq), 0.001, y)
+    torch.cuda.synchronize()
+    assert np.array_equal(bf16_bits(y), oracle.w8a8_linear(xq, wq, 0.001))
+    sx, sw = (rng.uniform(1e-3, 1e-2, n).astype(np.float32) for n in (M, N))
+    assert np.array_equal(run_scaled(xq, wq, sx, sw, tile), oracle.w8a8_linear_scaled(xq, wq, sx, sw))
+    tw.tweo_set_gemm_tile(tile)
+    out = torch.zeros((M, N), dtype=torch.int8, device=DEV)
+    tw.tweo_w8a8_linear_scaled_i8out(to_dev(xq), to_dev(wq), to_dev(sx), to_dev(sw), 0.7, out)
+    torch.cuda.synchronize()
+    assert np.array_equal(out.cpu().numpy(), oracle.w8a8_linear_scaled_i8out(xq, wq, sx, sw, np.float32(0.7)))
+
+
+@pytest.mark.parametrize("tile", RING, indirect=True)
+@pytest.mark.parametrize("shape", [(208, 272, 144), (1040, 128, 264)])
+def test_e5m2_gradients(shape, tile):
+    M, N, K = shape
+    say("ring E5M2 M=%d N=%d K=%d tile=%d" % (M, N, K, tile))
+    check_bwd_pair(shape, True)
+
+
+# default dispatch: runs of small tiles under a long contraction (a stage count they do not divide, ragged
+# rows, a tile and a bit), and both products in one launch on each shape that takes pairs
+@pytest.mark.parametrize("hybrid", [False, True])
+@pytest.mark.parametrize("shape", [(8576, 256, 256), (20480, 256, 256), (16400, 272, 264), (12288, 512, 512),
+                                   (256, 512, 512), (1024, 512, 1024), (2048, 1024, 1024), (4096, 704, 512), (672, 768, 3072),
+                                   (1552, 1040, 2064), (4096, 3072, 768)])
+def test_backward(shape, hybrid):
+    check_bwd_pair(shape, hybrid)
