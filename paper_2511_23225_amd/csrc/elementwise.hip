@@ -7,6 +7,7 @@
 #include <type_traits>
 #include "kernels.h"
 #include "device_utils.h"
+#include "finish.h"
 
 namespace tweo {
 
@@ -1112,8 +1113,10 @@ struct QuantTensor {
 
 template <bool THROUGH>
 __global__ __launch_bounds__(kQuantThreads) void cast2_tile_kernel(QuantTensor t0, int64_t blocks0,
-                                                                             QuantTensor t1)
+                                                                             QuantTensor t1, double *clear)
 {
+    if (clear != nullptr && blockIdx.x == 0 && threadIdx.x == 0)
+        *clear = 0.0;
     const bool first = (int64_t)blockIdx.x < blocks0;
     const QuantTensor &t = first ? t0 : t1;
     cast_tile_body<true, false, false, 0, false, true, THROUGH>(t.x, t.rows, t.cols, t.tiles_x, t.amax, t.q, t.qT, t.scale_out,
@@ -1126,7 +1129,7 @@ hipError_t launch_quantize2_e4m3(const void *x0_bf16, int64_t rows0, int64_t col
                                  uint8_t *q0T, float *scale0, float *scale0_inv, const void *x1_bf16,
                                  int64_t rows1, int64_t cols1, float *amax1, uint8_t *q1, uint8_t *q1T,
                                  float *scale1, float *scale1_inv, hipStream_t s, const uint32_t *partials0,
-                                 int n_partials0, const uint32_t *partials1, int n_partials1)
+                                 int n_partials0, const uint32_t *partials1, int n_partials1, double *clear)
 {
     auto tiles = [](int64_t v) { return (v + kTile - 1) / kTile; };
     QuantTensor t0{(const uint16_t *)x0_bf16, rows0, cols0, walk_width(rows0, cols0, true), amax0, q0, q0T, scale0, scale0_inv,
@@ -1135,9 +1138,9 @@ hipError_t launch_quantize2_e4m3(const void *x0_bf16, int64_t rows0, int64_t col
                    partials1, n_partials1, amax1};
     const int64_t b0 = tiles(rows0) * t0.tiles_x, b1 = tiles(rows1) * t1.tiles_x;
     if (writes_through(rows0 | rows1, cols0 | cols1, b0 + b1, kThroughTiles))
-        hipLaunchKernelGGL(cast2_tile_kernel<true>, dim3((unsigned)(b0 + b1)), dim3(kQuantThreads), 0, s, t0, b0, t1);
+        hipLaunchKernelGGL(cast2_tile_kernel<true>, dim3((unsigned)(b0 + b1)), dim3(kQuantThreads), 0, s, t0, b0, t1, clear);
     else
-        hipLaunchKernelGGL(cast2_tile_kernel<false>, dim3((unsigned)(b0 + b1)), dim3(kQuantThreads), 0, s, t0, b0, t1);
+        hipLaunchKernelGGL(cast2_tile_kernel<false>, dim3((unsigned)(b0 + b1)), dim3(kQuantThreads), 0, s, t0, b0, t1, clear);
     return hipGetLastError();
 }
 
@@ -1731,41 +1734,6 @@ __global__ void delayed_state_init_kernel(uint32_t *st)
         st[i] = (i == 17 || i == 18 || i == 21 || i == 22) ? f32_to_bits(1.0f) : 0u;
 }
 
-// Consumes the accumulated amax: remembers the scale that was just used, pushes the amax into
-// the ring, derives the next scale, clears the accumulator.  sc_out (optional): three fp32 of the
-// caller's: this tensor's amax, the scale its cast uses / used, and its inverse.  given (optional): the
-// tensor's amax, instead of the accumulated one.
-// One wave, lane i holds word i: one load and one store of the state.  (A single thread's chain of loads and
-// stores took 2.5 us more: this launch is all latency.)
-__device__ __forceinline__ void delayed_state_update(uint32_t *st, int bootstrap, float range, float *sc_out,
-                                                     const uint32_t *given = nullptr)
-{
-    const int lane = threadIdx.x & (kWave - 1);
-    const uint32_t v = lane < 32 ? st[lane] : 0u;
-    auto word = [&](int i) { return (uint32_t)__builtin_amdgcn_readlane((int)v, i); };
-    const uint32_t mine = given != nullptr ? *given : word(16);
-    const int pos = (int)word(19), filled = (int)word(20);
-    const uint32_t h = lane == (pos & 15) ? mine : v;  // the ring with this amax in it
-    // magnitude patterns order like unsigned integers (NaN on top)
-    const uint32_t m = wave_reduce_max_u32(lane < 16 ? h : 0u);
-    const float scale = scale_from_amax_range(bits_to_f32(m), range);  // 448 (E4M3) or 57344 (E5M2)
-    const uint32_t next = f32_to_bits(scale), next_inv = f32_to_bits(1.0f / scale);
-    // a bootstrap cast has not happened yet: it uses the new scale
-    const uint32_t used = bootstrap ? next : word(17), used_inv = bootstrap ? next_inv : word(18);
-    uint32_t w = h;
-    w = lane == 16 ? 0u : w;
-    w = lane == 17 ? next : w;
-    w = lane == 18 ? next_inv : w;
-    w = lane == 19 ? (uint32_t)((pos + 1) & 15) : w;
-    w = lane == 20 ? (uint32_t)(filled < 16 ? filled + 1 : 16) : w;
-    w = lane == 21 ? used : w;
-    w = lane == 22 ? used_inv : w;
-    if (lane < 23)
-        st[lane] = w;
-    if (sc_out != nullptr && lane < 3)
-        sc_out[lane] = bits_to_f32(lane == 0 ? mine : lane == 1 ? used : used_inv);
-}
-
 __global__ __launch_bounds__(kWave) void delayed_state_update_kernel(uint32_t *st, int bootstrap, float range,
                                                                      const uint32_t *partials = nullptr,
                                                                      int n_partials = 0, float *sc_out = nullptr)
@@ -1852,8 +1820,11 @@ struct QuantTensorDelayed {
 };
 
 __global__ __launch_bounds__(kQuantThreads) void cast2_delayed_tile_kernel(QuantTensorDelayed t0, int64_t blocks0,
-                                                                                QuantTensorDelayed t1, int64_t blocks1)
+                                                                                QuantTensorDelayed t1, int64_t blocks1,
+                                                                                double *clear)
 {
+    if (clear != nullptr && blockIdx.x == 0 && threadIdx.x == 0)
+        *clear = 0.0;
     const bool first = (int64_t)blockIdx.x < blocks0;
     const QuantTensorDelayed &t = first ? t0 : t1;
     cast_tile_body<true, true, false, 0, false, true>(t.x, t.rows, t.cols, t.tiles_x, t.scale, t.q, t.qT, nullptr, nullptr, t.amax_acc,
@@ -1864,7 +1835,7 @@ __global__ __launch_bounds__(kQuantThreads) void cast2_delayed_tile_kernel(Quant
 hipError_t launch_quantize2_e4m3_delayed(const void *x0_bf16, int64_t rows0, int64_t cols0, void *state0, uint8_t *q0,
                                          uint8_t *q0T, float *sc0, const void *x1_bf16, int64_t rows1, int64_t cols1,
                                          void *state1, uint8_t *q1, uint8_t *q1T, float *sc1, int bootstrap,
-                                         hipStream_t s)
+                                         hipStream_t s, double *clear)
 {
     // (not bootstrap: the caller launches the states' update)
     if (bootstrap) {  // empty histories: each tensor's own amax first (once per state)
@@ -1884,7 +1855,7 @@ hipError_t launch_quantize2_e4m3_delayed(const void *x0_bf16, int64_t rows0, int
     b1 = b1 < 1 ? 1 : (b1 > n1 ? n1 : b1);
     int64_t b0 = n_wg - b1;
     b0 = b0 < 1 ? 1 : (b0 > n0 ? n0 : b0);
-    hipLaunchKernelGGL(cast2_delayed_tile_kernel, dim3((unsigned)(b0 + b1)), dim3(kQuantThreads), 0, s, t0, b0, t1, b1);
+    hipLaunchKernelGGL(cast2_delayed_tile_kernel, dim3((unsigned)(b0 + b1)), dim3(kQuantThreads), 0, s, t0, b0, t1, b1, clear);
     return hipGetLastError();
 }
 
@@ -2155,38 +2126,21 @@ hipError_t launch_penalty_grad_inject(const void *dy_bf16, const void *a_bf16, i
 }
 
 // ---------------------------------------------------------------------------
-// Penalty finish: sums the per-workgroup fp32 partials in a fixed order in fp64.
-constexpr int kFinishThreads = 256;
-
-__device__ __forceinline__ void penalty_finish(const float *__restrict__ partials, int n, double *out)
-{
-    __shared__ double red[kFinishThreads];
-    double s = 0.0;
-    for (int i = threadIdx.x; i < n; i += kFinishThreads)
-        s += (double)partials[i];
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = kFinishThreads / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w)
-            red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0)
-        *out = red[0];
-}
-
+// Penalty finish
 __global__ __launch_bounds__(kFinishThreads) void penalty_finish_kernel(const float *__restrict__ partials, int n,
                                                                         double *out)
 {
-    penalty_finish(partials, n, out);
+    __shared__ double red[kFinishThreads];
+    penalty_finish(partials, n, out, red);
 }
 
 // ... and the update of two delayed-scaling states in the same launch
 __global__ __launch_bounds__(kFinishThreads) void penalty_finish_update2_kernel(const float *__restrict__ partials, int n,
                                                                                 double *out, DelayedUpdate2 u)
 {
+    __shared__ double red[kFinishThreads];
     if (blockIdx.x == 0)
-        penalty_finish(partials, n, out);
+        penalty_finish(partials, n, out, red);
     else if (threadIdx.x < kWave)
         delayed_state_update(blockIdx.x == 1 ? u.st0 : u.st1, 0, 448.0f, blockIdx.x == 1 ? u.sc0 : u.sc1);
 }

@@ -1427,6 +1427,12 @@ int fp8_gemm_partials(const GemmArgs &a)
 }
 
 
+bool fp8_gemm_finishes(const GemmArgs &a)
+{
+    const int v = resolve_variant(a);
+    return a.p != 0 && !a.a_e5m2 && ring_shape(v) >= 0 && fp8_gemm_partials(a) <= num_cus();
+}
+
 template <typename T, bool INT8, bool DMA, bool A_E5M2, bool RAGGED>
 static hipError_t launch_tile_inst(const GemmArgs &a, hipStream_t s)
 {

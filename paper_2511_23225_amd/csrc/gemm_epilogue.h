@@ -219,7 +219,7 @@ __device__ __forceinline__ void epilogue_impl(const GemmDev &g, ACC (&acc)[T::MT
 #pragma unroll
             for (int w = 0; w < T::THREADS / kWave; ++w)
                 s += red[w];
-            g.partials[partial_index] = s;
+            __hip_atomic_store(g.partials + partial_index, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
 }

@@ -19,6 +19,7 @@
 #include <utility>
 #include "gemm_common.h"
 #include "gemm_epilogue.h"
+#include "finish.h"
 
 namespace tweo {
 
@@ -39,11 +40,37 @@ struct TileR {
     static_assert(LDS_BYTES < 160 * 1024, "LDS capacity (with the epilogue's few words)");
 };
 
+// The penalty's end without a launch of its own, which would cost 3 us and more behind a kernel of 4 to 10.  Nobody
+// waits: every workgroup's partial sum is in memory before it counts itself, and the one that finds all others
+// counted adds them, in the order of the finishing kernel.  The counter is the low word of the result, which
+// the cast in front has cleared.  Up to one workgroup per CU: more of them queue up at the word.
+struct RingFinish {
+    double *sum;  // or nullptr
+    DelayedUpdate2 update;
+};
+__device__ __forceinline__ void ring_finish(const float *partials, const RingFinish &fin, uint8_t *smem, int workgroups,
+                                            int wave)
+{
+    __syncthreads();  // every wave is done with its staging
+    int *last = (int *)(smem + kFinishThreads * sizeof(double));
+    if (threadIdx.x == 0) {
+        wait_vmcnt<0>();  // this thread's store of the partial sum has been performed
+        *last = __hip_atomic_fetch_add((uint32_t *)fin.sum, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+                (uint32_t)workgroups - 1u;
+    }
+    __syncthreads();
+    if (*last == 0)
+        return;
+    penalty_finish<true>(partials, workgroups, fin.sum, (double *)smem);
+    if (fin.update.st0 != nullptr && wave < 2)
+        delayed_state_update(wave == 0 ? fin.update.st0 : fin.update.st1, 0, 448.0f, wave == 0 ? fin.update.sc0 : fin.update.sc1);
+}
+
 // KSPLIT: the grid is g.ksplit runs of the tile grid, run r multiplies its share of the stages and leaves fp32
 // (INT8: int32) sums in g.ksplit_out.  RAGGED: K may be no multiple of 128 (one of 16).  block: the workgroup's
 // number in g's grid.
-template <typename T, bool INT8, bool A_E5M2, bool KSPLIT, bool RAGGED>
-__device__ __forceinline__ void gemm_nt_ring_body(const GemmDev &g, const int block)
+template <typename T, bool INT8, bool A_E5M2, bool KSPLIT, bool RAGGED, bool FINISH>
+__device__ __forceinline__ void gemm_nt_ring_body(const GemmDev &g, const int block, const RingFinish &fin)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
@@ -271,13 +298,16 @@ __device__ __forceinline__ void gemm_nt_ring_body(const GemmDev &g, const int bl
     } else {
         NoBandHook no_hook;
         epilogue<Out, INT8>(g, acc, smem, tm, tn, wm, wn, lane, w, tid, block, no_hook, alpha);
+        if constexpr (FINISH)
+            if (fin.sum != nullptr)
+                ring_finish(g.partials, fin, smem, n_tiles, w);
     }
 }
 
 template <typename T, bool INT8, bool A_E5M2, bool KSPLIT, bool RAGGED>
-__global__ __launch_bounds__(T::THREADS, T::WG_PER_CU *T::NWAVES / 4) void gemm_nt_ring_kernel(GemmDev g)
+__global__ __launch_bounds__(T::THREADS, T::WG_PER_CU *T::NWAVES / 4) void gemm_nt_ring_kernel(GemmDev g, RingFinish fin)
 {
-    gemm_nt_ring_body<T, INT8, A_E5M2, KSPLIT, RAGGED>(g, (int)blockIdx.x);
+    gemm_nt_ring_body<T, INT8, A_E5M2, KSPLIT, RAGGED, !INT8 && !A_E5M2 && !KSPLIT>(g, (int)blockIdx.x, fin);
 }
 
 // The two products of a linear layer's backward in one launch: workgroups [0, n0) are the grid of g0,
@@ -291,7 +321,7 @@ __global__ __launch_bounds__(T::THREADS, T::WG_PER_CU *T::NWAVES / 4) void gemm_
     if (b >= n0 && b < n0_padded)
         return;
     const bool first = b < n0;
-    gemm_nt_ring_body<T, false, A_E5M2, false, RAGGED>(first ? g0 : g1, first ? b : b - n0_padded);
+    gemm_nt_ring_body<T, false, A_E5M2, false, RAGGED, false>(first ? g0 : g1, first ? b : b - n0_padded, RingFinish{});
 }
 
 }  // namespace tweo

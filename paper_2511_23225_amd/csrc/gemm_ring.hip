@@ -135,7 +135,8 @@ static hipError_t launch_inst(const GemmArgs &a, hipStream_t s)
     if (e != hipSuccess)
         return e;
     const GemmDev g = gemm_dev(a, T::BM, T::BN);
-    launch_gemm_kernel(kernel, dim3((unsigned)(g.tiles_m * g.tiles_n)), dim3(T::THREADS), T::LDS_BYTES, s, g);
+    const RingFinish fin{a.finish, a.update != nullptr ? *a.update : DelayedUpdate2{}};
+    launch_gemm_kernel(kernel, dim3((unsigned)(g.tiles_m * g.tiles_n)), dim3(T::THREADS), T::LDS_BYTES, s, g, fin);
     return hipGetLastError();
 }
 
@@ -176,9 +177,9 @@ static hipError_t launch_ksplit_inst(const GemmArgs &a, int runs, hipStream_t s,
     g.ksplit_out = (float *)a.sk_workspace;
     const dim3 grid((unsigned)(g.tiles_m * g.tiles_n * runs)), block(T::THREADS);
     if (start != nullptr)
-        hipExtLaunchKernelGGL(kernel, grid, block, T::LDS_BYTES, s, start, nullptr, 0, g);
+        hipExtLaunchKernelGGL(kernel, grid, block, T::LDS_BYTES, s, start, nullptr, 0, g, RingFinish{});
     else
-        hipLaunchKernelGGL(kernel, grid, block, T::LDS_BYTES, s, g);
+        hipLaunchKernelGGL(kernel, grid, block, T::LDS_BYTES, s, g, RingFinish{});
     return hipGetLastError();
 }
 

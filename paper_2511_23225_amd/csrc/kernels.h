@@ -15,13 +15,13 @@ hipError_t launch_amax2(const void *x0_bf16, int64_t n0, float *amax0_zeroed, co
                         float *amax1_zeroed, hipStream_t s);
 // two tensors (rows and cols multiples of 16), each with its transposed copy, in one launch; with
 // partials (from launch_amax2_partials) each workgroup first takes the maximum over them and
-// workgroup 0 stores it to *amax, else *amax is read
+// workgroup 0 stores it to *amax, else *amax is read; *clear (optional) is set to 0
 hipError_t launch_quantize2_e4m3(const void *x0_bf16, int64_t rows0, int64_t cols0, float *amax0, uint8_t *q0,
                                  uint8_t *q0T, float *scale0, float *scale0_inv, const void *x1_bf16,
                                  int64_t rows1, int64_t cols1, float *amax1, uint8_t *q1, uint8_t *q1T,
                                  float *scale1, float *scale1_inv, hipStream_t s,
                                  const uint32_t *partials0 = nullptr, int n_partials0 = 0,
-                                 const uint32_t *partials1 = nullptr, int n_partials1 = 0);
+                                 const uint32_t *partials1 = nullptr, int n_partials1 = 0, double *clear = nullptr);
 // amax without a cleared output and without atomics: one maximum (fp32 bit pattern) per workgroup
 // into partials[0 .. *blocks), at most kAmaxPartialsMax of them per tensor
 constexpr int kAmaxPartialsMax = 512;
@@ -75,7 +75,7 @@ hipError_t launch_delayed_update2(const DelayedUpdate2 &u, hipStream_t s);
 hipError_t launch_quantize2_e4m3_delayed(const void *x0_bf16, int64_t rows0, int64_t cols0, void *state0, uint8_t *q0,
                                          uint8_t *q0T, float *sc0, const void *x1_bf16, int64_t rows1, int64_t cols1,
                                          void *state1, uint8_t *q1, uint8_t *q1T, float *sc1, int bootstrap,
-                                         hipStream_t s);
+                                         hipStream_t s, double *clear = nullptr);
 // LayerNorm of x (or of h = bf16(x + res), stored to h_out) followed by the per-tensor E4M3 cast of
 // the normalised tensor; state == nullptr: current scaling (amax_out required), else delayed
 // scaling on that state.  stats: 2 doubles per row, partials: kAmaxPartialsMax words of scratch.
@@ -114,6 +114,8 @@ struct GemmArgs {
     float inv_tau;          // 1 / (tau + eps)
     int p;                  // penalty power; 0 = no penalty
     float *partials;        // one fp32 per workgroup when p != 0
+    double *finish;         // the penalty's sum, 0 before the launch, if the launch is to finish it (fp8_gemm_finishes)
+    const DelayedUpdate2 *update;  // two states to update with it, or nullptr
     bool a_e5m2;            // FP8 only: A holds E5M2 codes (B is always E4M3)
     void *sk_workspace;     // stream-K scratch (256-byte aligned) or nullptr: then no stream-K
     size_t sk_workspace_bytes;
@@ -140,6 +142,8 @@ hipError_t launch_ring_pair(const GemmArgs &dgrad, const GemmArgs &wgrad, int sh
 // Number of fp32 penalty partials the FP8 GEMM writes for these arguments.
 int fp8_gemm_partials(const GemmArgs &a);
 hipError_t launch_fp8_gemm(const GemmArgs &a, hipStream_t s);
+// whether the kernel these arguments run on can finish the penalty itself
+bool fp8_gemm_finishes(const GemmArgs &a);
 hipError_t launch_i8_gemm(const GemmArgs &a, hipStream_t s);
 // the two gradient products of a linear layer, in one launch where that is the faster way
 hipError_t launch_fp8_gemm_pair(const GemmArgs &dgrad, const GemmArgs &wgrad, hipStream_t s);

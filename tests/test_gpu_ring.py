@@ -99,3 +99,30 @@ def test_e5m2_gradients(shape, tile):
                                    (1552, 1040, 2064), (4096, 3072, 768)])
 def test_backward(shape, hybrid):
     check_bwd_pair(shape, hybrid)
+
+
+# the penalty finished by the last workgroup of the GEMM (up to one workgroup per CU, behind a cast that clears its sum)
+# against the finishing kernel on the same codes: the same bits, call after call, over a poisoned sum
+@pytest.mark.parametrize("shape", [(16, 16, 64), (256, 512, 512), (1024, 1024, 256), (1040, 1024, 256), (2048, 1024, 1024),
+                                   (816, 608, 2064), (2048, 2048, 256)])
+def test_penalty_finished_by_the_last_workgroup(shape):
+    M, N, K = shape
+    say("ring penalty finish M=%d N=%d K=%d" % shape)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(M + N)
+    u8 = lambda *s: torch.zeros(s, dtype=torch.uint8, device=DEV)
+    sc = torch.zeros(16, dtype=torch.float32, device=DEV)
+    xq, xqT, wq, wqT = u8(M, K), u8(K, M), u8(N, K), u8(K, N)
+    saved = tw.make_saved(xq, xqT, wq, wqT, sc)
+    ws = workspace(tw.TWEO_OP_FP8_LINEAR_FWD_BF16, M, N, K)
+    y, y2 = (torch.empty((M, N), dtype=torch.bfloat16, device=DEV) for _ in range(2))
+    S, S2 = (torch.full((1,), float("nan"), dtype=torch.float64, device=DEV) for _ in range(2))
+    w = (torch.randn((N, K), generator=g, device=DEV) * 0.1).bfloat16()
+    for pen in (PEN, PEN, (2.0, 0.5, 3)):
+        x = torch.randn((M, K), generator=g, device=DEV).bfloat16()
+        tw.tweo_fp8_linear_fwd_bf16(x, w, y, saved, pen=pen, penalty_sum=S, workspace=ws)
+        tw.tweo_fp8_linear_fwd(xq, sc[2:3], wq, sc[5:6], y2, pen=pen, penalty_sum=S2, workspace=ws)
+        torch.cuda.synchronize()
+        assert torch.equal(y, y2) and S.item() > 0.0
+        assert torch.equal(S.view(torch.int64), S2.view(torch.int64))
+        S.fill_(float("nan"))
