@@ -372,7 +372,7 @@ def time_w8a8(tw, torch, synth, dev, iters=20, copies=8):
             bytes_ = M * K + N * K + 2 * M * N
             call = lambda c: (lambda: tw.tweo_w8a8_linear(xq, wqs[c], step_x * step_w, ys[c % len(ys)], ws))
             r = {}
-            if M <= 128:  # the weight-streaming kernel
+            if M <= 128:  # decode sizes: bound by the weights, cold and warm
                 warm, cold = [call(0)] * 8, [call(c) for c in range(copies)]
                 stream_us(cold, copies)
                 r["cold_kernel_us"] = round(kernel_us(cold + cold), 2)
