@@ -95,6 +95,12 @@ __device__ __forceinline__ void gemm_nt_ring_body(const GemmDev &g, const int bl
     // code of that row of B but a NaN, which makes the whole column a NaN anyway.
     const int tail = RAGGED ? (g.K & (T::BK - 1)) >> 4 : 0;
     const bool ragged = RAGGED && tail != 0 && kt_begin + kt == kt_all;
+    // INT8, where the order of the sums is free: each XCD starts at another eighth of K, or all of them would read the
+    // same columns of rows that lie thousands of bytes apart, from a few of the memory's channels, at a time (call, weights
+    // cold, us: 64 rows of 4096 -> 12288 15.0 / 14.2, 256 and 512 of 11008 -> 4096 27.4 / 26.3, 45.4 / 43.7; five more
+    // equal within 2 %).  FP8 gains nothing: 768x2304 over 8192 tokens 26.9 / 28.6, 3072x1024 over 4096 18.8 / 17.7.
+    constexpr bool ROTATE = INT8;
+    const int first = ROTATE && !ragged ? (block & 7) * kt / 8 : 0;
     const float alpha = KSPLIT ? 0.0f : gemm_alpha<INT8>(g);
 
     // ---- operand stream: an instruction fills 8 rows x 128 bytes, chunks XOR-swizzled with (row/2)%8
@@ -115,7 +121,8 @@ __device__ __forceinline__ void gemm_nt_ring_body(const GemmDev &g, const int bl
         const bool is_a = p < T::A_DMA;
         const uint32_t dst = lds_base + (uint32_t)(s % T::NS) * T::STAGE_BYTES + (is_a ? 0 : T::A_BYTES) +
                              ((is_a ? p : p - T::A_DMA) * T::NWAVES + wave) * 1024;
-        const uint8_t *ptr = (is_a ? Ag : Bg) + (int64_t)s * T::BK;
+        const int at_s = ROTATE && s + first >= kt ? s + first - kt : s + first;
+        const uint8_t *ptr = (is_a ? Ag : Bg) + (int64_t)at_s * T::BK;
         if (RAGGED && rg && ragged && s == kt - 1) {
             const uint32_t at = k_first + (uint32_t)s * T::BK;
             dma_load16(dst, ptr - at, chunk < tail ? voff[p] + at : voff[p] - chunk * 16);

@@ -83,6 +83,19 @@ def test_int8(shape, tile):
     assert np.array_equal(out.cpu().numpy(), oracle.w8a8_linear_scaled_i8out(xq, wq, sx, sw, np.float32(0.7)))
 
 
+# every XCD starts at its own stage; fewer stages than XCDs, no whole number of eighths, and tiles alone or two on a CU
+@pytest.mark.parametrize("shape", [(100, 6200, 1152), (128, 12288, 384), (192, 12288, 512), (70, 4104, 1664), (512, 4096, 2176)])
+def test_int8_as_dispatched(shape):
+    M, N, K = shape
+    say("ring INT8 as dispatched M=%d N=%d K=%d" % (M, N, K))
+    rng = np.random.default_rng(M + K)
+    xq, wq = (rng.integers(-127, 128, (n, K), dtype=np.int8) for n in (M, N))
+    y = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device=DEV)
+    tw.tweo_w8a8_linear(to_dev(xq), to_dev(wq), 0.001, y)
+    torch.cuda.synchronize()
+    assert np.array_equal(bf16_bits(y), oracle.w8a8_linear(xq, wq, 0.001))
+
+
 @pytest.mark.parametrize("tile", RING, indirect=True)
 @pytest.mark.parametrize("shape", [(208, 272, 144), (1040, 128, 264)])
 def test_e5m2_gradients(shape, tile):
