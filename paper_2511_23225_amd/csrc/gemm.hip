@@ -1337,8 +1337,9 @@ static int pick_tiled(int64_t M, int64_t N, int64_t K, int forced)
 // to 6144 columns over 256 to 50432 rows, medians within 5 % per kernel, single ones within 25 %).  Per
 // 64-byte stage: a 128x128 tile alone on its CU 0.28, two 0.58 (streaming: 0.37; a contraction that is no
 // multiple of 64: 0.375 and 0.8, register-staged 0.57); a 256x256 tile 0.8 (1.05).  Per 128-byte stage: a
-// 256x256 tile of the deferred kernel 1.25, of the 8-wave kernel 1.45.
-static double tiled_us(int v, int64_t M, int64_t N, int64_t K)
+// 256x256 tile of the deferred kernel 1.25, of the 8-wave kernel 1.45.  int8, weights from memory: a 128x128
+// streaming tile alone 0.42 (4096 -> 12288, 96 to 256 rows, 31 us; the ring kernel's 128x128 tiles 22.8).
+static double tiled_us(int v, int64_t M, int64_t N, int64_t K, bool int8)
 {
     const double cus = num_cus(), kt = (double)(K + 127) / 128;
     const bool ragged = K % 64 != 0;
@@ -1352,7 +1353,7 @@ static double tiled_us(int v, int64_t M, int64_t N, int64_t K)
     if (v == 6)
         return (ragged ? 1.05 : 0.8) * 2.0 * kt * rounds(256, 256, cus) + 5.0;
     const bool alone = rounds(128, 128, cus) <= 1.0;
-    const double stage = v == 3 ? 0.57 : v == 13 ? (alone ? 0.28 : 0.37)
+    const double stage = v == 3 ? 0.57 : v == 13 ? (alone ? (int8 ? 0.42 : 0.28) : 0.37)
                                                  : (ragged ? (alone ? 0.375 : 0.8) : (alone ? 0.28 : 0.58));
     return stage * 2.0 * kt * rounds(128, 128, alone && v != 3 ? cus : 2.0 * cus) + 4.0;
 }
@@ -1363,26 +1364,25 @@ struct Pick {
     int v;
     double us;
 };
-static Pick pick(int64_t M, int64_t N, int64_t K)
+static Pick pick(int64_t M, int64_t N, int64_t K, bool int8 = false)
 {
     if (g_tile_override != 0) {
         const int v = g_tile_override == 17 ? 4 : g_tile_override;
         return Pick{ring_shape(v) >= 0 ? v : pick_tiled(M, N, K, v), 0.0};
     }
     const int v = pick_tiled(M, N, K, 0);
-    const double us = tiled_us(v, M, N, K);
+    const double us = tiled_us(v, M, N, K, int8);
     double ring_us;
-    const int shape = ring_pick(M, N, K, num_cus(), &ring_us);
+    const int shape = ring_pick(M, N, K, num_cus(), int8, &ring_us);
     return ring_us < us ? Pick{ring_variant(shape), ring_us} : Pick{v, us};
 }
-static int pick_variant(int64_t M, int64_t N, int64_t K) { return pick(M, N, K).v; }
 
 // the ring kernel's time for a product, 1e300 where it does not take it
-static double ring_us(int64_t M, int64_t N, int64_t K)
+static double ring_us(int64_t M, int64_t N, int64_t K, bool int8 = false)
 {
     double us = 1e300;
     if (g_tile_override == 0)
-        ring_pick(M, N, K, num_cus(), &us);
+        ring_pick(M, N, K, num_cus(), int8, &us);
     return us;
 }
 
@@ -1408,9 +1408,9 @@ static bool defer192_ok(const GemmArgs &a)
            a.row_step == nullptr && (a.p == 0 || a.p == 4) && a.N <= ((int64_t)1 << 22);
 }
 
-static int resolve_variant(const GemmArgs &a)
+static int resolve_variant(const GemmArgs &a, bool int8 = false)
 {
-    int v = pick_variant(a.M, a.N, a.K);
+    int v = pick(a.M, a.N, a.K, int8).v;
     if (v == 15 && !defer_ok(a))
         v = 11;
     if (v == 16 && !defer192_ok(a))
@@ -1597,7 +1597,7 @@ static hipError_t launch_defer192(const GemmArgs &a, hipStream_t s)
 template <bool INT8>
 static hipError_t launch_gemm(const GemmArgs &a, hipStream_t s)
 {
-    const int v = resolve_variant(a);
+    const int v = resolve_variant(a, INT8);
     if (ring_shape(v) >= 0)
         return launch_ring(a, ring_shape(v), INT8, s);
     switch (v) {
@@ -1691,7 +1691,7 @@ static Split pick_split(int64_t M, int64_t N, int64_t K)
 static int i8_defer_ksplit(int64_t M, int64_t N, int64_t K)
 {
     const int runs = defer_ksplit_runs(M, N, K);
-    return runs > 1 && ring_us(M, N, K) < kKsplitBias * ksplit_us(M, N, K, runs, true) ? 1 : runs;
+    return runs > 1 && ring_us(M, N, K, true) < kKsplitBias * ksplit_us(M, N, K, runs, true) ? 1 : runs;
 }
 
 // INT8, between decode and prefill sizes: the scratch that such products are given.  Outputs of few 128x128 tiles
@@ -1964,7 +1964,7 @@ hipError_t launch_i8_gemm(const GemmArgs &a, hipStream_t s)
     // has them for a third of the CUs (call, cold, us, streaming / ring: 4096 -> 12288 at M = 48 / 64 14.1 / 13.5,
     // 15.0 / 14.0; 2048 -> 5632 at M = 32 / 64 6.6 / 6.0, 7.3 / 6.1; with 64 and 32 tiles the stream is ahead:
     // 11008 -> 4096 at M = 64 18.2 / 29.0, 5632 -> 2048 9.2 / 10.2); above 64 rows the ring kernel throughout (M =
-    // 128, 4096 -> 11008 18.7 / 18.0, 11008 -> 4096 29.1 / 28.0, 5632 -> 2048 15.2 / 10.3, 2048 -> 5632 9.4 / 6.2).
+    // 128, 4096 -> 11008 19.6 / 17.9, 11008 -> 4096 29.0 / 26.3, 5632 -> 2048 15.2 / 10.3, 2048 -> 5632 9.4 / 6.2).
     const bool streaming = a.M <= 16 || (a.M <= kSkinnyMaxM && 3 * ((a.N + 63) / 64) < num_cus());
     if (((g_tile_override == 0 && streaming) || (g_tile_override == 17 && a.M <= kSkinnyMaxM)) && a.K % 64 == 0 && a.N % 4 == 0)
         return launch_skinny_ring_any(a, s);

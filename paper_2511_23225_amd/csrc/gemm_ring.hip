@@ -29,17 +29,21 @@ static const RingRate kRates[kRingShapes] = {
 // panels it fetches whole.  A long contraction under small tiles is bound by that: 1024x1024 over 24576 tokens on
 // 64x64 tiles moves 150 MB; weight gradients of the GPT-2 block in its step, operands from memory, 2.1-2.4 TB/s,
 // INT8 384 rows into 4096 columns over 11008 3.6.
-static double fabric_us(const RingRate &r, int64_t M, int64_t N, int64_t K, int64_t units, int runs)
+static double fabric_us(const RingRate &r, int64_t M, int64_t N, int64_t K, int64_t units, int runs, double rate = 3.0e6)
 {
     const int64_t tm = (M + r.bm - 1) / r.bm, per = (units + 7) / 8, rows = std::min<int64_t>({tm, 8, per});
     const double cols = (double)((per + rows - 1) / rows);
-    return r.launch + 8.0 * ((double)rows * r.bm + cols * r.bn) * (double)K / runs / 3.0e6;
+    return r.launch + 8.0 * ((double)rows * r.bm + cols * r.bn) * (double)K / runs / rate;
 }
 
 // stages of rows that are no whole lines lie across two
 static double ragged_rows(int64_t K) { return K % 128 != 0 ? 1.1 : 1.0; }
 
-int ring_pick(int64_t M, int64_t N, int64_t K, int cus, double *us)
+// int8: a layer's weights come from memory at every call, and workgroups in pairs then get less of them than lone
+// ones with twice the stages in flight (call, us, pairs of 64x64 tiles / 64x128 tiles alone: 128 rows of 4096 -> 12288
+// 21.4 / 18.7, 512 of 11008 -> 4096 44.9 / 38.2; 48 shapes of 40 to 512 rows 1.03 times as fast as with one rate for
+// all, weights cold or in the caches)
+int ring_pick(int64_t M, int64_t N, int64_t K, int cus, bool int8, double *us)
 {
     int best = -1;
     *us = 1e300;
@@ -49,7 +53,7 @@ int ring_pick(int64_t M, int64_t N, int64_t K, int cus, double *us)
         if (tiles > (int64_t)r.per_cu * cus)
             continue;
         const double t = std::max(r.launch + (tiles <= cus ? r.one : r.two) * (double)((K + 127) / 128) * ragged_rows(K),
-                                  fabric_us(r, M, N, K, tiles, 1));
+                                  fabric_us(r, M, N, K, tiles, 1, int8 && tiles > cus ? 2.6e6 : 3.0e6));
         if (t < *us) {
             *us = t;
             best = i;
