@@ -363,7 +363,10 @@ tweo_status tweo_w8a8_linear_scaled_i8out(const int8_t *xq, const int8_t *wq, in
  * pointers to caller-owned buffers.
  *   xq [M,K], xqT [K,M], wq [N,K], wqT [K,N]
  *   scalars: 16 fp32: [0] amax_x [1] sx [2] sx_inv [3] amax_w [4] sw [5] sw_inv
- *                     [6] amax_dy [7] sdy [8] sdy_inv, rest reserved.
+ *                     [6] amax_dy [7] sdy [8] sdy_inv, rest reserved ([15] counts
+ *                     the workgroups of a forward call with a penalty while
+ *                     it runs).  They belong to one call until that has
+ *                     finished.
  */
 typedef struct {
     uint8_t *xq;

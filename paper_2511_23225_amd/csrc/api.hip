@@ -9,7 +9,6 @@ using namespace tweo;
 
 namespace {
 
-inline bool aligned8(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 7u) == 0; }
 inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline size_t round256(size_t b) { return b == 0 ? 256 : (b + 255) / 256 * 256; }
 inline tweo_status hip_status(hipError_t e) { return e == hipSuccess ? TWEO_OK : TWEO_ERR_HIP; }
@@ -106,6 +105,9 @@ inline bool stream_k_candidate(int64_t rows, int64_t cols, int64_t contraction)
 {
     return stream_k_enabled() && contraction >= 2048 && rows >= 256 && cols >= 256;
 }
+
+// the word of the saved scalars that a GEMM which finishes the penalty counts its workgroups in
+constexpr int kArrivalsWord = 15;
 
 // head of the workspace of the bf16 entry points: two runs of kAmaxPartialsMax workgroup maxima
 constexpr size_t kAmaxScratchBytes = 2 * kAmaxPartialsMax * sizeof(uint32_t);
@@ -247,13 +249,13 @@ tweo_status tweo_quantize_e5m2_delayed(const void *x_bf16, int64_t rows, int64_t
 }
 
 // update (optional): two delayed-scaling states to update once the GEMM has read its scales from them; set
-// to nullptr if the launch that finishes the penalty took it along.  cleared: a launch in front has set
-// *penalty_sum to 0.
+// to nullptr if the launch that finishes the penalty took it along.  arrivals (optional): a word that a launch in
+// front has set to 0, for a GEMM that finishes the penalty itself.
 static tweo_status fp8_linear_fwd_impl(const uint8_t *xq, const float *sx_inv, const uint8_t *wq,
                                        const float *sw_inv, const void *residual_bf16, int64_t M, int64_t N,
                                        int64_t K, void *y_bf16, const tweo_penalty_cfg *pen, double *penalty_sum,
                                        void *workspace, size_t workspace_bytes, void *stream,
-                                       const DelayedUpdate2 **update, bool cleared)
+                                       const DelayedUpdate2 **update, uint32_t *arrivals)
 {
     if (!xq || !sx_inv || !wq || !sw_inv || !y_bf16 || M <= 0 || N <= 0 || K <= 0 ||
         !aligned16(xq) || !aligned16(wq) || !aligned16(y_bf16) ||
@@ -283,9 +285,10 @@ static tweo_status fp8_linear_fwd_impl(const uint8_t *xq, const float *sx_inv, c
     a.p = p;
     a.partials = (float *)workspace;
     attach_stream_k(a, workspace, workspace_bytes, penalty_bytes(M, N));
-    const bool finishes = cleared && fp8_gemm_finishes(a);
+    const bool finishes = arrivals != nullptr && fp8_gemm_finishes(a);
     if (finishes) {
         a.finish = penalty_sum;
+        a.arrivals = arrivals;
         a.update = update != nullptr ? *update : nullptr;
     }
     hipError_t e = launch_fp8_gemm(a, s);
@@ -308,7 +311,7 @@ tweo_status tweo_fp8_linear_fwd(const uint8_t *xq, const float *sx_inv, const ui
                                 void *stream)
 {
     return fp8_linear_fwd_impl(xq, sx_inv, wq, sw_inv, residual_bf16, M, N, K, y_bf16, pen, penalty_sum, workspace,
-                               workspace_bytes, stream, nullptr, false);
+                               workspace_bytes, stream, nullptr, nullptr);
 }
 
 // ---------------------------------------------------------------------------
@@ -619,27 +622,27 @@ tweo_status tweo_fp8_linear_fwd_bf16(const void *x_bf16, const void *w_bf16,
     // the small weight tensor is mostly launch and tail latency); the amax launch leaves one
     // maximum per workgroup, the cast launch reduces them: nothing to clear, no atomics
     // (or, where it applies, one launch for both steps that keeps the tensors on chip in between)
-    // the cast clears the penalty's sum for a GEMM that finishes it (see ring_finish)
-    double *clear = nullptr;
+    // the cast clears the counter of a GEMM that finishes the penalty itself (see ring_finish)
+    uint32_t *arrivals = nullptr;
     hipError_t e;
     if (fused_cast_applies(M, K, N, K, s)) {
         e = launch_amax_cast_fused(x_bf16, M, K, sc + 0, saved->xq, saved->xqT, sc + 1, sc + 2, w_bf16, N, K, sc + 3,
                                    saved->wq, saved->wqT, sc + 4, sc + 5, false, true, workspace, s);
     } else {
-        if (p != 0 && aligned8(penalty_sum))
-            clear = penalty_sum;
+        if (p != 0)
+            arrivals = (uint32_t *)(sc + kArrivalsWord);
         uint32_t *px = (uint32_t *)workspace, *pw = px + kAmaxPartialsMax;
         int nx = 0, nw = 0;
         e = launch_amax2_partials(x_bf16, M * K, px, &nx, w_bf16, N * K, pw, &nw, s);
         if (e == hipSuccess)
             e = launch_quantize2_e4m3(x_bf16, M, K, sc + 0, saved->xq, saved->xqT, sc + 1, sc + 2, w_bf16, N, K,
-                                      sc + 3, saved->wq, saved->wqT, sc + 4, sc + 5, s, px, nx, pw, nw, clear);
+                                      sc + 3, saved->wq, saved->wqT, sc + 4, sc + 5, s, px, nx, pw, nw, arrivals);
     }
     if (e != hipSuccess)
         return TWEO_ERR_HIP;
     return fp8_linear_fwd_impl(saved->xq, sc + 2, saved->wq, sc + 5, residual_bf16, M, N, K, y_bf16,
                                pen, penalty_sum, (uint8_t *)workspace + kAmaxScratchBytes,
-                               workspace_bytes - kAmaxScratchBytes, stream, nullptr, clear != nullptr);
+                               workspace_bytes - kAmaxScratchBytes, stream, nullptr, arrivals);
 }
 
 static tweo_status fp8_linear_bwd_bf16_impl(const void *dy_bf16, const tweo_fp8_saved *saved, int64_t M,
@@ -715,10 +718,10 @@ tweo_status tweo_fp8_linear_fwd_bf16_delayed(const void *x_bf16, const void *w_b
     int p = 0;
     const bool will_run = check_penalty(pen, penalty_sum, inv_tau, p) == TWEO_OK && p != 0 && workspace &&
                           workspace_bytes >= penalty_bytes(M, N);
-    double *clear = !bootstrap && will_run && aligned8(penalty_sum) ? penalty_sum : nullptr;
+    uint32_t *arrivals = !bootstrap && will_run ? (uint32_t *)(sc + kArrivalsWord) : nullptr;
     hipError_t e = launch_quantize2_e4m3_delayed(x_bf16, M, K, state_x, saved->xq, saved->xqT, sc + 0, w_bf16, N, K,
                                                  state_w, saved->wq, saved->wqT, sc + 3, bootstrap != 0,
-                                                 (hipStream_t)stream, clear);
+                                                 (hipStream_t)stream, arrivals);
     if (e != hipSuccess)
         return TWEO_ERR_HIP;
     const DelayedUpdate2 update{(uint32_t *)state_x, sc, (uint32_t *)state_w, sc + 3}, *left = &update;
@@ -730,7 +733,7 @@ tweo_status tweo_fp8_linear_fwd_bf16_delayed(const void *x_bf16, const void *w_b
     }
     const tweo_status st = fp8_linear_fwd_impl(saved->xq, (const float *)state_x + 18, saved->wq,
                                                (const float *)state_w + 18, residual_bf16, M, N, K, y_bf16, pen,
-                                               penalty_sum, workspace, workspace_bytes, stream, &left, clear != nullptr);
+                                               penalty_sum, workspace, workspace_bytes, stream, &left, arrivals);
     // the cast has run: its states are updated also where the product was refused
     if (left != nullptr && launch_delayed_update2(*left, (hipStream_t)stream) != hipSuccess)
         return TWEO_ERR_HIP;

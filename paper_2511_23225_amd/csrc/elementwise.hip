@@ -1113,10 +1113,10 @@ struct QuantTensor {
 
 template <bool THROUGH>
 __global__ __launch_bounds__(kQuantThreads) void cast2_tile_kernel(QuantTensor t0, int64_t blocks0,
-                                                                             QuantTensor t1, double *clear)
+                                                                             QuantTensor t1, uint32_t *clear)
 {
     if (clear != nullptr && blockIdx.x == 0 && threadIdx.x == 0)
-        *clear = 0.0;
+        *clear = 0u;
     const bool first = (int64_t)blockIdx.x < blocks0;
     const QuantTensor &t = first ? t0 : t1;
     cast_tile_body<true, false, false, 0, false, true, THROUGH>(t.x, t.rows, t.cols, t.tiles_x, t.amax, t.q, t.qT, t.scale_out,
@@ -1129,7 +1129,7 @@ hipError_t launch_quantize2_e4m3(const void *x0_bf16, int64_t rows0, int64_t col
                                  uint8_t *q0T, float *scale0, float *scale0_inv, const void *x1_bf16,
                                  int64_t rows1, int64_t cols1, float *amax1, uint8_t *q1, uint8_t *q1T,
                                  float *scale1, float *scale1_inv, hipStream_t s, const uint32_t *partials0,
-                                 int n_partials0, const uint32_t *partials1, int n_partials1, double *clear)
+                                 int n_partials0, const uint32_t *partials1, int n_partials1, uint32_t *clear)
 {
     auto tiles = [](int64_t v) { return (v + kTile - 1) / kTile; };
     QuantTensor t0{(const uint16_t *)x0_bf16, rows0, cols0, walk_width(rows0, cols0, true), amax0, q0, q0T, scale0, scale0_inv,
@@ -1821,10 +1821,10 @@ struct QuantTensorDelayed {
 
 __global__ __launch_bounds__(kQuantThreads) void cast2_delayed_tile_kernel(QuantTensorDelayed t0, int64_t blocks0,
                                                                                 QuantTensorDelayed t1, int64_t blocks1,
-                                                                                double *clear)
+                                                                                uint32_t *clear)
 {
     if (clear != nullptr && blockIdx.x == 0 && threadIdx.x == 0)
-        *clear = 0.0;
+        *clear = 0u;
     const bool first = (int64_t)blockIdx.x < blocks0;
     const QuantTensorDelayed &t = first ? t0 : t1;
     cast_tile_body<true, true, false, 0, false, true>(t.x, t.rows, t.cols, t.tiles_x, t.scale, t.q, t.qT, nullptr, nullptr, t.amax_acc,
@@ -1835,7 +1835,7 @@ __global__ __launch_bounds__(kQuantThreads) void cast2_delayed_tile_kernel(Quant
 hipError_t launch_quantize2_e4m3_delayed(const void *x0_bf16, int64_t rows0, int64_t cols0, void *state0, uint8_t *q0,
                                          uint8_t *q0T, float *sc0, const void *x1_bf16, int64_t rows1, int64_t cols1,
                                          void *state1, uint8_t *q1, uint8_t *q1T, float *sc1, int bootstrap,
-                                         hipStream_t s, double *clear)
+                                         hipStream_t s, uint32_t *clear)
 {
     // (not bootstrap: the caller launches the states' update)
     if (bootstrap) {  // empty histories: each tensor's own amax first (once per state)

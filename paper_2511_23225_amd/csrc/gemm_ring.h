@@ -42,10 +42,12 @@ struct TileR {
 
 // The penalty's end without a launch of its own, which would cost 3 us and more behind a kernel of 4 to 10.  Nobody
 // waits: every workgroup's partial sum is in memory before it counts itself, and the one that finds all others
-// counted adds them, in the order of the finishing kernel.  The counter is the low word of the result, which
-// the cast in front has cleared.  Up to one workgroup per CU: more of them queue up at the word.
+// counted adds them, in the order of the finishing kernel.  The counter is a word of the call's own scalars, which
+// the cast in front has cleared (the result may be shared by calls in flight, and is not touched before its end).
+// Up to one workgroup per CU: more of them queue up at the word.
 struct RingFinish {
     double *sum;  // or nullptr
+    uint32_t *arrivals;
     DelayedUpdate2 update;
 };
 __device__ __forceinline__ void ring_finish(const float *partials, const RingFinish &fin, uint8_t *smem, int workgroups,
@@ -55,13 +57,15 @@ __device__ __forceinline__ void ring_finish(const float *partials, const RingFin
     int *last = (int *)(smem + kFinishThreads * sizeof(double));
     if (threadIdx.x == 0) {
         wait_vmcnt<0>();  // this thread's store of the partial sum has been performed
-        *last = __hip_atomic_fetch_add((uint32_t *)fin.sum, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+        *last = __hip_atomic_fetch_add(fin.arrivals, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
                 (uint32_t)workgroups - 1u;
     }
     __syncthreads();
     if (*last == 0)
         return;
     penalty_finish<true>(partials, workgroups, fin.sum, (double *)smem);
+    if (threadIdx.x == 0)
+        *fin.arrivals = 0u;
     if (fin.update.st0 != nullptr && wave < 2)
         delayed_state_update(wave == 0 ? fin.update.st0 : fin.update.st1, 0, 448.0f, wave == 0 ? fin.update.sc0 : fin.update.sc1);
 }

@@ -139,7 +139,7 @@ static hipError_t launch_inst(const GemmArgs &a, hipStream_t s)
     if (e != hipSuccess)
         return e;
     const GemmDev g = gemm_dev(a, T::BM, T::BN);
-    const RingFinish fin{a.finish, a.update != nullptr ? *a.update : DelayedUpdate2{}};
+    const RingFinish fin{a.finish, a.arrivals, a.update != nullptr ? *a.update : DelayedUpdate2{}};
     launch_gemm_kernel(kernel, dim3((unsigned)(g.tiles_m * g.tiles_n)), dim3(T::THREADS), T::LDS_BYTES, s, g, fin);
     return hipGetLastError();
 }

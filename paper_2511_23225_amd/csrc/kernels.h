@@ -21,7 +21,7 @@ hipError_t launch_quantize2_e4m3(const void *x0_bf16, int64_t rows0, int64_t col
                                  int64_t rows1, int64_t cols1, float *amax1, uint8_t *q1, uint8_t *q1T,
                                  float *scale1, float *scale1_inv, hipStream_t s,
                                  const uint32_t *partials0 = nullptr, int n_partials0 = 0,
-                                 const uint32_t *partials1 = nullptr, int n_partials1 = 0, double *clear = nullptr);
+                                 const uint32_t *partials1 = nullptr, int n_partials1 = 0, uint32_t *clear = nullptr);
 // amax without a cleared output and without atomics: one maximum (fp32 bit pattern) per workgroup
 // into partials[0 .. *blocks), at most kAmaxPartialsMax of them per tensor
 constexpr int kAmaxPartialsMax = 512;
@@ -75,7 +75,7 @@ hipError_t launch_delayed_update2(const DelayedUpdate2 &u, hipStream_t s);
 hipError_t launch_quantize2_e4m3_delayed(const void *x0_bf16, int64_t rows0, int64_t cols0, void *state0, uint8_t *q0,
                                          uint8_t *q0T, float *sc0, const void *x1_bf16, int64_t rows1, int64_t cols1,
                                          void *state1, uint8_t *q1, uint8_t *q1T, float *sc1, int bootstrap,
-                                         hipStream_t s, double *clear = nullptr);
+                                         hipStream_t s, uint32_t *clear = nullptr);
 // LayerNorm of x (or of h = bf16(x + res), stored to h_out) followed by the per-tensor E4M3 cast of
 // the normalised tensor; state == nullptr: current scaling (amax_out required), else delayed
 // scaling on that state.  stats: 2 doubles per row, partials: kAmaxPartialsMax words of scratch.
@@ -114,7 +114,8 @@ struct GemmArgs {
     float inv_tau;          // 1 / (tau + eps)
     int p;                  // penalty power; 0 = no penalty
     float *partials;        // one fp32 per workgroup when p != 0
-    double *finish;         // the penalty's sum, 0 before the launch, if the launch is to finish it (fp8_gemm_finishes)
+    double *finish;         // the penalty's sum, if the launch is to finish it (fp8_gemm_finishes), or nullptr
+    uint32_t *arrivals;     // its counter: 0 before the launch and after it
     const DelayedUpdate2 *update;  // two states to update with it, or nullptr
     bool a_e5m2;            // FP8 only: A holds E5M2 codes (B is always E4M3)
     void *sk_workspace;     // stream-K scratch (256-byte aligned) or nullptr: then no stream-K

@@ -139,3 +139,65 @@ def test_penalty_finished_by_the_last_workgroup(shape):
         assert torch.equal(y, y2) and S.item() > 0.0
         assert torch.equal(S.view(torch.int64), S2.view(torch.int64))
         S.fill_(float("nan"))
+
+
+def penalised_layer(seed, M, N, K, delayed):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    u8 = lambda *s: torch.zeros(s, dtype=torch.uint8, device=DEV)
+    t = dict(x=torch.randn((M, K), generator=g, device=DEV).bfloat16(), w=(torch.randn((N, K), generator=g, device=DEV) * 0.1).bfloat16(),
+             y=torch.empty((M, N), dtype=torch.bfloat16, device=DEV), sc=torch.full((16,), 7.0, dtype=torch.float32, device=DEV),
+             codes=[u8(M, K), u8(K, M), u8(N, K), u8(K, N)], ws=workspace(tw.TWEO_OP_FP8_LINEAR_FWD_BF16, M, N, K))
+    t["saved"] = tw.make_saved(*t["codes"], t["sc"])
+    if delayed:
+        t["states"] = [torch.zeros(tw.DELAYED_STATE_WORDS, dtype=torch.float32, device=DEV) for _ in range(2)]
+        for st in t["states"]:
+            tw.tweo_delayed_state_init(st)
+    return t
+
+
+def forward(t, S, **more):
+    if "states" in t:
+        tw.tweo_fp8_linear_fwd_bf16_delayed(t["x"], t["w"], t["y"], t["saved"], *t["states"], pen=PEN, penalty_sum=S, workspace=t["ws"], **more)
+    else:
+        tw.tweo_fp8_linear_fwd_bf16(t["x"], t["w"], t["y"], t["saved"], pen=PEN, penalty_sum=S, workspace=t["ws"], **more)
+
+
+# an argument that is refused only behind the cast: nothing has written the sum by then
+@pytest.mark.parametrize("delayed", [False, True])
+def test_a_refused_call_leaves_the_sum(delayed):
+    M, N, K = 256, 512, 512
+    t = penalised_layer(1, M, N, K, delayed)
+    S = torch.full((1,), 0x5555555512345678, dtype=torch.int64, device=DEV).view(torch.float64)
+    if delayed:
+        forward(t, torch.zeros(1, dtype=torch.float64, device=DEV), bootstrap=True)
+    t["y"] = torch.empty(M * N + 8, dtype=torch.bfloat16, device=DEV)[1:1 + M * N].view(M, N)
+    with pytest.raises(tw.TweoError) as e:
+        forward(t, S)
+    torch.cuda.synchronize()
+    assert e.value.status == tw.TWEO_ERR_INVALID_ARG
+    assert S.view(torch.int64).item() == 0x5555555512345678
+
+
+# calls on two streams with one sum that nobody reads: their histories and scalars are those of calls with sums of
+# their own, and the words that the last workgroups counted in are 0 again
+@pytest.mark.parametrize("shape", [(256, 512, 512), (1024, 1024, 256)])
+def test_calls_in_flight_may_share_a_sum(shape):
+    M, N, K = shape
+    alone, shared = ([penalised_layer(3 + i, M, N, K, True) for i in range(2)] for _ in range(2))
+    S = torch.zeros(3, dtype=torch.float64, device=DEV)
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    for step in range(40):
+        for i in range(2):
+            forward(alone[i], S[i:i + 1], bootstrap=step == 0)
+            with torch.cuda.stream(streams[i]):
+                forward(shared[i], S[2:3], bootstrap=step == 0)
+                shared[i]["x"].mul_(1.0 + 0.25 * (step % 3 - 1))
+            alone[i]["x"].mul_(1.0 + 0.25 * (step % 3 - 1))
+    torch.cuda.synchronize()
+    for a, b in zip(alone, shared):
+        assert torch.equal(a["y"], b["y"]) and torch.equal(a["sc"], b["sc"]) and a["sc"][15].item() == 0.0
+        for k in range(2):
+            assert torch.equal(a["states"][k].view(torch.int32), b["states"][k].view(torch.int32))
+        assert int(b["states"][0].view(torch.int32)[19]) == 40 % 16
