@@ -124,6 +124,15 @@ def _ptr(t):
 _current = None  # (current device, raw stream handle of a device), once the GPU is initialised
 
 
+def _forget_current():
+    global _current
+    _current = None
+
+
+# a forked child cannot use its parent's GPU: it goes through torch.cuda.init() again, which refuses it
+os.register_at_fork(after_in_child=_forget_current)
+
+
 def _stream():
     """Handle of torch's current stream on the current device, looked up on every call.
 

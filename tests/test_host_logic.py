@@ -1,6 +1,7 @@
 """Host-side logic of the C-ABI library that needs no GPU: workspace sizing and the argument checks
 that return before anything is launched (the pointers below are never dereferenced)."""
 import ctypes
+import os
 
 import numpy as np
 import pytest
@@ -90,3 +91,20 @@ def test_bench_refuses_more_than_one_gpu():
                        timeout=120)
     assert r.returncode != 0
     assert "ONE GPU" in (r.stdout + r.stderr)
+
+
+def test_a_forked_child_looks_the_stream_up_anew(monkeypatch):
+    # the parent's lookups would hand the child its parent's GPU, past torch's own refusal of it
+    from paper_2511_23225_amd import binding
+    monkeypatch.setattr(binding, "_current", (lambda: 0, lambda device: 1234))
+    assert binding._stream() == 1234
+    pid = os.fork()
+    if pid == 0:
+        code = 1
+        try:
+            code = 1 if binding._stream() == 1234 else 0
+        except BaseException:  # no GPU here, or one that belongs to the parent
+            code = 0
+        finally:
+            os._exit(code)
+    assert os.waitstatus_to_exitcode(os.waitpid(pid, 0)[1]) == 0
