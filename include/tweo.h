@@ -76,8 +76,9 @@ enum {
  * tokens; an INT8 linear of a few hundred rows): several workgroups share a tile,
  * each multiplies a run of K and stores fp32 (INT8: int32) sums here (runs x rows x
  * cols x 4 bytes), a second launch adds the runs in index order - run-to-run
- * identical results.  With less, or with none, such a product runs on the plain
- * schedule. */
+ * identical results.  A backward call over more than 4096 rows may run both of its
+ * products in one launch with runs of the weight gradient here.  With less, or with
+ * none, such a product runs in fewer runs or on the plain schedule. */
 size_t tweo_workspace_bytes(int op, int64_t M, int64_t N, int64_t K);
 
 const char *tweo_status_string(tweo_status s);

@@ -125,7 +125,8 @@ size_t tweo_workspace_bytes(int op, int64_t M, int64_t N, int64_t K)
     case TWEO_OP_FP8_LINEAR_BWD:  // dgrad [M,K] over N, wgrad [N,K] over M
         return 256 + round256(std::max({stream_k_candidate(M, K, N) || stream_k_candidate(N, K, M)
                                             ? stream_k_workspace_bytes() : (size_t)0,
-                                        fp8_gemm_ksplit_bytes(M, K, N), fp8_gemm_ksplit_bytes(N, K, M)}));
+                                        fp8_gemm_ksplit_bytes(M, K, N), fp8_gemm_ksplit_bytes(N, K, M),
+                                        fp8_pair_bytes(M, N, K)}));
     case TWEO_OP_FP8_LINEAR_BWD_BF16:
         return kAmaxScratchBytes + tweo_workspace_bytes(TWEO_OP_FP8_LINEAR_BWD, M, N, K);
     case TWEO_OP_W8A8_LINEAR:

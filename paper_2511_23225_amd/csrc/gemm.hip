@@ -1341,7 +1341,7 @@ static int pick_tiled(int64_t M, int64_t N, int64_t K, int forced)
 // streaming tile alone 0.42 (4096 -> 12288, 96 to 256 rows, 31 us; the ring kernel's 128x128 tiles 22.8).
 static double tiled_us(int v, int64_t M, int64_t N, int64_t K, bool int8)
 {
-    const double cus = num_cus(), kt = (double)(K + 127) / 128;
+    const double cus = num_cus(), kt = (double)((K + 127) / 128);
     const bool ragged = K % 64 != 0;
     auto rounds = [&](int64_t tr, int64_t tc, double slots) {
         return std::ceil((double)(((M + tr - 1) / tr) * ((N + tc - 1) / tc)) / slots);
@@ -1391,7 +1391,7 @@ static double ring_us(int64_t M, int64_t N, int64_t K, bool int8 = false)
 static double ksplit_us(int64_t M, int64_t N, int64_t K, int splits, bool deferred)
 {
     const double kt = (double)(K + 127) / 128, mb = (double)splits * (double)M * (double)N * 4e-6;
-    return (deferred ? 1.3 * kt / splits + 3.0 : (K % 64 != 0 ? 1.3 : 0.85) * 2.0 * kt / splits + 5.0) + mb / 5.0 + 2.5 + mb / 6.5;
+    return (deferred ? 1.3 * kt / splits + 3.0 : (K % 64 != 0 ? 1.1 : 0.85) * 2.0 * kt / splits + 5.0) + mb / 5.0 + 2.5 + mb / 6.5;
 }
 
 // The deferred-epilogue kernel covers whole 256x256 tiles, K in whole stages with enough of
@@ -1659,10 +1659,10 @@ static int tiled_ksplit_runs(int64_t M, int64_t N, int64_t K)
     return splits >= 2 ? (int)splits : 1;
 }
 
-// What runs a product that scratch is asked for (by the rules above): one launch of the ring kernel over the whole
-// contraction, runs of its small tiles, or the runs above.  768x768 over 8192 tokens 25.3 us in the deferred
-// kernel's runs, 13.4 whole; 2304x768 30.2, 20.3; 256x256 over 20480 28.0, 11.9 in ten runs of 64x64 tiles, 512x512 28.7, 19.7; the estimate of the large tiles' runs is high by a
-// seventh there.
+// What runs a product in `scratch` bytes for runs of it.  By the rules above scratch is asked for: one launch of the ring
+// kernel over the whole contraction, runs of its small tiles, or the runs above.  768x768 over 8192 tokens 25.3 us in
+// the deferred kernel's runs, 13.4 whole; 2304x768 30.2, 20.3; 256x256 over 20480 28.0, 11.9 in ten runs of 64x64 tiles,
+// 512x512 28.7, 19.7; the estimate of the large tiles' runs is high by a seventh there.
 enum SplitWay { kWhole, kRingRuns, kDeferRuns, kTiledRuns };
 struct Split {
     SplitWay way;
@@ -1670,10 +1670,10 @@ struct Split {
     double us;
 };
 constexpr double kKsplitBias = 0.85;
-static Split pick_split(int64_t M, int64_t N, int64_t K)
+static Split pick_split(int64_t M, int64_t N, int64_t K, size_t scratch)
 {
     const int dr = defer_ksplit_runs(M, N, K), runs = dr > 1 ? dr : tiled_ksplit_runs(M, N, K);
-    if (runs <= 1)
+    if (runs <= 1 || scratch < (size_t)runs * (size_t)M * (size_t)N * sizeof(float))
         return Split{kWhole, 1, -1, pick(M, N, K).us};
     Split best{dr > 1 ? kDeferRuns : kTiledRuns, runs, -1, kKsplitBias * ksplit_us(M, N, K, runs, dr > 1)};
     const double whole = ring_us(M, N, K);
@@ -1682,7 +1682,8 @@ static Split pick_split(int64_t M, int64_t N, int64_t K)
     int shape = -1;
     double us;
     const int small = ring_ksplit_pick(M, N, K, num_cus(), runs, &shape, &us);
-    if (small > 1 && us < best.us)
+    // (of two ways in runs the large tiles' time is the surer one: they fetch half as much)
+    if (small > 1 && us < (best.way == kWhole ? 1.0 : 0.92) * best.us)
         best = Split{kRingRuns, small, shape, us};
     return best;
 }
@@ -1733,6 +1734,30 @@ size_t fp8_gemm_ksplit_bytes(int64_t M, int64_t N, int64_t K)
     if (splits <= 1)
         splits = tiled_ksplit_runs(M, N, K);
     return splits > 1 ? (size_t)splits * (size_t)M * (size_t)N * sizeof(float) : 0;
+}
+
+// The pair of gradient products of a layer in one launch: the shape, or -1 where they run one after the other, and the runs
+// of the weight gradient (1: whole).  scratch: what both have for runs.  Up to eight runs of contractions beyond 4096 (with more the sums weigh more than they are worth);
+// no more than the weight gradient would have by itself, if it has any (so scratch is asked for by one rule or the other).
+constexpr int kPairRuns = 8;
+static int pick_pair(int64_t M, int64_t N, int64_t K, size_t scratch, int *runs)
+{
+    const size_t run = (size_t)N * (size_t)K * sizeof(float), asked = fp8_gemm_ksplit_bytes(N, K, M);
+    const size_t fit = (asked != 0 ? std::min(scratch, asked) : scratch) / run;
+    double us;
+    const int shape = ring_pair_pick(M, N, K, num_cus(), M > 4096 ? (int)std::min<size_t>(fit, kPairRuns) : 1, runs, &us);
+    // (the one launch's time is the surer one: this was right oftener than 1, see ragged_rows)
+    const double sure = shape == kRing128x128x2 ? 0.97 : 0.94;
+    return shape >= 0 && sure * us < pick_split(M, K, N, scratch).us + pick_split(N, K, M, scratch).us ? shape : -1;
+}
+
+size_t fp8_pair_bytes(int64_t M, int64_t N, int64_t K)
+{
+    if (g_tile_override != 0 || !g_stream_k_off || M <= 4096 || fp8_gemm_ksplit_bytes(N, K, M) != 0)
+        return 0;
+    const size_t run = (size_t)N * (size_t)K * sizeof(float);
+    int runs = 1;
+    return pick_pair(M, N, K, kPairRuns * run, &runs) >= 0 && runs > 1 ? (size_t)runs * run : 0;
 }
 
 // the second launch of a K split whose runs lie as the output does
@@ -1821,6 +1846,12 @@ static hipError_t launch_ksplit_defer(const GemmArgs &a, hipStream_t s, int spli
     return hipGetLastError();
 }
 
+// bytes that a launch may leave runs of a K split in
+static size_t split_scratch(const GemmArgs &a)
+{
+    return a.sk_workspace != nullptr && ((uintptr_t)a.sk_workspace & 15u) == 0 ? a.sk_workspace_bytes : 0;
+}
+
 // both gradient products of a layer (d: [M, K] over N, w: [N, K] over M, no penalty, no residual)
 hipError_t launch_fp8_gemm_pair(const GemmArgs &d, const GemmArgs &w, hipStream_t s)
 {
@@ -1830,12 +1861,19 @@ hipError_t launch_fp8_gemm_pair(const GemmArgs &d, const GemmArgs &w, hipStream_
     };
     if (g_tile_override == 0 && g_stream_k_off && !overlap(w.out, w.M * w.N * 2, d.A, d.M * d.K) &&
         !overlap(w.out, w.M * w.N * 2, d.B, d.N * d.K)) {
-        // in one launch where both grids of tiles are resident at once and that is the faster way: a launch less, and
-        // no half-empty chip (1024x1024 -> 1024 8.4 us on 64-byte stages, 6.0; 2048x1024 -> 1024 12.8, 9.2)
-        double us;
-        const int shape = ring_pair_pick(d.M, d.K, d.N, num_cus(), &us);
-        if (shape >= 0 && us < pick_split(d.M, d.N, d.K).us + pick_split(w.M, w.N, w.K).us)
-            return launch_ring_pair(d, w, shape, s);
+        // in one launch where that is the faster way: a launch less, and no half-empty chip (1024x1024 -> 1024 8.4 us on
+        // 64-byte stages, 6.0; 2048x1024 -> 1024 12.8, 9.2; operands cold, 128x128 tiles in rounds,
+        // 5920x1536 -> 2816 89 apart, 73; the weight gradient in runs among them, 8240x336 -> 880 37, 25, 10928x1872 -> 352 52, 40)
+        int runs = 1;
+        const int shape = pick_pair(d.M, d.K, d.N, split_scratch(w), &runs);
+        if (shape >= 0 && runs == 1)
+            return launch_ring_pair(d, w, shape, 1, s, nullptr);
+        if (shape >= 0) {
+            hipEvent_t e0 = nullptr, e1 = nullptr;  // a profiled launch brackets both kernels
+            take_profile_events(&e0, &e1);
+            const hipError_t e = launch_ring_pair(d, w, shape, runs, s, e0);
+            return e != hipSuccess ? e : launch_splitk_reduce<false>(w, runs, s, e1);
+        }
     }
     const hipError_t e = launch_fp8_gemm(d, s);
     return e != hipSuccess ? e : launch_fp8_gemm(w, s);
@@ -1874,10 +1912,9 @@ static hipError_t launch_fp8_gemm_e5m2(const GemmArgs &a, hipStream_t s)
 
 hipError_t launch_fp8_gemm(const GemmArgs &a, hipStream_t s)
 {
-    if (a.p == 0 && a.residual == nullptr) {
-        const Split split = pick_split(a.M, a.N, a.K);
-        if (split.way != kWhole && a.sk_workspace != nullptr && ((uintptr_t)a.sk_workspace & 15u) == 0 &&
-            a.sk_workspace_bytes >= (size_t)split.runs * (size_t)a.M * (size_t)a.N * sizeof(float)) {
+    if (a.p == 0 && a.residual == nullptr && split_scratch(a) != 0) {
+        const Split split = pick_split(a.M, a.N, a.K, split_scratch(a));
+        if (split.way != kWhole) {
             if (split.way == kDeferRuns)
                 return a.a_e5m2 ? launch_ksplit_defer<true>(a, s, split.runs) : launch_ksplit_defer<false>(a, s, split.runs);
             if (split.way == kTiledRuns)

@@ -323,8 +323,8 @@ __global__ __launch_bounds__(T::THREADS, T::WG_PER_CU *T::NWAVES / 4) void gemm_
 
 // The two products of a linear layer's backward in one launch: workgroups [0, n0) are the grid of g0,
 // [n0_padded, ..) that of g1 (padded to a multiple of 8 so that a workgroup's number modulo 8 is its
-// XCD in both).
-template <typename T, bool A_E5M2, bool RAGGED>
+// XCD in both).  RUNS: one of them may be in runs of its contraction.
+template <typename T, bool A_E5M2, bool RAGGED, bool RUNS>
 __global__ __launch_bounds__(T::THREADS, T::WG_PER_CU *T::NWAVES / 4) void gemm_nt_ring_pair_kernel(GemmDev g0, GemmDev g1,
                                                                                                    int n0, int n0_padded)
 {
@@ -332,7 +332,10 @@ __global__ __launch_bounds__(T::THREADS, T::WG_PER_CU *T::NWAVES / 4) void gemm_
     if (b >= n0 && b < n0_padded)
         return;
     const bool first = b < n0;
-    gemm_nt_ring_body<T, false, A_E5M2, false, RAGGED, false>(first ? g0 : g1, first ? b : b - n0_padded, RingFinish{});
+    if (RUNS && (first ? g0 : g1).ksplit > 1)
+        gemm_nt_ring_body<T, false, A_E5M2, RUNS, RAGGED, false>(first ? g0 : g1, first ? b : b - n0_padded, RingFinish{});
+    else
+        gemm_nt_ring_body<T, false, A_E5M2, false, RAGGED, false>(first ? g0 : g1, first ? b : b - n0_padded, RingFinish{});
 }
 
 }  // namespace tweo

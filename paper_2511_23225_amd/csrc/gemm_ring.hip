@@ -22,22 +22,26 @@ static const RingRate kRates[kRingShapes] = {
     {64, 64, R64x64::WG_PER_CU, 2.6, 0.196, 0.35},    {64, 64, R64x64g2::WG_PER_CU, 3.0, 0.175, 0.0},
     {64, 128, R64x128::WG_PER_CU, 3.1, 0.283, 0.51},  {64, 128, R64x128g2::WG_PER_CU, 3.3, 0.258, 0.0},
     {128, 128, R128x128::WG_PER_CU, 4.2, 0.39, 0.0},  {96, 128, R96x128::WG_PER_CU, 3.8, 0.32, 0.0},
-    {128, 128, R128x128x2::WG_PER_CU, 4.4, 0.58, 0.69},
+    {128, 128, R128x128x2::WG_PER_CU, 4.4, 0.66, 0.85},
 };
 
 // Operands on their way to the XCDs' L2s: each works on a block of about eight rows of tiles (tile_from_id), whose
 // panels it fetches whole.  A long contraction under small tiles is bound by that: 1024x1024 over 24576 tokens on
 // 64x64 tiles moves 150 MB; weight gradients of the GPT-2 block in its step, operands from memory, 2.1-2.4 TB/s,
 // INT8 384 rows into 4096 columns over 11008 3.6.
-static double fabric_us(const RingRate &r, int64_t M, int64_t N, int64_t K, int64_t units, int runs, double rate = 3.0e6)
+static double fabric_us(const RingRate &r, int64_t M, int64_t N, int64_t K, int64_t units, int runs, double rate)
 {
     const int64_t tm = (M + r.bm - 1) / r.bm, per = (units + 7) / 8, rows = std::min<int64_t>({tm, 8, per});
     const double cols = (double)((per + rows - 1) / rows);
     return r.launch + 8.0 * ((double)rows * r.bm + cols * r.bn) * (double)K / runs / rate;
 }
 
-// stages of rows that are no whole lines lie across two
-static double ragged_rows(int64_t K) { return K % 128 != 0 ? 1.1 : 1.0; }
+// Rows that are no whole number of lines: a stage of one lies across two.  A lone product waits for that, runs of K and
+// several rounds of tiles less (1260 timings of backward calls of 256 to 50432 rows, operands cold and in the caches;
+// weight gradients over 8208 rows instead of 8192, 768x768 28.5 us / 18.6, 768x2304 41 / 28; INT8, a few hundred
+// rows: 1.1).  The lines come at 2.5 TB/s in the place of 3.
+static double ragged_rows(int64_t K, bool covered) { return K % 128 == 0 ? 1.0 : K % 64 == 0 ? 1.25 : covered ? 1.4 : 1.7; }
+static double fabric_rate(int64_t K) { return K % 128 == 0 ? 3.0e6 : 2.5e6; }
 
 // int8: a layer's weights come from memory at every call, and workgroups in pairs then get less of them than lone
 // ones with twice the stages in flight (call, us, pairs of 64x64 tiles / 64x128 tiles alone: 128 rows of 4096 -> 12288
@@ -52,8 +56,10 @@ int ring_pick(int64_t M, int64_t N, int64_t K, int cus, bool int8, double *us)
         const int64_t tiles = ((M + r.bm - 1) / r.bm) * ((N + r.bn - 1) / r.bn);
         if (tiles > (int64_t)r.per_cu * cus)
             continue;
-        const double t = std::max(r.launch + (tiles <= cus ? r.one : r.two) * (double)((K + 127) / 128) * ragged_rows(K),
-                                  fabric_us(r, M, N, K, tiles, 1, int8 && tiles > cus ? 2.6e6 : 3.0e6));
+        const double ragged = !int8 ? ragged_rows(K, false) : K % 128 != 0 ? 1.1 : 1.0;
+        const double rate = !int8 ? fabric_rate(K) : tiles > cus ? 2.6e6 : 3.0e6;
+        const double t = std::max(r.launch + (tiles <= cus ? r.one : r.two) * (double)((K + 127) / 128) * ragged,
+                                  fabric_us(r, M, N, K, tiles, 1, rate));
         if (t < *us) {
             *us = t;
             best = i;
@@ -74,8 +80,8 @@ int ring_ksplit_pick(int64_t M, int64_t N, int64_t K, int cus, int most, int *sh
         const int64_t tiles = ((M + r.bm - 1) / r.bm) * ((N + r.bn - 1) / r.bn);
         for (int runs = 2; runs <= most && tiles * runs <= (int64_t)r.per_cu * cus && kt / runs >= 4; ++runs) {
             const double mb = (double)runs * (double)M * (double)N * 4e-6;
-            const double t = std::max(r.launch + (tiles * runs <= cus ? r.one : r.two) * (double)((kt + runs - 1) / runs) * ragged_rows(K),
-                                      fabric_us(r, M, N, K, tiles * runs, runs)) +
+            const double t = std::max(r.launch + (tiles * runs <= cus ? r.one : r.two) * (double)((kt + runs - 1) / runs) * ragged_rows(K, true),
+                                      fabric_us(r, M, N, K, tiles * runs, runs, fabric_rate(K))) +
                              mb / 4.0 + 3.0 + mb / 6.5;
             if (t < *us) {
                 *us = t;
@@ -87,33 +93,38 @@ int ring_ksplit_pick(int64_t M, int64_t N, int64_t K, int cus, int most, int *sh
     return best;
 }
 
-int ring_pair_pick(int64_t M, int64_t N, int64_t K, int cus, double *us)
+// The weight gradient whole, or (128x128 tiles in rounds) in up to `most` runs of at least four stages, whose sums go out
+// and come back as those of ring_ksplit_pick.
+int ring_pair_pick(int64_t M, int64_t N, int64_t K, int cus, int most, int *runs, double *us)
 {
     int best = -1;
     *us = 1e300;
-    const double kd = (double)((N + 127) / 128) * ragged_rows(N), kw = (double)((M + 127) / 128) * ragged_rows(M);
     for (int i = 0; i < kRingShapes; ++i) {
         if (i == kRing128x128 || i == kRing96x128)
             continue;
         const RingRate &r = kRates[i];
+        const bool rounds = i == kRing128x128x2;  // two on a CU, in as many rounds as it takes
+        const double fd = ragged_rows(N, rounds), fw = ragged_rows(M, rounds);
+        const int64_t kd = (N + 127) / 128, kw = (M + 127) / 128;
         auto tiles = [&](int64_t a, int64_t b) { return ((a + r.bm - 1) / r.bm) * ((b + r.bn - 1) / r.bn); };
         const int64_t td = tiles(M, K), tw = tiles(N, K);
-        const bool resident = td + tw + 8 <= (int64_t)r.per_cu * cus;
-        const double longest = std::max(kd, kw);
-        // 128x128 tiles, two on a CU, in as many rounds as it takes; not under a long contraction, whose workgroups
-        // end up alone on their CUs with one stage in flight (the GPT-2 block's qkv layer 61 us, 54 apart)
-        if (i == kRing128x128x2 ? longest > 40.0 : !resident)
+        if (!rounds && td + tw + 8 > (int64_t)r.per_cu * cus)
             continue;
-        double t = r.launch + r.one * longest;
-        if (td + tw > cus) {  // two on a CU: the longest unit, or the average load of a slot
-            const double fill = resident ? 0.0 : 3.0;  // stages that a tile's start and end are worth
-            t = std::max(t, r.launch + r.two * ((double)td * (kd + fill) + (double)tw * (kw + fill)) / (2.0 * cus) + 0.25 * r.two * longest);
-        }
-        if (!resident)
-            t /= 0.88;  // several rounds of tiles: only where that is clearly ahead
-        if (t < *us) {
-            *us = t;
-            best = i;
+        const double load = ((double)(td * kd) * fd + (double)(tw * kw) * fw) / (2.0 * cus);
+        for (int n = 1; n == 1 || (rounds && n <= most && kw / n >= 4); ++n) {
+            const double longest = std::max((double)kd * fd, (double)((kw + n - 1) / n) * fw);
+            double t = r.launch + r.one * longest;
+            if (td + tw * n > cus)  // two on a CU: the longest unit, or the average load of a slot and an uneven end
+                t = std::max(t, r.launch + r.two * (load + 0.25 * longest));
+            if (n > 1) {
+                const double mb = (double)n * (double)N * (double)K * 4e-6;
+                t += mb / 4.0 + 3.0 + mb / 6.5;
+            }
+            if (t < *us) {
+                *us = t;
+                *runs = n;
+                best = i;
+            }
         }
     }
     return best;
@@ -197,20 +208,28 @@ hipError_t launch_ring_ksplit(const GemmArgs &a, int shape, int runs, hipStream_
     }
 }
 
-template <typename T, bool A_E5M2, bool RAGGED>
-static hipError_t launch_pair_inst(const GemmArgs &d, const GemmArgs &w, hipStream_t s)
+// runs > 1: of w, into its scratch; the launch that adds them is the caller's, and so are the profile events
+template <typename T, bool A_E5M2, bool RAGGED, bool RUNS>
+static hipError_t launch_pair_inst(const GemmArgs &d, const GemmArgs &w, int runs, hipStream_t s, hipEvent_t start)
 {
     static bool done = false;
-    constexpr auto kernel = gemm_nt_ring_pair_kernel<T, A_E5M2, RAGGED>;
+    constexpr auto kernel = gemm_nt_ring_pair_kernel<T, A_E5M2, RAGGED, RUNS>;
     const hipError_t e = raise_lds(kernel, T::LDS_BYTES, done);
     if (e != hipSuccess)
         return e;
     GemmDev g0 = gemm_dev(d, T::BM, T::BN), g1 = gemm_dev(w, T::BM, T::BN);
-    if (g0.K < g1.K)  // the longer units first
+    g1.ksplit = runs;
+    g1.ksplit_out = (float *)w.sk_workspace;
+    if (g0.K < g1.K / runs)  // the longer units first
         std::swap(g0, g1);
-    const int n0 = g0.tiles_m * g0.tiles_n, n0_padded = (n0 + 7) / 8 * 8;
-    launch_gemm_kernel(kernel, dim3((unsigned)(n0_padded + g1.tiles_m * g1.tiles_n)), dim3(T::THREADS), T::LDS_BYTES, s, g0, g1,
-                       n0, n0_padded);
+    const int n0 = g0.tiles_m * g0.tiles_n * g0.ksplit, n0_padded = (n0 + 7) / 8 * 8;
+    const dim3 grid((unsigned)(n0_padded + g1.tiles_m * g1.tiles_n * g1.ksplit)), block(T::THREADS);
+    if (!RUNS)
+        launch_gemm_kernel(kernel, grid, block, T::LDS_BYTES, s, g0, g1, n0, n0_padded);
+    else if (start != nullptr)
+        hipExtLaunchKernelGGL(kernel, grid, block, T::LDS_BYTES, s, start, nullptr, 0, g0, g1, n0, n0_padded);
+    else
+        hipLaunchKernelGGL(kernel, grid, block, T::LDS_BYTES, s, g0, g1, n0, n0_padded);
     return hipGetLastError();
 }
 
@@ -219,12 +238,15 @@ static hipError_t launch_pair_shape(const GemmArgs &d, const GemmArgs &w, hipStr
 {
     const bool ragged = d.K % T::BK != 0 || w.K % T::BK != 0;
     if (d.a_e5m2)
-        return ragged ? launch_pair_inst<T, true, true>(d, w, s) : launch_pair_inst<T, true, false>(d, w, s);
-    return ragged ? launch_pair_inst<T, false, true>(d, w, s) : launch_pair_inst<T, false, false>(d, w, s);
+        return ragged ? launch_pair_inst<T, true, true, false>(d, w, 1, s, nullptr) : launch_pair_inst<T, true, false, false>(d, w, 1, s, nullptr);
+    return ragged ? launch_pair_inst<T, false, true, false>(d, w, 1, s, nullptr) : launch_pair_inst<T, false, false, false>(d, w, 1, s, nullptr);
 }
 
-hipError_t launch_ring_pair(const GemmArgs &d, const GemmArgs &w, int shape, hipStream_t s)
+hipError_t launch_ring_pair(const GemmArgs &d, const GemmArgs &w, int shape, int runs, hipStream_t s, hipEvent_t start)
 {
+    if (runs > 1)
+        return d.a_e5m2 ? launch_pair_inst<R128x128x2, true, true, true>(d, w, runs, s, start)
+                        : launch_pair_inst<R128x128x2, false, true, true>(d, w, runs, s, start);
     switch (shape) {
     case kRing64x64: return launch_pair_shape<R64x64>(d, w, s);
     case kRing64x64g2: return launch_pair_shape<R64x64g2>(d, w, s);

@@ -133,12 +133,13 @@ struct GemmArgs {
 // runs fastest on if all its workgroups are resident at once, and the estimated time, or -1.
 enum RingShape { kRing64x64, kRing64x64g2, kRing64x128, kRing64x128g2, kRing128x128, kRing96x128, kRing128x128x2, kRingShapes };
 int ring_pick(int64_t M, int64_t N, int64_t K, int cus, bool int8, double *us);
-int ring_pair_pick(int64_t M, int64_t N, int64_t K, int cus, double *us);
+int ring_pair_pick(int64_t M, int64_t N, int64_t K, int cus, int most, int *runs, double *us);
 // K split of a product on a shape: the number of runs (1: none), at most `most`
 int ring_ksplit_pick(int64_t M, int64_t N, int64_t K, int cus, int most, int *shape, double *us);
 hipError_t launch_ring(const GemmArgs &a, int shape, bool int8, hipStream_t s);
 hipError_t launch_ring_ksplit(const GemmArgs &a, int shape, int runs, hipStream_t s, hipEvent_t start);
-hipError_t launch_ring_pair(const GemmArgs &dgrad, const GemmArgs &wgrad, int shape, hipStream_t s);
+// runs > 1 (kRing128x128x2): of the weight gradient, into its scratch; start: as launch_ring_ksplit
+hipError_t launch_ring_pair(const GemmArgs &dgrad, const GemmArgs &wgrad, int shape, int runs, hipStream_t s, hipEvent_t start);
 
 // Number of fp32 penalty partials the FP8 GEMM writes for these arguments.
 int fp8_gemm_partials(const GemmArgs &a);
@@ -148,6 +149,8 @@ bool fp8_gemm_finishes(const GemmArgs &a);
 hipError_t launch_i8_gemm(const GemmArgs &a, hipStream_t s);
 // the two gradient products of a linear layer, in one launch where that is the faster way
 hipError_t launch_fp8_gemm_pair(const GemmArgs &dgrad, const GemmArgs &wgrad, hipStream_t s);
+// ... and the fp32 scratch that way needs beyond fp8_gemm_ksplit_bytes (M, N, K of the layer)
+size_t fp8_pair_bytes(int64_t M, int64_t N, int64_t K);
 
 // K split of tile-starved FP8 GEMMs (no penalty, no residual): the fp32 scratch their runs need; given
 // through sk_workspace like the stream-K scratch, which it shares.

@@ -114,6 +114,34 @@ def test_backward(shape, hybrid):
     check_bwd_pair(shape, hybrid)
 
 
+# contractions over more than 4096 rows: both products in one launch, the weight gradient in two to seven runs (a stage count
+# that they do not divide, ragged rows and not, tiles past every edge); without a workspace whole
+@pytest.mark.parametrize("hybrid", [False, True])
+@pytest.mark.parametrize("shape", [(4112, 272, 272), (8240, 880, 336), (14208, 688, 384), (12208, 2736, 400), (5248, 672, 1552)])
+def test_backward_over_many_rows(shape, hybrid):
+    check_bwd_pair(shape, hybrid)
+
+
+# scratch for fewer runs than were asked for, down to none: the bytes past it stay as they are
+@pytest.mark.parametrize("runs", [6.5, 3.0, 1.9, 0.0])
+def test_backward_over_many_rows_in_less_scratch(runs):
+    M, N, K = 8240, 880, 336
+    say("ring backward over many rows, scratch of %.1f runs" % runs)
+    x, w, dy = synth.fp8_linear_inputs(1, 0, M=M, K=K, N=N)
+    (xq, xqT, sxi), (wq, wqT, swi), (dyq, dyqT, sdi) = (oracle_quantized(t) for t in (x, w, dy))
+    whole = torch.full((tw.tweo_workspace_bytes(tw.TWEO_OP_FP8_LINEAR_BWD, M, N, K) + 4096,), 0xA5, dtype=torch.uint8, device=DEV)
+    size = 256 + int(runs * N * K * 4)
+    dx = torch.full((M, K), float("nan"), dtype=torch.bfloat16, device=DEV)
+    dw = torch.full((N, K), float("nan"), dtype=torch.bfloat16, device=DEV)
+    args = [to_dev(np.ascontiguousarray(t)) for t in (dyq, dyqT, wqT, xqT)]
+    tw.tweo_fp8_linear_bwd(args[0], args[1], scalar_f32(sdi), args[2], scalar_f32(swi), args[3], scalar_f32(sxi), M, N, K, dx, dw,
+                           whole[:size])
+    torch.cuda.synchronize()
+    assert bool((whole[size:] == 0xA5).all())
+    check_gemm(bf16_bits(dx), *oracle.fp8_linear_dgrad(dyq, wq, sdi, swi), N, "dgrad")
+    check_gemm(bf16_bits(dw), *oracle.fp8_linear_wgrad(dyq, xq, sdi, sxi), M, "wgrad")
+
+
 # the penalty finished by the last workgroup of the GEMM (up to one workgroup per CU, behind a cast that clears its sum)
 # against the finishing kernel on the same codes: the same bits, call after call, over a poisoned sum
 @pytest.mark.parametrize("shape", [(16, 16, 64), (256, 512, 512), (1024, 1024, 256), (1040, 1024, 256), (2048, 1024, 1024),

@@ -108,3 +108,13 @@ def test_a_forked_child_looks_the_stream_up_anew(monkeypatch):
         finally:
             os._exit(code)
     assert os.waitstatus_to_exitcode(os.waitpid(pid, 0)[1]) == 0
+
+
+def test_scratch_for_the_weight_gradients_of_narrow_layers():
+    # contractions beyond 4096 that a lone product would leave CUs idle under: at most eight runs beside the other product
+    for M, N, K in ((8240, 880, 336), (14208, 688, 384), (12208, 2736, 400), (15072, 768, 512), (9584, 400, 1872)):
+        runs, rest = divmod(tw.tweo_workspace_bytes(tw.TWEO_OP_FP8_LINEAR_BWD, M, N, K) - 256, N * K * 4)
+        assert 2 <= runs <= 8 and rest < 256, (M, N, K)
+    # none up to 4096, none for outputs that fill the chip
+    for M, N, K in ((4096, 336, 880), (4096, 256, 256), (8208, 4096, 4096)):
+        assert tw.tweo_workspace_bytes(tw.TWEO_OP_FP8_LINEAR_BWD, M, N, K) == 512, (M, N, K)
