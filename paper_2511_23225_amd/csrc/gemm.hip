@@ -1338,7 +1338,7 @@ static int pick_tiled(int64_t M, int64_t N, int64_t K, int forced)
 // 64-byte stage: a 128x128 tile alone on its CU 0.28, two 0.58 (streaming: 0.37; a contraction that is no
 // multiple of 64: 0.375 and 0.8, register-staged 0.57); a 256x256 tile 0.8 (1.05).  Per 128-byte stage: a
 // 256x256 tile of the deferred kernel 1.25, of the 8-wave kernel 1.45.  int8, weights from memory: a 128x128
-// streaming tile alone 0.42 (4096 -> 12288, 96 to 256 rows, 31 us; the ring kernel's 128x128 tiles 22.8).
+// streaming tile alone 0.42 (4096 -> 12288, 96 to 256 rows, 31 us; the ring kernel's 128x128 tiles 22.8), two 0.6.
 static double tiled_us(int v, int64_t M, int64_t N, int64_t K, bool int8)
 {
     const double cus = num_cus(), kt = (double)((K + 127) / 128);
@@ -1353,9 +1353,29 @@ static double tiled_us(int v, int64_t M, int64_t N, int64_t K, bool int8)
     if (v == 6)
         return (ragged ? 1.05 : 0.8) * 2.0 * kt * rounds(256, 256, cus) + 5.0;
     const bool alone = rounds(128, 128, cus) <= 1.0;
-    const double stage = v == 3 ? 0.57 : v == 13 ? (alone ? (int8 ? 0.42 : 0.28) : 0.37)
+    const double stage = v == 3 ? 0.57 : v == 13 ? (alone ? (int8 ? 0.42 : 0.28) : (int8 ? 0.6 : 0.37))
                                                  : (ragged ? (alone ? 0.375 : 0.8) : (alone ? 0.28 : 0.58));
     return stage * 2.0 * kt * rounds(128, 128, alone && v != 3 ? cus : 2.0 * cus) + 4.0;
+}
+
+// INT8, up to 128 rows into more columns than the 128x128 tiles of one round (a vocabulary): the weights' way from memory, or the
+// rounds.  The tiles on 64-byte stages are ahead of the streaming kernel's unless the rounds are nearly full under a
+// short contraction (us, 17 rows, 64-byte stages / streaming: 4096 -> 72000 83 / 97, 4096 -> 151936 142 / 158, 2048 -> 128256
+// 56 / 52, 1024 -> 256000 61 / 58).  Both within 5 % of 162 such timings, as is the weight-streaming kernel's time.
+static bool wide_output(int64_t M, int64_t N) { return M <= 128 && (N + 127) / 128 > 2 * (int64_t)num_cus(); }
+static int wide_variant(int64_t N, int64_t K)
+{
+    const double tiles = (double)((N + 127) / 128), slots = 2.0 * num_cus();
+    return K >= 4096 || tiles < 0.85 * slots * std::ceil(tiles / slots) ? 8 : 13;
+}
+static double wide_us(int v, int64_t M, int64_t N, int64_t K)
+{
+    const double rounds = std::ceil((double)((N + 127) / 128) / (2.0 * num_cus())), mb = (double)N * (double)K * 1e-6;
+    return std::max(rounds * 1.24 * (double)((K + 127) / 128), mb * ((v == 8 ? 0.205 : 0.195) + 0.0005 * (double)M)) + 3.0;
+}
+static double weight_stream_us(int64_t M, int64_t N, int64_t K)
+{
+    return (double)N * (double)K * 1e-6 * (0.169 + 40.0 / (double)K + (double)M * (0.0008 + 1.1 / (double)K)) + 3.0;
 }
 
 // The kernel a product runs on and its estimated time: the ring kernel, where all its workgroups are resident
@@ -1370,8 +1390,11 @@ static Pick pick(int64_t M, int64_t N, int64_t K, bool int8 = false)
         const int v = g_tile_override == 17 ? 4 : g_tile_override;
         return Pick{ring_shape(v) >= 0 ? v : pick_tiled(M, N, K, v), 0.0};
     }
-    const int v = pick_tiled(M, N, K, 0);
-    const double us = tiled_us(v, M, N, K, int8);
+    int v = pick_tiled(M, N, K, 0);
+    const bool wide = int8 && v == 13 && wide_output(M, N);
+    if (wide)
+        v = wide_variant(N, K);
+    const double us = wide ? wide_us(v, M, N, K) : tiled_us(v, M, N, K, int8);
     double ring_us;
     const int shape = ring_pick(M, N, K, num_cus(), int8, &ring_us);
     return ring_us < us ? Pick{ring_variant(shape), ring_us} : Pick{v, us};
@@ -2001,8 +2024,12 @@ hipError_t launch_i8_gemm(const GemmArgs &a, hipStream_t s)
     // has them for a third of the CUs (call, cold, us, streaming / ring: 4096 -> 12288 at M = 48 / 64 14.1 / 13.5,
     // 15.0 / 14.0; 2048 -> 5632 at M = 32 / 64 6.6 / 6.0, 7.3 / 6.1; with 64 and 32 tiles the stream is ahead:
     // 11008 -> 4096 at M = 64 18.2 / 29.0, 5632 -> 2048 9.2 / 10.2); above 64 rows the ring kernel throughout (M =
-    // 128, 4096 -> 11008 19.6 / 17.9, 11008 -> 4096 29.0 / 26.3, 5632 -> 2048 15.2 / 10.3, 2048 -> 5632 9.4 / 6.2).
-    const bool streaming = a.M <= 16 || (a.M <= kSkinnyMaxM && 3 * ((a.N + 63) / 64) < num_cus());
+    // 128, 4096 -> 11008 19.6 / 17.9, 11008 -> 4096 29.0 / 26.3, 5632 -> 2048 15.2 / 10.3, 2048 -> 5632 9.4 / 6.2).  Into more
+    // columns than the ring kernel has tiles for, the faster of the stream and the tiles in rounds (17 / 64 rows of 4096 ->
+    // 65544, stream 59 / 73, tiles 84 / 86; of 2048 -> 128256 59 / 73, 52 / 59).
+    const bool streaming = a.M <= 16 || (a.M <= kSkinnyMaxM && (3 * ((a.N + 63) / 64) < num_cus() ||
+                                                               (g_tile_override == 0 && wide_output(a.M, a.N) &&
+                                                                weight_stream_us(a.M, a.N, a.K) < pick(a.M, a.N, a.K, true).us)));
     if (((g_tile_override == 0 && streaming) || (g_tile_override == 17 && a.M <= kSkinnyMaxM)) && a.K % 64 == 0 && a.N % 4 == 0)
         return launch_skinny_ring_any(a, s);
     // few whole 256x256 tiles under a long contraction (prefill chunks into a narrow projection): the K

@@ -43,10 +43,12 @@ static double fabric_us(const RingRate &r, int64_t M, int64_t N, int64_t K, int6
 static double ragged_rows(int64_t K, bool covered) { return K % 128 == 0 ? 1.0 : K % 64 == 0 ? 1.25 : covered ? 1.4 : 1.7; }
 static double fabric_rate(int64_t K) { return K % 128 == 0 ? 3.0e6 : 2.5e6; }
 
-// int8: a layer's weights come from memory at every call, and workgroups in pairs then get less of them than lone
-// ones with twice the stages in flight (call, us, pairs of 64x64 tiles / 64x128 tiles alone: 128 rows of 4096 -> 12288
-// 21.4 / 18.7, 512 of 11008 -> 4096 44.9 / 38.2; 48 shapes of 40 to 512 rows 1.03 times as fast as with one rate for
-// all, weights cold or in the caches)
+// int8: a layer's weights come from memory at every call.  Under one or two rows of tiles each line is fetched once and
+// streams, the better the more of them are in flight (17 rows of 4096 -> 32000 23.6 us on 64x64 tiles, 64 rows of 8192 -> 28672
+// 43 on 64x128; 17 rows of 4096 -> 11008 on 64x64 tiles with four stages 12.1, with eight 11.0); under more, workgroups in
+// pairs get less of them than lone ones with twice the stages in flight (call, us, pairs of 64x64 tiles / 64x128 tiles
+// alone: 128 rows of 4096 -> 12288 21.4 / 18.7, 512 of 11008 -> 4096 44.9 / 38.2).  800 timings of 17 to 512 rows, weights
+// cold and in the caches: 1 % behind the fastest kernel in the geometric mean, 5 % with one rate for all.
 int ring_pick(int64_t M, int64_t N, int64_t K, int cus, bool int8, double *us)
 {
     int best = -1;
@@ -56,9 +58,16 @@ int ring_pick(int64_t M, int64_t N, int64_t K, int cus, bool int8, double *us)
         const int64_t tiles = ((M + r.bm - 1) / r.bm) * ((N + r.bn - 1) / r.bn);
         if (tiles > (int64_t)r.per_cu * cus)
             continue;
-        const double ragged = !int8 ? ragged_rows(K, false) : K % 128 != 0 ? 1.1 : 1.0;
-        const double rate = !int8 ? fabric_rate(K) : tiles > cus ? 2.6e6 : 3.0e6;
-        const double t = std::max(r.launch + (tiles <= cus ? r.one : r.two) * (double)((K + 127) / 128) * ragged,
+        const bool lone = tiles <= cus;
+        double stage = lone ? r.one : r.two, rate = fabric_rate(K);
+        if (int8) {
+            const int64_t rows = (M + r.bm - 1) / r.bm;
+            stage *= K % 128 != 0 ? 1.21 : 1.1;
+            rate = rows == 1 ? (i == kRing64x64g2 || i == kRing64x128g2 ? 6.5e6 : 5.5e6) : rows == 2 ? 5.0e6 : lone ? 3.0e6 : 2.6e6;
+        } else {
+            stage *= ragged_rows(K, false);
+        }
+        const double t = std::max(r.launch + stage * (double)((K + 127) / 128),
                                   fabric_us(r, M, N, K, tiles, 1, rate));
         if (t < *us) {
             *us = t;

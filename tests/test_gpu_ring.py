@@ -229,3 +229,20 @@ def test_calls_in_flight_may_share_a_sum(shape):
         for k in range(2):
             assert torch.equal(a["states"][k].view(torch.int32), b["states"][k].view(torch.int32))
         assert int(b["states"][0].view(torch.int32)[19]) == 40 % 16
+
+
+# INT8 into more columns than the ring kernel has tiles resident for: the stream, 64-byte stages and the streaming kernel, as
+# estimated, on both sides of a round of 128x128 tiles
+@pytest.mark.parametrize("shape", [(33, 66048, 4096), (65, 66048, 512), (64, 65536, 1024), (48, 131080, 1024), (17, 32000, 2048), (128, 66056, 1088)])
+def test_int8_into_wide_outputs(shape):
+    M, N, K = shape
+    say("ring INT8 wide M=%d N=%d K=%d" % (M, N, K))
+    g = torch.Generator(device=DEV)
+    g.manual_seed(N + K)
+    xq, wq = (torch.randint(-127, 128, (n, K), generator=g, device=DEV, dtype=torch.int8) for n in (M, N))
+    y = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device=DEV)
+    tw.tweo_w8a8_linear(xq, wq, 0.001, y)
+    rows = torch.cat([torch.arange(64), torch.randint(0, N, (512,)), torch.arange(N - 64, N)]).to(DEV)
+    torch.cuda.synchronize()
+    want = oracle.w8a8_linear(xq.cpu().numpy(), wq[rows].cpu().numpy(), 0.001)
+    assert np.array_equal(bf16_bits(y[:, rows].contiguous()), want) and not bool(y.isnan().any())
