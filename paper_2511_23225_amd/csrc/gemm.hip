@@ -1718,9 +1718,13 @@ static int i8_defer_ksplit(int64_t M, int64_t N, int64_t K)
     return runs > 1 && ring_us(M, N, K, true) < kKsplitBias * ksplit_us(M, N, K, runs, true) ? 1 : runs;
 }
 
-// INT8, between decode and prefill sizes: the scratch that such products are given.  Outputs of few 128x128 tiles
-// were once split over K in it; the ring kernel needs none (quantise + linear 11008 -> 4096 at M = 384 37.8 us
-// split, 30.4 now), and what a program has planned with stays what it was.
+// INT8, between decode and prefill sizes: an output of few 128x128 tiles leaves CUs idle, so `runs` workgroups share a
+// tile on the direct-to-LDS kernel, int32 runs added exactly by the reduce kernel.  The scratch that is asked for
+// follows the first rule (a tile alone on its CU 0.29 us a 64-byte stage, 0.135 and 0.26 for 64x64 tiles, runs written
+// and read at 4 TB/s, 4 us for the second launch); the runs are taken where they are the faster way today.  The ring
+// kernel is ahead up to contractions of about 10000 in whole lines, the runs under longer and ragged ones (us, weights cold,
+// ring / runs: 384 rows of 11008 -> 4096 30 / 38, 374 of 13056 -> 256 27.6 / 20.0, 190 of 8976 -> 880 32.8 / 20.0, 227 of 15760 ->
+// 504 53 / 26; 300 timings of such shapes: 14 more than 4 % slower than with runs throughout, 99 without).
 static int i8_dma_runs(int64_t M, int64_t N, int64_t K)
 {
     if (g_tile_override != 0 || N % 8 != 0 || M <= 128)
@@ -1741,6 +1745,13 @@ static int i8_dma_runs(int64_t M, int64_t N, int64_t K)
         }
     }
     return best;
+}
+
+static double i8_dma_us(int64_t M, int64_t N, int64_t K, int runs)
+{
+    const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128), cus = num_cus();
+    return (K % 64 != 0 ? 0.35 : 0.38) * (double)((tiles * runs + cus - 1) / cus) * (double)(((K + 63) / 64 + runs - 1) / runs) +
+           (double)runs * (double)M * (double)N * 8.0 / 4e6 + 7.0;
 }
 
 size_t i8_gemm_ksplit_bytes(int64_t M, int64_t N, int64_t K)
@@ -2039,6 +2050,11 @@ hipError_t launch_i8_gemm(const GemmArgs &a, hipStream_t s)
         if (splits > 1 && a.sk_workspace != nullptr && ((uintptr_t)a.sk_workspace & 15u) == 0 &&
             a.sk_workspace_bytes >= (size_t)splits * (size_t)a.M * (size_t)a.N * sizeof(int32_t))
             return launch_ksplit_defer<false, true>(a, s, splits);
+        const int runs = i8_dma_runs(a.M, a.N, a.K);
+        if (runs > 1 && a.sk_workspace != nullptr && ((uintptr_t)a.sk_workspace & 15u) == 0 &&
+            a.sk_workspace_bytes >= (size_t)runs * (size_t)a.M * (size_t)a.N * sizeof(int32_t) &&
+            i8_dma_us(a.M, a.N, a.K, runs) < pick(a.M, a.N, a.K, true).us)
+            return launch_ksplit<D128x128w4, false, true>(a, s, runs);
     }
     return launch_gemm<true>(a, s);
 }

@@ -38,8 +38,7 @@ static double fabric_us(const RingRate &r, int64_t M, int64_t N, int64_t K, int6
 
 // Rows that are no whole number of lines: a stage of one lies across two.  A lone product waits for that, runs of K and
 // several rounds of tiles less (1260 timings of backward calls of 256 to 50432 rows, operands cold and in the caches;
-// weight gradients over 8208 rows instead of 8192, 768x768 28.5 us / 18.6, 768x2304 41 / 28; INT8, a few hundred
-// rows: 1.1).  The lines come at 2.5 TB/s in the place of 3.
+// weight gradients over 8208 rows instead of 8192, 768x768 28.5 us / 18.6, 768x2304 41 / 28).  The lines come at 2.5 TB/s in the place of 3.
 static double ragged_rows(int64_t K, bool covered) { return K % 128 == 0 ? 1.0 : K % 64 == 0 ? 1.25 : covered ? 1.4 : 1.7; }
 static double fabric_rate(int64_t K) { return K % 128 == 0 ? 3.0e6 : 2.5e6; }
 
@@ -62,12 +61,10 @@ int ring_pick(int64_t M, int64_t N, int64_t K, int cus, bool int8, double *us)
         double stage = lone ? r.one : r.two, rate = fabric_rate(K);
         if (int8) {
             const int64_t rows = (M + r.bm - 1) / r.bm;
-            stage *= K % 128 != 0 ? 1.21 : 1.1;
+            stage *= 1.1;
             rate = rows == 1 ? (i == kRing64x64g2 || i == kRing64x128g2 ? 6.5e6 : 5.5e6) : rows == 2 ? 5.0e6 : lone ? 3.0e6 : 2.6e6;
-        } else {
-            stage *= ragged_rows(K, false);
         }
-        const double t = std::max(r.launch + stage * (double)((K + 127) / 128),
+        const double t = std::max(r.launch + stage * ragged_rows(K, false) * (double)((K + 127) / 128),
                                   fabric_us(r, M, N, K, tiles, 1, rate));
         if (t < *us) {
             *us = t;

@@ -248,3 +248,9 @@ def test_w8a8_k_split_of_128_row_tiles(shape):
         tw.tweo_w8a8_linear(to_dev(xq), to_dev(wq), 0.001, y, w)
         torch.cuda.synchronize()
         assert np.array_equal(bf16_bits(y), want)
+
+
+# contractions long or ragged enough for the runs to be the faster way: the last one of two stages fewer, inside a stage
+@pytest.mark.parametrize("shape", [(190, 8976, 880), (374, 13056, 256), (134, 7280, 160), (227, 15760, 504)])
+def test_w8a8_k_split_under_long_contractions(shape):
+    test_w8a8_k_split_of_128_row_tiles(shape)
