@@ -44,7 +44,8 @@ static double fabric_rate(int64_t K) { return K % 128 == 0 ? 3.0e6 : 2.5e6; }
 
 // int8: a layer's weights come from memory at every call.  Under one or two rows of tiles each line is fetched once and
 // streams, the better the more of them are in flight (17 rows of 4096 -> 32000 23.6 us on 64x64 tiles, 64 rows of 8192 -> 28672
-// 43 on 64x128; 17 rows of 4096 -> 11008 on 64x64 tiles with four stages 12.1, with eight 11.0); under more, workgroups in
+// 43 on 64x128; 17 rows of 4096 -> 11008 on 64x64 tiles with four stages 12.1, with eight 11.0; at 64 rows the same, and in
+// the caches 9.8, 10.5); under more, workgroups in
 // pairs get less of them than lone ones with twice the stages in flight (call, us, pairs of 64x64 tiles / 64x128 tiles
 // alone: 128 rows of 4096 -> 12288 21.4 / 18.7, 512 of 11008 -> 4096 44.9 / 38.2).  800 timings of 17 to 512 rows, weights
 // cold and in the caches: 1 % behind the fastest kernel in the geometric mean, 5 % with one rate for all.
@@ -62,7 +63,8 @@ int ring_pick(int64_t M, int64_t N, int64_t K, int cus, bool int8, double *us)
         if (int8) {
             const int64_t rows = (M + r.bm - 1) / r.bm;
             stage *= 1.1;
-            rate = rows == 1 ? (i == kRing64x64g2 || i == kRing64x128g2 ? 6.5e6 : 5.5e6) : rows == 2 ? 5.0e6 : lone ? 3.0e6 : 2.6e6;
+            const bool deep = M <= 48 && (i == kRing64x64g2 || i == kRing64x128g2);
+            rate = rows == 1 ? (deep ? 6.5e6 : 5.5e6) : rows == 2 ? 5.0e6 : lone ? 3.0e6 : 2.6e6;
         }
         const double t = std::max(r.launch + stage * ragged_rows(K, false) * (double)((K + 127) / 128),
                                   fabric_us(r, M, N, K, tiles, 1, rate));
