@@ -157,3 +157,42 @@ def test_states_are_updated_behind_the_gemm(how):
             newest = int(states[k].view(torch.int32)[19]) - 1 & 15
             want = torch.stack([states[k][newest], states[k][tw.DELAYED_USED_SCALE], states[k][tw.DELAYED_USED_SCALE_INV]])
             assert torch.equal(sc[3 * k:3 * k + 3].view(torch.int32), want.view(torch.int32)), (step, k)
+
+
+# the same behind the kernels that leave the penalty to a finishing launch (more tiles than CUs: streaming, and the
+# deferred epilogue without and with a residual), and behind the ring kernel with one: the update rides on that launch
+@pytest.mark.parametrize("residual", [False, True])
+@pytest.mark.parametrize("shape", [(4096, 256, 4096), (4096, 512, 4096), (4096, 2048, 4096), (2064, 272, 2080), (512, 2560, 512)])
+def test_states_are_updated_with_the_penaltys_end(shape, residual):
+    M, K, N = shape
+    print("delayed forward, update with the penalty's end: M=%d K=%d N=%d residual=%s" % (M, K, N, residual), flush=True)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(11)
+    u8 = lambda *s: torch.zeros(s, dtype=torch.uint8, device=DEV)
+    states = [torch.zeros(tw.DELAYED_STATE_WORDS, dtype=torch.float32, device=DEV) for _ in range(4)]
+    for st in states:
+        tw.tweo_delayed_state_init(st)
+    sc = torch.zeros(16, dtype=torch.float32, device=DEV)
+    xq, xqT, wq, wqT, q = u8(M, K), u8(K, M), u8(N, K), u8(K, N), u8(max(M, N), K)
+    saved = tw.make_saved(xq, xqT, wq, wqT, sc)
+    y, y2 = (torch.empty((M, N), dtype=torch.bfloat16, device=DEV) for _ in range(2))
+    r = torch.randn((M, N), generator=g, device=DEV).bfloat16() if residual else None
+    S, S2 = (torch.zeros(1, dtype=torch.float64, device=DEV) for _ in range(2))
+    ws = torch.empty(tw.tweo_workspace_bytes(tw.TWEO_OP_FP8_LINEAR_FWD_BF16, M, N, K), dtype=torch.uint8, device=DEV)
+    for step in range(4):
+        x = (torch.randn((M, K), generator=g, device=DEV) * (1 + step % 3)).bfloat16()
+        w = (torch.randn((N, K), generator=g, device=DEV) * 0.02 * (1 + step % 2)).bfloat16()
+        S.view(torch.int64).fill_(0x5555555555555555)
+        sc[15:].view(torch.int32).fill_(-1)
+        tw.tweo_fp8_linear_fwd_bf16_delayed(x, w, y, saved, states[0], states[1], bootstrap=step == 0, residual_bf16=r, pen=PEN,
+                                            penalty_sum=S, workspace=ws)
+        tw.tweo_quantize_e4m3_delayed(x, states[2], q[:M], None, bootstrap=step == 0)
+        tw.tweo_quantize_e4m3_delayed(w, states[3], q[:N], None, bootstrap=step == 0)
+        tw.tweo_fp8_linear_fwd(xq, sc[2:3], wq, sc[5:6], y2, residual_bf16=r, pen=PEN, penalty_sum=S2, workspace=ws)
+        torch.cuda.synchronize()
+        for k in (0, 1):
+            assert torch.equal(states[k].view(torch.int32), states[k + 2].view(torch.int32)), (step, k)
+            newest = int(states[k].view(torch.int32)[19]) - 1 & 15
+            want = torch.stack([states[k][newest], states[k][tw.DELAYED_USED_SCALE], states[k][tw.DELAYED_USED_SCALE_INV]])
+            assert torch.equal(sc[3 * k:3 * k + 3].view(torch.int32), want.view(torch.int32)), (step, k)
+        assert torch.equal(y, y2) and torch.equal(S.view(torch.int64), S2.view(torch.int64)), step

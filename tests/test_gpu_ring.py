@@ -142,6 +142,28 @@ def test_backward_over_many_rows_in_less_scratch(runs):
     check_gemm(bf16_bits(dw), *oracle.fp8_linear_wgrad(dyq, xq, sdi, sxi), M, "wgrad")
 
 
+def penalised_layer(seed, M, N, K, delayed):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    u8 = lambda *s: torch.zeros(s, dtype=torch.uint8, device=DEV)
+    t = dict(x=torch.randn((M, K), generator=g, device=DEV).bfloat16(), w=(torch.randn((N, K), generator=g, device=DEV) * 0.1).bfloat16(),
+             y=torch.empty((M, N), dtype=torch.bfloat16, device=DEV), sc=torch.full((16,), 7.0, dtype=torch.float32, device=DEV),
+             codes=[u8(M, K), u8(K, M), u8(N, K), u8(K, N)], ws=workspace(tw.TWEO_OP_FP8_LINEAR_FWD_BF16, M, N, K))
+    t["saved"] = tw.make_saved(*t["codes"], t["sc"])
+    if delayed:
+        t["states"] = [torch.zeros(tw.DELAYED_STATE_WORDS, dtype=torch.float32, device=DEV) for _ in range(2)]
+        for st in t["states"]:
+            tw.tweo_delayed_state_init(st)
+    return t
+
+
+def forward(t, S, **more):
+    if "states" in t:
+        tw.tweo_fp8_linear_fwd_bf16_delayed(t["x"], t["w"], t["y"], t["saved"], *t["states"], pen=PEN, penalty_sum=S, workspace=t["ws"], **more)
+    else:
+        tw.tweo_fp8_linear_fwd_bf16(t["x"], t["w"], t["y"], t["saved"], pen=PEN, penalty_sum=S, workspace=t["ws"], **more)
+
+
 # the penalty finished by the last workgroup of the GEMM (up to one workgroup per CU, behind a cast that clears its sum)
 # against the finishing kernel on the same codes: the same bits, call after call, over a poisoned sum
 @pytest.mark.parametrize("shape", [(16, 16, 64), (256, 512, 512), (1024, 1024, 256), (1040, 1024, 256), (2048, 1024, 1024),
@@ -169,26 +191,30 @@ def test_penalty_finished_by_the_last_workgroup(shape):
         S.fill_(float("nan"))
 
 
-def penalised_layer(seed, M, N, K, delayed):
+# ... on every tile shape (two groups of waves, one of which has left by then, 96 and 128 rows), edges and whole tiles, with
+# a residual; what the counter and the sum held before does not matter
+@pytest.mark.parametrize("tile", RING, indirect=True)
+@pytest.mark.parametrize("residual", [False, True])
+@pytest.mark.parametrize("shape", [(16, 16, 64), (208, 272, 528), (384, 512, 1152)])
+def test_penalty_finished_on_every_shape(shape, residual, tile):
+    M, N, K = shape
+    say("ring penalty finish M=%d N=%d K=%d residual=%s tile=%d" % (shape + (residual, tile)))
+    t = penalised_layer(M + N, M, N, K, False)
     g = torch.Generator(device=DEV)
-    g.manual_seed(seed)
-    u8 = lambda *s: torch.zeros(s, dtype=torch.uint8, device=DEV)
-    t = dict(x=torch.randn((M, K), generator=g, device=DEV).bfloat16(), w=(torch.randn((N, K), generator=g, device=DEV) * 0.1).bfloat16(),
-             y=torch.empty((M, N), dtype=torch.bfloat16, device=DEV), sc=torch.full((16,), 7.0, dtype=torch.float32, device=DEV),
-             codes=[u8(M, K), u8(K, M), u8(N, K), u8(K, N)], ws=workspace(tw.TWEO_OP_FP8_LINEAR_FWD_BF16, M, N, K))
-    t["saved"] = tw.make_saved(*t["codes"], t["sc"])
-    if delayed:
-        t["states"] = [torch.zeros(tw.DELAYED_STATE_WORDS, dtype=torch.float32, device=DEV) for _ in range(2)]
-        for st in t["states"]:
-            tw.tweo_delayed_state_init(st)
-    return t
-
-
-def forward(t, S, **more):
-    if "states" in t:
-        tw.tweo_fp8_linear_fwd_bf16_delayed(t["x"], t["w"], t["y"], t["saved"], *t["states"], pen=PEN, penalty_sum=S, workspace=t["ws"], **more)
-    else:
-        tw.tweo_fp8_linear_fwd_bf16(t["x"], t["w"], t["y"], t["saved"], pen=PEN, penalty_sum=S, workspace=t["ws"], **more)
+    g.manual_seed(K)
+    r = torch.randn((M, N), generator=g, device=DEV).bfloat16() if residual else None
+    y2 = torch.empty((M, N), dtype=torch.bfloat16, device=DEV)
+    S, S2 = (torch.zeros(1, dtype=torch.float64, device=DEV) for _ in range(2))
+    for poison in (0x5555555555555555, -1, 0):
+        S.view(torch.int64).fill_(poison)
+        t["sc"][15:].view(torch.int32).fill_(poison >> 32)
+        forward(t, S, residual_bf16=r)
+        tw.tweo_fp8_linear_fwd(t["codes"][0], t["sc"][2:3], t["codes"][2], t["sc"][5:6], y2, residual_bf16=r, pen=PEN, penalty_sum=S2,
+                               workspace=t["ws"])
+        torch.cuda.synchronize()
+        assert torch.equal(t["y"], y2) and S.item() > 0.0
+        assert torch.equal(S.view(torch.int64), S2.view(torch.int64)) and t["sc"][15:].view(torch.int32).item() == 0
+        t["x"].mul_(1.25)
 
 
 # an argument that is refused only behind the cast: nothing has written the sum by then
