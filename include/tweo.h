@@ -417,7 +417,8 @@ tweo_status tweo_fp8_linear_bwd_bf16_hybrid(const void *dy_bf16, const tweo_fp8_
  * history (tweo_quantize_e4m3_delayed).  state_x, state_w, state_dy: one
  * delayed-scaling state per scaled tensor (tweo_delayed_state_init), distinct;
  * bootstrap != 0 on the first call on those states.  The activation and the weight
- * share one cast launch and one state-update launch.  saved->scalars receives, as
+ * share one cast launch; their states are updated in one launch, which with a penalty
+ * is the one that ends it, behind the GEMM.  saved->scalars receives, as
  * under current scaling, amax / scale used / its inverse of x (words 0-2), w (3-5)
  * and, by the backward call, dy (6-8).  dy_e5m2 = 1 casts the gradient to E5M2
  * (HYBRID), 0 to E4M3.  Shapes, workspace (that of tweo_fp8_linear_fwd /

@@ -1770,9 +1770,10 @@ size_t fp8_gemm_ksplit_bytes(int64_t M, int64_t N, int64_t K)
     return splits > 1 ? (size_t)splits * (size_t)M * (size_t)N * sizeof(float) : 0;
 }
 
-// The pair of gradient products of a layer in one launch: the shape, or -1 where they run one after the other, and the runs
-// of the weight gradient (1: whole).  scratch: what both have for runs.  Up to eight runs of contractions beyond 4096 (with more the sums weigh more than they are worth);
-// no more than the weight gradient would have by itself, if it has any (so scratch is asked for by one rule or the other).
+// The pair of gradient products of a layer in one launch: the shape, or -1 where they run one after the other, and the
+// runs of the weight gradient (1: whole).  scratch: what both have for runs.  Up to eight runs of contractions beyond
+// 4096 (16 were 1 % slower over 472 timings), but no more than the weight gradient would have by itself, if it has any:
+// scratch is asked for by one rule or the other.
 constexpr int kPairRuns = 8;
 static int pick_pair(int64_t M, int64_t N, int64_t K, size_t scratch, int *runs)
 {
@@ -1896,8 +1897,8 @@ hipError_t launch_fp8_gemm_pair(const GemmArgs &d, const GemmArgs &w, hipStream_
     if (g_tile_override == 0 && g_stream_k_off && !overlap(w.out, w.M * w.N * 2, d.A, d.M * d.K) &&
         !overlap(w.out, w.M * w.N * 2, d.B, d.N * d.K)) {
         // in one launch where that is the faster way: a launch less, and no half-empty chip (1024x1024 -> 1024 8.4 us on
-        // 64-byte stages, 6.0; 2048x1024 -> 1024 12.8, 9.2; operands cold, 128x128 tiles in rounds,
-        // 5920x1536 -> 2816 89 apart, 73; the weight gradient in runs among them, 8240x336 -> 880 37, 25, 10928x1872 -> 352 52, 40)
+        // 64-byte stages, 6.0; 2048x1024 -> 1024 12.8, 9.2; operands cold, 128x128 tiles in rounds, 5920x1536 -> 2816 89
+        // apart, 73; the weight gradient in runs among them, 8240x336 -> 880 37, 21, 10928x1872 -> 352 52, 40)
         int runs = 1;
         const int shape = pick_pair(d.M, d.K, d.N, split_scratch(w), &runs);
         if (shape >= 0 && runs == 1)

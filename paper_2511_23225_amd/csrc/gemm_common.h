@@ -151,7 +151,8 @@ static inline void launch_gemm_kernel(KERNEL kernel, dim3 grid, dim3 block, size
     }
 }
 
-// Outputs that the tiled kernels' epilogue writes through the L2s (store_through): whole lines, 4 to 16 MB.  What
+// Outputs that the tiled kernels' epilogue writes through the L2s (store_through): rows of whole lines (of which a wave
+// of 32 columns writes halves), 4 to 16 MB.  What
 // is dirty when a kernel ends is written back before the next one starts (2.4 us to it instead of 1.0 at 12
 // MB).  us, dirty / through: 8192x768 under 768 9.2 / 8.3, under 3072 22.4 / 20.7; 4096x1024 under 1024 9.1 / 8.5;
 // 2048x2048 under 2048 13.7 / 13.2.  Larger ones do not gain: 8192x2304 under 768 25.4 / 25.6, with the

@@ -130,7 +130,8 @@ struct GemmArgs {
 };
 
 // The ring GEMM (gemm_ring.h): tile shapes; the one that a product (a layer's two gradient products in one launch)
-// runs fastest on if all its workgroups are resident at once, and the estimated time, or -1.
+// runs fastest on if all its workgroups are resident at once (the pair: also in rounds of 128x128 tiles, the weight
+// gradient in up to `most` runs), and the estimated time, or -1.
 enum RingShape { kRing64x64, kRing64x64g2, kRing64x128, kRing64x128g2, kRing128x128, kRing96x128, kRing128x128x2, kRingShapes };
 int ring_pick(int64_t M, int64_t N, int64_t K, int cus, bool int8, double *us);
 int ring_pair_pick(int64_t M, int64_t N, int64_t K, int cus, int most, int *runs, double *us);
