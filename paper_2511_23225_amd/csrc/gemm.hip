@@ -1947,7 +1947,8 @@ static hipError_t launch_fp8_gemm_e5m2(const GemmArgs &a, hipStream_t s)
 
 hipError_t launch_fp8_gemm(const GemmArgs &a, hipStream_t s)
 {
-    if (a.p == 0 && a.residual == nullptr && split_scratch(a) != 0) {
+    const size_t asked = a.p == 0 && a.residual == nullptr ? fp8_gemm_ksplit_bytes(a.M, a.N, a.K) : 0;
+    if (asked != 0 && split_scratch(a) >= asked) {
         const Split split = pick_split(a.M, a.N, a.K, split_scratch(a));
         if (split.way != kWhole) {
             if (split.way == kDeferRuns)
