@@ -526,7 +526,8 @@ tweo_status tweo_set_gemm_tile(int variant);
  * (events recorded on the stream around a call also time the gap that recording
  * them opens in front of the kernel).  A GEMM of two kernels (a K split and the addition
  * of its runs), and both products of a narrow layer's backward where they share a launch,
- * record one pair: start of the first kernel, end of the last.  `events`: host array of 2 * pairs
+ * record one pair: start of the first kernel, end of the last (of a layer of whole 256x256
+ * tiles: one pair for both products, one for the addition of runs, if there are any).  `events`: host array of 2 * pairs
  * hipEvent_t handles created by the caller with timing enabled; at most 8
  * pairs; pairs = 0 cancels.  Process-wide, not thread safe.  Returns
  * TWEO_ERR_INVALID_ARG for a null handle, TWEO_ERR_UNSUPPORTED for more than 8

@@ -1770,20 +1770,49 @@ size_t fp8_gemm_ksplit_bytes(int64_t M, int64_t N, int64_t K)
     return splits > 1 ? (size_t)splits * (size_t)M * (size_t)N * sizeof(float) : 0;
 }
 
+// Time of a product by itself, for the choice between that and the pair on the deferred kernel: with what a tile costs beside
+// its stages (tiled_us, which compares kernels on one product, leaves it out): two stages on the deferred
+// kernel, 3 us on the 128x128 streaming tiles (8192x3072 under 768 27 us, 8192x768 under 768 10.5).
+static double apart_us(int64_t M, int64_t N, int64_t K, const Split &split)
+{
+    const int v = split.way == kWhole ? pick(M, N, K).v : 0;
+    auto rounds = [&](int64_t tr, int64_t tc, int64_t slots) { return std::ceil((double)(((M + tr - 1) / tr) * ((N + tc - 1) / tc)) / (double)slots); };
+    if (v == 15 || v == 16)
+        return split.us + 1.27 * 2.0 * (v == 15 ? 1.0 : 0.77) * rounds(v == 15 ? 256 : 192, 256, num_cus());
+    return v == 13 ? split.us + 3.0 * rounds(128, 128, 2 * num_cus()) : split.us;
+}
+
 // The pair of gradient products of a layer in one launch: the shape, or -1 where they run one after the other, and the
 // runs of the weight gradient (1: whole).  scratch: what both have for runs.  Up to eight runs of contractions beyond
 // 4096 (16 were 1 % slower over 472 timings), but no more than the weight gradient would have by itself, if it has any:
 // scratch is asked for by one rule or the other.
 constexpr int kPairRuns = 8;
-static int pick_pair(int64_t M, int64_t N, int64_t K, size_t scratch, int *runs)
+struct Pair {
+    int shape;        // of the ring kernel, or -1
+    int runs;
+    DeferPair defer;  // .runs != 0: on the deferred kernel
+};
+static Pair pick_pair(int64_t M, int64_t N, int64_t K, size_t scratch)
 {
+    Pair pair{-1, 1, {}};
     const size_t run = (size_t)N * (size_t)K * sizeof(float), asked = fp8_gemm_ksplit_bytes(N, K, M);
     const size_t fit = (asked != 0 ? std::min(scratch, asked) : scratch) / run;
     double us;
-    const int shape = ring_pair_pick(M, N, K, num_cus(), M > 4096 ? (int)std::min<size_t>(fit, kPairRuns) : 1, runs, &us);
+    const int shape = ring_pair_pick(M, N, K, num_cus(), M > 4096 ? (int)std::min<size_t>(fit, kPairRuns) : 1, &pair.runs, &us);
+    const Split dx = pick_split(M, K, N, scratch), dw = pick_split(N, K, M, scratch);
     // (the one launch's time is the surer one: this was right oftener than 1, see ragged_rows)
     const double sure = shape == kRing128x128x2 ? 0.97 : 0.94;
-    return shape >= 0 && sure * us < pick_split(M, K, N, scratch).us + pick_split(N, K, M, scratch).us ? shape : -1;
+    if (shape >= 0 && sure * us < dx.us + dw.us)
+        pair.shape = shape;
+    // The ring kernel's time is an estimate over operands in the caches and cold, and 5 to 35 % low for layers as large as
+    // these; over 162 layers of 1024 to 50432 rows, operands cold, the deferred pair below these lines was
+    // 1.07 times as fast as what ran before (1.073 had it always been chosen rightly), one layer 3 % slower, 4 more than 4 %
+    // faster left out
+    const double others = pair.shape >= 0 ? 1.15 * us : 1.1 * (apart_us(M, K, N, dx) + apart_us(N, K, M, dw));
+    pair.defer = defer_pair_pick(M, N, K, num_cus(), (int)std::min<size_t>(fit, kDeferPairRuns));
+    if (pair.defer.runs != 0 && pair.defer.us >= others)
+        pair.defer.runs = 0;
+    return pair;
 }
 
 size_t fp8_pair_bytes(int64_t M, int64_t N, int64_t K)
@@ -1791,8 +1820,8 @@ size_t fp8_pair_bytes(int64_t M, int64_t N, int64_t K)
     if (g_tile_override != 0 || !g_stream_k_off || M <= 4096 || fp8_gemm_ksplit_bytes(N, K, M) != 0)
         return 0;
     const size_t run = (size_t)N * (size_t)K * sizeof(float);
-    int runs = 1;
-    return pick_pair(M, N, K, kPairRuns * run, &runs) >= 0 && runs > 1 ? (size_t)runs * run : 0;
+    const Pair pair = pick_pair(M, N, K, kPairRuns * run);  // (the deferred kernel's pair makes do with what is asked for)
+    return pair.shape >= 0 && pair.runs > 1 ? (size_t)pair.runs * run : 0;
 }
 
 // the second launch of a K split whose runs lie as the output does
@@ -1837,6 +1866,22 @@ static hipError_t launch_ksplit(const GemmArgs &a, hipStream_t s, int splits)
     return e != hipSuccess ? e : launch_splitk_reduce<INT8>(a, splits, s, e1);
 }
 
+// the second launch of a K split on the deferred-epilogue kernel's tiles
+template <bool INT8>
+static hipError_t launch_splitk_reduce_defer(const GemmArgs &a, int splits, hipStream_t s, hipEvent_t start, hipEvent_t end)
+{
+    const int tiles_m = (int)(a.M / 256), tiles_n = (int)(a.N / 256);
+    const dim3 grid((unsigned)(tiles_m * tiles_n * 8));
+    if (end != nullptr)
+        hipExtLaunchKernelGGL(splitk_reduce_defer_kernel<INT8>, grid, dim3(256), 0, s, start, end, 0,
+                              (const float4 *)a.sk_workspace, splits, tiles_m, tiles_n, (int)a.N, a.s0, a.s1, a.alpha,
+                              (uint16_t *)a.out);
+    else
+        hipLaunchKernelGGL(splitk_reduce_defer_kernel<INT8>, grid, dim3(256), 0, s, (const float4 *)a.sk_workspace, splits,
+                           tiles_m, tiles_n, (int)a.N, a.s0, a.s1, a.alpha, (uint16_t *)a.out);
+    return hipGetLastError();
+}
+
 template <bool A_E5M2, bool INT8 = false>
 static hipError_t launch_ksplit_defer(const GemmArgs &a, hipStream_t s, int splits)
 {
@@ -1863,7 +1908,7 @@ static hipError_t launch_ksplit_defer(const GemmArgs &a, hipStream_t s, int spli
     g.ksplit = splits;
     g.ksplit_out = (float *)a.sk_workspace;
     const int n_tiles = g.tiles_m * g.tiles_n;
-    const dim3 grid((unsigned)(n_tiles * splits)), block(T::THREADS), rgrid((unsigned)(n_tiles * 8));
+    const dim3 grid((unsigned)(n_tiles * splits)), block(T::THREADS);
     hipEvent_t e0 = nullptr, e1 = nullptr;  // a profiled launch brackets both kernels
     take_profile_events(&e0, &e1);
     if (e0 != nullptr)
@@ -1871,20 +1916,26 @@ static hipError_t launch_ksplit_defer(const GemmArgs &a, hipStream_t s, int spli
                               nullptr, 0, g);
     else
         hipLaunchKernelGGL((gemm_nt_defer_kernel<INT8, 0, 3, 4, A_E5M2, true, true>), grid, block, T::LDS_BYTES, s, g);
-    if (e1 != nullptr)
-        hipExtLaunchKernelGGL(splitk_reduce_defer_kernel<INT8>, rgrid, dim3(256), 0, s, nullptr, e1, 0,
-                              (const float4 *)g.ksplit_out, splits, g.tiles_m, g.tiles_n, g.N, a.s0, a.s1, a.alpha,
-                              (uint16_t *)a.out);
-    else
-        hipLaunchKernelGGL(splitk_reduce_defer_kernel<INT8>, rgrid, dim3(256), 0, s, (const float4 *)g.ksplit_out, splits,
-                           g.tiles_m, g.tiles_n, g.N, a.s0, a.s1, a.alpha, (uint16_t *)a.out);
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : launch_splitk_reduce_defer<INT8>(a, splits, s, nullptr, e1);
 }
 
 // bytes that a launch may leave runs of a K split in
 static size_t split_scratch(const GemmArgs &a)
 {
     return a.sk_workspace != nullptr && ((uintptr_t)a.sk_workspace & 15u) == 0 ? a.sk_workspace_bytes : 0;
+}
+
+// the deferred kernel's two products in one launch; runs of the weight gradient are added by a second one, which takes a pair
+// of profile events of its own
+static hipError_t launch_defer_pair(const GemmArgs &d, const GemmArgs &w, const DeferPair &pair, hipStream_t s)
+{
+    const hipError_t e = launch_defer_pair_products(d, w, pair, s);
+    if (e != hipSuccess || pair.runs == 1)
+        return e;
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    take_profile_events(&e0, &e1);
+    return launch_splitk_reduce_defer<false>(w, pair.runs, s, e0, e1);
 }
 
 // both gradient products of a layer (d: [M, K] over N, w: [N, K] over M, no penalty, no residual)
@@ -1899,15 +1950,16 @@ hipError_t launch_fp8_gemm_pair(const GemmArgs &d, const GemmArgs &w, hipStream_
         // in one launch where that is the faster way: a launch less, and no half-empty chip (1024x1024 -> 1024 8.4 us on
         // 64-byte stages, 6.0; 2048x1024 -> 1024 12.8, 9.2; operands cold, 128x128 tiles in rounds, 5920x1536 -> 2816 89
         // apart, 73; the weight gradient in runs among them, 8240x336 -> 880 37, 21, 10928x1872 -> 352 52, 40)
-        int runs = 1;
-        const int shape = pick_pair(d.M, d.K, d.N, split_scratch(w), &runs);
-        if (shape >= 0 && runs == 1)
-            return launch_ring_pair(d, w, shape, 1, s, nullptr);
-        if (shape >= 0) {
+        const Pair pair = pick_pair(d.M, d.K, d.N, split_scratch(w));
+        if (pair.defer.runs != 0)
+            return launch_defer_pair(d, w, pair.defer, s);
+        if (pair.shape >= 0 && pair.runs == 1)
+            return launch_ring_pair(d, w, pair.shape, 1, s, nullptr);
+        if (pair.shape >= 0) {
             hipEvent_t e0 = nullptr, e1 = nullptr;  // a profiled launch brackets both kernels
             take_profile_events(&e0, &e1);
-            const hipError_t e = launch_ring_pair(d, w, shape, runs, s, e0);
-            return e != hipSuccess ? e : launch_splitk_reduce<false>(w, runs, s, e1);
+            const hipError_t e = launch_ring_pair(d, w, pair.shape, pair.runs, s, e0);
+            return e != hipSuccess ? e : launch_splitk_reduce<false>(w, pair.runs, s, e1);
         }
     }
     const hipError_t e = launch_fp8_gemm(d, s);

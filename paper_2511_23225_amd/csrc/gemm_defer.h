@@ -174,9 +174,9 @@ struct DrainPlanOf {  // evaluated once per tile shape and D, not once per slot 
 // spilled (88-100 bytes a lane; on 192x256 tiles, and without a residual, nothing goes to memory).  The
 // reloads at the tile boundary and in a tile's first stage each wait for the operand stream as well; the
 // counted waits stay right, since further memory operations only make them stricter.
-template <bool INT8, int PMODE, int D, int MT, bool A_E5M2 = false, bool LINES = true, bool KSPLIT = false,
-          bool RES = false>
-__global__ __launch_bounds__(256, 1) void gemm_nt_defer_kernel(GemmDev g)
+// work: the tiles of the workgroup, in order (DeferRounds, DeferClasses), or its one unit (DeferUnit).
+template <bool INT8, int PMODE, int D, int MT, bool A_E5M2, bool LINES, bool KSPLIT, bool RES, typename WORK>
+__device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work)
 {
     using T = DeferTile<MT>;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -184,18 +184,11 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_defer_kernel(GemmDev g)
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int wm = wave >> 1, wn = wave & 1;
     const int l31 = lane & 31, lh = lane >> 5;
-    const int n_tiles = g.tiles_m * g.tiles_n;
-    const int total = KSPLIT ? n_tiles * g.ksplit : n_tiles;
-    // persistent schedule: round r hands tile ids [r*G, (r+1)*G) to the G workgroups; inside a
-    // round each XCD (workgroup index mod 8) gets a contiguous run of ids
-    const int G = gridDim.x;
-    const int xcd = blockIdx.x & 7, per_xcd = G >> 3, rem_xcd = G & 7;
-    const int slot = xcd * per_xcd + (xcd < rem_xcd ? xcd : rem_xcd) + (blockIdx.x >> 3);
-    if (slot >= total)
+    if (!work.has(0))
         return;
     int kt = g.K / T::BK, k_first = 0;
     if constexpr (KSPLIT) {
-        const int split = slot / n_tiles, base = kt / g.ksplit, rem = kt % g.ksplit;
+        const int split = work.unit / work.tiles, base = kt / g.ksplit, rem = kt % g.ksplit;
         k_first = split * base + (split < rem ? split : rem);
         kt = base + (split < rem ? 1 : 0);
     }
@@ -229,15 +222,15 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_defer_kernel(GemmDev g)
     };
     Stream sa, sb;
     // Where this workgroup's tiles lie, 64 of them at a time: lane r holds the operand offsets of
-    // its tile number vec_r0 + r (id = slot + number * G), worked out by the vector unit once; at a
+    // its tile number vec_r0 + r, worked out by the vector unit once; at a
     // tile boundary the scalar side fetches one lane's values instead of dividing (the divisions
     // of the id raster cost both streams about 250 cycles per tile when done in scalar code).
     uint32_t ta_lo = 0, ta_hi = 0, tb_lo = 0, tb_hi = 0;
     int tvalid = 0, tmv = 0, tnv = 0, vec_r0 = 0;
     auto tiles_fill = [&](int r0) {
-        const int id_l = KSPLIT ? slot % n_tiles : slot + (r0 + lane) * G;
+        const int id_l = work.id(r0 + lane);
         int tm = 0, tn = 0;
-        if (id_l < (KSPLIT ? n_tiles : total))
+        if (work.has(r0 + lane))
             tile_from_id(id_l, g.tiles_m, g.tiles_n, tm, tn);
         const uint64_t oa = (uint64_t)tm * T::BM * (uint64_t)g.K, ob = (uint64_t)tn * T::BN * (uint64_t)g.K;
         ta_lo = (uint32_t)oa;
@@ -273,7 +266,7 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_defer_kernel(GemmDev g)
     int next_valid = 0, next_tm = 0, next_tn = 0;
     bool has_next = false;
     auto plan_next = [&](int r) {
-        has_next = !KSPLIT && slot + r * G < total;
+        has_next = !WORK::ONE && work.has(r);
         if (has_next) {
             if (r - vec_r0 >= kWave)
                 tiles_fill(r);
@@ -751,7 +744,7 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_defer_kernel(GemmDev g)
         wait_vmcnt<0>();
         // written through the L2s: the reduce kernel starts when they are clean (3072x768 over 8192 tokens,
         // 38 MB of runs, both launches 33.4 us with the runs left dirty, 31.8 now)
-        float4 *dst = (float4 *)g.ksplit_out + ((int64_t)slot * T::NWAVES + wave) * (T::NB * 4 * kWave) + lane;
+        float4 *dst = (float4 *)g.ksplit_out + ((int64_t)work.unit * T::NWAVES + wave) * (T::NB * 4 * kWave) + lane;
 #pragma unroll
         for (int b = 0; b < T::NB; ++b)
 #pragma unroll
@@ -771,7 +764,6 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_defer_kernel(GemmDev g)
             }
         return;
     }
-    int id = slot;
     if constexpr (RES) {
         // one copy of the residual stages for the first tile and the later ones
         auto residual_stages = [&](auto... rs) {
@@ -810,12 +802,11 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_defer_kernel(GemmDev g)
                                 integral_constant<int, 6>{}, integral_constant<int, 7>{});
             stage(no_drain{}, mid{}, true_type{});
             store_begin(tm, tn);
-            id += G;
-            if (id >= total)
+            ++round;
+            if (!work.has(round))
                 break;
             tm = next_tm;  // what the last plan_next fetched: this tile
             tn = next_tn;
-            ++round;
             plan_next(round + 1);
         }
     } else {
@@ -829,10 +820,9 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_defer_kernel(GemmDev g)
         store_begin(tm, tn);
     }
     // every further tile writes its predecessor out during its first D stages
-    int round = 0;
-    for (id += G; id < total; id += G) {
+    if constexpr (!WORK::ONE)
+    for (int round = 1; work.has(round); ++round) {
         const int tm = next_tm, tn = next_tn;  // what the last plan_next fetched: this tile
-        ++round;
         plan_next(round + 1);
         stage(integral_constant<int, 0>{}, integral_constant<int, 2>{}, false_type{});
         stage(integral_constant<int, 1>{}, mid{}, false_type{});
@@ -902,6 +892,40 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_defer_kernel(GemmDev g)
         }
     }
     pen_flush();
+}
+
+// Workgroup's place in the order in which each XCD (workgroup index mod 8, a private L2 each) has a contiguous run.
+__device__ __forceinline__ int xcd_slot()
+{
+    const int G = gridDim.x, xcd = blockIdx.x & 7, per_xcd = G >> 3, rem_xcd = G & 7;
+    return xcd * per_xcd + (xcd < rem_xcd ? xcd : rem_xcd) + (blockIdx.x >> 3);
+}
+
+// Round r hands tile ids [r*G, (r+1)*G) to the G workgroups.
+struct DeferRounds {
+    static constexpr bool ONE = false;
+    int slot, G, total;
+    __device__ __forceinline__ bool has(int r) const { return slot + r * G < total; }
+    __device__ __forceinline__ int id(int r) const { return slot + r * G; }
+};
+
+// One unit: run unit / tiles of the contraction of tile unit % tiles.
+struct DeferUnit {
+    static constexpr bool ONE = true;
+    int unit, tiles, units;
+    __device__ __forceinline__ bool has(int r) const { return r == 0 && unit < units; }
+    __device__ __forceinline__ int id(int) const { return unit % tiles; }
+};
+
+template <bool INT8, int PMODE, int D, int MT, bool A_E5M2 = false, bool LINES = true, bool KSPLIT = false,
+          bool RES = false>
+__global__ __launch_bounds__(256, 1) void gemm_nt_defer_kernel(GemmDev g)
+{
+    const int tiles = g.tiles_m * g.tiles_n;
+    if constexpr (KSPLIT)
+        defer_tiles<INT8, PMODE, D, MT, A_E5M2, LINES, KSPLIT, RES>(g, DeferUnit{xcd_slot(), tiles, tiles * g.ksplit});
+    else
+        defer_tiles<INT8, PMODE, D, MT, A_E5M2, LINES, KSPLIT, RES>(g, DeferRounds{xcd_slot(), (int)gridDim.x, tiles});
 }
 
 }  // namespace tweo

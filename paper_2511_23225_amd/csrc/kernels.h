@@ -142,6 +142,22 @@ hipError_t launch_ring_ksplit(const GemmArgs &a, int shape, int runs, hipStream_
 // runs > 1 (kRing128x128x2): of the weight gradient, into its scratch; start: as launch_ring_ksplit
 hipError_t launch_ring_pair(const GemmArgs &dgrad, const GemmArgs &wgrad, int shape, int runs, hipStream_t s, hipEvent_t start);
 
+// The deferred-epilogue kernel's two products of a layer in one launch (gemm_pair.hip).  Workgroups are taken in slots;
+// classes of consecutive slots have n[c] slots with count[c] tiles of the input gradient each, and the first runs *
+// (tiles of the weight gradient) slots a unit of that.
+struct DeferPairPlan {
+    int n[4], count[4];
+};
+struct DeferPair {
+    int runs;  // of the weight gradient; 0: not this way
+    DeferPairPlan plan;
+    double us;
+};
+constexpr int kDeferPairRuns = 16;
+DeferPair defer_pair_pick(int64_t M, int64_t N, int64_t K, int cus, int most);
+// (the launch that adds the runs is the caller's)
+hipError_t launch_defer_pair_products(const GemmArgs &dgrad, const GemmArgs &wgrad, const DeferPair &pair, hipStream_t s);
+
 // Number of fp32 penalty partials the FP8 GEMM writes for these arguments.
 int fp8_gemm_partials(const GemmArgs &a);
 hipError_t launch_fp8_gemm(const GemmArgs &a, hipStream_t s);

@@ -1,0 +1,44 @@
+"""Both gradient products of a layer in one launch of the deferred-epilogue GEMM."""
+import pytest
+import torch
+
+import paper_2511_23225_amd as tw
+from gpu_util import DEV, scalar_f32
+
+pytestmark = pytest.mark.gpu
+
+
+# both products in one launch of the deferred-epilogue kernel: the weight gradient whole and in runs, tiles for some of the
+# workgroups only, contractions of four to 44 stages under the input gradient's tiles, E5M2; against the products
+# one by one in float64, and against the scratch of fewer runs
+@pytest.mark.parametrize("hybrid", [False, True])
+@pytest.mark.parametrize("shape,scratch", [((1024, 1024, 5632), None), ((8192, 3072, 768), None), ((8192, 768, 3072), None),
+                                           ((13312, 512, 2304), None), ((16384, 1024, 1024), 2.0), ((16384, 1024, 1024), 0.0),
+                                           ((3328, 5632, 1280), None), ((31488, 3584, 256), 5.5)])
+def test_backward_of_whole_tiles_in_one_launch(shape, scratch, hybrid):
+    M, N, K = shape
+    print("deferred pair M=%d N=%d K=%d scratch %s hybrid %s" % (*shape, scratch, hybrid), flush=True)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(M + N + K)
+    f8, dyt = torch.float8_e4m3fn, torch.float8_e5m2 if hybrid else torch.float8_e4m3fn
+    rnd = lambda r, c, t: (torch.randn((r, c), generator=g, device=DEV) * 4).to(t)
+    dyq, wq, xq = rnd(M, N, dyt), rnd(N, K, f8), rnd(M, K, f8)
+    u8 = lambda t: t.contiguous().view(torch.uint8)
+    tr = lambda t: u8(t.view(torch.uint8).t())
+    one = scalar_f32(1.0)
+    size = tw.tweo_workspace_bytes(tw.TWEO_OP_FP8_LINEAR_BWD, M, N, K) if scratch is None else 256 + int(scratch * N * K * 4)
+    whole = torch.full((size + 4096,), 0xA5, dtype=torch.uint8, device=DEV)
+    dx = torch.full((M, K), float("nan"), dtype=torch.bfloat16, device=DEV)
+    dw = torch.full((N, K), float("nan"), dtype=torch.bfloat16, device=DEV)
+    bwd = tw.tweo_fp8_linear_bwd_hybrid if hybrid else tw.tweo_fp8_linear_bwd
+    for _ in range(2):  # a second call over the first one's runs
+        bwd(u8(dyq), tr(dyq), one, tr(wq), one, tr(xq), one, M, N, K, dx, dw, whole[:size])
+    torch.cuda.synchronize()
+    assert bool((whole[size:] == 0xA5).all())
+    for got, a, b in ((dx, dyq, wq), (dw, dyq.view(torch.uint8).t().view(dyt), xq)):
+        a, b = a.double(), b.double()
+        ref, refabs = a @ b, a.abs() @ b.abs()
+        diff = (got.double() - ref).abs()
+        # bf16 rounding, and what one FP8 MFMA loses (check_gemm)
+        assert bool((diff <= 2.0 ** -8 * ref.abs() + (2.0 ** -10 + a.shape[1] * 2.0 ** -24) * refabs).all())
+        assert float(diff.norm() / ref.norm()) < 3e-3
