@@ -1110,7 +1110,8 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restr
 
 // Second half of a K split on the deferred-epilogue kernel's tiles: the runs sit in the
 // workspace in the order the GEMM's lanes held them ([unit = split * tiles + tile][wave][block]
-// [quarter][lane] float4: rows lane % 32 of the block, columns 8 * quarter + 4 * (lane / 32) .. +3).
+// [quarter][lane] float4: DeferTile::lane_row(lane % 32) of the band, columns 32 * (lane / 32) + 16 * (block % 2) +
+// 4 * quarter .. +3 of the pair of blocks).
 // A wave of this kernel takes one pair of neighbouring blocks of one tile (64 columns x 32 rows),
 // adds the runs in index order, scales, rounds and regroups the lanes' values into whole 128-byte
 // lines of the output as the GEMM's own write-out does.
@@ -1161,14 +1162,21 @@ __global__ __launch_bounds__(256) void splitk_reduce_defer_kernel(const float4 *
             A[2 * q + h] = pack_bf16x2((float)sum[0][q][2 * h] * alpha, (float)sum[0][q][2 * h + 1] * alpha);
             B[2 * q + h] = pack_bf16x2((float)sum[1][q][2 * h] * alpha, (float)sum[1][q][2 * h + 1] * alpha);
         }
-    block_pair_to_lines(A, B);
+    const QuadMasks masks = quad_masks();
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        quad_exchange<0>(A[d], A[4 + d], B[d], B[4 + d], masks);
+        quad_exchange<1>(A[d], A[4 + d], B[d], B[4 + d], masks);
+    }
     int tm, tn;
     tile_from_id(tile, tiles_m, tiles_n, tm, tn);
-    const int64_t row0 = (int64_t)tm * T::BM + wm * 128 + i * 32 + (l31 & ~3);
+    const int64_t row0 = (int64_t)tm * T::BM + T::band_row(wm, i) + T::lane_row(l31 & ~3);
     const int64_t col0 = (int64_t)tn * T::BN + wn * 128 + jp * 64 + lh * 32 + (l31 & 3) * 8;
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-        *(uint4 *)(out + (row0 + u) * N + col0) = make_uint4(A[2 * u], A[2 * u + 1], B[2 * u], B[2 * u + 1]);
+    for (int u = 0; u < 4; ++u) {
+        const uint32_t *w = (u < 2 ? A : B) + 4 * (u & 1);
+        *(uint4 *)(out + (row0 + u) * N + col0) = make_uint4(w[0], w[1], w[2], w[3]);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1557,7 +1565,7 @@ static hipError_t launch_defer_inst(const GemmArgs &a, hipStream_t s)
 {
     using T = DeferTile<MT>;
     constexpr int LDS = RES ? T::LDS_BYTES_RES : T::LDS_BYTES;
-    constexpr auto kernel = gemm_nt_defer_kernel<INT8, PMODE, D, MT, A_E5M2, true, false, RES>;
+    constexpr auto kernel = gemm_nt_defer_kernel<INT8, PMODE, D, MT, A_E5M2, false, RES>;
     static bool attr_done = false;
     if (!attr_done) {
         hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
@@ -1886,7 +1894,7 @@ template <bool A_E5M2, bool INT8 = false>
 static hipError_t launch_ksplit_defer(const GemmArgs &a, hipStream_t s, int splits)
 {
     using T = DeferTile<4>;
-    const void *kern = (const void *)gemm_nt_defer_kernel<INT8, 0, 3, 4, A_E5M2, true, true>;
+    const void *kern = (const void *)gemm_nt_defer_kernel<INT8, 0, 3, 4, A_E5M2, true>;
     static bool attr_done = false;
     if (!attr_done) {
         hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
@@ -1912,10 +1920,10 @@ static hipError_t launch_ksplit_defer(const GemmArgs &a, hipStream_t s, int spli
     hipEvent_t e0 = nullptr, e1 = nullptr;  // a profiled launch brackets both kernels
     take_profile_events(&e0, &e1);
     if (e0 != nullptr)
-        hipExtLaunchKernelGGL((gemm_nt_defer_kernel<INT8, 0, 3, 4, A_E5M2, true, true>), grid, block, T::LDS_BYTES, s, e0,
+        hipExtLaunchKernelGGL((gemm_nt_defer_kernel<INT8, 0, 3, 4, A_E5M2, true>), grid, block, T::LDS_BYTES, s, e0,
                               nullptr, 0, g);
     else
-        hipLaunchKernelGGL((gemm_nt_defer_kernel<INT8, 0, 3, 4, A_E5M2, true, true>), grid, block, T::LDS_BYTES, s, g);
+        hipLaunchKernelGGL((gemm_nt_defer_kernel<INT8, 0, 3, 4, A_E5M2, true>), grid, block, T::LDS_BYTES, s, g);
     const hipError_t e = hipGetLastError();
     return e != hipSuccess ? e : launch_splitk_reduce_defer<INT8>(a, splits, s, nullptr, e1);
 }

@@ -73,8 +73,8 @@ __device__ __forceinline__ void dma_load16(uint32_t lds_addr, const uint8_t *bas
 // partner's lower register into its upper one, a lane whose bit is set the partner's upper
 // register into its lower one.  Each exchange is one v_cndmask_b32 whose first source comes
 // through the DPP quad permutation (vcc ? src1 : permuted src0); the compiler does not fuse the
-// two, hence asm.  A DPP source must have been written two wait states earlier: the order below
-// keeps every result two instructions away from its use, and the leading s_nop covers the inputs.
+// two, hence asm.  A DPP source must have been written two wait states earlier: the s_nop and the
+// s_mov in front cover the inputs.
 struct QuadMasks {
     uint64_t odd, even, upper, lower;  // lanes with lane & 1 set / clear, lane & 2 set / clear
 };
@@ -82,48 +82,36 @@ __device__ __forceinline__ QuadMasks quad_masks()
 {
     return QuadMasks{0xAAAAAAAAAAAAAAAAull, 0x5555555555555555ull, 0xCCCCCCCCCCCCCCCCull, 0x3333333333333333ull};
 }
-__device__ __forceinline__ void quad_transpose(uint32_t &p0, uint32_t &p1, uint32_t &p2, uint32_t &p3, const QuadMasks &m)
+template <int ROUND>
+__device__ __forceinline__ void quad_exchange(uint32_t &p0, uint32_t &p1, uint32_t &p2, uint32_t &p3, const QuadMasks &m)
 {
-    uint32_t n0, n1, n2, n3, r0, r1, r2, r3;
-    asm volatile("s_nop 1\n\t"
-                 "s_mov_b64 vcc, %[odd]\n\t"
-                 "v_cndmask_b32_dpp %[n1], %[p0], %[p1], vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-                 "v_cndmask_b32_dpp %[n3], %[p2], %[p3], vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-                 "s_mov_b64 vcc, %[even]\n\t"
-                 "v_cndmask_b32_dpp %[n0], %[p1], %[p0], vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-                 "v_cndmask_b32_dpp %[n2], %[p3], %[p2], vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-                 "s_mov_b64 vcc, %[upper]\n\t"
-                 "v_cndmask_b32_dpp %[r3], %[n1], %[n3], vcc quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-                 "v_cndmask_b32_dpp %[r2], %[n0], %[n2], vcc quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-                 "s_mov_b64 vcc, %[lower]\n\t"
-                 "v_cndmask_b32_dpp %[r1], %[n3], %[n1], vcc quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-                 "v_cndmask_b32_dpp %[r0], %[n2], %[n0], vcc quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf"
-                 : [n0] "=&v"(n0), [n1] "=&v"(n1), [n2] "=&v"(n2), [n3] "=&v"(n3), [r0] "=&v"(r0), [r1] "=&v"(r1),
-                   [r2] "=&v"(r2), [r3] "=&v"(r3)
-                 : [p0] "v"(p0), [p1] "v"(p1), [p2] "v"(p2), [p3] "v"(p3), [odd] "s"(m.odd), [even] "s"(m.even),
-                   [upper] "s"(m.upper), [lower] "s"(m.lower)
-                 : "vcc");
-    p0 = r0;
-    p1 = r1;
-    p2 = r2;
-    p3 = r3;
-}
-
-// Two neighbouring 32x32 blocks of an MFMA result, packed to bf16 pairs (word 2q+h of lane
-// (row, lh): columns 8q + 4lh + 2h, +1 of the block), regrouped for whole-line stores: on return
-// {A[2u], A[2u+1], B[2u], B[2u+1]} of lane (row, lh) are columns 32lh + 8(row % 4) .. +7 of the
-// block pair's 64 columns in row 4 * (row / 4) + u.
-__device__ __forceinline__ void block_pair_to_lines(uint32_t (&A)[8], uint32_t (&B)[8])
-{
-    const QuadMasks m = quad_masks();
-#pragma unroll
-    for (int w = 0; w < 8; ++w)  // block 2c+1 of the lower half-wave <-> block 2c of the upper one
-        asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(A[w]), "+v"(B[w]));
-#pragma unroll
-    for (int d = 0; d < 2; ++d) {
-        quad_transpose(A[d], A[2 + d], A[4 + d], A[6 + d], m);
-        quad_transpose(B[d], B[2 + d], B[4 + d], B[6 + d], m);
-    }
+    // the lower registers change in place, the upper ones go to fresh registers first
+    uint32_t r1, r3;
+    uint32_t &u0 = p0, &u1 = ROUND == 0 ? p2 : p1, &v0 = ROUND == 0 ? p1 : p2, &v1 = p3;  // pairs (u0, v0), (u1, v1)
+    if constexpr (ROUND == 0)
+        asm volatile("s_nop 0\n\t"
+                     "s_mov_b64 vcc, %[set]\n\t"
+                     "v_cndmask_b32_dpp %[r1], %[u0], %[v0], vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+                     "v_cndmask_b32_dpp %[r3], %[u1], %[v1], vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+                     "s_mov_b64 vcc, %[clear]\n\t"
+                     "v_cndmask_b32_dpp %[u0], %[v0], %[u0], vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+                     "v_cndmask_b32_dpp %[u1], %[v1], %[u1], vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
+                     : [u0] "+v"(u0), [u1] "+v"(u1), [r1] "=&v"(r1), [r3] "=&v"(r3)
+                     : [v0] "v"(v0), [v1] "v"(v1), [set] "s"(m.odd), [clear] "s"(m.even)
+                     : "vcc");
+    else
+        asm volatile("s_nop 0\n\t"
+                     "s_mov_b64 vcc, %[set]\n\t"
+                     "v_cndmask_b32_dpp %[r1], %[u0], %[v0], vcc quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+                     "v_cndmask_b32_dpp %[r3], %[u1], %[v1], vcc quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+                     "s_mov_b64 vcc, %[clear]\n\t"
+                     "v_cndmask_b32_dpp %[u0], %[v0], %[u0], vcc quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+                     "v_cndmask_b32_dpp %[u1], %[v1], %[u1], vcc quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf"
+                     : [u0] "+v"(u0), [u1] "+v"(u1), [r1] "=&v"(r1), [r3] "=&v"(r3)
+                     : [v0] "v"(v0), [v1] "v"(v1), [set] "s"(m.upper), [clear] "s"(m.lower)
+                     : "vcc");
+    v0 = r1;
+    v1 = r3;
 }
 
 template <int N>

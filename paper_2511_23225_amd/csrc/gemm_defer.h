@@ -27,11 +27,10 @@
 //    reads are issued back to back, a read followed at once by its use stalls),
 //    and the next tile's first MFMA on that block starts from zero (no
 //    clearing).  The packed values are written out *during the next tile*, a
-//    few instructions per slot: a lane of the MFMA layout holds four consecutive
-//    columns of a row and lane + 32 the next four, so one v_permlane32_swap per
-//    register pair gives every lane eight consecutive columns (16 bytes) to
-//    store; the TWEO penalty terms (Sec. 3.3; the term of the value as stored)
-//    are added from the same registers.  No LDS round trip: extra LDS
+//    few instructions per slot: the order of the rows in LDS (DeferTile::lane_row) leaves
+//    a lane with half of a 128-byte line, quads of lanes transpose their 16-byte
+//    pieces, and a store then covers whole lines; the TWEO penalty terms (Sec. 3.3; the term of
+//    the value as stored) are added from the same registers.  No LDS round trip: extra LDS
 //    instructions cost the matrix pipe about 25 cycles each.
 //
 // Fragments are single-buffered in registers and refilled just in time: the
@@ -61,8 +60,6 @@ struct DeferTile {
     static_assert(LDS_BYTES_RES <= 160 * 1024, "LDS capacity with a residual");
     static constexpr int SLAB = NB, SLOTS = 2 * NB;       // MFMA slots per K slab / per stage
     static constexpr int NA = BM / 32, NBP = BN / 32;     // operand pieces per wave per stage
-    static constexpr int STEPS_PER_BLOCK = 8;             // micro-steps of writing a block out
-    static constexpr int DRAIN_STEPS = NB * STEPS_PER_BLOCK;
     static constexpr int HALVES = 2 * NB;                 // half blocks to convert per tile
     static constexpr int PARTIALS_PER_WG = NWAVES;       // one fp32 sum per wave
     static constexpr bool EDGE = MT == 3;                 // M may end inside the last row of tiles
@@ -80,29 +77,37 @@ struct DeferTile {
     {
         return t < NA / 2 || (t >= SLAB && t < SLAB + NBP) || (t >= SLOTS - 4 && t < SLOTS - 4 + NA / 2);
     }
-    static constexpr int FREE = SLOTS - NA - NBP;         // slots without a load, per stage
-    __host__ __device__ __attribute__((always_inline)) static constexpr int clamp(int v, int hi) { return v < 0 ? 0 : (v > hi ? hi : v); }
-    __host__ __device__ __attribute__((always_inline)) static constexpr int free_index(int t)                // how many of them lie before slot t
+
+    // Rows and columns of a tile lie in LDS, and so in the MFMA's blocks, in an order in which a lane ends up with contiguous
+    // columns: 32-row block X of 64 rows holds in place 8q + 4b + i row 32b + 16X + 4q + i of them.  A lane (l31, lh) of the
+    // MFMA layout holds places 8q + 4lh + i of B's block, that is columns 32lh + 16X + 4q + i, for one place of A's: the
+    // 32 columns of a pair of blocks are the half line that it writes, without an exchange between the half-waves.
+    __host__ __device__ __attribute__((always_inline)) static constexpr int lane_row(int place)
     {
-        return t - clamp(t, NA / 2) - clamp(t - SLAB, NBP) - clamp(t - (SLOTS - 4), NA / 2);
+        return 32 * ((place >> 2) & 1) + 4 * (place >> 3) + (place & 3);
+    }
+    // first row of band i (32 places of A) of the waves in row wm
+    __host__ __device__ __attribute__((always_inline)) static constexpr int band_row(int wm, int i)
+    {
+        return 64 * ((wm * MT + i) >> 1) + 16 * ((wm * MT + i) & 1);
     }
 };
 
-// Where the write-out of a tile happens inside the first D stages of the next one (LINES).  Per
-// pair of neighbouring blocks there are 20 arithmetic micro-steps (penalty terms, lane exchanges)
+// Where the write-out of a tile happens inside the first D stages of the next one.  Per
+// pair of neighbouring blocks there are 8 arithmetic micro-steps (lane exchanges), 24 with the penalty's terms,
 // and 4 stores.  The arithmetic is dealt evenly over all slots from slot 2 on; a store goes to the
 // first slot without an operand load (the two share the address unit) after its pair's arithmetic,
 // one store per slot.  alu_lo/alu_hi: the arithmetic steps of slot s; store: the store of slot s or -1.
-template <typename T, int D>
+template <typename T, int D, bool PEN>
 struct DrainPlan {
-    static constexpr int NSLOT = D * T::SLOTS, PAIRS = T::NB / 2, ALU = PAIRS * 20, STORES = PAIRS * 4;
+    static constexpr int NSLOT = D * T::SLOTS, PAIRS = T::NB / 2, PER = PEN ? 24 : 8, ALU = PAIRS * PER, STORES = PAIRS * 4;
     int alu_lo[NSLOT], alu_hi[NSLOT], store[NSLOT];
     bool ok;
 };
-template <typename T, int D>
-constexpr DrainPlan<T, D> make_drain_plan()
+template <typename T, int D, bool PEN>
+constexpr DrainPlan<T, D, PEN> make_drain_plan()
 {
-    using P = DrainPlan<T, D>;
+    using P = DrainPlan<T, D, PEN>;
     constexpr int FIRST = 2;
     // the arithmetic ends as late as still leaves store slots for the last pairs (the last slots
     // of a stage carry loads)
@@ -121,7 +126,7 @@ constexpr DrainPlan<T, D> make_drain_plan()
         int s = 0;
         p.ok = true;
         for (int st = 0; st < P::STORES && p.ok; ++st) {
-            const int ready = at[(st / 4) * 20 + 19] + 1;  // the slot after the pair's last exchange
+            const int ready = at[(st / 4) * P::PER + P::PER - 1] + 1;  // the slot after the pair's last exchange
             if (s < ready)
                 s = ready;
             while (s < P::NSLOT && T::load_slot(s % T::SLOTS))
@@ -139,9 +144,9 @@ constexpr DrainPlan<T, D> make_drain_plan()
     return bad;
 }
 
-template <typename T, int D>
+template <typename T, int D, bool PEN>
 struct DrainPlanOf {  // evaluated once per tile shape and D, not once per slot body
-    static constexpr DrainPlan<T, D> value = make_drain_plan<T, D>();
+    static constexpr DrainPlan<T, D, PEN> value = make_drain_plan<T, D, PEN>();
 };
 
 // PMODE: 4 = TWEO penalty with p = 4 (the paper's setting), 0 = none.  D: number of stages of
@@ -149,11 +154,10 @@ struct DrainPlanOf {  // evaluated once per tile shape and D, not once per slot 
 // the tile's last stage, which converts its own blocks, takes no part in it).
 // A_E5M2 (FP8 only): the A operand holds E5M2 codes (the gradient of the HYBRID recipe, Sec. 4.3);
 // B is always E4M3.  The MFMA takes the format of each source from a modifier.
-// LINES: the write-out regroups the packed values among lanes first, so that the four lanes of a
-// quad store 64 contiguous bytes of one row and the matching quad of the other half-wave the next
-// 64 (whole 128-byte lines, 8 rows per instruction); otherwise a lane stores 16 bytes of its own
-// row (32 rows per instruction: 2.25 times the time in the store path, measured on stores that
-// hit in L2).
+// The write-out regroups the packed values among the lanes of a quad first, so that its four lanes
+// store 64 contiguous bytes of one row and the matching quad of the other half-wave the next
+// 64 (whole 128-byte lines, 8 rows per instruction; 16 bytes of a row per lane, 32 rows per
+// instruction, take 2.25 times as long in the store path, measured on stores that hit in L2).
 // KSPLIT: g.ksplit workgroups share a tile; workgroup id = split * tiles + tile multiplies its run
 // of K stages (at least two) and leaves the fp32 sums in g.ksplit_out in the order the lanes hold
 // them (unit, wave, block, quarter, lane: every store instruction writes 1 KB contiguously);
@@ -175,7 +179,7 @@ struct DrainPlanOf {  // evaluated once per tile shape and D, not once per slot 
 // reloads at the tile boundary and in a tile's first stage each wait for the operand stream as well; the
 // counted waits stay right, since further memory operations only make them stricter.
 // work: the tiles of the workgroup, in order (DeferRounds, DeferClasses), or its one unit (DeferUnit).
-template <bool INT8, int PMODE, int D, int MT, bool A_E5M2, bool LINES, bool KSPLIT, bool RES, typename WORK>
+template <bool INT8, int PMODE, int D, int MT, bool A_E5M2, bool KSPLIT, bool RES, typename WORK>
 __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work)
 {
     using T = DeferTile<MT>;
@@ -201,7 +205,7 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work)
 
     // ---- operand stream (direct-to-LDS loads), running ahead of the MFMAs -----------------
     // One instruction of a wave fills 1 KB = 8 rows x 128 B; lane -> (row, 16-byte chunk), the
-    // chunk XOR-swizzled with (row/2)%8.  Piece p of an operand is its rows (p*4 + wave)*8.. .
+    // chunk XOR-swizzled with (row/2)%8.  Piece p of an operand is its places (p*4 + wave)*8.. (DeferTile::lane_row).
     // A and B are two streams of their own over (tile, stage): the B half of an LDS stage is
     // released (and refilled) earlier than the A half.  An instruction costs three issue slots:
     // LDS destination = constant + buffer offset, one wait state, the load with a per-piece
@@ -212,7 +216,7 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work)
     const uint32_t dma_chunk = (uint32_t)((dma_p ^ ((dma_row >> 1) + 4 * (wave & 1))) << 4);
 #pragma unroll
     for (int p8 = 0; p8 < 8; ++p8)
-        voffs[p8] = (uint32_t)(p8 * 32 + wave * 8 + dma_row) * (uint32_t)g.K + dma_chunk;
+        voffs[p8] = (uint32_t)(T::band_row(0, p8) + T::lane_row(wave * 8 + dma_row)) * (uint32_t)g.K + dma_chunk;
     // A rows of a ragged last tile are clamped to the last valid one (EDGE only)
     uint32_t voffs_a[T::EDGE ? T::NA : 1];
     struct Stream {
@@ -256,7 +260,7 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work)
         if constexpr (T::EDGE) {
 #pragma unroll
             for (int p8 = 0; p8 < T::NA; ++p8) {
-                const int r = p8 * 32 + wave * 8 + dma_row;
+                const int r = T::band_row(0, p8) + T::lane_row(wave * 8 + dma_row);
                 voffs_a[p8] = (uint32_t)(r < valid ? r : valid - 1) * (uint32_t)g.K + dma_chunk;
             }
         }
@@ -387,7 +391,8 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work)
     };
 
     // ---- deferred epilogue -----------------------------------------------------------------
-    // packed[i][j][2q+h]: bf16 pair (rows l31, columns j*32 + 8q + 4lh + 2h, +1) of block (i, j)
+    // packed[i][j][2q+h]: bf16 pair of block (i, j): row lane_row(l31) of band i, columns 32lh + 16(j%2) + 4q + 2h, +1 of
+    // the pair of blocks j/2
     uint32_t packed[MT][4][8];
     float pen = 0.0f;
     // half h of block b = h/2 (i = b/4, j = b%4): accumulator words 8*(h%2) .. +7
@@ -431,90 +436,50 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work)
         }
     };
     // Stores walk the wave's sub-tile with one scalar pointer (first row of the band of blocks
-    // being written); block column and column half go into the instruction's offset field.
-    // Lane (row l31, half lh) stores the 16 bytes at row l31, columns 8*lh .. 8*lh+7 of a half.
+    // being written); the pair of blocks goes into the instruction's offset field.
     const uint8_t *sp = nullptr;
-    const int64_t rows32 = (int64_t)g.N * 64;
-    const uint32_t out_lane = (uint32_t)l31 * (uint32_t)g.N * 2u + (uint32_t)lh * 16u;
-    int prow_left = 0;  // EDGE: rows of the wave's sub-tile inside the matrix, for the tile in `packed`
+    const int64_t rows16 = (int64_t)g.N * 32;
+    auto next_band = [&](int i) { return ((wm * MT + i) & 1) ? 3 * rows16 : rows16; };  // from band i to the next one
+    int rows_valid = 0;  // EDGE: rows of the tile in `packed` inside the matrix
     auto store_begin = [&](int tm, int tn) {
         if constexpr (T::EDGE)
-            prow_left = g.M - tm * T::BM - wm * MT * 32;
+            rows_valid = g.M - tm * T::BM;
         sp = (const uint8_t *)g.out +
-             (((int64_t)tm * T::BM + wm * MT * 32) * g.N + (int64_t)tn * T::BN + wn * 128) * 2;
+             (((int64_t)tm * T::BM + T::band_row(wm, 0)) * g.N + (int64_t)tn * T::BN + wn * 128) * 2;
     };
-    // Micro-step q of writing a tile out: block q / 8 (in conversion order), column half
-    // P = (q % 8) / 4 (register words 4P .. 4P+3 = columns 16P .. 16P+15 of the block).  Step 0
-    // of a half exchanges words between lane and lane + 32 (word 4P+2 of the lower lanes <-> word
-    // 4P of the upper ones, likewise 4P+3 <-> 4P+1), after which the four words of a lane are
-    // eight consecutive columns; steps 1 and 2 add the penalty terms; step 3 stores.
-    auto drain_step = [&](int q) {
-        const int b = q / T::STEPS_PER_BLOCK, i = b >> 2, j = b & 3;
-        const int P = (q % T::STEPS_PER_BLOCK) >> 2, k = q & 3;
-        uint32_t *w = &packed[i][j][4 * P];
-        const bool row_ok = !T::EDGE || i * 32 + l31 < prow_left;
-        if (k == 0) {
-            // the swap reads its operands early: two wait states after a vector-ALU write (the
-            // compiler may have placed a register copy right in front of this statement)
-            asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %2\n\tv_permlane32_swap_b32 %1, %3"
-                         : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]));
-        } else if (k == 1) {
-            if (PMODE != 0 && row_ok) {
-                pen_word(w[0]);
-                pen_word(w[1]);
-            }
-        } else if (k == 2) {
-            if (PMODE != 0 && row_ok) {
-                pen_word(w[2]);
-                pen_word(w[3]);
-            }
-        } else if (row_ok) {
-            const v4i v = {(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
-            // a store of more than 8 bytes reads its data late: nothing may write those
-            // registers in the next wait states (the compiler does not know this is a store)
-            asm volatile("global_store_dwordx4 %0, %1, %2 offset:%3\n\ts_nop 1"
-                         :
-                         : "v"(out_lane), "v"(v), "s"(sp), "n"(j * 64 + P * 32)
-                         : "memory");
-        }
-        if (k == 3 && j == 3 && P == 1)
-            sp += rows32;
-    };
-    // LINES.  Arithmetic step a works on the pair of neighbouring blocks c = a / 20 (blocks 2c,
-    // 2c+1 of band i: 64 columns = one 128-byte line per row), r = a % 20, with A, B the register
-    // arrays of blocks 2c and 2c+1:
-    //  r = 0..15  word w = r/2: penalty terms of A[w] (even r) / of B[w] (odd r), after which B[w]
-    //             of the lower half-wave is exchanged with A[w] of the upper one.  After the eight
-    //             exchanges lane (row, lh) holds all 32 columns of its row in block 2c+lh: 16-byte
-    //             piece u = words {A[2u], A[2u+1], B[2u], B[2u+1]}.
-    //  r = 16..19 dword r-16 of the four pieces: 4x4 transposition over the lanes of a quad, after
-    //             which piece register u of lane a holds piece a of row 4*(row/4) + u.
+    const int lane_row = T::lane_row(l31);
+    // Arithmetic step a works on the pair of neighbouring blocks c = a / PER (blocks 2c,
+    // 2c+1 of band i: 64 columns = one 128-byte line per row), r = a % PER, with A, B the register
+    // arrays of blocks 2c and 2c+1; 16-byte piece u of a lane's half line is words 4u .. 4u+3 of A, then B:
+    //  with the penalty, r = 0..15: the terms of word r/2 of A (even r) / of B (odd r);
+    //  the last 8: dword d of the four pieces in two steps: 4x4 transposition over the lanes of a quad, after
+    //  which piece register u of lane a holds piece a of row 4*(row/4) + u.
     // Store step st: pair st / 4, u = st % 4: a quad writes 64 contiguous bytes of row
     // 4*(row/4) + u, the two half-waves the two halves of the line.
-    const uint32_t out_quad = (uint32_t)(l31 & ~3) * (uint32_t)g.N * 2u + (uint32_t)lh * 64u + (uint32_t)(l31 & 3) * 16u;
+    const uint32_t out_quad = (uint32_t)T::lane_row(l31 & ~3) * (uint32_t)g.N * 2u + (uint32_t)lh * 64u + (uint32_t)(l31 & 3) * 16u;
     const int64_t row_bytes = (int64_t)g.N * 2;
     const QuadMasks qmasks = quad_masks();
+    constexpr int PEN_STEPS = PMODE != 0 ? 16 : 0, PER = PEN_STEPS + 8;
     auto drain_alu = [&](int a) {
-        const int c = a / 20, r = a % 20, i = c >> 1, jp = c & 1;
+        const int c = a / PER, r = a % PER, i = c >> 1, jp = c & 1;
         uint32_t *A = packed[i][2 * jp], *B = packed[i][2 * jp + 1];
-        if (r < 16) {
-            const int w = r >> 1;
-            if (PMODE != 0 && (!T::EDGE || i * 32 + l31 < prow_left))
-                pen_word((r & 1) ? B[w] : A[w]);
-            // the swap reads its operands early, and what follows may read its results early
-            if (r & 1)
-                asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(A[w]), "+v"(B[w]));
+        if (r < PEN_STEPS) {
+            if (!T::EDGE || T::band_row(wm, i) + lane_row < rows_valid)
+                pen_word((r & 1) ? B[r >> 1] : A[r >> 1]);
         } else {
-            const int d = r - 16;
-            uint32_t *src = (d & 2) ? B : A;
-            quad_transpose(src[(d & 1)], src[2 + (d & 1)], src[4 + (d & 1)], src[6 + (d & 1)], qmasks);
+            const int d = (r - PEN_STEPS) >> 1;
+            if ((r & 1) == 0)
+                quad_exchange<0>(A[d], A[4 + d], B[d], B[4 + d], qmasks);
+            else
+                quad_exchange<1>(A[d], A[4 + d], B[d], B[4 + d], qmasks);
         }
     };
     auto drain_store = [&](int st) {
         const int c = st / 4, u = st % 4, i = c >> 1, jp = c & 1;
         uint32_t *A = packed[i][2 * jp], *B = packed[i][2 * jp + 1];
-        if (!T::EDGE || i * 32 + (l31 & ~3) + u < prow_left) {
-            const v4i v = {(int)A[2 * u], (int)A[2 * u + 1], (int)B[2 * u], (int)B[2 * u + 1]};
+        if (!T::EDGE || T::band_row(wm, i) + (lane_row & ~3) + u < rows_valid) {
+            const uint32_t *w = (u < 2 ? A : B) + 4 * (u & 1);
+            const v4i v = {(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
             const uint8_t *spu = sp + u * row_bytes;
             // a store of more than 8 bytes reads its data late: nothing may write those
             // registers in the next wait states (the compiler does not know this is a store)
@@ -527,7 +492,7 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work)
                          : "memory");
         }
         if (u == 3 && jp == 1)
-            sp += rows32;
+            sp += next_band(i);
     };
 
     // ---- residual (RES): unit c = block pair (band c / 2, columns 64 * (c % 2) .. +63) ------------
@@ -538,7 +503,7 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work)
     int res_valid = 0;            // EDGE: rows of the tile inside the matrix
     // chunk of a lane in an even load (rows 0..7 of 16); in an odd one its bit 2 is flipped, which is
     // bit 6 of the offset (a row is a multiple of 512 bytes)
-    const uint32_t res_voff = (uint32_t)dma_row * (uint32_t)g.N * 2u + (uint32_t)((dma_p ^ (dma_row >> 1)) << 4);
+    const uint32_t res_voff = (uint32_t)T::lane_row(dma_row) * (uint32_t)g.N * 2u + (uint32_t)((dma_p ^ (dma_row >> 1)) << 4);
     auto res_begin = [&](int tm, int tn) {
         const int64_t row0 = (int64_t)tm * T::BM + (T::EDGE ? 0 : wm * MT * 32);
         rp = (const uint8_t *)g.residual + (row0 * g.N + (int64_t)tn * T::BN + wn * 128) * 2;
@@ -547,31 +512,24 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work)
     auto res_load = [&](int c, int n) {
         const int i = c >> 1, jp = c & 1;
         const uint32_t dst = res_lds + (c & 1) * T::RES_UNIT_BYTES + n * 1024;
-        const int64_t unit = (int64_t)jp * 128 + (T::EDGE ? 0 : i * rows32);
+        const int64_t unit = (int64_t)jp * 128 + (T::EDGE ? 0 : (T::band_row(0, i) / 16) * rows16);
         if constexpr (T::EDGE) {  // rows past the matrix load the last valid one
-            const int rt = wm * MT * 32 + i * 32 + 8 * n + dma_row;
+            const int rt = T::band_row(wm, i) + T::lane_row(8 * n + dma_row);
             const uint32_t v = (uint32_t)(rt < res_valid ? rt : res_valid - 1) * (uint32_t)g.N * 2u +
                                (uint32_t)((dma_p ^ (dma_row >> 1) ^ (4 * (n & 1))) << 4);
             dma_load16(dst, rp + unit, v);
         } else {
-            dma_load16(dst, rp + unit + n * (rows32 >> 2), res_voff ^ (64u * (n & 1)));
+            dma_load16(dst, rp + unit + n * (rows16 >> 2), res_voff ^ (64u * (n & 1)));
         }
     };
-    // 16-byte piece (X, u) of lane (row, lh): columns 8 * (4X + 2u + lh) .. +7 of the unit's 64; the
-    // exchange between the half-waves leaves words 4u .. 4u+3 of block X as the accumulators lie
-    const uint32_t res_rd = (uint32_t)(T::LDS_BYTES + wave * T::RES_WAVE_BYTES + l31 * 128 + ((lh ^ sw) << 4));
+    // 16-byte piece (X, u) of lane (row, lh): columns 32lh + 16X + 8u .. +7 of the unit's 64, words 4u .. 4u+3 of block X
+    const uint32_t res_rd = (uint32_t)(T::LDS_BYTES + wave * T::RES_WAVE_BYTES + l31 * 128 + (((4 * lh) ^ sw) << 4));
     auto res_read = [&](int c, int X, int u) {
-        const v4i v = *(const v4i *)(smem + (res_rd ^ (uint32_t)((4 * X + 2 * u) << 4)) + (c & 1) * T::RES_UNIT_BYTES);
+        const v4i v = *(const v4i *)(smem + (res_rd ^ (uint32_t)((2 * X + u) << 4)) + (c & 1) * T::RES_UNIT_BYTES);
         uint32_t *w = &packed[c >> 1][2 * (c & 1) + X][4 * u];
 #pragma unroll
         for (int d = 0; d < 4; ++d)
             w[d] = (uint32_t)v[d];
-    };
-    auto res_swap = [&](int c, int X, int u) {
-        uint32_t *w = &packed[c >> 1][2 * (c & 1) + X][4 * u];
-        // the swap reads its operands early, and what follows may read its results early
-        asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %2\n\tv_permlane32_swap_b32 %1, %3\n\ts_nop 1"
-                     : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]));
     };
 
     // The penalty terms are summed per lane over every tile of the workgroup (a few thousand
@@ -594,7 +552,6 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work)
     // tile starts (1: the workgroup's first tile, 2: a later one, which also converts the last
     // half blocks of its predecessor).  LAST: a tile ends: its blocks are converted as they finish.
     // RS >= 0: residual stage RS of RES_STAGES.
-    constexpr int W = D * T::FREE;
     // The slot number is a compile-time constant of each slot's body (the bodies are stamped out
     // from an integer sequence): which pieces a slot carries is decided by the front end, not
     // left to constant propagation through unrolled loops.
@@ -657,8 +614,6 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work)
                         if constexpr (t == 1 || t == 2) {
                             res_read(RS - 2, t - 1, 0);
                             res_read(RS - 2, t - 1, 1);
-                        } else if constexpr (t >= 4 && t < 8) {
-                            res_swap(RS - 2, (t - 4) >> 1, (t - 4) & 1);
                         }
                     }
                     // conversion of the tile that ends here / ended in the previous stage
@@ -667,8 +622,8 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work)
                         if ((LAST && T::convert_slot(h) == t) || (FIRST == 2 && T::convert_slot(h) == t + T::SLOTS))
                             convert_half(h);
                     // write-out of the previous tile
-                    if constexpr (DR >= 0 && LINES) {
-                        using Plan = DrainPlanOf<T, D>;
+                    if constexpr (DR >= 0) {
+                        using Plan = DrainPlanOf<T, D, (PMODE != 0)>;
                         static_assert(Plan::value.ok, "the write-out fits the first D stages");
                         constexpr int ds = DR * T::SLOTS + t;
                         constexpr int a_lo = Plan::value.alu_lo[ds], a_hi = Plan::value.alu_hi[ds], st = Plan::value.store[ds];
@@ -681,17 +636,6 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work)
                             drain_alu(a_lo + 2);
                         if constexpr (st >= 0)
                             drain_store(st);
-                    } else if constexpr (DR >= 0 && !T::load_slot(t)) {
-                        constexpr int w = DR * T::FREE + T::free_index(t);
-                        constexpr int q_lo = (w * T::DRAIN_STEPS + W - 1) / W;
-                        constexpr int q_hi = ((w + 1) * T::DRAIN_STEPS + W - 1) / W;
-                        static_assert(T::DRAIN_STEPS <= 3 * W, "at most three micro-steps per slot");
-                        if constexpr (q_lo < q_hi)
-                            drain_step(q_lo);
-                        if constexpr (q_lo + 1 < q_hi)
-                            drain_step(q_lo + 1);
-                        if constexpr (q_lo + 2 < q_hi)
-                            drain_step(q_lo + 2);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -821,7 +765,7 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work)
     }
     // every further tile writes its predecessor out during its first D stages
     if constexpr (!WORK::ONE)
-    for (int round = 1; work.has(round); ++round) {
+    for (int round = 1; (WORK::TWO && round == 1) || work.has(round); ++round) {
         const int tm = next_tm, tn = next_tn;  // what the last plan_next fetched: this tile
         plan_next(round + 1);
         stage(integral_constant<int, 0>{}, integral_constant<int, 2>{}, false_type{});
@@ -867,7 +811,7 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work)
     {
         constexpr int ROW = 256 + 16;  // bytes: 128 bf16 + padding
         uint8_t *tb = smem + wave * 32768;
-        uint8_t *tb_wr = tb + l31 * ROW + lh * 8;
+        uint8_t *tb_wr = tb + l31 * ROW + lh * 64;
         const uint8_t *tb_rd = tb + (lane >> 4) * ROW + (lane & 15) * 16;
         const uint32_t lane_off = (uint32_t)(lane >> 4) * (uint32_t)g.N * 2u + (uint32_t)(lane & 15) * 16u;
         const int64_t rows4 = (int64_t)g.N * 8;
@@ -876,19 +820,24 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    *(uint2 *)(tb_wr + j * 64 + q * 16) = make_uint2(packed[i][j][2 * q], packed[i][j][2 * q + 1]);
+                for (int u = 0; u < 2; ++u) {
+                    const uint32_t *w = &packed[i][j][4 * u];
+                    *(uint4 *)(tb_wr + (j >> 1) * 128 + (j & 1) * 32 + u * 16) = make_uint4(w[0], w[1], w[2], w[3]);
+                }
+            // four rows at a time: places 8q + 4b .. +3, rows 32b + 4q .. +3 of the band
 #pragma unroll
             for (int ps = 0; ps < 8; ++ps) {
-                const v4i d = *(const v4i *)(tb_rd + ps * 4 * ROW);
-                if (!T::EDGE || i * 32 + ps * 4 + (lane >> 4) < prow_left) {
+                const int q = ps & 3, b = ps >> 2;
+                const v4i d = *(const v4i *)(tb_rd + (8 * q + 4 * b) * ROW);
+                const uint8_t *spr = sp + (8 * b + q) * rows4;
+                if (!T::EDGE || T::band_row(wm, i) + 32 * b + 4 * q + (lane >> 4) < rows_valid) {
 #pragma unroll
                     for (int w = 0; w < 4; ++w)
                         pen_word((uint32_t)d[w]);
-                    asm volatile("global_store_dwordx4 %0, %1, %2 nt\n\ts_nop 1" : : "v"(lane_off), "v"(d), "s"(sp) : "memory");
+                    asm volatile("global_store_dwordx4 %0, %1, %2 nt\n\ts_nop 1" : : "v"(lane_off), "v"(d), "s"(spr) : "memory");
                 }
-                sp += rows4;
             }
+            sp += next_band(i);
         }
     }
     pen_flush();
@@ -903,7 +852,7 @@ __device__ __forceinline__ int xcd_slot()
 
 // Round r hands tile ids [r*G, (r+1)*G) to the G workgroups.
 struct DeferRounds {
-    static constexpr bool ONE = false;
+    static constexpr bool ONE = false, TWO = false;  // one tile at most; two at least, if any
     int slot, G, total;
     __device__ __forceinline__ bool has(int r) const { return slot + r * G < total; }
     __device__ __forceinline__ int id(int r) const { return slot + r * G; }
@@ -911,21 +860,21 @@ struct DeferRounds {
 
 // One unit: run unit / tiles of the contraction of tile unit % tiles.
 struct DeferUnit {
-    static constexpr bool ONE = true;
+    static constexpr bool ONE = true, TWO = false;
     int unit, tiles, units;
     __device__ __forceinline__ bool has(int r) const { return r == 0 && unit < units; }
     __device__ __forceinline__ int id(int) const { return unit % tiles; }
 };
 
-template <bool INT8, int PMODE, int D, int MT, bool A_E5M2 = false, bool LINES = true, bool KSPLIT = false,
+template <bool INT8, int PMODE, int D, int MT, bool A_E5M2 = false, bool KSPLIT = false,
           bool RES = false>
 __global__ __launch_bounds__(256, 1) void gemm_nt_defer_kernel(GemmDev g)
 {
     const int tiles = g.tiles_m * g.tiles_n;
     if constexpr (KSPLIT)
-        defer_tiles<INT8, PMODE, D, MT, A_E5M2, LINES, KSPLIT, RES>(g, DeferUnit{xcd_slot(), tiles, tiles * g.ksplit});
+        defer_tiles<INT8, PMODE, D, MT, A_E5M2, KSPLIT, RES>(g, DeferUnit{xcd_slot(), tiles, tiles * g.ksplit});
     else
-        defer_tiles<INT8, PMODE, D, MT, A_E5M2, LINES, KSPLIT, RES>(g, DeferRounds{xcd_slot(), (int)gridDim.x, tiles});
+        defer_tiles<INT8, PMODE, D, MT, A_E5M2, KSPLIT, RES>(g, DeferRounds{xcd_slot(), (int)gridDim.x, tiles});
 }
 
 }  // namespace tweo

@@ -21,7 +21,7 @@ namespace tweo {
 // The workgroup's tiles of the input gradient.  Round r goes over all slots that have more than r tiles, in slot order, so
 // each XCD has a contiguous run of ids in every round.
 struct DeferClasses {
-    static constexpr bool ONE = false;
+    static constexpr bool ONE = false, TWO = true;
     DeferPairPlan p;
     int before[4];  // slots of class c in front of this one, for the classes before its own
     int place, mine;  // its place in its own class, its tiles
@@ -53,9 +53,14 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_defer_pair_kernel(GemmDev d, G
         }
         start += plan.n[c];
     }
-    defer_tiles<false, 0, 3, 4, A_E5M2, true, !WHOLE, false>(w, DeferUnit{slot, w_tiles, w_tiles * w.ksplit});
+    defer_tiles<false, 0, 3, 4, A_E5M2, !WHOLE, false>(w, DeferUnit{slot, w_tiles, w_tiles * w.ksplit});
     block_barrier();  // every wave is done with the stages in LDS
-    defer_tiles<false, 0, D, 4, A_E5M2, true, false, false>(d, work);
+    // (a path of its own for one tile: with one loop for any number of them 60 to 80 registers go through memory behind the
+    // first one's last stage, 724 bytes a lane, and the 8192-row layers lose 8 us of 50)
+    if (work.mine >= 2)
+        defer_tiles<false, 0, D, 4, A_E5M2, false, false>(d, work);
+    else if (work.mine == 1)
+        defer_tiles<false, 0, 3, 4, A_E5M2, false, false>(d, DeferUnit{work.id(0), d.tiles_m * d.tiles_n, d.tiles_m * d.tiles_n});
 }
 
 // Time of the longest workgroup, in stages of 1.37 us, fitted to 240 timings of 69 layers of 1024 to 50432 rows, operands cold (8 %
