@@ -1426,10 +1426,10 @@ static double ksplit_us(int64_t M, int64_t N, int64_t K, int splits, bool deferr
 }
 
 // The deferred-epilogue kernel covers whole 256x256 tiles, K in whole stages with enough of
-// them to drain a tile under (and, with a residual, to fetch that: 16 stages), p in {0, 4}.
+// them to drain a tile under (and, with a residual, to fetch that: 11 stages), p in {0, 4}.
 static bool defer_ok(const GemmArgs &a)
 {
-    return a.M % 256 == 0 && a.N % 256 == 0 && a.K % 128 == 0 && a.K >= (a.residual != nullptr ? 2048 : 512) &&
+    return a.M % 256 == 0 && a.N % 256 == 0 && a.K % 128 == 0 && a.K >= (a.residual != nullptr ? 11 * 128 : 512) &&
            a.row_step == nullptr && (a.p == 0 || a.p == 4) && a.N <= ((int64_t)1 << 22);
 }
 
@@ -1564,7 +1564,7 @@ template <bool INT8, int PMODE, int D, int MT, bool A_E5M2 = false, bool RES = f
 static hipError_t launch_defer_inst(const GemmArgs &a, hipStream_t s)
 {
     using T = DeferTile<MT>;
-    constexpr int LDS = RES ? T::LDS_BYTES_RES : T::LDS_BYTES;
+    constexpr int LDS = T::LDS_BYTES;
     constexpr auto kernel = gemm_nt_defer_kernel<INT8, PMODE, D, MT, A_E5M2, false, RES>;
     static bool attr_done = false;
     if (!attr_done) {
@@ -1587,15 +1587,10 @@ static hipError_t launch_defer(const GemmArgs &a, hipStream_t s)
     // a tile is written out over the first 15, 7, 5 or 3 stages of the next one (never its last)
     const int64_t kt = a.K / 128;
     if constexpr (!INT8) {
-        // with a residual the write-out (D stages), the residual's ten stages and the last one must fit:
-        // seven stages of write-out from 18 on, five for 16 and 17
-        if (a.residual != nullptr) {
-            if (a.p == 4)
-                return kt >= 18 ? launch_defer_inst<false, 4, 7, 4, false, true>(a, s)
-                                : launch_defer_inst<false, 4, 5, 4, false, true>(a, s);
-            return kt >= 18 ? launch_defer_inst<false, 0, 7, 4, false, true>(a, s)
-                            : launch_defer_inst<false, 0, 5, 4, false, true>(a, s);
-        }
+        // with a residual the write-out (5 stages), the residual's five and the last one must fit (over 7 stages: 2 us of 165
+        // slower under 5632 columns, 5 of 136 under 3072)
+        if (a.residual != nullptr)
+            return a.p == 4 ? launch_defer_inst<false, 4, 5, 4, false, true>(a, s) : launch_defer_inst<false, 0, 5, 4, false, true>(a, s);
         if (a.p == 4) {
             if (kt >= 16)
                 return launch_defer_inst<false, 4, 15, 4>(a, s);
@@ -1617,8 +1612,8 @@ static hipError_t launch_defer192(const GemmArgs &a, hipStream_t s)
 {
     if constexpr (!INT8) {
         if (a.residual != nullptr)
-            return a.p == 4 ? launch_defer_inst<false, 4, 7, 3, false, true>(a, s)
-                            : launch_defer_inst<false, 0, 7, 3, false, true>(a, s);
+            return a.p == 4 ? launch_defer_inst<false, 4, 5, 3, false, true>(a, s)
+                            : launch_defer_inst<false, 0, 5, 3, false, true>(a, s);
         if (a.p == 4)
             return launch_defer_inst<false, 4, 15, 3>(a, s);
     }

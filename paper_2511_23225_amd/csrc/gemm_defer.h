@@ -52,12 +52,12 @@ struct DeferTile {
     static constexpr int BM = MT * 64, BN = 256, BK = 128, NWAVES = 4, THREADS = 256;
     static constexpr int A_BYTES = BM * BK, STAGE_BYTES = (BM + BN) * BK;
     static constexpr int STAGE_STRIDE = 65536;            // power of two: buffers are toggled by XOR
-    static constexpr int LDS_BYTES = 2 * STAGE_STRIDE;
-    // residual form: 4 KB per pair of neighbouring blocks (32 rows x 128 B), two per wave, behind the stages
-    static constexpr int RES_UNITS = 2 * MT, RES_UNIT_BYTES = 4096, RES_WAVE_BYTES = 2 * RES_UNIT_BYTES;
-    static constexpr int RES_STAGES = RES_UNITS + 2;      // unit c is loaded in the c-th of them, read in the (c+2)-th
-    static constexpr int LDS_BYTES_RES = LDS_BYTES + NWAVES * RES_WAVE_BYTES;
-    static_assert(LDS_BYTES_RES <= 160 * 1024, "LDS capacity with a residual");
+    static constexpr int STAGES_BYTES = 2 * STAGE_STRIDE;
+    // behind the stages, 8 KB per wave: the last tile's write-out, the residual before that
+    static constexpr int WAVE_BYTES = 8192, LDS_BYTES = STAGES_BYTES + NWAVES * WAVE_BYTES;
+    static_assert(32 * 256 <= WAVE_BYTES, "a band of the write-out");
+    // residual form: 16-byte loads of a lane per tile, stages from the first load to the last exchange
+    static constexpr int RES_LOADS = 8 * MT, RES_STAGES = 5;
     static constexpr int SLAB = NB, SLOTS = 2 * NB;       // MFMA slots per K slab / per stage
     static constexpr int NA = BM / 32, NBP = BN / 32;     // operand pieces per wave per stage
     static constexpr int HALVES = 2 * NB;                 // half blocks to convert per tile
@@ -149,6 +149,11 @@ struct DrainPlanOf {  // evaluated once per tile shape and D, not once per slot 
     static constexpr DrainPlan<T, D, PEN> value = make_drain_plan<T, D, PEN>();
 };
 
+// no list follows
+struct DeferEnd {
+    __device__ __forceinline__ void operator()() const {}
+};
+
 // PMODE: 4 = TWEO penalty with p = 4 (the paper's setting), 0 = none.  D: number of stages of
 // the next tile over which the write-out of a tile is spread (3, 5, 7 or 15; needs K >= 128 * (D + 1):
 // the tile's last stage, which converts its own blocks, takes no part in it).
@@ -165,22 +170,19 @@ struct DrainPlanOf {  // evaluated once per tile shape and D, not once per slot 
 // unit per workgroup, so nothing is deferred.
 // RES (FP8): y = bf16(acc * alpha + residual).  The registers of the packed output are idle between
 // the end of a tile's write-out (stage D of the next tile) and the next conversion: the residual of
-// the current tile is brought there during the tile's last RES_STAGES stages before the final one
-// and the conversion becomes a multiply-add onto it.  It travels like the operands, by direct-to-LDS
-// loads of whole 128-byte lines (a load to registers in the MFMA layout touches 32 rows for 16 bytes
-// each, four times the address work), into 8 KB per wave behind the operand stages: nobody else
-// touches them, so no barrier is added.  Four loads per stage go in front of the B pieces, the wait
-// in front of the second barrier then leaves twelve loads in flight instead of eight, and a unit
-// has a whole stage (1.2 us) to arrive in.  Kernel times with the penalty on, against the 8-wave
-// streaming kernel, which adds the residual behind the tile with nothing running under it:
-// 50432x3072 -> 768 175 -> 133 us, 16384x5632 -> 2048 174 -> 140 us (without a residual 120 and 133).
-// On 256x256 tiles it needs more registers than there are: 28-31 vector and 15-23 scalar registers are
-// spilled (88-100 bytes a lane; on 192x256 tiles, and without a residual, nothing goes to memory).  The
-// reloads at the tile boundary and in a tile's first stage each wait for the operand stream as well; the
-// counted waits stay right, since further memory operations only make them stricter.
+// the current tile is loaded there, whole lines as the write-out stores them, all of it in one stage; two stages later
+// the quads' lanes exchange their pieces back, and the conversion becomes a multiply-add onto it.  Loads come back in
+// order, so what is late holds up the operand stream behind it, and a residual comes from HBM: once a tile, as here, that costs
+// about a stage (and the wait in front of the first exchange drains the stream), while units of 4 KB in eight stages,
+// through LDS, held up each of them.  Kernel, residuals from HBM, with the penalty: 16384x5632 -> 2048 187 -> 165 us (145 without
+// a residual), 50432x3072 -> 768 148 -> 136 (123).  256x256 tiles spill 13-32 vector registers, values of the last
+// write-out and of the tile boundary.
 // work: the tiles of the workgroup, in order (DeferRounds, DeferClasses), or its one unit (DeferUnit).
-template <bool INT8, int PMODE, int D, int MT, bool A_E5M2, bool KSPLIT, bool RES, typename WORK>
-__device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work)
+// A launch may go through several such lists, one after the other: opened: the first stages' loads have been issued (defer_open);
+// between(): called when nobody reads the stages any more, in front of the last write-out, to open the next list; pen: the
+// penalty terms of the wave's lanes.
+template <bool INT8, int PMODE, int D, int MT, bool A_E5M2, bool KSPLIT, bool RES, typename WORK, typename BETWEEN>
+__device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, bool opened, BETWEEN between, float &pen)
 {
     using T = DeferTile<MT>;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -188,6 +190,8 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work)
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int wm = wave >> 1, wn = wave & 1;
     const int l31 = lane & 31, lh = lane >> 5;
+    constexpr bool LAST_LIST = std::is_same<BETWEEN, DeferEnd>::value;
+    static_assert(LAST_LIST || MT == 4, "what follows counts on 32 stores of every wave");
     if (!work.has(0))
         return;
     int kt = g.K / T::BK, k_first = 0;
@@ -394,7 +398,6 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work)
     // packed[i][j][2q+h]: bf16 pair of block (i, j): row lane_row(l31) of band i, columns 32lh + 16(j%2) + 4q + 2h, +1 of
     // the pair of blocks j/2
     uint32_t packed[MT][4][8];
-    float pen = 0.0f;
     // half h of block b = h/2 (i = b/4, j = b%4): accumulator words 8*(h%2) .. +7
     auto convert_half = [&](int h) {
         const int i = h >> 3, j = (h >> 1) & 3, q0 = (h & 1) * 2;  // block h/2 = 4i + j
@@ -495,54 +498,38 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work)
             sp += next_band(i);
     };
 
-    // ---- residual (RES): unit c = block pair (band c / 2, columns 64 * (c % 2) .. +63) ------------
-    // load n of a unit fills rows 8n .. 8n+7 (128 bytes each, chunks XOR-swizzled with (row/2)%8 as
-    // in the operand stages); buffer c % 2 of the wave's own LDS
-    const uint32_t res_lds = lds_base + T::LDS_BYTES + wave * T::RES_WAVE_BYTES;
+    // ---- residual (RES): load n = store n of the write-out, turned round ---------------------------------
     const uint8_t *rp = nullptr;  // this wave's columns of the tile, from its first row (EDGE: the tile's) on
     int res_valid = 0;            // EDGE: rows of the tile inside the matrix
-    // chunk of a lane in an even load (rows 0..7 of 16); in an odd one its bit 2 is flipped, which is
-    // bit 6 of the offset (a row is a multiple of 512 bytes)
-    const uint32_t res_voff = (uint32_t)T::lane_row(dma_row) * (uint32_t)g.N * 2u + (uint32_t)((dma_p ^ (dma_row >> 1)) << 4);
     auto res_begin = [&](int tm, int tn) {
-        const int64_t row0 = (int64_t)tm * T::BM + (T::EDGE ? 0 : wm * MT * 32);
+        const int64_t row0 = (int64_t)tm * T::BM + (T::EDGE ? 0 : T::band_row(wm, 0));
         rp = (const uint8_t *)g.residual + (row0 * g.N + (int64_t)tn * T::BN + wn * 128) * 2;
         res_valid = g.M - tm * T::BM;
     };
-    auto res_load = [&](int c, int n) {
-        const int i = c >> 1, jp = c & 1;
-        const uint32_t dst = res_lds + (c & 1) * T::RES_UNIT_BYTES + n * 1024;
-        const int64_t unit = (int64_t)jp * 128 + (T::EDGE ? 0 : (T::band_row(0, i) / 16) * rows16);
+    auto res_load = [&](int n) {
+        const int c = n / 4, u = n % 4, i = c >> 1, jp = c & 1;
+        const uint8_t *from = rp + jp * 128;
+        uint32_t off = out_quad;
         if constexpr (T::EDGE) {  // rows past the matrix load the last valid one
-            const int rt = T::band_row(wm, i) + T::lane_row(8 * n + dma_row);
-            const uint32_t v = (uint32_t)(rt < res_valid ? rt : res_valid - 1) * (uint32_t)g.N * 2u +
-                               (uint32_t)((dma_p ^ (dma_row >> 1) ^ (4 * (n & 1))) << 4);
-            dma_load16(dst, rp + unit, v);
+            const int r = T::band_row(wm, i) + (lane_row & ~3) + u;
+            off = (uint32_t)(r < res_valid ? r : res_valid - 1) * (uint32_t)g.N * 2u + (uint32_t)lh * 64u + (uint32_t)(l31 & 3) * 16u;
         } else {
-            dma_load16(dst, rp + unit + n * (rows16 >> 2), res_voff ^ (64u * (n & 1)));
+            from += (T::band_row(0, i) / 16) * rows16 + u * row_bytes;
         }
-    };
-    // 16-byte piece (X, u) of lane (row, lh): columns 32lh + 16X + 8u .. +7 of the unit's 64, words 4u .. 4u+3 of block X
-    const uint32_t res_rd = (uint32_t)(T::LDS_BYTES + wave * T::RES_WAVE_BYTES + l31 * 128 + (((4 * lh) ^ sw) << 4));
-    auto res_read = [&](int c, int X, int u) {
-        const v4i v = *(const v4i *)(smem + (res_rd ^ (uint32_t)((2 * X + u) << 4)) + (c & 1) * T::RES_UNIT_BYTES);
-        uint32_t *w = &packed[c >> 1][2 * (c & 1) + X][4 * u];
+        asm("" : "+s"(from));  // one scalar base and one offset register for all of them
+        const v4i v = *(const v4i *)(from + off);
+        uint32_t *w = packed[i][2 * jp + (u >> 1)] + 4 * (u & 1);
 #pragma unroll
         for (int d = 0; d < 4; ++d)
             w[d] = (uint32_t)v[d];
     };
-
-    // The penalty terms are summed per lane over every tile of the workgroup (a few thousand
-    // fp32 terms), reduced over the wave once, at the end, and written as
-    // partials[workgroup][wave]; the finishing kernel adds them in index order in fp64.
-    // Sum of a^4 here, times 1/(tau+eps)^4 at the end.
-    auto pen_flush = [&]() {
-        if constexpr (PMODE != 0) {
-            const float it2 = g.inv_tau * g.inv_tau;
-            const float v = wave_reduce_sum(pen * (it2 * it2));
-            if (lane == 0)
-                g.partials[blockIdx.x * T::PARTIALS_PER_WG + wave] = v;
-        }
+    auto res_exchange = [&](int a) {
+        const int c = a / 8, i = c >> 1, jp = c & 1, d = (a % 8) >> 1;
+        uint32_t *A = packed[i][2 * jp], *B = packed[i][2 * jp + 1];
+        if ((a & 1) == 0)
+            quad_exchange<0>(A[d], A[4 + d], B[d], B[4 + d], qmasks);
+        else
+            quad_exchange<1>(A[d], A[4 + d], B[d], B[4 + d], qmasks);
     };
 
     // ---- one stage: 2 slabs x 16 MFMA slots ------------------------------------------------
@@ -558,7 +545,8 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work)
     auto stage = [&](auto dr_c, auto first_c, auto last_c, auto... rs_c) {
         constexpr int DR = decltype(dr_c)::value, FIRST = decltype(first_c)::value;
         constexpr int RS = (-1 + ... + (decltype(rs_c)::value + 1));
-        constexpr bool RES_LOADS = RS >= 0 && RS < T::RES_UNITS;
+        // residual loads issued before slot t of its first stage: behind A's pieces, so that no wait of that stage needs them
+        constexpr auto res_before = [](int t) { return t <= T::NA / 2 ? 0 : (t - T::NA / 2) * T::RES_LOADS / (T::SLOTS - T::NA / 2); };
         constexpr bool LAST = decltype(last_c)::value;
         auto slot_body = [&](auto t_c) {
                 {
@@ -568,14 +556,16 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work)
                         // every wave has read the B half of this stage (its slab-1 fragments were
                         // requested in the last four slots of slab 0): the half can be refilled
                         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                        if constexpr (RS == 2)
+                            __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0), where the compiler sees it: the residual is there
                         block_barrier();
                     }
                     if constexpr (t == T::SLOTS - 4) {
                         // every LDS read of this stage has been issued: wait for them and for this
                         // wave's share of the next stage (everything but the eight B pieces of the
                         // stage after next, the youngest loads), then publish
-                        // (and, of a residual, the four loads in front of those)
-                        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(RES_LOADS ? 12 : 8) : "memory");
+                        // (and what has been asked for of a residual)
+                        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(RS == 0 ? 8 + res_before(T::SLOTS - 4) : 8) : "memory");
                         block_barrier();
                         flip(T::STAGE_STRIDE ^ 64u);
                     }
@@ -608,13 +598,16 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work)
                     } else if constexpr (t >= T::SLOTS - 4 && t < T::SLOTS - 4 + T::NA / 2) {
                         dma_piece_a(t - (T::SLOTS - 4));
                     }
-                    if constexpr (RES_LOADS && t >= T::SLAB - 4 && t < T::SLAB)
-                        res_load(RS, t - (T::SLAB - 4));
+                    if constexpr (RS == 0) {
+#pragma unroll
+                        for (int n = 0; n < T::RES_LOADS; ++n)
+                            if (n >= res_before(t) && n < res_before(t + 1))
+                                res_load(n);
+                    }
                     if constexpr (RS >= 2) {
-                        if constexpr (t == 1 || t == 2) {
-                            res_read(RS - 2, t - 1, 0);
-                            res_read(RS - 2, t - 1, 1);
-                        }
+                        constexpr int a = (RS - 2) * T::SLOTS + t - (T::SLAB + 2);
+                        if constexpr (a >= 0 && a < 2 * T::RES_LOADS)
+                            res_exchange(a);
                     }
                     // conversion of the tile that ends here / ended in the previous stage
 #pragma unroll
@@ -657,21 +650,31 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work)
     set_voffs_a(__builtin_amdgcn_readlane(tvalid, 0));
     const int first_tm = __builtin_amdgcn_readlane(tmv, 0), first_tn = __builtin_amdgcn_readlane(tnv, 0);
     plan_next(1);
+    if (!opened) {
 #pragma unroll
-    for (int p8 = 0; p8 < T::NA; ++p8)
-        dma_piece_a(p8);
+        for (int p8 = 0; p8 < T::NA; ++p8)
+            dma_piece_a(p8);
+    }
     stream_advance(sa, false);
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
+        if (!opened) {
 #pragma unroll
-        for (int p8 = 0; p8 < T::NBP; ++p8)
-            dma_piece_b(p8);
+            for (int p8 = 0; p8 < T::NBP; ++p8)
+                dma_piece_b(p8);
+        }
         stream_advance(sb, true);
     }
+    if (!opened) {
 #pragma unroll
-    for (int p8 = 0; p8 < T::NA / 2; ++p8)
-        dma_piece_a(p8);
-    wait_vmcnt<T::NBP + T::NA / 2>();
+        for (int p8 = 0; p8 < T::NA / 2; ++p8)
+            dma_piece_a(p8);
+        wait_vmcnt<T::NBP + T::NA / 2>();
+    } else {
+        // the stores of the write-out that came in between (32, of a unit's sums 64) are younger, and the counter goes down
+        // in order: with no more than these and the youngest loads left, stage 0 is in
+        wait_vmcnt<T::NBP + T::NA / 2 + 32>();
+    }
     block_barrier();
     load_a(fa[0], 0);
 #pragma unroll
@@ -686,6 +689,10 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work)
         // read written as asm against them): a few hundred cycles
         asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7\n\ts_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
         wait_vmcnt<0>();
+        if constexpr (!LAST_LIST) {
+            block_barrier();
+            between();
+        }
         // written through the L2s: the reduce kernel starts when they are clean (3072x768 over 8192 tokens,
         // 38 MB of runs, both launches 33.4 us with the runs left dirty, 31.8 now)
         float4 *dst = (float4 *)g.ksplit_out + ((int64_t)work.unit * T::NWAVES + wave) * (T::NB * 4 * kWave) + lane;
@@ -725,25 +732,14 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work)
                 stage(integral_constant<int, 2>{}, mid{}, false_type{});
                 stage(integral_constant<int, 3>{}, mid{}, false_type{});
                 stage(integral_constant<int, 4>{}, mid{}, false_type{});
-                if constexpr (D >= 7) {
-                    stage(integral_constant<int, 5>{}, mid{}, false_type{});
-                    stage(integral_constant<int, 6>{}, mid{}, false_type{});
-                }
                 s = D;
             }
-            static_assert(!RES || D == 5 || D == 7, "stages stamped out above");
+            static_assert(D == 5, "stages stamped out above");
             res_begin(tm, tn);
             for (; s < kt - 1 - T::RES_STAGES; ++s)
                 stage(no_drain{}, mid{}, false_type{});
-            if constexpr (MT == 4)
-                residual_stages(integral_constant<int, 0>{}, integral_constant<int, 1>{}, integral_constant<int, 2>{},
-                                integral_constant<int, 3>{}, integral_constant<int, 4>{}, integral_constant<int, 5>{},
-                                integral_constant<int, 6>{}, integral_constant<int, 7>{}, integral_constant<int, 8>{},
-                                integral_constant<int, 9>{});
-            else
-                residual_stages(integral_constant<int, 0>{}, integral_constant<int, 1>{}, integral_constant<int, 2>{},
-                                integral_constant<int, 3>{}, integral_constant<int, 4>{}, integral_constant<int, 5>{},
-                                integral_constant<int, 6>{}, integral_constant<int, 7>{});
+            residual_stages(integral_constant<int, 0>{}, integral_constant<int, 1>{}, integral_constant<int, 2>{},
+                            integral_constant<int, 3>{}, integral_constant<int, 4>{});
             stage(no_drain{}, mid{}, true_type{});
             store_begin(tm, tn);
             ++round;
@@ -795,11 +791,11 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work)
         store_begin(tm, tn);
     }
     }
-    // The workgroup's last tile: the rest of its conversion, then its write-out with nothing to
+    // The last tile: the rest of its conversion, then its write-out with nothing to
     // hide it under.  Here every CU of the chip stores at the same time, and 16-byte pieces would
-    // queue up at the L2s (eight times the requests of whole lines).  The LDS is idle now, so a
-    // band of the wave's sub-tile (32 rows x 128 columns) goes through a wave-private 32 KB of
-    // the stage buffers and comes back with 16 lanes per row: whole 128-byte lines per store.
+    // queue up at the L2s (eight times the requests of whole lines).  A
+    // band of the wave's sub-tile (32 rows x 128 columns) goes through the wave's own 8 KB
+    // of LDS and comes back with 16 lanes per row: whole 128-byte lines per store.  16-byte chunks XOR-swizzled with the row.
 #pragma unroll
     for (int h = 0; h < T::HALVES; ++h)
         if (T::convert_slot(h) >= T::SLOTS) {
@@ -807,12 +803,14 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work)
             __builtin_amdgcn_sched_barrier(0);
         }
     wait_vmcnt<0>();  // the operand stream's last (unused) loads have landed in the stage buffers
-    block_barrier();  // ... and every wave is done reading them
+    if constexpr (!LAST_LIST) {
+        block_barrier();  // ... and every wave is done reading them
+        between();
+    }
     {
-        constexpr int ROW = 256 + 16;  // bytes: 128 bf16 + padding
-        uint8_t *tb = smem + wave * 32768;
-        uint8_t *tb_wr = tb + l31 * ROW + lh * 64;
-        const uint8_t *tb_rd = tb + (lane >> 4) * ROW + (lane & 15) * 16;
+        uint8_t *tb = smem + T::STAGES_BYTES + wave * T::WAVE_BYTES;
+        const uint32_t wr = (uint32_t)(l31 * 256 + (((4 * lh) ^ (l31 & 15)) << 4));
+        const uint32_t rd = (uint32_t)((lane >> 4) * 256 + (((lane & 15) ^ (lane >> 4)) << 4));
         const uint32_t lane_off = (uint32_t)(lane >> 4) * (uint32_t)g.N * 2u + (uint32_t)(lane & 15) * 16u;
         const int64_t rows4 = (int64_t)g.N * 8;
 #pragma unroll
@@ -822,13 +820,13 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work)
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
                     const uint32_t *w = &packed[i][j][4 * u];
-                    *(uint4 *)(tb_wr + (j >> 1) * 128 + (j & 1) * 32 + u * 16) = make_uint4(w[0], w[1], w[2], w[3]);
+                    *(uint4 *)(tb + (wr ^ (uint32_t)((8 * (j >> 1) + 2 * (j & 1) + u) << 4))) = make_uint4(w[0], w[1], w[2], w[3]);
                 }
             // four rows at a time: places 8q + 4b .. +3, rows 32b + 4q .. +3 of the band
 #pragma unroll
             for (int ps = 0; ps < 8; ++ps) {
                 const int q = ps & 3, b = ps >> 2;
-                const v4i d = *(const v4i *)(tb_rd + (8 * q + 4 * b) * ROW);
+                const v4i d = *(const v4i *)(tb + (8 * q + 4 * b) * 256 + (rd ^ (uint32_t)((8 * (q & 1) + 4 * b) << 4)));
                 const uint8_t *spr = sp + (8 * b + q) * rows4;
                 if (!T::EDGE || T::band_row(wm, i) + 32 * b + 4 * q + (lane >> 4) < rows_valid) {
 #pragma unroll
@@ -840,7 +838,60 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work)
             sp += next_band(i);
         }
     }
-    pen_flush();
+}
+
+// The penalty terms are summed per lane over every tile of the workgroup (a few thousand
+// fp32 terms), reduced over the wave once, at the end, and written as
+// partials[workgroup][wave]; the finishing kernel adds them in index order in fp64.
+// Sum of a^4 here, times 1/(tau+eps)^4 at the end.
+template <int PMODE>
+__device__ __forceinline__ void defer_penalty(const GemmDev &g, float pen)
+{
+    if constexpr (PMODE != 0) {
+        const float it2 = g.inv_tau * g.inv_tau;
+        const float v = wave_reduce_sum(pen * (it2 * it2));
+        if ((threadIdx.x & (kWave - 1)) == 0)
+            g.partials[blockIdx.x * DeferTile<4>::PARTIALS_PER_WG + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave)] = v;
+    }
+}
+
+// The loads in front of the first stage of a list (as in defer_tiles): stage 0 whole, B of stage 1, the first half of A's pieces.
+template <int MT, typename WORK>
+__device__ __forceinline__ void defer_open(const GemmDev &g, const WORK &work)
+{
+    using T = DeferTile<MT>;
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    if (!work.has(0))
+        return;
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    int tm, tn;
+    tile_from_id(work.id(0), g.tiles_m, g.tiles_n, tm, tn);
+    tm = __builtin_amdgcn_readfirstlane(tm);
+    tn = __builtin_amdgcn_readfirstlane(tn);
+    const uint8_t *a = g.A + (int64_t)tm * T::BM * g.K, *b = g.B + (int64_t)tn * T::BN * g.K;
+    const int place = wave * 8 + (lane >> 3), valid = g.M - tm * T::BM;
+    const uint32_t chunk = (uint32_t)(((lane & 7) ^ ((lane >> 4) + 4 * (wave & 1))) << 4);
+    const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)smem + wave * 1024;
+    auto piece_a = [&](int p8, int stage) {
+        const int row = T::band_row(0, p8) + T::lane_row(place);
+        dma_load16(lds + p8 * 4096 + stage * T::STAGE_STRIDE, a + stage * T::BK,
+                   (uint32_t)(!T::EDGE || row < valid ? row : valid - 1) * (uint32_t)g.K + chunk);
+    };
+    auto piece_b = [&](int p8, int stage) {
+        dma_load16(lds + T::A_BYTES + p8 * 4096 + stage * T::STAGE_STRIDE, b + stage * T::BK,
+                   (uint32_t)(T::band_row(0, p8) + T::lane_row(place)) * (uint32_t)g.K + chunk);
+    };
+#pragma unroll
+    for (int p8 = 0; p8 < T::NA; ++p8)
+        piece_a(p8, 0);
+#pragma unroll
+    for (int st = 0; st < 2; ++st)
+#pragma unroll
+        for (int p8 = 0; p8 < T::NBP; ++p8)
+            piece_b(p8, st);
+#pragma unroll
+    for (int p8 = 0; p8 < T::NA / 2; ++p8)
+        piece_a(p8, 1);
 }
 
 // Workgroup's place in the order in which each XCD (workgroup index mod 8, a private L2 each) has a contiguous run.
@@ -871,10 +922,12 @@ template <bool INT8, int PMODE, int D, int MT, bool A_E5M2 = false, bool KSPLIT 
 __global__ __launch_bounds__(256, 1) void gemm_nt_defer_kernel(GemmDev g)
 {
     const int tiles = g.tiles_m * g.tiles_n;
+    float pen = 0.0f;
     if constexpr (KSPLIT)
-        defer_tiles<INT8, PMODE, D, MT, A_E5M2, KSPLIT, RES>(g, DeferUnit{xcd_slot(), tiles, tiles * g.ksplit});
+        defer_tiles<INT8, PMODE, D, MT, A_E5M2, KSPLIT, RES>(g, DeferUnit{xcd_slot(), tiles, tiles * g.ksplit}, false, DeferEnd{}, pen);
     else
-        defer_tiles<INT8, PMODE, D, MT, A_E5M2, KSPLIT, RES>(g, DeferRounds{xcd_slot(), (int)gridDim.x, tiles});
+        defer_tiles<INT8, PMODE, D, MT, A_E5M2, KSPLIT, RES>(g, DeferRounds{xcd_slot(), (int)gridDim.x, tiles}, false, DeferEnd{}, pen);
+    defer_penalty<PMODE>(g, pen);
 }
 
 }  // namespace tweo
