@@ -1239,13 +1239,14 @@ size_t stream_k_workspace_bytes()
 // deferred-epilogue persistent kernel (256x256, four waves; M, N % 256 == 0, K % 128 == 0, K >= 512).  16: the same
 // kernel on 192x256 tiles (any M, K >= 2048).  17: the INT8 weight-streaming kernel (M <= 64).  4, 18 to 22: the
 // ring kernel on 64x64, 64x64 (two groups), 64x128, 64x128 (two groups), 128x128 and 96x128 tiles.
-constexpr int kNumVariants = 22;
+// 23: the deferred-epilogue kernel on both in one launch (any M, K >= 768).
+constexpr int kNumVariants = 23;
 static const int kVariantBM[kNumVariants + 1] = {0, 256, 256, 128, 64, 256, 256, 256, 128, 256, 128, 256, 256, 128, 192, 256, 192, 64,
-                                                 64, 64, 64, 128, 96};
+                                                 64, 64, 64, 128, 96, 256};
 static const int kVariantBN[kNumVariants + 1] = {0, 256, 128, 128, 64, 256, 256, 128, 128, 128, 256, 256, 128, 128, 256, 256, 256, 64,
-                                                 64, 128, 128, 128, 128};
+                                                 64, 128, 128, 128, 128, 256};
 static int ring_variant(int shape) { return shape == 0 ? 4 : 17 + shape; }
-static int ring_shape(int variant) { return variant == 4 ? 0 : variant >= 18 ? variant - 17 : -1; }
+static int ring_shape(int variant) { return variant == 4 ? 0 : variant >= 18 && variant <= 22 ? variant - 17 : -1; }
 int gemm_num_variants() { return kNumVariants; }
 bool gemm_variant_exists(int v)
 {
@@ -1386,16 +1387,25 @@ static double weight_stream_us(int64_t M, int64_t N, int64_t K)
     return (double)N * (double)K * 1e-6 * (0.169 + 40.0 / (double)K + (double)M * (0.0008 + 1.1 / (double)K)) + 3.0;
 }
 
+// What the persistent kernels' tiles cost beside their stages (tiled_us, which compares kernels, leaves it out).
+static double tile_overhead_us(int v, int64_t M, int64_t N)
+{
+    const int bm = v == 15 || v == 11 ? 256 : 192;
+    return 1.27 * 2.0 * (bm == 256 ? 1.0 : 0.77) * std::ceil((double)(((M + bm - 1) / bm) * (N / 256)) / (double)num_cus());
+}
+
 // The kernel a product runs on and its estimated time: the ring kernel, where all its workgroups are resident
 // at once and that is the faster way.
 struct Pick {
     int v;
     double us;
 };
-static Pick pick(int64_t M, int64_t N, int64_t K, bool int8 = false)
+static Pick pick(int64_t M, int64_t N, int64_t K, bool int8 = false, bool mixed = true)
 {
     if (g_tile_override != 0) {
         const int v = g_tile_override == 17 ? 4 : g_tile_override;
+        if (v == 23)
+            return mixed && defer_mix_pick(M, N, K, num_cus()).workgroups != 0 ? Pick{v, 0.0} : Pick{pick_tiled(M, N, K, 16), 0.0};
         return Pick{ring_shape(v) >= 0 ? v : pick_tiled(M, N, K, v), 0.0};
     }
     int v = pick_tiled(M, N, K, 0);
@@ -1405,7 +1415,21 @@ static Pick pick(int64_t M, int64_t N, int64_t K, bool int8 = false)
     const double us = wide ? wide_us(v, M, N, K) : tiled_us(v, M, N, K, int8);
     double ring_us;
     const int shape = ring_pick(M, N, K, num_cus(), int8, &ring_us);
-    return ring_us < us ? Pick{ring_variant(shape), ring_us} : Pick{v, us};
+    if (ring_us < us)
+        return Pick{ring_variant(shape), ring_us};
+    // Two tile heights in one launch.  In the place of one height of the same kernel (whole tiles, or K >= 2048) from 16 stages on, where
+    // it saves a twentieth of the rounds (forward products, us: 50432x3072 -> 768 with residual and penalty 139 / 128, 20000x2048
+    // -> 2048 69 / 67; 15120x2176 -> 2816, at 0.951, 2 % slower); in the place of the 8-wave kernel (ragged rows under shorter contractions)
+    // wherever it is not estimated slower (33007x1024 -> 2048 1.42 times as fast, 7400x1664 -> 3584 1.14, 15248x768 -> 2048
+    // 1.07), INT8 where it is a tenth faster (8912x1024 -> 1280, at 0.935, 4 % slower).
+    if (mixed && (v == 11 || v == 14 || v == 15 || v == 16)) {
+        const DeferMix mix = defer_mix_pick(M, N, K, num_cus());
+        const bool same = v == 15 || v == 16;
+        if (mix.workgroups != 0 && (!same || K >= 2048) &&
+            mix.us < (same ? 0.945 : int8 ? 0.91 : 1.0) * (tiled_us(v, M, N, K, int8) + tile_overhead_us(v, M, N)))
+            return Pick{23, std::min(us, mix.us)};
+    }
+    return Pick{v, us};
 }
 
 // the ring kernel's time for a product, 1e300 where it does not take it
@@ -1439,9 +1463,16 @@ static bool defer192_ok(const GemmArgs &a)
            a.row_step == nullptr && (a.p == 0 || a.p == 4) && a.N <= ((int64_t)1 << 22);
 }
 
+static bool defer_mix_ok(const GemmArgs &a)  // (that defer_mix_pick has rows for it is known)
+{
+    return (a.residual == nullptr || a.K >= 11 * 128) && a.row_step == nullptr && (a.p == 0 || a.p == 4);
+}
+
 static int resolve_variant(const GemmArgs &a, bool int8 = false)
 {
     int v = pick(a.M, a.N, a.K, int8).v;
+    if (v == 23 && !defer_mix_ok(a))
+        v = pick(a.M, a.N, a.K, int8, false).v;
     if (v == 15 && !defer_ok(a))
         v = 11;
     if (v == 16 && !defer192_ok(a))
@@ -1452,6 +1483,8 @@ static int resolve_variant(const GemmArgs &a, bool int8 = false)
 int fp8_gemm_partials(const GemmArgs &a)
 {
     const int v = resolve_variant(a);
+    if (v == 23)
+        return defer_mix_pick(a.M, a.N, a.K, num_cus()).workgroups * DeferTile<4>::PARTIALS_PER_WG;
     if (v == 15 || v == 16)  // one partial per wave of each workgroup (never more than per 64x64 block)
         return defer_workgroups(a.M, a.N, kVariantBM[v]) * DeferTile<4>::PARTIALS_PER_WG;
     return (int)(((a.M + kVariantBM[v] - 1) / kVariantBM[v]) * ((a.N + kVariantBN[v] - 1) / kVariantBN[v]));
@@ -1635,6 +1668,7 @@ static hipError_t launch_gemm(const GemmArgs &a, hipStream_t s)
     case 13: return launch_stream<S128x128w4, INT8, 2>(a, s);
     case 14: return launch_stream<S192x256w8, INT8, 1>(a, s);
     case 15: return launch_defer<INT8>(a, s);
+    case 23: return launch_defer_mixed(a, defer_mix_pick(a.M, a.N, a.K, num_cus()), INT8, s);
     default: return launch_defer192<INT8>(a, s);
     }
 }
@@ -1781,7 +1815,9 @@ static double apart_us(int64_t M, int64_t N, int64_t K, const Split &split)
     const int v = split.way == kWhole ? pick(M, N, K).v : 0;
     auto rounds = [&](int64_t tr, int64_t tc, int64_t slots) { return std::ceil((double)(((M + tr - 1) / tr) * ((N + tc - 1) / tc)) / (double)slots); };
     if (v == 15 || v == 16)
-        return split.us + 1.27 * 2.0 * (v == 15 ? 1.0 : 0.77) * rounds(v == 15 ? 256 : 192, 256, num_cus());
+        return split.us + tile_overhead_us(v, M, N);
+    if (v == 23)
+        return defer_mix_pick(M, N, K, num_cus()).us;
     return v == 13 ? split.us + 3.0 * rounds(128, 128, 2 * num_cus()) : split.us;
 }
 
@@ -1812,9 +1848,7 @@ static Pair pick_pair(int64_t M, int64_t N, int64_t K, size_t scratch)
     // 1.07 times as fast as what ran before (1.073 had it always been chosen rightly), one layer 3 % slower, 4 more than 4 %
     // faster left out
     const double others = pair.shape >= 0 ? 1.15 * us : 1.1 * (apart_us(M, K, N, dx) + apart_us(N, K, M, dw));
-    pair.defer = defer_pair_pick(M, N, K, num_cus(), (int)std::min<size_t>(fit, kDeferPairRuns));
-    if (pair.defer.runs != 0 && pair.defer.us >= others)
-        pair.defer.runs = 0;
+    pair.defer = defer_pair_pick(M, N, K, num_cus(), (int)std::min<size_t>(fit, kDeferPairRuns), others);
     return pair;
 }
 
@@ -1988,6 +2022,7 @@ static hipError_t launch_fp8_gemm_e5m2(const GemmArgs &a, hipStream_t s)
     case 11: return launch_stream<S256x256w8, false, 1, true>(a, s);
     case 13: return launch_stream<S128x128w4, false, 2, true>(a, s);
     case 14: return launch_stream<S192x256w8, false, 1, true>(a, s);
+    case 23: return launch_defer_mixed(a, defer_mix_pick(a.M, a.N, a.K, num_cus()), false, s);
     case 15: {
         const int64_t kt = a.K / 128;
         if (kt >= 16)

@@ -70,9 +70,9 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_defer_pair_kernel(GemmDev d, G
 // costs nothing more as long as there are few of them, and up to 4 when the output, of two thirds of the traffic then, is written by
 // many in a row (768 -> 3072: 8192 rows, 1.5 tiles a CU, 53 us; 50432 rows 225-240).  A unit costs 5, for the first
 // stages and its sums; the runs' sums come back at 2.9 TB/s, both ways, in a launch of 4.4 us.
-DeferPair defer_pair_pick(int64_t M, int64_t N, int64_t K, int cus, int most)
+DeferPair defer_pair_pick(int64_t M, int64_t N, int64_t K, int cus, int most, double below)
 {
-    DeferPair best{0, {}, 1e300};
+    DeferPair best{0, {}, below};
     constexpr int64_t kMax = (int64_t)1 << 22;
     if (M % 256 != 0 || N % 256 != 0 || K % 256 != 0 || N < 512 || M > kMax || N > kMax || K > kMax)
         return best;
@@ -82,18 +82,21 @@ DeferPair defer_pair_pick(int64_t M, int64_t N, int64_t K, int cus, int most)
     for (int64_t runs = 1; (runs == 1 || runs <= most) && runs * tw <= cus && kw / runs >= 4; ++runs) {
         const int64_t units = runs * tw, others = cus - units;
         const double unit = (double)((kw + runs - 1) / runs) + 5.0;
+        const double mb = runs > 1 ? (double)runs * (double)N * (double)K * 4e-6 : 0.0, adding = runs > 1 ? mb / 2.9 + 4.4 : 0.0;
+        const double average = ((double)td * tile + (double)units * unit) / (double)cus;
+        if (1.37 * std::max(average, unit) + adding >= best.us)
+            continue;
         auto many = [&](double t) { return t < 0.0 ? (int64_t)0 : (int64_t)(t / tile + 1e-6); };
         // the shortest time in stages in which all tiles of the input gradient fit: a slot with a unit ends with it, or a
         // slot without one does
         double t = 1e300;
         for (double base : {unit, 0.0}) {
-            double n = std::max(0.0, std::floor((((double)td * tile + (double)units * unit) / (double)cus - base) / tile) - 1.0);
+            double n = std::max(0.0, std::floor((average - base) / tile) - 1.0);
             while (base + n * tile < unit || units * many(base + n * tile - unit) + others * many(base + n * tile) < td)
                 n += 1.0;
             t = std::min(t, base + n * tile);
         }
-        const double mb = runs > 1 ? (double)runs * (double)N * (double)K * 4e-6 : 0.0;
-        const double us = 1.37 * t + (runs > 1 ? mb / 2.9 + 4.4 : 0.0);
+        const double us = 1.37 * t + adding;
         if (us >= best.us)
             continue;
         const int64_t o = std::min(td, others * many(t)), u = td - o;

@@ -154,9 +154,18 @@ struct DeferPair {
     double us;
 };
 constexpr int kDeferPairRuns = 16;
-DeferPair defer_pair_pick(int64_t M, int64_t N, int64_t K, int cus, int most);
+// at most `most` runs; only what is estimated below so many us
+DeferPair defer_pair_pick(int64_t M, int64_t N, int64_t K, int cus, int most, double below);
 // (the launch that adds the runs is the caller's)
 hipError_t launch_defer_pair_products(const GemmArgs &dgrad, const GemmArgs &wgrad, const DeferPair &pair, hipStream_t s);
+
+// The deferred-epilogue kernel on tile rows of 256 and, behind the first rows256 of them, of 192 (gemm_mixed.hip).
+struct DeferMix {
+    int rows256, workgroups;  // no workgroups: not this way
+    double us;
+};
+DeferMix defer_mix_pick(int64_t M, int64_t N, int64_t K, int cus);
+hipError_t launch_defer_mixed(const GemmArgs &a, const DeferMix &mix, bool int8, hipStream_t s);
 
 // Number of fp32 penalty partials the FP8 GEMM writes for these arguments.
 int fp8_gemm_partials(const GemmArgs &a);

@@ -1,7 +1,9 @@
-"""The deferred-epilogue GEMM: the residual under contractions of as few stages as it takes."""
+"""The deferred-epilogue GEMM: the residual under contractions of as few stages as it takes, two tile heights in one launch."""
 import pytest
+import torch
 
-from gpu_util import PEN
+import paper_2511_23225_amd as tw
+from gpu_util import DEV, PEN, scalar_f32, workspace
 from test_gpu_fp8_linear import test_fwd_residual_on_the_deferred_kernels as check_residual
 
 pytestmark = pytest.mark.gpu
@@ -12,3 +14,67 @@ pytestmark = pytest.mark.gpu
                                   (15, 8448, 1536, 2048, None)])
 def test_residual_under_short_contractions(case):
     check_residual(case)
+
+
+def products(kind, M, N, K):
+    """What computes the product into y (and the penalty's sum into S) on the kernel that is set."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(M + N + K)
+    u8 = lambda t: t.contiguous().view(torch.uint8)
+    rnd = lambda r, c, t: u8((torch.randn((r, c), generator=g, device=DEV) * 4).to(t))
+    one = scalar_f32(0.01)
+    a = rnd(M, K, torch.int8 if kind == "int8" else torch.float8_e5m2 if kind == "e5m2" else torch.float8_e4m3fn)
+    b = rnd(N, K, torch.int8 if kind == "int8" else torch.float8_e4m3fn)
+    res = torch.randn((M, N), generator=g, device=DEV).bfloat16() if kind == "residual" else None
+    ws = workspace(tw.TWEO_OP_FP8_LINEAR_FWD, M, N, K)
+
+    def run(tile):
+        y = torch.full((M + 1, N), float("nan"), dtype=torch.bfloat16, device=DEV)
+        S = torch.zeros(2, dtype=torch.float64, device=DEV)
+        tw.tweo_set_gemm_tile(tile)
+        try:
+            if kind == "int8":
+                tw.tweo_w8a8_linear(a.view(torch.int8), b.view(torch.int8), 0.01, y[:M])
+            elif kind == "e5m2":  # an input gradient of a layer [K, N] -> dx [M, N]
+                tw.tweo_fp8_linear_bwd_hybrid(a, None, one, b, one, None, None, M, K, N, y[:M], None, ws)
+            else:
+                tw.tweo_fp8_linear_fwd(a, one, b, one, y[:M], residual_bf16=res, pen=PEN if kind != "plain" else None,
+                                       penalty_sum=S if kind != "plain" else None, workspace=ws)
+            torch.cuda.synchronize()
+        finally:
+            tw.tweo_set_gemm_tile(0)
+        assert bool(y[M].isnan().all())  # nothing behind the last row
+        return y[:M], float(S[0].cpu())
+
+    return run
+
+
+# contractions over five, seven and fifteen stages of write-out; 192-row tiles alone (the first two), one and two rounds of either
+# height, workgroups without a tile of one of them; rows that end inside a tile, and inside the first quad of one; against the 8-wave
+# kernel, with a residual (one rounding less) the 192-row tiles: the same bits
+@pytest.mark.parametrize("shape,kinds", [((200, 512, 768), "plain penalty"), ((4104, 512, 1152), "penalty int8"),
+                                         ((4112, 6144, 768), "plain penalty int8 e5m2"), ((4097, 6144, 1152), "penalty e5m2"),
+                                         ((8193, 4864, 2048), "plain penalty residual int8 e5m2"), ((512, 256, 2048), "penalty residual"),
+                                         ((20000, 2048, 2176), "penalty residual"), ((50432, 768, 2304), "residual int8")])
+def test_two_tile_heights_in_one_launch(shape, kinds):
+    M, N, K = shape
+    for kind in kinds.split():
+        if kind == "e5m2" and M % 16 != 0:
+            continue
+        print("two tile heights M=%d N=%d K=%d %s" % (M, N, K, kind), flush=True)
+        run = products(kind, M, N, K)
+        y, S = run(23)
+        ref, Sref = run(16 if kind == "residual" else 11)
+        assert torch.equal(y.view(torch.int16), ref.view(torch.int16)), kind
+        # (fp32 sums of each wave's own tiles: some thousand terms a lane)
+        assert abs(S - Sref) <= 2e-6 * Sref, kind
+        again, S2 = run(23)
+        assert torch.equal(y.view(torch.int16), again.view(torch.int16)) and S == S2
+
+
+# as dispatched: ragged rows under a short contraction, whole rows with a badly filled last round of 256
+@pytest.mark.parametrize("shape", [(7400, 3584, 1664), (50432, 768, 3072)])
+def test_two_tile_heights_as_dispatched(shape):
+    run = products("penalty", *shape)
+    (y, S), (ref, Sref) = run(0), run(23)
+    assert torch.equal(y.view(torch.int16), ref.view(torch.int16)) and S == Sref
