@@ -1446,7 +1446,7 @@ static double ring_us(int64_t M, int64_t N, int64_t K, bool int8 = false)
 static double ksplit_us(int64_t M, int64_t N, int64_t K, int splits, bool deferred)
 {
     const double kt = (double)(K + 127) / 128, mb = (double)splits * (double)M * (double)N * 4e-6;
-    return (deferred ? 1.3 * kt / splits + 3.0 : (K % 64 != 0 ? 1.1 : 0.85) * 2.0 * kt / splits + 5.0) + mb / 5.0 + 2.5 + mb / 6.5;
+    return (deferred ? 1.3 * (K % 128 != 0 ? 1.3 : 1.0) * kt / splits + 3.0 : (K % 64 != 0 ? 1.1 : 0.85) * 2.0 * kt / splits + 5.0) + mb / 5.0 + 2.5 + mb / 6.5;
 }
 
 // The deferred-epilogue kernel covers whole 256x256 tiles, K in whole stages with enough of
@@ -1686,14 +1686,17 @@ static hipError_t launch_gemm(const GemmArgs &a, hipStream_t s)
 // 768x768 48 -> 30 us, 3072x768 51 -> 39 us; a contraction of 4096 loses (14 -> 20 us), and so do
 // 64 tiles over 8192 (40 -> 46 us).  From 80 stages on, up to half as many tiles as CUs are split
 // (INT8, 4096 wide over 11008: 64 tiles 67 -> 60 us, 80 tiles 106 -> 68 us): the INT8 flavour of the
-// same kernel leaves int32 runs, which the reduce kernel adds exactly.
+// same kernel leaves int32 runs, which the reduce kernel adds exactly.  FP8 contractions that are no multiple of 128 may go the same way,
+// their stages, across two lines a row, 1.3 times as long (pick_split).
 constexpr int kKsplitDeferMinStages = 16, kKsplitDeferMinKt = 64;
-static int defer_ksplit_runs(int64_t M, int64_t N, int64_t K)
+static int defer_ksplit_runs(int64_t M, int64_t N, int64_t K, bool int8 = false)
 {
-    if (g_tile_override != 0 || M % 256 != 0 || N % 256 != 0 || K % 128 != 0 || N > ((int64_t)1 << 22))
+    if (g_tile_override != 0 || M % 256 != 0 || N % 256 != 0 || K % (int8 ? 128 : 16) != 0 || N > ((int64_t)1 << 22) || K > ((int64_t)1 << 22))
         return 1;
-    const int64_t tiles = (M / 256) * (N / 256), kt = K / 128, cus = num_cus();
+    const int64_t tiles = (M / 256) * (N / 256), kt = (K + 127) / 128, cus = num_cus();
     if (kt < kKsplitDeferMinKt || tiles * (kt >= 80 ? 2 : 6) > cus)
+        return 1;
+    if (K % 128 != 0 && kt < 128 && tiles <= 32)  // the ring kernel is ahead, whole or beside the other product in runs of its own
         return 1;
     int64_t splits = cus / tiles;
     if (splits > kt / kKsplitDeferMinStages)
@@ -1730,28 +1733,52 @@ struct Split {
     double us;
 };
 constexpr double kKsplitBias = 0.85;
+// the runs that scratch is asked for
+static int ksplit_runs(int64_t M, int64_t N, int64_t K, int *deferred)
+{
+    *deferred = defer_ksplit_runs(M, N, K);
+    return *deferred > 1 && K % 128 == 0 ? *deferred : std::max(*deferred, tiled_ksplit_runs(M, N, K));
+}
 static Split pick_split(int64_t M, int64_t N, int64_t K, size_t scratch)
 {
-    const int dr = defer_ksplit_runs(M, N, K), runs = dr > 1 ? dr : tiled_ksplit_runs(M, N, K);
-    if (runs <= 1 || scratch < (size_t)runs * (size_t)M * (size_t)N * sizeof(float))
+    int dr;
+    const int asked = ksplit_runs(M, N, K, &dr);
+    if (asked <= 1 || scratch < (size_t)asked * (size_t)M * (size_t)N * sizeof(float))
         return Split{kWhole, 1, -1, pick(M, N, K).us};
-    Split best{dr > 1 ? kDeferRuns : kTiledRuns, runs, -1, kKsplitBias * ksplit_us(M, N, K, runs, dr > 1)};
-    const double whole = ring_us(M, N, K);
-    if (whole < best.us)
-        best = Split{kWhole, 1, -1, whole};
-    int shape = -1;
-    double us;
-    const int small = ring_ksplit_pick(M, N, K, num_cus(), runs, &shape, &us);
-    // (of two ways in runs the large tiles' time is the surer one: they fetch half as much)
-    if (small > 1 && us < (best.way == kWhole ? 1.0 : 0.92) * best.us)
-        best = Split{kRingRuns, small, shape, us};
+    const bool ragged = K % 128 != 0;
+    const int runs = ragged ? tiled_ksplit_runs(M, N, K) : asked;
+    Split best{kWhole, 1, -1, 0.0};
+    if (runs > 1) {
+        const bool deferred = !ragged && dr > 1;
+        best = Split{deferred ? kDeferRuns : kTiledRuns, runs, -1, kKsplitBias * ksplit_us(M, N, K, runs, deferred)};
+        const double whole = ring_us(M, N, K);
+        if (whole < best.us)
+            best = Split{kWhole, 1, -1, whole};
+        int shape = -1;
+        double us;
+        const int small = ring_ksplit_pick(M, N, K, num_cus(), runs, &shape, &us);
+        // (of two ways in runs the large tiles' time is the surer one: they fetch half as much)
+        if (small > 1 && us < (best.way == kWhole ? 1.0 : 0.92) * best.us)
+            best = Split{kRingRuns, small, shape, us};
+    } else {
+        best.us = pick(M, N, K).us;
+    }
+    // Ragged contractions on the deferred kernel's tiles (us, wgrads, operands cold, before / in its runs: 768x6144 over 15408 149
+    // / 98, 3072x768 over 50448 174 / 139, 2816x1536 over 15680 144 / 84; 1792x2304 over 18752, 252 units, 104 / 121).  Runs of
+    // 64-byte stages take up to 1.35 times their estimate, the longer the more; over 45 layers of 8000 to 50000 rows none is slower.
+    if (ragged && dr > 1) {
+        const double us = 1.08 * (10 * (M / 256) * (N / 256) * dr > 9 * (int64_t)num_cus() ? 1.2 : 1.0) * ksplit_us(M, N, K, dr, true);
+        const double length = (double)((K + 127) / 128) / (double)std::max(runs, 1);
+        if (us < (best.way == kTiledRuns ? 1.0 + 0.35 * std::min(1.0, std::max(0.0, (length - 10.0) / 20.0)) : 0.9) * best.us)
+            best = Split{kDeferRuns, dr, -1, us};
+    }
     return best;
 }
 
 // INT8: the deferred kernel's runs, unless the ring kernel is faster over the whole contraction
 static int i8_defer_ksplit(int64_t M, int64_t N, int64_t K)
 {
-    const int runs = defer_ksplit_runs(M, N, K);
+    const int runs = defer_ksplit_runs(M, N, K, true);
     return runs > 1 && ring_us(M, N, K, true) < kKsplitBias * ksplit_us(M, N, K, runs, true) ? 1 : runs;
 }
 
@@ -1793,7 +1820,7 @@ static double i8_dma_us(int64_t M, int64_t N, int64_t K, int runs)
 
 size_t i8_gemm_ksplit_bytes(int64_t M, int64_t N, int64_t K)
 {
-    int splits = defer_ksplit_runs(M, N, K);
+    int splits = defer_ksplit_runs(M, N, K, true);
     if (splits <= 1)
         splits = i8_dma_runs(M, N, K);
     return splits > 1 ? (size_t)splits * (size_t)M * (size_t)N * sizeof(int32_t) : 0;
@@ -1801,9 +1828,8 @@ size_t i8_gemm_ksplit_bytes(int64_t M, int64_t N, int64_t K)
 
 size_t fp8_gemm_ksplit_bytes(int64_t M, int64_t N, int64_t K)
 {
-    int splits = defer_ksplit_runs(M, N, K);
-    if (splits <= 1)
-        splits = tiled_ksplit_runs(M, N, K);
+    int deferred;
+    const int splits = ksplit_runs(M, N, K, &deferred);
     return splits > 1 ? (size_t)splits * (size_t)M * (size_t)N * sizeof(float) : 0;
 }
 
@@ -1846,7 +1872,7 @@ static Pair pick_pair(int64_t M, int64_t N, int64_t K, size_t scratch)
     // The ring kernel's time is an estimate over operands in the caches and cold, and 5 to 35 % low for layers as large as
     // these; over 162 layers of 1024 to 50432 rows, operands cold, the deferred pair below these lines was
     // 1.07 times as fast as what ran before (1.073 had it always been chosen rightly), one layer 3 % slower, 4 more than 4 %
-    // faster left out
+    // faster left out; over 63 of ragged rows 1.12 times, one layer 4 % slower, two 1-2
     const double others = pair.shape >= 0 ? 1.15 * us : 1.1 * (apart_us(M, K, N, dx) + apart_us(N, K, M, dw));
     pair.defer = defer_pair_pick(M, N, K, num_cus(), (int)std::min<size_t>(fit, kDeferPairRuns), others);
     return pair;
@@ -1919,14 +1945,16 @@ static hipError_t launch_splitk_reduce_defer(const GemmArgs &a, int splits, hipS
     return hipGetLastError();
 }
 
-template <bool A_E5M2, bool INT8 = false>
+template <bool A_E5M2, bool INT8 = false, bool RAGGED = false>
 static hipError_t launch_ksplit_defer(const GemmArgs &a, hipStream_t s, int splits)
 {
+    if (!INT8 && !RAGGED && a.K % 128 != 0)
+        return launch_ksplit_defer<A_E5M2, INT8, !INT8>(a, s, splits);
     using T = DeferTile<4>;
-    const void *kern = (const void *)gemm_nt_defer_kernel<INT8, 0, 3, 4, A_E5M2, true>;
+    constexpr auto kern = gemm_nt_defer_kernel<INT8, 0, 3, 4, A_E5M2, true, false, RAGGED>;
     static bool attr_done = false;
     if (!attr_done) {
-        hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
+        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
         if (e != hipSuccess)
             return e;
         attr_done = true;
@@ -1949,10 +1977,9 @@ static hipError_t launch_ksplit_defer(const GemmArgs &a, hipStream_t s, int spli
     hipEvent_t e0 = nullptr, e1 = nullptr;  // a profiled launch brackets both kernels
     take_profile_events(&e0, &e1);
     if (e0 != nullptr)
-        hipExtLaunchKernelGGL((gemm_nt_defer_kernel<INT8, 0, 3, 4, A_E5M2, true>), grid, block, T::LDS_BYTES, s, e0,
-                              nullptr, 0, g);
+        hipExtLaunchKernelGGL(kern, grid, block, T::LDS_BYTES, s, e0, nullptr, 0, g);
     else
-        hipLaunchKernelGGL((gemm_nt_defer_kernel<INT8, 0, 3, 4, A_E5M2, true>), grid, block, T::LDS_BYTES, s, g);
+        hipLaunchKernelGGL(kern, grid, block, T::LDS_BYTES, s, g);
     const hipError_t e = hipGetLastError();
     return e != hipSuccess ? e : launch_splitk_reduce_defer<INT8>(a, splits, s, nullptr, e1);
 }

@@ -181,7 +181,10 @@ struct DeferEnd {
 // A launch may go through several such lists, one after the other: opened: the first stages' loads have been issued (defer_open);
 // between(): called when nobody reads the stages any more, in front of the last write-out, to open the next list; pen: the
 // penalty terms of the wave's lanes.
-template <bool INT8, int PMODE, int D, int MT, bool A_E5M2, bool KSPLIT, bool RES, typename WORK, typename BETWEEN>
+// RAGGED (one unit, 256-row tiles): a contraction that is no multiple of 128.  The lanes whose chunk of the last stage lies past
+// its end load the row's last stage from its first chunk instead, so the offsets change once, two stages before; the wave then
+// clears what it has brought of A there, in front of the barrier that publishes the stage.
+template <bool INT8, int PMODE, int D, int MT, bool A_E5M2, bool KSPLIT, bool RES, bool RAGGED, typename WORK, typename BETWEEN>
 __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, bool opened, BETWEEN between, float &pen)
 {
     using T = DeferTile<MT>;
@@ -192,9 +195,11 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, 
     const int l31 = lane & 31, lh = lane >> 5;
     constexpr bool LAST_LIST = std::is_same<BETWEEN, DeferEnd>::value;
     static_assert(LAST_LIST || MT == 4, "what follows counts on 32 stores of every wave");
+    static_assert(!RAGGED || (WORK::ONE && MT == 4), "one unit, its last three stages apart");
     if (!work.has(0))
         return;
-    int kt = g.K / T::BK, k_first = 0;
+    const int kt_all = RAGGED ? (g.K + T::BK - 1) / T::BK : g.K / T::BK;
+    int kt = kt_all, k_first = 0;
     if constexpr (KSPLIT) {
         const int split = work.unit / work.tiles, base = kt / g.ksplit, rem = kt % g.ksplit;
         k_first = split * base + (split < rem ? split : rem);
@@ -221,6 +226,8 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, 
 #pragma unroll
     for (int p8 = 0; p8 < 8; ++p8)
         voffs[p8] = (uint32_t)(T::band_row(0, p8) + T::lane_row(wave * 8 + dma_row)) * (uint32_t)g.K + dma_chunk;
+    // RAGGED: 0, or the offset of a chunk that lies past the end in the last stage
+    const uint32_t past = RAGGED && k_first + kt == kt_all && (int)dma_chunk >= g.K - (kt_all - 1) * T::BK ? dma_chunk : 0u;
     // A rows of a ragged last tile are clamped to the last valid one (EDGE only)
     uint32_t voffs_a[T::EDGE ? T::NA : 1];
     struct Stream {
@@ -542,6 +549,7 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, 
     // The slot number is a compile-time constant of each slot's body (the bodies are stamped out
     // from an integer sequence): which pieces a slot carries is decided by the front end, not
     // left to constant propagation through unrolled loops.
+    // DR -3, -2 (RAGGED): the stages two and one before the last.
     auto stage = [&](auto dr_c, auto first_c, auto last_c, auto... rs_c) {
         constexpr int DR = decltype(dr_c)::value, FIRST = decltype(first_c)::value;
         constexpr int RS = (-1 + ... + (decltype(rs_c)::value + 1));
@@ -566,11 +574,25 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, 
                         // stage after next, the youngest loads), then publish
                         // (and what has been asked for of a residual)
                         asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(RS == 0 ? 8 + res_before(T::SLOTS - 4) : 8) : "memory");
+                        if constexpr (DR == -2) {
+                            if (past != 0) {
+                                uint8_t *own = smem + ((kt - 1) & 1) * T::STAGE_STRIDE + wave * 1024 + lane * 16;
+#pragma unroll
+                                for (int p8 = 0; p8 < T::NA; ++p8)
+                                    *(uint4 *)(own + p8 * 4096) = make_uint4(0, 0, 0, 0);
+                            }
+                            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                        }
                         block_barrier();
                         flip(T::STAGE_STRIDE ^ 64u);
                     }
                     if constexpr (t == T::SLAB - 4)
                         flip(64u);
+                    if constexpr (DR == -3 && t == T::NA / 2 + 1) {  // from B of the last stage on (slot SLAB)
+#pragma unroll
+                        for (int p8 = 0; p8 < 8; ++p8)
+                            voffs[p8] -= past;
+                    }
                     if constexpr (FIRST != 0 && kk == 0)
                         mfma_first(kk, i, j);
                     else
@@ -683,8 +705,13 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, 
 
     if constexpr (KSPLIT) {
         stage(no_drain{}, integral_constant<int, 1>{}, false_type{});
-        for (int s = 1; s < kt; ++s)
+        for (int s = 1; s < kt - (RAGGED ? 3 : 0); ++s)
             stage(no_drain{}, mid{}, false_type{});
+        if constexpr (RAGGED) {
+            stage(integral_constant<int, -3>{}, mid{}, false_type{});
+            stage(integral_constant<int, -2>{}, mid{}, false_type{});
+            stage(no_drain{}, mid{}, false_type{});
+        }
         // the last MFMAs are still in the pipe (the hardware does not interlock an accumulator
         // read written as asm against them): a few hundred cycles
         asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7\n\ts_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
@@ -754,8 +781,12 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, 
     {
         const int tm = first_tm, tn = first_tn;
         stage(no_drain{}, integral_constant<int, 1>{}, false_type{});
-        for (int s = 1; s < kt - 1; ++s)
+        for (int s = 1; s < kt - (RAGGED ? 3 : 1); ++s)
             stage(no_drain{}, mid{}, false_type{});
+        if constexpr (RAGGED) {
+            stage(integral_constant<int, -3>{}, mid{}, false_type{});
+            stage(integral_constant<int, -2>{}, mid{}, false_type{});
+        }
         stage(no_drain{}, mid{}, true_type{});
         store_begin(tm, tn);
     }
@@ -918,15 +949,15 @@ struct DeferUnit {
 };
 
 template <bool INT8, int PMODE, int D, int MT, bool A_E5M2 = false, bool KSPLIT = false,
-          bool RES = false>
+          bool RES = false, bool RAGGED = false>
 __global__ __launch_bounds__(256, 1) void gemm_nt_defer_kernel(GemmDev g)
 {
     const int tiles = g.tiles_m * g.tiles_n;
     float pen = 0.0f;
     if constexpr (KSPLIT)
-        defer_tiles<INT8, PMODE, D, MT, A_E5M2, KSPLIT, RES>(g, DeferUnit{xcd_slot(), tiles, tiles * g.ksplit}, false, DeferEnd{}, pen);
+        defer_tiles<INT8, PMODE, D, MT, A_E5M2, KSPLIT, RES, RAGGED>(g, DeferUnit{xcd_slot(), tiles, tiles * g.ksplit}, false, DeferEnd{}, pen);
     else
-        defer_tiles<INT8, PMODE, D, MT, A_E5M2, KSPLIT, RES>(g, DeferRounds{xcd_slot(), (int)gridDim.x, tiles}, false, DeferEnd{}, pen);
+        defer_tiles<INT8, PMODE, D, MT, A_E5M2, KSPLIT, RES, RAGGED>(g, DeferRounds{xcd_slot(), (int)gridDim.x, tiles}, false, DeferEnd{}, pen);
     defer_penalty<PMODE>(g, pen);
 }
 

@@ -14,7 +14,10 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("hybrid", [False, True])
 @pytest.mark.parametrize("shape,scratch", [((1024, 1024, 5632), None), ((8192, 3072, 768), None), ((8192, 768, 3072), None),
                                            ((13312, 512, 2304), None), ((16384, 1024, 1024), 2.0), ((16384, 1024, 1024), 0.0),
-                                           ((3328, 5632, 1280), None), ((31488, 3584, 256), 5.5)])
+                                           ((3328, 5632, 1280), None), ((31488, 3584, 256), 5.5),
+                                           # rows that end inside a stage of the weight gradient and inside a tile
+                                           ((1872, 3072, 1792), None), ((3696, 3584, 1280), None), ((8208, 768, 3072), None),
+                                           ((7200, 1536, 768), None), ((16400, 1024, 1024), 2.0), ((7088, 3072, 4608), None)])
 def test_backward_of_whole_tiles_in_one_launch(shape, scratch, hybrid):
     M, N, K = shape
     print("deferred pair M=%d N=%d K=%d scratch %s hybrid %s" % (*shape, scratch, hybrid), flush=True)
@@ -42,3 +45,36 @@ def test_backward_of_whole_tiles_in_one_launch(shape, scratch, hybrid):
         # bf16 rounding, and what one FP8 MFMA loses (check_gemm)
         assert bool((diff <= 2.0 ** -8 * ref.abs() + (2.0 ** -10 + a.shape[1] * 2.0 ** -24) * refabs).all())
         assert float(diff.norm() / ref.norm()) < 3e-3
+
+
+# the weight gradient alone, in runs over a contraction that ends 16, 48 and 112 into a stage, and at one; a NaN of either
+# operand stays in its row or column, also where a lane past the end loads its row's first chunk
+@pytest.mark.parametrize("hybrid", [False, True])
+@pytest.mark.parametrize("shape", [(16400, 512, 768), (15408, 768, 1536), (16496, 256, 512), (16512, 256, 512)])
+def test_weight_gradient_of_ragged_rows(shape, hybrid):
+    M, N, K = shape
+    print("weight gradient M=%d N=%d K=%d hybrid %s" % (*shape, hybrid), flush=True)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(M + N + K)
+    dyt = torch.float8_e5m2 if hybrid else torch.float8_e4m3fn
+    dyT = (torch.randn((N, M), generator=g, device=DEV) * 4).to(dyt)
+    xT = (torch.randn((K, M), generator=g, device=DEV) * 4).to(torch.float8_e4m3fn)
+    one = scalar_f32(1.0)
+    ws = torch.full((tw.tweo_workspace_bytes(tw.TWEO_OP_FP8_LINEAR_BWD, M, N, K),), 0xA5, dtype=torch.uint8, device=DEV)
+    bwd = tw.tweo_fp8_linear_bwd_hybrid if hybrid else tw.tweo_fp8_linear_bwd
+
+    def run():
+        dw = torch.full((N, K), float("nan"), dtype=torch.bfloat16, device=DEV)
+        bwd(None, dyT.view(torch.uint8), one, None, None, xT.view(torch.uint8), one, M, N, K, None, dw, ws)
+        torch.cuda.synchronize()
+        return dw.double()
+
+    got, a, b = run(), dyT.double(), xT.double()
+    ref, refabs = a @ b.t(), a.abs() @ b.abs().t()
+    assert bool(((got - ref).abs() <= 2.0 ** -8 * ref.abs() + (2.0 ** -10 + M * 2.0 ** -24) * refabs).all())
+    dyT.view(torch.uint8)[3, 5] = xT.view(torch.uint8)[7, 11] = 0x7F
+    xT.view(torch.uint8)[9, M - 1] = 0x7F
+    nan = run().isnan()
+    want = torch.zeros_like(nan)
+    want[3, :] = want[:, 7] = want[:, 9] = True
+    assert torch.equal(nan, want)
