@@ -6,7 +6,7 @@ import sys
 PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libtweo_hip.so")
-SOURCES = ["api.hip", "elementwise.hip", "gemm.hip", "gemm_ring.hip", "gemm_pair.hip", "gemm_mixed.hip"]
+SOURCES = ["api.hip", "elementwise.hip", "gemm.hip", "gemm_ring.hip", "gemm_pair.hip", "gemm_mixed.hip", "gemm_any.hip"]
 HEADERS = ["kernels.h", "device_utils.h", "gemm_common.h", "gemm_defer.h", "gemm_epilogue.h", "gemm_ring.h", "finish.h", os.path.join("..", "..", "include", "tweo.h")]
 # packed-fp32 code generation is switched off: the compiler must not form v_pk_*_f32
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-Xclang",

@@ -1240,11 +1240,12 @@ size_t stream_k_workspace_bytes()
 // kernel on 192x256 tiles (any M, K >= 2048).  17: the INT8 weight-streaming kernel (M <= 64).  4, 18 to 22: the
 // ring kernel on 64x64, 64x64 (two groups), 64x128, 64x128 (two groups), 128x128 and 96x128 tiles.
 // 23: the deferred-epilogue kernel on both in one launch (any M, K >= 768).
-constexpr int kNumVariants = 23;
+// 24: the same on 192x256 tiles, any N and K >= 912.
+constexpr int kNumVariants = 24;
 static const int kVariantBM[kNumVariants + 1] = {0, 256, 256, 128, 64, 256, 256, 256, 128, 256, 128, 256, 256, 128, 192, 256, 192, 64,
-                                                 64, 64, 64, 128, 96, 256};
+                                                 64, 64, 64, 128, 96, 256, 192};
 static const int kVariantBN[kNumVariants + 1] = {0, 256, 128, 128, 64, 256, 256, 128, 128, 128, 256, 256, 128, 128, 256, 256, 256, 64,
-                                                 64, 128, 128, 128, 128, 256};
+                                                 64, 128, 128, 128, 128, 256, 256};
 static int ring_variant(int shape) { return shape == 0 ? 4 : 17 + shape; }
 static int ring_shape(int variant) { return variant == 4 ? 0 : variant >= 18 && variant <= 22 ? variant - 17 : -1; }
 int gemm_num_variants() { return kNumVariants; }
@@ -1406,6 +1407,8 @@ static Pick pick(int64_t M, int64_t N, int64_t K, bool int8 = false, bool mixed 
         const int v = g_tile_override == 17 ? 4 : g_tile_override;
         if (v == 23)
             return mixed && defer_mix_pick(M, N, K, num_cus()).workgroups != 0 ? Pick{v, 0.0} : Pick{pick_tiled(M, N, K, 16), 0.0};
+        if (v == 24)
+            return mixed && defer_any_us(M, N, K, num_cus()) < 1e300 ? Pick{v, 0.0} : Pick{pick_tiled(M, N, K, 3), 0.0};
         return Pick{ring_shape(v) >= 0 ? v : pick_tiled(M, N, K, v), 0.0};
     }
     int v = pick_tiled(M, N, K, 0);
@@ -1428,6 +1431,16 @@ static Pick pick(int64_t M, int64_t N, int64_t K, bool int8 = false, bool mixed 
         if (mix.workgroups != 0 && (!same || K >= 2048) &&
             mix.us < (same ? 0.945 : int8 ? 0.91 : 1.0) * (tiled_us(v, M, N, K, int8) + tile_overhead_us(v, M, N)))
             return Pick{23, std::min(us, mix.us)};
+    }
+    // Columns or contractions that end inside a tile or a stage, on 192x256 tiles of that kernel, up to so many times the other's
+    // estimate (which is low for each of them; forward products, us: register-staged 14897x2528 -> 2528 at 1.00 1.34 times as fast,
+    // 5475x5872 -> 1168 at 1.19 1.11, 9003x3312 -> 480 at 1.24 0.99; 64-byte stages 8192x1600 -> 6400 at 1.14 1.14, 20883x928 -> 4352 at
+    // 1.01 1.32, 12345x2000 -> 5632 at 0.83 1.32, 3594x5344 -> 3680 at 1.26 0.79; 128x128 tiles of them 1287x4160 -> 4576 at 1.19
+    // 1.20; 8-wave kernel 21846x4096 -> 880 at 0.95 1.09, INT8 1.03; 128x128 streaming tiles 11929x4480 -> 352 at 0.93 0.87).
+    if (mixed && !wide && v != 13 && (N % 256 != 0 || K % 128 != 0)) {
+        const double any = defer_any_us(M, N, K, num_cus());
+        if (any < (v == 3 || v == 8 ? 1.2 : v == 6 ? 1.15 : int8 ? 0.9 : 1.05) * us)
+            return Pick{24, std::min(us, any)};
     }
     return Pick{v, us};
 }
@@ -1471,7 +1484,7 @@ static bool defer_mix_ok(const GemmArgs &a)  // (that defer_mix_pick has rows fo
 static int resolve_variant(const GemmArgs &a, bool int8 = false)
 {
     int v = pick(a.M, a.N, a.K, int8).v;
-    if (v == 23 && !defer_mix_ok(a))
+    if ((v == 23 && !defer_mix_ok(a)) || (v == 24 && (a.residual != nullptr || a.row_step != nullptr || (a.p != 0 && a.p != 4))))
         v = pick(a.M, a.N, a.K, int8, false).v;
     if (v == 15 && !defer_ok(a))
         v = 11;
@@ -1485,6 +1498,8 @@ int fp8_gemm_partials(const GemmArgs &a)
     const int v = resolve_variant(a);
     if (v == 23)
         return defer_mix_pick(a.M, a.N, a.K, num_cus()).workgroups * DeferTile<4>::PARTIALS_PER_WG;
+    if (v == 24)
+        return defer_any_workgroups(a.M, a.N, num_cus()) * DeferTile<4>::PARTIALS_PER_WG;
     if (v == 15 || v == 16)  // one partial per wave of each workgroup (never more than per 64x64 block)
         return defer_workgroups(a.M, a.N, kVariantBM[v]) * DeferTile<4>::PARTIALS_PER_WG;
     return (int)(((a.M + kVariantBM[v] - 1) / kVariantBM[v]) * ((a.N + kVariantBN[v] - 1) / kVariantBN[v]));
@@ -1669,6 +1684,7 @@ static hipError_t launch_gemm(const GemmArgs &a, hipStream_t s)
     case 14: return launch_stream<S192x256w8, INT8, 1>(a, s);
     case 15: return launch_defer<INT8>(a, s);
     case 23: return launch_defer_mixed(a, defer_mix_pick(a.M, a.N, a.K, num_cus()), INT8, s);
+    case 24: return launch_defer_any(a, num_cus(), INT8, s);
     default: return launch_defer192<INT8>(a, s);
     }
 }
@@ -2050,6 +2066,7 @@ static hipError_t launch_fp8_gemm_e5m2(const GemmArgs &a, hipStream_t s)
     case 13: return launch_stream<S128x128w4, false, 2, true>(a, s);
     case 14: return launch_stream<S192x256w8, false, 1, true>(a, s);
     case 23: return launch_defer_mixed(a, defer_mix_pick(a.M, a.N, a.K, num_cus()), false, s);
+    case 24: return launch_defer_any(a, num_cus(), false, s);
     case 15: {
         const int64_t kt = a.K / 128;
         if (kt >= 16)

@@ -181,10 +181,12 @@ struct DeferEnd {
 // A launch may go through several such lists, one after the other: opened: the first stages' loads have been issued (defer_open);
 // between(): called when nobody reads the stages any more, in front of the last write-out, to open the next list; pen: the
 // penalty terms of the wave's lanes.
-// RAGGED (one unit, 256-row tiles): a contraction that is no multiple of 128.  The lanes whose chunk of the last stage lies past
+// ANY (192-row tiles, D + 3 stages at least): columns and contractions that end inside a tile and a stage (multiples of 8 and 16).  Rows of B
+// past the last one are loaded as copies of that, as A's are, and their columns neither stored nor counted.
+// RAGGED (one unit of 256 rows) or ANY: a contraction that is no multiple of 128.  The lanes whose chunk of the last stage lies past
 // its end load the row's last stage from its first chunk instead, so the offsets change once, two stages before; the wave then
 // clears what it has brought of A there, in front of the barrier that publishes the stage.
-template <bool INT8, int PMODE, int D, int MT, bool A_E5M2, bool KSPLIT, bool RES, bool RAGGED, typename WORK, typename BETWEEN>
+template <bool INT8, int PMODE, int D, int MT, bool A_E5M2, bool KSPLIT, bool RES, bool RAGGED, bool ANY, typename WORK, typename BETWEEN>
 __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, bool opened, BETWEEN between, float &pen)
 {
     using T = DeferTile<MT>;
@@ -198,7 +200,8 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, 
     static_assert(!RAGGED || (WORK::ONE && MT == 4), "one unit, its last three stages apart");
     if (!work.has(0))
         return;
-    const int kt_all = RAGGED ? (g.K + T::BK - 1) / T::BK : g.K / T::BK;
+    static_assert(!ANY || (MT == 3 && !RES && !KSPLIT && LAST_LIST), "edges on every side");
+    const int kt_all = RAGGED || ANY ? (g.K + T::BK - 1) / T::BK : g.K / T::BK;
     int kt = kt_all, k_first = 0;
     if constexpr (KSPLIT) {
         const int split = work.unit / work.tiles, base = kt / g.ksplit, rem = kt % g.ksplit;
@@ -227,7 +230,17 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, 
     for (int p8 = 0; p8 < 8; ++p8)
         voffs[p8] = (uint32_t)(T::band_row(0, p8) + T::lane_row(wave * 8 + dma_row)) * (uint32_t)g.K + dma_chunk;
     // RAGGED: 0, or the offset of a chunk that lies past the end in the last stage
-    const uint32_t past = RAGGED && k_first + kt == kt_all && (int)dma_chunk >= g.K - (kt_all - 1) * T::BK ? dma_chunk : 0u;
+    const uint32_t past = (RAGGED || ANY) && k_first + kt == kt_all && (int)dma_chunk >= g.K - (kt_all - 1) * T::BK ? dma_chunk : 0u;
+    auto set_voffs_b = [&](int tn) {  // ANY: rows past the matrix load the last valid one
+        if constexpr (ANY) {
+            const int valid = g.N - tn * T::BN;
+#pragma unroll
+            for (int p8 = 0; p8 < 8; ++p8) {
+                const int r = T::band_row(0, p8) + T::lane_row(wave * 8 + dma_row);
+                voffs[p8] = (uint32_t)(r < valid ? r : valid - 1) * (uint32_t)g.K + dma_chunk;
+            }
+        }
+    };
     // A rows of a ragged last tile are clamped to the last valid one (EDGE only)
     uint32_t voffs_a[T::EDGE ? T::NA : 1];
     struct Stream {
@@ -304,6 +317,8 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, 
             st.s = 0;
             if (!is_b)
                 set_voffs_a(next_valid);
+            else
+                set_voffs_b(next_tn);
         }
     };
     auto dma_piece_a = [&](int p8) {
@@ -451,9 +466,12 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, 
     const int64_t rows16 = (int64_t)g.N * 32;
     auto next_band = [&](int i) { return ((wm * MT + i) & 1) ? 3 * rows16 : rows16; };  // from band i to the next one
     int rows_valid = 0;  // EDGE: rows of the tile in `packed` inside the matrix
+    int cols_valid = 0;  // ANY: columns of the wave's part of it
     auto store_begin = [&](int tm, int tn) {
         if constexpr (T::EDGE)
             rows_valid = g.M - tm * T::BM;
+        if constexpr (ANY)
+            cols_valid = g.N - tn * T::BN - wn * 128;
         sp = (const uint8_t *)g.out +
              (((int64_t)tm * T::BM + T::band_row(wm, 0)) * g.N + (int64_t)tn * T::BN + wn * 128) * 2;
     };
@@ -474,7 +492,8 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, 
         const int c = a / PER, r = a % PER, i = c >> 1, jp = c & 1;
         uint32_t *A = packed[i][2 * jp], *B = packed[i][2 * jp + 1];
         if (r < PEN_STEPS) {
-            if (!T::EDGE || T::band_row(wm, i) + lane_row < rows_valid)
+            const int col = 64 * jp + 16 * (r & 1) + 4 * (r >> 2) + 2 * ((r >> 1) & 1);
+            if ((!T::EDGE || T::band_row(wm, i) + lane_row < rows_valid) && (!ANY || col + 32 * lh < cols_valid))
                 pen_word((r & 1) ? B[r >> 1] : A[r >> 1]);
         } else {
             const int d = (r - PEN_STEPS) >> 1;
@@ -487,7 +506,8 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, 
     auto drain_store = [&](int st) {
         const int c = st / 4, u = st % 4, i = c >> 1, jp = c & 1;
         uint32_t *A = packed[i][2 * jp], *B = packed[i][2 * jp + 1];
-        if (!T::EDGE || T::band_row(wm, i) + (lane_row & ~3) + u < rows_valid) {
+        if ((!T::EDGE || T::band_row(wm, i) + (lane_row & ~3) + u < rows_valid) &&
+            (!ANY || jp * 64 + lh * 32 + (l31 & 3) * 8 < cols_valid)) {
             const uint32_t *w = (u < 2 ? A : B) + 4 * (u & 1);
             const v4i v = {(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
             const uint8_t *spu = sp + u * row_bytes;
@@ -576,7 +596,7 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, 
                         asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(RS == 0 ? 8 + res_before(T::SLOTS - 4) : 8) : "memory");
                         if constexpr (DR == -2) {
                             if (past != 0) {
-                                uint8_t *own = smem + ((kt - 1) & 1) * T::STAGE_STRIDE + wave * 1024 + lane * 16;
+                                uint8_t *own = smem + (sa.bufoff ^ T::STAGE_STRIDE) + wave * 1024 + lane * 16;  // the last stage's
 #pragma unroll
                                 for (int p8 = 0; p8 < T::NA; ++p8)
                                     *(uint4 *)(own + p8 * 4096) = make_uint4(0, 0, 0, 0);
@@ -592,6 +612,11 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, 
 #pragma unroll
                         for (int p8 = 0; p8 < 8; ++p8)
                             voffs[p8] -= past;
+                        if constexpr (T::EDGE) {  // (the next tile's, when the streams come to it, are worked out anew)
+#pragma unroll
+                            for (int p8 = 0; p8 < T::NA; ++p8)
+                                voffs_a[p8] -= past;
+                        }
                     }
                     if constexpr (FIRST != 0 && kk == 0)
                         mfma_first(kk, i, j);
@@ -671,6 +696,7 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, 
     sb.ptr = tile_b(0);
     set_voffs_a(__builtin_amdgcn_readlane(tvalid, 0));
     const int first_tm = __builtin_amdgcn_readlane(tmv, 0), first_tn = __builtin_amdgcn_readlane(tnv, 0);
+    set_voffs_b(first_tn);
     plan_next(1);
     if (!opened) {
 #pragma unroll
@@ -781,9 +807,9 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, 
     {
         const int tm = first_tm, tn = first_tn;
         stage(no_drain{}, integral_constant<int, 1>{}, false_type{});
-        for (int s = 1; s < kt - (RAGGED ? 3 : 1); ++s)
+        for (int s = 1; s < kt - (RAGGED || ANY ? 3 : 1); ++s)
             stage(no_drain{}, mid{}, false_type{});
-        if constexpr (RAGGED) {
+        if constexpr (RAGGED || ANY) {
             stage(integral_constant<int, -3>{}, mid{}, false_type{});
             stage(integral_constant<int, -2>{}, mid{}, false_type{});
         }
@@ -816,8 +842,12 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, 
             stage(integral_constant<int, 13>{}, mid{}, false_type{});
             stage(integral_constant<int, 14>{}, mid{}, false_type{});
         }
-        for (int s = D; s < kt - 1; ++s)
+        for (int s = D; s < kt - (ANY ? 3 : 1); ++s)
             stage(no_drain{}, mid{}, false_type{});
+        if constexpr (ANY) {
+            stage(integral_constant<int, -3>{}, mid{}, false_type{});
+            stage(integral_constant<int, -2>{}, mid{}, false_type{});
+        }
         stage(no_drain{}, mid{}, true_type{});
         store_begin(tm, tn);
     }
@@ -859,7 +889,7 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, 
                 const int q = ps & 3, b = ps >> 2;
                 const v4i d = *(const v4i *)(tb + (8 * q + 4 * b) * 256 + (rd ^ (uint32_t)((8 * (q & 1) + 4 * b) << 4)));
                 const uint8_t *spr = sp + (8 * b + q) * rows4;
-                if (!T::EDGE || T::band_row(wm, i) + 32 * b + 4 * q + (lane >> 4) < rows_valid) {
+                if ((!T::EDGE || T::band_row(wm, i) + 32 * b + 4 * q + (lane >> 4) < rows_valid) && (!ANY || (lane & 15) * 8 < cols_valid)) {
 #pragma unroll
                     for (int w = 0; w < 4; ++w)
                         pen_word((uint32_t)d[w]);
@@ -949,15 +979,15 @@ struct DeferUnit {
 };
 
 template <bool INT8, int PMODE, int D, int MT, bool A_E5M2 = false, bool KSPLIT = false,
-          bool RES = false, bool RAGGED = false>
+          bool RES = false, bool RAGGED = false, bool ANY = false>
 __global__ __launch_bounds__(256, 1) void gemm_nt_defer_kernel(GemmDev g)
 {
     const int tiles = g.tiles_m * g.tiles_n;
     float pen = 0.0f;
     if constexpr (KSPLIT)
-        defer_tiles<INT8, PMODE, D, MT, A_E5M2, KSPLIT, RES, RAGGED>(g, DeferUnit{xcd_slot(), tiles, tiles * g.ksplit}, false, DeferEnd{}, pen);
+        defer_tiles<INT8, PMODE, D, MT, A_E5M2, KSPLIT, RES, RAGGED, ANY>(g, DeferUnit{xcd_slot(), tiles, tiles * g.ksplit}, false, DeferEnd{}, pen);
     else
-        defer_tiles<INT8, PMODE, D, MT, A_E5M2, KSPLIT, RES, RAGGED>(g, DeferRounds{xcd_slot(), (int)gridDim.x, tiles}, false, DeferEnd{}, pen);
+        defer_tiles<INT8, PMODE, D, MT, A_E5M2, KSPLIT, RES, RAGGED, ANY>(g, DeferRounds{xcd_slot(), (int)gridDim.x, tiles}, false, DeferEnd{}, pen);
     defer_penalty<PMODE>(g, pen);
 }
 

@@ -57,13 +57,13 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_defer_pair_kernel(GemmDev d, G
     }
     float pen = 0.0f;
     const DeferUnit unit{slot, w_tiles, w_tiles * w.ksplit};
-    defer_tiles<false, 0, 3, 4, A_E5M2, !WHOLE, false, MT == 3>(w, unit, false, [&] { defer_open<MT>(d, work); }, pen);
+    defer_tiles<false, 0, 3, 4, A_E5M2, !WHOLE, false, MT == 3, false>(w, unit, false, [&] { defer_open<MT>(d, work); }, pen);
     // (a path of its own for one tile: with one loop for any number of them 60 to 80 registers go through memory behind the
     // first one's last stage, 724 bytes a lane, and the 8192-row layers lose 8 us of 50)
     if (work.mine >= 2)
-        defer_tiles<false, 0, D, MT, A_E5M2, false, false, false>(d, work, unit.has(0), DeferEnd{}, pen);
+        defer_tiles<false, 0, D, MT, A_E5M2, false, false, false, false>(d, work, unit.has(0), DeferEnd{}, pen);
     else if (work.mine == 1)
-        defer_tiles<false, 0, 5, MT, A_E5M2, false, false, false>(d, DeferUnit{work.id(0), d.tiles_m * d.tiles_n, d.tiles_m * d.tiles_n},
+        defer_tiles<false, 0, 5, MT, A_E5M2, false, false, false, false>(d, DeferUnit{work.id(0), d.tiles_m * d.tiles_n, d.tiles_m * d.tiles_n},
                                                                   unit.has(0), DeferEnd{}, pen);
 }
 

@@ -167,6 +167,11 @@ struct DeferMix {
 DeferMix defer_mix_pick(int64_t M, int64_t N, int64_t K, int cus);
 hipError_t launch_defer_mixed(const GemmArgs &a, const DeferMix &mix, bool int8, hipStream_t s);
 
+// The deferred-epilogue kernel for columns and contractions that end inside a tile and a stage (gemm_any.hip); 1e300: not this way.
+double defer_any_us(int64_t M, int64_t N, int64_t K, int cus);
+int defer_any_workgroups(int64_t M, int64_t N, int cus);
+hipError_t launch_defer_any(const GemmArgs &a, int cus, bool int8, hipStream_t s);
+
 // Number of fp32 penalty partials the FP8 GEMM writes for these arguments.
 int fp8_gemm_partials(const GemmArgs &a);
 hipError_t launch_fp8_gemm(const GemmArgs &a, hipStream_t s);

@@ -1,4 +1,5 @@
-"""The deferred-epilogue GEMM: the residual under contractions of as few stages as it takes, two tile heights in one launch."""
+"""The deferred-epilogue GEMM: the residual under contractions of as few stages as it takes, two tile heights in one
+launch, edges on every side."""
 import pytest
 import torch
 
@@ -70,6 +71,44 @@ def test_two_tile_heights_in_one_launch(shape, kinds):
         assert abs(S - Sref) <= 2e-6 * Sref, kind
         again, S2 = run(23)
         assert torch.equal(y.view(torch.int16), again.view(torch.int16)) and S == S2
+
+
+# columns, rows and contractions that end inside a tile, inside a stage, at one; eight stages and more under write-outs of five,
+# seven and fifteen; one tile, several for some workgroups; against the register-staged kernel, which takes any of them: the same bits
+@pytest.mark.parametrize("shape,kinds", [((193, 136, 912), "plain penalty int8"), ((10, 264, 1008), "penalty int8"), ((208, 512, 1040), "penalty e5m2"),
+                                         ((8193, 1608, 912), "plain penalty int8"), ((8208, 1616, 1200), "penalty e5m2 int8"),
+                                         ((8193, 1544, 2416), "penalty int8"), ((8208, 1552, 2320), "plain e5m2"),
+                                         ((50000, 264, 2304), "penalty")])
+def test_edges_on_every_side(shape, kinds):
+    M, N, K = shape
+    for kind in kinds.split():
+        print("edges on every side M=%d N=%d K=%d %s" % (M, N, K, kind), flush=True)
+        run = products(kind, M, N, K)
+        y, S = run(24)
+        ref, Sref = run(3)
+        assert torch.equal(y.view(torch.int16), ref.view(torch.int16)), kind
+        assert abs(S - Sref) <= 2e-6 * Sref, kind
+        again, S2 = run(24)
+        assert torch.equal(y.view(torch.int16), again.view(torch.int16)) and S == S2
+
+
+# a NaN of the weight stays in its column and one of the activation in its row, also where a row's first chunk is loaded again
+def test_nan_under_edges_on_every_side():
+    M, N, K = 8193, 1608, 912
+    g = torch.Generator(device=DEV)
+    g.manual_seed(5)
+    a, b = ((torch.randn(s, generator=g, device=DEV) * 4).to(torch.float8_e4m3fn).view(torch.uint8) for s in ((M, K), (N, K)))
+    a[3, 5] = a[8192, K - 1] = b[7, 11] = b[1607, K - 1] = 0x7F
+    y = torch.zeros((M, N), dtype=torch.bfloat16, device=DEV)
+    tw.tweo_set_gemm_tile(24)
+    try:
+        tw.tweo_fp8_linear_fwd(a, scalar_f32(1.0), b, scalar_f32(1.0), y)
+        torch.cuda.synchronize()
+    finally:
+        tw.tweo_set_gemm_tile(0)
+    want = torch.zeros((M, N), dtype=torch.bool, device=DEV)
+    want[3] = want[8192] = want[:, 7] = want[:, 1607] = True
+    assert torch.equal(y.isnan(), want)
 
 
 # as dispatched: ragged rows under a short contraction, whole rows with a badly filled last round of 256
