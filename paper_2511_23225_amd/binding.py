@@ -7,6 +7,7 @@ stream.  A non-zero status raises TweoError; a missing library raises at load
 time - there is no fallback path.
 """
 import ctypes
+import functools
 import os
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
@@ -118,7 +119,9 @@ def status_string(status):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    # The functions' argtypes make a pointer of it.  An object per argument, and a struct per penalty, took 0.9 of the 20.8 us
+    # that issuing a small layer's forward and backward took, 0.5 of 9.2 of quantise + W8A8 linear.
+    return None if t is None else t.data_ptr()
 
 
 _current = None  # (current device, raw stream handle of a device), once the GPU is initialised
@@ -153,17 +156,22 @@ def _check(status, where):
         raise TweoError(status, where)
 
 
+@functools.lru_cache(maxsize=64)
+def _pen_cfg(tau, eps, p):  # by value; the library only reads it
+    return ctypes.byref(PenaltyCfg(tau, eps, p))
+
+
 def _pen(pen):
     if pen is None:
         return None
     tau, eps, p = pen
-    return ctypes.byref(PenaltyCfg(float(tau), float(eps), int(p)))
+    return _pen_cfg(float(tau), float(eps), int(p))
 
 
 def _ws(workspace):
     if workspace is None:
         return None, 0
-    return _ptr(workspace), workspace.numel() * workspace.element_size()
+    return workspace.data_ptr(), workspace.nbytes
 
 
 def tweo_workspace_bytes(op, M, N, K):
