@@ -94,8 +94,9 @@ class GemmEvents:
     """HIP events that the GEMM kernels of the timed steps record at their own start and end
     (tweo_profile_gemm_launches: hipExtLaunchKernelGGL on the launch stream), so that a pair
     times one kernel launch, like a profiler's kernel trace does, without draining the stream.
-    Both gradient products of a narrow layer may share a launch: it records the first pair armed
-    for the call and leaves the second, which close() cancels and which counts 0."""
+    Both gradient products of a layer may share a launch: it records the first pair armed
+    for the call and leaves the second to the addition of the weight gradient's runs, or, where there
+    is none, to close(), which cancels it and it counts 0."""
 
     def __init__(self, torch, tw):
         self.torch, self.tw, self.pairs, self.flops, self.first = torch, tw, [], [], []
@@ -616,8 +617,8 @@ def main():
         where = {"fwd": li, "dgrad": nl + 2 * (nl - 1 - li), "wgrad": nl + 2 * (nl - 1 - li) + 1}
         ms = {name: sum(dur[j] for j in range(len(dur)) if j % per_step == at) * per_step / len(dur)
               for name, at in where.items()}
-        if ms["wgrad"] == 0.0:  # both gradient products in one launch
-            ms = {"fwd": ms["fwd"], "dgrad + wgrad": ms["dgrad"]}
+        if fl / (FP8_PEAK_TFLOPS * 1e9) > ms["wgrad"]:  # both gradient products in one launch, the second pair on the addition of runs
+            ms = {"fwd": ms["fwd"], "dgrad + wgrad": ms["dgrad"] + ms["wgrad"]}
         for name, t in ms.items():
             parts.append("%s %7.1f us %5.0f TFLOP/s" % (name, 1e3 * t, fl * (1 + ("+" in name)) / t / 1e9))
         log("  %-5s %s" % (L.name, "   ".join(parts)))

@@ -505,10 +505,13 @@ tweo_status tweo_fused_cast_timeouts(unsigned *count);
  * persistent streaming kernel with 128-byte stages (K % 128 == 0): 256x256,
  * 128x128, 192x256.  15 = the deferred-epilogue persistent kernel (256x256 tiles, M
  * and N multiples of 256, K a multiple of 128 and at least 512, with a residual at
- * least 2048, p in {0, 4}); it falls back to variant 11 otherwise.  16 = the same kernel on 192x256
+ * least 1408, p in {0, 4}); it falls back to variant 11 otherwise.  16 = the same kernel on 192x256
  * tiles (any M, N a multiple of 256, K a multiple of 128 and at least 2048); it
  * falls back to variant 14 otherwise.  17 (INT8 only, M <= 64, K % 64 == 0,
- * N % 4 == 0) = the weight-streaming kernel; elsewhere it means variant 4.  A variant whose K requirement is not met falls
+ * N % 4 == 0) = the weight-streaming kernel; elsewhere it means variant 4.  23 = the deferred-epilogue
+ * kernel on both tile heights in one launch (any M, N a multiple of 256, K of 128 and at least 768, with a
+ * residual 1408); where that has no use, 16.  24 = the same on 192x256 tiles for any N % 8 == 0 and K % 16
+ * == 0 from 912 on, without a residual; elsewhere 3.  A variant whose K requirement is not met falls
  * back to the nearest one that fits.  Results are identical up to the fp32
  * summation order.  Returns TWEO_ERR_INVALID_ARG for an unknown (or retired:
  * 2, 5, 7, 9, 10, 12) variant.
