@@ -1432,6 +1432,20 @@ static Pick pick(int64_t M, int64_t N, int64_t K, bool int8 = false, bool mixed 
             mix.us < (same ? 0.945 : int8 ? 0.91 : 1.0) * (tiled_us(v, M, N, K, int8) + tile_overhead_us(v, M, N)))
             return Pick{23, std::min(us, mix.us)};
     }
+    // In the place of more than one round of 128x128 streaming tiles as well, whose end costs 3 us a round (a last round of
+    // a sixteenth of the slots half of one: 33280x768 -> 512 at 2.03 rounds 20 us, at 2.2 24).  Their estimate, FP8's for both kinds, is
+    // right for full rounds and low for others, and grows lower with the rounds: at ratios to 0.92 every one of 120
+    // forward products gains, by 1.03-1.3 up to seven rounds and by 1.3-1.8 beyond eight (27136x768 -> 4096 133 / 75 us,
+    // 18048x768 -> 4096 86 / 52, 8192x768 -> 2304 24.3 / 21.7; INT8 1.00-1.6, with a residual 1.3-1.5), from 1.0 on they lose (8192x768 -> 3072, three full
+    // rounds, 22.6 / 25.1; 6453x768 -> 2560 16.1 / 19.5).
+    if (mixed && !wide && v == 13) {
+        const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128), slots = 2 * (int64_t)num_cus();
+        const int64_t last = tiles % slots;
+        const double rounds = std::ceil((double)tiles / (double)slots) - (last != 0 && last <= slots / 16 ? 0.5 : 0.0);
+        const DeferMix mix = tiles > slots ? defer_mix_pick(M, N, K, num_cus()) : DeferMix{0, 0, 1e300};
+        if (mix.workgroups != 0 && mix.us < 0.95 * (0.37 * 2.0 * rounds * (double)(K / 128) + 4.0 + 3.0 * rounds))
+            return Pick{23, std::min(us, mix.us)};
+    }
     // Columns or contractions that end inside a tile or a stage, on 192x256 tiles of that kernel, up to so many times the other's
     // estimate (which is low for each of them; forward products, us: register-staged 14897x2528 -> 2528 at 1.00 1.34 times as fast,
     // 5475x5872 -> 1168 at 1.19 1.11, 9003x3312 -> 480 at 1.24 0.99; 64-byte stages 8192x1600 -> 6400 at 1.14 1.14, 20883x928 -> 4352 at

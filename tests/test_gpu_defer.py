@@ -73,6 +73,21 @@ def test_two_tile_heights_in_one_launch(shape, kinds):
         assert torch.equal(y.view(torch.int16), again.view(torch.int16)) and S == S2
 
 
+# in the place of the 128x128 streaming tiles, which the shape alone decides: three to six rounds of those, rows that end inside a tile,
+# one height and two; full rounds, which stay (the last)
+@pytest.mark.parametrize("shape,kinds", [((8704, 2304, 768), "plain penalty int8 e5m2"), ((10737, 2048, 896), "penalty int8"),
+                                         ((6224, 6144, 1664), "plain penalty residual e5m2"), ((7388, 5120, 1408), "residual"),
+                                         ((8192, 3072, 768), "plain penalty")])
+def test_two_tile_heights_by_the_shape(shape, kinds):
+    M, N, K = shape
+    for kind in kinds.split():
+        print("by the shape M=%d N=%d K=%d %s" % (M, N, K, kind), flush=True)
+        run = products(kind, M, N, K)
+        (y, S), (ref, Sref) = run(0), run(23 if kind == "residual" else 11)
+        assert torch.equal(y.view(torch.int16), ref.view(torch.int16)), kind
+        assert abs(S - Sref) <= 2e-6 * Sref, kind
+
+
 # columns, rows and contractions that end inside a tile, inside a stage, at one; eight stages and more under write-outs of five,
 # seven and fifteen; one tile, several for some workgroups; against the register-staged kernel, which takes any of them: the same bits
 @pytest.mark.parametrize("shape,kinds", [((193, 136, 912), "plain penalty int8"), ((10, 264, 1008), "penalty int8"), ((208, 512, 1040), "penalty e5m2"),
