@@ -174,8 +174,9 @@ struct DeferEnd {
 // the quads' lanes exchange their pieces back, and the conversion becomes a multiply-add onto it.  Loads come back in
 // order, so what is late holds up the operand stream behind it, and a residual comes from HBM: once a tile, as here, that costs
 // about a stage (and the wait in front of the first exchange drains the stream), while units of 4 KB in eight stages,
-// through LDS, held up each of them.  Kernel, residuals from HBM, with the penalty: 16384x5632 -> 2048 187 -> 165 us (145 without
-// a residual), 50432x3072 -> 768 148 -> 136 (123).  256x256 tiles spill 13-32 vector registers, values of the last
+// through LDS, held up each of them.  Kernel, residuals from HBM, with the penalty: 16384x5632 -> 2048 187 us in such units, 165
+// in one stage of FLAT loads, for which every wait for fragments waited too, 149 now (142 without a residual); 50432x3072 -> 768 148,
+// 136 and, on two tile heights (gemm_mixed.hip), 128, 114 now (103).  256x256 tiles spill 17-25 vector registers, values of the last
 // write-out and of the tile boundary.
 // work: the tiles of the workgroup, in order (DeferRounds, DeferClasses), or its one unit (DeferUnit).
 // A launch may go through several such lists, one after the other: opened: the first stages' loads have been issued (defer_open);
@@ -534,8 +535,13 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, 
         res_valid = g.M - tm * T::BM;
     };
     auto res_load = [&](int n) {
+        // Global loads, told the compiler by the address space: behind the asm below it cannot see that the pointer is one,
+        // and a FLAT load counts in lgkmcnt too (every wait for fragments then waits for the residual) and may end out of
+        // order, which the counted waits for the operand stream do not allow.
+        typedef const __attribute__((address_space(1))) uint8_t *global_bytes;
+        typedef const __attribute__((address_space(1))) v4i *global_v4i;
         const int c = n / 4, u = n % 4, i = c >> 1, jp = c & 1;
-        const uint8_t *from = rp + jp * 128;
+        global_bytes from = (global_bytes)(rp + jp * 128);
         uint32_t off = out_quad;
         if constexpr (T::EDGE) {  // rows past the matrix load the last valid one
             const int r = T::band_row(wm, i) + (lane_row & ~3) + u;
@@ -544,7 +550,7 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, 
             from += (T::band_row(0, i) / 16) * rows16 + u * row_bytes;
         }
         asm("" : "+s"(from));  // one scalar base and one offset register for all of them
-        const v4i v = *(const v4i *)(from + off);
+        const v4i v = *(global_v4i)(from + off);
         uint32_t *w = packed[i][2 * jp + (u >> 1)] + 4 * (u & 1);
 #pragma unroll
         for (int d = 0; d < 4; ++d)
