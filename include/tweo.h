@@ -523,6 +523,22 @@ tweo_status tweo_fused_cast_timeouts(unsigned *count);
 tweo_status tweo_set_gemm_tile(int variant);
 
 /*
+ * Which kernel an FP8 call of these sizes runs on, for tests and measurements: nothing is launched, and without a GPU 256
+ * CUs are assumed.  op TWEO_OP_FP8_LINEAR_FWD: p (0: no penalty) and residual (non-zero: there is one) as in the call; a
+ * gradient by itself is the product of its sizes, dX (M, K, N), dW (N, K, M).  op TWEO_OP_FP8_LINEAR_BWD: both
+ * gradients, whose buffers do not overlap; p and residual are ignored.  workspace_bytes: of a 256-byte aligned workspace, as
+ * in the call; 0: none.  kernel: a variant of tweo_set_gemm_tile; runs > 1: the contraction in so many runs, added by a second launch, on
+ * variant 15, 6 or a ring variant's tiles; shared: both gradients in one launch, runs then those of the weight
+ * gradient and kernel that of the input gradient's tiles (15, 16: the deferred-epilogue kernel); backward without it: kernel and
+ * runs of the weight gradient.  Returns TWEO_ERR_INVALID_ARG for a null plan or sizes below 1, TWEO_ERR_UNSUPPORTED for another op.
+ */
+typedef struct tweo_gemm_plan_info {
+    int kernel, runs, shared;
+} tweo_gemm_plan_info;
+tweo_status tweo_gemm_plan(int op, int64_t M, int64_t N, int64_t K, int p, int residual, size_t workspace_bytes,
+                           tweo_gemm_plan_info *plan);
+
+/*
  * Measurement hook for benchmarks: the next `pairs` GEMM kernels (FP8 or INT8, any
  * entry point) or reduction kernels of tweo_amax that the library launches record events[2i] when the
  * kernel starts and events[2i + 1] when it ends, i.e. the kernel's own duration

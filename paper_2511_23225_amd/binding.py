@@ -20,7 +20,7 @@ TWEO_OK, TWEO_ERR_INVALID_ARG, TWEO_ERR_UNSUPPORTED, TWEO_ERR_WORKSPACE, TWEO_ER
 EXPORTS = ("tweo_workspace_bytes", "tweo_status_string", "tweo_amax", "tweo_quantize_e4m3",
            "tweo_fp8_linear_fwd", "tweo_fp8_linear_bwd", "tweo_quantize_i8", "tweo_w8a8_linear",
            "tweo_fp8_linear_fwd_bf16", "tweo_fp8_linear_bwd_bf16", "tweo_set_gemm_tile",
-           "tweo_set_stream_k", "tweo_set_fused_cast", "tweo_fused_cast_timeouts", "tweo_amax_quantize_f8",
+           "tweo_set_stream_k", "tweo_gemm_plan", "tweo_set_fused_cast", "tweo_fused_cast_timeouts", "tweo_amax_quantize_f8",
            "tweo_penalty_grad_inject", "tweo_delayed_state_bytes",
            "tweo_delayed_state_init", "tweo_quantize_e4m3_delayed", "tweo_profile_gemm_launches",
            "tweo_quantize_e5m2", "tweo_fp8_linear_bwd_hybrid", "tweo_fp8_linear_bwd_bf16_hybrid",
@@ -39,6 +39,10 @@ class TweoError(RuntimeError):
 
 class PenaltyCfg(ctypes.Structure):
     _fields_ = [("tau", ctypes.c_float), ("eps", ctypes.c_float), ("p", ctypes.c_int)]
+
+
+class GemmPlan(ctypes.Structure):
+    _fields_ = [("kernel", ctypes.c_int), ("runs", ctypes.c_int), ("shared", ctypes.c_int)]
 
 
 class Fp8Saved(ctypes.Structure):
@@ -97,6 +101,7 @@ def load():
                                                   ctypes.POINTER(Fp8Saved), i64, i64, i64, vp, vp, vp, vp, vp, sz, vp]
     L.tweo_set_gemm_tile.argtypes = [ctypes.c_int]
     L.tweo_set_stream_k.argtypes = [ctypes.c_int]
+    L.tweo_gemm_plan.argtypes = [ctypes.c_int, i64, i64, i64, ctypes.c_int, ctypes.c_int, sz, ctypes.POINTER(GemmPlan)]
     L.tweo_set_fused_cast.argtypes = [ctypes.c_int]
     L.tweo_fused_cast_timeouts.argtypes = [ctypes.POINTER(ctypes.c_uint)]
     L.tweo_profile_gemm_launches.argtypes = [ctypes.POINTER(ctypes.c_void_p), ctypes.c_int]
@@ -184,6 +189,13 @@ def tweo_set_gemm_tile(variant):
 
 def tweo_set_stream_k(on):
     _check(load().tweo_set_stream_k(1 if on else 0), "tweo_set_stream_k")
+
+
+def tweo_gemm_plan(op, M, N, K, p=0, residual=False, workspace_bytes=0):
+    """(kernel variant, runs of the contraction, both gradients in one launch) of an FP8 call of these sizes."""
+    plan = GemmPlan()
+    _check(load().tweo_gemm_plan(op, M, N, K, p, 1 if residual else 0, workspace_bytes, ctypes.byref(plan)), "tweo_gemm_plan")
+    return plan.kernel, plan.runs, bool(plan.shared)
 
 
 def tweo_amax_quantize_f8(x_bf16, amax_out, q, qT, scale_out, scale_inv_out, workspace, e5m2=False):

@@ -153,6 +153,39 @@ inline void attach_stream_k(GemmArgs &a, void *workspace, size_t workspace_bytes
 }
 }  // namespace
 
+tweo_status tweo_gemm_plan(int op, int64_t M, int64_t N, int64_t K, int p, int residual, size_t workspace_bytes,
+                           tweo_gemm_plan_info *plan)
+{
+    if (plan == nullptr || M <= 0 || N <= 0 || K <= 0)
+        return TWEO_ERR_INVALID_ARG;
+    if ((op != TWEO_OP_FP8_LINEAR_FWD && op != TWEO_OP_FP8_LINEAR_BWD) || !dims_ok(M, N, K))
+        return TWEO_ERR_UNSUPPORTED;
+    // an address for what is there; nothing reads it
+    void *const some = reinterpret_cast<void *>((uintptr_t)256);
+    GemmArgs a{}, w{};
+    a.M = M;
+    GemmPlan r;
+    if (op == TWEO_OP_FP8_LINEAR_FWD) {
+        a.N = N;
+        a.K = K;
+        a.p = p;
+        a.residual = residual != 0 ? some : nullptr;
+        attach_stream_k(a, some, workspace_bytes, penalty_bytes(M, N));
+        r = fp8_gemm_plan(a);
+    } else {
+        a.N = K;
+        a.K = N;
+        w.M = N;
+        w.N = K;
+        w.K = M;
+        attach_stream_k(a, some, workspace_bytes, 256);
+        attach_stream_k(w, some, workspace_bytes, 256);
+        r = fp8_gemm_pair_plan(a, w);
+    }
+    *plan = tweo_gemm_plan_info{r.kernel, r.runs, r.shared ? 1 : 0};
+    return TWEO_OK;
+}
+
 tweo_status tweo_amax(const void *x_bf16, int64_t n, float *amax_out, void *stream)
 {
     if (!x_bf16 || !amax_out || n <= 0 || !aligned16(x_bf16))

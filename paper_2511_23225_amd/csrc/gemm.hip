@@ -2032,6 +2032,12 @@ static hipError_t launch_defer_pair(const GemmArgs &d, const GemmArgs &w, const 
     return launch_splitk_reduce_defer<false>(w, pair.runs, s, e0, e1);
 }
 
+// how both gradient products of a layer run, if what they read and write is apart: neither in one launch where .shape < 0 and .defer.runs == 0
+static Pair choose_pair(const GemmArgs &d, const GemmArgs &w)
+{
+    return g_tile_override == 0 && g_stream_k_off ? pick_pair(d.M, d.K, d.N, split_scratch(w)) : Pair{-1, 1, {}};
+}
+
 // both gradient products of a layer (d: [M, K] over N, w: [N, K] over M, no penalty, no residual)
 hipError_t launch_fp8_gemm_pair(const GemmArgs &d, const GemmArgs &w, hipStream_t s)
 {
@@ -2039,12 +2045,11 @@ hipError_t launch_fp8_gemm_pair(const GemmArgs &d, const GemmArgs &w, hipStream_
     auto overlap = [](const void *p, int64_t np, const void *q, int64_t nq) {
         return (uintptr_t)p < (uintptr_t)q + (uint64_t)nq && (uintptr_t)q < (uintptr_t)p + (uint64_t)np;
     };
-    if (g_tile_override == 0 && g_stream_k_off && !overlap(w.out, w.M * w.N * 2, d.A, d.M * d.K) &&
-        !overlap(w.out, w.M * w.N * 2, d.B, d.N * d.K)) {
+    if (!overlap(w.out, w.M * w.N * 2, d.A, d.M * d.K) && !overlap(w.out, w.M * w.N * 2, d.B, d.N * d.K)) {
         // in one launch where that is the faster way: a launch less, and no half-empty chip (1024x1024 -> 1024 8.4 us on
         // 64-byte stages, 6.0; 2048x1024 -> 1024 12.8, 9.2; operands cold, 128x128 tiles in rounds, 5920x1536 -> 2816 89
         // apart, 73; the weight gradient in runs among them, 8240x336 -> 880 37, 21, 10928x1872 -> 352 52, 40)
-        const Pair pair = pick_pair(d.M, d.K, d.N, split_scratch(w));
+        const Pair pair = choose_pair(d, w);
         if (pair.defer.runs != 0)
             return launch_defer_pair(d, w, pair.defer, s);
         if (pair.shape >= 0 && pair.runs == 1)
@@ -2093,22 +2098,40 @@ static hipError_t launch_fp8_gemm_e5m2(const GemmArgs &a, hipStream_t s)
     }
 }
 
-hipError_t launch_fp8_gemm(const GemmArgs &a, hipStream_t s)
+static Split choose_split(const GemmArgs &a)
 {
     const size_t asked = a.p == 0 && a.residual == nullptr ? fp8_gemm_ksplit_bytes(a.M, a.N, a.K) : 0;
-    if (asked != 0 && split_scratch(a) >= asked) {
-        const Split split = pick_split(a.M, a.N, a.K, split_scratch(a));
-        if (split.way != kWhole) {
-            if (split.way == kDeferRuns)
-                return a.a_e5m2 ? launch_ksplit_defer<true>(a, s, split.runs) : launch_ksplit_defer<false>(a, s, split.runs);
-            if (split.way == kTiledRuns)
-                return a.a_e5m2 ? launch_ksplit<D256x256w8, true>(a, s, split.runs)
-                                : launch_ksplit<D256x256w8, false>(a, s, split.runs);
-            hipEvent_t e0 = nullptr, e1 = nullptr;  // a profiled launch brackets both kernels
-            take_profile_events(&e0, &e1);
-            const hipError_t e = launch_ring_ksplit(a, split.shape, split.runs, s, e0);
-            return e != hipSuccess ? e : launch_splitk_reduce<false>(a, split.runs, s, e1);
-        }
+    return asked != 0 && split_scratch(a) >= asked ? pick_split(a.M, a.N, a.K, split_scratch(a)) : Split{kWhole, 1, -1, 0.0};
+}
+
+GemmPlan fp8_gemm_plan(const GemmArgs &a)
+{
+    const Split split = choose_split(a);
+    return GemmPlan{split.way == kWhole ? resolve_variant(a) : split.way == kDeferRuns ? 15 : split.way == kTiledRuns ? 6 : ring_variant(split.shape),
+                    split.way == kWhole ? 1 : split.runs, false};
+}
+
+GemmPlan fp8_gemm_pair_plan(const GemmArgs &d, const GemmArgs &w)
+{
+    const Pair pair = choose_pair(d, w);
+    if (pair.defer.runs != 0)
+        return GemmPlan{d.M % 256 != 0 ? 16 : 15, pair.defer.runs, true};
+    return pair.shape >= 0 ? GemmPlan{pair.shape == kRing128x128x2 ? 21 : ring_variant(pair.shape), pair.runs, true} : fp8_gemm_plan(w);
+}
+
+hipError_t launch_fp8_gemm(const GemmArgs &a, hipStream_t s)
+{
+    const Split split = choose_split(a);
+    if (split.way != kWhole) {
+        if (split.way == kDeferRuns)
+            return a.a_e5m2 ? launch_ksplit_defer<true>(a, s, split.runs) : launch_ksplit_defer<false>(a, s, split.runs);
+        if (split.way == kTiledRuns)
+            return a.a_e5m2 ? launch_ksplit<D256x256w8, true>(a, s, split.runs)
+                            : launch_ksplit<D256x256w8, false>(a, s, split.runs);
+        hipEvent_t e0 = nullptr, e1 = nullptr;  // a profiled launch brackets both kernels
+        take_profile_events(&e0, &e1);
+        const hipError_t e = launch_ring_ksplit(a, split.shape, split.runs, s, e0);
+        return e != hipSuccess ? e : launch_splitk_reduce<false>(a, split.runs, s, e1);
     }
     return a.a_e5m2 ? launch_fp8_gemm_e5m2(a, s) : launch_gemm<false>(a, s);
 }

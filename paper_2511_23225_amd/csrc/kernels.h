@@ -172,6 +172,14 @@ double defer_any_us(int64_t M, int64_t N, int64_t K, int cus);
 int defer_any_workgroups(int64_t M, int64_t N, int cus);
 hipError_t launch_defer_any(const GemmArgs &a, int cus, bool int8, hipStream_t s);
 
+// What a product, or both gradient products of a layer, run on (tweo_gemm_plan).
+struct GemmPlan {
+    int kernel, runs;
+    bool shared;
+};
+GemmPlan fp8_gemm_plan(const GemmArgs &a);
+GemmPlan fp8_gemm_pair_plan(const GemmArgs &dgrad, const GemmArgs &wgrad);
+
 // Number of fp32 penalty partials the FP8 GEMM writes for these arguments.
 int fp8_gemm_partials(const GemmArgs &a);
 hipError_t launch_fp8_gemm(const GemmArgs &a, hipStream_t s);

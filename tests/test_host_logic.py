@@ -118,3 +118,26 @@ def test_scratch_for_the_weight_gradients_of_narrow_layers():
     # none up to 4096, none for outputs that fill the chip
     for M, N, K in ((4096, 336, 880), (4096, 256, 256), (8208, 4096, 4096)):
         assert tw.tweo_workspace_bytes(tw.TWEO_OP_FP8_LINEAR_BWD, M, N, K) == 512, (M, N, K)
+
+
+def test_plan_of_a_call():
+    B, F = tw.TWEO_OP_FP8_LINEAR_BWD, tw.TWEO_OP_FP8_LINEAR_FWD
+    plan = lambda op, M, N, K, **kw: tw.tweo_gemm_plan(op, M, N, K, **{"workspace_bytes": tw.tweo_workspace_bytes(op, M, N, K), **kw})
+    assert plan(F, 16384, 6144, 2048, p=4) == (15, 1, False)
+    assert plan(F, 50432, 768, 3072, p=4, residual=True) == (23, 1, False)
+    assert plan(F, 12345, 5632, 2000) == (24, 1, False)
+    assert plan(F, 12345, 5632, 2000, p=3)[0] != 24 and plan(F, 12345, 5632, 2000, residual=True)[0] != 24
+    # runs of the contraction only with the scratch for them, and without a penalty
+    assert plan(F, 768, 768, 8192)[1] > 1
+    assert plan(F, 768, 768, 8192, workspace_bytes=0)[1] == 1 and plan(F, 768, 768, 8192, p=4)[1] == 1
+    assert plan(B, 8192, 3072, 768) == (15, 3, True) and plan(B, 8208, 768, 3072) == (16, 3, True)
+    assert plan(B, 1024, 1024, 5632) == (21, 1, True)
+    try:
+        tw.tweo_set_gemm_tile(14)
+        assert plan(F, 300, 512, 1024) == (14, 1, False) and not plan(B, 8192, 3072, 768)[2]
+    finally:
+        tw.tweo_set_gemm_tile(0)
+    info = tw.binding.GemmPlan()
+    call = lambda op, M, out: tw.load().tweo_gemm_plan(op, M, 256, 256, 0, 0, 0, out)
+    assert call(F, 256, None) == tw.TWEO_ERR_INVALID_ARG and call(F, 0, ctypes.byref(info)) == tw.TWEO_ERR_INVALID_ARG
+    assert call(tw.TWEO_OP_W8A8_LINEAR, 256, ctypes.byref(info)) == tw.TWEO_ERR_UNSUPPORTED
