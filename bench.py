@@ -94,9 +94,9 @@ class GemmEvents:
     """HIP events that the GEMM kernels of the timed steps record at their own start and end
     (tweo_profile_gemm_launches: hipExtLaunchKernelGGL on the launch stream), so that a pair
     times one kernel launch, like a profiler's kernel trace does, without draining the stream.
-    Both gradient products of a layer may share a launch: it records the first pair armed
-    for the call and leaves the second to the addition of the weight gradient's runs, or, where there
-    is none, to close(), which cancels it and it counts 0."""
+    Both gradient products of a layer may share a launch (tweo_gemm_plan): it records the first pair armed
+    for the call.  The second goes to the addition of the weight gradient's runs or stands empty behind a launch of the deferred-epilogue
+    kernel, or close() cancels it (the ring kernel, whose first pair holds both): an empty or cancelled one counts 0."""
 
     def __init__(self, torch, tw):
         self.torch, self.tw, self.pairs, self.flops, self.first = torch, tw, [], [], []
@@ -123,6 +123,25 @@ class GemmEvents:
     def durations_ms(self):
         # a pair that no kernel recorded still carries its creation, before the call's first kernel
         return [s.elapsed_time(e) if a.elapsed_time(s) >= 0.0 else 0.0 for (s, e), a in zip(self.pairs, self.first)]
+
+
+def backward_plan(tw, L):
+    """(kernel, runs, both gradients in one launch) of a layer's backward in run_step."""
+    op = tw.TWEO_OP_FP8_LINEAR_BWD
+    head = tw.tweo_workspace_bytes(tw.TWEO_OP_FP8_LINEAR_BWD_BF16, L.M, L.N, L.K) - tw.tweo_workspace_bytes(op, L.M, L.N, L.K)
+    return tw.tweo_gemm_plan(op, L.M, L.N, L.K, workspace_bytes=L.ws.numel() - head)
+
+
+def step_durations_ms(tw, layers, ev):
+    """Durations of the launches of the instrumented steps: the forwards of layers 0..n-1, then two a layer of n-1..0; one launch
+    for both gradients, without runs to add, leaves the second pair empty."""
+    dur, n = ev.durations_ms(), len(layers)
+    empty = set()
+    for li, L in enumerate(layers):
+        _, runs, shared = backward_plan(tw, L)
+        if shared and runs == 1:
+            empty.add(n + 2 * (n - 1 - li) + 1)
+    return [0.0 if j % (3 * n) in empty else d for j, d in enumerate(dur)]
 
 
 def time_elementwise(tw, torch, L, peers, iters=20):
@@ -511,7 +530,7 @@ def time_workload(tw, torch, synth, cfg, dev, steps, warmup):
         run_step(tw, layers)
     e.record()
     torch.cuda.synchronize()
-    dur = ev.durations_ms()
+    dur = step_durations_ms(tw, layers, ev)
     gemm_ms = sum(dur)
     res = {"workload": synth.CONFIGS[cfg]["name"], "ms_per_step": round(ms, 4),
            "ms_per_step_stream_events": round(s.elapsed_time(e) / steps, 4),
@@ -604,7 +623,7 @@ def main():
     torch.cuda.synchronize()
     wall = time.perf_counter() - t0
     ms_per_step = wall * 1e3 / a.steps
-    dur = ev.durations_ms()
+    dur = step_durations_ms(tw, layers, ev)
     gemm_ms = sum(dur)
     # per-kernel detail on stderr: three launches per layer per timed step (fwd, dgrad, wgrad)
     per_step = 3 * len(layers)
@@ -617,7 +636,7 @@ def main():
         where = {"fwd": li, "dgrad": nl + 2 * (nl - 1 - li), "wgrad": nl + 2 * (nl - 1 - li) + 1}
         ms = {name: sum(dur[j] for j in range(len(dur)) if j % per_step == at) * per_step / len(dur)
               for name, at in where.items()}
-        if fl / (FP8_PEAK_TFLOPS * 1e9) > ms["wgrad"]:  # both gradient products in one launch, the second pair on the addition of runs
+        if backward_plan(tw, L)[2]:
             ms = {"fwd": ms["fwd"], "dgrad + wgrad": ms["dgrad"] + ms["wgrad"]}
         for name, t in ms.items():
             parts.append("%s %7.1f us %5.0f TFLOP/s" % (name, 1e3 * t, fl * (1 + ("+" in name)) / t / 1e9))

@@ -545,8 +545,9 @@ tweo_status tweo_gemm_plan(int op, int64_t M, int64_t N, int64_t K, int p, int r
  * (events recorded on the stream around a call also time the gap that recording
  * them opens in front of the kernel).  A GEMM of two kernels (a K split and the addition
  * of its runs), and both products of a narrow layer's backward where they share a launch,
- * record one pair: start of the first kernel, end of the last (of a layer of whole 256x256
- * tiles: one pair for both products, one for the addition of runs, if there are any).  `events`: host array of 2 * pairs
+ * record one pair: start of the first kernel, end of the last.  Where a backward's products share a launch of the
+ * deferred-epilogue kernel (variants 15 and 16 of tweo_gemm_plan; N and K multiples of 256, any M), they record two: that launch,
+ * and the addition of the weight gradient's runs or, without runs, nothing (both events behind the launch).  `events`: host array of 2 * pairs
  * hipEvent_t handles created by the caller with timing enabled; at most 8
  * pairs; pairs = 0 cancels.  Process-wide, not thread safe.  Returns
  * TWEO_ERR_INVALID_ARG for a null handle, TWEO_ERR_UNSUPPORTED for more than 8

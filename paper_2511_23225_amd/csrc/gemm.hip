@@ -2021,15 +2021,21 @@ static size_t split_scratch(const GemmArgs &a)
 }
 
 // the deferred kernel's two products in one launch; runs of the weight gradient are added by a second one, which takes a pair
-// of profile events of its own
+// of profile events of its own.  Layers of these sizes take two pairs a backward, as the two products apart do: without runs the second
+// stands empty behind the launch.
 static hipError_t launch_defer_pair(const GemmArgs &d, const GemmArgs &w, const DeferPair &pair, hipStream_t s)
 {
     const hipError_t e = launch_defer_pair_products(d, w, pair, s);
-    if (e != hipSuccess || pair.runs == 1)
+    if (e != hipSuccess)
         return e;
     hipEvent_t e0 = nullptr, e1 = nullptr;
-    take_profile_events(&e0, &e1);
-    return launch_splitk_reduce_defer<false>(w, pair.runs, s, e0, e1);
+    const bool armed = take_profile_events(&e0, &e1);
+    if (pair.runs > 1)
+        return launch_splitk_reduce_defer<false>(w, pair.runs, s, e0, e1);
+    if (!armed)
+        return hipSuccess;
+    const hipError_t e2 = hipEventRecord(e0, s);
+    return e2 != hipSuccess ? e2 : hipEventRecord(e1, s);
 }
 
 // how both gradient products of a layer run, if what they read and write is apart: neither in one launch where .shape < 0 and .defer.runs == 0

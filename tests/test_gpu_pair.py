@@ -55,6 +55,33 @@ def test_backward_of_whole_tiles_in_one_launch(shape, scratch, plan, hybrid):
         assert float(diff.norm() / ref.norm()) < 3e-3
 
 
+# events armed for both products of a backward call whose products share a launch of the deferred-epilogue kernel: two pairs, as the
+# products apart record, the second for the addition of runs or empty; the next GEMM finds none of them
+@pytest.mark.parametrize("shape,plan", [((13312, 3072, 2048), (15, 1, True)), ((1872, 3072, 1792), (16, 1, True)), ((8208, 768, 3072), (16, 3, True))])
+def test_profile_events_of_a_shared_launch(shape, plan):
+    M, N, K = shape
+    print("profile events M=%d N=%d K=%d" % shape, flush=True)
+    u8 = lambda *s: torch.full(s, 0x30, dtype=torch.uint8, device=DEV)
+    dyq, dyqT, wqT, xqT = u8(M, N), u8(N, M), u8(K, N), u8(K, M)
+    dx, dw = (torch.empty(s, dtype=torch.bfloat16, device=DEV) for s in ((M, K), (N, K)))
+    ws = torch.empty(tw.tweo_workspace_bytes(tw.TWEO_OP_FP8_LINEAR_BWD, M, N, K), dtype=torch.uint8, device=DEV)
+    assert tw.tweo_gemm_plan(tw.TWEO_OP_FP8_LINEAR_BWD, M, N, K, workspace_bytes=ws.numel()) == plan
+    one = scalar_f32(1.0)
+    call = lambda: tw.tweo_fp8_linear_bwd(dyq, dyqT, one, wqT, one, xqT, one, M, N, K, dx, dw, ws)
+    call()
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(8)]
+    for e in ev:
+        e.record()  # creates the handle, in front of the call
+    tw.tweo_profile_gemm_launches([e.cuda_event for e in ev[:6]])
+    call()
+    tw.tweo_profile_gemm_launches([])
+    ev[7].record()
+    torch.cuda.synchronize()
+    assert [ev[6].elapsed_time(e) > 0.0 for e in ev[:6]] == [True] * 4 + [False] * 2
+    assert 0.0 < ev[0].elapsed_time(ev[1]) < ev[6].elapsed_time(ev[7])
+    assert ev[1].elapsed_time(ev[2]) >= 0.0 and ev[2].elapsed_time(ev[3]) >= 0.0 and ev[3].elapsed_time(ev[7]) >= 0.0
+
+
 # the weight gradient alone, in runs over a contraction that ends 16, 48, 80 and 112 into a stage, and at one; a NaN of either
 # operand stays in its row or column, also where a lane past the end loads its row's first chunk
 @pytest.mark.parametrize("hybrid", [False, True])
