@@ -1403,6 +1403,7 @@ struct Pick {
 };
 static Pick pick(int64_t M, int64_t N, int64_t K, bool int8 = false, bool mixed = true)
 {
+    mixed = mixed && (g_stream_k_off || g_tile_override != 0);  // (stream-K splits the last round of the kernels that these replace)
     if (g_tile_override != 0) {
         const int v = g_tile_override == 17 ? 4 : g_tile_override;
         if (v == 23)

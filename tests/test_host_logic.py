@@ -141,3 +141,15 @@ def test_plan_of_a_call():
     call = lambda op, M, out: tw.load().tweo_gemm_plan(op, M, 256, 256, 0, 0, 0, out)
     assert call(F, 256, None) == tw.TWEO_ERR_INVALID_ARG and call(F, 0, ctypes.byref(info)) == tw.TWEO_ERR_INVALID_ARG
     assert call(tw.TWEO_OP_W8A8_LINEAR, 256, ctypes.byref(info)) == tw.TWEO_ERR_UNSUPPORTED
+
+
+def test_stream_k_keeps_the_kernels_that_it_splits():
+    F = tw.TWEO_OP_FP8_LINEAR_FWD
+    shapes = ((7400, 3584, 1664), (33007, 2048, 1024), (21846, 880, 4096))
+    kernels = lambda: [tw.tweo_gemm_plan(F, M, N, K, p=4)[0] for M, N, K in shapes]
+    assert kernels() == [23, 23, 24]
+    tw.tweo_set_stream_k(True)
+    try:
+        assert kernels() == [11, 14, 14]
+    finally:
+        tw.tweo_set_stream_k(False)
