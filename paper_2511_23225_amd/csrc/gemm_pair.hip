@@ -70,7 +70,8 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_defer_pair_kernel(GemmDev d, G
 // Time of the longest workgroup, in stages of 1.37 us, fitted to 240 timings of 69 layers of 1024 to 50432 rows, operands cold (8 %
 // rms).  A tile costs 2.3 stages beside its own, for its conversion and write-out; one of less than eight stages
 // costs nothing more as long as there are few of them, and up to 4 when the output, of two thirds of the traffic then, is written by
-// many in a row (768 -> 3072: 8192 rows, 1.5 tiles a CU, 53 us; 50432 rows 225-240).  A unit costs 5, for the first
+// many in a row (768 -> 3072: 8192 rows, 1.5 tiles a CU, 53 us; 50432 rows 225-240), 5.5 over three stages (512 -> 2560: 30208 rows
+// 120 us, estimated 97 with 4).  A unit costs 5, for the first
 // stages and its sums; the runs' sums come back at 2.9 TB/s, both ways, in a launch of 4.4 us.  Ragged rows: 192-row tiles, 0.77
 // as long, and stages of the weight gradient across two lines a row, 1.3 times as long.
 DeferPair defer_pair_pick(int64_t M, int64_t N, int64_t K, int cus, int most, double below)
@@ -82,7 +83,7 @@ DeferPair defer_pair_pick(int64_t M, int64_t N, int64_t K, int cus, int most, do
         return best;
     const int64_t td = (ragged ? (M + 191) / 192 : M / 256) * (K / 256), kd = N / 128, tw = (N / 256) * (K / 256), kw = (M + 127) / 128;
     const double many_tiles = std::min(1.0, std::max(0.0, ((double)td / (double)cus - 1.5) / 0.7));
-    const double tile = (ragged ? 0.77 : 1.0) * ((double)kd + (kd < 8 ? 1.0 + 3.0 * many_tiles : 2.3));
+    const double tile = (ragged ? 0.77 : 1.0) * ((double)kd + (kd < 8 ? 1.0 + (kd < 6 ? 4.5 : 3.0) * many_tiles : 2.3));
     for (int64_t runs = 1; (runs == 1 || runs <= most) && runs * tw <= cus && kw / runs >= 4; ++runs) {
         const int64_t units = runs * tw, others = cus - units;
         const double unit = (M % 128 != 0 ? 1.3 : 1.0) * (double)((kw + runs - 1) / runs) + 5.0;

@@ -17,8 +17,8 @@ pytestmark = pytest.mark.gpu
     ((13312, 3072, 2048), None, (15, 1)), ((16384, 1024, 3072), None, (15, 3)), ((16384, 1024, 3072), 2.0, (15, 2)),
     ((10240, 1792, 3072), None, (15, 2)), ((10240, 1792, 3072), 0.0, (15, 1)),
     # rows that end inside a stage of the weight gradient and inside a tile
-    ((1872, 3072, 1792), None, (16, 1)), ((8208, 768, 3072), None, (16, 3)), ((16400, 1280, 1280), None, (16, 5)),
-    ((12304, 1024, 3072), 2.0, (16, 2)), ((8208, 1792, 3072), 0.0, (16, 1)), ((16400, 2048, 1536), 2.0, (16, 2)),
+    ((1872, 3072, 2304), None, (16, 1)), ((8208, 768, 3072), None, (16, 3)), ((16400, 1280, 1280), None, (16, 5)),
+    ((12304, 1024, 3072), 2.0, (16, 2)), ((6160, 1792, 4096), 0.0, (16, 1)), ((16400, 2048, 1536), 2.0, (16, 2)),
     ((12304, 2048, 2048), None, (16, 2)), ((7088, 3072, 4608), None, (16, 1)),
     # the ring kernel's instead, and one after the other
     ((1024, 1024, 5632), None, (21, 1)), ((16384, 1024, 1024), 2.0, (21, 2)), ((3328, 5632, 1280), None, (21, 1)),
@@ -57,7 +57,7 @@ def test_backward_of_whole_tiles_in_one_launch(shape, scratch, plan, hybrid):
 
 # events armed for both products of a backward call whose products share a launch of the deferred-epilogue kernel: two pairs, as the
 # products apart record, the second for the addition of runs or empty; the next GEMM finds none of them
-@pytest.mark.parametrize("shape,plan", [((13312, 3072, 2048), (15, 1, True)), ((1872, 3072, 1792), (16, 1, True)), ((8208, 768, 3072), (16, 3, True))])
+@pytest.mark.parametrize("shape,plan", [((13312, 3072, 2048), (15, 1, True)), ((1872, 3072, 2304), (16, 1, True)), ((8208, 768, 3072), (16, 3, True))])
 def test_profile_events_of_a_shared_launch(shape, plan):
     M, N, K = shape
     print("profile events M=%d N=%d K=%d" % shape, flush=True)

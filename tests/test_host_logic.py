@@ -153,3 +153,17 @@ def test_stream_k_keeps_the_kernels_that_it_splits():
         assert kernels() == [11, 14, 14]
     finally:
         tw.tweo_set_stream_k(False)
+
+
+def test_backwards_that_share_a_launch_of_the_deferred_kernel():
+    plan = lambda M, N, K: tw.tweo_gemm_plan(tw.TWEO_OP_FP8_LINEAR_BWD, M, N, K,
+                                             workspace_bytes=tw.tweo_workspace_bytes(tw.TWEO_OP_FP8_LINEAR_BWD, M, N, K))
+    on_it = lambda p: p[2] and p[0] in (15, 16)
+    # measured 4-22 % slower there than as they run: many runs against the ring kernel, ragged rows, write-outs over three stages in many tiles
+    for shape in ((29152, 768, 512), (12176, 2560, 512), (37840, 1536, 256), (16768, 1536, 512), (19488, 1280, 512), (38752, 768, 512),
+                  (23888, 768, 768), (23040, 768, 768), (30208, 512, 2560)):
+        assert not on_it(plan(*shape)), shape
+    # 1.08-1.28 times as fast
+    for shape in ((28000, 768, 768), (32000, 768, 768), (24000, 1024, 768), (24000, 768, 1024), (25856, 3328, 256), (20736, 3072, 256),
+                  (50432, 3072, 768), (38016, 768, 1280), (10240, 512, 2816)):
+        assert on_it(plan(*shape)), shape
