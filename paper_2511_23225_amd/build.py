@@ -46,7 +46,7 @@ def build_library(force=True, verbose=False, extra_flags=()):
                 for f, o in zip(SOURCES, objects)]
         with ThreadPoolExecutor(max(1, min(len(jobs), int(os.environ.get("MAX_JOBS") or os.cpu_count() or 1)))) as pool:
             out = "\n".join(o for o in pool.map(run, jobs) if o.strip())
-        run([hipcc, "--offload-arch=gfx950", "-fPIC", "-shared", "-o", LIB] + objects)
+        run([hipcc, "--offload-arch=gfx950", "-fPIC", "-shared"] + list(extra_flags) + ["-o", LIB] + objects)
     if verbose and out.strip():
         print(out)
     return LIB

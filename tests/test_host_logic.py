@@ -167,3 +167,15 @@ def test_backwards_that_share_a_launch_of_the_deferred_kernel():
     for shape in ((28000, 768, 768), (32000, 768, 768), (24000, 1024, 768), (24000, 768, 1024), (25856, 3328, 256), (20736, 3072, 256),
                   (50432, 3072, 768), (38016, 768, 1280), (10240, 512, 2816)):
         assert on_it(plan(*shape)), shape
+
+
+def test_build_links_with_the_extra_flags(monkeypatch):
+    import subprocess
+    from paper_2511_23225_amd import build
+    commands = []
+    monkeypatch.setattr(subprocess, "run", lambda cmd, **kw: (commands.append(cmd), subprocess.CompletedProcess(cmd, 0, stdout=""))[1])
+    build.build_library(force=True, extra_flags=["-g"])
+    compiles, links = [c for c in commands if "-c" in c], [c for c in commands if "-c" not in c]
+    assert len(compiles) == len(build.SOURCES) and len(links) == 1
+    assert all("-g" in c for c in commands) and not any("-shared" in c for c in compiles) and "-shared" in links[0]
+    assert links[0][links[0].index("-o") + 1] == build.LIB
