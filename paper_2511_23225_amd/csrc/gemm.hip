@@ -1422,8 +1422,8 @@ static Pick pick(int64_t M, int64_t N, int64_t K, bool int8 = false, bool mixed 
     if (ring_us < us)
         return Pick{ring_variant(shape), ring_us};
     // Two tile heights in one launch.  In the place of one height of the same kernel (whole tiles, or K >= 2048) from 16 stages on, where
-    // it saves a twentieth of the rounds (forward products, us: 50432x3072 -> 768 with residual and penalty 139 / 128, 20000x2048
-    // -> 2048 69 / 67; 15120x2176 -> 2816, at 0.951, 2 % slower); in the place of the 8-wave kernel (ragged rows under shorter contractions)
+    // it saves a twentieth of the rounds (forward products, us: 50432x3072 -> 768 with residual and penalty 129 / 119, 20000x2048
+    // -> 2048 76 / 71; 15120x2176 -> 2816, at 0.951, 2 % slower); in the place of the 8-wave kernel (ragged rows under shorter contractions)
     // wherever it is not estimated slower (33007x1024 -> 2048 1.42 times as fast, 7400x1664 -> 3584 1.14, 15248x768 -> 2048
     // 1.07), INT8 where it is a tenth faster (8912x1024 -> 1280, at 0.935, 4 % slower).
     if (mixed && (v == 11 || v == 14 || v == 15 || v == 16)) {
@@ -1623,7 +1623,7 @@ static hipError_t launch_stream(const GemmArgs &a, hipStream_t s)
     return launch_stream_inst<T, INT8, WG_PER_CU, false, A_E5M2>(a, s, grid, 0);
 }
 
-template <bool INT8, int PMODE, int D, int MT, bool A_E5M2 = false, bool RES = false>
+template <bool INT8, int PMODE, int D, int MT, bool A_E5M2 = false, int RES = 0>
 static hipError_t launch_defer_inst(const GemmArgs &a, hipStream_t s)
 {
     using T = DeferTile<MT>;
@@ -1637,11 +1637,19 @@ static hipError_t launch_defer_inst(const GemmArgs &a, hipStream_t s)
         attr_done = true;
     }
     GemmDev g = gemm_dev(a, T::BM, T::BN);
-    if (!RES)
+    if (RES == 0)
         g.residual = nullptr;
     const int grid = defer_workgroups(a.M, a.N, T::BM);
     launch_gemm_kernel(kernel, dim3((unsigned)grid), dim3(T::THREADS), LDS, s, g);
     return hipGetLastError();
+}
+
+// a residual, over eight stages if they fit
+template <int PMODE, int MT>
+static hipError_t launch_defer_residual(const GemmArgs &a, hipStream_t s)
+{
+    return a.K >= kDeferResSpreadK ? launch_defer_inst<false, PMODE, 5, MT, false, kDeferResSpread>(a, s)
+                                   : launch_defer_inst<false, PMODE, 5, MT, false, 1>(a, s);
 }
 
 template <bool INT8>
@@ -1650,10 +1658,8 @@ static hipError_t launch_defer(const GemmArgs &a, hipStream_t s)
     // a tile is written out over the first 15, 7, 5 or 3 stages of the next one (never its last)
     const int64_t kt = a.K / 128;
     if constexpr (!INT8) {
-        // with a residual the write-out (5 stages), the residual's five and the last one must fit (over 7 stages: 2 us of 165
-        // slower under 5632 columns, 5 of 136 under 3072)
         if (a.residual != nullptr)
-            return a.p == 4 ? launch_defer_inst<false, 4, 5, 4, false, true>(a, s) : launch_defer_inst<false, 0, 5, 4, false, true>(a, s);
+            return a.p == 4 ? launch_defer_residual<4, 4>(a, s) : launch_defer_residual<0, 4>(a, s);
         if (a.p == 4) {
             if (kt >= 16)
                 return launch_defer_inst<false, 4, 15, 4>(a, s);
@@ -1675,8 +1681,7 @@ static hipError_t launch_defer192(const GemmArgs &a, hipStream_t s)
 {
     if constexpr (!INT8) {
         if (a.residual != nullptr)
-            return a.p == 4 ? launch_defer_inst<false, 4, 5, 3, false, true>(a, s)
-                            : launch_defer_inst<false, 0, 5, 3, false, true>(a, s);
+            return a.p == 4 ? launch_defer_residual<4, 3>(a, s) : launch_defer_residual<0, 3>(a, s);
         if (a.p == 4)
             return launch_defer_inst<false, 4, 15, 3>(a, s);
     }

@@ -56,8 +56,9 @@ struct DeferTile {
     // behind the stages, 8 KB per wave: the last tile's write-out, the residual before that
     static constexpr int WAVE_BYTES = 8192, LDS_BYTES = STAGES_BYTES + NWAVES * WAVE_BYTES;
     static_assert(32 * 256 <= WAVE_BYTES, "a band of the write-out");
-    // residual form: 16-byte loads of a lane per tile, stages from the first load to the last exchange
-    static constexpr int RES_LOADS = 8 * MT, RES_STAGES = 5;
+    // residual form: 16-byte loads of a lane per tile, stages from the first load (over so many stages) to the last exchange
+    static constexpr int RES_LOADS = 8 * MT;
+    static constexpr int res_stages(int over) { return over + 4; }
     static constexpr int SLAB = NB, SLOTS = 2 * NB;       // MFMA slots per K slab / per stage
     static constexpr int NA = BM / 32, NBP = BN / 32;     // operand pieces per wave per stage
     static constexpr int HALVES = 2 * NB;                 // half blocks to convert per tile
@@ -149,6 +150,9 @@ struct DrainPlanOf {  // evaluated once per tile shape and D, not once per slot 
     static constexpr DrainPlan<T, D, PEN> value = make_drain_plan<T, D, PEN>();
 };
 
+// stages over which a residual is loaded, and the contraction that has room for them
+constexpr int kDeferResSpread = 8, kDeferResSpreadK = 128 * (5 + DeferTile<4>::res_stages(kDeferResSpread) + 1);
+
 // no list follows
 struct DeferEnd {
     __device__ __forceinline__ void operator()() const {}
@@ -170,14 +174,14 @@ struct DeferEnd {
 // unit per workgroup, so nothing is deferred.
 // RES (FP8): y = bf16(acc * alpha + residual).  The registers of the packed output are idle between
 // the end of a tile's write-out (stage D of the next tile) and the next conversion: the residual of
-// the current tile is loaded there, whole lines as the write-out stores them, all of it in one stage; two stages later
-// the quads' lanes exchange their pieces back, and the conversion becomes a multiply-add onto it.  Loads come back in
-// order, so what is late holds up the operand stream behind it, and a residual comes from HBM: once a tile, as here, that costs
-// about a stage (and the wait in front of the first exchange drains the stream), while units of 4 KB in eight stages,
-// through LDS, held up each of them.  Kernel, residuals from HBM, with the penalty: 16384x5632 -> 2048 187 us in such units, 165
-// in one stage of FLAT loads, for which every wait for fragments waited too, 149 now (142 without a residual); 50432x3072 -> 768 148,
-// 136 and, on two tile heights (gemm_mixed.hip), 128, 114 now (103).  256x256 tiles spill 17-25 vector registers, values of the last
-// write-out and of the tile boundary.
+// the current tile is loaded there, whole lines as the write-out stores them, over RES stages; two stages later
+// the quads' lanes exchange their pieces back, and the conversion becomes a multiply-add onto it (the wait in front of the first
+// exchange drains the operand stream).  Loads come back in order, so what is late holds up the operand stream behind it, and a
+// residual comes from HBM.  RES = 8 where the contraction has the stages (18: five of write-out, eight and four, the last one), 1
+// below: the CUs run in step, and 32 MB asked for within one stage take the memory 6 us a round.  Kernel with the penalty inside a
+// training step, us, in one stage / over eight (without a residual): 16384x5632 -> 2048 148 / 143 (135), 50432x3072 -> 768 126 / 124
+// (109); by itself 12304x3072 -> 2048 85 / 79 (74); over two and four stages as in one.  256x256 tiles spill 15-35
+// vector registers, values of the last write-out and of the tile boundary.
 // work: the tiles of the workgroup, in order (DeferRounds, DeferClasses), or its one unit (DeferUnit).
 // A launch may go through several such lists, one after the other: opened: the first stages' loads have been issued (defer_open);
 // between(): called when nobody reads the stages any more, in front of the last write-out, to open the next list; pen: a
@@ -187,7 +191,7 @@ struct DeferEnd {
 // RAGGED (one unit of 256 rows) or ANY: a contraction that is no multiple of 128.  The lanes whose chunk of the last stage lies past
 // its end load the row's last stage from its first chunk instead, so the offsets change once, two stages before; the wave then
 // clears what it has brought of A there, in front of the barrier that publishes the stage.
-template <bool INT8, int PMODE, int D, int MT, bool A_E5M2, bool KSPLIT, bool RES, bool RAGGED, bool ANY, typename WORK, typename BETWEEN>
+template <bool INT8, int PMODE, int D, int MT, bool A_E5M2, bool KSPLIT, int RES, bool RAGGED, bool ANY, typename WORK, typename BETWEEN>
 __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, bool opened, BETWEEN between, double &pen)
 {
     using T = DeferTile<MT>;
@@ -201,7 +205,7 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, 
     static_assert(!RAGGED || (WORK::ONE && MT == 4), "one unit, its last three stages apart");
     if (!work.has(0))
         return;
-    static_assert(!ANY || (MT == 3 && !RES && !KSPLIT && LAST_LIST), "edges on every side");
+    static_assert(!ANY || (MT == 3 && RES == 0 && !KSPLIT && LAST_LIST), "edges on every side");
     const int kt_all = RAGGED || ANY ? (g.K + T::BK - 1) / T::BK : g.K / T::BK;
     int kt = kt_all, k_first = 0;
     if constexpr (KSPLIT) {
@@ -438,7 +442,7 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, 
         for (int d = 0; d < 4; ++d)
         {
             uint32_t &w = packed[i][j][2 * q0 + d];
-            if constexpr (RES)
+            if constexpr (RES != 0)
                 w = pack_bf16x2(__builtin_fmaf((float)t[2 * d], alpha, bf16lo_to_f32(w)),
                                 __builtin_fmaf((float)t[2 * d + 1], alpha, bf16hi_to_f32(w)));
             else
@@ -584,7 +588,7 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, 
     // micro-steps are dealt evenly over the slots of the first D stages, from slot 2 on.  FIRST: a
     // tile starts (1: the workgroup's first tile, 2: a later one, which also converts the last
     // half blocks of its predecessor).  LAST: a tile ends: its blocks are converted as they finish.
-    // RS >= 0: residual stage RS of RES_STAGES.
+    // RS >= 0: residual stage RS of res_stages(RES).
     // The slot number is a compile-time constant of each slot's body (the bodies are stamped out
     // from an integer sequence): which pieces a slot carries is decided by the front end, not
     // left to constant propagation through unrolled loops.
@@ -592,8 +596,10 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, 
     auto stage = [&](auto dr_c, auto first_c, auto last_c, auto... rs_c) {
         constexpr int DR = decltype(dr_c)::value, FIRST = decltype(first_c)::value;
         constexpr int RS = (-1 + ... + (decltype(rs_c)::value + 1));
-        // residual loads issued before slot t of its first stage: behind A's pieces, so that no wait of that stage needs them
-        constexpr auto res_before = [](int t) { return t <= T::NA / 2 ? 0 : (t - T::NA / 2) * T::RES_LOADS / (T::SLOTS - T::NA / 2); };
+        // residual loads issued before slot t of a stage that issues some: behind A's pieces, so that no wait of that stage needs them
+        constexpr int RES_PER = T::RES_LOADS / (RES != 0 ? RES : 1);
+        static_assert(RES == 0 || RES_PER * RES == T::RES_LOADS, "as many in each stage");
+        constexpr auto res_before = [](int t) { return t <= T::NA / 2 ? 0 : (t - T::NA / 2) * RES_PER / (T::SLOTS - T::NA / 2); };
         constexpr bool LAST = decltype(last_c)::value;
         auto slot_body = [&](auto t_c) {
                 {
@@ -603,7 +609,7 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, 
                         // every wave has read the B half of this stage (its slab-1 fragments were
                         // requested in the last four slots of slab 0): the half can be refilled
                         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                        if constexpr (RS == 2)
+                        if constexpr (RES != 0 && RS == RES + 1)
                             __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0), where the compiler sees it: the residual is there
                         block_barrier();
                     }
@@ -612,7 +618,7 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, 
                         // wave's share of the next stage (everything but the eight B pieces of the
                         // stage after next, the youngest loads), then publish
                         // (and what has been asked for of a residual)
-                        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(RS == 0 ? 8 + res_before(T::SLOTS - 4) : 8) : "memory");
+                        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(RS >= 0 && RS < RES ? 8 + res_before(T::SLOTS - 4) : 8) : "memory");
                         if constexpr (DR == -2) {
                             if (past != 0) {
                                 uint8_t *own = smem + (sa.bufoff ^ T::STAGE_STRIDE) + wave * 1024 + lane * 16;  // the last stage's
@@ -664,14 +670,14 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, 
                     } else if constexpr (t >= T::SLOTS - 4 && t < T::SLOTS - 4 + T::NA / 2) {
                         dma_piece_a(t - (T::SLOTS - 4));
                     }
-                    if constexpr (RS == 0) {
+                    if constexpr (RS >= 0 && RS < RES) {
 #pragma unroll
-                        for (int n = 0; n < T::RES_LOADS; ++n)
+                        for (int n = 0; n < RES_PER; ++n)
                             if (n >= res_before(t) && n < res_before(t + 1))
-                                res_load(n);
+                                res_load(RS * RES_PER + n);
                     }
-                    if constexpr (RS >= 2) {
-                        constexpr int a = (RS - 2) * T::SLOTS + t - (T::SLAB + 2);
+                    if constexpr (RES != 0 && RS > RES) {
+                        constexpr int a = (RS - (RES + 1)) * T::SLOTS + t - (T::SLAB + 2);
                         if constexpr (a >= 0 && a < 2 * T::RES_LOADS)
                             res_exchange(a);
                     }
@@ -787,11 +793,9 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, 
             }
         return;
     }
-    if constexpr (RES) {
+    if constexpr (RES != 0) {
         // one copy of the residual stages for the first tile and the later ones
-        auto residual_stages = [&](auto... rs) {
-            (stage(no_drain{}, mid{}, false_type{}, rs), ...);
-        };
+        auto residual_stages = [&](auto rs) { stage(no_drain{}, mid{}, false_type{}, rs); };
         int tm = first_tm, tn = first_tn, round = 0;
         for (;;) {
             int s;
@@ -808,10 +812,9 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, 
             }
             static_assert(D == 5, "stages stamped out above");
             res_begin(tm, tn);
-            for (; s < kt - 1 - T::RES_STAGES; ++s)
+            for (; s < kt - 1 - T::res_stages(RES); ++s)
                 stage(no_drain{}, mid{}, false_type{});
-            residual_stages(integral_constant<int, 0>{}, integral_constant<int, 1>{}, integral_constant<int, 2>{},
-                            integral_constant<int, 3>{}, integral_constant<int, 4>{});
+            for_each_constant(std::make_integer_sequence<int, T::res_stages(RES)>{}, residual_stages);
             stage(no_drain{}, mid{}, true_type{});
             store_begin(tm, tn);
             ++round;
@@ -999,7 +1002,7 @@ struct DeferUnit {
 };
 
 template <bool INT8, int PMODE, int D, int MT, bool A_E5M2 = false, bool KSPLIT = false,
-          bool RES = false, bool RAGGED = false, bool ANY = false>
+          int RES = 0, bool RAGGED = false, bool ANY = false>
 __global__ __launch_bounds__(256, 1) void gemm_nt_defer_kernel(GemmDev g)
 {
     const int tiles = g.tiles_m * g.tiles_n;

@@ -5,7 +5,7 @@
 // of 3.  The second list's first stages load while the first one's last tile is written out.  The rows behind may end inside a tile, so
 // ragged row counts take this kernel under contractions of 768 on, with 192-row tiles alone if those fit better
 // (kernels of their own exist for one height: 256 rows for whole tiles, 192 from K = 2048 on).
-// Forward products, us, one height / here: 50432x3072 -> 768 with residual and penalty 139 / 128, 20000x2048 -> 2048 69 / 67;
+// Forward products, us, one height / here: 50432x3072 -> 768 with residual and penalty 129 / 119, 20000x2048 -> 2048 76 / 71;
 // against the 8-wave kernel: 33007x1024 -> 2048 1.42 times as fast, 16348x1024 -> 5376 1.32, 7400x1664 -> 3584 1.14.
 // What bounds it: as the kernel it is made of; the change of height costs about two stages.
 #include <algorithm>
@@ -15,7 +15,7 @@
 
 namespace tweo {
 
-template <bool INT8, int PMODE, int D, bool A_E5M2, bool RES>
+template <bool INT8, int PMODE, int D, bool A_E5M2, int RES>
 __global__ __launch_bounds__(256, 1) void gemm_nt_defer_mixed_kernel(GemmDev g, int rows256)
 {
     GemmDev h = g;  // the rows behind
@@ -26,7 +26,7 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_defer_mixed_kernel(GemmDev g, 
     h.tiles_m = (h.M + 191) / 192;
     h.A += rows * g.K;
     h.out += rows * g.N;
-    if constexpr (RES)
+    if constexpr (RES != 0)
         h.residual += rows * g.N;
     const int slot = xcd_slot();
     const DeferRounds first{slot, (int)gridDim.x, g.tiles_m * g.tiles_n}, second{slot, (int)gridDim.x, h.tiles_m * h.tiles_n};
@@ -58,7 +58,7 @@ DeferMix defer_mix_pick(int64_t M, int64_t N, int64_t K, int cus)
     return best;
 }
 
-template <bool INT8, int PMODE, int D, bool A_E5M2, bool RES>
+template <bool INT8, int PMODE, int D, bool A_E5M2, int RES>
 static hipError_t launch_inst(const GemmArgs &a, const DeferMix &mix, hipStream_t s)
 {
     using T = DeferTile<4>;
@@ -80,9 +80,17 @@ static hipError_t launch_stages(const GemmArgs &a, const DeferMix &mix, hipStrea
 {
     const int64_t kt = a.K / 128;
     if (kt >= 16)
-        return launch_inst<INT8, PMODE, 15, A_E5M2, false>(a, mix, s);
-    return kt >= 8 ? launch_inst<INT8, PMODE, 7, A_E5M2, false>(a, mix, s)
-                   : launch_inst<INT8, PMODE, 5, A_E5M2, false>(a, mix, s);
+        return launch_inst<INT8, PMODE, 15, A_E5M2, 0>(a, mix, s);
+    return kt >= 8 ? launch_inst<INT8, PMODE, 7, A_E5M2, 0>(a, mix, s)
+                   : launch_inst<INT8, PMODE, 5, A_E5M2, 0>(a, mix, s);
+}
+
+// a residual, over eight stages if they fit
+template <int PMODE>
+static hipError_t launch_residual(const GemmArgs &a, const DeferMix &mix, hipStream_t s)
+{
+    return a.K >= kDeferResSpreadK ? launch_inst<false, PMODE, 5, false, kDeferResSpread>(a, mix, s)
+                                   : launch_inst<false, PMODE, 5, false, 1>(a, mix, s);
 }
 
 hipError_t launch_defer_mixed(const GemmArgs &a, const DeferMix &mix, bool int8, hipStream_t s)
@@ -90,7 +98,7 @@ hipError_t launch_defer_mixed(const GemmArgs &a, const DeferMix &mix, bool int8,
     if (int8)
         return launch_stages<true, 0, false>(a, mix, s);
     if (a.residual != nullptr)
-        return a.p == 4 ? launch_inst<false, 4, 5, false, true>(a, mix, s) : launch_inst<false, 0, 5, false, true>(a, mix, s);
+        return a.p == 4 ? launch_residual<4>(a, mix, s) : launch_residual<0>(a, mix, s);
     if (a.a_e5m2)
         return launch_stages<false, 0, true>(a, mix, s);
     return a.p == 4 ? launch_stages<false, 4, false>(a, mix, s) : launch_stages<false, 0, false>(a, mix, s);

@@ -14,7 +14,9 @@ pytestmark = pytest.mark.gpu
 # alone and behind 256-row ones, 11 and 15 stages
 @pytest.mark.parametrize("case", [(15, 256, 1408, 256, PEN), (15, 512, 1408, 512, None), (15, 8448, 1408, 2048, PEN),
                                   (15, 8448, 1536, 2048, None), (23, 200, 1408, 512, PEN), (23, 4112, 1408, 6144, PEN),
-                                  (23, 4112, 1920, 6144, None)])
+                                  (23, 4112, 1920, 6144, None),
+                                  # 18 stages and more: the residual over eight of them
+                                  (15, 8448, 2304, 2048, None), (16, 4160, 2304, 3072, PEN), (16, 200, 2432, 512, None), (23, 4112, 2304, 6144, PEN)])
 def test_residual_under_short_contractions(case):
     check_residual(case)
 
