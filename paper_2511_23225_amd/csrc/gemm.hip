@@ -1906,9 +1906,7 @@ static Pair pick_pair(int64_t M, int64_t N, int64_t K, size_t scratch)
     if (shape >= 0 && sure * us < dx.us + dw.us)
         pair.shape = shape;
     // The ring kernel's time is an estimate over operands in the caches and cold, and 5 to 35 % low for layers as large as
-    // these; over 162 layers of 1024 to 50432 rows, operands cold, the deferred pair below these lines was
-    // 1.07 times as fast as what ran before (1.073 had it always been chosen rightly), one layer 3 % slower, 4 more than 4 %
-    // faster left out; over 63 of ragged rows 1.12 times, one layer 4 % slower, two 1-2.  Against the ring kernel's pair many runs count for
+    // these, hence the factors.  Against the ring kernel's pair many runs count for
     // more than estimated (measured over estimated, 126 layers: to seven runs 1.03, eight to eleven 1.12, to fifteen 1.21, sixteen 1.27), and
     // of ragged rows its own time is less of an underestimate (1.11-1.18, of whole tiles 1.18-1.29): without the two 53 of 545 layers were
     // 2-22 % slower than before (29152x512 -> 768 50 / 60 us), with them 11, 2-10, and all 1.144 times as fast, 1.137 without.

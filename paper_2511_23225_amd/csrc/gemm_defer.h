@@ -1,9 +1,14 @@
 // Deferred-epilogue persistent 8-bit "NT" GEMM for gfx950 (FP8 E4M3 / INT8):
 // the large-shape kernel of the per-tensor FP8 linear (Sec. 4.3) and of the
-// W8A8 linear (Sec. 4.4) when M and N are multiples of 256 and K of 128.
+// W8A8 linear (Sec. 4.4).  Forms:
+//   256x256 tiles: M and N multiples of 256, K of 128, from 512 on (with a residual from 1408 on);
+//   192x256 tiles (EDGE): any M; with ANY also any N % 8 == 0 and K % 16 == 0, from 912 on and without a residual;
+//   both heights one after the other in a launch (gemm_mixed.hip);
+//   one unit of a K split (KSPLIT): 256x256 tiles, K in runs, with RAGGED any K % 16 == 0;
+//   both gradients of a layer, such a unit or a whole tile of the one and then tiles of the other, in a launch (gemm_pair.hip).
 //
 // One workgroup of four waves per CU (one wave per SIMD, so a wave may hold
-// 512 registers): a 256x256 output tile, each wave a 128x128 sub-tile = 4x4
+// 512 registers): a 256x256 output tile (192x256: three quarters of what follows), each wave a 128x128 sub-tile = 4x4
 // MFMA blocks of 32x32 = 256 accumulator registers.  Operands stream through
 // two 64 KB LDS stages of 128 bytes of K (direct-to-LDS loads, whole 128-byte
 // lines per row), as one uninterrupted stream over all the tiles a workgroup

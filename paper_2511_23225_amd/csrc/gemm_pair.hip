@@ -6,10 +6,10 @@
 // the weight gradient, or none, and then as many tiles of the input gradient as make all workgroups end at about the same
 // time.  176 whole tiles of 128 stages stand beside 1408 of 16; 36 tiles over 394 stages go in four to six runs in the
 // place of seven.  The other order, and the orders in turn on every other XCD, measured the same.
-// Backward of a layer N x K, us, operands cold, before / here, the addition of runs included: 50432 rows, 3072x768 219 /
-// 196, 2304x768 173 / 154; 16384 rows, 2048x5632 293 / 265, 2048x2048 124 / 114; 8192 rows, 3072x768 62 / 49,
-// 768x3072 65 / 53, 4096x1024 89 / 63.  Ragged rows (192-row tiles of the input gradient, the weight gradient's last stage
-// cleared past the end): 12304 rows of 5632x2048 320 / 247, 8736 of 3072x4096 241 / 185, 3696 of 3584x1280 59 / 48.
+// Backward of a layer N x K, us, operands cold, before / here, the addition of runs included: 50432 rows, 3072x768 227 /
+// 213, 2304x768 173 / 159; 16384 rows, 2048x5632 300 / 274, 2048x2048 125 / 116; 8192 rows, 3072x768 63 / 51,
+// 768x3072 65 / 52.  Ragged rows (192-row tiles of the input gradient, the weight gradient's last stage
+// cleared past the end): 12304 rows of 5632x2048 319 / 246, 8736 of 3072x4096 241 / 189, 16400 of 1280x1280 83 / 75.
 // What bounds it: the clock of the matrix pipes at that load (2.4-2.8 PFLOP/s), and under contractions of less than eight
 // stages the write-out of the tiles.
 #include <algorithm>
