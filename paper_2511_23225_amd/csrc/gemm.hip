@@ -1644,12 +1644,19 @@ static hipError_t launch_defer_inst(const GemmArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
-// a residual, over eight stages if they fit
-template <int PMODE, int MT>
+// a residual, over eight stages if they fit; 192-row tiles, whose contraction has 16 at least, load theirs over six (93 products: under 16
+// and 17 stages 0.969 of the time that one stage takes, beyond 1.002 of that of eight)
+template <int PMODE>
 static hipError_t launch_defer_residual(const GemmArgs &a, hipStream_t s)
 {
-    return a.K >= kDeferResSpreadK ? launch_defer_inst<false, PMODE, 5, MT, false, kDeferResSpread>(a, s)
-                                   : launch_defer_inst<false, PMODE, 5, MT, false, 1>(a, s);
+    return a.K >= kDeferResSpreadK ? launch_defer_inst<false, PMODE, 5, 4, false, kDeferResSpread>(a, s)
+                                   : launch_defer_inst<false, PMODE, 5, 4, false, 1>(a, s);
+}
+template <int PMODE>
+static hipError_t launch_defer192_residual(const GemmArgs &a, hipStream_t s)
+{
+    static_assert(5 + DeferTile<3>::res_stages(6) + 1 == 16, "K >= 2048");
+    return launch_defer_inst<false, PMODE, 5, 3, false, 6>(a, s);
 }
 
 template <bool INT8>
@@ -1659,7 +1666,7 @@ static hipError_t launch_defer(const GemmArgs &a, hipStream_t s)
     const int64_t kt = a.K / 128;
     if constexpr (!INT8) {
         if (a.residual != nullptr)
-            return a.p == 4 ? launch_defer_residual<4, 4>(a, s) : launch_defer_residual<0, 4>(a, s);
+            return a.p == 4 ? launch_defer_residual<4>(a, s) : launch_defer_residual<0>(a, s);
         if (a.p == 4) {
             if (kt >= 16)
                 return launch_defer_inst<false, 4, 15, 4>(a, s);
@@ -1681,7 +1688,7 @@ static hipError_t launch_defer192(const GemmArgs &a, hipStream_t s)
 {
     if constexpr (!INT8) {
         if (a.residual != nullptr)
-            return a.p == 4 ? launch_defer_residual<4, 3>(a, s) : launch_defer_residual<0, 3>(a, s);
+            return a.p == 4 ? launch_defer192_residual<4>(a, s) : launch_defer192_residual<0>(a, s);
         if (a.p == 4)
             return launch_defer_inst<false, 4, 15, 3>(a, s);
     }

@@ -193,7 +193,7 @@ def test_fwd_stream_k_split_of_the_last_round(with_residual):
 
 
 # the deferred-epilogue kernels with a residual: stages 16 and 17 (the residual in one stage), 18 and
-# more (over eight), 192-row tiles with a ragged last row; 264 tiles give some workgroups a second tile
+# more (over eight), over six on 192-row tiles with a ragged last row; 264 tiles give some workgroups a second tile
 RESIDUAL_CASES = [
     (15, 256, 2048, 512, PEN), (15, 512, 2304, 256, PEN), (15, 8448, 2176, 2048, PEN), (15, 8448, 2432, 2048, None),
     (15, 512, 2048, 256, None), (16, 200, 2048, 512, PEN), (16, 4160, 2176, 3072, PEN), (16, 4160, 2048, 3072, None),
