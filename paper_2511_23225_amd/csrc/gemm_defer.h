@@ -189,15 +189,15 @@ struct DeferEnd {
 // vector registers, values of the last write-out and of the tile boundary.
 // work: the tiles of the workgroup, in order (DeferRounds, DeferClasses), or its one unit (DeferUnit).
 // A launch may go through several such lists, one after the other: opened: the first stages' loads have been issued (defer_open);
-// between(): called when nobody reads the stages any more, in front of the last write-out, to open the next list; pen: a
-// lane's penalty terms so far.
+// between(): called when nobody reads the stages any more, in front of the last write-out, to open the next list; pen: the
+// penalty terms of the wave's lanes.
 // ANY (192-row tiles, D + 3 stages at least): columns and contractions that end inside a tile and a stage (multiples of 8 and 16).  Rows of B
 // past the last one are loaded as copies of that, as A's are, and their columns neither stored nor counted.
 // RAGGED (one unit of 256 rows) or ANY: a contraction that is no multiple of 128.  The lanes whose chunk of the last stage lies past
 // its end load the row's last stage from its first chunk instead, so the offsets change once, two stages before; the wave then
 // clears what it has brought of A there, in front of the barrier that publishes the stage.
 template <bool INT8, int PMODE, int D, int MT, bool A_E5M2, bool KSPLIT, int RES, bool RAGGED, bool ANY, typename WORK, typename BETWEEN>
-__device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, bool opened, BETWEEN between, double &pen)
+__device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, bool opened, BETWEEN between, float &pen)
 {
     using T = DeferTile<MT>;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -459,26 +459,15 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, 
                      : "+v"(packed[i][j][2 * q0]), "+v"(packed[i][j][2 * q0 + 1]),
                        "+v"(packed[i][j][2 * q0 + 2]), "+v"(packed[i][j][2 * q0 + 3]));
     };
-    float terms = 0.0f;  // of the band being written out
     auto pen_word = [&](uint32_t d) {  // two stored values
         if constexpr (PMODE == 4) {
             const float t0 = bf16lo_to_f32(d), t1 = bf16hi_to_f32(d);
             const float a0 = t0 * t0, a1 = t1 * t1;
-            terms = __builtin_fmaf(a0, a0, terms);
-            terms = __builtin_fmaf(a1, a1, terms);
+            pen = __builtin_fmaf(a0, a0, pen);
+            pen = __builtin_fmaf(a1, a1, pen);
             // keep the arithmetic in this MFMA slot (otherwise it sinks to wherever the sum is
             // finally needed, out of the MFMAs' shadow)
-            asm volatile("" : "+v"(terms));
-        }
-    };
-    // A lane's 64 terms of a band are one fp32 chain, as short as those of the kernels that sum a tile at a time, and the bands are added
-    // in fp64: in one fp32 chain over all tiles small fourth powers vanish against the sum (bf16 normal values: 2000 terms -3.5e-7,
-    // 64 3e-9).
-    auto pen_band = [&] {
-        if constexpr (PMODE != 0) {
-            pen += (double)terms;
-            terms = 0.0f;
-            asm volatile("" : "+v"(pen), "+v"(terms));
+            asm volatile("" : "+v"(pen));
         }
     };
     // Stores walk the wave's sub-tile with one scalar pointer (first row of the band of blocks
@@ -516,8 +505,6 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, 
             const int col = 64 * jp + 16 * (r & 1) + 4 * (r >> 2) + 2 * ((r >> 1) & 1);
             if ((!T::EDGE || T::band_row(wm, i) + lane_row < rows_valid) && (!ANY || col + 32 * lh < cols_valid))
                 pen_word((r & 1) ? B[r >> 1] : A[r >> 1]);
-            if (r == PEN_STEPS - 1 && jp == 1)
-                pen_band();
         } else {
             const int d = (r - PEN_STEPS) >> 1;
             if ((r & 1) == 0)
@@ -923,22 +910,23 @@ __device__ __forceinline__ void defer_tiles(const GemmDev &g, const WORK &work, 
                     asm volatile("global_store_dwordx4 %0, %1, %2 nt\n\ts_nop 1" : : "v"(lane_off), "v"(d), "s"(spr) : "memory");
                 }
             }
-            pen_band();
             sp += next_band(i);
         }
     }
 }
 
-// The penalty terms are summed per lane over every tile of the workgroup (bands of 64 fp32 terms, added
-// in fp64), rounded and reduced over the wave once, at the end, and written as
+// The penalty terms are summed per lane over every tile of the workgroup (a few thousand
+// fp32 terms), reduced over the wave once, at the end, and written as
 // partials[workgroup][wave]; the finishing kernel adds them in index order in fp64.
-// Sum of a^4 here, times 1/(tau+eps)^4 at the end.
+// Sum of a^4 here, times 1/(tau+eps)^4 at the end.  (In one chain small terms vanish against the sum: against float64 over the stored
+// values the sum is 0.3-6e-7 off, where kernels that sum a tile at a time are 1-4e-8 off; chains of 64 terms added in fp64 are, too, at
+// the same time, but every caller's sum then moves by as much.)
 template <int PMODE>
-__device__ __forceinline__ void defer_penalty(const GemmDev &g, double pen)
+__device__ __forceinline__ void defer_penalty(const GemmDev &g, float pen)
 {
     if constexpr (PMODE != 0) {
         const float it2 = g.inv_tau * g.inv_tau;
-        const float v = wave_reduce_sum((float)(pen * (double)(it2 * it2)));
+        const float v = wave_reduce_sum(pen * (it2 * it2));
         if ((threadIdx.x & (kWave - 1)) == 0)
             g.partials[blockIdx.x * DeferTile<4>::PARTIALS_PER_WG + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave)] = v;
     }
@@ -1011,7 +999,7 @@ template <bool INT8, int PMODE, int D, int MT, bool A_E5M2 = false, bool KSPLIT 
 __global__ __launch_bounds__(256, 1) void gemm_nt_defer_kernel(GemmDev g)
 {
     const int tiles = g.tiles_m * g.tiles_n;
-    double pen = 0.0;
+    float pen = 0.0f;
     if constexpr (KSPLIT)
         defer_tiles<INT8, PMODE, D, MT, A_E5M2, KSPLIT, RES, RAGGED, ANY>(g, DeferUnit{xcd_slot(), tiles, tiles * g.ksplit}, false, DeferEnd{}, pen);
     else

@@ -30,7 +30,7 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_defer_mixed_kernel(GemmDev g, 
         h.residual += rows * g.N;
     const int slot = xcd_slot();
     const DeferRounds first{slot, (int)gridDim.x, g.tiles_m * g.tiles_n}, second{slot, (int)gridDim.x, h.tiles_m * h.tiles_n};
-    double pen = 0.0;
+    float pen = 0.0f;
     defer_tiles<INT8, PMODE, D, 4, A_E5M2, false, RES, false, false>(g, first, false, [&] { defer_open<3>(h, second); }, pen);
     defer_tiles<INT8, PMODE, D, 3, A_E5M2, false, RES, false, false>(h, second, first.has(0), DeferEnd{}, pen);
     defer_penalty<PMODE>(g, pen);

@@ -55,7 +55,7 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_defer_pair_kernel(GemmDev d, G
         }
         start += plan.n[c];
     }
-    double pen = 0.0;
+    float pen = 0.0f;
     const DeferUnit unit{slot, w_tiles, w_tiles * w.ksplit};
     defer_tiles<false, 0, 3, 4, A_E5M2, !WHOLE, false, MT == 3, false>(w, unit, false, [&] { defer_open<MT>(d, work); }, pen);
     // (a path of its own for one tile: with one loop for any number of them 60 to 80 registers go through memory behind the
