@@ -185,7 +185,7 @@ struct DeferEnd {
 // residual comes from HBM.  RES = 8 where the contraction has the stages (18: five of write-out, eight and four, the last one), 1
 // below, 6 on 192-row tiles alone: the CUs run in step, and 32 MB asked for within one stage take the memory 6 us a round.  Kernel with the penalty inside a
 // training step, us, in one stage / over eight (without a residual): 16384x5632 -> 2048 148 / 143 (135), 50432x3072 -> 768 126 / 124
-// (109); by itself 12304x3072 -> 2048 85 / 79 (74); over two and four stages as in one.  256x256 tiles spill 15-35
+// (109); by itself 12304x3072 -> 2048 85 / 79 (74); over two and four stages as in one.  256x256 tiles spill 17-31
 // vector registers, values of the last write-out and of the tile boundary.
 // work: the tiles of the workgroup, in order (DeferRounds, DeferClasses), or its one unit (DeferUnit).
 // A launch may go through several such lists, one after the other: opened: the first stages' loads have been issued (defer_open);
