@@ -1918,7 +1918,17 @@ static Pair pick_pair(int64_t M, int64_t N, int64_t K, size_t scratch)
     // of ragged rows its own time is less of an underestimate (1.11-1.18, of whole tiles 1.18-1.29): without the two 53 of 545 layers were
     // 2-22 % slower than before (29152x512 -> 768 50 / 60 us), with them 11, 2-10, and all 1.144 times as fast, 1.137 without.
     const bool ragged = M % 256 != 0;
-    const double others = pair.shape >= 0 ? (ragged ? 1.1 : 1.15) * us : 1.1 * (apart_us(M, K, N, dx) + apart_us(N, K, M, dw));
+    // Two whole products on that kernel are estimated as closely as the pair if they are short (measured over estimated, 85 layers: to 80 us 0.99,
+    // to 110 1.03, beyond, where the clock falls, 1.07; the pair 1.01), and the others' factor sent 12 of them where they were 2-14 % slower (us,
+    // apart / here: 2816x4096 -> 2560 54 / 61, 2560x4608 -> 3328 67 / 75): now 2, up to 4, and all 1.069 times as fast, 1.057 with 1.1 for all,
+    // 1.046 with 0.98.
+    auto own = [](int64_t m, int64_t n, int64_t k, const Split &split) {
+        const int v = split.way == kWhole ? pick(m, n, k).v : 0;
+        return v == 15 || v == 16;
+    };
+    const double apart = apart_us(M, K, N, dx) + apart_us(N, K, M, dw);
+    const double factor = own(M, K, N, dx) && own(N, K, M, dw) ? 0.98 + 0.12 * std::min(1.0, std::max(0.0, (apart - 90.0) / 50.0)) : 1.1;
+    const double others = pair.shape >= 0 ? (ragged ? 1.1 : 1.15) * us : factor * apart;
     pair.defer = defer_pair_pick(M, N, K, num_cus(), (int)std::min<size_t>(fit, kDeferPairRuns), others);
     if (pair.shape >= 0 && pair.defer.us * (1.0 + 0.015 * std::max(0, pair.defer.runs - 5)) >= others)
         pair.defer.runs = 0;

@@ -169,6 +169,19 @@ def test_backwards_that_share_a_launch_of_the_deferred_kernel():
         assert on_it(plan(*shape)), shape
 
 
+def test_short_backwards_of_two_products_on_the_deferred_kernel():
+    plan = lambda M, N, K: tw.tweo_gemm_plan(tw.TWEO_OP_FP8_LINEAR_BWD, M, N, K,
+                                             workspace_bytes=tw.tweo_workspace_bytes(tw.TWEO_OP_FP8_LINEAR_BWD, M, N, K))
+    # measured 5-14 % slower in one launch than one after the other
+    for shape in ((2816, 2560, 4096), (2304, 2048, 5888), (2560, 3328, 4608), (3328, 3584, 3840), (4096, 4608, 3072), (2048, 2560, 5376),
+                  (3072, 2048, 5376), (1792, 2304, 6144), (3840, 3072, 3072)):
+        assert not plan(*shape)[2], shape
+    # 7-21 % faster
+    for shape in ((3328, 2048, 5632), (3584, 2048, 6144), (4352, 2560, 4352), (5888, 2816, 4352), (5888, 2560, 3840), (8448, 1792, 5888),
+                  (13312, 2816, 4352), (15104, 1792, 5120), (18432, 2816, 3328)):
+        assert plan(*shape) in ((15, 1, True), (16, 1, True)), shape
+
+
 def test_build_links_with_the_extra_flags(monkeypatch):
     import subprocess
     from paper_2511_23225_amd import build
